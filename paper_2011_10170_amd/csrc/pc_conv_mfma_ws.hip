@@ -145,18 +145,51 @@ __device__ __forceinline__ void pc_ks_loader_role(const uint16_t *__restrict__ i
 // End of a tile when the MFMA wavefronts split the pixels: every wavefront stores its own 32*B_T pixels, 64 at a time
 // through a private LDS area (pixel-major bf16 rows): read back, 8 consecutive lanes hold the 128 contiguous bytes of
 // one pixel's 64 channels and the stores are whole 16-byte pieces of full lines instead of scattered 8-byte ones.
+
+// Output offsets of the 8 pieces a lane stores of one half (64 pixels) of its wavefront's pixels.
+template <int A_T, int B_T>
+__device__ __forceinline__ void pc_ks_piece_offsets(const MfmaArgs &g, int w, int lane, int half, int mt, int tn, int gy0, int gx0,
+                                                    int npix, uint32_t (&off)[8])
+{
+    constexpr uint32_t OOB_OUT = 0x80000000u;
+#pragma unroll
+    for (int it = 0; it < 8; ++it) {
+        const int px = it * 8 + (lane >> 3), c16 = lane & 7;
+        const int q = (w * B_T + half * 2) * 32 + px;
+        const int ti = (int)pc_udiv((uint32_t)q, g.mg_THTW);
+        const int rem = q - ti * g.TH * g.TW;
+        const int y = (int)pc_udiv((uint32_t)rem, g.mg_TW), x = rem - y * g.TW;
+        const int n = tn + ti, gy = gy0 + y, gx = gx0 + x;
+        const int m = mt * (32 * A_T) + c16 * 8;
+        const bool ok = q < npix && n < g.N && gy < g.GH && gx < g.GW && m < g.out_CH && c16 < 4 * A_T;
+        const int oy = gy * g.oscale + g.ooff_y, ox = gx * g.oscale + g.ooff_x;
+        off[it] = ok ? (uint32_t)((n * g.out_H + oy) * g.out_W + ox) * (uint32_t)(g.out_CH * 2) + (uint32_t)(m * 2) : OOB_OUT;
+    }
+}
+
+// The mask elements of a half. They are requested together before the half's first store: the compiler cannot move a
+// load over a store that may alias it, so a load next to its own store waits for one memory round trip per piece
+// (224 x 224, 64 channels, batch 32: 247 us with the loads next to the stores).
+__device__ __forceinline__ void pc_ks_load_mask(__amdgpu_buffer_rsrc_t msrc, const uint32_t (&off)[8], v4u32 (&mk)[8])
+{
+#pragma unroll
+    for (int it = 0; it < 8; ++it) mk[it] = __builtin_amdgcn_raw_buffer_load_b128(msrc, (int)off[it], 0, 0);
+}
+
+// off, mk: offsets and mask elements of the first half where B_T == 2 (a tile of B_T == 4 has no registers to spare for
+// them across the barrier); mask elements are used under PC_ACT_RELU_MASK only.
 template <int A_T, int B_T, int ACT>
 __device__ __forceinline__ void pc_ks_store_pixels(const f32x16 (&acc)[A_T][B_T], unsigned char *lds, const MfmaArgs &g, int w, int lane,
                                                    int mt, int tn, int gy0, int gx0, int npix, __amdgpu_buffer_rsrc_t osrc,
-                                                   __amdgpu_buffer_rsrc_t msrc)
+                                                   __amdgpu_buffer_rsrc_t msrc, uint32_t (&off)[8], v4u32 (&mk)[8])
 {
-    constexpr uint32_t OOB_OUT = 0x80000000u;
-    // Every wavefront stores its own 32*B_T pixels, 64 at a time through a private LDS area (pixel-major
-    // bf16 rows): read back, 8 consecutive lanes hold the 128 contiguous bytes of one pixel's 64 channels
-    // and the stores are whole 16-byte pieces of full lines instead of scattered 8-byte ones.
     unsigned char *stg = lds + g.red_off + w * (64 * 144);
 #pragma unroll
     for (int half = 0; half < B_T / 2; ++half) {
+        if (half > 0 || B_T == 4) {
+            pc_ks_piece_offsets<A_T, B_T>(g, w, lane, half, mt, tn, gy0, gx0, npix, off);
+            if (ACT == PC_ACT_RELU_MASK) pc_ks_load_mask(msrc, off, mk);
+        }
 #pragma unroll
         for (int jj = 0; jj < 2; ++jj)
 #pragma unroll
@@ -173,25 +206,15 @@ __device__ __forceinline__ void pc_ks_store_pixels(const f32x16 (&acc)[A_T][B_T]
         for (int it = 0; it < 8; ++it) {
             const int px = it * 8 + (lane >> 3), c16 = lane & 7;
             const uint4 v = *reinterpret_cast<const uint4 *>(stg + px * 144 + c16 * 16);
-            const int q = (w * B_T + half * 2) * 32 + px;
-            const int ti = (int)pc_udiv((uint32_t)q, g.mg_THTW);
-            const int rem = q - ti * g.TH * g.TW;
-            const int y = (int)pc_udiv((uint32_t)rem, g.mg_TW), x = rem - y * g.TW;
-            const int n = tn + ti, gy = gy0 + y, gx = gx0 + x;
-            const int m = mt * (32 * A_T) + c16 * 8;
-            const bool ok = q < npix && n < g.N && gy < g.GH && gx < g.GW && m < g.out_CH && c16 < 4 * A_T;
-            const int oy = gy * g.oscale + g.ooff_y, ox = gx * g.oscale + g.ooff_x;
-            const uint32_t off = ok ? (uint32_t)((n * g.out_H + oy) * g.out_W + ox) * (uint32_t)(g.out_CH * 2) + (uint32_t)(m * 2) : OOB_OUT;
             v4u32 pv = {v.x, v.y, v.z, v.w};
             if (ACT == PC_ACT_RELU) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) pv[e] = pc_relu_bf16x2(pv[e]);
             } else if (ACT == PC_ACT_RELU_MASK) {
-                const v4u32 mk = __builtin_amdgcn_raw_buffer_load_b128(msrc, (int)off, 0, 0);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) pv[e] = pc_mask_bf16x2(pv[e], mk[e]);
+                for (int e = 0; e < 4; ++e) pv[e] = pc_mask_bf16x2(pv[e], mk[it][e]);
             }
-            __builtin_amdgcn_raw_buffer_store_b128(pv, osrc, (int)off, 0, 0);
+            __builtin_amdgcn_raw_buffer_store_b128(pv, osrc, (int)off[it], 0, 0);
         }
     }
 }
@@ -383,14 +406,36 @@ pc_mfma_conv_ks_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__ o
                                         acc[tau / B_T][tau % B_T][q4 * 4 + 2], acc[tau / B_T][tau % B_T][q4 * 4 + 3]);
                 }
         }
+        // The offsets of the tile's stores, and the mask elements at them: requested before the barrier and before any
+        // store of the tile (see pc_ks_load_mask).
+        uint32_t poff[8], opix_off = OOB_OUT;
+        v4u32 pmk[8];
+        v2u32 rmk[ROUNDS][4];
+        if (ch == nch - 1) {
+            if (KSP == 1 && B_T == 2) {
+                pc_ks_piece_offsets<A_T, B_T>(g, w, lane, 0, mt, tn, gy0, gx0, npix, poff);
+                if (ACT == PC_ACT_RELU_MASK) pc_ks_load_mask(msrc, poff, pmk);
+            } else if (KSP == 4) {
+                const int n = tn + o_ti, gy = gy0 + o_y, gx = gx0 + o_x;
+                const bool pix_ok = qo < npix && n < g.N && gy < g.GH && gx < g.GW;
+                const int oy = gy * g.oscale + g.ooff_y, ox = gx * g.oscale + g.ooff_x;
+                opix_off = pix_ok ? (uint32_t)((n * g.out_H + oy) * g.out_W + ox) * (uint32_t)(g.out_CH * 2) : OOB_OUT;
+                if (ACT == PC_ACT_RELU_MASK && w < NOWN) {
+#pragma unroll
+                    for (int r = 0; r < ROUNDS; ++r)
+#pragma unroll
+                        for (int q4 = 0; q4 < 4; ++q4) {
+                            const int m = (mt * A_T + (r * 4 + w) / B_T) * 32 + q4 * 8 + (lane >> 5) * 4;
+                            rmk[r][q4] = __builtin_amdgcn_raw_buffer_load_b64(msrc, (int)((m < g.out_CH ? opix_off : OOB_OUT) + (uint32_t)(m * 2)), 0, 0);
+                        }
+                }
+            }
+        }
         __syncthreads();
 
-        if (KSP == 1 && ch == nch - 1) pc_ks_store_pixels<A_T, B_T, ACT>(acc, lds, g, w, lane, mt, tn, gy0, gx0, npix, osrc, msrc);
+        if (KSP == 1 && ch == nch - 1)
+            pc_ks_store_pixels<A_T, B_T, ACT>(acc, lds, g, w, lane, mt, tn, gy0, gx0, npix, osrc, msrc, poff, pmk);
         if (KSP == 4 && ch == nch - 1) {
-            const int n = tn + o_ti, gy = gy0 + o_y, gx = gx0 + o_x;
-            const bool pix_ok = qo < npix && n < g.N && gy < g.GH && gx < g.GW;
-            const int oy = gy * g.oscale + g.ooff_y, ox = gx * g.oscale + g.ooff_x;
-            const uint32_t opix_off = pix_ok ? (uint32_t)((n * g.out_H + oy) * g.out_W + ox) * (uint32_t)(g.out_CH * 2) : OOB_OUT;
 #pragma unroll
             for (int r = 0; r < ROUNDS; ++r) {
 #pragma unroll
@@ -423,9 +468,8 @@ pc_mfma_conv_ks_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__ o
                             pv[0] = pc_relu_bf16x2(pv[0]);
                             pv[1] = pc_relu_bf16x2(pv[1]);
                         } else if (ACT == PC_ACT_RELU_MASK) {
-                            const v2u32 mk = __builtin_amdgcn_raw_buffer_load_b64(msrc, ooff, 0, 0);
-                            pv[0] = pc_mask_bf16x2(pv[0], mk[0]);
-                            pv[1] = pc_mask_bf16x2(pv[1], mk[1]);
+                            pv[0] = pc_mask_bf16x2(pv[0], rmk[r][q4][0]);
+                            pv[1] = pc_mask_bf16x2(pv[1], rmk[r][q4][1]);
                         }
                         __builtin_amdgcn_raw_buffer_store_b64(pv, osrc, ooff, 0, 0);
                     }
@@ -742,9 +786,15 @@ __device__ __forceinline__ void pc_sp_mfma_role(uint16_t *__restrict__ out, cons
                 }
             }
         }
+        uint32_t poff[8];
+        v4u32 pmk[8];
+        if (ch == nch - 1) {
+            pc_ks_piece_offsets<A_T, B_T>(g, w, lane, 0, mt, tn, gy0, gx0, npix, poff);
+            if (ACT == PC_ACT_RELU_MASK) pc_ks_load_mask(msrc, poff, pmk);
+        }
         __syncthreads();
         if (ch == nch - 1) {
-            pc_ks_store_pixels<A_T, B_T, ACT>(acc, lds, g, w, lane, mt, tn, gy0, gx0, npix, osrc, msrc);
+            pc_ks_store_pixels<A_T, B_T, ACT>(acc, lds, g, w, lane, mt, tn, gy0, gx0, npix, osrc, msrc, poff, pmk);
 #pragma unroll
             for (int ii = 0; ii < A_T; ++ii)
 #pragma unroll
