@@ -263,7 +263,7 @@ extern "C" pc_status pc_pattern_select_batch(pc_ctx *ctx, int32_t n_layers, cons
 static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // Carves the slab. With base == nullptr only the size is computed.
-static size_t carve(PackView *v, PackView **v_dev, char *base, int F, int C, bool mfma, bool sparse)
+static size_t carve(PackView *v, PackView **v_dev, char *base, int F, int C, bool mfma, bool sparse, bool f32)
 {
     size_t off = 0;
     size_t cap = (size_t)F * C;
@@ -274,10 +274,12 @@ static size_t carve(PackView *v, PackView **v_dev, char *base, int F, int C, boo
     };
     v->F = F;
     v->C = C;
-    v->Fp = (F + 127) / 128 * 128;
-    v->Cp = (C + 127) / 128 * 128;
-    v->Fk = (F + 63) / 64 * 64;
-    v->Ck = (C + 63) / 64 * 64;
+    v->f32 = f32;
+    const int rows = f32 ? 32 : 128, red = f32 ? 32 : 64;
+    v->Fp = (F + rows - 1) / rows * rows;
+    v->Cp = (C + rows - 1) / rows * rows;
+    v->Fk = (F + red - 1) / red * red;
+    v->Ck = (C + red - 1) / red * red;
     *v_dev = (PackView *)take(sizeof(PackView));
     v->fm_rowptr = (int32_t *)take(sizeof(int32_t) * (F + 1));
     v->fm_grp = (int32_t *)take(sizeof(int32_t) * (size_t)F * (PC_MAX_P + 1));
@@ -295,8 +297,9 @@ static size_t carve(PackView *v, PackView **v_dev, char *base, int F, int C, boo
     v->cm_slot = (int32_t *)take(sizeof(int32_t) * cap);
     v->cm_val = (float4 *)take(sizeof(float4) * cap);
     if (mfma) {
-        v->wz_fwd = (uint16_t *)take(sizeof(uint16_t) * 9 * (size_t)v->Fp * v->Ck);
-        v->wz_bwd = (uint16_t *)take(sizeof(uint16_t) * 9 * (size_t)v->Cp * v->Fk);
+        const size_t esz = f32 ? sizeof(float) : sizeof(uint16_t);
+        v->wz_fwd = (uint16_t *)take(esz * 9 * (size_t)v->Fp * v->Ck);
+        v->wz_bwd = (uint16_t *)take(esz * 9 * (size_t)v->Cp * v->Fk);
     } else {
         v->wz_fwd = v->wz_bwd = nullptr;
     }
@@ -331,15 +334,58 @@ static size_t carve(PackView *v, PackView **v_dev, char *base, int F, int C, boo
     return off;
 }
 
+static void pc_release_event(pc_packed *pk)
+{
+    pc_pack_event *v = pk->evt;
+    pk->evt = nullptr;
+    pk->evt_recorded = false;
+    if (v && v->refs.fetch_sub(1) == 1) {
+        (void)hipEventDestroy(v->e);
+        delete v;
+    }
+}
+
+// Records the completion of a pack of n handles on the stream of ctx: one event for all of them. The event the handles
+// share already is used again when no other handle points to it.
+static pc_status pc_record_packed(pc_ctx *ctx, int n, pc_packed *const *packs)
+{
+    // An event recorded while the stream is being captured into a graph cannot be waited on afterwards, so a
+    // captured pack records none; pc_packed_info then waits for the context's stream instead.
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(ctx->stream, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        cap = hipStreamCaptureStatusNone;
+    }
+    for (int l = 0; l < n; ++l) packs[l]->evt_recorded = false;
+    if (cap != hipStreamCaptureStatusNone) return PC_OK;
+    pc_pack_event *v = packs[0]->evt;
+    for (int l = 1; l < n; ++l)
+        if (packs[l]->evt != v) v = nullptr;
+    if (v && v->refs.load() != n) v = nullptr;
+    if (!v) {
+        v = new (std::nothrow) pc_pack_event();
+        if (!v) return pc_fail(ctx, PC_ERR_NOMEM, "pc_pack: host allocation failed");
+        if (hipEventCreateWithFlags(&v->e, hipEventDisableTiming) != hipSuccess) {
+            delete v;
+            return pc_fail(ctx, PC_ERR_DEVICE, "pc_pack: event creation failed");
+        }
+        v->refs.store(n);
+        for (int l = 0; l < n; ++l) {
+            pc_release_event(packs[l]);
+            packs[l]->evt = v;
+        }
+    }
+    pc_status s = pc_hip_check(ctx, hipEventRecord(v->e, ctx->stream), "hipEventRecord");
+    for (int l = 0; l < n; ++l) packs[l]->evt_recorded = s == PC_OK;
+    return s;
+}
+
 extern "C" void pc_packed_free(pc_packed *pk)
 {
     if (!pk) return;
     (void)hipSetDevice(pk->device);
-    if (pk->packed_evt) {
-        (void)hipEventSynchronize(pk->packed_evt);
-        (void)hipEventDestroy(pk->packed_evt);
-    }
     (void)hipDeviceSynchronize();
+    pc_release_event(pk);
     if (pk->slab) (void)hipFree(pk->slab);
     delete pk;
 }
@@ -358,10 +404,10 @@ extern "C" pc_status pc_pack(pc_ctx *ctx, const float *W, const uint8_t *pid, co
     if (s != PC_OK) return pc_fail(ctx, s, "pc_pack: bad library (P=%d)", P);
 
     int variant;
-    bool can_mfma = (dt == PC_BF16) && pc_mfma_supports(F, C);
+    const bool can_mfma = pc_mfma_supports(F, C);
     const bool want_sparse = ctx->forced == PC_VARIANT_MFMA_SPARSE;
     if (ctx->forced == PC_VARIANT_MFMA || want_sparse) {
-        if (!can_mfma)
+        if (!can_mfma || dt != PC_BF16)
             return pc_fail(ctx, PC_ERR_UNSUPPORTED, "pc_pack: MFMA variant needs bf16 and supported F=%d C=%d", F, C);
         variant = PC_VARIANT_MFMA;
     } else if (ctx->forced == PC_VARIANT_VALU) {
@@ -382,24 +428,19 @@ extern "C" pc_status pc_pack(pc_ctx *ctx, const float *W, const uint8_t *pid, co
         memset(pk, 0, sizeof(*pk));
         pk->device = ctx->device;
         pk->dtype = dt;
-        bool tiles = (dt == PC_BF16) && pc_mfma_supports(F, C);
-        pk->slab_bytes = carve(&pk->v, &pk->v_dev, nullptr, F, C, tiles, want_sparse);
+        const bool tiles = can_mfma, f32 = dt == PC_F32;
+        pk->slab_bytes = carve(&pk->v, &pk->v_dev, nullptr, F, C, tiles, want_sparse, f32);
         hipError_t e = hipMalloc(&pk->slab, pk->slab_bytes);
         if (e != hipSuccess) {
             delete pk;
             return pc_hip_check(ctx, e, "pc_pack: hipMalloc");
         }
-        carve(&pk->v, &pk->v_dev, (char *)pk->slab, F, C, tiles, want_sparse);
+        carve(&pk->v, &pk->v_dev, (char *)pk->slab, F, C, tiles, want_sparse, f32);
         e = hipMemcpy(pk->v_dev, &pk->v, sizeof(PackView), hipMemcpyHostToDevice);   // pointers and extents: fixed for the handle's life
         if (e != hipSuccess) {
             (void)hipFree(pk->slab);
             delete pk;
             return pc_hip_check(ctx, e, "pc_pack: hipMemcpy");
-        }
-        if (hipEventCreateWithFlags(&pk->packed_evt, hipEventDisableTiming) != hipSuccess) {
-            (void)hipFree(pk->slab);
-            delete pk;
-            return pc_fail(ctx, PC_ERR_DEVICE, "pc_pack: event creation failed");
         }
     }
     pk->variant = variant;
@@ -410,18 +451,8 @@ extern "C" pc_status pc_pack(pc_ctx *ctx, const float *W, const uint8_t *pid, co
     pc_fill_lib(&la, lib, P);
     memcpy(pk->taps, la.taps, sizeof(pk->taps));
     s = pc_launch_pack(ctx, pk, W, pid, keep);
-    // An event recorded while the stream is being captured into a graph cannot be waited on afterwards, so a
-    // captured pack records none; pc_packed_info then waits for the context's stream instead.
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(ctx->stream, &cap) != hipSuccess) {
-        (void)hipGetLastError();
-        cap = hipStreamCaptureStatusNone;
-    }
-    pk->evt_recorded = false;
-    if (s == PC_OK && cap == hipStreamCaptureStatusNone) {
-        s = pc_hip_check(ctx, hipEventRecord(pk->packed_evt, ctx->stream), "hipEventRecord");
-        pk->evt_recorded = s == PC_OK;
-    }
+    if (s == PC_OK) s = pc_record_packed(ctx, 1, &pk);
+    else pk->evt_recorded = false;
     if (s != PC_OK) {
         if (!*out) pc_packed_free(pk);
         return s;
@@ -458,19 +489,7 @@ extern "C" pc_status pc_pack_batch(pc_ctx *ctx, int32_t n_layers, const float *c
         memcpy(pk->taps, la.taps, sizeof(pk->taps));
     }
     s = pc_launch_pack_batch(ctx, n_layers, packs, W, pid, keep, la);
-    if (s != PC_OK) return s;
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(ctx->stream, &cap) != hipSuccess) {
-        (void)hipGetLastError();
-        cap = hipStreamCaptureStatusNone;
-    }
-    if (cap == hipStreamCaptureStatusNone)
-        for (int l = 0; l < n_layers; ++l) {
-            s = pc_hip_check(ctx, hipEventRecord(packs[l]->packed_evt, ctx->stream), "hipEventRecord");
-            if (s != PC_OK) return s;
-            packs[l]->evt_recorded = true;
-        }
-    return PC_OK;
+    return s == PC_OK ? pc_record_packed(ctx, n_layers, packs) : s;
 }
 
 extern "C" pc_status pc_update_values(pc_ctx *ctx, pc_packed *pk, const float *W)
@@ -507,7 +526,7 @@ extern "C" pc_status pc_packed_info(pc_ctx *ctx, const pc_packed *pk, int64_t *n
         pc_packed *m = const_cast<pc_packed *>(pk);
         if (m->nnzk < 0) {
             PC_HIP(ctx, hipSetDevice(ctx->device));
-            if (pk->evt_recorded) PC_HIP(ctx, hipEventSynchronize(pk->packed_evt));
+            if (pk->evt_recorded) PC_HIP(ctx, hipEventSynchronize(pk->evt->e));
             else PC_HIP(ctx, hipStreamSynchronize(ctx->stream));
             int32_t n = 0;
             PC_HIP(ctx, hipMemcpy(&n, pk->v.fm_rowptr + pk->v.F, sizeof(int32_t), hipMemcpyDeviceToHost));
@@ -636,12 +655,14 @@ extern "C" pc_status pc_conv_bwd_weight_batch(pc_ctx *ctx, int32_t n_layers, con
         for (int m = 0; m < l; ++m)
             if (dw[m] == dw[l]) return pc_fail(ctx, PC_ERR_INVALID_ARG, "pc_conv_bwd_weight_batch: layers %d and %d share dw", m, l);
     }
-    // the gather kernels one layer at a time, then the matrix-core layers together
+    // float32 layers and the gather kernels one layer at a time, then the bf16 matrix-core layers together
     for (int l = 0; l < n_layers; ++l) {
-        if (packs[l]->variant == PC_VARIANT_MFMA) {
+        const bool mfma = packs[l]->variant == PC_VARIANT_MFMA;
+        if (mfma && descs[l].dtype == PC_BF16) {
             md.push_back(descs[l]); mp.push_back(packs[l]); mx.push_back(x[l]); mdy.push_back(dy[l]); mdw.push_back(dw[l]);
         } else {
-            pc_status s = pc_valu_bwd_weight(ctx, &descs[l], packs[l], x[l], dy[l], dw[l]);
+            pc_status s = mfma ? pc_mfma_bwd_weight(ctx, &descs[l], packs[l], x[l], dy[l], dw[l])
+                               : pc_valu_bwd_weight(ctx, &descs[l], packs[l], x[l], dy[l], dw[l]);
             if (s != PC_OK) return s;
         }
     }

@@ -1,0 +1,620 @@
+// Float32 layers on the matrix cores (Section 5.2, forward and backward phase): v_mfma_f32_32x32x2_f32, float32 products
+// and sums throughout.
+//
+// The gather kernels of pc_conv_valu.hip multiply kept taps only, but every multiply-add takes an LDS word and every kept
+// kernel a chain of scalar loads: they reach 2 % of the vector rate. The matrix instruction needs 256 bytes of operand per
+// 64 cycles, so the zero-filled contraction runs at the matrix rate (the same as the vector rate, 157 TFLOP/s) with one
+// LDS read per four instructions, whatever the density. 28 x 28, 128 -> 128, batch 64, keep 0.25: see the kernels below.
+//
+// Operand layout: lane l holds row (A) / column (B) l % 32 and k = l / 32; accumulator register r of lane l is row
+// 8*(r/4) + 4*(l/32) + r%4, column l % 32. A fragment is 8 reduction entries: lane half h holds entries 4h .. 4h+3 in one
+// 16-byte load, and instruction j of the fragment multiplies entries j and 4 + j.
+#include "pc_mfma.h"
+
+// ------------------------------------------------------------------ forward / backward-data
+// A workgroup computes 32*WM output channels x 32*WN pixels, one 32 x 32 tile per wavefront (WK = 4: one tile, the four
+// wavefronts split the reduction and add up in wavefront order). The pixels of a tile are consecutive in raster order
+// over (image, row, column of a strip of Ws columns), so a tile is full whatever the map size; what it reads is a
+// range of rows of the "virtual" image in which the images follow each other with one zero row between them.
+// Several workgroups share a CU: the staging of one runs under the matrix instructions of the others.
+#define F32_NE 8        // 16-byte elements staged per thread and chunk
+
+struct F32Class {
+    int32_t GH, GW, ooff_y, ooff_x;   // pixel grid of this launch part; output pixel = grid * oscale + ooff
+    int32_t Ws, tiles;                // strip width, tiles per strip
+    int32_t R, IW;                    // staged rows and columns
+    int32_t first;                    // first workgroup of this part
+    int32_t ntaps;
+    int32_t o0, dr, ds;               // the full 3 x 3: tap 3r + s at LDS byte offset o0 + r*dr + s*ds
+    int32_t tap_w[4], tap_off[4];     // a part with fewer taps: weight tap and LDS byte offset
+};
+
+struct F32ConvArgs {
+    int32_t N, in_H, in_W, in_CH, out_H, out_W, out_CH;
+    int32_t oscale, lstep, HP, ioff;  // virtual row v is input row v % HP + ioff (HP = in_H + 1)
+    int32_t KC, lparts, nchunk, KS;   // channels per chunk (8, 16 or 32), log2(KC / 4), chunks, fragments of 8 per tap in the operand
+    int32_t pitch;                    // bytes per staged pixel
+    int32_t m_tiles, ncls;
+    int32_t act;
+    const float *act_mask;
+    F32Class cls[4];
+};
+
+template <int NTAPS, int WM, int WN, int WK>
+__device__ __forceinline__ void pc_f32_conv_body(const float *__restrict__ in, float *__restrict__ out, const float *__restrict__ wz,
+                                                 const F32ConvArgs &g, const F32Class &c, int b, unsigned char *lds)
+{
+    constexpr int BN = 32 * WN;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wk = wave % WK, wn = (wave / WK) % WN, wm = wave / WK / WN;
+    const int mt = b % g.m_tiles, pt = b / g.m_tiles;
+    const int strip = pt / c.tiles, x0 = strip * c.Ws, p0 = (pt - strip * c.tiles) * BN;
+    const int np = g.N * c.GH * c.Ws;
+    const int r0 = p0 / c.Ws, n0 = r0 / c.GH, v0 = n0 * g.HP + (r0 - n0 * c.GH) * g.lstep;
+
+    // this lane's pixel
+    const int p = p0 + wn * 32 + (lane & 31);
+    const int pr = (p < np ? p : np - 1) / c.Ws, px = (p < np ? p : np - 1) - pr * c.Ws;
+    const int pn = pr / c.GH, py = pr - pn * c.GH;
+    const unsigned char *bp = lds + ((pn * g.HP + py * g.lstep - v0) * c.IW + px * g.lstep) * g.pitch + (lane >> 5) * 16;
+
+    // elements this thread stages: 16 bytes (4 channels, the same ones of every pixel) of a pixel each; pix = the input
+    // pixel counted from the first image of the tile
+    const int total = (c.R * c.IW) << g.lparts;
+    const int part = (int)threadIdx.x & ((1 << g.lparts) - 1), q0 = (int)threadIdx.x >> g.lparts, dq = 256 >> g.lparts;
+    const float *in0 = in + (int64_t)n0 * g.in_H * g.in_W * g.in_CH + part * 4;
+    uint32_t pix[F32_NE];
+#pragma unroll
+    for (int i = 0; i < F32_NE; ++i) {
+        const int q = q0 + i * dq;
+        const int iy = q / c.IW, ix = q - iy * c.IW;
+        const int v = v0 + iy, n = v / g.HP, y = v - n * g.HP + g.ioff, x = x0 * g.lstep + ix + g.ioff;
+        const bool ok = iy < c.R && n < g.N && y >= 0 && y < g.in_H && x >= 0 && x < g.in_W;
+        pix[i] = ok ? (uint32_t)(((n - n0) * g.in_H + y) * g.in_W + x) : 0xFFFFFFFFu;
+    }
+    float4 R[F32_NE];
+    auto issue = [&](int ch) {
+        const int c0 = ch * g.KC;
+        if ((g.in_CH & 3) == 0) {
+#pragma unroll
+            for (int i = 0; i < F32_NE; ++i)
+                if (i * 256 < total) {
+                    const bool ok = pix[i] != 0xFFFFFFFFu && c0 + part * 4 < g.in_CH;
+                    const float4 t = *reinterpret_cast<const float4 *>(ok ? in0 + ((uint64_t)pix[i] * (uint32_t)g.in_CH + c0) : in);
+                    R[i] = make_float4(ok ? t.x : 0.f, ok ? t.y : 0.f, ok ? t.z : 0.f, ok ? t.w : 0.f);
+                }
+        } else {                      // rows are not 16-byte aligned: by element
+#pragma unroll
+            for (int i = 0; i < F32_NE; ++i)
+                if (i * 256 < total) {
+                    float t[4];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const bool ok = pix[i] != 0xFFFFFFFFu && c0 + part * 4 + k < g.in_CH;
+                        const float u = *(ok ? in0 + ((uint64_t)pix[i] * (uint32_t)g.in_CH + c0 + k) : in);
+                        t[k] = ok ? u : 0.f;
+                    }
+                    R[i] = make_float4(t[0], t[1], t[2], t[3]);
+                }
+        }
+    };
+    auto put = [&]() {
+        unsigned char *dst = lds + q0 * g.pitch + part * 16;
+#pragma unroll
+        for (int i = 0; i < F32_NE; ++i)
+            if ((int)threadIdx.x + 256 * i < total) *reinterpret_cast<float4 *>(dst + i * dq * g.pitch) = R[i];
+    };
+
+    // weight fragments: [row tile][tap][fragment][64 lanes][4], a row tile past the last reads the last (not stored)
+    int rt = mt * WM + wm;
+    const int rt_last = (g.out_CH - 1) >> 5;
+    if (rt > rt_last) rt = rt_last;
+    const float *wl = wz + (int64_t)rt * 9 * g.KS * 256 + lane * 4;
+    auto a_load = [&](int tap, int kf) -> float4 {
+        const int tw = NTAPS == 9 ? tap : c.tap_w[tap & 3];
+        return *reinterpret_cast<const float4 *>(wl + (int64_t)(tw * g.KS + (kf < g.KS ? kf : g.KS - 1)) * 256);
+    };
+    auto tap_off = [&](int tap) -> int { return NTAPS == 9 ? c.o0 + tap / 3 * c.dr + tap % 3 * c.ds : c.tap_off[tap & 3]; };
+    constexpr int RD = NTAPS == 9 ? 3 : NTAPS;    // weight fragments in flight
+
+    f32x16 acc;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
+    issue(0);
+    float4 ar[RD];
+#pragma unroll
+    for (int t = 0; t < RD; ++t) ar[t] = a_load(t, wk);
+    const int KF = g.KC >> 3;
+    for (int ch = 0; ch < g.nchunk; ++ch) {
+        if (ch) __syncthreads();
+        put();
+        __syncthreads();
+        if (ch + 1 < g.nchunk) issue(ch + 1);
+        const int left = (g.in_CH - ch * g.KC + 7) >> 3, nf = left < KF ? left : KF;
+        for (int f = wk; f < nf; f += WK) {
+            const int kf = ch * KF + f, kn = f + WK < nf ? kf + WK : (ch + 1) * KF + wk;   // this fragment and the one after it
+#pragma unroll
+            for (int t = 0; t < NTAPS; ++t) {
+                const float4 bq = *reinterpret_cast<const float4 *>(bp + tap_off(t) + f * 32);
+                const float4 a = ar[t % RD];
+                ar[t % RD] = t + RD < NTAPS ? a_load(t + RD < NTAPS ? t + RD : 0, kf) : a_load((t + RD) % NTAPS, kn);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, bq.x, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, bq.y, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, bq.z, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, bq.w, acc, 0, 0, 0);
+            }
+        }
+    }
+    float4 o[4];
+    if (WK > 1) {
+        // partial tiles added in wavefront order, wavefront w finishes rows 8w .. 8w+7
+        float4 *red = reinterpret_cast<float4 *>(lds);
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 4; ++q) red[(wave * 4 + q) * 64 + lane] = make_float4(acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]);
+        __syncthreads();
+        float4 s = red[wk * 64 + lane];
+#pragma unroll
+        for (int k = 1; k < WK; ++k) {
+            const float4 u = red[(k * 4 + wk) * 64 + lane];
+            s.x += u.x; s.y += u.y; s.z += u.z; s.w += u.w;
+        }
+        o[0] = s;
+    } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) o[q] = make_float4(acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]);
+    }
+    if (p >= np || x0 + px >= c.GW) return;
+    const int64_t opix = ((int64_t)pn * g.out_H + py * g.oscale + c.ooff_y) * g.out_W + (x0 + px) * g.oscale + c.ooff_x;
+#pragma unroll
+    for (int q = 0; q < (WK > 1 ? 1 : 4); ++q) {
+        const int m = (mt * WM + wm) * 32 + (WK > 1 ? wk : q) * 8 + (lane >> 5) * 4;
+        if (m >= g.out_CH) continue;
+        const int64_t at = opix * g.out_CH + m;
+        float v[4] = {o[q].x, o[q].y, o[q].z, o[q].w};
+        const int ne = (g.out_CH & 3) == 0 ? 4 : (g.out_CH - m < 4 ? g.out_CH - m : 4);
+        if (g.act == PC_ACT_RELU) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = v[e] > 0.0f ? v[e] : 0.0f;
+        } else if (g.act == PC_ACT_RELU_MASK) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = (e < ne && g.act_mask[at + e] > 0.0f) ? v[e] : 0.0f;
+        }
+        if ((g.out_CH & 3) == 0) *reinterpret_cast<float4 *>(out + at) = make_float4(v[0], v[1], v[2], v[3]);
+        else
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (e < ne) out[at + e] = v[e];
+    }
+}
+
+// MC: the four parity classes of a stride-2 backward-data pass (4, 2, 2 and 1 taps), each a range of workgroups.
+template <int WM, int WN, int WK, bool MC>
+__global__ void __launch_bounds__(256, 4)
+pc_f32_conv_kernel(const float *__restrict__ in, float *__restrict__ out, const float *__restrict__ wz, F32ConvArgs g)
+{
+    extern __shared__ __align__(16) unsigned char lds[];
+    int b = (int)blockIdx.x;
+    if (!MC && (gridDim.x & 7) == 0) b = (b & 7) * ((int)gridDim.x >> 3) + (b >> 3);   // workgroups that share pixels share an XCD
+    if constexpr (MC) {           // (the parts differ in taps: in launch order they spread over the XCDs)
+        int k = 0;
+        while (k + 1 < g.ncls && b >= g.cls[k + 1].first) ++k;
+        const F32Class &c = g.cls[k];
+        if (c.ntaps == 4) pc_f32_conv_body<4, WM, WN, WK>(in, out, wz, g, c, b - c.first, lds);
+        else if (c.ntaps == 2) pc_f32_conv_body<2, WM, WN, WK>(in, out, wz, g, c, b - c.first, lds);
+        else pc_f32_conv_body<1, WM, WN, WK>(in, out, wz, g, c, b - c.first, lds);
+    } else {
+        pc_f32_conv_body<9, WM, WN, WK>(in, out, wz, g, g.cls[0], b, lds);
+    }
+}
+
+// ---- plan and launch
+// Strips and staged extent of one part for BN pixels per tile; false when it does not fit the staging registers.
+static bool f32_plan_class(const F32ConvArgs &g, F32Class *c, int ext, int BN)
+{
+    int64_t best = -1;
+    for (int ns = 1; ns <= c->GW; ++ns) {
+        const int Ws = (c->GW + ns - 1) / ns;
+        if ((c->GW + Ws - 1) / Ws != ns) continue;
+        const int64_t np = (int64_t)g.N * c->GH * Ws;
+        if (np + BN >= ((int64_t)1 << 31)) continue;
+        const int rows = BN % Ws == 0 ? BN / Ws : (BN + Ws - 2) / Ws + 1;         // output rows a tile touches at most
+        const int cross = (rows - 1 + c->GH - 1) / c->GH;                         // image boundaries among them
+        const int gap = g.HP - c->GH * g.lstep;                                   // virtual rows between two images beyond the step
+        const int64_t vr = (int64_t)g.N * g.HP + 8;
+        if (vr >= ((int64_t)1 << 31)) return false;
+        const int R = (rows - 1) * g.lstep + cross * (gap > 0 ? gap : 0) + ext, IW = (Ws - 1) * g.lstep + ext;
+        if ((int64_t)R * IW * (g.KC / 4) > 256 * F32_NE) continue;
+        // columns past the map cost matrix work, staged pixels cost less
+        const int64_t cost = (int64_t)ns * Ws * (8 * BN + R * IW);
+        if (best < 0 || cost < best) {
+            best = cost;
+            c->Ws = Ws; c->R = R; c->IW = IW;
+            c->tiles = (int)((np + BN - 1) / BN);
+        }
+    }
+    return best >= 0;
+}
+
+struct F32Shape { int wm, wn, wk; };
+static const F32Shape kF32Shapes[] = {{2, 2, 1}, {1, 4, 1}, {4, 1, 1}, {1, 1, 4}};
+
+// g holds the tensors' extents; cls[].{GH, GW, ooff, ntaps, tap_w} and the tap positions tr, tc are set.
+static pc_status f32_run(pc_ctx *ctx, F32ConvArgs g, bool mc, int ext, const int (*tr)[9], const int (*tc)[9], const float *in, float *out,
+                         const float *wz)
+{
+    F32ConvArgs best;
+    int best_k = -1;
+    int64_t best_blocks = 0;
+    double best_cost = 0.0;
+    const int c8 = (g.in_CH + 7) / 8 * 8;
+    for (int k = 0; k < 4; ++k) {
+        const F32Shape &s = kF32Shapes[k];
+        // chunks of 32 channels, shorter ones where the staged tile would not fit (four wavefronts that split the
+        // reduction take one fragment of 8 each)
+        for (int kc = 32; kc >= (s.wk > 1 ? 32 : 8); kc >>= 1) {
+            if (kc >= 2 * c8 && s.wk == 1) continue;
+            F32ConvArgs t = g;
+            t.KC = kc;
+            t.lparts = kc == 32 ? 3 : kc == 16 ? 2 : 1;
+            t.pitch = t.KC * 4 + 16;
+            t.nchunk = (g.in_CH + t.KC - 1) / t.KC;
+            t.m_tiles = (g.out_CH + 32 * s.wm - 1) / (32 * s.wm);
+            int64_t blocks = 0;
+            bool ok = true;
+            double work = 0.0;
+            for (int i = 0; i < g.ncls && ok; ++i) {
+                F32Class &c = t.cls[i];
+                ok = f32_plan_class(t, &c, ext, 32 * s.wn);
+                if (!ok) break;
+                const int ns = (c.GW + c.Ws - 1) / c.Ws;
+                c.first = (int32_t)blocks;
+                blocks += (int64_t)c.tiles * ns * t.m_tiles;
+                if (blocks >= ((int64_t)1 << 31)) ok = false;
+                work += (double)c.tiles * ns * t.m_tiles * c.ntaps;
+                if (mc) {
+                    for (int q = 0; q < c.ntaps; ++q) c.tap_off[q] = (tr[i][q] * c.IW + tc[i][q]) * t.pitch;
+                } else {                  // tap rows and columns ascend (forward) or descend (rotated)
+                    c.o0 = (tr[i][0] * c.IW + tc[i][0]) * t.pitch;
+                    c.dr = (tr[i][3] - tr[i][0]) * c.IW * t.pitch;
+                    c.ds = (tc[i][1] - tc[i][0]) * t.pitch;
+                }
+            }
+            if (!ok) continue;
+            // cycles of a SIMD: 256 per fragment and tap of every workgroup it serves, plus start and end of a workgroup
+            // (hidden where several share the CU)
+            const double rounds = (double)((blocks + ctx->num_cu - 1) / ctx->num_cu);
+            const double per = work / (double)blocks * (c8 / 8) * 256.0 / s.wk + (s.wk > 1 ? 800.0 : 0.0);
+            const double cost = rounds * per + 5000.0 + (rounds > 1 ? (rounds - 1) * 600.0 : 0.0) + 100.0 * t.nchunk * rounds;
+            if (best_k < 0 || cost < best_cost) { best = t; best_k = k; best_blocks = blocks; best_cost = cost; }
+            break;
+        }
+    }
+    if (best_k < 0) return pc_fail(ctx, PC_ERR_UNSUPPORTED, "float32 conv: no tile fits");
+    size_t lds = 0;
+    for (int i = 0; i < best.ncls; ++i) {
+        const size_t n = (size_t)best.cls[i].R * best.cls[i].IW * best.pitch;
+        if (n > lds) lds = n;
+    }
+    if (kF32Shapes[best_k].wk > 1 && lds < 16384) lds = 16384;
+    const dim3 grid((unsigned)best_blocks), blk(256);
+    hipStream_t st = ctx->stream;
+#define F32_LAUNCH(WM, WN, WK)                                                                                              \
+    do {                                                                                                                    \
+        if (mc) hipLaunchKernelGGL((pc_f32_conv_kernel<WM, WN, WK, true>), grid, blk, lds, st, in, out, wz, best);          \
+        else hipLaunchKernelGGL((pc_f32_conv_kernel<WM, WN, WK, false>), grid, blk, lds, st, in, out, wz, best);            \
+    } while (0)
+    switch (best_k) {
+    case 0: F32_LAUNCH(2, 2, 1); break;
+    case 1: F32_LAUNCH(1, 4, 1); break;
+    case 2: F32_LAUNCH(4, 1, 1); break;
+    default: F32_LAUNCH(1, 1, 4); break;
+    }
+#undef F32_LAUNCH
+    pc_note_kernel(ctx, "pc_f32_conv_kernel<%d, %d, %d, %s>", kF32Shapes[best_k].wm, kF32Shapes[best_k].wn, kF32Shapes[best_k].wk, mc ? "true" : "false");
+    return pc_hip_check(ctx, hipGetLastError(), "float32 conv launch");
+}
+
+pc_status pc_f32_fwd(pc_ctx *ctx, const pc_conv_desc *d, const pc_packed *pk, const void *x, void *y, int act)
+{
+    F32ConvArgs g;
+    memset(&g, 0, sizeof(g));
+    g.N = d->N; g.in_H = d->H; g.in_W = d->W; g.in_CH = d->C;
+    g.out_H = (d->H - 1) / d->stride + 1; g.out_W = (d->W - 1) / d->stride + 1; g.out_CH = d->F;
+    g.oscale = 1; g.lstep = d->stride; g.HP = d->H + 1; g.ioff = -1;
+    g.KS = pk->v.Ck / 8;
+    g.act = act; g.ncls = 1;
+    F32Class &c = g.cls[0];
+    c.GH = g.out_H; c.GW = g.out_W; c.ntaps = 9;
+    int tr[1][9], tc[1][9];
+    for (int t = 0; t < 9; ++t) { tr[0][t] = t / 3; tc[0][t] = t % 3; }
+    return f32_run(ctx, g, false, 3, tr, tc, (const float *)x, (float *)y, (const float *)pk->v.wz_fwd);
+}
+
+pc_status pc_f32_bwd_data(pc_ctx *ctx, const pc_conv_desc *d, const pc_packed *pk, const void *dy, void *dx, int act, const void *act_mask)
+{
+    F32ConvArgs g;
+    memset(&g, 0, sizeof(g));
+    g.N = d->N; g.in_H = (d->H - 1) / d->stride + 1; g.in_W = (d->W - 1) / d->stride + 1; g.in_CH = d->F;
+    g.out_H = d->H; g.out_W = d->W; g.out_CH = d->C;
+    g.oscale = d->stride; g.lstep = 1; g.HP = g.in_H + 1;
+    g.KS = pk->v.Fk / 8;
+    g.act = act; g.act_mask = (const float *)act_mask;
+    int tr[4][9], tc[4][9];
+    if (d->stride == 1) {
+        // dx[iy,ix] reads dy[iy+1-r, ix+1-s]: tap (r,s) at staged offset (2-r, 2-s) from (iy-1, ix-1)
+        g.ioff = -1; g.ncls = 1;
+        F32Class &c = g.cls[0];
+        c.GH = d->H; c.GW = d->W; c.ntaps = 9;
+        for (int t = 0; t < 9; ++t) { tr[0][t] = 2 - t / 3; tc[0][t] = 2 - t % 3; }
+        return f32_run(ctx, g, false, 3, tr, tc, (const float *)dy, (float *)dx, (const float *)pk->v.wz_bwd);
+    }
+    // stride 2: input pixel (2a+py, 2b+px) receives tap (r,s) iff py+1-r and px+1-s are even, from dy[a+(py+1-r)/2, b+(px+1-s)/2]
+    static const int order[4][2] = {{1, 1}, {1, 0}, {0, 1}, {0, 0}};
+    for (int k = 0; k < 4; ++k) {
+        const int py = order[k][0], px = order[k][1];
+        F32Class &c = g.cls[g.ncls];
+        c.GH = (d->H - py + 1) / 2; c.GW = (d->W - px + 1) / 2;
+        if (c.GH < 1 || c.GW < 1) continue;
+        c.ooff_y = py; c.ooff_x = px;
+        for (int t = 0; t < 9; ++t) {
+            const int r = t / 3, s = t % 3;
+            if ((py + 1 - r) % 2 || (px + 1 - s) % 2) continue;
+            c.tap_w[c.ntaps] = t;
+            tr[g.ncls][c.ntaps] = (py + 1 - r) / 2; tc[g.ncls][c.ntaps] = (px + 1 - s) / 2;
+            ++c.ntaps;
+        }
+        ++g.ncls;
+    }
+    return f32_run(ctx, g, true, 2, tr, tc, (const float *)dy, (float *)dx, (const float *)pk->v.wz_bwd);
+}
+
+// ------------------------------------------------------------------ backward-weight
+// dW[t][f][c] = sum over output pixels of dy[pixel][f] * x[pixel shifted by tap t][c]. The pixels are the reduction and a
+// lane holds one float of one pixel, so NHWC rows in LDS are the operands as they are: no transpose. A wavefront holds a
+// 32 x 32 (filter, channel) tile of all 9 taps (144 accumulators) and reads 10 words per 9 matrix instructions.
+// WF x WC wavefronts cover 32*WF filters x 32*WC channels; where a layer needs fewer than four, the 4 / (WF*WC)
+// remaining ones take every WK-th pixel pair and write partial planes of their own. Pixel tiles are split over the
+// workgroups (two per CU); every split writes the kept taps in compact slot order, pc_wgrad_reduce adds the planes in
+// a fixed order.
+// THIN (at most 3 channels): the 9 * C (tap, channel) pairs are the columns of one tile, one instruction instead of 9.
+#define F32W_ND 2       // 16-byte elements of dy, and
+#define F32W_NX 6       // of x, staged per thread and pixel tile
+
+struct F32WgradArgs {
+    int32_t N, H, W, C, F, Ho, Wo, stride;
+    int32_t TR, TC, TCe, IR, IW;          // pixel tile, its columns rounded up to even, staged extent of x
+    int32_t tiles_r, tiles_c, n_tiles, ksplit, ct, ft;
+    int32_t nd, nx;                       // elements per tile
+    uint32_t mg_half;                     // division by TCe / 2
+    int64_t pstride;                      // slots per partial plane
+};
+
+template <int WF, int WC, bool THIN>
+__global__ void __launch_bounds__(256, 2)
+pc_f32_wgrad_kernel(const float *__restrict__ x, const float *__restrict__ dy, F32WgradArgs a, const uint32_t *__restrict__ kinfo,
+                    float4 *__restrict__ partial)
+{
+    extern __shared__ __align__(16) float smem[];
+    constexpr int WK = 4 / (WF * WC), FD = 32 * WF, CD = THIN ? 4 : 32 * WC;
+    constexpr int PD = FD + 4, PX = THIN ? 4 : CD + 4;       // floats per staged pixel
+    constexpr int NT = THIN ? 1 : 9;
+    const int lane = threadIdx.x & 63, h = lane >> 5, n32 = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wk = wave % WK, wc = (wave / WK) % WC, wf = wave / WK / WC;
+    const int b = (int)blockIdx.x, split = b % a.ksplit, tile = b / a.ksplit;
+    const int c0 = (tile % a.ct) * CD, f0 = (tile / a.ct) * FD;
+    float *sd = smem, *sx = smem + a.TR * a.TCe * PD;
+
+    // staged elements: position inside the tile (or its x region) and offset inside an image
+    int dpos[F32W_ND], xpos[F32W_NX], doff[F32W_ND], xoff[F32W_NX];
+#pragma unroll
+    for (int i = 0; i < F32W_ND; ++i) {
+        const int e = (int)threadIdx.x + 256 * i, q = e / (FD / 4), f = f0 + (e - q * (FD / 4)) * 4;
+        const int r = q / a.TCe, col = q - r * a.TCe;
+        dpos[i] = e < a.nd && col < a.TC && f < a.F ? (r << 16) | col : -1;
+        doff[i] = (r * a.Wo + col) * a.F + f;
+    }
+#pragma unroll
+    for (int i = 0; i < F32W_NX; ++i) {
+        const int e = (int)threadIdx.x + 256 * i, q = e / (CD / 4), cc = c0 + (e - q * (CD / 4)) * 4;
+        const int r = q / a.IW, col = q - r * a.IW;
+        xpos[i] = e < a.nx && cc < a.C ? (r << 16) | col : -1;
+        xoff[i] = (r * a.W + col) * a.C + cc;
+    }
+    const bool d4 = (a.F & 3) == 0, x4 = (a.C & 3) == 0;
+    float4 RD[F32W_ND], RX[F32W_NX];
+    auto load4 = [&](const float *src, int64_t at, bool ok, bool vec, int left) -> float4 {
+        if (vec) {
+            const float4 t = *reinterpret_cast<const float4 *>(src + (ok ? at : 0));
+            return make_float4(ok ? t.x : 0.f, ok ? t.y : 0.f, ok ? t.z : 0.f, ok ? t.w : 0.f);
+        }
+        float t[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const bool o = ok && k < left;
+            const float u = src[o ? at + k : 0];
+            t[k] = o ? u : 0.f;
+        }
+        return make_float4(t[0], t[1], t[2], t[3]);
+    };
+    auto issue = [&](int kt) {
+        int q = kt;
+        const int tc = q % a.tiles_c; q /= a.tiles_c;
+        const int tr = q % a.tiles_r, n = q / a.tiles_r;
+        const int oy = tr * a.TR, ox = tc * a.TC, iy = oy * a.stride - 1, ix = ox * a.stride - 1;
+        const int64_t db = ((int64_t)n * a.Ho * a.Wo + (int64_t)oy * a.Wo + ox) * a.F;
+        const int64_t xb = ((int64_t)n * a.H * a.W + (int64_t)iy * a.W + ix) * a.C;
+#pragma unroll
+        for (int i = 0; i < F32W_ND; ++i)
+            if (i * 256 < a.nd) {
+                const bool ok = dpos[i] >= 0 && oy + (dpos[i] >> 16) < a.Ho && ox + (dpos[i] & 0xFFFF) < a.Wo;
+                RD[i] = load4(dy, db + doff[i], ok, d4, a.F - (f0 + ((int)threadIdx.x + 256 * i) % (FD / 4) * 4));
+            }
+#pragma unroll
+        for (int i = 0; i < F32W_NX; ++i)
+            if (i * 256 < a.nx) {
+                const int yy = iy + (xpos[i] >> 16), xx = ix + (xpos[i] & 0xFFFF);
+                const bool ok = xpos[i] >= 0 && yy >= 0 && yy < a.H && xx >= 0 && xx < a.W;
+                RX[i] = load4(x, xb + xoff[i], ok, x4, a.C - (c0 + ((int)threadIdx.x + 256 * i) % (CD / 4) * 4));
+            }
+    };
+    auto put = [&]() {
+#pragma unroll
+        for (int i = 0; i < F32W_ND; ++i) {
+            const int e = (int)threadIdx.x + 256 * i, q = e / (FD / 4);
+            if (e < a.nd) *reinterpret_cast<float4 *>(sd + q * PD + (e - q * (FD / 4)) * 4) = RD[i];
+        }
+#pragma unroll
+        for (int i = 0; i < F32W_NX; ++i) {
+            const int e = (int)threadIdx.x + 256 * i, q = e / (CD / 4);
+            if (e < a.nx) *reinterpret_cast<float4 *>(sx + q * PX + (e - q * (CD / 4)) * 4) = RX[i];
+        }
+    };
+
+    f32x16 acc[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[t][r] = 0.0f;
+    const int half = a.TCe >> 1, steps = a.TR * half;
+    const int a_base = h * PD + wf * 32 + n32;
+    int b_base;
+    if (THIN) {
+        const int tap = n32 < 9 * a.C ? n32 / a.C : 0, cn = n32 < 9 * a.C ? n32 - tap * a.C : 0;
+        b_base = (h * a.stride + tap / 3 * a.IW + tap % 3) * PX + cn;
+    } else {
+        b_base = h * a.stride * PX + wc * 32 + n32;
+    }
+    const int row = a.IW * PX;
+    float fa[2], fb[2][NT];
+    auto read = [&](int s, int k) {
+        const int y = (int)pc_udiv((uint32_t)s, a.mg_half), xs = (s - y * half) * 2;
+        fa[k] = sd[a_base + (y * a.TCe + xs) * PD];
+        const float *q = sx + b_base + (y * a.IW + xs) * a.stride * PX;
+        if (THIN) fb[k][0] = q[0];
+        else
+#pragma unroll
+            for (int t = 0; t < NT; ++t) fb[k][t] = q[t / 3 * row + t % 3 * PX];
+    };
+    int kt = split;
+    if (kt < a.n_tiles) issue(kt);
+    for (bool first = true; kt < a.n_tiles; kt += a.ksplit, first = false) {
+        if (!first) __syncthreads();
+        put();
+        __syncthreads();
+        if (kt + a.ksplit < a.n_tiles) issue(kt + a.ksplit);
+        // operands of a pixel pair are read one pair ahead
+        if (wk < steps) read(wk, 0);
+        for (int s = wk; s < steps; s += 2 * WK) {
+            if (s + WK < steps) read(s + WK, 1);
+#pragma unroll
+            for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[0], fb[0][t], acc[t], 0, 0, 0);
+            if (s + WK < steps) {
+                if (s + 2 * WK < steps) read(s + 2 * WK, 0);
+#pragma unroll
+                for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[1], fb[1][t], acc[t], 0, 0, 0);
+            }
+        }
+    }
+    // kept taps in compact order, straight from the accumulators: a lane holds one channel and 16 filters
+    float4 *pout = partial + (int64_t)(split * WK + wk) * a.pstride;
+    if (THIN) {
+        if (n32 < 9 * a.C) {
+            const int tap = n32 / a.C, c = n32 - tap * a.C;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int f = f0 + wf * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
+                const uint32_t info = f < a.F ? kinfo[(int64_t)f * a.C + c] : 0xFFFFFFFFu;
+                if (info != 0xFFFFFFFFu && ((info >> tap) & 1u))
+                    reinterpret_cast<float *>(pout + (info >> 9))[__popc(info & ((1u << tap) - 1u))] = acc[0][r];
+            }
+        }
+        return;
+    }
+    const int c = c0 + wc * 32 + n32;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int f = f0 + wf * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
+        const uint32_t info = f < a.F && c < a.C ? kinfo[(int64_t)f * a.C + c] : 0xFFFFFFFFu;
+        if (info == 0xFFFFFFFFu) continue;
+        float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int t = NT - 1; t >= 0; --t) {           // the four set bits of the mask, ascending
+            const bool on = (info >> t) & 1u;
+            o.w = on ? o.z : o.w; o.z = on ? o.y : o.z; o.y = on ? o.x : o.y;
+            o.x = on ? acc[t][r] : o.x;
+        }
+        pout[info >> 9] = o;
+    }
+}
+
+pc_status pc_f32_bwd_weight(pc_ctx *ctx, const pc_conv_desc *d, const pc_packed *pk, const void *x, const void *dy, float *dw)
+{
+    const int64_t nslots = pk->nnzk >= 0 ? pk->nnzk : (int64_t)pk->v.F * pk->v.C;
+    if (nslots == 0) return PC_OK;
+    F32WgradArgs a;
+    memset(&a, 0, sizeof(a));
+    a.N = d->N; a.H = d->H; a.W = d->W; a.C = d->C; a.F = d->F; a.stride = d->stride;
+    a.Ho = (d->H - 1) / d->stride + 1; a.Wo = (d->W - 1) / d->stride + 1;
+    const bool thin = d->C <= 3;
+    const int wf = d->F > 32 ? 2 : 1, wc = !thin && d->C > 32 ? 2 : 1, wk = 4 / (wf * wc);
+    const int FD = 32 * wf, CD = thin ? 4 : 32 * wc;
+    a.ft = (d->F + FD - 1) / FD;
+    a.ct = thin ? 1 : (d->C + CD - 1) / CD;
+    // pixel tile: the staging registers bound it; fewest matrix steps over the map, then fewest staged pixels
+    double best = -1.0;
+    const int max_pos = 256 * F32W_ND / (FD / 4);
+    for (int tr = 1; tr <= max_pos && tr <= a.Ho; ++tr)
+        for (int tc = 1; tr * tc <= max_pos && tc <= a.Wo; ++tc) {
+            const int tce = (tc + 1) / 2 * 2;
+            if (tr * tce > max_pos) break;
+            const int ir = (tr - 1) * d->stride + 3, iw = (tce - 1) * d->stride + 3;
+            if (ir * iw * (CD / 4) > 256 * F32W_NX) continue;
+            const int nr = (a.Ho + tr - 1) / tr, nc = (a.Wo + tc - 1) / tc;
+            const double steps = (double)((tr * tce / 2 + wk - 1) / wk);
+            const double cost = (double)nr * nc * (steps * 576.0 + 400.0 + 6.0 * (ir * iw * (CD / 4) + tr * tce * (FD / 4)) / 4);
+            if (best < 0.0 || cost < best) {
+                best = cost;
+                a.TR = tr; a.TC = tc; a.TCe = tce; a.IR = ir; a.IW = iw; a.tiles_r = nr; a.tiles_c = nc;
+            }
+        }
+    if (best < 0.0) return pc_fail(ctx, PC_ERR_UNSUPPORTED, "float32 bwd_weight: no pixel tile fits");
+    const int64_t nkt = (int64_t)a.N * a.tiles_r * a.tiles_c;
+    if (nkt >= ((int64_t)1 << 31)) return pc_fail(ctx, PC_ERR_UNSUPPORTED, "float32 bwd_weight: too many pixel tiles");
+    a.n_tiles = (int)nkt;
+    a.nd = a.TR * a.TCe * (FD / 4);
+    a.nx = a.IR * a.IW * (CD / 4);
+    a.mg_half = pc_udiv_magic(a.TCe / 2);
+    a.pstride = nslots;
+    // two workgroups per CU; the partial planes stay within 16 MiB
+    int64_t ks = (2 * (int64_t)ctx->num_cu + a.ft * a.ct - 1) / ((int64_t)a.ft * a.ct);
+    const int64_t cap = ((int64_t)1 << 20) / (nslots * wk);
+    if (ks > cap) ks = cap;
+    if (ks > a.n_tiles) ks = a.n_tiles;
+    if (ks < 1) ks = 1;
+    a.ksplit = (int)ks;
+    const int planes = a.ksplit * wk;
+    void *scr = nullptr;
+    if (planes > 1) {
+        pc_status s = pc_scratch(ctx, sizeof(float4) * (size_t)planes * (size_t)nslots, &scr);
+        if (s != PC_OK) return s;
+    }
+    const int PD = FD + 4, PX = thin ? 4 : CD + 4;
+    const size_t lds = sizeof(float) * ((size_t)a.TR * a.TCe * PD + (size_t)a.IR * a.IW * PX);
+    const dim3 grid((unsigned)(a.ft * a.ct * a.ksplit)), blk(256);
+    float4 *po = planes > 1 ? (float4 *)scr : (float4 *)dw;
+    const float *xp = (const float *)x, *dp = (const float *)dy;
+    hipStream_t st = ctx->stream;
+    if (thin && wf == 2) hipLaunchKernelGGL((pc_f32_wgrad_kernel<2, 1, true>), grid, blk, lds, st, xp, dp, a, pk->v.kinfo, po);
+    else if (thin) hipLaunchKernelGGL((pc_f32_wgrad_kernel<1, 1, true>), grid, blk, lds, st, xp, dp, a, pk->v.kinfo, po);
+    else if (wf == 2 && wc == 2) hipLaunchKernelGGL((pc_f32_wgrad_kernel<2, 2, false>), grid, blk, lds, st, xp, dp, a, pk->v.kinfo, po);
+    else if (wf == 2) hipLaunchKernelGGL((pc_f32_wgrad_kernel<2, 1, false>), grid, blk, lds, st, xp, dp, a, pk->v.kinfo, po);
+    else if (wc == 2) hipLaunchKernelGGL((pc_f32_wgrad_kernel<1, 2, false>), grid, blk, lds, st, xp, dp, a, pk->v.kinfo, po);
+    else hipLaunchKernelGGL((pc_f32_wgrad_kernel<1, 1, false>), grid, blk, lds, st, xp, dp, a, pk->v.kinfo, po);
+    pc_note_kernel(ctx, "pc_f32_wgrad_kernel<%d, %d, %s>", wf, wc, thin ? "true" : "false");
+    pc_status s = pc_hip_check(ctx, hipGetLastError(), "float32 bwd_weight launch");
+    if (s != PC_OK || planes == 1) return s;
+    return pc_launch_wgrad_reduce(ctx, (const float *)scr, planes, nslots, nslots, pk, dw);
+}

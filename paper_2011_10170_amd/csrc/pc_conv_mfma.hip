@@ -534,6 +534,10 @@ static pc_status try_thin(pc_ctx *ctx, const pc_conv_desc *d, const pc_packed *p
 
 pc_status pc_mfma_fwd(pc_ctx *ctx, const pc_conv_desc *d, const pc_packed *pk, const void *x, void *y, int act, bool *fused)
 {
+    if (d->dtype == PC_F32) {
+        if (fused) *fused = act != PC_ACT_NONE;
+        return pc_f32_fwd(ctx, d, pk, x, y, fused ? act : PC_ACT_NONE);
+    }
     {
         bool taken = false;
         const pc_status s = try_thin(ctx, d, pk, x, y, true, act, fused, &taken);
@@ -556,6 +560,10 @@ pc_status pc_mfma_fwd(pc_ctx *ctx, const pc_conv_desc *d, const pc_packed *pk, c
 pc_status pc_mfma_bwd_data(pc_ctx *ctx, const pc_conv_desc *d, const pc_packed *pk, const void *dy, void *dx, int act,
                            const void *act_mask, bool *fused)
 {
+    if (d->dtype == PC_F32) {
+        if (fused) *fused = act != PC_ACT_NONE;
+        return pc_f32_bwd_data(ctx, d, pk, dy, dx, fused ? act : PC_ACT_NONE, act_mask);
+    }
     {
         bool taken = false;
         const pc_status s = try_thin(ctx, d, pk, dy, dx, false, act, fused, &taken);

@@ -6,6 +6,8 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <atomic>
+
 #include "pc.h"
 
 #define PC_MAX_P 126
@@ -52,7 +54,7 @@ struct PackView {
     uint16_t *cm_f;       // [cap]
     int32_t *cm_slot;     // [cap]   filter-major slot of the entry
     float4 *cm_val;       // [cap]
-    // MFMA operand tiles (bf16 bit patterns, zero at every pruned position), fragment order
+    // MFMA operand tiles (bf16 bit patterns, or float32 of a float32 pack; zero at every pruned position), fragment order
     uint16_t *wz_fwd;     // A operand of the forward pass
     uint16_t *wz_bwd;     // A operand of the backward-data pass
     // The same operands for the structured-sparse matrix instruction (at most 2 nonzeros in every 4 consecutive
@@ -81,6 +83,14 @@ struct PackView {
     uint2 *ov_fwd_sub_ent, *ov_bwd_sub_ent;
     int32_t Fp, Cp;       // F and C rounded up to 128 (row extent of the operand tiles)
     int32_t Fk, Ck;       // F and C rounded up to 64, the largest channel chunk a kernel walks (reduction extent of the operand tiles)
+    int32_t f32;          // operand tiles in float32 ([row tile][tap][entry / 8][64 lanes][4]); Fp, Cp, Fk, Ck are then multiples of 32
+};
+
+// The completion of one pc_pack / pc_pack_batch call. A record costs several microseconds on the stream, so the packs of
+// a batch call share one (16 records of a residual network's layers: 72 us between its pack and the first conv).
+struct pc_pack_event {
+    hipEvent_t e;
+    std::atomic<int> refs;       // handles that point here; re-recorded only by a call that re-packs all of them
 };
 
 struct pc_packed {
@@ -93,7 +103,7 @@ struct pc_packed {
     size_t slab_bytes;
     PackView v;
     PackView *v_dev;             // copy of v at the start of the slab, for kernels that serve several packs at once
-    hipEvent_t packed_evt;       // recorded after the last pack on this handle
+    pc_pack_event *evt;          // recorded after the last pack on this handle; handles packed by one call share it (nullptr: none yet)
     bool evt_recorded;           // false when that pack was enqueued under stream capture (no event then)
     int64_t nnzk;                // -1 until read back
 };
@@ -177,6 +187,11 @@ pc_status pc_thin_bwd_data(pc_ctx *ctx, const pc_conv_desc *d, const pc_packed *
 // In-place ReLU of n elements; and in-place "keep where the matching element of a is positive, else +0".
 pc_status pc_launch_relu(pc_ctx *ctx, void *z, int64_t n, pc_dtype dtype);
 pc_status pc_launch_relu_mask(pc_ctx *ctx, void *dz, const void *a, int64_t n, pc_dtype dtype);
+// The passes of float32 packs with operand tiles. act, act_mask: a ReLU step on the stored values (PC_ACT_*).
+pc_status pc_f32_fwd(pc_ctx *ctx, const pc_conv_desc *d, const pc_packed *pk, const void *x, void *y, int act);
+pc_status pc_f32_bwd_data(pc_ctx *ctx, const pc_conv_desc *d, const pc_packed *pk, const void *dy, void *dx, int act,
+                          const void *act_mask);
+pc_status pc_f32_bwd_weight(pc_ctx *ctx, const pc_conv_desc *d, const pc_packed *pk, const void *x, const void *dy, float *dw);
 pc_status pc_mfma_bwd_weight_group(pc_ctx *ctx, int n, const pc_conv_desc *d, const pc_packed *const *pk, const void *const *x,
                                    const void *const *dy, float *const *dw);
 pc_status pc_mfma_bwd_weight(pc_ctx *ctx, const pc_conv_desc *d, const pc_packed *pk, const void *x,

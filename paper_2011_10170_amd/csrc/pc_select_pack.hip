@@ -628,13 +628,70 @@ __device__ __forceinline__ void pc_sparse_compress16(const uint16_t *src, uint4 
     *idx = ix;
     *n_ovf = no;
 }
+// LDS of a tile block, shared by the bf16 and the float32 form.
+__device__ __forceinline__ unsigned char *pc_tile_lds()
+{
+    __shared__ __align__(16) unsigned char buf[2 * 9 * 32 * PC_TILE_PITCH * 2];
+    return buf;
+}
+
+// The float32 form: [row tile][tap][entry / 8][lane][4], lane l of a fragment holds row l % 32 and entries
+// 4 * (l / 32) .. + 3. The block's weights are masked into LDS as they lie in W and read in both orientations.
+template <bool FROM_KINFO>
+__device__ __forceinline__ void pc_pack_tile_block_f32(const float *__restrict__ W, const uint8_t *__restrict__ pid,
+                                                       const uint8_t *__restrict__ keep, const LibArg &la, const PackView &v,
+                                                       int fb, int cb)
+{
+    constexpr int PITCH = 289;                    // odd: rows and columns spread over the banks
+    float *tw = reinterpret_cast<float *>(pc_tile_lds());
+    __shared__ uint16_t tm[32][32];
+    const int tid = threadIdx.x, f0 = fb * 32, c0 = cb * 32;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int i = j * 256 + tid, f = f0 + (i >> 5), c = c0 + (i & 31);
+        unsigned m = 0;
+        if (f < v.F && c < v.C) {
+            const int64_t k = (int64_t)f * v.C + c;
+            if (FROM_KINFO) {
+                const uint32_t u = v.kinfo[k];
+                m = u == 0xFFFFFFFFu ? 0u : (u & 511u);
+            } else {
+                const int kp = keep[k], pd = pid[k];
+                m = kp && pd < la.P ? la.mask[pd] : 0u;
+            }
+        }
+        tm[i >> 5][i & 31] = (uint16_t)m;
+    }
+    __syncthreads();
+    const int ncols = v.C - c0 < 32 ? v.C - c0 : 32, nrows = v.F - f0 < 32 ? v.F - f0 : 32;
+#pragma unroll 4
+    for (int i = tid; i < 32 * 288; i += 256) {
+        const int r = i / 288, j = i - r * 288, cl = j / 9, tap = j - cl * 9;
+        const bool in = r < nrows && cl < ncols;
+        const float w = W[in ? ((int64_t)(f0 + r) * v.C + c0) * 9 + j : 0];
+        tw[r * PITCH + j] = in && ((tm[r][cl] >> tap) & 1u) ? w : 0.0f;
+    }
+    __syncthreads();
+    const int KSf = v.Ck / 8, KSb = v.Fk / 8;
+    float4 *of = reinterpret_cast<float4 *>(v.wz_fwd), *ob = reinterpret_cast<float4 *>(v.wz_bwd);
+    for (int o = tid; o < 9 * 4 * 64; o += 256) {
+        const int lane = o & 63, q = o >> 6, tap = q >> 2, ks = q & 3;
+        const int row = lane & 31, e = ks * 8 + 4 * (lane >> 5);
+        const float *p = tw + row * PITCH + e * 9 + tap;
+        of[((int64_t)(fb * 9 + tap) * KSf + cb * 4 + ks) * 64 + lane] = make_float4(p[0], p[9], p[18], p[27]);
+        const float *t = tw + e * PITCH + row * 9 + tap;
+        ob[((int64_t)(cb * 9 + tap) * KSb + fb * 4 + ks) * 64 + lane] = make_float4(t[0], t[PITCH], t[2 * PITCH], t[3 * PITCH]);
+    }
+}
+
 template <bool FROM_KINFO>
 __device__ __forceinline__ void pc_pack_tile_block(const float *__restrict__ W, const uint8_t *__restrict__ pid,
                                                    const uint8_t *__restrict__ keep, const LibArg &la, const PackView &v,
                                                    int fb, int cb)
 {
-    __shared__ __align__(16) uint16_t tA[9][32][PC_TILE_PITCH];   // [tap][filter][channel]
-    __shared__ __align__(16) uint16_t tB[9][32][PC_TILE_PITCH];   // [tap][channel][filter]
+    if (v.f32) return pc_pack_tile_block_f32<FROM_KINFO>(W, pid, keep, la, v, fb, cb);
+    uint16_t (*tA)[32][PC_TILE_PITCH] = reinterpret_cast<uint16_t (*)[32][PC_TILE_PITCH]>(pc_tile_lds());   // [tap][filter][channel]
+    uint16_t (*tB)[32][PC_TILE_PITCH] = tA + 9;                   // [tap][channel][filter]
     __shared__ uint16_t tm[32][32];                               // pattern mask of kernel (f,c), 0 = pruned / outside
     __shared__ uint16_t lm[PC_MAX_P + 2];                         // the pool's masks
     const int tid = threadIdx.x, f0 = fb * 32, c0 = cb * 32;

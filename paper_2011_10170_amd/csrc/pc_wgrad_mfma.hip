@@ -802,6 +802,7 @@ static pc_status pc_mfma_bwd_weight_ws(pc_ctx *ctx, const pc_conv_desc *d, const
 pc_status pc_mfma_bwd_weight(pc_ctx *ctx, const pc_conv_desc *d, const pc_packed *pk, const void *x, const void *dy,
                              float *dw)
 {
+    if (d->dtype == PC_F32) return pc_f32_bwd_weight(ctx, d, pk, x, dy, dw);
     // The kernels find the kept kernels and their slots on the device; the host only needs an upper bound of
     // the slot count to size and stride the partial planes: the exact count when a read-back has already
     // happened, else the capacity of the pack. No read-back is forced here, so a step that re-packs stays
