@@ -314,7 +314,8 @@ def main() -> int:
     # Roofline time of a call = max(algorithmic bytes / HBM peak, nonzero flops / peak of the unit that multiplies):
     # the method's own work, i.e. |in| + |out| + the kept weights, and 8*N*Ho*Wo*nnzk flops per pass -- never the
     # zero-filled flops the matrix-core kernels issue (those give "mfma_util", reported beside it). The unit peak is
-    # the bf16 matrix rate for the matrix-core kernels and the float32 vector rate for the gather kernels; select
+    # the bf16 matrix rate for the bf16 matrix-core kernels and the float32 vector rate (also that of the float32 matrix
+    # instructions) for the other kernels; select
     # and pack are priced by bytes alone.
     calls = []
     log("%-3s %-22s %-10s %9s %9s %8s %6s %6s  %s" % ("#", "layer", "pass", "us", "nz TF/s", "GB/s", "roof", "mfma", "kernel"))
@@ -329,11 +330,11 @@ def main() -> int:
             fl = dfl = 0.0
             mfma = False
         elif li < 0:                                         # the weight gradients of all layers in one call
-            mfma = all(x["variant"] in (B.PC_VARIANT_MFMA, B.PC_VARIANT_MFMA_SPARSE) for x in layers)
+            mfma = wl.dtype == "bf16" and all(x["variant"] in (B.PC_VARIANT_MFMA, B.PC_VARIANT_MFMA_SPARSE) for x in layers)
             fl, dfl = sum(x["flops"] for x in layers), sum(x["dense_flops"] for x in layers)
             byts = float(sum(x["act_in"] + x["act_out"] + 16 * x["nnzk"] for x in layers))
         else:
-            mfma = d["variant"] in (B.PC_VARIANT_MFMA, B.PC_VARIANT_MFMA_SPARSE)
+            mfma = wl.dtype == "bf16" and d["variant"] in (B.PC_VARIANT_MFMA, B.PC_VARIANT_MFMA_SPARSE)
             fl, dfl = d["flops"], d["dense_flops"]
             wbytes = d["nnzk"] * (4 * esz + 2)
             byts = float(d["act_in"] + d["act_out"] + (16 * d["nnzk"] if which == "bwd_weight" else wbytes))

@@ -61,9 +61,10 @@ typedef enum { PC_SCORE_RETAINED = 0, PC_SCORE_KERNEL = 1 } pc_score_mode;
 
 /* Kernel family used by the three conv passes of a packed layer. */
 typedef enum {
-    PC_VARIANT_AUTO = 0,  /* chosen at pack time from dtype and shape */
+    PC_VARIANT_AUTO = 0,  /* chosen at pack time from dtype and shape: the matrix cores below 2^23 kernels, else VALU */
     PC_VARIANT_VALU = 1,  /* pattern-grouped gather on the vector ALUs: only kept taps are multiplied */
-    PC_VARIANT_MFMA = 2,  /* bf16 only: matrix-core contraction over tap-major zero-filled weight tiles */
+    PC_VARIANT_MFMA = 2,  /* matrix-core contraction over tap-major zero-filled weight tiles, in the layer's dtype (float32:
+                             float32 matrix instructions, under AUTO only; forcing it takes bf16) */
     /* bf16 only, never chosen by AUTO: as MFMA, but the forward / backward-data passes of stride-1 layers with at
      * least 64 reduction channels multiply with the structured-sparse matrix instruction (2 nonzeros in 4 reduction
      * entries, twice the reduction length per instruction); the weights that exceed that form go through a second

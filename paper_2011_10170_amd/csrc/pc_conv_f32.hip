@@ -9,6 +9,12 @@
 // Operand layout: lane l holds row (A) / column (B) l % 32 and k = l / 32; accumulator register r of lane l is row
 // 8*(r/4) + 4*(l/32) + r%4, column l % 32. A fragment is 8 reduction entries: lane half h holds entries 4h .. 4h+3 in one
 // 16-byte load, and instruction j of the fragment multiplies entries j and 4 + j.
+//
+// The float32 matrix instructions occupy the vector units: a vector instruction of any wavefront of the SIMD adds its four
+// cycles to the kernel's time (measured: taking out the loads, the LDS writes and the LDS reads of the weight-gradient loop
+// one after the other gives back 9, 8 and 10 %, exactly their vector instructions). So the loops keep addresses in scalar
+// offsets of buffer loads and in immediate offsets of LDS reads, let the range check of a buffer load supply the zeros of
+// the padding, and copy no operand registers.
 #include "pc_mfma.h"
 
 // ------------------------------------------------------------------ forward / backward-data
@@ -17,7 +23,7 @@
 // over (image, row, column of a strip of Ws columns), so a tile is full whatever the map size; what it reads is a
 // range of rows of the "virtual" image in which the images follow each other with one zero row between them.
 // Several workgroups share a CU: the staging of one runs under the matrix instructions of the others.
-#define F32_NE 8        // 16-byte elements staged per thread and chunk
+#define F32_NE 6        // 16-byte elements staged per thread and chunk
 
 struct F32Class {
     int32_t GH, GW, ooff_y, ooff_x;   // pixel grid of this launch part; output pixel = grid * oscale + ooff
@@ -40,7 +46,7 @@ struct F32ConvArgs {
     F32Class cls[4];
 };
 
-template <int NTAPS, int WM, int WN, int WK>
+template <int NTAPS, int WM, int WN, int WK, bool VEC>
 __device__ __forceinline__ void pc_f32_conv_body(const float *__restrict__ in, float *__restrict__ out, const float *__restrict__ wz,
                                                  const F32ConvArgs &g, const F32Class &c, int b, unsigned char *lds)
 {
@@ -73,76 +79,104 @@ __device__ __forceinline__ void pc_f32_conv_body(const float *__restrict__ in, f
         const bool ok = iy < c.R && n < g.N && y >= 0 && y < g.in_H && x >= 0 && x < g.in_W;
         pix[i] = ok ? (uint32_t)(((n - n0) * g.in_H + y) * g.in_W + x) : 0xFFFFFFFFu;
     }
-    float4 R[F32_NE];
+    // VEC: rows of whole quads, and the images a tile touches within 2 GiB: buffer loads, zeros come from the range check.
+    // Else element by element through 64-bit addresses. (Loads stand under no condition: one that does merges with the
+    // register's old value, and the copy waits for it.)
+    constexpr uint32_t OOB = 0x80000000u;
+    const __amdgpu_buffer_rsrc_t isrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float *>(in + (int64_t)n0 * g.in_H * g.in_W * g.in_CH), 0, 0x7FFFFFFF, 0x00020000);
+    if (VEC) {
+#pragma unroll
+        for (int i = 0; i < F32_NE; ++i) pix[i] = pix[i] != 0xFFFFFFFFu ? pix[i] * (uint32_t)(g.in_CH * 4) + part * 16 : OOB;
+    }
+    const bool part_in_last = (g.nchunk - 1) * g.KC + part * 4 < g.in_CH;
+    v4u32 R[F32_NE];
     auto issue = [&](int ch) {
         const int c0 = ch * g.KC;
-        if ((g.in_CH & 3) == 0) {
+        const bool cut = ch == g.nchunk - 1 && !part_in_last;
 #pragma unroll
-            for (int i = 0; i < F32_NE; ++i)
-                if (i * 256 < total) {
-                    const bool ok = pix[i] != 0xFFFFFFFFu && c0 + part * 4 < g.in_CH;
-                    const float4 t = *reinterpret_cast<const float4 *>(ok ? in0 + ((uint64_t)pix[i] * (uint32_t)g.in_CH + c0) : in);
-                    R[i] = make_float4(ok ? t.x : 0.f, ok ? t.y : 0.f, ok ? t.z : 0.f, ok ? t.w : 0.f);
+        for (int i = 0; i < F32_NE; ++i) {
+            if (VEC) {
+                R[i] = __builtin_amdgcn_raw_buffer_load_b128(isrc, (int)(cut ? OOB : pix[i]), c0 * 4, 0);
+            } else {
+                float t[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const bool ok = pix[i] != 0xFFFFFFFFu && c0 + part * 4 + k < g.in_CH;
+                    t[k] = *(ok ? in0 + ((uint64_t)pix[i] * (uint32_t)g.in_CH + c0 + k) : in);
                 }
-        } else {                      // rows are not 16-byte aligned: by element
-#pragma unroll
-            for (int i = 0; i < F32_NE; ++i)
-                if (i * 256 < total) {
-                    float t[4];
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        const bool ok = pix[i] != 0xFFFFFFFFu && c0 + part * 4 + k < g.in_CH;
-                        const float u = *(ok ? in0 + ((uint64_t)pix[i] * (uint32_t)g.in_CH + c0 + k) : in);
-                        t[k] = ok ? u : 0.f;
-                    }
-                    R[i] = make_float4(t[0], t[1], t[2], t[3]);
-                }
+                __builtin_memcpy(&R[i], t, 16);
+            }
         }
     };
-    auto put = [&]() {
+    auto put = [&](int ch) {
         unsigned char *dst = lds + q0 * g.pitch + part * 16;
+        const int left = g.in_CH - ch * g.KC - part * 4;
 #pragma unroll
         for (int i = 0; i < F32_NE; ++i)
-            if ((int)threadIdx.x + 256 * i < total) *reinterpret_cast<float4 *>(dst + i * dq * g.pitch) = R[i];
+            if ((int)threadIdx.x + 256 * i < total) {
+                if (!VEC) {           // (zeros go in here: a select behind the load would wait for it)
+                    const bool ok = pix[i] != 0xFFFFFFFFu;
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) R[i][k] = ok && left > k ? R[i][k] : 0u;
+                }
+                *reinterpret_cast<v4u32 *>(dst + i * dq * g.pitch) = R[i];
+            }
     };
 
     // weight fragments: [row tile][tap][fragment][64 lanes][4], a row tile past the last reads the last (not stored)
     int rt = mt * WM + wm;
     const int rt_last = (g.out_CH - 1) >> 5;
     if (rt > rt_last) rt = rt_last;
-    const float *wl = wz + (int64_t)rt * 9 * g.KS * 256 + lane * 4;
+    const __amdgpu_buffer_rsrc_t wsrc =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(wz + (int64_t)rt * 9 * g.KS * 256), 0, 9 * g.KS * 1024, 0x00020000);
     auto a_load = [&](int tap, int kf) -> float4 {
         const int tw = NTAPS == 9 ? tap : c.tap_w[tap & 3];
-        return *reinterpret_cast<const float4 *>(wl + (int64_t)(tw * g.KS + (kf < g.KS ? kf : g.KS - 1)) * 256);
+        const v4u32 u = __builtin_amdgcn_raw_buffer_load_b128(wsrc, lane * 16, (tw * g.KS + (kf < g.KS ? kf : g.KS - 1)) * 1024, 0);
+        float4 r;
+        __builtin_memcpy(&r, &u, 16);
+        return r;
     };
     auto tap_off = [&](int tap) -> int { return NTAPS == 9 ? c.o0 + tap / 3 * c.dr + tap % 3 * c.ds : c.tap_off[tap & 3]; };
-    constexpr int RD = NTAPS == 9 ? 3 : NTAPS;    // weight fragments in flight
-
     f32x16 acc;
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
     issue(0);
-    float4 ar[RD];
+    // One fragment of weights per tap is in flight (a wavefront's loads retire in order: the nine cover the round trip of
+    // the next chunk's pixels, which are requested in front of them); LDS reads run one tap ahead. The scheduling barriers
+    // keep the loads ahead of the matrix instructions they are to overlap.
+    float4 ar[NTAPS];
 #pragma unroll
-    for (int t = 0; t < RD; ++t) ar[t] = a_load(t, wk);
+    for (int t = 0; t < NTAPS; ++t) ar[t] = a_load(t, wk);
     const int KF = g.KC >> 3;
+    constexpr int RB = NTAPS % 3 == 0 ? 3 : NTAPS % 2 == 0 ? 2 : 1;   // the pixel fragments rotate without copies from one fragment to the next
+    float4 bq[RB];
+    const unsigned char *bt[NTAPS];
+#pragma unroll
+    for (int t = 0; t < NTAPS; ++t) bt[t] = bp + tap_off(t);
     for (int ch = 0; ch < g.nchunk; ++ch) {
         if (ch) __syncthreads();
-        put();
+        put(ch);
         __syncthreads();
         if (ch + 1 < g.nchunk) issue(ch + 1);
         const int left = (g.in_CH - ch * g.KC + 7) >> 3, nf = left < KF ? left : KF;
+        if (wk >= nf) continue;
+        bq[0] = *reinterpret_cast<const float4 *>(bt[0] + wk * 32);
         for (int f = wk; f < nf; f += WK) {
-            const int kf = ch * KF + f, kn = f + WK < nf ? kf + WK : (ch + 1) * KF + wk;   // this fragment and the one after it
+            const int fn = f + WK < nf ? f + WK : f;
+            const int kn = f + WK < nf ? ch * KF + fn : (ch + 1) * KF + wk;   // the fragment after this one
 #pragma unroll
             for (int t = 0; t < NTAPS; ++t) {
-                const float4 bq = *reinterpret_cast<const float4 *>(bp + tap_off(t) + f * 32);
-                const float4 a = ar[t % RD];
-                ar[t % RD] = t + RD < NTAPS ? a_load(t + RD < NTAPS ? t + RD : 0, kf) : a_load((t + RD) % NTAPS, kn);
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, bq.x, acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, bq.y, acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, bq.z, acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, bq.w, acc, 0, 0, 0);
+                const float4 a = ar[t], bv = bq[t % RB];
+                if (RB > 1) bq[(t + 1) % RB] = *reinterpret_cast<const float4 *>(t + 1 < NTAPS ? bt[t + 1 < NTAPS ? t + 1 : 0] + f * 32 : bt[0] + fn * 32);
+                __builtin_amdgcn_sched_barrier(0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, bv.x, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, bv.y, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, bv.z, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, bv.w, acc, 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                ar[t] = a_load(t, kn);        // behind its last use: the register is free
+                if (RB == 1) bq[0] = *reinterpret_cast<const float4 *>(bt[0] + fn * 32);
             }
         }
     }
@@ -190,7 +224,7 @@ __device__ __forceinline__ void pc_f32_conv_body(const float *__restrict__ in, f
 }
 
 // MC: the four parity classes of a stride-2 backward-data pass (4, 2, 2 and 1 taps), each a range of workgroups.
-template <int WM, int WN, int WK, bool MC>
+template <int WM, int WN, int WK, bool MC, bool VEC>
 __global__ void __launch_bounds__(256, 4)
 pc_f32_conv_kernel(const float *__restrict__ in, float *__restrict__ out, const float *__restrict__ wz, F32ConvArgs g)
 {
@@ -201,11 +235,11 @@ pc_f32_conv_kernel(const float *__restrict__ in, float *__restrict__ out, const 
         int k = 0;
         while (k + 1 < g.ncls && b >= g.cls[k + 1].first) ++k;
         const F32Class &c = g.cls[k];
-        if (c.ntaps == 4) pc_f32_conv_body<4, WM, WN, WK>(in, out, wz, g, c, b - c.first, lds);
-        else if (c.ntaps == 2) pc_f32_conv_body<2, WM, WN, WK>(in, out, wz, g, c, b - c.first, lds);
-        else pc_f32_conv_body<1, WM, WN, WK>(in, out, wz, g, c, b - c.first, lds);
+        if (c.ntaps == 4) pc_f32_conv_body<4, WM, WN, WK, VEC>(in, out, wz, g, c, b - c.first, lds);
+        else if (c.ntaps == 2) pc_f32_conv_body<2, WM, WN, WK, VEC>(in, out, wz, g, c, b - c.first, lds);
+        else pc_f32_conv_body<1, WM, WN, WK, VEC>(in, out, wz, g, c, b - c.first, lds);
     } else {
-        pc_f32_conv_body<9, WM, WN, WK>(in, out, wz, g, g.cls[0], b, lds);
+        pc_f32_conv_body<9, WM, WN, WK, VEC>(in, out, wz, g, g.cls[0], b, lds);
     }
 }
 
@@ -299,11 +333,21 @@ static pc_status f32_run(pc_ctx *ctx, F32ConvArgs g, bool mc, int ext, const int
     }
     if (kF32Shapes[best_k].wk > 1 && lds < 16384) lds = 16384;
     const dim3 grid((unsigned)best_blocks), blk(256);
+    // images a tile may touch: its first one and those the rows of a tile reach into
+    int64_t span = 0;
+    for (int i = 0; i < best.ncls; ++i) {
+        const F32Class &c = best.cls[i];
+        const int64_t n = 2 + (32 * kF32Shapes[best_k].wn + c.Ws - 1) / c.Ws / c.GH;
+        if (n > span) span = n;
+    }
+    const bool vec = (g.in_CH & 3) == 0 && span * g.in_H * g.in_W * g.in_CH * 4 < ((int64_t)1 << 31);
     hipStream_t st = ctx->stream;
 #define F32_LAUNCH(WM, WN, WK)                                                                                              \
     do {                                                                                                                    \
-        if (mc) hipLaunchKernelGGL((pc_f32_conv_kernel<WM, WN, WK, true>), grid, blk, lds, st, in, out, wz, best);          \
-        else hipLaunchKernelGGL((pc_f32_conv_kernel<WM, WN, WK, false>), grid, blk, lds, st, in, out, wz, best);            \
+        if (mc && vec) hipLaunchKernelGGL((pc_f32_conv_kernel<WM, WN, WK, true, true>), grid, blk, lds, st, in, out, wz, best);   \
+        else if (mc) hipLaunchKernelGGL((pc_f32_conv_kernel<WM, WN, WK, true, false>), grid, blk, lds, st, in, out, wz, best);    \
+        else if (vec) hipLaunchKernelGGL((pc_f32_conv_kernel<WM, WN, WK, false, true>), grid, blk, lds, st, in, out, wz, best);   \
+        else hipLaunchKernelGGL((pc_f32_conv_kernel<WM, WN, WK, false, false>), grid, blk, lds, st, in, out, wz, best);           \
     } while (0)
     switch (best_k) {
     case 0: F32_LAUNCH(2, 2, 1); break;
@@ -312,7 +356,8 @@ static pc_status f32_run(pc_ctx *ctx, F32ConvArgs g, bool mc, int ext, const int
     default: F32_LAUNCH(1, 1, 4); break;
     }
 #undef F32_LAUNCH
-    pc_note_kernel(ctx, "pc_f32_conv_kernel<%d, %d, %d, %s>", kF32Shapes[best_k].wm, kF32Shapes[best_k].wn, kF32Shapes[best_k].wk, mc ? "true" : "false");
+    pc_note_kernel(ctx, "pc_f32_conv_kernel<%d, %d, %d, %s, %s>", kF32Shapes[best_k].wm, kF32Shapes[best_k].wn, kF32Shapes[best_k].wk,
+                   mc ? "true" : "false", vec ? "true" : "false");
     return pc_hip_check(ctx, hipGetLastError(), "float32 conv launch");
 }
 
@@ -391,7 +436,7 @@ struct F32WgradArgs {
     int64_t pstride;                      // slots per partial plane
 };
 
-template <int WF, int WC, bool THIN>
+template <int WF, int WC, bool THIN, bool VEC>
 __global__ void __launch_bounds__(256, 2)
 pc_f32_wgrad_kernel(const float *__restrict__ x, const float *__restrict__ dy, F32WgradArgs a, const uint32_t *__restrict__ kinfo,
                     float4 *__restrict__ partial)
@@ -407,70 +452,77 @@ pc_f32_wgrad_kernel(const float *__restrict__ x, const float *__restrict__ dy, F
     const int c0 = (tile % a.ct) * CD, f0 = (tile / a.ct) * FD;
     float *sd = smem, *sx = smem + a.TR * a.TCe * PD;
 
-    // staged elements: position inside the tile (or its x region) and offset inside an image
+    // staged elements: a thread takes the same 4 filters (channels) of several positions; position inside the tile (or
+    // its x region) and offset inside an image
+    const int dp = (int)threadIdx.x % (FD / 4), dq = (int)threadIdx.x / (FD / 4), xp = (int)threadIdx.x % (CD / 4), xq = (int)threadIdx.x / (CD / 4);
+    const int dleft = a.F - (f0 + dp * 4), xleft = a.C - (c0 + xp * 4);
     int dpos[F32W_ND], xpos[F32W_NX], doff[F32W_ND], xoff[F32W_NX];
 #pragma unroll
     for (int i = 0; i < F32W_ND; ++i) {
-        const int e = (int)threadIdx.x + 256 * i, q = e / (FD / 4), f = f0 + (e - q * (FD / 4)) * 4;
-        const int r = q / a.TCe, col = q - r * a.TCe;
-        dpos[i] = e < a.nd && col < a.TC && f < a.F ? (r << 16) | col : -1;
-        doff[i] = (r * a.Wo + col) * a.F + f;
+        const int q = dq + i * (1024 / FD), r = q / a.TCe, col = q - r * a.TCe;
+        dpos[i] = r < a.TR && col < a.TC && dleft > 0 ? (r << 16) | col : -1;
+        doff[i] = (r * a.Wo + col) * a.F + f0 + dp * 4;
     }
 #pragma unroll
     for (int i = 0; i < F32W_NX; ++i) {
-        const int e = (int)threadIdx.x + 256 * i, q = e / (CD / 4), cc = c0 + (e - q * (CD / 4)) * 4;
-        const int r = q / a.IW, col = q - r * a.IW;
-        xpos[i] = e < a.nx && cc < a.C ? (r << 16) | col : -1;
-        xoff[i] = (r * a.W + col) * a.C + cc;
+        const int q = xq + i * (1024 / CD), r = q / a.IW, col = q - r * a.IW;
+        xpos[i] = r < a.IR && xleft > 0 ? (r << 16) | col : -1;
+        xoff[i] = (r * a.W + col) * a.C + c0 + xp * 4;
     }
-    const bool d4 = (a.F & 3) == 0, x4 = (a.C & 3) == 0;
-    float4 RD[F32W_ND], RX[F32W_NX];
-    auto load4 = [&](const float *src, int64_t at, bool ok, bool vec, int left) -> float4 {
-        if (vec) {
-            const float4 t = *reinterpret_cast<const float4 *>(src + (ok ? at : 0));
-            return make_float4(ok ? t.x : 0.f, ok ? t.y : 0.f, ok ? t.z : 0.f, ok ? t.w : 0.f);
-        }
+    constexpr uint32_t OOB = 0x80000000u;
+    v4u32 RD[F32W_ND], RX[F32W_NX];
+    auto load4 = [&](const float *src, int64_t at, bool ok, int left) -> v4u32 {
         float t[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const bool o = ok && k < left;
-            const float u = src[o ? at + k : 0];
-            t[k] = o ? u : 0.f;
-        }
-        return make_float4(t[0], t[1], t[2], t[3]);
+        for (int k = 0; k < 4; ++k) t[k] = src[ok && k < left ? at + k : 0];
+        v4u32 r;
+        __builtin_memcpy(&r, t, 16);
+        return r;
     };
+    // valid elements of the tile in the registers, one bit each (not VEC: zeros go in when the element goes to LDS, a
+    // select behind a load would wait for it); VEC: rows of whole quads, an image within 2 GiB
+    uint32_t okd = 0, okx = 0;
     auto issue = [&](int kt) {
         int q = kt;
         const int tc = q % a.tiles_c; q /= a.tiles_c;
         const int tr = q % a.tiles_r, n = q / a.tiles_r;
         const int oy = tr * a.TR, ox = tc * a.TC, iy = oy * a.stride - 1, ix = ox * a.stride - 1;
-        const int64_t db = ((int64_t)n * a.Ho * a.Wo + (int64_t)oy * a.Wo + ox) * a.F;
-        const int64_t xb = ((int64_t)n * a.H * a.W + (int64_t)iy * a.W + ix) * a.C;
-#pragma unroll
-        for (int i = 0; i < F32W_ND; ++i)
-            if (i * 256 < a.nd) {
-                const bool ok = dpos[i] >= 0 && oy + (dpos[i] >> 16) < a.Ho && ox + (dpos[i] & 0xFFFF) < a.Wo;
-                RD[i] = load4(dy, db + doff[i], ok, d4, a.F - (f0 + ((int)threadIdx.x + 256 * i) % (FD / 4) * 4));
-            }
-#pragma unroll
-        for (int i = 0; i < F32W_NX; ++i)
-            if (i * 256 < a.nx) {
-                const int yy = iy + (xpos[i] >> 16), xx = ix + (xpos[i] & 0xFFFF);
-                const bool ok = xpos[i] >= 0 && yy >= 0 && yy < a.H && xx >= 0 && xx < a.W;
-                RX[i] = load4(x, xb + xoff[i], ok, x4, a.C - (c0 + ((int)threadIdx.x + 256 * i) % (CD / 4) * 4));
-            }
-    };
-    auto put = [&]() {
+        const float *dimg = dy + (int64_t)n * a.Ho * a.Wo * a.F, *ximg = x + (int64_t)n * a.H * a.W * a.C;
+        const int db = (oy * a.Wo + ox) * a.F, xb = (iy * a.W + ix) * a.C;
+        const __amdgpu_buffer_rsrc_t dsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(dimg), 0, 0x7FFFFFFF, 0x00020000);
+        const __amdgpu_buffer_rsrc_t xsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(ximg), 0, 0x7FFFFFFF, 0x00020000);
+        okd = okx = 0;
 #pragma unroll
         for (int i = 0; i < F32W_ND; ++i) {
-            const int e = (int)threadIdx.x + 256 * i, q = e / (FD / 4);
-            if (e < a.nd) *reinterpret_cast<float4 *>(sd + q * PD + (e - q * (FD / 4)) * 4) = RD[i];
+            const bool ok = dpos[i] >= 0 && oy + (dpos[i] >> 16) < a.Ho && ox + (dpos[i] & 0xFFFF) < a.Wo;
+            if (VEC) RD[i] = __builtin_amdgcn_raw_buffer_load_b128(dsrc, (int)(ok ? (uint32_t)(db + doff[i]) * 4u : OOB), 0, 0);
+            else { RD[i] = load4(dimg, (int64_t)db + doff[i], ok, dleft); okd |= ok ? 1u << i : 0u; }
         }
 #pragma unroll
         for (int i = 0; i < F32W_NX; ++i) {
-            const int e = (int)threadIdx.x + 256 * i, q = e / (CD / 4);
-            if (e < a.nx) *reinterpret_cast<float4 *>(sx + q * PX + (e - q * (CD / 4)) * 4) = RX[i];
+            const int yy = iy + (xpos[i] >> 16), xx = ix + (xpos[i] & 0xFFFF);
+            const bool ok = xpos[i] >= 0 && (unsigned)yy < (unsigned)a.H && (unsigned)xx < (unsigned)a.W;
+            if (VEC) RX[i] = __builtin_amdgcn_raw_buffer_load_b128(xsrc, (int)(ok ? (uint32_t)(xb + xoff[i]) * 4u : OOB), 0, 0);
+            else { RX[i] = load4(ximg, (int64_t)xb + xoff[i], ok, xleft); okx |= ok ? 1u << i : 0u; }
         }
+    };
+    auto put = [&]() {
+#pragma unroll
+        for (int i = 0; i < F32W_ND; ++i)
+            if ((int)threadIdx.x + 256 * i < a.nd) {
+                if (!VEC)
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) RD[i][k] = ((okd >> i) & 1u) && dleft > k ? RD[i][k] : 0u;
+                *reinterpret_cast<v4u32 *>(sd + (dq + i * (1024 / FD)) * PD + dp * 4) = RD[i];
+            }
+#pragma unroll
+        for (int i = 0; i < F32W_NX; ++i)
+            if ((int)threadIdx.x + 256 * i < a.nx) {
+                if (!VEC)
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) RX[i][k] = ((okx >> i) & 1u) && xleft > k ? RX[i][k] : 0u;
+                *reinterpret_cast<v4u32 *>(sx + (xq + i * (1024 / CD)) * PX + xp * 4) = RX[i];
+            }
     };
 
     f32x16 acc[NT];
@@ -488,8 +540,9 @@ pc_f32_wgrad_kernel(const float *__restrict__ x, const float *__restrict__ dy, F
         b_base = h * a.stride * PX + wc * 32 + n32;
     }
     const int row = a.IW * PX;
+    // operands of two pixel pairs, used in turn
     float fa[2], fb[2][NT];
-    auto read = [&](int s, int k) {
+    auto read = [&](int s, int k) __attribute__((always_inline)) {
         const int y = (int)pc_udiv((uint32_t)s, a.mg_half), xs = (s - y * half) * 2;
         fa[k] = sd[a_base + (y * a.TCe + xs) * PD];
         const float *q = sx + b_base + (y * a.IW + xs) * a.stride * PX;
@@ -498,47 +551,56 @@ pc_f32_wgrad_kernel(const float *__restrict__ x, const float *__restrict__ dy, F
 #pragma unroll
             for (int t = 0; t < NT; ++t) fb[k][t] = q[t / 3 * row + t % 3 * PX];
     };
+    auto multiply = [&](int k) __attribute__((always_inline)) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[k], fb[k][t], acc[t], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
     int kt = split;
     if (kt < a.n_tiles) issue(kt);
+    // (compact slot, pattern mask) of the 16 kernels this lane writes at the end, requested here: behind the loop they
+    // would cost 16 memory round trips in a row
+    const int e_tap = THIN && n32 < 9 * a.C ? n32 / a.C : 0;
+    const int e_c = THIN ? n32 - e_tap * a.C : c0 + wc * 32 + n32;
+    const bool e_on = THIN ? n32 < 9 * a.C : e_c < a.C;
+    uint32_t kinf[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int f = f0 + wf * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
+        const bool on = e_on && f < a.F;
+        const uint32_t u = kinfo[on ? (int64_t)f * a.C + e_c : 0];
+        kinf[r] = on ? u : 0xFFFFFFFFu;
+    }
     for (bool first = true; kt < a.n_tiles; kt += a.ksplit, first = false) {
         if (!first) __syncthreads();
         put();
         __syncthreads();
         if (kt + a.ksplit < a.n_tiles) issue(kt + a.ksplit);
-        // operands of a pixel pair are read one pair ahead
-        if (wk < steps) read(wk, 0);
-        for (int s = wk; s < steps; s += 2 * WK) {
-            if (s + WK < steps) read(s + WK, 1);
-#pragma unroll
-            for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[0], fb[0][t], acc[t], 0, 0, 0);
-            if (s + WK < steps) {
-                if (s + 2 * WK < steps) read(s + 2 * WK, 0);
-#pragma unroll
-                for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[1], fb[1][t], acc[t], 0, 0, 0);
-            }
+        // operands of a pixel pair are read one pair ahead (past the last pair: this one again, unused, so that the reads
+        // stand under no condition and the waits count them)
+        if (wk >= steps) continue;
+        read(wk, 0);
+        int s = wk;
+        for (; s + WK < steps; s += 2 * WK) {
+            read(s + WK, 1);
+            multiply(0);
+            read(s + 2 * WK < steps ? s + 2 * WK : s, 0);
+            multiply(1);
         }
+        if (s < steps) multiply(0);
     }
     // kept taps in compact order, straight from the accumulators: a lane holds one channel and 16 filters
     float4 *pout = partial + (int64_t)(split * WK + wk) * a.pstride;
-    if (THIN) {
-        if (n32 < 9 * a.C) {
-            const int tap = n32 / a.C, c = n32 - tap * a.C;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int f = f0 + wf * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
-                const uint32_t info = f < a.F ? kinfo[(int64_t)f * a.C + c] : 0xFFFFFFFFu;
-                if (info != 0xFFFFFFFFu && ((info >> tap) & 1u))
-                    reinterpret_cast<float *>(pout + (info >> 9))[__popc(info & ((1u << tap) - 1u))] = acc[0][r];
-            }
-        }
-        return;
-    }
-    const int c = c0 + wc * 32 + n32;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-        const int f = f0 + wf * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
-        const uint32_t info = f < a.F && c < a.C ? kinfo[(int64_t)f * a.C + c] : 0xFFFFFFFFu;
+        const uint32_t info = kinf[r];
         if (info == 0xFFFFFFFFu) continue;
+        if (THIN) {
+            if ((info >> e_tap) & 1u)
+                reinterpret_cast<float *>(pout + (info >> 9))[__popc(info & ((1u << e_tap) - 1u))] = acc[0][r];
+            continue;
+        }
         float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
         for (int t = NT - 1; t >= 0; --t) {           // the four set bits of the mask, ascending
@@ -607,13 +669,21 @@ pc_status pc_f32_bwd_weight(pc_ctx *ctx, const pc_conv_desc *d, const pc_packed 
     float4 *po = planes > 1 ? (float4 *)scr : (float4 *)dw;
     const float *xp = (const float *)x, *dp = (const float *)dy;
     hipStream_t st = ctx->stream;
-    if (thin && wf == 2) hipLaunchKernelGGL((pc_f32_wgrad_kernel<2, 1, true>), grid, blk, lds, st, xp, dp, a, pk->v.kinfo, po);
-    else if (thin) hipLaunchKernelGGL((pc_f32_wgrad_kernel<1, 1, true>), grid, blk, lds, st, xp, dp, a, pk->v.kinfo, po);
-    else if (wf == 2 && wc == 2) hipLaunchKernelGGL((pc_f32_wgrad_kernel<2, 2, false>), grid, blk, lds, st, xp, dp, a, pk->v.kinfo, po);
-    else if (wf == 2) hipLaunchKernelGGL((pc_f32_wgrad_kernel<2, 1, false>), grid, blk, lds, st, xp, dp, a, pk->v.kinfo, po);
-    else if (wc == 2) hipLaunchKernelGGL((pc_f32_wgrad_kernel<1, 2, false>), grid, blk, lds, st, xp, dp, a, pk->v.kinfo, po);
-    else hipLaunchKernelGGL((pc_f32_wgrad_kernel<1, 1, false>), grid, blk, lds, st, xp, dp, a, pk->v.kinfo, po);
-    pc_note_kernel(ctx, "pc_f32_wgrad_kernel<%d, %d, %s>", wf, wc, thin ? "true" : "false");
+    const bool vec = (d->F & 3) == 0 && (d->C & 3) == 0 && (int64_t)a.H * a.W * a.C * 4 < ((int64_t)1 << 31) &&
+                     (int64_t)a.Ho * a.Wo * a.F * 4 < ((int64_t)1 << 31);
+#define F32W_LAUNCH(WF, WC)                                                                                                              \
+    do {                                                                                                                                 \
+        if (vec) hipLaunchKernelGGL((pc_f32_wgrad_kernel<WF, WC, false, true>), grid, blk, lds, st, xp, dp, a, pk->v.kinfo, po);         \
+        else hipLaunchKernelGGL((pc_f32_wgrad_kernel<WF, WC, false, false>), grid, blk, lds, st, xp, dp, a, pk->v.kinfo, po);            \
+    } while (0)
+    if (thin && wf == 2) hipLaunchKernelGGL((pc_f32_wgrad_kernel<2, 1, true, false>), grid, blk, lds, st, xp, dp, a, pk->v.kinfo, po);
+    else if (thin) hipLaunchKernelGGL((pc_f32_wgrad_kernel<1, 1, true, false>), grid, blk, lds, st, xp, dp, a, pk->v.kinfo, po);
+    else if (wf == 2 && wc == 2) F32W_LAUNCH(2, 2);
+    else if (wf == 2) F32W_LAUNCH(2, 1);
+    else if (wc == 2) F32W_LAUNCH(1, 2);
+    else F32W_LAUNCH(1, 1);
+#undef F32W_LAUNCH
+    pc_note_kernel(ctx, "pc_f32_wgrad_kernel<%d, %d, %s, %s>", wf, wc, thin ? "true" : "false", vec ? "true" : "false");
     pc_status s = pc_hip_check(ctx, hipGetLastError(), "float32 bwd_weight launch");
     if (s != PC_OK || planes == 1) return s;
     return pc_launch_wgrad_reduce(ctx, (const float *)scr, planes, nslots, nslots, pk, dw);

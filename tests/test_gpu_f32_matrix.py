@@ -1,0 +1,40 @@
+"""The float32 matrix-core kernels at the edges of their tiles: one pixel, maps narrower than a strip and strips that do
+not divide the map, tiles that cross images, channel counts around 8, 32 and 64 and rows that are no whole 16 bytes, the
+first layer's (tap, channel) columns, stride 2 on odd maps; all three passes against the oracle element by element."""
+import pytest
+
+from tests.test_gpu_parity import run_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_2011_10170_amd import binding
+    binding.load()
+    return binding
+
+
+@pytest.fixture(scope="module")
+def ctx(B):
+    import torch
+    c = B.pc_create(0, torch.cuda.current_stream().cuda_stream)
+    yield c
+    B.pc_destroy(c)
+
+
+@pytest.mark.parametrize("shape", [
+    (1, 1, 1, 3, 5, 1), (1, 1, 1, 8, 32, 2), (9, 1, 1, 33, 64, 1), (2, 5, 67, 33, 36, 1), (3, 7, 7, 40, 130, 2), (5, 9, 2, 4, 97, 1),
+    (1, 3, 200, 8, 32, 1), (2, 6, 5, 64, 64, 2), (17, 3, 3, 72, 24, 1), (2, 31, 29, 2, 48, 1), (4, 13, 13, 1, 70, 2), (3, 8, 8, 256, 31, 1),
+    (40, 14, 14, 65, 68, 1), (6, 4, 33, 24, 200, 2)])
+def test_edges(B, ctx, oracle, shape):
+    run_case(B, ctx, oracle, shape, "f32", 8, 0.4, B.PC_VARIANT_AUTO, "f32_matrix")
+    assert B.pc_last_kernel(ctx).startswith("pc_f32_wgrad_kernel")
+
+
+@pytest.mark.parametrize("shape", [(2, 9, 9, 24, 40, 1), (3, 8, 7, 12, 33, 2)])
+def test_gather_kernels_still_take_float32(B, ctx, oracle, shape):
+    run_case(B, ctx, oracle, shape, "f32", 8, 0.4, B.PC_VARIANT_VALU, "f32_gather")
+    assert B.pc_last_kernel(ctx).startswith("pc_wgrad_valu_kernel")
