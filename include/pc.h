@@ -203,16 +203,16 @@ pc_status pc_pack_batch(pc_ctx *ctx, int32_t n_layers, const float *const *W_dev
  * dense-to-sparse conversion of Section 5.1). */
 pc_status pc_update_values(pc_ctx *ctx, pc_packed *pk, const float *W_dev);
 
-/* pc_update_values for several handles (all distinct) at once: one launch per 32 matrix-core packs that were made
- * with the same pool; other packs are updated one by one inside the call.
+/* pc_update_values for several handles (all distinct) at once: one launch per 32 matrix-core packs; other packs
+ * are updated one by one inside the call.
  *   packs_host : HOST array [n_layers] of handles; W_dev_host : HOST array [n_layers] of device pointers */
 pc_status pc_update_values_batch(pc_ctx *ctx, int32_t n_layers, pc_packed *const *packs_host,
                                  const float *const *W_dev_host);
 
 /* nnz_kernels = number of kept kernels; variant = family in use. The count is read back from the device the
- * first time it is asked for after a pack: that call waits for the pack to finish (for a pack that was
- * enqueued while its stream was being captured into a HIP graph it waits for the whole stream of ctx, and it
- * must not be made during the capture). No other call needs the count on the host: a step of
+ * first time it is asked for after a pack: that call waits for the stream the pack was enqueued on (for a
+ * pack that was enqueued while its stream was being captured into a HIP graph: for the stream of ctx; it must not
+ * be made during the capture). No other call needs the count on the host: a step of
  * pc_pattern_select, pc_pack and the three passes enqueues without any read-back and can be captured. */
 pc_status pc_packed_info(pc_ctx *ctx, const pc_packed *pk, int64_t *nnz_kernels, int32_t *variant);
 void pc_packed_free(pc_packed *pk);

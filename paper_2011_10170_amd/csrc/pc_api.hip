@@ -112,6 +112,11 @@ static hipError_t pc_fixed_scratch_lookup(int device)
 }
 
 // ------------------------------------------------------------------ context
+static void pc_release_stream(pc_stream_ref *r)
+{
+    if (r && r->refs.fetch_sub(1) == 1) delete r;
+}
+
 extern "C" pc_status pc_create(pc_ctx **out, int device, void *hip_stream)
 {
     if (!out) return PC_ERR_INVALID_ARG;
@@ -131,7 +136,13 @@ extern "C" pc_status pc_create(pc_ctx **out, int device, void *hip_stream)
     hipDeviceProp_t prop;
     if (hipGetDeviceProperties(&prop, device) != hipSuccess) { delete ctx; return PC_ERR_DEVICE; }
     ctx->num_cu = prop.multiProcessorCount;
+    ctx->ref = new (std::nothrow) pc_stream_ref();
+    if (!ctx->ref) { delete ctx; return PC_ERR_NOMEM; }
+    ctx->ref->refs.store(1);
+    ctx->ref->stream = ctx->stream;
+    ctx->ref->open = true;
     if (hipHostMalloc((void **)&ctx->nnz_pinned, sizeof(int64_t), hipHostMallocDefault) != hipSuccess) {
+        delete ctx->ref;
         delete ctx;
         return PC_ERR_NOMEM;
     }
@@ -144,6 +155,11 @@ extern "C" void pc_destroy(pc_ctx *ctx)
     if (!ctx) return;
     (void)hipSetDevice(ctx->device);
     (void)hipStreamSynchronize(ctx->stream);
+    {
+        std::lock_guard<std::mutex> hold(ctx->ref->lock);
+        ctx->ref->open = false;
+    }
+    pc_release_stream(ctx->ref);
     if (ctx->scratch) (void)hipFree(ctx->scratch);
     for (int i = 0; i < ctx->n_retired; ++i) (void)hipFree(ctx->retired[i]);
     free(ctx->retired);
@@ -334,50 +350,23 @@ static size_t carve(PackView *v, PackView **v_dev, char *base, int F, int C, boo
     return off;
 }
 
-static void pc_release_event(pc_packed *pk)
+// Notes that n handles were packed on the stream of ctx. A pack captured into a graph runs when the graph does, on a stream
+// unknown here: pc_packed_info then waits for the stream of its context instead.
+static void pc_note_packed(pc_ctx *ctx, int n, pc_packed *const *packs)
 {
-    pc_pack_event *v = pk->evt;
-    pk->evt = nullptr;
-    pk->evt_recorded = false;
-    if (v && v->refs.fetch_sub(1) == 1) {
-        (void)hipEventDestroy(v->e);
-        delete v;
-    }
-}
-
-// Records the completion of a pack of n handles on the stream of ctx: one event for all of them. The event the handles
-// share already is used again when no other handle points to it.
-static pc_status pc_record_packed(pc_ctx *ctx, int n, pc_packed *const *packs)
-{
-    // An event recorded while the stream is being captured into a graph cannot be waited on afterwards, so a
-    // captured pack records none; pc_packed_info then waits for the context's stream instead.
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(ctx->stream, &cap) != hipSuccess) {
         (void)hipGetLastError();
         cap = hipStreamCaptureStatusNone;
     }
-    for (int l = 0; l < n; ++l) packs[l]->evt_recorded = false;
-    if (cap != hipStreamCaptureStatusNone) return PC_OK;
-    pc_pack_event *v = packs[0]->evt;
-    for (int l = 1; l < n; ++l)
-        if (packs[l]->evt != v) v = nullptr;
-    if (v && v->refs.load() != n) v = nullptr;
-    if (!v) {
-        v = new (std::nothrow) pc_pack_event();
-        if (!v) return pc_fail(ctx, PC_ERR_NOMEM, "pc_pack: host allocation failed");
-        if (hipEventCreateWithFlags(&v->e, hipEventDisableTiming) != hipSuccess) {
-            delete v;
-            return pc_fail(ctx, PC_ERR_DEVICE, "pc_pack: event creation failed");
-        }
-        v->refs.store(n);
-        for (int l = 0; l < n; ++l) {
-            pc_release_event(packs[l]);
-            packs[l]->evt = v;
-        }
+    pc_stream_ref *now = cap == hipStreamCaptureStatusNone ? ctx->ref : nullptr;
+    for (int l = 0; l < n; ++l) {
+        pc_stream_ref *old = packs[l]->packed_on;
+        if (old == now) continue;
+        if (now) now->refs.fetch_add(1);
+        packs[l]->packed_on = now;
+        pc_release_stream(old);
     }
-    pc_status s = pc_hip_check(ctx, hipEventRecord(v->e, ctx->stream), "hipEventRecord");
-    for (int l = 0; l < n; ++l) packs[l]->evt_recorded = s == PC_OK;
-    return s;
 }
 
 extern "C" void pc_packed_free(pc_packed *pk)
@@ -385,7 +374,7 @@ extern "C" void pc_packed_free(pc_packed *pk)
     if (!pk) return;
     (void)hipSetDevice(pk->device);
     (void)hipDeviceSynchronize();
-    pc_release_event(pk);
+    pc_release_stream(pk->packed_on);
     if (pk->slab) (void)hipFree(pk->slab);
     delete pk;
 }
@@ -451,8 +440,7 @@ extern "C" pc_status pc_pack(pc_ctx *ctx, const float *W, const uint8_t *pid, co
     pc_fill_lib(&la, lib, P);
     memcpy(pk->taps, la.taps, sizeof(pk->taps));
     s = pc_launch_pack(ctx, pk, W, pid, keep);
-    if (s == PC_OK) s = pc_record_packed(ctx, 1, &pk);
-    else pk->evt_recorded = false;
+    pc_note_packed(ctx, 1, &pk);
     if (s != PC_OK) {
         if (!*out) pc_packed_free(pk);
         return s;
@@ -484,12 +472,12 @@ extern "C" pc_status pc_pack_batch(pc_ctx *ctx, int32_t n_layers, const float *c
         pc_packed *pk = packs[l];
         pk->v.P = P;
         pk->nnzk = -1;
-        pk->evt_recorded = false;
         memcpy(pk->lib, lib, sizeof(uint16_t) * P);
         memcpy(pk->taps, la.taps, sizeof(pk->taps));
     }
     s = pc_launch_pack_batch(ctx, n_layers, packs, W, pid, keep, la);
-    return s == PC_OK ? pc_record_packed(ctx, n_layers, packs) : s;
+    pc_note_packed(ctx, n_layers, packs);
+    return s;
 }
 
 extern "C" pc_status pc_update_values(pc_ctx *ctx, pc_packed *pk, const float *W)
@@ -526,8 +514,12 @@ extern "C" pc_status pc_packed_info(pc_ctx *ctx, const pc_packed *pk, int64_t *n
         pc_packed *m = const_cast<pc_packed *>(pk);
         if (m->nnzk < 0) {
             PC_HIP(ctx, hipSetDevice(ctx->device));
-            if (pk->evt_recorded) PC_HIP(ctx, hipEventSynchronize(pk->evt->e));
-            else PC_HIP(ctx, hipStreamSynchronize(ctx->stream));
+            if (pk->packed_on) {
+                std::lock_guard<std::mutex> hold(pk->packed_on->lock);
+                if (pk->packed_on->open) PC_HIP(ctx, hipStreamSynchronize(pk->packed_on->stream));
+            } else {
+                PC_HIP(ctx, hipStreamSynchronize(ctx->stream));
+            }
             int32_t n = 0;
             PC_HIP(ctx, hipMemcpy(&n, pk->v.fm_rowptr + pk->v.F, sizeof(int32_t), hipMemcpyDeviceToHost));
             m->nnzk = n;

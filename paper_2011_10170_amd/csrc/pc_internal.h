@@ -7,6 +7,7 @@
 #include <string.h>
 
 #include <atomic>
+#include <mutex>
 
 #include "pc.h"
 
@@ -15,6 +16,7 @@
 #define PC_OV_SUB 32           // overflow weights a 32 x 32 block's list holds
 #define PC_OV_BAD 0xFFFFFFFFu
 
+struct pc_stream_ref;
 struct pc_ctx {
     int device;
     hipStream_t stream;
@@ -31,6 +33,7 @@ struct pc_ctx {
     bool fixed_scratch;    // set for the duration of an entry point that must not allocate: pc_scratch then hands out the
                            // device's fixed buffer, or fails when the request exceeds it
     char last_kernel[160]; // symbol of the kernel that did the work of the last conv call (pc_last_kernel)
+    pc_stream_ref *ref;
     int64_t *nnz_pinned;   // pinned host word for reading back a pack's kernel count
 };
 
@@ -86,11 +89,14 @@ struct PackView {
     int32_t f32;          // operand tiles in float32 ([row tile][tap][entry / 8][64 lanes][4]); Fp, Cp, Fk, Ck are then multiples of 32
 };
 
-// The completion of one pc_pack / pc_pack_batch call. A record costs several microseconds on the stream, so the packs of
-// a batch call share one (16 records of a residual network's layers: 72 us between its pack and the first conv).
-struct pc_pack_event {
-    hipEvent_t e;
-    std::atomic<int> refs;       // handles that point here; re-recorded only by a call that re-packs all of them
+// The stream of a context, shared with the handles packed on it, for as long as it may be waited for. A pack leaves no event
+// behind: a record costs 5 microseconds on the stream and as many on the host, while the kept-kernel count, all that is ever
+// waited for, is seldom read back. pc_destroy waits for the stream and closes it: what was packed on it is complete then.
+struct pc_stream_ref {
+    std::mutex lock;
+    std::atomic<int> refs;
+    hipStream_t stream;
+    bool open;
 };
 
 struct pc_packed {
@@ -103,8 +109,7 @@ struct pc_packed {
     size_t slab_bytes;
     PackView v;
     PackView *v_dev;             // copy of v at the start of the slab, for kernels that serve several packs at once
-    pc_pack_event *evt;          // recorded after the last pack on this handle; handles packed by one call share it (nullptr: none yet)
-    bool evt_recorded;           // false when that pack was enqueued under stream capture (no event then)
+    pc_stream_ref *packed_on;    // stream of the last pack on this handle (nullptr: it was enqueued under stream capture, or none yet)
     int64_t nnzk;                // -1 until read back
 };
 
@@ -140,12 +145,13 @@ pc_status pc_launch_select(pc_ctx *ctx, const float *W, const float *G, int F, i
 pc_status pc_launch_pack(pc_ctx *ctx, pc_packed *pk, const float *W, const uint8_t *pid, const uint8_t *keep);
 // Several layers per launch (at most PC_BATCH_MAX per kernel; longer lists are cut into groups).
 #define PC_BATCH_MAX 32
-// Index l of the range [first[l], first[l + 1]) that holds workgroup b, 0 <= l < n (uniform over the workgroup).
+// Index l of the range [first[l], first[l + 1]) that holds workgroup b, 0 <= l < n <= 64 (uniform over the workgroup; all
+// lanes take part). The lanes look at one bound each: a walk over the bounds is a chain of scalar loads.
 __device__ __forceinline__ int pc_batch_find(const int32_t *first, int n, int b)
 {
-    int l = 0;
-    while (l + 1 < n && b >= first[l + 1]) ++l;
-    return l;
+    const int lane = threadIdx.x & 63;
+    const int bound = first[lane + 1 < n ? lane + 1 : 0];
+    return (int)__popcll(__ballot(lane + 1 < n && b >= bound));
 }
 pc_status pc_launch_select_batch(pc_ctx *ctx, int n, const float *const *W, const float *const *G, const int32_t *F,
                                  const int32_t *C, const LibArg &la, pc_keep_mode km, const int64_t *n_keep, pc_score_mode sm,

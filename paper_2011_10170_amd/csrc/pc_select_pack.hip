@@ -2,24 +2,22 @@
 //
 // Selection is bit-reproducible: float32, fixed operation order, no fused multiply-add
 // (this file must be compiled with -ffp-contract=off).
-#include "pc_internal.h"
+#include "pc_importance.h"
 
 // ------------------------------------------------------------------ selection
-// Tap importances of one kernel -> best pattern of the pool and the ranking score. Every sum is taken in
-// ascending tap order, one rounded float32 addition at a time. The importances are squares, so none is below +0
-// and adding +0 for a tap outside the pattern changes no bit: the 9 unconditional additions below give exactly
-// ((s_a + s_b) + s_c) + s_d of the pattern's taps a < b < c < d. masks may point to kernel arguments or LDS.
-__device__ __forceinline__ void pc_score_taps(const float (&s)[9], const uint16_t *masks, int P, int score_mode,
-                                              int *pid_out, float *rank_out)
+// Tap importances of one kernel -> best pattern of the pool and the ranking score. Every sum is taken in ascending tap
+// order, one rounded float32 addition at a time. s points to the thread's 9 importances in LDS: the taps of a pattern are
+// the same for the whole wavefront (scalar loads from the kernel arguments), so a pattern is 4 LDS reads and 3 additions.
+// (With the importances in registers a pattern took 9 additions of s_t or +0, i.e. 9 bit tests and selects besides:
+// selection of 1.63 M kernels with 16 patterns 48 us, bound by those vector instructions.)
+__device__ __forceinline__ void pc_score_taps(const float *s, const LibArg &la, int score_mode, int *pid_out, float *rank_out)
 {
     int best = 0;
     float best_score = 0.0f;
-#pragma unroll 2
-    for (int p = 0; p < P; ++p) {
-        const unsigned m = masks[p];
-        float acc = 0.0f;
-#pragma unroll
-        for (int t = 0; t < 9; ++t) acc = acc + (((m >> t) & 1u) ? s[t] : 0.0f);
+#pragma unroll 4
+    for (int p = 0; p < la.P; ++p) {
+        const uint32_t w = *reinterpret_cast<const uint32_t *>(la.taps[p]);
+        const float acc = ((s[w & 255u] + s[(w >> 8) & 255u]) + s[(w >> 16) & 255u]) + s[w >> 24];
         if (p == 0 || acc > best_score) {
             best_score = acc;
             best = p;
@@ -36,243 +34,200 @@ __device__ __forceinline__ void pc_score_taps(const float (&s)[9], const uint16_
     }
 }
 
-// One thread per kernel (f,c): 9 tap importances, the best pattern of the pool, the ranking score.
+// Scores of all kernels for the segments ranked by the kernels below; the first nzero words of zero are cleared for them.
 __global__ void __launch_bounds__(256)
-pc_select_score_kernel(const float *__restrict__ W, const float *__restrict__ G, int64_t nk, LibArg la,
-                       int score_mode, uint8_t *__restrict__ pid, float *__restrict__ R)
+pc_select_score_kernel(const float *__restrict__ W, const float *__restrict__ G, int64_t nk, LibArg la, int score_mode,
+                       uint8_t *__restrict__ pid, float *__restrict__ R, uint32_t *__restrict__ zero, int nzero)
 {
-    int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= nk) return;
-    float s[9];
-#pragma unroll
-    for (int t = 0; t < 9; ++t) {
-        float w = W[k * 9 + t];
-        if (G) {
-            float gw = G[k * 9 + t] * w;
-            s[t] = gw * gw;
-        } else {
-            s[t] = w * w;
-        }
-    }
+    __shared__ __align__(16) float s[4][64 * 9];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int i = (int)blockIdx.x * 256 + (int)threadIdx.x; i < nzero; i += (int)gridDim.x * 256) zero[i] = 0u;
+    const int64_t k0 = ((int64_t)blockIdx.x * 4 + wave) * 64;
+    if (k0 >= nk) return;
+    const int n = nk - k0 < 64 ? (int)(nk - k0) : 64;
+    PcImpRegs r;
+    pc_imp_issue(W, G, k0, n, r);
+    pc_imp_put(r, G != nullptr, n, s[wave]);
+    if (lane >= n) return;
     int best;
-    float r;
-    pc_score_taps(s, la.mask, la.P, score_mode, &best, &r);
-    pid[k] = (uint8_t)best;
-    R[k] = r;
+    float sc;
+    pc_score_taps(s[wave] + lane * 9, la, score_mode, &best, &sc);
+    pid[k0 + lane] = (uint8_t)best;
+    R[k0 + lane] = sc;
 }
 
-// Exact top-n_keep of every row of R (n rows of length L, L <= PC_TOPN_MAX) in the order (score descending,
-// index ascending), one workgroup per row: a 4-pass radix select over order-preserving 32-bit keys finds the
-// score of the n_keep-th kernel and how many kernels with exactly that score are kept; those are the ones
-// with the lowest indices. Counts are integers: the result does not depend on the order of the atomics.
-#define PC_TOPN_MAX 8192
+// ---- exact top-n of a segment in the order (score descending, index ascending): a radix select over order-preserving
+// 32-bit keys. A pass counts the next digit of the keys that share the prefix found so far; the digit that holds the
+// rem-th largest of them joins the prefix. As soon as all keys of that digit are kept the rest of the key does not
+// matter; otherwise, after the last digit, the keys equal to the threshold are kept by index. Counts are integers: the
+// result does not depend on the order of the atomics.
+#define PC_TOPN_WG 16384        // longest layer ranked by one workgroup
 __device__ __forceinline__ uint32_t pc_order_key(float f)
 {
     const uint32_t b = __float_as_uint(f);
     return b ^ ((b >> 31) ? 0xFFFFFFFFu : 0x80000000u);   // a > b as floats  <=>  key(a) > key(b) as unsigned
 }
 
-__global__ void __launch_bounds__(256)
-pc_select_topn_row_kernel(const float *__restrict__ R, int L, int n_keep, uint8_t *__restrict__ keep)
+// The digit of a finished histogram of T * PER bins (h: bins PER * threadIdx.x .. of this thread) that holds the rem-th
+// largest key, 1 <= rem <= keys counted: in out[0], with the number of keys of larger digits in out[1] and its own count in
+// out[2]. Called by all T threads; ends with a barrier. part: T / 64 ints of LDS.
+template <int T, int PER>
+__device__ __forceinline__ void pc_topn_digit(const uint32_t (&h)[PER], int rem, int *part, int *out)
 {
-    extern __shared__ uint32_t keys[];          // L keys
-    __shared__ int hist[256], above[256];
-    __shared__ uint32_t s_prefix;
-    __shared__ int s_remaining, s_wave_cnt[4], s_base;
-    const float *seg = R + (int64_t)blockIdx.x * L;
-    uint8_t *out = keep + (int64_t)blockIdx.x * L;
-    if (n_keep <= 0 || n_keep >= L) {
-        for (int i = threadIdx.x; i < L; i += 256) out[i] = n_keep > 0 ? 1 : 0;
-        return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int mine = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) mine += (int)h[j];
+    int incl = mine;                            // bins of this lane and of the higher lanes of the wavefront
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int t = __shfl_down(incl, off);
+        if (lane + off < 64) incl += t;
     }
-    for (int i = threadIdx.x; i < L; i += 256) keys[i] = pc_order_key(seg[i]);
-    if (threadIdx.x == 0) { s_prefix = 0u; s_remaining = n_keep; }
+    if (lane == 0) part[wave] = incl;
     __syncthreads();
-    for (int shift = 24; shift >= 0; shift -= 8) {
-        hist[threadIdx.x] = 0;
-        __syncthreads();
-        const uint32_t prefix = s_prefix;
-        const uint32_t himask = shift == 24 ? 0u : 0xFFFFFFFFu << (shift + 8);
-        for (int i = threadIdx.x; i < L; i += 256) {
-            const uint32_t k = keys[i];
-            if ((k & himask) == prefix) atomicAdd(&hist[(k >> shift) & 255u], 1);
+    int above = incl - mine;
+#pragma unroll
+    for (int w = 0; w < T / 64; ++w) above += w > wave ? part[w] : 0;
+    if (above < rem && rem <= above + mine) {   // exactly one thread
+#pragma unroll
+        for (int j = PER - 1; j >= 0; --j) {
+            const int n = (int)h[j];
+            if (above < rem && rem <= above + n) { out[0] = tid * PER + j; out[1] = above; out[2] = n; }
+            above += n;
         }
-        __syncthreads();
-        // above[d] = number of candidates whose digit is larger than d (suffix sum, exclusive)
-        above[threadIdx.x] = hist[threadIdx.x];
-        __syncthreads();
-        for (int d = 1; d < 256; d <<= 1) {
-            const int add = threadIdx.x + d < 256 ? above[threadIdx.x + d] : 0;
-            __syncthreads();
-            above[threadIdx.x] += add;
-            __syncthreads();
-        }
-        const int incl = above[threadIdx.x], excl = incl - hist[threadIdx.x];
-        const int rem = s_remaining;
-        __syncthreads();
-        if (excl < rem && rem <= incl) {        // exactly one digit holds the rem-th largest candidate
-            s_prefix = prefix | ((uint32_t)threadIdx.x << shift);
-            s_remaining = rem - excl;
-        }
-        __syncthreads();
     }
-    const uint32_t T = s_prefix;
-    const int take_equal = s_remaining;         // kernels with key == T that are kept: the first ones by index
-    if (threadIdx.x == 0) s_base = 0;
     __syncthreads();
+}
+
+// Position of each of the flagged elements among the flagged elements of the workgroup, by thread; *total: their number.
+__device__ __forceinline__ int pc_block_rank(bool flag, int *wcnt, int nwaves, int *total)
+{
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int i0 = 0; i0 < L; i0 += 256) {
-        const int i = i0 + threadIdx.x;
-        const uint32_t k = i < L ? keys[i] : 0u;
-        const bool eq = i < L && k == T;
-        const unsigned long long b = __ballot(eq);
-        if (lane == 0) s_wave_cnt[wave] = __popcll(b);
-        __syncthreads();
-        int before = s_base + __popcll(b & ((1ull << lane) - 1ull));
-        for (int w2 = 0; w2 < wave; ++w2) before += s_wave_cnt[w2];
-        if (i < L) out[i] = (k > T || (eq && before < take_equal)) ? 1 : 0;
-        __syncthreads();
-        if (threadIdx.x == 0) s_base += s_wave_cnt[0] + s_wave_cnt[1] + s_wave_cnt[2] + s_wave_cnt[3];
-        __syncthreads();
-    }
-}
-
-// Selection of one filter row in one workgroup (rows of up to PC_TOPN_MAX kernels): scores as in the kernel
-// above, then the top n_keep of the row by the same radix select, without the round trip of the scores through
-// memory. W and G reach the lanes through LDS so that the global loads are contiguous.
-__device__ __forceinline__ void pc_select_row_body(const float *__restrict__ W, const float *__restrict__ G, int C, const LibArg &la,
-                                                   int score_mode, int n_keep, uint8_t *__restrict__ pid,
-                                                   uint8_t *__restrict__ keep, int row)
-{
-    extern __shared__ uint32_t dyn[];           // C keys, then blockDim.x * 9 floats of W, then as many of G
-    __shared__ int hist[256];
-    __shared__ uint32_t s_prefix;
-    __shared__ int s_remaining, s_wave_cnt[16], s_base;
-    __shared__ uint16_t s_mask[PC_MAX_P + 2];
-    const int T = blockDim.x, tid = threadIdx.x;
-    if (tid < la.P) s_mask[tid] = la.mask[tid];   // visible after the first barrier of the loop below
-    uint32_t *keys = dyn;
-    float *sw = reinterpret_cast<float *>(dyn + C);
-    float *sg = sw + (size_t)T * 9;
-    const int64_t row0 = (int64_t)row * C;
-    for (int c0 = 0; c0 < C; c0 += T) {
-        const int n = C - c0 < T ? C - c0 : T;
-        const float *wsrc = W + (row0 + c0) * 9;
-        const float *gsrc = G ? G + (row0 + c0) * 9 : nullptr;
-        if (c0) __syncthreads();
-        // all loads of the thread first (index clamped, so they are unconditional), then the LDS writes: one memory
-        // round trip per chunk instead of one per element
-        float rw[9], rg[9];
-#pragma unroll
-        for (int j = 0; j < 9; ++j) {
-            const int i = j * T + tid, ic = i < n * 9 ? i : n * 9 - 1;
-            rw[j] = wsrc[ic];
-            rg[j] = gsrc ? gsrc[ic] : 0.0f;
-        }
-#pragma unroll
-        for (int j = 0; j < 9; ++j) {
-            const int i = j * T + tid;
-            if (i < n * 9) {
-                sw[i] = rw[j];
-                if (gsrc) sg[i] = rg[j];
-            }
-        }
-        __syncthreads();
-        if (tid < n) {
-            float s[9];
-#pragma unroll
-            for (int t = 0; t < 9; ++t) {
-                const float w = sw[tid * 9 + t];
-                if (gsrc) {
-                    const float gw = sg[tid * 9 + t] * w;
-                    s[t] = gw * gw;
-                } else {
-                    s[t] = w * w;
-                }
-            }
-            int best;
-            float r;
-            pc_score_taps(s, s_mask, la.P, score_mode, &best, &r);
-            pid[row0 + c0 + tid] = (uint8_t)best;
-            keys[c0 + tid] = pc_order_key(r);
-        }
-    }
-    uint8_t *out = keep + row0;
-    if (n_keep <= 0 || n_keep >= C) {
-        for (int i = tid; i < C; i += T) out[i] = n_keep > 0 ? 1 : 0;
-        return;
-    }
-    if (tid == 0) { s_prefix = 0u; s_remaining = n_keep; }
-    const int lane = tid & 63, wave = tid >> 6;
-    for (int shift = 24; shift >= 0; shift -= 8) {
-        if (tid < 256) hist[tid] = 0;
-        __syncthreads();                        // also orders the keys / s_prefix writes before their readers
-        const uint32_t prefix = s_prefix;
-        const uint32_t himask = shift == 24 ? 0u : 0xFFFFFFFFu << (shift + 8);
-        for (int i = tid; i < C; i += T) {
-            const uint32_t k = keys[i];
-            if ((k & himask) == prefix) atomicAdd(&hist[(k >> shift) & 255u], 1);
-        }
-        __syncthreads();
-        if (wave == 0) {
-            // lane l owns digits 4l..4l+3; hi = candidates with a digit above the lane's four
-            const int h0 = hist[4 * lane], h1 = hist[4 * lane + 1], h2 = hist[4 * lane + 2], h3 = hist[4 * lane + 3];
-            const int mine = h0 + h1 + h2 + h3;
-            int incl = mine;
-            for (int off = 1; off < 64; off <<= 1) {
-                const int t = __shfl_down(incl, off);
-                if (lane + off < 64) incl += t;
-            }
-            const int rem = s_remaining;
-            const int hi = incl - mine;
-            // exactly one digit d has (candidates above d) < rem <= (candidates above d) + hist[d]
-            const int e3 = hi, e2 = e3 + h3, e1 = e2 + h2, e0 = e1 + h1;
-            int d = -1, ex = 0;
-            if (e3 < rem && rem <= e3 + h3) { d = 3; ex = e3; }
-            else if (e2 < rem && rem <= e2 + h2) { d = 2; ex = e2; }
-            else if (e1 < rem && rem <= e1 + h1) { d = 1; ex = e1; }
-            else if (e0 < rem && rem <= e0 + h0) { d = 0; ex = e0; }
-            if (d >= 0) {
-                s_prefix = prefix | ((uint32_t)(4 * lane + d) << shift);
-                s_remaining = rem - ex;
-            }
-        }
-        __syncthreads();
-    }
-    const uint32_t Tk = s_prefix;
-    const int take_equal = s_remaining;         // kernels with key == Tk that are kept: the first ones by index
-    const int nwaves = T >> 6;
-    if (tid == 0) s_base = 0;
+    const unsigned long long b = __ballot(flag);
+    __syncthreads();                            // wcnt of an earlier call has been read
+    if (lane == 0) wcnt[wave] = __popcll(b);
     __syncthreads();
-    for (int i0 = 0; i0 < C; i0 += T) {
-        const int i = i0 + tid;
-        const uint32_t k = i < C ? keys[i] : 0u;
-        const bool eq = i < C && k == Tk;
-        const unsigned long long b = __ballot(eq);
-        if (lane == 0) s_wave_cnt[wave] = __popcll(b);
-        __syncthreads();
-        int before = s_base + __popcll(b & ((1ull << lane) - 1ull));
-        for (int w2 = 0; w2 < wave; ++w2) before += s_wave_cnt[w2];
-        if (i < C) out[i] = (k > Tk || (eq && before < take_equal)) ? 1 : 0;
-        __syncthreads();
-        if (tid == 0) {
-            int add = 0;
-            for (int w2 = 0; w2 < nwaves; ++w2) add += s_wave_cnt[w2];
-            s_base += add;
+    int before = __popcll(b & ((1ull << lane) - 1ull)), sum = 0;
+    for (int w = 0; w < nwaves; ++w) {
+        before += w < wave ? wcnt[w] : 0;
+        sum += wcnt[w];
+    }
+    *total = sum;
+    return before;
+}
+
+// A row's keys in one wavefront, key i in register i / 64 of lane i % 64 (registers past the row hold 0): keep flags of the
+// registers j0 <= j < j1. The threshold comes from a binary search over the bits of the key: a step is one comparison per
+// register, the lanes that pass are counted by the scalar unit, and no LDS or barrier takes part. It ends when exactly
+// n_keep keys pass (after about 20 steps), or with the threshold key itself, whose copies are kept by index.
+#define PC_ROW_MAX 512          // longest row ranked in registers
+template <int NV>
+__device__ __forceinline__ void pc_row_keep(const uint32_t (&key)[NV], int C, int n_keep, int j0, int j1, uint8_t *__restrict__ out)
+{
+    const int lane = threadIdx.x & 63;
+    uint32_t T = 0u;
+    int above = 0, cnt = -1;                    // keys known to exceed every later threshold; keys that pass T (-1: not counted)
+    if (n_keep >= C) {
+        cnt = n_keep;
+    } else if (n_keep <= 0) {
+        T = 0xFFFFFFFFu;
+    } else {
+        for (int bit = 31; bit >= 0 && cnt != n_keep; --bit) {
+            const uint32_t t = T | (1u << bit);
+            int c = 0;
+#pragma unroll
+            for (int j = 0; j < NV; ++j) c += (int)__popcll(__ballot(key[j] >= t));
+            if (c >= n_keep) { T = t; cnt = c; }
+            else above = c;
         }
-        __syncthreads();
+    }
+    const bool all = cnt == n_keep;             // every key that passes T is kept
+    int rank = 0;                               // otherwise: keys equal to T seen so far, of which the first n_keep - above stay
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+        bool take = key[j] >= T;
+        if (!all) {
+            const bool eq = key[j] == T && j * 64 + lane < C;
+            const unsigned long long b = __ballot(eq);
+            take = key[j] > T || (eq && rank + (int)__popcll(b & ((1ull << lane) - 1ull)) < n_keep - above);
+            rank += (int)__popcll(b);
+        }
+        if (j >= j0 && j < j1 && j * 64 + lane < C) out[j * 64 + lane] = n_keep > 0 && take ? 1 : 0;
     }
 }
 
-__global__ void __launch_bounds__(512)
-pc_select_row_kernel(const float *__restrict__ W, const float *__restrict__ G, int C, LibArg la, int score_mode,
-                     int n_keep, uint8_t *__restrict__ pid, uint8_t *__restrict__ keep)
+// Selection of one filter row of at most 64 * NV kernels by one wavefront (s: 64 * 9 floats of LDS): the next 64 kernels
+// are on their way from memory while 64 are scored.
+template <int NV>
+__device__ __forceinline__ void pc_select_row_wave(const float *__restrict__ W, const float *__restrict__ G, int C, const LibArg &la,
+                                                   int score_mode, int n_keep, uint8_t *__restrict__ pid,
+                                                   uint8_t *__restrict__ keep, int row, float *s)
 {
-    pc_select_row_body(W, G, C, la, score_mode, n_keep, pid, keep, (int)blockIdx.x);
+    const int lane = threadIdx.x & 63;
+    const int64_t row0 = (int64_t)row * C;
+    uint32_t key[NV];
+    PcImpRegs r;
+    pc_imp_issue(W, G, row0, C < 64 ? C : 64, r);
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+        key[j] = 0u;
+        const int n = C - j * 64 < 64 ? C - j * 64 : 64;
+        if (n > 0) {
+            pc_imp_put(r, G != nullptr, n, s);
+            if (n == 64 && C > (j + 1) * 64)
+                pc_imp_issue(W, G, row0 + (j + 1) * 64, C - (j + 1) * 64 < 64 ? C - (j + 1) * 64 : 64, r);
+            if (lane < n) {
+                int best;
+                float sc;
+                pc_score_taps(s + lane * 9, la, score_mode, &best, &sc);
+                pid[row0 + j * 64 + lane] = (uint8_t)best;
+                key[j] = pc_order_key(sc);
+            }
+        }
+    }
+    pc_row_keep<NV>(key, C, n_keep, 0, NV, keep + row0);
 }
 
-// The same for the filter rows of several layers in one launch: workgroup b serves row b - row0[l] of the layer l
-// whose range holds b. Dynamic LDS is sized for the widest layer.
+// One row of at most PC_ROW_MAX kernels per workgroup of ceil(C / 64) wavefronts, for launches with too few rows to fill the
+// chip with a wavefront each: every wavefront scores 64 kernels, then all of them find the threshold of the whole row (one
+// barrier, no second one) and each writes its own part.
+__device__ __forceinline__ void pc_select_row_group(const float *__restrict__ W, const float *__restrict__ G, int C, const LibArg &la,
+                                                    int score_mode, int n_keep, uint8_t *__restrict__ pid,
+                                                    uint8_t *__restrict__ keep, int row)
+{
+    __shared__ __align__(16) float s[PC_ROW_MAX / 64][64 * 9];
+    __shared__ uint32_t keys[PC_ROW_MAX];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t row0 = (int64_t)row * C;
+    const int n = C - wave * 64 < 64 ? C - wave * 64 : 64;
+    if (n > 0) {
+        PcImpRegs r;
+        pc_imp_issue(W, G, row0 + wave * 64, n, r);
+        pc_imp_put(r, G != nullptr, n, s[wave]);
+        if (lane < n) {
+            int best;
+            float sc;
+            pc_score_taps(s[wave] + lane * 9, la, score_mode, &best, &sc);
+            pid[row0 + wave * 64 + lane] = (uint8_t)best;
+            keys[wave * 64 + lane] = pc_order_key(sc);
+        }
+    }
+    __syncthreads();
+    if (n <= 0) return;
+    if (C <= 64) {
+        const uint32_t key[1] = {lane < C ? keys[lane] : 0u};
+        pc_row_keep<1>(key, C, n_keep, wave, wave + 1, keep + row0);
+    } else {
+        uint32_t key[PC_ROW_MAX / 64];
+#pragma unroll
+        for (int j = 0; j < PC_ROW_MAX / 64; ++j) key[j] = j * 64 + lane < C ? keys[j * 64 + lane] : 0u;
+        pc_row_keep<PC_ROW_MAX / 64>(key, C, n_keep, wave, wave + 1, keep + row0);
+    }
+}
+
+// Filter rows of several layers in one launch; PER_WAVE: a wavefront (workgroup of 64) per row, else a workgroup per row.
+// Row b - row0[l] of the layer l whose range holds b.
 struct SelBatchArg {
     int32_t n, score_mode;
     int32_t row0[PC_BATCH_MAX + 1];
@@ -281,153 +236,193 @@ struct SelBatchArg {
     uint8_t *pid[PC_BATCH_MAX], *keep[PC_BATCH_MAX];
 };
 
-__global__ void __launch_bounds__(512) pc_select_rows_batch_kernel(SelBatchArg b, LibArg la)
+template <bool PER_WAVE>
+__global__ void __launch_bounds__(PER_WAVE ? 64 : PC_ROW_MAX) pc_select_rows_kernel(SelBatchArg b, LibArg la)
 {
-    const int l = pc_batch_find(b.row0, b.n, (int)blockIdx.x);
-    pc_select_row_body(b.W[l], b.G[l], b.C[l], la, b.score_mode, b.n_keep[l], b.pid[l], b.keep[l], (int)blockIdx.x - b.row0[l]);
+    const int l = pc_batch_find(b.row0, b.n, (int)blockIdx.x), row = (int)blockIdx.x - b.row0[l], C = b.C[l];
+    if constexpr (PER_WAVE) {
+        __shared__ __align__(16) float s[64 * 9];
+        if (C <= 64) pc_select_row_wave<1>(b.W[l], b.G[l], C, la, b.score_mode, b.n_keep[l], b.pid[l], b.keep[l], row, s);
+        else pc_select_row_wave<PC_ROW_MAX / 64>(b.W[l], b.G[l], C, la, b.score_mode, b.n_keep[l], b.pid[l], b.keep[l], row, s);
+    } else {
+        pc_select_row_group(b.W[l], b.G[l], C, la, b.score_mode, b.n_keep[l], b.pid[l], b.keep[l], row);
+    }
 }
 
-// ---- exact top-n_keep of long segments (more than PC_TOPN_MAX scores): the same radix select across workgroups.
-// Segment g has L scores; state per segment: hist[4][256] (zeroed first), then per-workgroup counts of the scores
-// equal to the threshold. Pass q counts the digit (bits 31-8q .. 24-8q of the order-preserving key) of the
-// scores whose higher digits equal the prefix chosen by the passes before; every workgroup derives that prefix
-// again from the finished histograms (a 256-bin scan per pass) instead of reading it from a single writer.
-#define PC_TOPN_CHUNK 2048      // scores per workgroup in the counting and writing kernels
-
-// Wave 0 replays passes 0..upto-1: prefix and remaining count after them. All threads call it; ends with a barrier.
-__device__ __forceinline__ void pc_topn_replay(const uint32_t *__restrict__ hist, int upto, int n_keep, uint32_t *s_prefix,
-                                               int *s_rem)
+// Top n_keep of segment blockIdx.x of R (L <= 1024 * NV scores): one workgroup with the keys in registers, digits of 12,
+// 10 and 10 bits. A 256 x 256 layer ranked as a whole: one launch where counting across workgroups took eight (zeroing,
+// four digits, equal scores, their scan, writing: 44 us with the gaps between them).
+template <int NV>
+__global__ void __launch_bounds__(1024)
+pc_topn_wg_kernel(const float *__restrict__ R, int L, int n_keep, uint8_t *__restrict__ keep)
 {
-    if (threadIdx.x < 64) {
-        const int lane = threadIdx.x;
-        uint32_t prefix = 0u;
-        int rem = n_keep;
-        for (int q = 0; q < upto; ++q) {
-            const uint32_t *h = hist + q * 256 + 4 * lane;      // lane owns digits 4*lane .. 4*lane+3
-            const int h0 = (int)h[0], h1 = (int)h[1], h2 = (int)h[2], h3 = (int)h[3];
-            const int mine = h0 + h1 + h2 + h3;
-            int incl = mine;
-            for (int off = 1; off < 64; off <<= 1) {
-                const int t = __shfl_down(incl, off);
-                if (lane + off < 64) incl += t;
-            }
-            const int e3 = incl - mine, e2 = e3 + h3, e1 = e2 + h2, e0 = e1 + h1;   // candidates with a larger digit
-            int d = -1, ex = 0;
-            if (e3 < rem && rem <= e3 + h3) { d = 3; ex = e3; }
-            else if (e2 < rem && rem <= e2 + h2) { d = 2; ex = e2; }
-            else if (e1 < rem && rem <= e1 + h1) { d = 1; ex = e1; }
-            else if (e0 < rem && rem <= e0 + h0) { d = 0; ex = e0; }
-            const unsigned long long found = __ballot(d >= 0);  // exactly one lane while 1 <= rem <= candidates
-            const int src = found ? __ffsll((long long)found) - 1 : 0;
-            const int digit = __shfl(4 * lane + (d < 0 ? 0 : d), src);
-            const int exs = __shfl(ex, src);
-            prefix |= (uint32_t)digit << (24 - 8 * q);
-            rem -= exs;
+    __shared__ uint32_t hist[4096];
+    __shared__ int part[16], dig[3];
+    const float *seg = R + (int64_t)blockIdx.x * L;
+    uint8_t *out = keep + (int64_t)blockIdx.x * L;
+    const int tid = threadIdx.x;
+    float r[NV];
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+        const int i = j * 1024 + tid;
+        r[j] = seg[i < L ? i : L - 1];
+    }
+    for (int i = tid; i < 4096; i += 1024) hist[i] = 0u;
+    uint32_t prefix = 0u;
+    int rem = n_keep, shift = 20;
+    bool all;
+    for (int pass = 0;; ++pass, shift -= 10) {
+        const uint32_t himask = pass == 0 ? 0u : 0xFFFFFFFFu << (shift + 10);
+        const uint32_t dmask = pass == 0 ? 4095u : 1023u;
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < NV; ++j) {
+            const uint32_t k = pc_order_key(r[j]);
+            if (j * 1024 + tid < L && (k & himask) == prefix) atomicAdd(&hist[(k >> shift) & dmask], 1u);
         }
-        if (lane == 0) { *s_prefix = prefix; *s_rem = rem; }
+        __syncthreads();
+        if (pass == 0) {
+            const uint32_t h[4] = {hist[4 * tid], hist[4 * tid + 1], hist[4 * tid + 2], hist[4 * tid + 3]};
+            pc_topn_digit<1024, 4>(h, rem, part, dig);
+        } else {
+            const uint32_t h[1] = {hist[tid]};
+            pc_topn_digit<1024, 1>(h, rem, part, dig);
+        }
+        prefix |= (uint32_t)dig[0] << shift;
+        rem -= dig[1];
+        all = dig[2] == rem;
+        if (all || shift == 0) break;
+        hist[tid] = 0u;                         // read before the barrier that ended pc_topn_digit
     }
-    __syncthreads();
+    const uint32_t himask = 0xFFFFFFFFu << shift;
+    int base = 0;
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+        const int i = j * 1024 + tid;
+        const uint32_t k = pc_order_key(r[j]);
+        bool take = (k & himask) >= prefix;
+        if (!all) {                             // uniform: of the keys equal to the threshold the first rem by index
+            const bool eq = i < L && k == prefix;
+            int total;
+            const int before = base + pc_block_rank(eq, part, 16, &total);
+            take = k > prefix || (eq && before < rem);
+            base += total;
+        }
+        if (i < L) out[i] = take ? 1 : 0;
+    }
 }
 
-__global__ void __launch_bounds__(256) pc_topn_zero_kernel(uint32_t *__restrict__ state, int64_t n)
+// Segments above PC_TOPN_WG (whole layers ranked at once), across workgroups: three counting passes (11, 11 and 10 bits;
+// hist[3][2048], zeroed by the score kernel) and a writing pass. Every workgroup walks its chunk of the scores and derives
+// the prefix again from the finished histograms instead of reading it from a single writer; the last counting pass leaves
+// the histogram of every chunk, from which the writing pass takes the number of threshold keys in the chunks before.
+#define PC_TOPN_CHUNKS 1024     // at most so many chunks
+#define PC_TOPN_BINS 2048
+struct TopnState { uint32_t prefix; int rem, count; };   // count: keys that share the prefix
+
+// UPTO finished passes; their histograms are requested together. The caller's next LDS use of part and dig needs no barrier.
+template <int UPTO>
+__device__ __forceinline__ TopnState pc_topn_replay(const uint32_t *__restrict__ hist, int n_keep, int *part, int *dig)
 {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) state[i] = 0u;
+    TopnState s = {0u, n_keep, 0};
+    uint32_t h[UPTO > 0 ? UPTO : 1][PC_TOPN_BINS / 256];
+#pragma unroll
+    for (int q = 0; q < UPTO; ++q) {
+        const uint4 *src = reinterpret_cast<const uint4 *>(hist + q * PC_TOPN_BINS) + threadIdx.x * 2;
+        const uint4 a = src[0], b = src[1];
+        h[q][0] = a.x; h[q][1] = a.y; h[q][2] = a.z; h[q][3] = a.w;
+        h[q][4] = b.x; h[q][5] = b.y; h[q][6] = b.z; h[q][7] = b.w;
+    }
+#pragma unroll
+    for (int q = 0; q < UPTO; ++q) {
+        pc_topn_digit<256, PC_TOPN_BINS / 256>(h[q], s.rem, part, dig);
+        s.prefix |= (uint32_t)dig[0] << (q == 0 ? 21 : q == 1 ? 10 : 0);
+        s.rem -= dig[1];
+        s.count = dig[2];
+        __syncthreads();
+    }
+    return s;
 }
 
+template <int PASS>
 __global__ void __launch_bounds__(256)
-pc_topn_hist_kernel(const float *__restrict__ R, int64_t L, int n_keep, uint32_t *__restrict__ hist_all, int pass)
+pc_topn_hist_kernel(const float *__restrict__ R, int64_t L, int64_t chunk, int n_keep, uint32_t *__restrict__ hist,
+                    uint32_t *__restrict__ chunk_hist)
 {
-    __shared__ int lh[256];
-    __shared__ uint32_t s_prefix;
-    __shared__ int s_rem;
-    const float *seg = R + (int64_t)blockIdx.y * L;
-    uint32_t *hist = hist_all + (int64_t)blockIdx.y * 1024;
-    lh[threadIdx.x] = 0;
-    pc_topn_replay(hist, pass, n_keep, &s_prefix, &s_rem);
-    const uint32_t prefix = s_prefix;
-    const int shift = 24 - 8 * pass;
-    const uint32_t himask = pass == 0 ? 0u : 0xFFFFFFFFu << (shift + 8);
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < L; i += (int64_t)gridDim.x * 256) {
-        const uint32_t k = pc_order_key(seg[i]);
-        if ((k & himask) == prefix) atomicAdd(&lh[(k >> shift) & 255u], 1);
+    constexpr int SHIFT = PASS == 0 ? 21 : PASS == 1 ? 10 : 0, BINS = PASS == 2 ? 1024 : PC_TOPN_BINS;
+    constexpr uint32_t HIMASK = PASS == 0 ? 0u : PASS == 1 ? 0xFFFFFFFFu << 21 : 0xFFFFFFFFu << 10;
+    __shared__ uint32_t lh[BINS];
+    __shared__ int part[4], dig[3];
+    const int tid = threadIdx.x;
+    const int64_t i0 = (int64_t)blockIdx.x * chunk, i1 = i0 + chunk < L ? i0 + chunk : L;
+    float r[4];                                 // the next 1024 scores, on their way during the replay
+    auto load = [&](int64_t j0) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) r[j] = R[j0 + j * 256 + tid < i1 ? j0 + j * 256 + tid : i1 - 1];
+    };
+    load(i0);
+    for (int i = tid; i < BINS; i += 256) lh[i] = 0u;
+    const TopnState s = pc_topn_replay<PASS>(hist, n_keep, part, dig);
+    __syncthreads();
+    for (int64_t j0 = i0; j0 < i1; j0 += 1024) {
+        uint32_t k[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) k[j] = pc_order_key(r[j]);
+        if (j0 + 1024 < i1) load(j0 + 1024);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (j0 + j * 256 + tid < i1 && (k[j] & HIMASK) == s.prefix) atomicAdd(&lh[(k[j] >> SHIFT) & (uint32_t)(BINS - 1)], 1u);
     }
     __syncthreads();
-    if (lh[threadIdx.x]) atomicAdd(&hist[pass * 256 + threadIdx.x], (uint32_t)lh[threadIdx.x]);   // integers: order-free
+    for (int i = tid; i < BINS; i += 256) {
+        const uint32_t c = lh[i];
+        if (c) atomicAdd(&hist[PASS * PC_TOPN_BINS + i], c);   // integers: order-free
+        if (PASS == 2) chunk_hist[(int64_t)blockIdx.x * 1024 + i] = c;
+    }
 }
 
-// Scores equal to the threshold in every chunk of PC_TOPN_CHUNK scores.
+// keep = 1 for scores above the threshold and for the first of the scores equal to it (by index).
 __global__ void __launch_bounds__(256)
-pc_topn_count_equal_kernel(const float *__restrict__ R, int64_t L, int n_keep, const uint32_t *__restrict__ hist_all,
-                           uint32_t *__restrict__ blk_eq, int nchunks)
+pc_topn_write_kernel(const float *__restrict__ R, int64_t L, int64_t chunk, int n_keep, const uint32_t *__restrict__ hist,
+                     const uint32_t *__restrict__ chunk_hist, uint8_t *__restrict__ keep)
 {
-    __shared__ uint32_t s_prefix;
-    __shared__ int s_rem, s_cnt[4];
-    const float *seg = R + (int64_t)blockIdx.y * L;
-    pc_topn_replay(hist_all + (int64_t)blockIdx.y * 1024, 4, n_keep, &s_prefix, &s_rem);
-    const uint32_t T = s_prefix;
-    const int64_t i0 = (int64_t)blockIdx.x * PC_TOPN_CHUNK;
-    int cnt = 0;
-    for (int j = threadIdx.x; j < PC_TOPN_CHUNK; j += 256)
-        if (i0 + j < L && pc_order_key(seg[i0 + j]) == T) ++cnt;
-    for (int off = 32; off > 0; off >>= 1) cnt += __shfl_down(cnt, off);
-    if ((threadIdx.x & 63) == 0) s_cnt[threadIdx.x >> 6] = cnt;
-    __syncthreads();
-    if (threadIdx.x == 0) blk_eq[(int64_t)blockIdx.y * nchunks + blockIdx.x] = (uint32_t)(s_cnt[0] + s_cnt[1] + s_cnt[2] + s_cnt[3]);
-}
-
-// In-place exclusive scan of the chunk counts of every segment (one workgroup per segment).
-__global__ void __launch_bounds__(256) pc_topn_scan_kernel(uint32_t *__restrict__ blk_eq, int nchunks)
-{
-    __shared__ uint32_t part[256];
-    uint32_t *v = blk_eq + (int64_t)blockIdx.x * nchunks;
-    const int per = (nchunks + 255) / 256;
-    const int lo = threadIdx.x * per, hi = lo + per < nchunks ? lo + per : nchunks;
-    uint32_t sum = 0;
-    for (int i = lo; i < hi; ++i) sum += v[i];
-    part[threadIdx.x] = sum;
-    __syncthreads();
-    for (int d = 1; d < 256; d <<= 1) {
-        const uint32_t add = threadIdx.x >= d ? part[threadIdx.x - d] : 0u;
-        __syncthreads();
-        part[threadIdx.x] += add;
-        __syncthreads();
+    __shared__ int part[4], dig[3], s_base;
+    const int tid = threadIdx.x;
+    const int64_t i0 = (int64_t)blockIdx.x * chunk, i1 = i0 + chunk < L ? i0 + chunk : L;
+    float r[4];
+    auto load = [&](int64_t j0) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) r[j] = R[j0 + j * 256 + tid < i1 ? j0 + j * 256 + tid : i1 - 1];
+    };
+    load(i0);
+    const TopnState s = pc_topn_replay<3>(hist, n_keep, part, dig);
+    if (s.count == s.rem) {                     // all scores equal to the threshold are kept
+        for (int64_t j0 = i0; j0 < i1; j0 += 1024) {
+            uint8_t q[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) q[j] = pc_order_key(r[j]) >= s.prefix ? 1 : 0;
+            if (j0 + 1024 < i1) load(j0 + 1024);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (j0 + j * 256 + tid < i1) keep[j0 + j * 256 + tid] = q[j];
+        }
+        return;
     }
-    uint32_t run = part[threadIdx.x] - sum;
-    for (int i = lo; i < hi; ++i) {
-        const uint32_t c = v[i];
-        v[i] = run;
-        run += c;
-    }
-}
-
-// keep = 1 for scores above the threshold and for the first take_equal scores equal to it (by index).
-__global__ void __launch_bounds__(256)
-pc_topn_write_kernel(const float *__restrict__ R, int64_t L, int n_keep, const uint32_t *__restrict__ hist_all,
-                     const uint32_t *__restrict__ blk_excl, int nchunks, uint8_t *__restrict__ keep)
-{
-    __shared__ uint32_t s_prefix;
-    __shared__ int s_rem, s_wave_cnt[4];
-    const float *seg = R + (int64_t)blockIdx.y * L;
-    uint8_t *out = keep + (int64_t)blockIdx.y * L;
-    pc_topn_replay(hist_all + (int64_t)blockIdx.y * 1024, 4, n_keep, &s_prefix, &s_rem);
-    const uint32_t T = s_prefix;
-    const int take_equal = s_rem;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int base = (int)blk_excl[(int64_t)blockIdx.y * nchunks + blockIdx.x];
-    const int64_t i0 = (int64_t)blockIdx.x * PC_TOPN_CHUNK;
-    for (int j0 = 0; j0 < PC_TOPN_CHUNK; j0 += 256) {
-        const int64_t i = i0 + j0 + threadIdx.x;
-        const uint32_t k = i < L ? pc_order_key(seg[i]) : 0u;
-        const bool eq = i < L && k == T;
-        const unsigned long long b = __ballot(eq);
-        if (lane == 0) s_wave_cnt[wave] = __popcll(b);
-        __syncthreads();
-        int before = base + __popcll(b & ((1ull << lane) - 1ull));
-        for (int w2 = 0; w2 < wave; ++w2) before += s_wave_cnt[w2];
-        if (i < L) out[i] = (k > T || (eq && before < take_equal)) ? 1 : 0;
-        base += s_wave_cnt[0] + s_wave_cnt[1] + s_wave_cnt[2] + s_wave_cnt[3];
-        __syncthreads();
+    if (tid == 0) s_base = 0;
+    __syncthreads();
+    int before_chunk = 0;
+    for (int c = tid; c < (int)blockIdx.x; c += 256) before_chunk += (int)chunk_hist[(int64_t)c * 1024 + (s.prefix & 1023u)];
+    if (before_chunk) atomicAdd(&s_base, before_chunk);
+    __syncthreads();
+    int base = s_base;
+    for (int64_t j0 = i0; j0 < i1; j0 += 256) {
+        const int64_t i = j0 + tid;
+        const uint32_t k = i < i1 ? pc_order_key(R[i]) : 0u;
+        const bool eq = i < i1 && k == s.prefix;
+        int total;
+        const int before = base + pc_block_rank(eq, part, 4, &total);
+        if (i < i1) keep[i] = (k > s.prefix || (eq && before < s.rem)) ? 1 : 0;
+        base += total;
     }
 }
 
@@ -437,88 +432,75 @@ __global__ void __launch_bounds__(256) pc_fill_u8_kernel(uint8_t *__restrict__ p
     if (i < n) p[i] = v;
 }
 
-pc_status pc_launch_select(pc_ctx *ctx, const float *W, const float *G, int F, int C, const LibArg &la,
-                           pc_keep_mode km, int64_t n_keep, pc_score_mode sm, uint8_t *pid, uint8_t *keep)
+// Rows of at most PC_ROW_MAX kernels: a wavefront per row where the launch has at least this many rows per CU, so that the
+// wavefronts fill the chip; fewer rows get a workgroup each.
+#define PC_ROWS_PER_CU 8
+static pc_status pc_launch_rows(pc_ctx *ctx, SelBatchArg *b, int cmax, const LibArg &la)
 {
-    int64_t nk = (int64_t)F * C;
-    if (km == PC_KEEP_PER_FILTER && C <= PC_TOPN_MAX) {
-        const int T = C <= 256 ? 256 : 512;
-        const size_t lds = sizeof(uint32_t) * (size_t)C + 2 * sizeof(float) * 9 * (size_t)T;   // at most 68 KiB
-        static pc_per_device_once attr;
-        if (pc_once_pending(attr, ctx->device)) {
-            PC_HIP(ctx, hipFuncSetAttribute((const void *)pc_select_row_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                            (int)(sizeof(uint32_t) * PC_TOPN_MAX + 2 * sizeof(float) * 9 * 512)));
-            pc_once_done(attr, ctx->device);
-        }
-        const int nk_row = (int)(n_keep < C ? n_keep : C);
-        hipLaunchKernelGGL(pc_select_row_kernel, dim3((unsigned)F), dim3((unsigned)T), lds, ctx->stream, W, G, C, la, (int)sm,
-                           nk_row, pid, keep);
-        return pc_hip_check(ctx, hipGetLastError(), "select launch");
-    }
+    if (b->n == 0) return PC_OK;
+    const unsigned rows = (unsigned)b->row0[b->n];
+    if (rows >= (unsigned)(PC_ROWS_PER_CU * ctx->num_cu))
+        hipLaunchKernelGGL(pc_select_rows_kernel<true>, dim3(rows), dim3(64), 0, ctx->stream, *b, la);
+    else
+        hipLaunchKernelGGL(pc_select_rows_kernel<false>, dim3(rows), dim3((unsigned)((cmax + 63) / 64 * 64)), 0, ctx->stream, *b, la);
+    b->n = 0;
+    return pc_hip_check(ctx, hipGetLastError(), "select launch");
+}
+
+// Rows longer than PC_ROW_MAX, and layers ranked as a whole: scores to memory, then the ranking of every segment.
+static pc_status pc_launch_select_segments(pc_ctx *ctx, const float *W, const float *G, int F, int C, const LibArg &la,
+                                           pc_keep_mode km, int64_t n_keep, pc_score_mode sm, uint8_t *pid, uint8_t *keep)
+{
+    const int64_t nk = (int64_t)F * C;
     const int64_t L = (km == PC_KEEP_PER_FILTER) ? C : nk;
     const unsigned nseg = (km == PC_KEEP_PER_FILTER) ? (unsigned)F : 1u;
     if (L >= ((int64_t)1 << 31)) return pc_fail(ctx, PC_ERR_UNSUPPORTED, "select: %lld scores in one segment (limit 2^31 - 1)", (long long)L);
-    const int nchunks = (int)((L + PC_TOPN_CHUNK - 1) / PC_TOPN_CHUNK);
+    // one workgroup per segment while it holds the keys in few registers, and for every row (65535 kernels at most)
+    const bool rank = n_keep > 0 && n_keep < L, across = rank && km != PC_KEEP_PER_FILTER && L > PC_TOPN_WG;
+    int64_t chunk = (L + PC_TOPN_CHUNKS - 1) / PC_TOPN_CHUNKS;
+    chunk = chunk < 1024 ? 1024 : (chunk + 255) / 256 * 256;
+    const unsigned nchunks = (unsigned)((L + chunk - 1) / chunk);
     const size_t r_bytes = (sizeof(float) * (size_t)nk + 255) / 256 * 256;
-    const size_t state_words = L > PC_TOPN_MAX ? (size_t)nseg * (1024 + (size_t)nchunks) : 0;
+    const int nzero = across ? 3 * PC_TOPN_BINS : 0;
     void *scr = nullptr;
-    pc_status s = pc_scratch(ctx, r_bytes + sizeof(uint32_t) * state_words, &scr);
+    pc_status s = pc_scratch(ctx, r_bytes + (across ? sizeof(uint32_t) * ((size_t)nzero + 1024 * (size_t)nchunks) : 0), &scr);
     if (s != PC_OK) return s;
     float *R = (float *)scr;
-    unsigned blocks = (unsigned)((nk + 255) / 256);
-    hipLaunchKernelGGL(pc_select_score_kernel, dim3(blocks), dim3(256), 0, ctx->stream, W, G, nk, la, (int)sm, pid, R);
-    if (L <= PC_TOPN_MAX) {
-        hipLaunchKernelGGL(pc_select_topn_row_kernel, dim3(nseg), dim3(256), sizeof(uint32_t) * (size_t)L, ctx->stream, R, (int)L,
-                           (int)(n_keep < L ? n_keep : L), keep);
-    } else if (n_keep <= 0 || n_keep >= L) {
+    uint32_t *hist = reinterpret_cast<uint32_t *>(static_cast<unsigned char *>(scr) + r_bytes), *chunk_hist = hist + nzero;
+    const unsigned blocks = (unsigned)((nk + 255) / 256);
+    hipLaunchKernelGGL(pc_select_score_kernel, dim3(blocks), dim3(256), 0, ctx->stream, W, G, nk, la, (int)sm, pid, R, hist, nzero);
+    if (!rank) {
         hipLaunchKernelGGL(pc_fill_u8_kernel, dim3(blocks), dim3(256), 0, ctx->stream, keep, nk, (uint8_t)(n_keep > 0 ? 1 : 0));
+    } else if (!across) {
+        const int n = (int)n_keep, Li = (int)L;
+        if (L <= 4096)
+            hipLaunchKernelGGL(pc_topn_wg_kernel<4>, dim3(nseg), dim3(1024), 0, ctx->stream, R, Li, n, keep);
+        else if (L <= 16384)
+            hipLaunchKernelGGL(pc_topn_wg_kernel<16>, dim3(nseg), dim3(1024), 0, ctx->stream, R, Li, n, keep);
+        else
+            hipLaunchKernelGGL(pc_topn_wg_kernel<64>, dim3(nseg), dim3(1024), 0, ctx->stream, R, Li, n, keep);
     } else {
-        uint32_t *hist = reinterpret_cast<uint32_t *>(static_cast<unsigned char *>(scr) + r_bytes);
-        uint32_t *blk_eq = hist + (size_t)nseg * 1024;
-        hipLaunchKernelGGL(pc_topn_zero_kernel, dim3((unsigned)((nseg * 1024 + 255) / 256)), dim3(256), 0, ctx->stream, hist,
-                           (int64_t)nseg * 1024);
-        int hb = (int)((L + 255) / 256);
-        const int hb_max = nseg >= 64 ? 8 : 4 * ctx->num_cu;     // workgroups per segment in the counting passes
-        if (hb > hb_max) hb = hb_max;
-        for (int pass = 0; pass < 4; ++pass)
-            hipLaunchKernelGGL(pc_topn_hist_kernel, dim3((unsigned)hb, nseg), dim3(256), 0, ctx->stream, R, L, (int)n_keep, hist, pass);
-        hipLaunchKernelGGL(pc_topn_count_equal_kernel, dim3((unsigned)nchunks, nseg), dim3(256), 0, ctx->stream, R, L, (int)n_keep,
-                           hist, blk_eq, nchunks);
-        hipLaunchKernelGGL(pc_topn_scan_kernel, dim3(nseg), dim3(256), 0, ctx->stream, blk_eq, nchunks);
-        hipLaunchKernelGGL(pc_topn_write_kernel, dim3((unsigned)nchunks, nseg), dim3(256), 0, ctx->stream, R, L, (int)n_keep, hist,
-                           blk_eq, nchunks, keep);
+        hipLaunchKernelGGL(pc_topn_hist_kernel<0>, dim3(nchunks), dim3(256), 0, ctx->stream, R, L, chunk, (int)n_keep, hist, chunk_hist);
+        hipLaunchKernelGGL(pc_topn_hist_kernel<1>, dim3(nchunks), dim3(256), 0, ctx->stream, R, L, chunk, (int)n_keep, hist, chunk_hist);
+        hipLaunchKernelGGL(pc_topn_hist_kernel<2>, dim3(nchunks), dim3(256), 0, ctx->stream, R, L, chunk, (int)n_keep, hist, chunk_hist);
+        hipLaunchKernelGGL(pc_topn_write_kernel, dim3(nchunks), dim3(256), 0, ctx->stream, R, L, chunk, (int)n_keep, hist, chunk_hist, keep);
     }
     return pc_hip_check(ctx, hipGetLastError(), "select launch");
 }
 
-// Layers whose rows fit the one-workgroup kernel go into launches of up to PC_BATCH_MAX layers; the others are
-// served one by one by pc_launch_select.
+// Layers whose rows are ranked in registers go into launches of up to PC_BATCH_MAX layers, the others one by one.
 pc_status pc_launch_select_batch(pc_ctx *ctx, int n, const float *const *W, const float *const *G, const int32_t *F,
                                  const int32_t *C, const LibArg &la, pc_keep_mode km, const int64_t *n_keep, pc_score_mode sm,
                                  uint8_t *const *pid, uint8_t *const *keep)
 {
-    static pc_per_device_once attr;
-    if (pc_once_pending(attr, ctx->device)) {
-        PC_HIP(ctx, hipFuncSetAttribute((const void *)pc_select_rows_batch_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                        (int)(sizeof(uint32_t) * PC_TOPN_MAX + 2 * sizeof(float) * 9 * 512)));
-        pc_once_done(attr, ctx->device);
-    }
     SelBatchArg b;
     memset(&b, 0, sizeof(b));
     b.score_mode = (int)sm;
     int cmax = 0;
-    auto flush = [&]() -> pc_status {
-        if (b.n == 0) return PC_OK;
-        const int T = cmax <= 256 ? 256 : 512;
-        const size_t lds = sizeof(uint32_t) * (size_t)cmax + 2 * sizeof(float) * 9 * (size_t)T;
-        hipLaunchKernelGGL(pc_select_rows_batch_kernel, dim3((unsigned)b.row0[b.n]), dim3((unsigned)T), lds, ctx->stream, b, la);
-        b.n = 0;
-        cmax = 0;
-        return pc_hip_check(ctx, hipGetLastError(), "select (several layers) launch");
-    };
     for (int l = 0; l < n; ++l) {
-        if (km != PC_KEEP_PER_FILTER || C[l] > PC_TOPN_MAX) {
-            pc_status s = pc_launch_select(ctx, W[l], G ? G[l] : nullptr, F[l], C[l], la, km, n_keep[l], sm, pid[l], keep[l]);
+        pc_status s = PC_OK;
+        if (km != PC_KEEP_PER_FILTER || C[l] > PC_ROW_MAX) {
+            s = pc_launch_select_segments(ctx, W[l], G ? G[l] : nullptr, F[l], C[l], la, km, n_keep[l], sm, pid[l], keep[l]);
             if (s != PC_OK) return s;
             continue;
         }
@@ -529,11 +511,18 @@ pc_status pc_launch_select_batch(pc_ctx *ctx, int n, const float *const *W, cons
         b.row0[i + 1] = b.row0[i] + F[l];
         if (C[l] > cmax) cmax = C[l];
         if (++b.n == PC_BATCH_MAX) {
-            pc_status s = flush();
+            s = pc_launch_rows(ctx, &b, cmax, la);
             if (s != PC_OK) return s;
+            cmax = 0;
         }
     }
-    return flush();
+    return pc_launch_rows(ctx, &b, cmax, la);
+}
+
+pc_status pc_launch_select(pc_ctx *ctx, const float *W, const float *G, int F, int C, const LibArg &la,
+                           pc_keep_mode km, int64_t n_keep, pc_score_mode sm, uint8_t *pid, uint8_t *keep)
+{
+    return pc_launch_select_batch(ctx, 1, &W, &G, &F, &C, la, km, &n_keep, sm, &pid, &keep);
 }
 
 // ------------------------------------------------------------------ packing
@@ -544,27 +533,32 @@ pc_status pc_launch_select_batch(pc_ctx *ctx, int n, const float *const *W, cons
 // matrix-core variant, writes the operand tiles (they depend on W and the masks only). The second places the
 // kernels: every workgroup adds up the totals of the rows before its own, so no separate scan is needed.
 
-// Kept kernels of one row, per pattern id, and their total.
-__device__ __forceinline__ void pc_pack_count_row(const uint8_t *__restrict__ pid, const uint8_t *__restrict__ keep, int row,
-                                                  int len, int64_t row_stride, int64_t elem_stride, int P,
-                                                  int32_t *__restrict__ grp, int32_t *__restrict__ rowtot)
+// Kept kernels per pattern id, and their total, of PC_PACK_ROWS rows by one workgroup: a wavefront per row.
+#define PC_PACK_ROWS 4
+__device__ __forceinline__ void pc_pack_count_rows(const uint8_t *__restrict__ pid, const uint8_t *__restrict__ keep, int row0, int rows,
+                                                   int len, int64_t row_stride, int64_t elem_stride, int P,
+                                                   int32_t *__restrict__ grp, int32_t *__restrict__ rowtot)
 {
-    __shared__ int hist[PC_MAX_P + 1];
-    for (int p = threadIdx.x; p <= PC_MAX_P; p += blockDim.x) hist[p] = 0;
+    __shared__ int hist_all[PC_PACK_ROWS][128];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, row = row0 + wave;
+    int *hist = hist_all[wave];
+    hist[lane] = 0;
+    hist[lane + 64] = 0;
     __syncthreads();
-    for (int e = threadIdx.x; e < len; e += blockDim.x) {
-        int64_t k = row * row_stride + e * elem_stride;
-        const int kp = keep[k], pd = pid[k];                      // both loads at once, not one behind the other
-        if (kp && pd < P) atomicAdd(&hist[pd], 1);                // integer counts: order does not matter
-    }
-    __syncthreads();
-    for (int p = threadIdx.x; p < P; p += blockDim.x) grp[(int64_t)row * (PC_MAX_P + 1) + p] = hist[p];
-    if (threadIdx.x < 64) {
+    if (row < rows) {
         int tot = 0;
-        for (int p = threadIdx.x; p < P; p += 64) tot += hist[p];
+#pragma unroll 4
+        for (int e = lane; e < len; e += 64) {
+            const int64_t k = row * row_stride + e * elem_stride;
+            const int kp = keep[k], pd = pid[k];                  // both loads at once, not one behind the other
+            if (kp && pd < P) { atomicAdd(&hist[pd], 1); ++tot; } // integer counts: order does not matter
+        }
         for (int off = 32; off > 0; off >>= 1) tot += __shfl_down(tot, off);
-        if (threadIdx.x == 0) rowtot[row] = tot;
+        if (lane == 0) rowtot[row] = tot;
     }
+    __syncthreads();
+    if (row < rows)
+        for (int p = lane; p < P; p += 64) grp[(int64_t)row * (PC_MAX_P + 1) + p] = hist[p];
 }
 
 // Operand tiles of one 32-filter x 32-channel block, all 9 taps.
@@ -635,6 +629,41 @@ __device__ __forceinline__ unsigned char *pc_tile_lds()
     return buf;
 }
 
+// The 4 kernels of a 32 x 32 block that a thread brings to LDS: channel cl, filters r0 .. r0 + 3 of the block. Every thread
+// loads the 9 weights of its own kernels (the 9 loads of 64 neighbours touch the same 18 cache lines), so the pattern mask
+// is looked up once per kernel and no element index is divided: with contiguous loads and a mask test per element the two
+// launches that build tiles took 36 us (pack) and 51 us (value update) for the 1.6 M kernels of the largest networks.
+// Kernels outside the layer get mask 0. All loads are unconditional and issued before the first use.
+struct PackTileRegs { unsigned m[4]; float w[4][9]; };
+template <bool FROM_KINFO>
+__device__ __forceinline__ void pc_pack_tile_load(const float *__restrict__ W, const uint8_t *__restrict__ pid,
+                                                  const uint8_t *__restrict__ keep, const LibArg &la, const PackView &v, int fb, int cb,
+                                                  PackTileRegs &t)
+{
+    __shared__ uint16_t lm[PC_MAX_P + 2];         // the pool's masks
+    const int tid = threadIdx.x, cl = tid & 31, r0 = 4 * (tid >> 5), c = cb * 32 + cl;
+    if (!FROM_KINFO && tid < la.P) lm[tid] = la.mask[tid];
+    int kp[4], pd[4];
+    uint32_t u[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int f = fb * 32 + r0 + i;
+        const bool in = f < v.F && c < v.C;
+        const int64_t k = in ? (int64_t)f * v.C + c : 0;
+        if (FROM_KINFO) u[i] = v.kinfo[k];
+        else { kp[i] = keep[k]; pd[i] = pid[k]; }
+#pragma unroll
+        for (int j = 0; j < 9; ++j) t.w[i][j] = W[k * 9 + j];
+    }
+    if (!FROM_KINFO) __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const bool in = fb * 32 + r0 + i < v.F && c < v.C;
+        if (FROM_KINFO) t.m[i] = in && u[i] != 0xFFFFFFFFu ? u[i] & 511u : 0u;
+        else t.m[i] = in && kp[i] && pd[i] < la.P ? lm[pd[i]] : 0u;
+    }
+}
+
 // The float32 form: [row tile][tap][entry / 8][lane][4], lane l of a fragment holds row l % 32 and entries
 // 4 * (l / 32) .. + 3. The block's weights are masked into LDS as they lie in W and read in both orientations.
 template <bool FROM_KINFO>
@@ -644,33 +673,13 @@ __device__ __forceinline__ void pc_pack_tile_block_f32(const float *__restrict__
 {
     constexpr int PITCH = 289;                    // odd: rows and columns spread over the banks
     float *tw = reinterpret_cast<float *>(pc_tile_lds());
-    __shared__ uint16_t tm[32][32];
-    const int tid = threadIdx.x, f0 = fb * 32, c0 = cb * 32;
+    const int tid = threadIdx.x, cl = tid & 31, r0 = 4 * (tid >> 5);
+    PackTileRegs t;
+    pc_pack_tile_load<FROM_KINFO>(W, pid, keep, la, v, fb, cb, t);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int i = j * 256 + tid, f = f0 + (i >> 5), c = c0 + (i & 31);
-        unsigned m = 0;
-        if (f < v.F && c < v.C) {
-            const int64_t k = (int64_t)f * v.C + c;
-            if (FROM_KINFO) {
-                const uint32_t u = v.kinfo[k];
-                m = u == 0xFFFFFFFFu ? 0u : (u & 511u);
-            } else {
-                const int kp = keep[k], pd = pid[k];
-                m = kp && pd < la.P ? la.mask[pd] : 0u;
-            }
-        }
-        tm[i >> 5][i & 31] = (uint16_t)m;
-    }
-    __syncthreads();
-    const int ncols = v.C - c0 < 32 ? v.C - c0 : 32, nrows = v.F - f0 < 32 ? v.F - f0 : 32;
-#pragma unroll 4
-    for (int i = tid; i < 32 * 288; i += 256) {
-        const int r = i / 288, j = i - r * 288, cl = j / 9, tap = j - cl * 9;
-        const bool in = r < nrows && cl < ncols;
-        const float w = W[in ? ((int64_t)(f0 + r) * v.C + c0) * 9 + j : 0];
-        tw[r * PITCH + j] = in && ((tm[r][cl] >> tap) & 1u) ? w : 0.0f;
-    }
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 9; ++j) tw[(r0 + i) * PITCH + cl * 9 + j] = ((t.m[i] >> j) & 1u) ? t.w[i][j] : 0.0f;
     __syncthreads();
     const int KSf = v.Ck / 8, KSb = v.Fk / 8;
     float4 *of = reinterpret_cast<float4 *>(v.wz_fwd), *ob = reinterpret_cast<float4 *>(v.wz_bwd);
@@ -679,8 +688,8 @@ __device__ __forceinline__ void pc_pack_tile_block_f32(const float *__restrict__
         const int row = lane & 31, e = ks * 8 + 4 * (lane >> 5);
         const float *p = tw + row * PITCH + e * 9 + tap;
         of[((int64_t)(fb * 9 + tap) * KSf + cb * 4 + ks) * 64 + lane] = make_float4(p[0], p[9], p[18], p[27]);
-        const float *t = tw + e * PITCH + row * 9 + tap;
-        ob[((int64_t)(cb * 9 + tap) * KSb + fb * 4 + ks) * 64 + lane] = make_float4(t[0], t[PITCH], t[2 * PITCH], t[3 * PITCH]);
+        const float *s = tw + e * PITCH + row * 9 + tap;
+        ob[((int64_t)(cb * 9 + tap) * KSb + fb * 4 + ks) * 64 + lane] = make_float4(s[0], s[PITCH], s[2 * PITCH], s[3 * PITCH]);
     }
 }
 
@@ -692,73 +701,20 @@ __device__ __forceinline__ void pc_pack_tile_block(const float *__restrict__ W, 
     if (v.f32) return pc_pack_tile_block_f32<FROM_KINFO>(W, pid, keep, la, v, fb, cb);
     uint16_t (*tA)[32][PC_TILE_PITCH] = reinterpret_cast<uint16_t (*)[32][PC_TILE_PITCH]>(pc_tile_lds());   // [tap][filter][channel]
     uint16_t (*tB)[32][PC_TILE_PITCH] = tA + 9;                   // [tap][channel][filter]
-    __shared__ uint16_t tm[32][32];                               // pattern mask of kernel (f,c), 0 = pruned / outside
-    __shared__ uint16_t lm[PC_MAX_P + 2];                         // the pool's masks
-    const int tid = threadIdx.x, f0 = fb * 32, c0 = cb * 32;
-    if (!FROM_KINFO) {
-        if (tid < la.P) lm[tid] = la.mask[tid];
-        uint8_t kp[4], pd[4];
+    const int tid = threadIdx.x, cl = tid & 31, r0 = 4 * (tid >> 5);
+    PackTileRegs t;
+    pc_pack_tile_load<FROM_KINFO>(W, pid, keep, la, v, fb, cb, t);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int i = j * 256 + tid, f = f0 + (i >> 5), c = c0 + (i & 31);
-            const bool in = f < v.F && c < v.C;
-            const int64_t k = in ? (int64_t)f * v.C + c : 0;
-            kp[j] = in ? keep[k] : (uint8_t)0;
-            pd[j] = pid[k];
-        }
-        __syncthreads();
+    for (int j = 0; j < 9; ++j) {
+        uint32_t pr[2];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int i = j * 256 + tid;
-            tm[i >> 5][i & 31] = (kp[j] && pd[j] < la.P) ? lm[pd[j]] : (uint16_t)0;
+        for (int h = 0; h < 2; ++h) {             // filters r0 + 2h (low half) and r0 + 2h + 1
+            const uint32_t lo = (uint32_t)-(int)((t.m[2 * h] >> j) & 1u), hi = (uint32_t)-(int)((t.m[2 * h + 1] >> j) & 1u);
+            pr[h] = pc_pack_bf16x2(t.w[2 * h][j], t.w[2 * h + 1][j]) & ((lo & 0xFFFFu) | (hi & 0xFFFF0000u));
+            tA[j][r0 + 2 * h][cl] = (uint16_t)pr[h];
+            tA[j][r0 + 2 * h + 1][cl] = (uint16_t)(pr[h] >> 16);
         }
-    } else {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int i = j * 256 + tid, f = f0 + (i >> 5), c = c0 + (i & 31);
-            uint32_t u = 0xFFFFFFFFu;
-            if (f < v.F && c < v.C) u = v.kinfo[(int64_t)f * v.C + c];
-            tm[i >> 5][i & 31] = u == 0xFFFFFFFFu ? (uint16_t)0 : (uint16_t)(u & 511u);
-        }
-    }
-    __syncthreads();
-    const int ncols = v.C - c0 < 32 ? (v.C - c0 > 0 ? v.C - c0 : 0) : 32;
-    if ((v.C & 3) == 0 && (reinterpret_cast<uintptr_t>(W) & 15) == 0) {
-        // a filter row of the block is ncols*9 contiguous floats starting on a 16-byte boundary
-        const int nq = ncols * 9 / 4;
-        // all 9 loads of the thread are issued before the first value is used: one memory round trip, not nine
-        float4 wq[9];
-#pragma unroll
-        for (int it = 0; it < 9; ++it) {
-            const int q = it * 256 + tid;            // 32 rows x 72 quads
-            const int r = q / 72, jq = q - r * 72;
-            wq[it] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (f0 + r < v.F && jq < nq)
-                wq[it] = *reinterpret_cast<const float4 *>(W + ((int64_t)(f0 + r) * v.C + c0) * 9 + jq * 4);
-        }
-#pragma unroll
-        for (int it = 0; it < 9; ++it) {
-            const int q = it * 256 + tid;
-            const int r = q / 72, jq = q - r * 72;
-            const float4 w4 = wq[it];
-            const float wv[4] = {w4.x, w4.y, w4.z, w4.w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int j = jq * 4 + e, cl = j / 9, tap = j - cl * 9;
-                const uint16_t val = ((tm[r][cl] >> tap) & 1u) ? pc_f32_to_bf16(wv[e]) : (uint16_t)0;
-                tA[tap][r][cl] = val;
-                tB[tap][cl][r] = val;
-            }
-        }
-    } else {
-        for (int idx = tid; idx < 32 * 288; idx += 256) {
-            const int r = idx / 288, j = idx - r * 288, cl = j / 9, tap = j - cl * 9;
-            uint16_t val = 0;
-            if (f0 + r < v.F && cl < ncols && ((tm[r][cl] >> tap) & 1u))
-                val = pc_f32_to_bf16(W[((int64_t)(f0 + r) * v.C + c0 + cl) * 9 + tap]);
-            tA[tap][r][cl] = val;
-            tB[tap][cl][r] = val;
-        }
+        *reinterpret_cast<uint2 *>(&tB[j][cl][r0]) = make_uint2(pr[0], pr[1]);
     }
     __shared__ uint32_t lflag[2];
     __shared__ uint32_t ocnt[2];                     // overflow weights of this block, forward / backward-data orientation
@@ -883,19 +839,21 @@ __device__ __forceinline__ void pc_pack_ovf_merge_body(const PackView &v, int li
 __global__ void __launch_bounds__(64) pc_pack_ovf_merge_kernel(PackView v) { pc_pack_ovf_merge_body(v, (int)blockIdx.x); }
 
 
-// First launch of a pack: workgroups [0, F) count the filter rows, [F, F + ncm) the channel rows (ncm = C for the
-// gather variant, else 0), the rest write the operand tiles (matrix-core variant), one 32 x 32 block each.
+// First launch of a pack: the first workgroups count the filter rows, the next ncm the channel rows (gather variant, else
+// none), the rest write the operand tiles (matrix-core variant), one 32 x 32 block each.
+static int pc_pack_row_wgs(int rows) { return (rows + PC_PACK_ROWS - 1) / PC_PACK_ROWS; }
 __device__ __forceinline__ void pc_pack_stage1_body(const float *__restrict__ W, const uint8_t *__restrict__ pid,
                                                     const uint8_t *__restrict__ keep, const LibArg &la, const PackView &v, int ncm,
                                                     int tiles_c, int b)
 {
-    if (b < v.F) {
-        pc_pack_count_row(pid, keep, b, v.C, (int64_t)v.C, 1, v.P, v.fm_grp, v.fm_rowtot);
+    const int nfm = (v.F + PC_PACK_ROWS - 1) / PC_PACK_ROWS;
+    if (b < nfm) {
+        pc_pack_count_rows(pid, keep, b * PC_PACK_ROWS, v.F, v.C, (int64_t)v.C, 1, la.P, v.fm_grp, v.fm_rowtot);
         return;
     }
-    b -= v.F;
+    b -= nfm;
     if (b < ncm) {
-        pc_pack_count_row(pid, keep, b, v.F, 1, (int64_t)v.C, v.P, v.cm_grp, v.cm_rowtot);
+        pc_pack_count_rows(pid, keep, b * PC_PACK_ROWS, v.C, v.F, 1, (int64_t)v.C, la.P, v.cm_grp, v.cm_rowtot);
         return;
     }
     b -= ncm;
@@ -923,8 +881,7 @@ struct PackBatchArg {
 __global__ void __launch_bounds__(256) pc_pack_stage1_batch_kernel(PackBatchArg b, LibArg la)
 {
     const int l = pc_batch_find(b.blk0, b.n, (int)blockIdx.x);
-    PackView v = *b.view[l];
-    v.P = la.P;
+    const PackView v = *b.view[l];
     pc_pack_stage1_body(b.W[l], b.pid[l], b.keep[l], la, v, b.ncm[l], b.tiles_c[l], (int)blockIdx.x - b.blk0[l]);
 }
 
@@ -945,140 +902,169 @@ __device__ __forceinline__ uint32_t pc_taps_word(const LibArg &la, int p)
     return (uint32_t)la.taps[p][0] | ((uint32_t)la.taps[p][1] << 8) | ((uint32_t)la.taps[p][2] << 16) | ((uint32_t)la.taps[p][3] << 24);
 }
 
-// Values again from new weights with unchanged tables, one launch for the matrix-core variant: workgroups
-// [0, ntiles) rebuild the operand tiles (masks from the kinfo table), the others re-gather the compact values.
-__device__ __forceinline__ void pc_pack_revalue_body(const float *__restrict__ W, const LibArg &la, int bf16, const PackView &v,
-                                                     int tiles_c, int ntiles, int b)
-{
-    if (b < ntiles) {
-        pc_pack_tile_block<true>(W, nullptr, nullptr, la, v, b / tiles_c, b % tiles_c);
-        return;
-    }
-    const int64_t k = (int64_t)(b - ntiles) * 256 + threadIdx.x;
-    if (k >= (int64_t)v.F * v.C) return;
-    const uint32_t u = v.kinfo[k];
-    if (u == 0xFFFFFFFFu) return;
-    const int slot = (int)(u >> 9);
-    v.fm_val[slot] = pc_gather_taps(W, k, pc_taps_word(la, v.fm_pid[slot]), bf16 != 0);
-}
-
+// Values again from new weights with unchanged tables, one launch for the matrix-core variant: every workgroup rebuilds the
+// operand tiles of a block (masks from the kinfo table).
 __global__ void __launch_bounds__(256)
-pc_pack_revalue_kernel(const float *__restrict__ W, LibArg la, int bf16, PackView v, int tiles_c, int ntiles)
+pc_pack_revalue_kernel(const float *__restrict__ W, PackView v, int tiles_c)
 {
-    pc_pack_revalue_body(W, la, bf16, v, tiles_c, ntiles, (int)blockIdx.x);
+    pc_pack_tile_block<true>(W, nullptr, nullptr, LibArg(), v, (int)blockIdx.x / tiles_c, (int)blockIdx.x % tiles_c);
 }
 
-// Value update of several matrix-core packs (ncm holds the tile count of pack l here; the pool's tap lists are
-// those of the pool the packs were made with).
-__global__ void __launch_bounds__(256) pc_pack_revalue_batch_kernel(PackBatchArg b, LibArg la)
+// The same for several packs.
+__global__ void __launch_bounds__(256) pc_pack_revalue_batch_kernel(PackBatchArg b)
 {
-    const int l = pc_batch_find(b.blk0, b.n, (int)blockIdx.x);
-    PackView v = *b.view[l];
-    v.P = la.P;
-    pc_pack_revalue_body(b.W[l], la, b.bf16[l], v, b.tiles_c[l], b.ncm[l], (int)blockIdx.x - b.blk0[l]);
+    const int l = pc_batch_find(b.blk0, b.n, (int)blockIdx.x), blk = (int)blockIdx.x - b.blk0[l];
+    const PackView v = *b.view[l];
+    pc_pack_tile_block<true>(b.W[l], nullptr, nullptr, LibArg(), v, blk / b.tiles_c[l], blk % b.tiles_c[l]);
 }
 
-// Places the kept kernels of one row at (kept kernels of the rows before) + (pattern group start) + (rank inside
-// the group); the rank of an element is the number of earlier members of its group in the row, so the order
-// inside a group is ascending. The row is walked 256 elements at a time: every wave ballots each pattern id,
-// the per-wave counts go through LDS. All counts are integers, so no result depends on an execution order.
-template <bool FM>
-__device__ __forceinline__ void pc_pack_place_body(const float *__restrict__ W, const uint8_t *__restrict__ pid,
-                                                   const uint8_t *__restrict__ keep, int rows, int len, int64_t row_stride,
-                                                   int64_t elem_stride, const LibArg &la, int bf16, const PackView &v, int row)
+// Places the kept kernels of one row at (kept kernels of the rows before) + (pattern group start) + (rank inside the group);
+// the rank of an element is the number of earlier members of its group in the row, so the order inside a group is ascending.
+// A workgroup per row: every wavefront ranks 64 * NE consecutive elements by ballots over the bits of their ids and leaves its
+// count per pattern in LDS; one barrier later every slot is known. Everything a row needs from memory before that barrier is
+// requested at once. All counts are integers, so no result depends on an execution order.
+// PLACE_SLOTS: the kinfo table, all that the matrix-core kernels read (their weights are in the operand tiles; gathering the
+// compact values too took 18.5 us for 3840 rows). PLACE_FM, PLACE_CM: the filter-major and channel-major tables of the
+// gather kernels.
+enum { PLACE_SLOTS = 0, PLACE_FM = 1, PLACE_CM = 2 };
+template <int KIND>
+__device__ __forceinline__ void pc_pack_place_row(const float *__restrict__ W, const uint8_t *__restrict__ pid,
+                                                  const uint8_t *__restrict__ keep, int rows, int len, int64_t row_stride,
+                                                  int64_t elem_stride, const LibArg &la, int bf16, const PackView &v, int row)
 {
-    __shared__ int start[PC_MAX_P + 1];          // next free slot of every pattern group
-    __shared__ int wcnt[4][PC_MAX_P + 2];        // members of every group in the current 256 elements, per wave
-    __shared__ int red[4];
-    __shared__ uint32_t ltaps[PC_MAX_P + 2];      // tap lists and masks of the pool
-    __shared__ uint16_t lmask[PC_MAX_P + 2];
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    constexpr bool FM = KIND != PLACE_CM;
+    constexpr int NE = 2;                        // 512 elements of the row at a time
+    __shared__ int start[128], wcnt[4][128], red[4];   // first slot of every group (less the rows before), members by wavefront
+    __shared__ uint32_t ltaps[128];              // tap lists and masks of the pool
+    __shared__ uint16_t lmask[128];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int P = la.P;
-    if (tid < P) { ltaps[tid] = pc_taps_word(la, tid); lmask[tid] = la.mask[tid]; }
     int32_t *grp = (FM ? v.fm_grp : v.cm_grp) + (int64_t)row * (PC_MAX_P + 1);
     int32_t *rowptr = FM ? v.fm_rowptr : v.cm_rowptr;
     const int32_t *rowtot = FM ? v.fm_rowtot : v.cm_rowtot;
-    // kept kernels in the rows before this one
-    int part = 0;
+    const int idbits = P > 1 ? 32 - __builtin_clz(P - 1) : 0;
+    int code[NE], rank[NE];
+    auto load_codes = [&](int e0) {
+#pragma unroll
+        for (int j = 0; j < NE; ++j) {
+            const int e = e0 + (wave * NE + j) * 64 + lane, ec = e < len ? e : len - 1;
+            const int64_t k = row * row_stride + ec * elem_stride;
+            const int kp = keep[k], pd = pid[k];
+            code[j] = e < len && kp && pd < P ? pd : 255;
+        }
+    };
+    load_codes(0);
+    if (tid < la.P) { ltaps[tid] = pc_taps_word(la, tid); lmask[tid] = la.mask[tid]; }
+    int part = 0;                                // kept kernels in the rows before this one
     for (int i = tid; i < row; i += 256) part += rowtot[i];
+    if (wave == 0) {
+        const int n0 = lane < P ? grp[lane] : 0, n1 = lane + 64 < P ? grp[lane + 64] : 0;
+        int s0 = n0, s1 = n1;                    // inclusive sums over the patterns
+        for (int off = 1; off < 64; off <<= 1) {
+            const int t0 = __shfl_up(s0, off), t1 = __shfl_up(s1, off);
+            if (lane >= off) { s0 += t0; s1 += t1; }
+        }
+        start[lane] = s0 - n0;
+        start[lane + 64] = __shfl(s0, 63) + s1 - n1;
+    }
     for (int off = 32; off > 0; off >>= 1) part += __shfl_down(part, off);
     if (lane == 0) red[wave] = part;
-    if (tid < P) start[tid] = grp[tid];          // counts for now
-    __syncthreads();
-    const int base = red[0] + red[1] + red[2] + red[3];
-    if (tid == 0) {
-        rowptr[row] = base;
-        if (row == rows - 1) rowptr[rows] = base + rowtot[row];
-        int run = base;
-        for (int p = 0; p < P; ++p) {
-            const int cnt = start[p];
-            start[p] = run;
-            run += cnt;
-        }
-        start[P] = run;
-    }
-    __syncthreads();
-    if (tid <= P) grp[tid] = start[tid];         // group starts, [P] = row end
-    for (int e0 = 0; e0 < len; e0 += 256) {
-        const int e = e0 + tid;
-        const int64_t k = row * row_stride + e * elem_stride;
-        int code = 255;
-        if (e < len) {
-            const int kp = keep[k], pd = pid[k];
-            if (kp && pd < P) code = pd;
-        }
-        int my_rank = 0, c0 = 0, c1 = 0;
-        for (int p = 0; p < P; ++p) {
-            const unsigned long long b = __ballot(code == p);
-            if (code == p) my_rank = __popcll(b & ((1ull << lane) - 1ull));
-            const int n = __popcll(b);
-            if (lane == (p & 63)) { if (p < 64) c0 = n; else c1 = n; }
-        }
-        if (lane < P) wcnt[wave][lane] = c0;
-        if (lane + 64 < P) wcnt[wave][lane + 64] = c1;
-        __syncthreads();
-        if (code != 255) {
-            int slot = start[code] + my_rank;
-            for (int w2 = 0; w2 < wave; ++w2) slot += wcnt[w2][code];
-            const float4 val = pc_gather_taps(W, k, ltaps[code], bf16 != 0);
-            if (FM) {
-                v.fm_c[slot] = (uint16_t)e;
-                v.fm_pid[slot] = (uint8_t)code;
-                v.slot_f[slot] = (uint16_t)row;
-                v.fm_val[slot] = val;
-                v.slot_of[k] = slot;
-                if (v.kinfo) v.kinfo[k] = ((uint32_t)slot << 9) | lmask[code];
-            } else {
-                v.cm_f[slot] = (uint16_t)e;
-                v.cm_slot[slot] = v.slot_of[k];
-                v.cm_val[slot] = val;
+    for (int e0 = 0;;) {
+        wcnt[wave][lane] = 0;
+        wcnt[wave][lane + 64] = 0;
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int j = 0; j < NE; ++j) {
+            unsigned long long same = __ballot(code[j] != 255);   // lanes of the same pattern, bit by bit of its id
+            for (int bit = 0; bit < idbits; ++bit) {
+                const bool on = (code[j] >> bit) & 1;
+                const unsigned long long b = __ballot(on);
+                same &= on ? b : ~b;
             }
-        } else if (FM && e < len) {
-            v.slot_of[k] = -1;
-            if (v.kinfo) v.kinfo[k] = 0xFFFFFFFFu;
+            const int members = (int)__popcll(same);
+            rank[j] = (int)__popcll(same & ((1ull << lane) - 1ull));
+            const int before = code[j] != 255 ? wcnt[wave][code[j]] : 0;
+            const bool first = rank[j] == 0;
+            rank[j] += before;
+            __builtin_amdgcn_wave_barrier();
+            if (code[j] != 255 && first) wcnt[wave][code[j]] = before + members;
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
         }
         __syncthreads();
-        if (tid < P) start[tid] += wcnt[0][tid] + wcnt[1][tid] + wcnt[2][tid] + wcnt[3][tid];
+        const int base = (red[0] + red[1]) + (red[2] + red[3]);
+        if (e0 == 0) {
+            const int end = base + rowtot[row];
+            if (KIND != PLACE_SLOTS) {
+                if (tid < P) grp[tid] = base + start[tid];
+                if (tid == 0) grp[P] = end;      // [P] = row end
+            }
+            if (tid == 0) {
+                rowptr[row] = base;
+                if (row == rows - 1) rowptr[rows] = end;
+            }
+        }
+        int slot[NE];
+        float4 val[NE];
+        int32_t fs[NE];
+#pragma unroll
+        for (int j = 0; j < NE; ++j) {
+            const int e = e0 + (wave * NE + j) * 64 + lane, ec = e < len ? e : len - 1;
+            const int64_t k = row * row_stride + ec * elem_stride;
+            const int c = code[j] != 255 ? code[j] : 0;
+            slot[j] = base + start[c] + rank[j];
+            for (int w = 0; w < wave; ++w) slot[j] += wcnt[w][c];
+            if (KIND != PLACE_SLOTS && code[j] != 255) val[j] = pc_gather_taps(W, k, ltaps[c], bf16 != 0);
+            fs[j] = FM ? 0 : v.slot_of[k];
+        }
+#pragma unroll
+        for (int j = 0; j < NE; ++j) {
+            const int e = e0 + (wave * NE + j) * 64 + lane;
+            const int64_t k = row * row_stride + e * elem_stride;
+            if (e >= len) continue;
+            const bool kept = code[j] != 255;
+            if (KIND == PLACE_SLOTS) {
+                v.kinfo[k] = kept ? ((uint32_t)slot[j] << 9) | lmask[code[j]] : 0xFFFFFFFFu;
+            } else if (FM) {
+                v.slot_of[k] = kept ? slot[j] : -1;
+                if (kept) {
+                    v.fm_c[slot[j]] = (uint16_t)e;
+                    v.fm_pid[slot[j]] = (uint8_t)code[j];
+                    v.slot_f[slot[j]] = (uint16_t)row;
+                    v.fm_val[slot[j]] = val[j];
+                }
+            } else if (kept) {
+                v.cm_f[slot[j]] = (uint16_t)e;
+                v.cm_slot[slot[j]] = fs[j];
+                v.cm_val[slot[j]] = val[j];
+            }
+        }
+        e0 += 256 * NE;
+        if (e0 >= len) break;
+        load_codes(e0);
+        __syncthreads();
+        if (tid < P) start[tid] += (wcnt[0][tid] + wcnt[1][tid]) + (wcnt[2][tid] + wcnt[3][tid]);
         __syncthreads();
     }
 }
 
-template <bool FM>
+template <int KIND>
 __global__ void __launch_bounds__(256)
 pc_pack_place_kernel(const float *__restrict__ W, const uint8_t *__restrict__ pid, const uint8_t *__restrict__ keep,
                      int rows, int len, int64_t row_stride, int64_t elem_stride, LibArg la, int bf16, PackView v)
 {
-    pc_pack_place_body<FM>(W, pid, keep, rows, len, row_stride, elem_stride, la, bf16, v, (int)blockIdx.x);
+    pc_pack_place_row<KIND>(W, pid, keep, rows, len, row_stride, elem_stride, la, bf16, v, (int)blockIdx.x);
 }
 
-template <bool FM> __global__ void __launch_bounds__(256) pc_pack_place_batch_kernel(PackBatchArg b, LibArg la)
+template <int KIND> __global__ void __launch_bounds__(256) pc_pack_place_batch_kernel(PackBatchArg b, LibArg la)
 {
     const int l = pc_batch_find(b.blk0, b.n, (int)blockIdx.x);
-    PackView v = *b.view[l];
-    v.P = la.P;
+    const PackView v = *b.view[l];
     const int row = (int)blockIdx.x - b.blk0[l];
-    if constexpr (FM) pc_pack_place_body<true>(b.W[l], b.pid[l], b.keep[l], v.F, v.C, (int64_t)v.C, (int64_t)1, la, b.bf16[l], v, row);
-    else pc_pack_place_body<false>(b.W[l], b.pid[l], b.keep[l], v.C, v.F, (int64_t)1, (int64_t)v.C, la, b.bf16[l], v, row);
+    if constexpr (KIND == PLACE_CM)
+        pc_pack_place_row<KIND>(b.W[l], b.pid[l], b.keep[l], v.C, v.F, (int64_t)1, (int64_t)v.C, la, b.bf16[l], v, row);
+    else
+        pc_pack_place_row<KIND>(b.W[l], b.pid[l], b.keep[l], v.F, v.C, (int64_t)v.C, (int64_t)1, la, b.bf16[l], v, row);
 }
 
 // Re-gathers values with unchanged tables (one thread per kernel (f,c)).
@@ -1135,27 +1121,31 @@ pc_status pc_launch_pack(pc_ctx *ctx, pc_packed *pk, const float *W, const uint8
     hipStream_t st = ctx->stream;
     const bool mfma = pk->variant == PC_VARIANT_MFMA;
     // the channel-major table serves the gather kernels' backward-data pass (the matrix-core kernels read operand tiles)
-    const int ncm = mfma ? 0 : v.C;
+    const int nfm = pc_pack_row_wgs(v.F), ncm = mfma ? 0 : pc_pack_row_wgs(v.C);
     const int tiles_c = v.Cp / 32, ntiles = mfma ? (v.Fp / 32) * tiles_c : 0;
-    hipLaunchKernelGGL(pc_pack_stage1_kernel, dim3((unsigned)(v.F + ncm + ntiles)), dim3(256), 0, st, W, pid, keep, la, v, ncm,
+    hipLaunchKernelGGL(pc_pack_stage1_kernel, dim3((unsigned)(nfm + ncm + ntiles)), dim3(256), 0, st, W, pid, keep, la, v, ncm,
                        tiles_c);
-    hipLaunchKernelGGL(pc_pack_place_kernel<true>, dim3(v.F), dim3(256), 0, st, W, pid, keep, v.F, v.C, (int64_t)v.C,
-                       (int64_t)1, la, bf16, v);
-    if (!mfma)
-        hipLaunchKernelGGL(pc_pack_place_kernel<false>, dim3(v.C), dim3(256), 0, st, W, pid, keep, v.C, v.F, (int64_t)1,
+    if (mfma) {
+        hipLaunchKernelGGL(pc_pack_place_kernel<PLACE_SLOTS>, dim3((unsigned)v.F), dim3(256), 0, st, W, pid, keep, v.F, v.C,
+                           (int64_t)v.C, (int64_t)1, la, bf16, v);
+    } else {
+        hipLaunchKernelGGL(pc_pack_place_kernel<PLACE_FM>, dim3((unsigned)v.F), dim3(256), 0, st, W, pid, keep, v.F, v.C,
+                           (int64_t)v.C, (int64_t)1, la, bf16, v);
+        hipLaunchKernelGGL(pc_pack_place_kernel<PLACE_CM>, dim3((unsigned)v.C), dim3(256), 0, st, W, pid, keep, v.C, v.F, (int64_t)1,
                            (int64_t)v.C, la, bf16, v);
+    }
     pc_launch_ovf_merge(ctx, v);
     return pc_hip_check(ctx, hipGetLastError(), "pack launch");
 }
 
-// Re-packs several handles with one pool: three launches per group of up to PC_BATCH_MAX packs (two when none uses
-// the gather kernels).
+// Re-packs several handles with one pool: two launches per group of up to PC_BATCH_MAX packs (four when some use the
+// gather kernels).
 pc_status pc_launch_pack_batch(pc_ctx *ctx, int n, pc_packed *const *pk, const float *const *W, const uint8_t *const *pid,
                                const uint8_t *const *keep, const LibArg &la)
 {
     for (int l0 = 0; l0 < n; l0 += PC_BATCH_MAX) {
         const int m = n - l0 < PC_BATCH_MAX ? n - l0 : PC_BATCH_MAX;
-        PackBatchArg s1, fm, cm;
+        PackBatchArg s1, sl, fm, cm;
         memset(&s1, 0, sizeof(s1));
         s1.n = m;
         for (int i = 0; i < m; ++i) {
@@ -1163,23 +1153,28 @@ pc_status pc_launch_pack_batch(pc_ctx *ctx, int n, pc_packed *const *pk, const f
             const bool mfma = p->variant == PC_VARIANT_MFMA;
             s1.W[i] = W[l0 + i]; s1.pid[i] = pid[l0 + i]; s1.keep[i] = keep[l0 + i];
             s1.view[i] = p->v_dev;
-            s1.ncm[i] = mfma ? 0 : p->v.C;
+            s1.ncm[i] = mfma ? 0 : pc_pack_row_wgs(p->v.C);
             s1.tiles_c[i] = p->v.Cp / 32;
             s1.bf16[i] = p->dtype == PC_BF16;
         }
+        sl = s1;
         fm = s1;
         cm = s1;
         for (int i = 0; i < m; ++i) {
             const pc_packed *p = pk[l0 + i];
             const bool mfma = p->variant == PC_VARIANT_MFMA;
-            s1.blk0[i + 1] = s1.blk0[i] + p->v.F + s1.ncm[i] + (mfma ? (p->v.Fp / 32) * s1.tiles_c[i] : 0);
-            fm.blk0[i + 1] = fm.blk0[i] + p->v.F;
+            s1.blk0[i + 1] = s1.blk0[i] + pc_pack_row_wgs(p->v.F) + s1.ncm[i] + (mfma ? (p->v.Fp / 32) * s1.tiles_c[i] : 0);
+            sl.blk0[i + 1] = sl.blk0[i] + (mfma ? p->v.F : 0);
+            fm.blk0[i + 1] = fm.blk0[i] + (mfma ? 0 : p->v.F);
             cm.blk0[i + 1] = cm.blk0[i] + (mfma ? 0 : p->v.C);
         }
         hipLaunchKernelGGL(pc_pack_stage1_batch_kernel, dim3((unsigned)s1.blk0[m]), dim3(256), 0, ctx->stream, s1, la);
-        hipLaunchKernelGGL(pc_pack_place_batch_kernel<true>, dim3((unsigned)fm.blk0[m]), dim3(256), 0, ctx->stream, fm, la);
-        if (cm.blk0[m] > 0)
-            hipLaunchKernelGGL(pc_pack_place_batch_kernel<false>, dim3((unsigned)cm.blk0[m]), dim3(256), 0, ctx->stream, cm, la);
+        if (sl.blk0[m] > 0)
+            hipLaunchKernelGGL(pc_pack_place_batch_kernel<PLACE_SLOTS>, dim3((unsigned)sl.blk0[m]), dim3(256), 0, ctx->stream, sl, la);
+        if (fm.blk0[m] > 0) {
+            hipLaunchKernelGGL(pc_pack_place_batch_kernel<PLACE_FM>, dim3((unsigned)fm.blk0[m]), dim3(256), 0, ctx->stream, fm, la);
+            hipLaunchKernelGGL(pc_pack_place_batch_kernel<PLACE_CM>, dim3((unsigned)cm.blk0[m]), dim3(256), 0, ctx->stream, cm, la);
+        }
         pc_launch_ovf_merge_batch(ctx, m, pk + l0);
         pc_status s = pc_hip_check(ctx, hipGetLastError(), "pack (several layers) launch");
         if (s != PC_OK) return s;
@@ -1187,32 +1182,22 @@ pc_status pc_launch_pack_batch(pc_ctx *ctx, int n, pc_packed *const *pk, const f
     return PC_OK;
 }
 
-// Matrix-core packs made with the pool of the first such pack share launches of up to PC_BATCH_MAX; the others
-// (gather-kernel packs, other pools) are updated one by one.
+// Matrix-core packs share launches of up to PC_BATCH_MAX; gather-kernel packs are updated one by one.
 pc_status pc_launch_update_values_batch(pc_ctx *ctx, int n, pc_packed *const *pk, const float *const *W)
 {
     PackBatchArg b;
     memset(&b, 0, sizeof(b));
     pc_packed *bpk[PC_BATCH_MAX];
-    LibArg la;
-    const pc_packed *first = nullptr;
     auto flush = [&]() -> pc_status {
         if (b.n == 0) return PC_OK;
-        hipLaunchKernelGGL(pc_pack_revalue_batch_kernel, dim3((unsigned)b.blk0[b.n]), dim3(256), 0, ctx->stream, b, la);
+        hipLaunchKernelGGL(pc_pack_revalue_batch_kernel, dim3((unsigned)b.blk0[b.n]), dim3(256), 0, ctx->stream, b);
         pc_launch_ovf_merge_batch(ctx, b.n, bpk);
         b.n = 0;
         return pc_hip_check(ctx, hipGetLastError(), "update_values (several layers) launch");
     };
     for (int l = 0; l < n; ++l) {
         pc_packed *p = pk[l];
-        bool same = p->variant == PC_VARIANT_MFMA;
-        if (same && !first) {
-            first = p;
-            pc_fill_lib(&la, p->lib, p->v.P);
-        }
-        if (same && (p->v.P != first->v.P || memcmp(p->lib, first->lib, sizeof(uint16_t) * p->v.P) != 0)) same = false;
-        const int64_t nblk = ((int64_t)p->v.F * p->v.C + 255) / 256;
-        if (!same) {
+        if (p->variant != PC_VARIANT_MFMA) {
             pc_status s = pc_launch_update_values(ctx, p, W[l]);
             if (s != PC_OK) return s;
             continue;
@@ -1222,9 +1207,7 @@ pc_status pc_launch_update_values_batch(pc_ctx *ctx, int n, pc_packed *const *pk
         b.W[i] = W[l];
         b.view[i] = p->v_dev;
         b.tiles_c[i] = p->v.Cp / 32;
-        b.ncm[i] = (p->v.Fp / 32) * b.tiles_c[i];
-        b.bf16[i] = p->dtype == PC_BF16;
-        b.blk0[i + 1] = b.blk0[i] + b.ncm[i] + (int32_t)nblk;
+        b.blk0[i + 1] = b.blk0[i] + (p->v.Fp / 32) * b.tiles_c[i];
         if (++b.n == PC_BATCH_MAX) {
             pc_status s = flush();
             if (s != PC_OK) return s;
@@ -1236,58 +1219,123 @@ pc_status pc_launch_update_values_batch(pc_ctx *ctx, int n, pc_packed *const *pk
 pc_status pc_launch_update_values(pc_ctx *ctx, pc_packed *pk, const float *W)
 {
     PackView v = pk->v;
-    LibArg la;
-    pc_fill_lib(&la, pk->lib, v.P);
-    int bf16 = pk->dtype == PC_BF16;
-    int64_t nk = (int64_t)v.F * v.C;
-    unsigned blocks = (unsigned)((nk + 255) / 256);
     if (pk->variant == PC_VARIANT_MFMA) {
         const int tiles_c = v.Cp / 32, ntiles = (v.Fp / 32) * tiles_c;
-        hipLaunchKernelGGL(pc_pack_revalue_kernel, dim3((unsigned)ntiles + blocks), dim3(256), 0, ctx->stream, W, la, bf16, v,
-                           tiles_c, ntiles);
+        hipLaunchKernelGGL(pc_pack_revalue_kernel, dim3((unsigned)ntiles), dim3(256), 0, ctx->stream, W, v, tiles_c);
         pc_launch_ovf_merge(ctx, v);
     } else {
+        LibArg la;
+        pc_fill_lib(&la, pk->lib, v.P);
+        const int bf16 = pk->dtype == PC_BF16;
+        const unsigned blocks = (unsigned)(((int64_t)v.F * v.C + 255) / 256);
         hipLaunchKernelGGL(pc_pack_regather_fm_kernel, dim3(blocks), dim3(256), 0, ctx->stream, W, la, bf16, v);
         hipLaunchKernelGGL(pc_pack_regather_cm_kernel, dim3(blocks), dim3(256), 0, ctx->stream, v);
     }
     return pc_hip_check(ctx, hipGetLastError(), "update_values launch");
 }
 
-// dense[f][c][t] = value of the kept tap, 0 elsewhere. Source: a compact array or the pack's own values.
+// dense[f][c][t] = value of the kept tap, 0 elsewhere. The 9 values of a workgroup's 256 kernels go through LDS, so that the
+// stores are contiguous. The slots come from the kinfo table of a matrix-core pack or the tables of a gather-kernel pack;
+// compact == nullptr (the latter only): the pack's own values.
+template <bool KINFO>
 __global__ void __launch_bounds__(256)
 pc_scatter_kernel(const float *__restrict__ compact, float *__restrict__ dense, LibArg la, PackView v)
 {
-    int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= (int64_t)v.F * v.C) return;
-    float out[9];
+    __shared__ __align__(16) float s[256 * 9];
+    const int tid = threadIdx.x;
+    const int64_t nk = (int64_t)v.F * v.C, k0 = (int64_t)blockIdx.x * 256, k = k0 + tid < nk ? k0 + tid : nk - 1;
+    int slot = -1;
+    unsigned m = 0u;
+    if (KINFO) {
+        const uint32_t u = v.kinfo[k];
+        if (u != 0xFFFFFFFFu) { slot = (int)(u >> 9); m = u & 511u; }
+    } else {
+        slot = v.slot_of[k];
+        if (slot >= 0) m = la.mask[v.fm_pid[slot]];
+    }
+    float4 val = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (slot >= 0) val = compact ? reinterpret_cast<const float4 *>(compact)[slot] : v.fm_val[slot];
+    int j = 0;
 #pragma unroll
-    for (int t = 0; t < 9; ++t) out[t] = 0.0f;
-    int slot = v.slot_of[k];
-    if (slot >= 0) {
-        float4 val = compact ? reinterpret_cast<const float4 *>(compact)[slot] : v.fm_val[slot];
-        unsigned m = la.mask[v.fm_pid[slot]];
-        float vv[4] = {val.x, val.y, val.z, val.w};
-        int j = 0;
+    for (int t = 0; t < 9; ++t) {
+        const bool on = (m >> t) & 1u;
+        s[tid * 9 + t] = !on ? 0.0f : j == 0 ? val.x : j == 1 ? val.y : j == 2 ? val.z : val.w;
+        j += on;
+    }
+    __syncthreads();
+    const int n = nk - k0 < 256 ? (int)(nk - k0) * 9 : 256 * 9;
+    float *dst = dense + k0 * 9;
+    if ((reinterpret_cast<uintptr_t>(dense) & 15) == 0) {
 #pragma unroll
-        for (int t = 0; t < 9; ++t) {
-            if (m & (1u << t)) {
-                out[t] = j == 0 ? vv[0] : j == 1 ? vv[1] : j == 2 ? vv[2] : vv[3];
-                ++j;
+        for (int i = tid; i < 256 * 9 / 4; i += 256)
+            if (i * 4 + 3 < n) reinterpret_cast<float4 *>(dst)[i] = reinterpret_cast<const float4 *>(s)[i];
+        const int i = (n & ~3) + tid;
+        if (i < n) dst[i] = s[i];
+    } else {
+        for (int i = tid; i < n; i += 256) dst[i] = s[i];
+    }
+}
+
+// The own values of a matrix-core pack: they are in the operand tiles of the forward pass, zeros included. One 32-filter x
+// 32-channel block per workgroup, fragments in, rows of 32 * 9 floats out.
+__global__ void __launch_bounds__(256) pc_unpack_tiles_kernel(float *__restrict__ dense, PackView v, int tiles_c)
+{
+    constexpr int PITCH = 289;                    // odd: rows and columns spread over the banks
+    __shared__ float s[32 * PITCH];
+    const int tid = threadIdx.x, fb = (int)blockIdx.x / tiles_c, cb = (int)blockIdx.x - fb * tiles_c;
+    if (v.f32) {
+        const float4 *in = reinterpret_cast<const float4 *>(v.wz_fwd);
+        float4 q[9];
+#pragma unroll
+        for (int i = 0; i < 9; ++i) {             // tap i, 8-entry step tid / 64
+            const int ks = cb * 4 + (tid >> 6);
+            q[i] = ks < v.Ck / 8 ? in[((int64_t)(fb * 9 + i) * (v.Ck / 8) + ks) * 64 + (tid & 63)] : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+#pragma unroll
+        for (int i = 0; i < 9; ++i) {
+            float *d = s + (tid & 31) * PITCH + ((tid >> 6) * 8 + 4 * ((tid >> 5) & 1)) * 9 + i;
+            d[0] = q[i].x; d[9] = q[i].y; d[18] = q[i].z; d[27] = q[i].w;
+        }
+    } else {
+        const uint4 *in = reinterpret_cast<const uint4 *>(v.wz_fwd);
+        uint4 q[5];
+#pragma unroll
+        for (int i = 0; i < 5; ++i) {             // fragment (tap, 16-entry step) i * 4 + tid / 64 of 18
+            const int fr = i * 4 + (tid >> 6), tap = fr >> 1, ks = cb * 2 + (fr & 1);
+            q[i] = fr < 18 && ks < v.Ck / 16 ? in[((int64_t)(fb * 9 + tap) * (v.Ck / 16) + ks) * 64 + (tid & 63)] : make_uint4(0u, 0u, 0u, 0u);
+        }
+#pragma unroll
+        for (int i = 0; i < 5; ++i) {
+            const int fr = i * 4 + (tid >> 6);
+            if (fr >= 18) break;
+            float *d = s + (tid & 31) * PITCH + ((fr & 1) * 16 + 8 * ((tid >> 5) & 1)) * 9 + (fr >> 1);
+            const uint32_t w[4] = {q[i].x, q[i].y, q[i].z, q[i].w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                d[18 * e] = __uint_as_float(w[e] << 16);
+                d[18 * e + 9] = __uint_as_float(w[e] & 0xFFFF0000u);
             }
         }
     }
-#pragma unroll
-    for (int t = 0; t < 9; ++t) dense[k * 9 + t] = out[t];
+    __syncthreads();
+    const int nrows = v.F - fb * 32 < 32 ? v.F - fb * 32 : 32, ncols = v.C - cb * 32 < 32 ? v.C - cb * 32 : 32;
+    for (int r = tid >> 6; r < nrows; r += 4)
+        for (int j = tid & 63; j < ncols * 9; j += 64) dense[((int64_t)(fb * 32 + r) * v.C + cb * 32) * 9 + j] = s[r * PITCH + j];
 }
 
 pc_status pc_launch_scatter(pc_ctx *ctx, const pc_packed *pk, const float *compact, float *dense, int from_pack)
 {
-    PackView v = pk->v;
+    const PackView v = pk->v;
+    const bool mfma = pk->variant == PC_VARIANT_MFMA;
+    if (mfma && from_pack) {
+        const int tiles_c = (v.C + 31) / 32;
+        hipLaunchKernelGGL(pc_unpack_tiles_kernel, dim3((unsigned)((v.F + 31) / 32 * tiles_c)), dim3(256), 0, ctx->stream, dense, v, tiles_c);
+        return pc_hip_check(ctx, hipGetLastError(), "unpack launch");
+    }
     LibArg la;
     pc_fill_lib(&la, pk->lib, v.P);
-    int64_t nk = (int64_t)v.F * v.C;
-    unsigned blocks = (unsigned)((nk + 255) / 256);
-    hipLaunchKernelGGL(pc_scatter_kernel, dim3(blocks), dim3(256), 0, ctx->stream, from_pack ? nullptr : compact, dense,
-                       la, v);
+    const unsigned blocks = (unsigned)(((int64_t)v.F * v.C + 255) / 256);
+    if (mfma) hipLaunchKernelGGL(pc_scatter_kernel<true>, dim3(blocks), dim3(256), 0, ctx->stream, compact, dense, la, v);
+    else hipLaunchKernelGGL(pc_scatter_kernel<false>, dim3(blocks), dim3(256), 0, ctx->stream, from_pack ? nullptr : compact, dense, la, v);
     return pc_hip_check(ctx, hipGetLastError(), "scatter launch");
 }
