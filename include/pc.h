@@ -119,6 +119,9 @@ pc_status pc_set_variant(pc_ctx *ctx, pc_variant v);
  *   14, 15 as 9 with 128-channel chunks, and with tiles of 32 output channels x 32 pixels
  *   17, 18 as 13, 16 with 16-channel chunks (first layers); 19 as 13 with tiles of 32 output channels;
  *          20 as 16 with 64-channel chunks; 21 as 8 with 128-channel chunks
+ *   24..29 the same kernel with tiles of 32 output channels: 24, 25 x 256 pixels, pixels split, 64- and 32-channel
+ *          chunks; 26 x 512 pixels, pixels split, 16-channel chunks; 27, 29 x 64 pixels, reduction split, 128- and
+ *          64-channel chunks; 28 x 128 pixels, reduction split, 64-channel chunks
  *   10, 11 backward-weight: the cooperative / the wave-specialised kernel (the other passes stay automatic)
  *   22     forward/backward-data: the structured-sparse kernel (packs made under PC_VARIANT_MFMA_SPARSE only)
  *   23     the first-layer kernels (stride 1, at most 4 input channels): the automatic choice takes them wherever

@@ -894,11 +894,26 @@ static hipError_t launch_sp(int device, hipStream_t st, int grid, size_t lds, co
     return launch_sp_act<B_T, KC, PC_ACT_NONE>(device, st, grid, lds, in, out, sp, g);
 }
 
-// Fills the tile plan; false when the staged tile does not fit. ksp = 4: the MFMA wavefronts split the
-// reduction of a tile of 32*bt pixels (64-channel chunks); ksp = 1: they split a tile of 128*bt pixels
-// (32-channel chunks, no reduction across wavefronts).
-static bool plan_ks(const MfmaArgs &g, int ext, int at, int bt, int ksp, int kc, MfmaArgs *out, size_t *lds_bytes, double *est, int num_cu)
+// ksp = 4: the MFMA wavefronts split the reduction of a tile of 32*bt pixels; ksp = 1: they split a tile of 128*bt pixels (no
+// reduction across wavefronts).
+// The kernels of this file that a launch can take, by override code. The last three columns are the constants of the time
+// estimate below.
+struct KsCand { int code, at, bt, ksp, kc; double mfma, item, tile; };
+static const KsCand kKs[] = {
+    {7, 2, 4, 4, 64, 0.90, 637, 3969},   {8, 2, 2, 4, 64, 1.27, 299, 1760},   {9, 2, 1, 4, 64, 1.77, 660, 1135},
+    {14, 2, 1, 4, 128, 1.90, 596, 978},  {15, 1, 1, 4, 128, 1.91, 812, 1103}, {21, 2, 2, 4, 128, 1.26, 86, 2120},
+    {27, 1, 2, 4, 128, 1.45, 358, 1473}, {28, 1, 4, 4, 64, 1.30, 341, 2156},  {29, 1, 2, 4, 64, 2.21, 78, 1494},
+    {16, 2, 2, 1, 32, 1.35, 283, 2811},  {17, 2, 4, 1, 16, 1.22, 279, 5427},  {18, 2, 2, 1, 16, 1.47, 476, 2795},
+    {19, 1, 4, 1, 32, 1.19, 582, 4713},  {20, 2, 2, 1, 64, 1.15, 361, 3048},  {24, 1, 2, 1, 64, 0.90, 1340, 2540},
+    {25, 1, 2, 1, 32, 1.46, 699, 2702},  {26, 1, 4, 1, 16, 1.02, 940, 4807},
+    {13, 2, 4, 1, 32, 0, 0, 0},          // by override only: the 256-pixel tiles and the 16-channel chunks beat it everywhere
+};
+static const int kNumKs = sizeof(kKs) / sizeof(kKs[0]);
+
+// Fills the tile plan of a candidate and its estimated time in microseconds; false when it does not fit.
+static bool plan_ks(const MfmaArgs &g, int ext, const KsCand &cand, MfmaArgs *out, size_t *lds_bytes, double *est, int num_cu)
 {
+    const int at = cand.at, bt = cand.bt, ksp = cand.ksp, kc = cand.kc;
     const int pitch = 2 * kc + 16, parts = kc / 8, nv = ksp == 4 ? KS_NV : KS_NV1;
     MfmaArgs t = g;
     pc_plan_mfma_tiles(&t, (ksp == 4 ? 32 : 128) * bt, ext);
@@ -946,20 +961,22 @@ static bool plan_ks(const MfmaArgs &g, int ext, int at, int bt, int ksp, int kc,
     t.mg_fd = magic(t.fdiv); t.mg_tx = magic(t.tiles_x); t.mg_ty = magic(t.tiles_y);
     t.nchunks = (g.in_CH + kc - 1) / kc;
     t.cps = t.nchunks;
-    // cycles of one workgroup: tiles per workgroup x (MFMAs of a tile at 32 cycles each per wavefront + the tile's
-    // fixed cost: the reduction across wavefronts, or just the store)
-    const int64_t rounds = (total + num_cu - 1) / num_cu;
-    // (an item also costs a barrier and the refill of the fragment pipelines: about 450 cycles; inside an item the
-    // MFMAs issue at about 70 % of their peak rate in both splits, which weighs the fixed costs against them)
-    const double mfma_eff = 0.7;
-    if (ksp == 4) *est = (double)rounds * ((double)t.nchunks * (288.0 * at * bt * kc / 64 / mfma_eff + 450.0) + 2500.0);
-    else *est = (double)rounds * ((double)t.nchunks * (18.0 * kc * at * bt / mfma_eff + 450.0) + 1200.0);
-    // A workgroup with a single 512-pixel tile overlaps nothing: it loads its whole input, multiplies, then stores.
-    // Two 256-pixel tiles hide the second load and the first store (measured with cold caches on 32x32 maps,
-    // 64 -> 64 channels, batch 128: 23.5 us against 29.8 us), which the cycle count above does not see.
-    // With more tiles the smaller tile still gains in the step (shorter loader and store bursts): 1-1.5 % of the
-    // ImageNet-sized workloads' steps, measured with this factor at 1.2 and at 1.5.
-    if (ksp == 1 && bt == 4) *est *= rounds == 1 ? 1.6 : 1.2;
+    // Estimated time. A workgroup's tiles follow each other, a tile is a sequence of items (chunks of kc channels) and an end.
+    // An item takes its matrix instructions (32 cycles each, times a factor for what of them the kernel fails to issue back
+    // to back) or its staging, whichever is longer, and a barrier with the refill of the fragment pipelines; the end of a
+    // tile a fixed part and its bytes; the whole launch at least what the tensors take, the input with its halo and in pieces
+    // of 64 bytes. The constants (factor, item and tile cycles per kernel, the shared ones here) are a least-squares fit over
+    // the measured times of every kernel on 355 layer shapes (1 to 128 images, 4 x 4 to 224 x 224, 8 to 512 channels, both
+    // strides, back to back): 5 % rms over 11 500 timings. The kernel with the least estimate is on average 2 % slower than
+    // the fastest of a shape; the rule it replaces, made for channel counts from 64 up, 22 %.
+    const double rounds = (double)((total + num_cu - 1) / num_cu);
+    const double mfma = 9.0 * (kc / 16) * at * bt * 32.0 / (ksp == 4 ? 4 : 1) * cand.mfma, stage = t.nelem * 16.0 * 0.0418;
+    const double end = cand.tile + 64.0 * at * t.TI * t.TH * t.TW * 0.0143;
+    const double busy = rounds * (t.nchunks * ((mfma > stage ? mfma : stage) + cand.item) + end) / 2000.0;
+    const int pieces = t.nchunks * (g.in_CH < 32 ? g.in_CH : 32);
+    const double bytes = 2.0 * ((double)p_tiles * HP * (pieces > g.in_CH ? pieces : g.in_CH)) + (double)out_bytes;
+    const double move = bytes / 5.02e6;
+    *est = 3.7 + (busy > move ? busy + 0.1 * move : move + 0.1 * busy);
     *out = t;
     return true;
 }
@@ -975,7 +992,8 @@ pc_status pc_run_mfma_conv_ws(pc_ctx *ctx, int pcfg, const MfmaArgs &g0, int ext
         MfmaArgs t;
         size_t lds;
         double est;
-        bool ok = plan_ks(g0, ext, 2, 2, 1, 64, &t, &lds, &est, ctx->num_cu);
+        const KsCand tile = {22, 2, 2, 1, 64, 1.0, 0, 0};
+        bool ok = plan_ks(g0, ext, tile, &t, &lds, &est, ctx->num_cu);
         for (int q = 0; q < 9 && ok; ++q)
             if (t.tap_w[q] != q || tr[q] != (tr[0] ? 2 - q / 3 : q / 3) || tc[q] != (tc[0] ? 2 - q % 3 : q % 3)) ok = false;
         if (ok) {
@@ -993,33 +1011,22 @@ pc_status pc_run_mfma_conv_ws(pc_ctx *ctx, int pcfg, const MfmaArgs &g0, int ext
         if (pcfg == 22) return pc_fail(ctx, PC_ERR_UNSUPPORTED, "MFMA conv: the structured-sparse kernel does not fit this launch");
     }
     if (pcfg == 22) return pc_fail(ctx, PC_ERR_UNSUPPORTED, "MFMA conv: the pack holds no structured-sparse operand");
-    // candidates: (pixel-tile factor, reduction split); override codes 7, 8, 9 and 13 force one of them
-    enum { NCAND = 12 };
-    static const int kAt[NCAND] = {2, 2, 2, 2, 2, 1, 2, 2, 2, 1, 2, 2}, kBt[NCAND] = {4, 2, 1, 4, 1, 1, 2, 4, 2, 4, 2, 2},
-                     kKsp[NCAND] = {4, 4, 4, 1, 4, 4, 1, 1, 1, 1, 1, 4}, kKc[NCAND] = {64, 64, 64, 32, 128, 128, 32, 16, 16, 32, 64, 128},
-                     kCode[NCAND] = {7, 8, 9, 13, 14, 15, 16, 17, 18, 19, 20, 21};
     MfmaArgs best;
     size_t best_lds = 0;
     double best_est = 0.0;
     int best_k = -1;
-    for (int k = 0; k < NCAND; ++k) {
-        if (pcfg >= 7 && pcfg != kCode[k]) continue;
-        // 16-channel chunks are for the few input channels of a first layer and for stride-2 forward passes (the staged tile
-        // has four times the pixels of the output tile: with wider chunks it no longer fits and the output tile shrinks:
-        // 56 x 56, 128 -> 128, batch 64: 47.6 -> 40.5 us), 32-row tiles for a first layer's few output channels
-        if (pcfg < 0 && ((kKc[k] == 16 && g0.in_CH > 16 && g0.lstep != 2) || (kKc[k] != 16 && g0.in_CH <= 16) || (kAt[k] == 1 && kKsp[k] == 1) != (g0.out_CH <= 32))) continue;
+    for (int k = 0; k < kNumKs; ++k) {
+        if (pcfg >= 7 ? pcfg != kKs[k].code : kKs[k].tile == 0) continue;
         MfmaArgs t;
         size_t lds;
         double est;
-        if (!plan_ks(g0, ext, kAt[k], kBt[k], kKsp[k], kKc[k], &t, &lds, &est, ctx->num_cu)) continue;
+        if (!plan_ks(g0, ext, kKs[k], &t, &lds, &est, ctx->num_cu)) continue;
         if (best_k < 0 || est < best_est) { best = t; best_lds = lds; best_est = est; best_k = k; }
     }
     if (best_k < 0) return PC_OK;
-    // The end-of-tile reduction costs about as much as 64 channels of MFMA work: up to 128 reduction channels
-    // the cooperative kernel's output split is faster, unless every workgroup has a single tile.
-    if (pcfg < 0 && kKsp[best_k] == 4 && (g0.in_CH <= 64 || (g0.in_CH <= 128 && best.total_tiles > ctx->num_cu))) return PC_OK;
+    const KsCand &c = kKs[best_k];
     MfmaArgs g = best;
-    const int pitch = 2 * kKc[best_k] + 16;
+    const int pitch = 2 * c.kc + 16;
     // the tap list is the full 3x3 in tap order, forward (offset (r, s)) or rotated (offset (2-r, 2-s))
     for (int t = 0; t < 9; ++t)
         if (g.tap_w[t] != t || tr[t] != (tr[0] ? 2 - t / 3 : t / 3) || tc[t] != (tc[0] ? 2 - t % 3 : t % 3)) return PC_OK;
@@ -1029,21 +1036,30 @@ pc_status pc_run_mfma_conv_ws(pc_ctx *ctx, int pcfg, const MfmaArgs &g0, int ext
     g.wz_bytes = (uint32_t)((size_t)((g.out_CH + 127) / 128 * 4) * 9 * g.KS * 1024);
     const int grid = g.total_tiles < ctx->num_cu ? g.total_tiles : ctx->num_cu;
     hipError_t e;
-    switch (best_k) {
-    case 0: e = launch_ks<2, 4, 64, 4>(ctx->device, ctx->stream, grid, best_lds, in, out, wz, g, act); break;
-    case 1: e = launch_ks<2, 2, 64, 4>(ctx->device, ctx->stream, grid, best_lds, in, out, wz, g, act); break;
-    case 2: e = launch_ks<2, 1, 64, 4>(ctx->device, ctx->stream, grid, best_lds, in, out, wz, g, act); break;
-    case 3: e = launch_ks<2, 4, 32, 1>(ctx->device, ctx->stream, grid, best_lds, in, out, wz, g, act); break;
-    case 4: e = launch_ks<2, 1, 128, 4>(ctx->device, ctx->stream, grid, best_lds, in, out, wz, g, act); break;
-    case 5: e = launch_ks<1, 1, 128, 4>(ctx->device, ctx->stream, grid, best_lds, in, out, wz, g, act); break;
-    case 6: e = launch_ks<2, 2, 32, 1>(ctx->device, ctx->stream, grid, best_lds, in, out, wz, g, act); break;
-    case 7: e = launch_ks<2, 4, 16, 1>(ctx->device, ctx->stream, grid, best_lds, in, out, wz, g, act); break;
-    case 8: e = launch_ks<2, 2, 16, 1>(ctx->device, ctx->stream, grid, best_lds, in, out, wz, g, act); break;
-    case 9: e = launch_ks<1, 4, 32, 1>(ctx->device, ctx->stream, grid, best_lds, in, out, wz, g, act); break;
-    case 10: e = launch_ks<2, 2, 64, 1>(ctx->device, ctx->stream, grid, best_lds, in, out, wz, g, act); break;
-    default: e = launch_ks<2, 2, 128, 4>(ctx->device, ctx->stream, grid, best_lds, in, out, wz, g, act); break;
+    switch (c.code) {
+#define KS_CASE(CODE, A, B, K, KC) case CODE: e = launch_ks<A, B, KC, K>(ctx->device, ctx->stream, grid, best_lds, in, out, wz, g, act); break;
+    KS_CASE(7, 2, 4, 4, 64)
+    KS_CASE(8, 2, 2, 4, 64)
+    KS_CASE(9, 2, 1, 4, 64)
+    KS_CASE(13, 2, 4, 1, 32)
+    KS_CASE(14, 2, 1, 4, 128)
+    KS_CASE(15, 1, 1, 4, 128)
+    KS_CASE(16, 2, 2, 1, 32)
+    KS_CASE(17, 2, 4, 1, 16)
+    KS_CASE(18, 2, 2, 1, 16)
+    KS_CASE(19, 1, 4, 1, 32)
+    KS_CASE(20, 2, 2, 1, 64)
+    KS_CASE(21, 2, 2, 4, 128)
+    KS_CASE(24, 1, 2, 1, 64)
+    KS_CASE(25, 1, 2, 1, 32)
+    KS_CASE(26, 1, 4, 1, 16)
+    KS_CASE(27, 1, 2, 4, 128)
+    KS_CASE(28, 1, 4, 4, 64)
+    KS_CASE(29, 1, 2, 4, 64)
+    default: return pc_fail(ctx, PC_ERR_UNSUPPORTED, "MFMA conv: no kernel has code %d", c.code);
+#undef KS_CASE
     }
     *launched = true;
-    pc_note_kernel(ctx, "pc_mfma_conv_ks_kernel<%d, %d, 9, %d, %d, %d>", kAt[best_k], kBt[best_k], kKc[best_k], kKsp[best_k], act);
+    pc_note_kernel(ctx, "pc_mfma_conv_ks_kernel<%d, %d, 9, %d, %d, %d>", c.at, c.bt, c.kc, c.ksp, act);
     return pc_hip_check(ctx, e, "MFMA conv (wave-specialised) launch");
 }
