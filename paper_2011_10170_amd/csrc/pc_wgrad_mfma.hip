@@ -2,6 +2,9 @@
 // (Section 5.3: only the kept positions are needed).
 #include "pc_mfma.h"
 
+#include <algorithm>
+#include <vector>
+
 // ------------------------------------------------------------------ backward-weight
 // dW[t][f][c] = sum over output pixels of dy[pixel][f] * x[pixel shifted by tap t][c]: for every tap a
 // GEMM with M = filters, N = channels and the pixels as the reduction. Both MFMA operands need 8
@@ -296,6 +299,9 @@ struct WgradWsArgs {
     uint32_t x_bytes, dy_bytes;            // tensor sizes (bounds of the buffer loads)
     uint32_t mg_tc, mg_tr;                 // multiply-high constants of the divisions by tiles_c and tiles_r
     uint32_t mg_npos, mg_TC, mg_xs, mg_IC; // and by npos, TC, xs_per_g, IC (slot tables below)
+    // A batch that is no multiple of 8 may be cut into strips: the 8 entries of a group are then 8 >> lgS images of 1 << lgS
+    // strips each, SR output rows to a strip (lgS = 0: whole images).
+    int32_t lgS, SR;
 };
 
 // dy slot -> (image group << 16) | (row << 8) | column of the pixel tile; 0xFFFFFFFF = unused
@@ -323,6 +329,7 @@ __device__ __forceinline__ uint32_t ws_x_tab(const WgradWsArgs &a, int xs)
 }
 
 // lin: index of the workgroup in the layer's grid of gx x gy tiles x ksplit splits (x fastest).
+template <bool STRIPS>
 __device__ __forceinline__ void pc_mfma_wgrad_ws_body(const uint16_t *__restrict__ x, const uint16_t *__restrict__ dy,
                                                       const WgradWsArgs &a, const uint32_t *__restrict__ kinfo,
                                                       float *__restrict__ partial, float *__restrict__ dw, int lin, int gx, int gy)
@@ -404,6 +411,8 @@ __device__ __forceinline__ void pc_mfma_wgrad_ws_body(const uint16_t *__restrict
         const __amdgpu_buffer_rsrc_t src0 = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(dy0 ? dy : x), 0,
                                                                                dy0 ? a.dy_bytes : a.x_bytes, 0x00020000);
         const int dy_img = a.Ho * a.Wo * a.F * 2, x_img = a.H * a.W * a.C * 2;   // bytes per image
+        const int gimg = STRIPS ? 8 >> a.lgS : 8, smask = (1 << a.lgS) - 1;                  // images per group, strips per image - 1
+        const int x_strip = a.SR * a.stride * a.W * a.C * 2;                      // bytes per strip
         // task 0: slot tl>>3 (dy) or (tl-128)>>3 (x slots 0..15); task 1: x slot 16 + tl>>3 (x slots 16..47)
         const int slot0 = dy0 ? tl >> 3 : (tl - 128) >> 3;
         const int slot1 = 16 + (tl >> 3);
@@ -415,10 +424,21 @@ __device__ __forceinline__ void pc_mfma_wgrad_ws_body(const uint16_t *__restrict
         const bool use0 = tab0 != 0xFFFFFFFFu && chan0;
         const bool use1 = tab1 != 0xFFFFFFFFu && c0 + cg * 8 < a.C;
         // byte offset of the task's first image relative to the pixel tile's origin
-        const int rel0 = dy0 ? ig0 * 8 * dy_img + ((r0 * a.Wo + q0) * a.F + f0 + cg * 8) * 2
-                             : ig0 * 8 * x_img + ((r0 * a.W + q0) * a.C + c0 + cg * 8) * 2;
-        const int rel1 = ig1 * 8 * x_img + ((r1 * a.W + q1) * a.C + c0 + cg * 8) * 2;
-        const int img0 = dy0 ? dy_img : x_img;
+        const int rel0 = dy0 ? ig0 * gimg * dy_img + ((r0 * a.Wo + q0) * a.F + f0 + cg * 8) * 2
+                             : ig0 * gimg * x_img + ((r0 * a.W + q0) * a.C + c0 + cg * 8) * 2;
+        const int rel1 = ig1 * gimg * x_img + ((r1 * a.W + q1) * a.C + c0 + cg * 8) * 2;
+        const int img0 = dy0 ? dy_img : x_img, strip0 = dy0 ? a.SR * a.Wo * a.F * 2 : x_strip;
+        // The entries (image, strip) of a group whose first image is n that have row y of the strip (an output row, or an input
+        // row counted from the strip's first: -1 is real input unless the strip is an image's first). Bit i: entry i.
+        const uint32_t first = 0xFFu / (uint32_t)((2 << smask) - 1), last = first << smask;   // entries that are first / last strips
+        auto entries = [&](int n, int y, bool of_dy) -> uint32_t {
+            const int end = of_dy ? a.Ho - smask * a.SR : a.H - smask * a.SR * a.stride;      // rows of a last strip
+            const int left = (a.N - n) << a.lgS;
+            uint32_t m = left >= 8 ? 0xFFu : left > 0 ? (1u << left) - 1u : 0u;
+            if (y < 0) m &= ~first;
+            if (y >= end) m &= ~last;
+            return y >= (of_dy ? a.SR : (a.SR - 1) * a.stride + 2) ? 0u : m;   // rows of the next strip
+        };
         const int pitch0 = dy0 ? WS_DY_PLANE : a.xplane;
         const int dst0 = (dy0 ? 0 : XT_OFF) + (cg * 8) * pitch0 + cg * 16 + (slot0 << 4);
         const int dst1 = XT_OFF + (cg * 8) * a.xplane + cg * 16 + (slot1 << 4);
@@ -430,11 +450,33 @@ __device__ __forceinline__ void pc_mfma_wgrad_ws_body(const uint16_t *__restrict
             const int tc = kt - (int)u * a.tiles_c;
             const uint32_t tn = pc_udiv(u, a.mg_tr);
             const int tr = (int)u - (int)tn * a.tiles_r;
-            const int oy0 = tr * a.TR, ox0 = tc * a.TC, n0 = (int)tn * a.ng * 8;
+            const int oy0 = tr * a.TR, ox0 = tc * a.TC, n0 = (int)tn * a.ng * gimg;
             const int xy0 = oy0 * a.stride - 1, xx0 = ox0 * a.stride - 1;
             const int org_d = n0 * dy_img + (oy0 * a.Wo + ox0) * a.F * 2;
             const int org_x = n0 * x_img + (xy0 * a.W + xx0) * a.C * 2;
             bool ok0, ok1;
+            if (STRIPS) {
+                // what exists differs between the entries of a group: a mask switches them off one by one
+                const bool col0 = live && use0 && (unsigned)((dy0 ? ox0 : xx0) + q0) < (unsigned)(dy0 ? a.Wo : a.W);
+                const bool col1 = live && use1 && (unsigned)(xx0 + q1) < (unsigned)a.W;
+                const uint32_t at0 = (uint32_t)(rel0 + (dy0 ? org_d : org_x)), at1 = (uint32_t)(rel1 + org_x);
+                const uint32_t m0 = col0 ? entries(n0 + ig0 * gimg, dy0 ? oy0 + r0 : xy0 + r0, dy0) : 0u;
+                const uint32_t m1 = col1 ? entries(n0 + ig1 * gimg, xy0 + r1, false) : 0u;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const uint32_t off = at0 + (uint32_t)((i >> a.lgS) * img0 + (i & smask) * strip0);
+                    const v4u32 t0 = __builtin_amdgcn_raw_buffer_load_b128(src0, (int)(((m0 >> i) & 1u) ? off : OOB), 0, 0);
+                    A[i] = make_uint4(t0.x, t0.y, t0.z, t0.w);
+                }
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const uint32_t off = at1 + (uint32_t)((i >> a.lgS) * x_img + (i & smask) * x_strip);
+                    const v4u32 t1 = __builtin_amdgcn_raw_buffer_load_b128(xsrc, (int)(((m1 >> i) & 1u) ? off : OOB), 0, 0);
+                    B[i] = make_uint4(t1.x, t1.y, t1.z, t1.w);
+                }
+                kt += a.ksplit;
+                return;
+            }
             if (dy0) ok0 = oy0 + r0 < a.Ho && ox0 + q0 < a.Wo;
             else ok0 = (unsigned)(xy0 + r0) < (unsigned)a.H && (unsigned)(xx0 + q0) < (unsigned)a.W;
             ok0 = ok0 && live && use0 && n0 + ig0 * 8 < a.N;
@@ -641,12 +683,13 @@ __device__ __forceinline__ void pc_mfma_wgrad_ws_body(const uint16_t *__restrict
     }
 }
 
+template <bool STRIPS>
 __global__ void __launch_bounds__(512, 1)
 pc_mfma_wgrad_ws_kernel(const uint16_t *__restrict__ x, const uint16_t *__restrict__ dy, WgradWsArgs a,
                         const uint32_t *__restrict__ kinfo, float *__restrict__ partial, float *__restrict__ dw)
 {
     const int lin = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
-    pc_mfma_wgrad_ws_body(x, dy, a, kinfo, partial, dw, lin, (int)gridDim.x, (int)gridDim.y);
+    pc_mfma_wgrad_ws_body<STRIPS>(x, dy, a, kinfo, partial, dw, lin, (int)gridDim.x, (int)gridDim.y);
 }
 
 // The layers of a network in one launch (all of them independent once every x and dy exists): workgroup b serves
@@ -674,13 +717,13 @@ struct WgradWsGroup {
     WgradWsLayer layer[WS_GROUP_MAX];
 };
 
-__global__ void __launch_bounds__(512, 1) pc_mfma_wgrad_ws_group_kernel(WgradWsGroup g)
+template <bool STRIPS> __global__ void __launch_bounds__(512, 1) pc_mfma_wgrad_ws_group_kernel(WgradWsGroup g)
 {
     const int l = pc_batch_find(g.blk0, g.n, (int)blockIdx.x);
     const WgradWsLayer &y = g.layer[l];
     const int lin = (int)blockIdx.x - g.blk0[l];
     if (lin >= y.gx * y.gy * y.a.ksplit) return;
-    pc_mfma_wgrad_ws_body(y.x, y.dy, y.a, y.kinfo, y.partial, y.dw, lin, y.gx, y.gy);
+    pc_mfma_wgrad_ws_body<STRIPS>(y.x, y.dy, y.a, y.kinfo, y.partial, y.dw, lin, y.gx, y.gy);
 }
 
 // Plan of the wave-specialised kernel for one layer; false when the layer is outside what that kernel takes (the
@@ -705,34 +748,47 @@ static bool ws_plan(const pc_ctx *ctx, const pc_conv_desc *d, int64_t nslots, Wg
     if (xb >= ((int64_t)1 << 31) || db >= ((int64_t)1 << 31)) return false;
     const int ft = (a.F + WG_T - 1) / WG_T, ct = (a.C + WG_T - 1) / WG_T;
     a.x_bytes = (uint32_t)xb; a.dy_bytes = (uint32_t)db;
+    // The pixel tile, and the cut of the batch into groups of 8. A k-step multiplies 8 entries at a time, so a batch of 1 to 7
+    // (or a rest of 1 to 7) leaves places of every group empty; cutting the images into 2, 4 or 8 strips of rows fills them:
+    // 183 x 180, 120 -> 104, batch 2 60.8 -> 28.9 us. The strips' loads take four more instructions each, so the cut has to
+    // save a tenth of the work, and half of it where no workgroup has more than one pixel tile to begin with.
     int best_tr = 0, best_tc = 0, best_ng = 0;
-    double best_eff = -1.0;
-    const int ngroups = (a.N + 7) / 8;
-    for (int tr = 1; tr <= WS_NSLOT; ++tr)
-        for (int tc = 1; tr * tc <= WS_NSLOT; ++tc) {
-            if ((tr > a.Ho && tr > 1) || (tc > a.Wo && tc > 1)) continue;
-            const int xs1 = ((tr - 1) * st + 3) * ((tc - 1) * st + 3);
-            int ngc = WS_NSLOT / (tr * tc);
-            if (ngc > ngroups) ngc = ngroups;
-            while (ngc > 1 && ngc * xs1 > WS_XSLOTS) --ngc;
-            if (ngc * xs1 > WS_XSLOTS) continue;
-            const int nr = (a.Ho + tr - 1) / tr, nc = (a.Wo + tc - 1) / tc;
-            const double cover = (double)a.Ho * a.Wo / ((double)nr * tr * nc * tc);
-            const double fill = (double)(ngc * tr * tc) / WS_NSLOT;
-            const double halo = (double)(tr * tc) / xs1;
-            const double eff = cover * fill * (0.75 + 0.25 * halo);
-            if (eff > best_eff) { best_eff = eff; best_tr = tr; best_tc = tc; best_ng = ngc; }
+    double best_eff = -1.0, gain = 1.0;
+    for (int lg = 0; lg <= ((a.N & 7) ? 3 : 0); ++lg) {
+        const int ns = 1 << lg, sr = (a.Ho + ns - 1) / ns, ngroups = (a.N * ns + 7) / 8;
+        if ((ns - 1) * sr >= a.Ho) break;                     // every strip has rows
+        for (int tr = 1; tr <= WS_NSLOT; ++tr)
+            for (int tc = 1; tr * tc <= WS_NSLOT; ++tc) {
+                if ((tr > sr && tr > 1) || (tc > a.Wo && tc > 1)) continue;
+                const int xs1 = ((tr - 1) * st + 3) * ((tc - 1) * st + 3);
+                int ngc = WS_NSLOT / (tr * tc);
+                if (ngc > ngroups) ngc = ngroups;
+                while (ngc > 1 && ngc * xs1 > WS_XSLOTS) --ngc;
+                if (ngc * xs1 > WS_XSLOTS) continue;
+                const int nr = (sr + tr - 1) / tr, nc = (a.Wo + tc - 1) / tc;
+                const double cover = (double)a.Ho * a.Wo / ((double)ns * nr * tr * nc * tc);
+                const double fill = (double)(ngc * tr * tc) / WS_NSLOT;
+                const double halo = (double)(tr * tc) / xs1;
+                const double groups = (a.N & 7) ? (double)a.N * ns / (8.0 * ngc * ((ngroups + ngc - 1) / ngc)) : 1.0;
+                const double eff = cover * fill * groups * (0.75 + 0.25 * halo);
+                if (eff > best_eff * (lg && a.lgS != lg ? gain : 1.0)) { best_eff = eff; best_tr = tr; best_tc = tc; best_ng = ngc; a.lgS = lg; }
+            }
+        if (lg == 0) {
+            if (best_eff < 0.0) return false;
+            const int64_t tiles = (int64_t)((ngroups + best_ng - 1) / best_ng) * ((a.Ho + best_tr - 1) / best_tr) * ((a.Wo + best_tc - 1) / best_tc);
+            gain = tiles * ft * ct > ctx->num_cu ? 1.1 : 1.5;
         }
-    if (best_eff < 0.0) return false;
+    }
+    a.SR = (a.Ho + (1 << a.lgS) - 1) >> a.lgS;
     a.TR = best_tr; a.TC = best_tc; a.npos = a.TR * a.TC; a.ng = best_ng;
     a.IR = (a.TR - 1) * st + 3; a.IC = (a.TC - 1) * st + 3;
     a.xs_per_g = a.IR * a.IC;
     a.xslots = (a.ng * a.xs_per_g + 7) / 8 * 8;
     if (a.xslots > WS_XSLOTS) return false;
     a.xplane = a.xslots * 16 + 16;
-    a.tiles_r = (a.Ho + a.TR - 1) / a.TR;
+    a.tiles_r = (a.SR + a.TR - 1) / a.TR;
     a.tiles_c = (a.Wo + a.TC - 1) / a.TC;
-    const int tiles_n = (ngroups + a.ng - 1) / a.ng;
+    const int tiles_n = (((a.N << a.lgS) + 7) / 8 + a.ng - 1) / a.ng;
     const int64_t nkt = (int64_t)tiles_n * a.tiles_r * a.tiles_c;
     if (nkt * (a.tiles_r > a.tiles_c ? a.tiles_r : a.tiles_c) >= ((int64_t)1 << 31)) return false;
     a.n_ktiles = (int)nkt;
@@ -757,8 +813,9 @@ static pc_status ws_set_lds_attr(pc_ctx *ctx)
 {
     static pc_per_device_once attr;
     if (pc_once_pending(attr, ctx->device)) {
-        PC_HIP(ctx, hipFuncSetAttribute((const void *)pc_mfma_wgrad_ws_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, WS_LDS_MAX));
-        PC_HIP(ctx, hipFuncSetAttribute((const void *)pc_mfma_wgrad_ws_group_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, WS_LDS_MAX));
+        for (const void *f : {(const void *)pc_mfma_wgrad_ws_kernel<false>, (const void *)pc_mfma_wgrad_ws_kernel<true>,
+                              (const void *)pc_mfma_wgrad_ws_group_kernel<false>, (const void *)pc_mfma_wgrad_ws_group_kernel<true>})
+            PC_HIP(ctx, hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, WS_LDS_MAX));
         pc_once_done(attr, ctx->device);
     }
     return PC_OK;
@@ -790,8 +847,10 @@ static pc_status pc_mfma_bwd_weight_ws(pc_ctx *ctx, const pc_conv_desc *d, const
     }
     pc_status s = ws_set_lds_attr(ctx);
     if (s != PC_OK) return s;
-    hipLaunchKernelGGL(pc_mfma_wgrad_ws_kernel, dim3((unsigned)ct, (unsigned)ft, (unsigned)ks), dim3(512), lds, ctx->stream,
-                       (const uint16_t *)x, (const uint16_t *)dy, a, pk->v.kinfo, (float *)scr, dw);
+    const dim3 grid((unsigned)ct, (unsigned)ft, (unsigned)ks);
+    const uint16_t *xq = (const uint16_t *)x, *dyq = (const uint16_t *)dy;
+    if (a.lgS) hipLaunchKernelGGL(pc_mfma_wgrad_ws_kernel<true>, grid, dim3(512), lds, ctx->stream, xq, dyq, a, pk->v.kinfo, (float *)scr, dw);
+    else hipLaunchKernelGGL(pc_mfma_wgrad_ws_kernel<false>, grid, dim3(512), lds, ctx->stream, xq, dyq, a, pk->v.kinfo, (float *)scr, dw);
     *launched = true;
     pc_note_kernel(ctx, "pc_mfma_wgrad_ws_kernel");
     s = pc_hip_check(ctx, hipGetLastError(), "MFMA bwd_weight (wave-specialised) launch");
@@ -967,13 +1026,16 @@ pc_status pc_mfma_bwd_weight_group(pc_ctx *ctx, int n, const pc_conv_desc *d, co
     std::vector<WgradReduceItem> red;
     std::vector<int64_t> red_nslots;
     std::vector<const pc_packed *> red_pk;
-    for (size_t i0 = 0; i0 < items.size(); i0 += WS_GROUP_MAX) {
-        const int m = (int)(items.size() - i0 < WS_GROUP_MAX ? items.size() - i0 : WS_GROUP_MAX);
+    // whole-image layers and layers in strips run different kernels (the layers of a network share the batch: mostly one)
+    std::stable_partition(items.begin(), items.end(), [](const Item &it) { return it.a.lgS == 0; });
+    for (size_t i0 = 0, m = 0; i0 < items.size(); i0 += m) {
+        const bool strips = items[i0].a.lgS > 0;
+        for (m = 1; m < WS_GROUP_MAX && i0 + m < items.size() && (items[i0 + m].a.lgS > 0) == strips;) ++m;
         WgradWsGroup g;
         memset(&g, 0, sizeof(g));
-        g.n = m;
+        g.n = (int)m;
         size_t lds = 0;
-        for (int i = 0; i < m; ++i) {
+        for (size_t i = 0; i < m; ++i) {
             const Item &it = items[i0 + i];
             WgradWsLayer &y = g.layer[i];
             y.a = it.a;
@@ -1000,7 +1062,8 @@ pc_status pc_mfma_bwd_weight_group(pc_ctx *ctx, int n, const pc_conv_desc *d, co
                 red_pk.push_back(pk[it.l]);
             }
         }
-        hipLaunchKernelGGL(pc_mfma_wgrad_ws_group_kernel, dim3((unsigned)g.blk0[m]), dim3(512), lds, ctx->stream, g);
+        if (strips) hipLaunchKernelGGL(pc_mfma_wgrad_ws_group_kernel<true>, dim3((unsigned)g.blk0[m]), dim3(512), lds, ctx->stream, g);
+        else hipLaunchKernelGGL(pc_mfma_wgrad_ws_group_kernel<false>, dim3((unsigned)g.blk0[m]), dim3(512), lds, ctx->stream, g);
         pc_note_kernel(ctx, "pc_mfma_wgrad_ws_group_kernel");
         s = pc_hip_check(ctx, hipGetLastError(), "MFMA bwd_weight (several layers) launch");
         if (s != PC_OK) return s;
