@@ -179,7 +179,7 @@ __device__ __forceinline__ void pc_ks_load_mask(__amdgpu_buffer_rsrc_t msrc, con
 // off, mk: offsets and mask elements of the first half where B_T == 2 (a tile of B_T == 4 has no registers to spare for
 // them across the barrier); mask elements are used under PC_ACT_RELU_MASK only.
 template <int A_T, int B_T, int ACT>
-__device__ __forceinline__ void pc_ks_store_pixels(const f32x16 (&acc)[A_T][B_T], unsigned char *lds, const MfmaArgs &g, int w, int lane,
+__device__ __forceinline__ void pc_ks_store_pixels(const f32x16 (&acc)[A_T][B_T], unsigned char *lds, const MfmaArgs &g, int w, int pw, int lane,
                                                    int mt, int tn, int gy0, int gx0, int npix, __amdgpu_buffer_rsrc_t osrc,
                                                    __amdgpu_buffer_rsrc_t msrc, uint32_t (&off)[8], v4u32 (&mk)[8])
 {
@@ -187,7 +187,7 @@ __device__ __forceinline__ void pc_ks_store_pixels(const f32x16 (&acc)[A_T][B_T]
 #pragma unroll
     for (int half = 0; half < B_T / 2; ++half) {
         if (half > 0 || B_T == 4) {
-            pc_ks_piece_offsets<A_T, B_T>(g, w, lane, half, mt, tn, gy0, gx0, npix, off);
+            pc_ks_piece_offsets<A_T, B_T>(g, pw, lane, half, mt, tn, gy0, gx0, npix, off);
             if (ACT == PC_ACT_RELU_MASK) pc_ks_load_mask(msrc, off, mk);
         }
 #pragma unroll
@@ -227,9 +227,11 @@ pc_mfma_conv_ks_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__ o
 {
     extern __shared__ __align__(16) unsigned char lds[];
     constexpr int KSC = KC / 16;          // k-steps per chunk
-    static_assert(KSP == 4 || KSP == 1, "the MFMA wavefronts split the reduction four ways or not at all");
-    constexpr int KSW = KC / (16 * KSP);  // k-steps per chunk, tap and MFMA wavefront
-    constexpr int NV = KSP == 4 ? KS_NV : KS_NV1;   // 16-byte elements staged per loader thread and item
+    static_assert(KSP == 4 || KSP == 2 || KSP == 1, "the MFMA wavefronts split the reduction, rows and pixels, or pixels");
+    constexpr bool RED = KSP == 4;        // the wavefronts split the reduction; otherwise the tile itself:
+    constexpr int WR = KSP == 2 ? 2 : 1;  // rows of wavefronts (KSP = 2: two of 32*A_T output channels, two halves of the pixels)
+    constexpr int KSW = RED ? KC / 64 : KC / 16;  // k-steps per chunk, tap and MFMA wavefront
+    constexpr int NV = RED ? KS_NV : KS_NV1;   // 16-byte elements staged per loader thread and item
     constexpr int S = NTAPS * KSW;        // steps per item and wavefront
     constexpr int NF = S * A_T;           // A fragments per item and wavefront
     // the ring has to cover an L2 round trip in MFMA time: narrow pixel tiles issue fewer MFMAs per fragment
@@ -261,11 +263,12 @@ pc_mfma_conv_ks_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__ o
 
     // ---------------------------------------------------------------- MFMA wavefronts
     const int npix = g.TI * g.TH * g.TW;
+    const int pw = WR == 2 ? w >> 1 : w, rw = WR == 2 ? w & 1 : 0;   // this wavefront's pixels and rows
     int base[B_T];
 #pragma unroll
     for (int j = 0; j < B_T; ++j) {
         // reduction split: every wavefront covers all pixels and its own k-steps; otherwise its own pixels
-        int q = ((KSP == 1 ? w * B_T : 0) + j) * 32 + (lane & 31);
+        int q = ((RED ? 0 : pw * B_T) + j) * 32 + (lane & 31);
         if (q >= npix) q = npix - 1;
         const int ti = (int)pc_udiv((uint32_t)q, g.mg_THTW);
         const int rem = q - ti * g.TH * g.TW;
@@ -316,7 +319,7 @@ pc_mfma_conv_ks_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__ o
         gx0_ = tx * g.TW;
     };
     auto a_base = [&](int mt_, int ch_) -> int {   // byte offset of the item's first fragment for this wavefront
-        return ((mt_ * A_T * 9) * g.KS + ch_ * KSC + (KSP == 4 ? w * KSW : 0)) * 1024;
+        return (((mt_ * WR + rw) * A_T * 9) * g.KS + ch_ * KSC + (RED ? w * KSW : 0)) * 1024;
     };
     tile_of(0, mt, tn, gy0, gx0);
     int k = 0, ch = 0;
@@ -412,8 +415,8 @@ pc_mfma_conv_ks_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__ o
         v4u32 pmk[8];
         v2u32 rmk[ROUNDS][4];
         if (ch == nch - 1) {
-            if (KSP == 1 && B_T == 2) {
-                pc_ks_piece_offsets<A_T, B_T>(g, w, lane, 0, mt, tn, gy0, gx0, npix, poff);
+            if (!RED && B_T == 2) {
+                pc_ks_piece_offsets<A_T, B_T>(g, pw, lane, 0, mt * WR + rw, tn, gy0, gx0, npix, poff);
                 if (ACT == PC_ACT_RELU_MASK) pc_ks_load_mask(msrc, poff, pmk);
             } else if (KSP == 4) {
                 const int n = tn + o_ti, gy = gy0 + o_y, gx = gx0 + o_x;
@@ -433,8 +436,8 @@ pc_mfma_conv_ks_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__ o
         }
         __syncthreads();
 
-        if (KSP == 1 && ch == nch - 1)
-            pc_ks_store_pixels<A_T, B_T, ACT>(acc, lds, g, w, lane, mt, tn, gy0, gx0, npix, osrc, msrc, poff, pmk);
+        if (!RED && ch == nch - 1)
+            pc_ks_store_pixels<A_T, B_T, ACT>(acc, lds, g, w, pw, lane, mt * WR + rw, tn, gy0, gx0, npix, osrc, msrc, poff, pmk);
         if (KSP == 4 && ch == nch - 1) {
 #pragma unroll
             for (int r = 0; r < ROUNDS; ++r) {
@@ -794,7 +797,7 @@ __device__ __forceinline__ void pc_sp_mfma_role(uint16_t *__restrict__ out, cons
         }
         __syncthreads();
         if (ch == nch - 1) {
-            pc_ks_store_pixels<A_T, B_T, ACT>(acc, lds, g, w, lane, mt, tn, gy0, gx0, npix, osrc, msrc, poff, pmk);
+            pc_ks_store_pixels<A_T, B_T, ACT>(acc, lds, g, w, w, lane, mt, tn, gy0, gx0, npix, osrc, msrc, poff, pmk);
 #pragma unroll
             for (int ii = 0; ii < A_T; ++ii)
 #pragma unroll
@@ -840,6 +843,181 @@ pc_mfma_conv_sp_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__ o
         if constexpr (KC == 64) pc_sp_mfma_role<B_T, KC, ACT, true>(out, sp, g, lds, vb, G, ntile_blk, nch, lane, w);
     } else {
         pc_sp_mfma_role<B_T, KC, ACT, false>(out, sp, g, lds, vb, G, ntile_blk, nch, lane, w);
+    }
+}
+
+// ------------------------------------------------------------------ stride-2 backward-data
+// The four parity classes of input pixels (2gy + py, 2gx + px) get 4, 2, 2 and 1 of the nine taps, all from the same 2 x 2
+// neighbourhood of output gradients (gy..gy+1, gx..gx+1). One pass over a tile of (gy, gx) serves all of them: the nine taps of
+// a k-step are nine steps as in the kernel above, each into the accumulators of its class, and a B fragment read for one of
+// the four neighbours serves every tap that uses it (4, 2, 2 and 1). A tile of 32 channels x 128 * B_T positions holds
+// 4 * B_T accumulator tiles. (As four ranges of workgroups of the cooperative kernel, each staging for itself and three of
+// them with half or a quarter of the work per staged byte: 56 x 56, 128 -> 128, batch 64 40.5 us.)
+template <int B_T, int KC>
+__global__ void __launch_bounds__(512, 1)
+pc_mfma_conv_mc_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__ out, const uint16_t *__restrict__ wz, MfmaArgs g)
+{
+    extern __shared__ __align__(16) unsigned char lds[];
+    constexpr int KSC = KC / 16;
+    constexpr int PITCH = 2 * KC + 16;
+    // the nine taps in the order of the neighbour they read, (0,0), (1,1), (1,0), (0,1), and their classes 2 * py + px
+    constexpr int TAP[9] = {8, 7, 5, 4, 0, 2, 1, 6, 3}, CLS[9] = {3, 2, 1, 0, 3, 3, 2, 3, 1}, GRP[9] = {0, 0, 0, 0, 1, 2, 2, 3, 3};
+    constexpr int NF = 9 * KSC;                      // A fragments per item
+    constexpr int PFD = pc_ring_depth(NF, 12);
+    constexpr int NG = 4 * KSC;                      // B fragment groups per item, read two groups ahead
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int w = wave & 3;
+    const int G = gridDim.x;
+    int vb = blockIdx.x;
+    if ((G & 7) == 0) vb = (blockIdx.x & 7) * (G >> 3) + (blockIdx.x >> 3);
+    const int ntile_blk = (g.total_tiles - vb + G - 1) / G;
+    const int nch = g.nchunks;
+    const int I = ntile_blk * nch;
+    if (wave >= 4) {
+        pc_ks_loader_role<KC, KS_NV1>(in, g, lds, vb, G, ntile_blk, nch);
+        return;
+    }
+    const int npix = g.TI * g.TH * g.TW;
+    int base[B_T];
+#pragma unroll
+    for (int j = 0; j < B_T; ++j) {
+        int q = (w * B_T + j) * 32 + (lane & 31);
+        if (q >= npix) q = npix - 1;
+        const int ti = (int)pc_udiv((uint32_t)q, g.mg_THTW);
+        const int rem = q - ti * g.TH * g.TW;
+        const int y = (int)pc_udiv((uint32_t)rem, g.mg_TW), x = rem - y * g.TW;
+        base[j] = ((ti * g.IH + y) * g.IW + x) * PITCH + (lane >> 5) * 16;
+    }
+    const __amdgpu_buffer_rsrc_t osrc = __builtin_amdgcn_make_buffer_rsrc(out, 0, g.out_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t wsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(wz), 0, g.wz_bytes, 0x00020000);
+    const int a_voff = lane * 16, ksb = g.KS * 1024;
+    auto a_frag = [&](int item_base, int f) -> bf16x8 {   // f: compile-time fragment index inside the item
+        const v4u32 r = __builtin_amdgcn_raw_buffer_load_b128(wsrc, a_voff, item_base + TAP[f % 9] * ksb + (f / 9) * 1024, 0);
+        bf16x8 o;
+        __builtin_memcpy(&o, &r, 16);
+        return o;
+    };
+    const int goff[4] = {0, (g.IW + 1) * PITCH, g.IW * PITCH, PITCH};
+    int mt = 0, tn = 0, gy0 = 0, gx0 = 0;
+    auto tile_of = [&](int k, int &mt_, int &tn_, int &gy0_, int &gx0_) {
+        const uint32_t t = (uint32_t)(vb + k * G);
+        const uint32_t tq = pc_udiv(t, g.mg_fd), trm = t - tq * g.fdiv;
+        const uint32_t pt = g.m_fast ? tq : trm;
+        mt_ = (int)(g.m_fast ? trm : tq);
+        const uint32_t u = pc_udiv(pt, g.mg_tx);
+        const int tx = (int)(pt - u * g.tiles_x);
+        const uint32_t tnn = pc_udiv(u, g.mg_ty);
+        const int ty = (int)(u - tnn * g.tiles_y);
+        tn_ = (int)tnn * g.TI;
+        gy0_ = ty * g.TH;
+        gx0_ = tx * g.TW;
+    };
+    auto a_base = [&](int mt_, int ch_) -> int { return (mt_ * 9 * g.KS + ch_ * KSC) * 1024; };
+    tile_of(0, mt, tn, gy0, gx0);
+    int k = 0, ch = 0, ab = a_base(mt, 0);
+
+    f32x16 acc[4][B_T];
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int j = 0; j < B_T; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[c][j][r] = 0.0f;
+    bf16x8 aring[PFD];
+#pragma unroll
+    for (int f = 0; f < PFD; ++f) aring[f] = a_frag(ab, f);
+
+    __syncthreads();
+    for (int i = 0; i < I; ++i) {
+        int nk = k, nchk = ch + 1, nmt = mt, ntn = tn, ngy0 = gy0, ngx0 = gx0;
+        if (nchk == nch) {
+            nchk = 0;
+            nk = k + 1;
+            if (nk < ntile_blk) tile_of(nk, nmt, ntn, ngy0, ngx0);
+            else nchk = ch;
+        }
+        const int abn = a_base(nmt, nchk);
+        const unsigned char *xb = lds + (i & 1) * g.xbuf;
+        bf16x8 bring[3][B_T];
+        auto read_b = [&](int gi) __attribute__((always_inline)) {   // group gi of the item
+#pragma unroll
+            for (int j = 0; j < B_T; ++j)
+                bring[gi % 3][j] = *reinterpret_cast<const bf16x8 *>(xb + base[j] + goff[gi % 4] + (gi / 4) * 32);
+        };
+        read_b(0);
+        read_b(1);
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            const int e = f % 9, gi = (f / 9) * 4 + GRP[e];
+            const bool opens = e == 0 || GRP[e] != GRP[e - (e > 0)];
+            if (opens && gi + 2 < NG) read_b(gi + 2);
+            const bf16x8 anow = aring[f % PFD];
+            const int nf = f + PFD;
+            aring[f % PFD] = nf < NF ? a_frag(ab, nf < NF ? nf : 0) : a_frag(abn, nf < NF ? 0 : nf - NF);
+#pragma unroll
+            for (int j = 0; j < B_T; ++j)
+                acc[CLS[e]][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(anow, bring[gi % 3][j], acc[CLS[e]][j], 0, 0, 0);
+#pragma unroll
+            for (int m = 0; m < B_T; ++m) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);       // one MFMA
+                __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);       // address arithmetic
+                if (opens) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                if (m == 0) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        __syncthreads();
+        if (ch == nch - 1) {
+            // End of a tile: a wavefront's 32 * B_T positions of every class through its private LDS rows (32 channels, 80-byte
+            // pitch), read back 4 lanes to a position.
+            constexpr uint32_t OOB_OUT = 0x80000000u;
+            unsigned char *stg = lds + g.red_off + w * (32 * B_T * 80);
+            const int m = mt * 32 + (lane & 3) * 8;
+            uint32_t off[2 * B_T];
+            bool last_y[2 * B_T], last_x[2 * B_T];
+#pragma unroll
+            for (int it = 0; it < 2 * B_T; ++it) {
+                const int q = w * B_T * 32 + it * 16 + (lane >> 2);
+                const int ti = (int)pc_udiv((uint32_t)q, g.mg_THTW);
+                const int rem = q - ti * g.TH * g.TW;
+                const int y = (int)pc_udiv((uint32_t)rem, g.mg_TW), x = rem - y * g.TW;
+                const int n = tn + ti, gy = gy0 + y, gx = gx0 + x;
+                const bool ok = q < npix && n < g.N && gy < g.GH && gx < g.GW && m < g.out_CH;
+                off[it] = ok ? (uint32_t)((n * g.out_H + 2 * gy) * g.out_W + 2 * gx) * (uint32_t)(g.out_CH * 2) + (uint32_t)(m * 2) : OOB_OUT;
+                last_y[it] = 2 * gy + 1 >= g.out_H;
+                last_x[it] = 2 * gx + 1 >= g.out_W;
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+#pragma unroll
+                for (int j = 0; j < B_T; ++j)
+#pragma unroll
+                    for (int q4 = 0; q4 < 4; ++q4) {
+                        uint2 pkd;
+                        pkd.x = pc_pack_bf16x2(acc[c][j][q4 * 4 + 0], acc[c][j][q4 * 4 + 1]);
+                        pkd.y = pc_pack_bf16x2(acc[c][j][q4 * 4 + 2], acc[c][j][q4 * 4 + 3]);
+                        *reinterpret_cast<uint2 *>(stg + (j * 32 + (lane & 31)) * 80 + (q4 * 8 + (lane >> 5) * 4) * 2) = pkd;
+                    }
+                const uint32_t cls_off = (uint32_t)(((c >> 1) * g.out_W + (c & 1)) * g.out_CH * 2);
+#pragma unroll
+                for (int it = 0; it < 2 * B_T; ++it) {
+                    const uint4 v = *reinterpret_cast<const uint4 *>(stg + (it * 16 + (lane >> 2)) * 80 + (lane & 3) * 16);
+                    const bool no = off[it] == OOB_OUT || ((c >> 1) && last_y[it]) || ((c & 1) && last_x[it]);
+                    const v4u32 pv = {v.x, v.y, v.z, v.w};
+                    __builtin_amdgcn_raw_buffer_store_b128(pv, osrc, (int)(no ? OOB_OUT : off[it] + cls_off), 0, 0);
+                }
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+#pragma unroll
+                for (int j = 0; j < B_T; ++j)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[c][j][r] = 0.0f;
+        }
+        k = nk; ch = nchk; mt = nmt; tn = ntn; gy0 = ngy0; gx0 = ngx0;
+        ab = abn;
     }
 }
 
@@ -895,7 +1073,7 @@ static hipError_t launch_sp(int device, hipStream_t st, int grid, size_t lds, co
 }
 
 // ksp = 4: the MFMA wavefronts split the reduction of a tile of 32*bt pixels; ksp = 1: they split a tile of 128*bt pixels (no
-// reduction across wavefronts).
+// reduction across wavefronts); ksp = 2: two halves of 64*at output channels, two of 64*bt pixels.
 // The kernels of this file that a launch can take, by override code. The last three columns are the constants of the time
 // estimate below.
 struct KsCand { int code, at, bt, ksp, kc; double mfma, item, tile; };
@@ -906,6 +1084,10 @@ static const KsCand kKs[] = {
     {16, 2, 2, 1, 32, 1.35, 283, 2811},  {17, 2, 4, 1, 16, 1.22, 279, 5427},  {18, 2, 2, 1, 16, 1.47, 476, 2795},
     {19, 1, 4, 1, 32, 1.19, 582, 4713},  {20, 2, 2, 1, 64, 1.15, 361, 3048},  {24, 1, 2, 1, 64, 0.90, 1340, 2540},
     {25, 1, 2, 1, 32, 1.46, 699, 2702},  {26, 1, 4, 1, 16, 1.02, 940, 4807},
+    // two rows of wavefronts: 128 output channels x 128 and 256 pixels. For stride 2 only, where a tile's input is four times its
+    // pixels and is then staged for twice the channels (56 x 56, 128 -> 128, batch 64 33.8 -> 26.5 us); at stride 1 the weights
+    // weigh more and 64 rows are faster everywhere.
+    {30, 2, 2, 2, 32, 1.41, 545, 2146},  {31, 2, 4, 2, 16, 1.38, 483, 4517},
     {13, 2, 4, 1, 32, 0, 0, 0},          // by override only: the 256-pixel tiles and the 16-channel chunks beat it everywhere
 };
 static const int kNumKs = sizeof(kKs) / sizeof(kKs[0]);
@@ -914,9 +1096,9 @@ static const int kNumKs = sizeof(kKs) / sizeof(kKs[0]);
 static bool plan_ks(const MfmaArgs &g, int ext, const KsCand &cand, MfmaArgs *out, size_t *lds_bytes, double *est, int num_cu)
 {
     const int at = cand.at, bt = cand.bt, ksp = cand.ksp, kc = cand.kc;
-    const int pitch = 2 * kc + 16, parts = kc / 8, nv = ksp == 4 ? KS_NV : KS_NV1;
+    const int pitch = 2 * kc + 16, parts = kc / 8, nv = ksp == 4 ? KS_NV : KS_NV1, rows = 32 * at * (ksp == 2 ? 2 : 1);
     MfmaArgs t = g;
-    pc_plan_mfma_tiles(&t, (ksp == 4 ? 32 : 128) * bt, ext);
+    pc_plan_mfma_tiles(&t, (ksp == 4 ? 32 : 128 / ksp) * bt, ext);
     const int nt = at * bt, nown = nt >= 4 ? 4 : nt;
     const int red_bytes = ksp == 4 ? (nt >= 4 ? nt / 4 : 1) * nown * 12288 : 4 * 64 * 144;   // reduction area / store staging
     // staged pixels: within the loader's registers (nv 16-byte elements per thread) and within LDS
@@ -936,7 +1118,7 @@ static bool plan_ks(const MfmaArgs &g, int ext, const KsCand &cand, MfmaArgs *ou
     t.red_off = 2 * t.xbuf;
     *lds_bytes = (size_t)t.red_off + (size_t)red_bytes;
     if (*lds_bytes > KS_LDS_MAX) return false;
-    t.m_tiles = (g.out_CH + 32 * at - 1) / (32 * at);
+    t.m_tiles = (g.out_CH + rows - 1) / rows;
     const int64_t p_tiles = (int64_t)((t.N + t.TI - 1) / t.TI) * t.tiles_y * t.tiles_x;
     const int64_t total = p_tiles * t.m_tiles;
     if (total > (1 << 30)) return false;
@@ -971,7 +1153,7 @@ static bool plan_ks(const MfmaArgs &g, int ext, const KsCand &cand, MfmaArgs *ou
     // the fastest of a shape; the rule it replaces, made for channel counts from 64 up, 22 %.
     const double rounds = (double)((total + num_cu - 1) / num_cu);
     const double mfma = 9.0 * (kc / 16) * at * bt * 32.0 / (ksp == 4 ? 4 : 1) * cand.mfma, stage = t.nelem * 16.0 * 0.0418;
-    const double end = cand.tile + 64.0 * at * t.TI * t.TH * t.TW * 0.0143;
+    const double end = cand.tile + 2.0 * rows * t.TI * t.TH * t.TW * 0.0143;
     const double busy = rounds * (t.nchunks * ((mfma > stage ? mfma : stage) + cand.item) + end) / 2000.0;
     const int pieces = t.nchunks * (g.in_CH < 32 ? g.in_CH : 32);
     const double bytes = 2.0 * ((double)p_tiles * HP * (pieces > g.in_CH ? pieces : g.in_CH)) + (double)out_bytes;
@@ -1016,7 +1198,7 @@ pc_status pc_run_mfma_conv_ws(pc_ctx *ctx, int pcfg, const MfmaArgs &g0, int ext
     double best_est = 0.0;
     int best_k = -1;
     for (int k = 0; k < kNumKs; ++k) {
-        if (pcfg >= 7 ? pcfg != kKs[k].code : kKs[k].tile == 0) continue;
+        if (pcfg >= 7 ? pcfg != kKs[k].code : kKs[k].tile == 0 || (kKs[k].ksp == 2 && g0.lstep != 2)) continue;
         MfmaArgs t;
         size_t lds;
         double est;
@@ -1056,10 +1238,70 @@ pc_status pc_run_mfma_conv_ws(pc_ctx *ctx, int pcfg, const MfmaArgs &g0, int ext
     KS_CASE(27, 1, 2, 4, 128)
     KS_CASE(28, 1, 4, 4, 64)
     KS_CASE(29, 1, 2, 4, 64)
+    KS_CASE(30, 2, 2, 2, 32)
+    KS_CASE(31, 2, 4, 2, 16)
     default: return pc_fail(ctx, PC_ERR_UNSUPPORTED, "MFMA conv: no kernel has code %d", c.code);
 #undef KS_CASE
     }
     *launched = true;
     pc_note_kernel(ctx, "pc_mfma_conv_ks_kernel<%d, %d, 9, %d, %d, %d>", c.at, c.bt, c.kc, c.ksp, act);
     return pc_hip_check(ctx, e, "MFMA conv (wave-specialised) launch");
+}
+
+// Stride-2 backward-data in one pass over the four parity classes. g0: the class grid (GH x GW positions), the output gradient
+// as input, 2 x 2 neighbours. pcfg: -1 or one of the codes below.
+pc_status pc_run_mfma_conv_mc(pc_ctx *ctx, int pcfg, const MfmaArgs &g0, const uint16_t *in, uint16_t *out, const uint16_t *wz, bool *launched)
+{
+    *launched = false;
+    // (constants of the time estimate from the measured times of 171 layer shapes, 7 % rms)
+    static const KsCand kMc[] = {
+        {32, 1, 2, 1, 64, 1.24, 321, 3878}, {33, 1, 2, 1, 32, 1.37, 529, 3823}, {34, 1, 2, 1, 16, 1.63, 719, 3829},
+        {35, 1, 1, 1, 64, 1.66, 934, 3251}, {36, 1, 1, 1, 32, 1.64, 901, 2974},
+    };
+    MfmaArgs best;
+    size_t best_lds = 0;
+    double best_est = 0.0;
+    int best_code = -1;
+    for (const KsCand &c : kMc) {
+        if (pcfg >= 0 && pcfg != c.code) continue;
+        MfmaArgs t;
+        size_t lds;
+        double est;
+        if (!plan_ks(g0, 2, c, &t, &lds, &est, ctx->num_cu)) continue;
+        if (best_code < 0 || est < best_est) { best = t; best_lds = lds; best_est = est; best_code = c.code; }
+    }
+    if (best_code < 0) return PC_OK;
+    // Layers of few workgroups: the cooperative kernel, which spreads the four classes over workgroups of their own, takes
+    // about 4.2 us and 1.4 us per 64-channel chunk for every 1.4 workgroups a CU gets (0.7 us up to 16 channels).
+    if (pcfg < 0) {
+        const bool few = g0.in_CH <= 16;
+        MfmaArgs t = g0;
+        pc_plan_mfma_tiles(&t, few ? 128 : 64, 2);
+        const double wgs = 4.0 * ((t.N + t.TI - 1) / t.TI) * t.tiles_y * t.tiles_x * ((g0.out_CH + 63) / 64) / (ctx->num_cu * (few ? 1.0 : 1.4));
+        if (4.2 + (few ? 0.7 : 1.4 * ((g0.in_CH + 63) / 64)) * (wgs > 1.0 ? wgs : 1.0) < best_est) return PC_OK;
+    }
+    best.wz_bytes = (uint32_t)((size_t)((best.out_CH + 127) / 128 * 4) * 9 * best.KS * 1024);
+    const int grid = best.total_tiles < ctx->num_cu ? best.total_tiles : ctx->num_cu;
+    auto launch = [&](auto kernel, pc_per_device_once &attr) -> hipError_t {
+        if (pc_once_pending(attr, ctx->device)) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, KS_LDS_MAX);
+            if (e != hipSuccess) return e;
+            pc_once_done(attr, ctx->device);
+        }
+        hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(512), best_lds, ctx->stream, in, out, wz, best);
+        return hipGetLastError();
+    };
+    static pc_per_device_once attr[5];
+    hipError_t e;
+    int bt, kc;
+    switch (best_code) {
+    case 32: bt = 2; kc = 64; e = launch(&pc_mfma_conv_mc_kernel<2, 64>, attr[0]); break;
+    case 33: bt = 2; kc = 32; e = launch(&pc_mfma_conv_mc_kernel<2, 32>, attr[1]); break;
+    case 34: bt = 2; kc = 16; e = launch(&pc_mfma_conv_mc_kernel<2, 16>, attr[2]); break;
+    case 35: bt = 1; kc = 64; e = launch(&pc_mfma_conv_mc_kernel<1, 64>, attr[3]); break;
+    default: bt = 1; kc = 32; e = launch(&pc_mfma_conv_mc_kernel<1, 32>, attr[4]); break;
+    }
+    *launched = true;
+    pc_note_kernel(ctx, "pc_mfma_conv_mc_kernel<%d, %d>", bt, kc);
+    return pc_hip_check(ctx, e, "MFMA conv (stride-2 backward-data) launch");
 }
