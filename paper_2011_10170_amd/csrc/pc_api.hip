@@ -141,11 +141,6 @@ extern "C" pc_status pc_create(pc_ctx **out, int device, void *hip_stream)
     ctx->ref->refs.store(1);
     ctx->ref->stream = ctx->stream;
     ctx->ref->open = true;
-    if (hipHostMalloc((void **)&ctx->nnz_pinned, sizeof(int64_t), hipHostMallocDefault) != hipSuccess) {
-        delete ctx->ref;
-        delete ctx;
-        return PC_ERR_NOMEM;
-    }
     *out = ctx;
     return PC_OK;
 }
@@ -163,7 +158,6 @@ extern "C" void pc_destroy(pc_ctx *ctx)
     if (ctx->scratch) (void)hipFree(ctx->scratch);
     for (int i = 0; i < ctx->n_retired; ++i) (void)hipFree(ctx->retired[i]);
     free(ctx->retired);
-    if (ctx->nnz_pinned) (void)hipHostFree(ctx->nnz_pinned);
     delete ctx;
 }
 

@@ -16,6 +16,7 @@
 // offsets of buffer loads and in immediate offsets of LDS reads, let the range check of a buffer load supply the zeros of
 // the padding, and copy no operand registers.
 #include "pc_mfma.h"
+#include <type_traits>
 
 // ------------------------------------------------------------------ forward / backward-data
 // A workgroup computes 32*WM output channels x 32*WN pixels, one 32 x 32 tile per wavefront (WK = 4: one tile, the four
@@ -23,7 +24,9 @@
 // over (image, row, column of a strip of Ws columns), so a tile is full whatever the map size; what it reads is a
 // range of rows of the "virtual" image in which the images follow each other with one zero row between them.
 // Several workgroups share a CU: the staging of one runs under the matrix instructions of the others.
-#define F32_NE 6        // 16-byte elements staged per thread and chunk
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+// 16-byte elements staged per thread and chunk, tiles of T = 32 or 16
+__host__ __device__ constexpr int f32_ne(int T) { return T == 32 ? 6 : 8; }
 
 struct F32Class {
     int32_t GH, GW, ooff_y, ooff_x;   // pixel grid of this launch part; output pixel = grid * oscale + ooff
@@ -46,11 +49,11 @@ struct F32ConvArgs {
     F32Class cls[4];
 };
 
-template <int NTAPS, int WM, int WN, int WK, bool VEC>
+template <int T, int NTAPS, int WM, int WN, int WK, bool VEC>
 __device__ __forceinline__ void pc_f32_conv_body(const float *__restrict__ in, float *__restrict__ out, const float *__restrict__ wz,
                                                  const F32ConvArgs &g, const F32Class &c, int b, unsigned char *lds)
 {
-    constexpr int BN = 32 * WN;
+    constexpr int BN = T * WN, FR = T == 32 ? 8 : 16, F32_NE = f32_ne(T);   // FR: channels per fragment
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wk = wave % WK, wn = (wave / WK) % WN, wm = wave / WK / WN;
@@ -60,10 +63,10 @@ __device__ __forceinline__ void pc_f32_conv_body(const float *__restrict__ in, f
     const int r0 = p0 / c.Ws, n0 = r0 / c.GH, v0 = n0 * g.HP + (r0 - n0 * c.GH) * g.lstep;
 
     // this lane's pixel
-    const int p = p0 + wn * 32 + (lane & 31);
+    const int p = p0 + wn * T + (lane & (T - 1));
     const int pr = (p < np ? p : np - 1) / c.Ws, px = (p < np ? p : np - 1) - pr * c.Ws;
     const int pn = pr / c.GH, py = pr - pn * c.GH;
-    const unsigned char *bp = lds + ((pn * g.HP + py * g.lstep - v0) * c.IW + px * g.lstep) * g.pitch + (lane >> 5) * 16;
+    const unsigned char *bp = lds + ((pn * g.HP + py * g.lstep - v0) * c.IW + px * g.lstep) * g.pitch + lane / T * 16;
 
     // elements this thread stages: 16 bytes (4 channels, the same ones of every pixel) of a pixel each; pix = the input
     // pixel counted from the first image of the tile
@@ -125,22 +128,33 @@ __device__ __forceinline__ void pc_f32_conv_body(const float *__restrict__ in, f
     };
 
     // weight fragments: [row tile][tap][fragment][64 lanes][4], a row tile past the last reads the last (not stored)
+    // (tiles of 16 rows: lane l holds row l % 16 and entries 4 * (l / 16) .. + 3 of 16, two fragments of the 32-row operand;
+    // where the second one does not exist its lanes read zeros)
     int rt = mt * WM + wm;
-    const int rt_last = (g.out_CH - 1) >> 5;
+    const int rt_last = (g.out_CH - 1) / T;
     if (rt > rt_last) rt = rt_last;
-    const __amdgpu_buffer_rsrc_t wsrc =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(wz + (int64_t)rt * 9 * g.KS * 256), 0, 9 * g.KS * 1024, 0x00020000);
+    const __amdgpu_buffer_rsrc_t wsrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float *>(wz + (int64_t)(T == 32 ? rt : rt >> 1) * 9 * g.KS * 256), 0, 9 * g.KS * 1024, 0x00020000);
+    const int KSF = T == 32 ? g.KS : (g.KS + 1) >> 1;
+    const uint32_t wvo = T == 32 ? lane * 16u : (lane >> 5) * 1024u + ((rt & 1) * 16 + (lane & 15) + (lane & 16) * 2) * 16u;
+    const uint32_t wvo_last = T == 32 || !(g.KS & 1) || lane < 32 ? wvo : OOB;
     auto a_load = [&](int tap, int kf) -> float4 {
         const int tw = NTAPS == 9 ? tap : c.tap_w[tap & 3];
-        const v4u32 u = __builtin_amdgcn_raw_buffer_load_b128(wsrc, lane * 16, (tw * g.KS + (kf < g.KS ? kf : g.KS - 1)) * 1024, 0);
+        const int k = kf < KSF - 1 ? kf : KSF - 1;
+        const uint32_t vo = T == 32 ? wvo : kf < KSF - 1 ? wvo : wvo_last;
+        const v4u32 u = __builtin_amdgcn_raw_buffer_load_b128(wsrc, (int)vo, (tw * g.KS + k * (FR / 8)) * 1024, 0);
         float4 r;
         __builtin_memcpy(&r, &u, 16);
         return r;
     };
     auto tap_off = [&](int tap) -> int { return NTAPS == 9 ? c.o0 + tap / 3 * c.dr + tap % 3 * c.ds : c.tap_off[tap & 3]; };
-    f32x16 acc;
+    typename std::conditional<T == 32, f32x16, f32x4>::type acc;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
+    for (int i = 0; i < T * T / 64; ++i) acc[i] = 0.0f;
+    auto mma = [&](float a, float bv) {
+        if constexpr (T == 32) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a, bv, acc, 0, 0, 0);
+        else acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a, bv, acc, 0, 0, 0);
+    };
     issue(0);
     // One fragment of weights per tap is in flight (a wavefront's loads retire in order: the nine cover the round trip of
     // the next chunk's pixels, which are requested in front of them); LDS reads run one tap ahead. The scheduling barriers
@@ -148,7 +162,7 @@ __device__ __forceinline__ void pc_f32_conv_body(const float *__restrict__ in, f
     float4 ar[NTAPS];
 #pragma unroll
     for (int t = 0; t < NTAPS; ++t) ar[t] = a_load(t, wk);
-    const int KF = g.KC >> 3;
+    const int KF = g.KC / FR;
     constexpr int RB = NTAPS % 3 == 0 ? 3 : NTAPS % 2 == 0 ? 2 : 1;   // the pixel fragments rotate without copies from one fragment to the next
     float4 bq[RB];
     const unsigned char *bt[NTAPS];
@@ -159,29 +173,44 @@ __device__ __forceinline__ void pc_f32_conv_body(const float *__restrict__ in, f
         put(ch);
         __syncthreads();
         if (ch + 1 < g.nchunk) issue(ch + 1);
-        const int left = (g.in_CH - ch * g.KC + 7) >> 3, nf = left < KF ? left : KF;
+        const int left = (g.in_CH - ch * g.KC + FR - 1) / FR, nf = left < KF ? left : KF;
         if (wk >= nf) continue;
-        bq[0] = *reinterpret_cast<const float4 *>(bt[0] + wk * 32);
+        bq[0] = *reinterpret_cast<const float4 *>(bt[0] + wk * FR * 4);
         for (int f = wk; f < nf; f += WK) {
             const int fn = f + WK < nf ? f + WK : f;
             const int kn = f + WK < nf ? ch * KF + fn : (ch + 1) * KF + wk;   // the fragment after this one
 #pragma unroll
             for (int t = 0; t < NTAPS; ++t) {
                 const float4 a = ar[t], bv = bq[t % RB];
-                if (RB > 1) bq[(t + 1) % RB] = *reinterpret_cast<const float4 *>(t + 1 < NTAPS ? bt[t + 1 < NTAPS ? t + 1 : 0] + f * 32 : bt[0] + fn * 32);
+                if (RB > 1) bq[(t + 1) % RB] = *reinterpret_cast<const float4 *>(t + 1 < NTAPS ? bt[t + 1 < NTAPS ? t + 1 : 0] + f * FR * 4 : bt[0] + fn * FR * 4);
                 __builtin_amdgcn_sched_barrier(0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, bv.x, acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, bv.y, acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, bv.z, acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, bv.w, acc, 0, 0, 0);
+                mma(a.x, bv.x);
+                mma(a.y, bv.y);
+                mma(a.z, bv.z);
+                mma(a.w, bv.w);
                 __builtin_amdgcn_sched_barrier(0);
                 ar[t] = a_load(t, kn);        // behind its last use: the register is free
-                if (RB == 1) bq[0] = *reinterpret_cast<const float4 *>(bt[0] + fn * 32);
+                if (RB == 1) bq[0] = *reinterpret_cast<const float4 *>(bt[0] + fn * FR * 4);
             }
         }
     }
     float4 o[4];
-    if (WK > 1) {
+    if constexpr (T == 16) {
+        if (WK > 1) {
+            // the first wavefront of each pixel tile adds the partial tiles in wavefront order
+            float4 *red = reinterpret_cast<float4 *>(lds);
+            __syncthreads();
+            if (wk) red[(wk * WM * WN + wave / WK) * 64 + lane] = make_float4(acc[0], acc[1], acc[2], acc[3]);
+            __syncthreads();
+            if (wk) return;
+#pragma unroll
+            for (int k = 1; k < WK; ++k) {
+                const float4 u = red[(k * WM * WN + wave / WK) * 64 + lane];
+                acc[0] += u.x; acc[1] += u.y; acc[2] += u.z; acc[3] += u.w;
+            }
+        }
+        o[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
+    } else if constexpr (WK > 1) {
         // partial tiles added in wavefront order, wavefront w finishes rows 8w .. 8w+7
         float4 *red = reinterpret_cast<float4 *>(lds);
         __syncthreads();
@@ -202,8 +231,8 @@ __device__ __forceinline__ void pc_f32_conv_body(const float *__restrict__ in, f
     if (p >= np || x0 + px >= c.GW) return;
     const int64_t opix = ((int64_t)pn * g.out_H + py * g.oscale + c.ooff_y) * g.out_W + (x0 + px) * g.oscale + c.ooff_x;
 #pragma unroll
-    for (int q = 0; q < (WK > 1 ? 1 : 4); ++q) {
-        const int m = (mt * WM + wm) * 32 + (WK > 1 ? wk : q) * 8 + (lane >> 5) * 4;
+    for (int q = 0; q < (T == 16 || WK > 1 ? 1 : 4); ++q) {
+        const int m = (mt * WM + wm) * T + (T == 16 ? 0 : WK > 1 ? wk : q) * 8 + lane / T * 4;
         if (m >= g.out_CH) continue;
         const int64_t at = opix * g.out_CH + m;
         float v[4] = {o[q].x, o[q].y, o[q].z, o[q].w};
@@ -224,7 +253,7 @@ __device__ __forceinline__ void pc_f32_conv_body(const float *__restrict__ in, f
 }
 
 // MC: the four parity classes of a stride-2 backward-data pass (4, 2, 2 and 1 taps), each a range of workgroups.
-template <int WM, int WN, int WK, bool MC, bool VEC>
+template <int T, int WM, int WN, int WK, bool MC, bool VEC>
 __global__ void __launch_bounds__(256, 4)
 pc_f32_conv_kernel(const float *__restrict__ in, float *__restrict__ out, const float *__restrict__ wz, F32ConvArgs g)
 {
@@ -235,22 +264,20 @@ pc_f32_conv_kernel(const float *__restrict__ in, float *__restrict__ out, const 
         int k = 0;
         while (k + 1 < g.ncls && b >= g.cls[k + 1].first) ++k;
         const F32Class &c = g.cls[k];
-        if (c.ntaps == 4) pc_f32_conv_body<4, WM, WN, WK, VEC>(in, out, wz, g, c, b - c.first, lds);
-        else if (c.ntaps == 2) pc_f32_conv_body<2, WM, WN, WK, VEC>(in, out, wz, g, c, b - c.first, lds);
-        else pc_f32_conv_body<1, WM, WN, WK, VEC>(in, out, wz, g, c, b - c.first, lds);
+        if (c.ntaps == 4) pc_f32_conv_body<T, 4, WM, WN, WK, VEC>(in, out, wz, g, c, b - c.first, lds);
+        else if (c.ntaps == 2) pc_f32_conv_body<T, 2, WM, WN, WK, VEC>(in, out, wz, g, c, b - c.first, lds);
+        else pc_f32_conv_body<T, 1, WM, WN, WK, VEC>(in, out, wz, g, c, b - c.first, lds);
     } else {
-        pc_f32_conv_body<9, WM, WN, WK, VEC>(in, out, wz, g, g.cls[0], b, lds);
+        pc_f32_conv_body<T, 9, WM, WN, WK, VEC>(in, out, wz, g, g.cls[0], b, lds);
     }
 }
 
 // ---- plan and launch
 // Strips and staged extent of one part for BN pixels per tile; false when it does not fit the staging registers.
-static bool f32_plan_class(const F32ConvArgs &g, F32Class *c, int ext, int BN)
+static bool f32_plan_class(const F32ConvArgs &g, F32Class *c, int ext, int BN, int NE)
 {
     int64_t best = -1;
-    for (int ns = 1; ns <= c->GW; ++ns) {
-        const int Ws = (c->GW + ns - 1) / ns;
-        if ((c->GW + Ws - 1) / Ws != ns) continue;
+    for (int ns = 1, Ws = c->GW; Ws >= 1; ns = Ws > 1 ? (c->GW + Ws - 2) / (Ws - 1) : 1, Ws = Ws > 1 ? (c->GW + ns - 1) / ns : 0) {
         const int64_t np = (int64_t)g.N * c->GH * Ws;
         if (np + BN >= ((int64_t)1 << 31)) continue;
         const int rows = BN % Ws == 0 ? BN / Ws : (BN + Ws - 2) / Ws + 1;         // output rows a tile touches at most
@@ -259,7 +286,7 @@ static bool f32_plan_class(const F32ConvArgs &g, F32Class *c, int ext, int BN)
         const int64_t vr = (int64_t)g.N * g.HP + 8;
         if (vr >= ((int64_t)1 << 31)) return false;
         const int R = (rows - 1) * g.lstep + cross * (gap > 0 ? gap : 0) + ext, IW = (Ws - 1) * g.lstep + ext;
-        if ((int64_t)R * IW * (g.KC / 4) > 256 * F32_NE) continue;
+        if ((int64_t)R * IW * (g.KC / 4) > 256 * NE) continue;
         // columns past the map cost matrix work, staged pixels cost less
         const int64_t cost = (int64_t)ns * Ws * (8 * BN + R * IW);
         if (best < 0 || cost < best) {
@@ -271,8 +298,35 @@ static bool f32_plan_class(const F32ConvArgs &g, F32Class *c, int ext, int BN)
     return best >= 0;
 }
 
-struct F32Shape { int wm, wn, wk; };
-static const F32Shape kF32Shapes[] = {{2, 2, 1}, {1, 4, 1}, {4, 1, 1}, {1, 1, 4}};
+// Tile shapes: a workgroup's tile is T*wm output channels x T*wn pixels, wk wavefronts split its reduction; `mma` is the time of
+// its matrix instructions in units of their issue cycles. Tiles of 16 x 16 have a quarter of the work per workgroup: layers
+// with few pixels fill the chip (2 x 11 x 13, 360 -> 24 forward: 9 tiles of 32 took 21.9 us, 42 of 16 take 9.3), and
+// layers of up to 16 output channels do half the matrix work (45 x 44, 384 -> 16: 21.7 -> 12 us). The larger tiles read
+// fewer weights and pixels per multiply-add and win where there are enough of them.
+struct F32Shape { int t, wm, wn, wk; double mma; };
+static const F32Shape kF32Shapes[] = {{32, 2, 2, 1, 0.959}, {32, 1, 4, 1, 0.941}, {32, 4, 1, 1, 0.937}, {32, 1, 1, 4, 0.830},
+                                      {16, 1, 4, 1, 0.895}, {16, 1, 2, 2, 0.847}, {16, 1, 1, 4, 0.773}};
+
+// Time estimate in us, least squares over 4800 measured launches (240 layers of 1 .. 100 images, 4 .. 224 pixels wide, 3 .. 500 channels,
+// both passes and strides; the choice is 0.8 % behind the best shape on average, on other layers too, the worst one 19 %):
+// a workgroup costs its matrix cycles, its start and end, staging per 256 elements of 16 bytes, and per chunk a round trip
+// that the other workgroups of the CU hide; then the output and the weights from the L2s. Chunks of less than a cache line fetch
+// lines again where the pixels under way exceed the L2s.
+static double f32_time(const pc_ctx *ctx, const F32Shape &s, const F32ConvArgs &t, int64_t blocks, double taps, double staged, size_t lds, int64_t out_bytes)
+{
+    const int fr = s.t == 32 ? 8 : 16, left = t.in_CH - (t.nchunk - 1) * t.KC;
+    const int frags = (t.nchunk - 1) * (t.KC / fr / s.wk) + ((left + fr - 1) / fr + s.wk - 1) / s.wk;
+    const double n = (double)blocks / ctx->num_cu, up = (double)((blocks + ctx->num_cu - 1) / ctx->num_cu);
+    int occ = (int)(160 * 1024 / lds);
+    if (occ > 4) occ = 4;
+    const double conc = up < occ ? up : occ;
+    const double per = taps * frags * (s.t == 32 ? 256.0 : 128.0) * s.mma + staged / 256.0 * t.nchunk * 119.0 + 1039.0 + 1037.0 * t.nchunk / conc;
+    const double wbytes = (double)blocks * s.t * s.wm * taps * ((t.in_CH + 7) / 8 * 32);
+    double us = 4.0 + (up <= 4.0 ? up : n + 0.68) * per / 2350.0 + (double)out_bytes / 5.5e6 + wbytes / 140e6;
+    const double res = n < occ ? (double)blocks : (double)occ * ctx->num_cu;
+    if (t.KC < 32 && staged * 16.0 * t.nchunk * res / 8 > 4e6) us += (double)blocks * staged * 16.0 * t.nchunk * (32 / t.KC - 1) / 80e6;
+    return us;
+}
 
 // g holds the tensors' extents; cls[].{GH, GW, ooff, ntaps, tap_w} and the tap positions tr, tc are set.
 static pc_status f32_run(pc_ctx *ctx, F32ConvArgs g, bool mc, int ext, const int (*tr)[9], const int (*tc)[9], const float *in, float *out,
@@ -281,32 +335,41 @@ static pc_status f32_run(pc_ctx *ctx, F32ConvArgs g, bool mc, int ext, const int
     F32ConvArgs best;
     int best_k = -1;
     int64_t best_blocks = 0;
-    double best_cost = 0.0;
+    size_t lds = 0;
+    double best_us = 0.0;
     const int c8 = (g.in_CH + 7) / 8 * 8;
-    for (int k = 0; k < 4; ++k) {
+    const int64_t out_bytes = (int64_t)g.N * g.out_H * g.out_W * g.out_CH * 4;
+    const int32_t key[PC_CHOICE_KEY] = {1, g.N, g.in_H, g.in_W, g.in_CH, g.out_H, g.out_W, g.out_CH, g.lstep, mc};
+    bool known;
+    int32_t *choice = pc_choice(ctx, key, &known);
+    for (int k = 0; k < (int)(sizeof(kF32Shapes) / sizeof(kF32Shapes[0])); ++k) {
         const F32Shape &s = kF32Shapes[k];
-        // chunks of 32 channels, shorter ones where the staged tile would not fit (four wavefronts that split the
-        // reduction take one fragment of 8 each)
-        for (int kc = 32; kc >= (s.wk > 1 ? 32 : 8); kc >>= 1) {
-            if (kc >= 2 * c8 && s.wk == 1) continue;
+        // chunks of 32 (128) channels, shorter ones where the staged tile would not fit, down to one fragment per wavefront
+        const int kc_min = (s.t == 16 ? 16 : 8) * s.wk;
+        for (int kc = s.t == 16 ? 128 : 32; kc >= kc_min; kc >>= 1) {
+            if (known ? *choice != k * 256 + kc : kc >= 2 * c8 && kc > kc_min) continue;
             F32ConvArgs t = g;
             t.KC = kc;
-            t.lparts = kc == 32 ? 3 : kc == 16 ? 2 : 1;
+            t.lparts = 0;
+            while ((4 << t.lparts) < kc) ++t.lparts;
             t.pitch = t.KC * 4 + 16;
             t.nchunk = (g.in_CH + t.KC - 1) / t.KC;
-            t.m_tiles = (g.out_CH + 32 * s.wm - 1) / (32 * s.wm);
+            t.m_tiles = (g.out_CH + s.t * s.wm - 1) / (s.t * s.wm);
             int64_t blocks = 0;
             bool ok = true;
-            double work = 0.0;
+            double taps = 0.0, staged = 0.0;                              // sums over the workgroups
+            size_t need = s.wk > 1 ? 16384 : 0;
             for (int i = 0; i < g.ncls && ok; ++i) {
                 F32Class &c = t.cls[i];
-                ok = f32_plan_class(t, &c, ext, 32 * s.wn);
+                ok = f32_plan_class(t, &c, ext, s.t * s.wn, f32_ne(s.t));
                 if (!ok) break;
-                const int ns = (c.GW + c.Ws - 1) / c.Ws;
+                const int64_t nb = (int64_t)c.tiles * ((c.GW + c.Ws - 1) / c.Ws) * t.m_tiles;
                 c.first = (int32_t)blocks;
-                blocks += (int64_t)c.tiles * ns * t.m_tiles;
+                blocks += nb;
                 if (blocks >= ((int64_t)1 << 31)) ok = false;
-                work += (double)c.tiles * ns * t.m_tiles * c.ntaps;
+                taps += (double)nb * c.ntaps;
+                staged += (double)nb * c.R * c.IW * (kc / 4);
+                if ((size_t)c.R * c.IW * t.pitch > need) need = (size_t)c.R * c.IW * t.pitch;
                 if (mc) {
                     for (int q = 0; q < c.ntaps; ++q) c.tap_off[q] = (tr[i][q] * c.IW + tc[i][q]) * t.pitch;
                 } else {                  // tap rows and columns ascend (forward) or descend (rotated)
@@ -316,47 +379,40 @@ static pc_status f32_run(pc_ctx *ctx, F32ConvArgs g, bool mc, int ext, const int
                 }
             }
             if (!ok) continue;
-            // cycles of a SIMD: 256 per fragment and tap of every workgroup it serves, plus start and end of a workgroup
-            // (hidden where several share the CU)
-            const double rounds = (double)((blocks + ctx->num_cu - 1) / ctx->num_cu);
-            const double per = work / (double)blocks * (c8 / 8) * 256.0 / s.wk + (s.wk > 1 ? 800.0 : 0.0);
-            const double cost = rounds * per + 5000.0 + (rounds > 1 ? (rounds - 1) * 600.0 : 0.0) + 100.0 * t.nchunk * rounds;
-            if (best_k < 0 || cost < best_cost) { best = t; best_k = k; best_blocks = blocks; best_cost = cost; }
-            break;
+            const double us = f32_time(ctx, s, t, blocks, taps / (double)blocks, staged / (double)blocks, need, out_bytes);
+            if (best_k < 0 || us < best_us) { best = t; best_k = k; best_blocks = blocks; best_us = us; lds = need; }
         }
     }
     if (best_k < 0) return pc_fail(ctx, PC_ERR_UNSUPPORTED, "float32 conv: no tile fits");
-    size_t lds = 0;
-    for (int i = 0; i < best.ncls; ++i) {
-        const size_t n = (size_t)best.cls[i].R * best.cls[i].IW * best.pitch;
-        if (n > lds) lds = n;
-    }
-    if (kF32Shapes[best_k].wk > 1 && lds < 16384) lds = 16384;
+    *choice = best_k * 256 + best.KC;
     const dim3 grid((unsigned)best_blocks), blk(256);
     // images a tile may touch: its first one and those the rows of a tile reach into
     int64_t span = 0;
     for (int i = 0; i < best.ncls; ++i) {
         const F32Class &c = best.cls[i];
-        const int64_t n = 2 + (32 * kF32Shapes[best_k].wn + c.Ws - 1) / c.Ws / c.GH;
+        const int64_t n = 2 + (kF32Shapes[best_k].t * kF32Shapes[best_k].wn + c.Ws - 1) / c.Ws / c.GH;
         if (n > span) span = n;
     }
     const bool vec = (g.in_CH & 3) == 0 && span * g.in_H * g.in_W * g.in_CH * 4 < ((int64_t)1 << 31);
     hipStream_t st = ctx->stream;
-#define F32_LAUNCH(WM, WN, WK)                                                                                              \
+#define F32_LAUNCH(T, WM, WN, WK)                                                                                            \
     do {                                                                                                                    \
-        if (mc && vec) hipLaunchKernelGGL((pc_f32_conv_kernel<WM, WN, WK, true, true>), grid, blk, lds, st, in, out, wz, best);   \
-        else if (mc) hipLaunchKernelGGL((pc_f32_conv_kernel<WM, WN, WK, true, false>), grid, blk, lds, st, in, out, wz, best);    \
-        else if (vec) hipLaunchKernelGGL((pc_f32_conv_kernel<WM, WN, WK, false, true>), grid, blk, lds, st, in, out, wz, best);   \
-        else hipLaunchKernelGGL((pc_f32_conv_kernel<WM, WN, WK, false, false>), grid, blk, lds, st, in, out, wz, best);           \
+        if (mc && vec) hipLaunchKernelGGL((pc_f32_conv_kernel<T, WM, WN, WK, true, true>), grid, blk, lds, st, in, out, wz, best);   \
+        else if (mc) hipLaunchKernelGGL((pc_f32_conv_kernel<T, WM, WN, WK, true, false>), grid, blk, lds, st, in, out, wz, best);    \
+        else if (vec) hipLaunchKernelGGL((pc_f32_conv_kernel<T, WM, WN, WK, false, true>), grid, blk, lds, st, in, out, wz, best);   \
+        else hipLaunchKernelGGL((pc_f32_conv_kernel<T, WM, WN, WK, false, false>), grid, blk, lds, st, in, out, wz, best);           \
     } while (0)
     switch (best_k) {
-    case 0: F32_LAUNCH(2, 2, 1); break;
-    case 1: F32_LAUNCH(1, 4, 1); break;
-    case 2: F32_LAUNCH(4, 1, 1); break;
-    default: F32_LAUNCH(1, 1, 4); break;
+    case 0: F32_LAUNCH(32, 2, 2, 1); break;
+    case 1: F32_LAUNCH(32, 1, 4, 1); break;
+    case 2: F32_LAUNCH(32, 4, 1, 1); break;
+    case 3: F32_LAUNCH(32, 1, 1, 4); break;
+    case 4: F32_LAUNCH(16, 1, 4, 1); break;
+    case 5: F32_LAUNCH(16, 1, 2, 2); break;
+    default: F32_LAUNCH(16, 1, 1, 4); break;
     }
 #undef F32_LAUNCH
-    pc_note_kernel(ctx, "pc_f32_conv_kernel<%d, %d, %d, %s, %s>", kF32Shapes[best_k].wm, kF32Shapes[best_k].wn, kF32Shapes[best_k].wk,
+    pc_note_kernel(ctx, "pc_f32_conv_kernel<%d, %d, %d, %d, %s, %s>", kF32Shapes[best_k].t, kF32Shapes[best_k].wm, kF32Shapes[best_k].wn, kF32Shapes[best_k].wk,
                    mc ? "true" : "false", vec ? "true" : "false");
     return pc_hip_check(ctx, hipGetLastError(), "float32 conv launch");
 }

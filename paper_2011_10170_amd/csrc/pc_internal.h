@@ -17,6 +17,9 @@
 #define PC_OV_BAD 0xFFFFFFFFu
 
 struct pc_stream_ref;
+#define PC_CHOICES 128
+#define PC_CHOICE_KEY 10
+
 struct pc_ctx {
     int device;
     hipStream_t stream;
@@ -34,8 +37,21 @@ struct pc_ctx {
                            // device's fixed buffer, or fails when the request exceeds it
     char last_kernel[160]; // symbol of the kernel that did the work of the last conv call (pc_last_kernel)
     pc_stream_ref *ref;
-    int64_t *nnz_pinned;   // pinned host word for reading back a pack's kernel count
+    // kernels chosen for the shapes seen last, direct mapped (an estimate over all candidates takes longer than a launch)
+    struct { int32_t key[PC_CHOICE_KEY]; int32_t kernel; } choice[PC_CHOICES];
 };
+
+// The entry of a shape in the context's table: *hit when `kernel` holds its choice, else the caller fills it in.
+// key[0] names the table's user and is not 0.
+static inline int32_t *pc_choice(pc_ctx *ctx, const int32_t (&key)[PC_CHOICE_KEY], bool *hit)
+{
+    uint32_t h = 0;
+    for (int i = 0; i < PC_CHOICE_KEY; ++i) h = (h ^ (uint32_t)key[i]) * 0x9E3779B1u;
+    auto &e = ctx->choice[(h >> 16) % PC_CHOICES];
+    *hit = memcmp(e.key, key, sizeof(key)) == 0;
+    if (!*hit) { memcpy(e.key, key, sizeof(key)); e.kernel = -1; }
+    return &e.kernel;
+}
 
 // Device-side view of a packed layer. All pointers point into one slab.
 struct PackView {
