@@ -301,7 +301,7 @@ static bool f32_plan_class(const F32ConvArgs &g, F32Class *c, int ext, int BN, i
 // Tile shapes: a workgroup's tile is T*wm output channels x T*wn pixels, wk wavefronts split its reduction; `mma` is the time of
 // its matrix instructions in units of their issue cycles. Tiles of 16 x 16 have a quarter of the work per workgroup: layers
 // with few pixels fill the chip (2 x 11 x 13, 360 -> 24 forward: 9 tiles of 32 took 21.9 us, 42 of 16 take 9.3), and
-// layers of up to 16 output channels do half the matrix work (45 x 44, 384 -> 16: 21.7 -> 12 us). The larger tiles read
+// layers of up to 16 output channels do half the matrix work (45 x 44, 384 -> 16: 21.7 -> 9.2 us). The larger tiles read
 // fewer weights and pixels per multiply-add and win where there are enough of them.
 struct F32Shape { int t, wm, wn, wk; double mma; };
 static const F32Shape kF32Shapes[] = {{32, 2, 2, 1, 0.959}, {32, 1, 4, 1, 0.941}, {32, 4, 1, 1, 0.937}, {32, 1, 1, 4, 0.830},
