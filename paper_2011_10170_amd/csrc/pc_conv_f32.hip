@@ -16,6 +16,7 @@
 // offsets of buffer loads and in immediate offsets of LDS reads, let the range check of a buffer load supply the zeros of
 // the padding, and copy no operand registers.
 #include "pc_mfma.h"
+#include <math.h>
 #include <type_traits>
 
 // ------------------------------------------------------------------ forward / backward-data
@@ -44,6 +45,7 @@ struct F32ConvArgs {
     int32_t KC, lparts, nchunk, KS;   // channels per chunk (8, 16 or 32), log2(KC / 4), chunks, fragments of 8 per tap in the operand
     int32_t pitch;                    // bytes per staged pixel
     int32_t m_tiles, ncls;
+    int32_t tail_first, tail_R;       // tiles and workgroups from tail_first on: a workgroup per part of 32 x 32; its staged rows
     int32_t act;
     const float *act_mask;
     F32Class cls[4];
@@ -51,14 +53,14 @@ struct F32ConvArgs {
 
 template <int T, int NTAPS, int WM, int WN, int WK, bool VEC>
 __device__ __forceinline__ void pc_f32_conv_body(const float *__restrict__ in, float *__restrict__ out, const float *__restrict__ wz,
-                                                 const F32ConvArgs &g, const F32Class &c, int b, unsigned char *lds)
+                                                 const F32ConvArgs &g, const F32Class &c, int rows, int mt, int strip, int p0,
+                                                 unsigned char *lds)
 {
-    constexpr int BN = T * WN, FR = T == 32 ? 8 : 16, F32_NE = f32_ne(T);   // FR: channels per fragment
+    constexpr int FR = T == 32 ? 8 : 16, F32_NE = f32_ne(T);   // FR: channels per fragment
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wk = wave % WK, wn = (wave / WK) % WN, wm = wave / WK / WN;
-    const int mt = b % g.m_tiles, pt = b / g.m_tiles;
-    const int strip = pt / c.tiles, x0 = strip * c.Ws, p0 = (pt - strip * c.tiles) * BN;
+    const int x0 = strip * c.Ws;
     const int np = g.N * c.GH * c.Ws;
     const int r0 = p0 / c.Ws, n0 = r0 / c.GH, v0 = n0 * g.HP + (r0 - n0 * c.GH) * g.lstep;
 
@@ -70,7 +72,7 @@ __device__ __forceinline__ void pc_f32_conv_body(const float *__restrict__ in, f
 
     // elements this thread stages: 16 bytes (4 channels, the same ones of every pixel) of a pixel each; pix = the input
     // pixel counted from the first image of the tile
-    const int total = (c.R * c.IW) << g.lparts;
+    const int total = (rows * c.IW) << g.lparts;
     const int part = (int)threadIdx.x & ((1 << g.lparts) - 1), q0 = (int)threadIdx.x >> g.lparts, dq = 256 >> g.lparts;
     const float *in0 = in + (int64_t)n0 * g.in_H * g.in_W * g.in_CH + part * 4;
     uint32_t pix[F32_NE];
@@ -79,7 +81,7 @@ __device__ __forceinline__ void pc_f32_conv_body(const float *__restrict__ in, f
         const int q = q0 + i * dq;
         const int iy = q / c.IW, ix = q - iy * c.IW;
         const int v = v0 + iy, n = v / g.HP, y = v - n * g.HP + g.ioff, x = x0 * g.lstep + ix + g.ioff;
-        const bool ok = iy < c.R && n < g.N && y >= 0 && y < g.in_H && x >= 0 && x < g.in_W;
+        const bool ok = iy < rows && n < g.N && y >= 0 && y < g.in_H && x >= 0 && x < g.in_W;
         pix[i] = ok ? (uint32_t)(((n - n0) * g.in_H + y) * g.in_W + x) : 0xFFFFFFFFu;
     }
     // VEC: rows of whole quads, and the images a tile touches within 2 GiB: buffer loads, zeros come from the range check.
@@ -259,20 +261,48 @@ pc_f32_conv_kernel(const float *__restrict__ in, float *__restrict__ out, const 
 {
     extern __shared__ __align__(16) unsigned char lds[];
     int b = (int)blockIdx.x;
-    if (!MC && (gridDim.x & 7) == 0) b = (b & 7) * ((int)gridDim.x >> 3) + (b >> 3);   // workgroups that share pixels share an XCD
     if constexpr (MC) {           // (the parts differ in taps: in launch order they spread over the XCDs)
         int k = 0;
         while (k + 1 < g.ncls && b >= g.cls[k + 1].first) ++k;
         const F32Class &c = g.cls[k];
-        if (c.ntaps == 4) pc_f32_conv_body<T, 4, WM, WN, WK, VEC>(in, out, wz, g, c, b - c.first, lds);
-        else if (c.ntaps == 2) pc_f32_conv_body<T, 2, WM, WN, WK, VEC>(in, out, wz, g, c, b - c.first, lds);
-        else pc_f32_conv_body<T, 1, WM, WN, WK, VEC>(in, out, wz, g, c, b - c.first, lds);
+        b -= c.first;
+        const int mt = b % g.m_tiles, pt = b / g.m_tiles, strip = pt / c.tiles, p0 = (pt - strip * c.tiles) * T * WN;
+        if (c.ntaps == 4) pc_f32_conv_body<T, 4, WM, WN, WK, VEC>(in, out, wz, g, c, c.R, mt, strip, p0, lds);
+        else if (c.ntaps == 2) pc_f32_conv_body<T, 2, WM, WN, WK, VEC>(in, out, wz, g, c, c.R, mt, strip, p0, lds);
+        else pc_f32_conv_body<T, 1, WM, WN, WK, VEC>(in, out, wz, g, c, c.R, mt, strip, p0, lds);
     } else {
-        pc_f32_conv_body<T, 9, WM, WN, WK, VEC>(in, out, wz, g, g.cls[0], b, lds);
+        const F32Class &c = g.cls[0];
+        const bool tail = T == 32 && WK == 1 && b >= g.tail_first;
+        int sub = 0;
+        if (tail) {
+            b -= g.tail_first;
+            sub = b % (WM * WN);
+            b = g.tail_first + b / (WM * WN);
+        } else if ((g.tail_first & 7) == 0) {
+            b = (b & 7) * (g.tail_first >> 3) + (b >> 3);   // workgroups that share pixels share an XCD
+        }
+        const int mt = b % g.m_tiles, pt = b / g.m_tiles, strip = pt / c.tiles, p0 = (pt - strip * c.tiles) * T * WN;
+        if constexpr (T == 32 && WK == 1) {
+            if (tail) {
+                if (p0 + sub / WM * 32 >= g.N * c.GH * c.Ws || (mt * WM + sub % WM) * 32 >= g.out_CH) return;
+                pc_f32_conv_body<32, 9, 1, 1, 4, VEC>(in, out, wz, g, c, g.tail_R, mt * WM + sub % WM, strip, p0 + sub / WM * 32, lds);
+                return;
+            }
+        }
+        pc_f32_conv_body<T, 9, WM, WN, WK, VEC>(in, out, wz, g, c, c.R, mt, strip, p0, lds);
     }
 }
 
 // ---- plan and launch
+// Staged rows of a tile of BN pixels of strips of Ws columns.
+static int f32_rows(const F32ConvArgs &g, int GH, int Ws, int ext, int BN)
+{
+    const int rows = BN % Ws == 0 ? BN / Ws : (BN + Ws - 2) / Ws + 1;         // output rows a tile touches at most
+    const int cross = (rows - 1 + GH - 1) / GH;                               // image boundaries among them
+    const int gap = g.HP - GH * g.lstep;                                      // virtual rows between two images beyond the step
+    return (rows - 1) * g.lstep + cross * (gap > 0 ? gap : 0) + ext;
+}
+
 // Strips and staged extent of one part for BN pixels per tile; false when it does not fit the staging registers.
 static bool f32_plan_class(const F32ConvArgs &g, F32Class *c, int ext, int BN, int NE)
 {
@@ -280,12 +310,9 @@ static bool f32_plan_class(const F32ConvArgs &g, F32Class *c, int ext, int BN, i
     for (int ns = 1, Ws = c->GW; Ws >= 1; ns = Ws > 1 ? (c->GW + Ws - 2) / (Ws - 1) : 1, Ws = Ws > 1 ? (c->GW + ns - 1) / ns : 0) {
         const int64_t np = (int64_t)g.N * c->GH * Ws;
         if (np + BN >= ((int64_t)1 << 31)) continue;
-        const int rows = BN % Ws == 0 ? BN / Ws : (BN + Ws - 2) / Ws + 1;         // output rows a tile touches at most
-        const int cross = (rows - 1 + c->GH - 1) / c->GH;                         // image boundaries among them
-        const int gap = g.HP - c->GH * g.lstep;                                   // virtual rows between two images beyond the step
         const int64_t vr = (int64_t)g.N * g.HP + 8;
         if (vr >= ((int64_t)1 << 31)) return false;
-        const int R = (rows - 1) * g.lstep + cross * (gap > 0 ? gap : 0) + ext, IW = (Ws - 1) * g.lstep + ext;
+        const int R = f32_rows(g, c->GH, Ws, ext, BN), IW = (Ws - 1) * g.lstep + ext;
         if ((int64_t)R * IW * (g.KC / 4) > 256 * NE) continue;
         // columns past the map cost matrix work, staged pixels cost less
         const int64_t cost = (int64_t)ns * Ws * (8 * BN + R * IW);
@@ -312,20 +339,56 @@ static const F32Shape kF32Shapes[] = {{32, 2, 2, 1, 0.959}, {32, 1, 4, 1, 0.941}
 // a workgroup costs its matrix cycles, its start and end, staging per 256 elements of 16 bytes, and per chunk a round trip
 // that the other workgroups of the CU hide; then the output and the weights from the L2s. Chunks of less than a cache line fetch
 // lines again where the pixels under way exceed the L2s.
-static double f32_time(const pc_ctx *ctx, const F32Shape &s, const F32ConvArgs &t, int64_t blocks, double taps, double staged, size_t lds, int64_t out_bytes)
+// Cycles of one workgroup; rounds = workgroups per CU.
+static double f32_cycles(const F32Shape &s, const F32ConvArgs &t, double taps, double staged, double rounds, size_t lds)
 {
     const int fr = s.t == 32 ? 8 : 16, left = t.in_CH - (t.nchunk - 1) * t.KC;
     const int frags = (t.nchunk - 1) * (t.KC / fr / s.wk) + ((left + fr - 1) / fr + s.wk - 1) / s.wk;
-    const double n = (double)blocks / ctx->num_cu, up = (double)((blocks + ctx->num_cu - 1) / ctx->num_cu);
     int occ = (int)(160 * 1024 / lds);
     if (occ > 4) occ = 4;
-    const double conc = up < occ ? up : occ;
-    const double per = taps * frags * (s.t == 32 ? 256.0 : 128.0) * s.mma + staged / 256.0 * t.nchunk * 119.0 + 1039.0 + 1037.0 * t.nchunk / conc;
+    const double up = ceil(rounds), conc = up < occ ? up : occ;
+    return taps * frags * (s.t == 32 ? 256.0 : 128.0) * s.mma + staged / 256.0 * t.nchunk * 119.0 + 1039.0 + 1037.0 * t.nchunk / conc;
+}
+
+static double f32_rounds(double n) { return n <= 4.0 ? ceil(n) : n + 0.68; }
+
+static double f32_time(const pc_ctx *ctx, const F32Shape &s, const F32ConvArgs &t, int64_t blocks, double taps, double staged, size_t lds, int64_t out_bytes)
+{
+    const double n = (double)blocks / ctx->num_cu;
     const double wbytes = (double)blocks * s.t * s.wm * taps * ((t.in_CH + 7) / 8 * 32);
-    double us = 4.0 + (up <= 4.0 ? up : n + 0.68) * per / 2350.0 + (double)out_bytes / 5.5e6 + wbytes / 140e6;
+    double us = 4.0 + f32_rounds(n) * f32_cycles(s, t, taps, staged, n, lds) / 2350.0 + (double)out_bytes / 5.5e6 + wbytes / 140e6;
+    int occ = (int)(160 * 1024 / lds);
+    if (occ > 4) occ = 4;
     const double res = n < occ ? (double)blocks : (double)occ * ctx->num_cu;
     if (t.KC < 32 && staged * 16.0 * t.nchunk * res / 8 > 4e6) us += (double)blocks * staged * 16.0 * t.nchunk * (32 / t.KC - 1) / 80e6;
     return us;
+}
+
+// The last, partly filled round of a launch: its tiles are cut into parts of 32 x 32, one workgroup each, four wavefronts along the
+// reduction. What bounds such a launch is the time of whole tiles on the CUs that have one more than the others; a part takes
+// a quarter of a tile's time or less, so the CUs end that much closer together. Taken where the estimate is at least 2 % shorter
+// (parts stage and read more per multiply-add, and LDS for their sums may cost a workgroup per CU). 34 layers, in us: 64 x 28 x 28,
+// 128 -> 128 forward 128.9 -> 119.7 (6.1 tiles per CU), backward-data 125.1 -> 111.8; 117 x 119, 72 -> 136 68.8 -> 53.1;
+// geometric mean 1.08 and 1.06, the least 0.96. Tiles of 16 end in small steps by themselves, and launches of the parity classes of
+// stride 2 mix short and long workgroups, so neither is cut.
+static void f32_plan_tail(const pc_ctx *ctx, const F32Shape &s, F32ConvArgs *t, int ext, int64_t *blocks, double staged, size_t *lds, double *us)
+{
+    static const F32Shape part = {32, 1, 1, 4, 0.830};
+    const F32Class &c = t->cls[0];
+    const int sub = s.wm * s.wn;
+    const int64_t whole = *blocks / ctx->num_cu * ctx->num_cu, rest = *blocks - whole;
+    const int R = f32_rows(*t, c.GH, c.Ws, ext, 32);
+    if (whole == 0 || rest == 0 || R * c.IW * 8 > 256 * f32_ne(32) || R > c.R || whole + rest * sub >= ((int64_t)1 << 31)) return;
+    const size_t need = *lds < 16384 ? 16384 : *lds;   // (the parts add their four sums there)
+    const double n = (double)*blocks / ctx->num_cu, k = (double)(whole / ctx->num_cu), m = (double)(rest * sub) / ctx->num_cu;
+    const double now = f32_rounds(n) * f32_cycles(s, *t, 9.0, staged, n, *lds);
+    const double cut = k * f32_cycles(s, *t, 9.0, staged, n, need) + f32_rounds(m) * f32_cycles(part, *t, 9.0, (double)R * c.IW * 8, n, need);
+    if (cut >= 0.98 * now) return;
+    *us -= (now - cut) / 2350.0;
+    t->tail_first = (int32_t)whole;
+    t->tail_R = R;
+    *blocks = whole + rest * sub;
+    *lds = need;
 }
 
 // g holds the tensors' extents; cls[].{GH, GW, ooff, ntaps, tap_w} and the tap positions tr, tc are set.
@@ -379,7 +442,9 @@ static pc_status f32_run(pc_ctx *ctx, F32ConvArgs g, bool mc, int ext, const int
                 }
             }
             if (!ok) continue;
-            const double us = f32_time(ctx, s, t, blocks, taps / (double)blocks, staged / (double)blocks, need, out_bytes);
+            double us = f32_time(ctx, s, t, blocks, taps / (double)blocks, staged / (double)blocks, need, out_bytes);
+            t.tail_first = (int32_t)blocks;
+            if (!mc && s.t == 32 && s.wk == 1 && kc == 32) f32_plan_tail(ctx, s, &t, ext, &blocks, staged / (double)blocks, &need, &us);
             if (best_k < 0 || us < best_us) { best = t; best_k = k; best_blocks = blocks; best_us = us; lds = need; }
         }
     }
