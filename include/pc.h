@@ -183,8 +183,9 @@ pc_status pc_pack(pc_ctx *ctx, const float *W_dev, const uint8_t *pid_dev, const
                   pc_dtype compute_dtype, pc_packed **out);
 
 /* pc_pattern_select for several layers at once (the per-batch selection of Section 4.3 runs over every layer of the
- * network): the same results as n_layers single calls, from one launch per 32 layers where every row has at most
- * 8192 kernels and keep_mode is PC_KEEP_PER_FILTER (other layers are served one by one inside the call).
+ * network): the same results as n_layers single calls, from one launch per 32 layers whose rows have at most 512 kernels and one
+ * per 32 layers of 513 to 8192 kernels per row, keep_mode PC_KEEP_PER_FILTER (other layers, and a single layer of few long
+ * rows, are served one by one inside the call). Rows of at most 8192 kernels never need scratch memory during a stream capture.
  * One pool, keep mode and score mode for all layers.
  *   W_dev_host, G_dev_host, pid_dev_host, keep_dev_host : HOST arrays [n_layers] of device pointers with the
  *       meaning they have in pc_pattern_select (G_dev_host may be NULL, and so may any of its entries)

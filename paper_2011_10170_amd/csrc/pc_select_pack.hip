@@ -312,6 +312,103 @@ pc_topn_wg_kernel(const float *__restrict__ R, int L, int n_keep, uint8_t *__res
     }
 }
 
+// Rows of PC_ROW_MAX + 1 .. PC_ROW_LONG kernels of several layers in one launch, a workgroup per row: every wavefront scores 64
+// kernels at a time, the keys stay in LDS (a thread ranks those it wrote) and the workgroup ranks them. No score goes through
+// memory and the call needs no scratch. Bound by HBM where the rows fill the chip: 16 layers of 1024 x 1024 222 us = 5.6 TB/s,
+// in two launches per layer with the scores in scratch 437 us (16 of 256 x 768: 45, 172 us). FEW, for at most one row per CU:
+// bound by the scoring of a row on one CU, so more wavefronts, each with two units of 64 on their way (16 rows of 8192: 34 -> 26 us).
+#define PC_ROW_LONG 8192        // longest row ranked in LDS
+template <bool FEW>
+__global__ void __launch_bounds__(FEW ? 1024 : 512) pc_select_long_rows_kernel(SelBatchArg b, LibArg la)
+{
+    constexpr int T = FEW ? 1024 : 512, DEPTH = FEW ? 2 : 1;   // threads; units of 64 kernels a wavefront has on their way
+    extern __shared__ uint32_t keys[];          // as many as the longest row of the launch
+    __shared__ __align__(16) float s[T / 64][64 * 9];   // staged importances, then the histogram
+    __shared__ int part[T / 64], dig[3];
+    static_assert(sizeof(s) >= 4096 * sizeof(uint32_t), "the histogram takes the place of the staged importances");
+    const int l = pc_batch_find(b.row0, b.n, (int)blockIdx.x), row = (int)blockIdx.x - b.row0[l], C = b.C[l], n_keep = b.n_keep[l];
+    const float *W = b.W[l], *G = b.G[l];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t row0 = (int64_t)row * C;
+    uint8_t *out = b.keep[l] + row0;
+    PcImpRegs r[DEPTH];
+    auto issue = [&](int k, PcImpRegs &to) __attribute__((always_inline)) {
+        if (k < C) pc_imp_issue(W, G, row0 + k, C - k < 64 ? C - k : 64, to);
+    };
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) issue(wave * 64 + d * T, r[d]);
+    for (int k0 = wave * 64; k0 < C; k0 += DEPTH * T) {
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) {
+            const int k = k0 + d * T, n = C - k < 64 ? C - k : 64;
+            if (n <= 0) break;
+            pc_imp_put(r[d], G != nullptr, n, s[wave]);
+            issue(k + DEPTH * T, r[d]);
+            if (lane < n) {
+                int best;
+                float sc;
+                pc_score_taps(s[wave] + lane * 9, la, b.score_mode, &best, &sc);
+                b.pid[l][row0 + k + lane] = (uint8_t)best;
+                keys[k + lane] = pc_order_key(sc);
+            }
+        }
+    }
+    const int tid = threadIdx.x;
+    if (n_keep <= 0 || n_keep >= C) {
+        for (int i = tid; i < C; i += T) out[i] = n_keep > 0 ? 1 : 0;
+        return;
+    }
+    // as pc_topn_wg_kernel
+    uint32_t *hist = reinterpret_cast<uint32_t *>(s);
+    __syncthreads();                            // the staged importances have been read
+    for (int i = tid; i < 4096; i += T) hist[i] = 0u;
+    uint32_t prefix = 0u;
+    int rem = n_keep, shift = 20;
+    bool all;
+    for (int pass = 0;; ++pass, shift -= 10) {
+        const uint32_t himask = pass == 0 ? 0u : 0xFFFFFFFFu << (shift + 10);
+        const uint32_t dmask = pass == 0 ? 4095u : 1023u;
+        __syncthreads();
+        for (int i = tid; i < C; i += T) {
+            const uint32_t key = keys[i];
+            if ((key & himask) == prefix) atomicAdd(&hist[(key >> shift) & dmask], 1u);
+        }
+        __syncthreads();
+        if (pass == 0) {
+            uint32_t h[4096 / T];
+#pragma unroll
+            for (int i = 0; i < 4096 / T; ++i) h[i] = hist[4096 / T * tid + i];
+            pc_topn_digit<T, 4096 / T>(h, rem, part, dig);
+        } else {
+            uint32_t h[1024 / T];
+#pragma unroll
+            for (int i = 0; i < 1024 / T; ++i) h[i] = hist[1024 / T * tid + i];
+            pc_topn_digit<T, 1024 / T>(h, rem, part, dig);
+        }
+        prefix |= (uint32_t)dig[0] << shift;
+        rem -= dig[1];
+        all = dig[2] == rem;
+        if (all || shift == 0) break;
+#pragma unroll
+        for (int i = tid; i < 1024; i += T) hist[i] = 0u;   // read before the barrier that ended pc_topn_digit
+    }
+    const uint32_t himask = 0xFFFFFFFFu << shift;
+    if (all) {
+        for (int i = tid; i < C; i += T) out[i] = (keys[i] & himask) >= prefix ? 1 : 0;
+        return;
+    }
+    int base = 0;                               // of the keys equal to the threshold the first rem by index
+    for (int i0 = 0; i0 < C; i0 += T) {
+        const int i = i0 + tid;
+        const uint32_t key = i < C ? keys[i] : 0u;
+        const bool eq = i < C && key == prefix;
+        int total;
+        const int before = base + pc_block_rank(eq, part, T / 64, &total);
+        if (i < C) out[i] = key > prefix || (eq && before < rem) ? 1 : 0;
+        base += total;
+    }
+}
+
 // Segments above PC_TOPN_WG (whole layers ranked at once), across workgroups: three counting passes (11, 11 and 10 bits;
 // hist[3][2048], zeroed by the score kernel) and a writing pass. Every workgroup walks its chunk of the scores and derives
 // the prefix again from the finished histograms instead of reading it from a single writer; the last counting pass leaves
@@ -433,13 +530,28 @@ __global__ void __launch_bounds__(256) pc_fill_u8_kernel(uint8_t *__restrict__ p
 }
 
 // Rows of at most PC_ROW_MAX kernels: a wavefront per row where the launch has at least this many rows per CU, so that the
-// wavefronts fill the chip; fewer rows get a workgroup each.
+// wavefronts fill the chip; fewer rows, and longer ones, get a workgroup each.
 #define PC_ROWS_PER_CU 8
-static pc_status pc_launch_rows(pc_ctx *ctx, SelBatchArg *b, int cmax, const LibArg &la)
+static pc_status pc_launch_rows(pc_ctx *ctx, SelBatchArg *b, const LibArg &la)
 {
     if (b->n == 0) return PC_OK;
     const unsigned rows = (unsigned)b->row0[b->n];
-    if (rows >= (unsigned)(PC_ROWS_PER_CU * ctx->num_cu))
+    int cmax = 0;
+    for (int i = 0; i < b->n; ++i) cmax = b->C[i] > cmax ? b->C[i] : cmax;
+    if (cmax > PC_ROW_MAX) {
+        const size_t lds = sizeof(uint32_t) * (size_t)cmax;
+        const bool few = rows <= (unsigned)ctx->num_cu;
+        if (few) {
+            static pc_per_device_once attr;
+            if (pc_once_pending(attr, ctx->device)) {
+                PC_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&pc_select_long_rows_kernel<true>),
+                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(uint32_t) * PC_ROW_LONG));
+                pc_once_done(attr, ctx->device);
+            }
+            hipLaunchKernelGGL(pc_select_long_rows_kernel<true>, dim3(rows), dim3(1024), lds, ctx->stream, *b, la);
+        }
+        else hipLaunchKernelGGL(pc_select_long_rows_kernel<false>, dim3(rows), dim3(512), lds, ctx->stream, *b, la);
+    } else if (rows >= (unsigned)(PC_ROWS_PER_CU * ctx->num_cu))
         hipLaunchKernelGGL(pc_select_rows_kernel<true>, dim3(rows), dim3(64), 0, ctx->stream, *b, la);
     else
         hipLaunchKernelGGL(pc_select_rows_kernel<false>, dim3(rows), dim3((unsigned)((cmax + 63) / 64 * 64)), 0, ctx->stream, *b, la);
@@ -447,7 +559,7 @@ static pc_status pc_launch_rows(pc_ctx *ctx, SelBatchArg *b, int cmax, const Lib
     return pc_hip_check(ctx, hipGetLastError(), "select launch");
 }
 
-// Rows longer than PC_ROW_MAX, and layers ranked as a whole: scores to memory, then the ranking of every segment.
+// Rows longer than PC_ROW_LONG (or few of more than PC_ROW_SPLIT), and layers ranked as a whole: scores to memory, then the ranking of every segment.
 static pc_status pc_launch_select_segments(pc_ctx *ctx, const float *W, const float *G, int F, int C, const LibArg &la,
                                            pc_keep_mode km, int64_t n_keep, pc_score_mode sm, uint8_t *pid, uint8_t *keep)
 {
@@ -488,35 +600,57 @@ static pc_status pc_launch_select_segments(pc_ctx *ctx, const float *W, const fl
     return pc_hip_check(ctx, hipGetLastError(), "select launch");
 }
 
-// Layers whose rows are ranked in registers go into launches of up to PC_BATCH_MAX layers, the others one by one.
+// One layer of at most one row per CU and more than PC_ROW_SPLIT kernels per row goes through memory after all: two launches, but
+// the scoring spreads over the chip (64 x 4096 10.5 us against 16.9 us, 16 x 2048 8.6 against 11.0, 256 x 4096 20.5 against 22.9;
+// up to 1024 kernels, 384 rows, or 4 such layers in a call, the one launch is as fast or faster: 64 x 1024 8.8 against 8.4, 4 of
+// 64 x 4096 47.8 against 23.0). Not where the scratch for it would have to be allocated during a stream capture, or cannot be: the
+// other way needs none.
+#define PC_ROW_SPLIT 1024
+static bool pc_rows_through_memory(pc_ctx *ctx, const SelBatchArg &b)
+{
+    if (b.n != 1 || b.row0[1] > ctx->num_cu || b.C[0] <= PC_ROW_SPLIT) return false;
+    const size_t bytes = sizeof(float) * (size_t)b.row0[1] * (size_t)b.C[0] + 256;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    void *scr;
+    if (bytes <= ctx->scratch_bytes) return true;
+    if (hipStreamIsCapturing(ctx->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone && pc_scratch(ctx, bytes, &scr) == PC_OK) return true;
+    (void)hipGetLastError();
+    return false;
+}
+
+// Layers ranked by rows go into launches of up to PC_BATCH_MAX layers, rows of at most PC_ROW_MAX kernels and longer ones apart;
+// the others one by one.
 pc_status pc_launch_select_batch(pc_ctx *ctx, int n, const float *const *W, const float *const *G, const int32_t *F,
                                  const int32_t *C, const LibArg &la, pc_keep_mode km, const int64_t *n_keep, pc_score_mode sm,
                                  uint8_t *const *pid, uint8_t *const *keep)
 {
-    SelBatchArg b;
-    memset(&b, 0, sizeof(b));
-    b.score_mode = (int)sm;
-    int cmax = 0;
+    SelBatchArg rows[2];
+    memset(rows, 0, sizeof(rows));
+    rows[0].score_mode = rows[1].score_mode = (int)sm;
     for (int l = 0; l < n; ++l) {
         pc_status s = PC_OK;
-        if (km != PC_KEEP_PER_FILTER || C[l] > PC_ROW_MAX) {
+        if (km != PC_KEEP_PER_FILTER || C[l] > PC_ROW_LONG) {
             s = pc_launch_select_segments(ctx, W[l], G ? G[l] : nullptr, F[l], C[l], la, km, n_keep[l], sm, pid[l], keep[l]);
             if (s != PC_OK) return s;
             continue;
         }
+        SelBatchArg &b = rows[C[l] > PC_ROW_MAX];
         const int i = b.n;
         b.W[i] = W[l]; b.G[i] = G ? G[l] : nullptr; b.C[i] = C[l];
         b.n_keep[i] = (int32_t)(n_keep[l] < C[l] ? n_keep[l] : C[l]);
         b.pid[i] = pid[l]; b.keep[i] = keep[l];
         b.row0[i + 1] = b.row0[i] + F[l];
-        if (C[l] > cmax) cmax = C[l];
         if (++b.n == PC_BATCH_MAX) {
-            s = pc_launch_rows(ctx, &b, cmax, la);
+            s = pc_launch_rows(ctx, &b, la);
             if (s != PC_OK) return s;
-            cmax = 0;
         }
     }
-    return pc_launch_rows(ctx, &b, cmax, la);
+    pc_status s = pc_launch_rows(ctx, &rows[0], la);
+    if (s != PC_OK) return s;
+    const SelBatchArg &b = rows[1];
+    if (pc_rows_through_memory(ctx, b))
+        return pc_launch_select_segments(ctx, b.W[0], b.G[0], b.row0[1], b.C[0], la, km, b.n_keep[0], sm, b.pid[0], b.keep[0]);
+    return pc_launch_rows(ctx, &rows[1], la);
 }
 
 pc_status pc_launch_select(pc_ctx *ctx, const float *W, const float *G, int F, int C, const LibArg &la,
