@@ -59,24 +59,38 @@ struct F32ConvArgs {
 // 28 x 28, 128 -> 128, batch 64 takes 115.5 us without and 115.4 us with it.)
 __device__ __forceinline__ float pc_f32_kept_taps(const float *__restrict__ in, const float *__restrict__ wz, const F32ConvArgs &g, int n, int oy, int ox, int m)
 {
-    const float *img = in + (int64_t)n * g.in_H * g.in_W * g.in_CH;
+    const float *img = in + (int64_t)n * g.in_H * g.in_W * g.in_CH, *wrow = wz + (int64_t)(m >> 5) * 9 * g.KS * 256 + (m & 31) * 4;
     float acc = 0.0f;
-    for (int k = 0; k < g.in_CH && acc == acc; ++k) {
-        const uint32_t info = g.kinfo[m * g.k_row + k * g.k_red];
-        if (info == 0xFFFFFFFFu) continue;
-        for (uint32_t left = info & 511u; left; left &= left - 1u) {
-            const int t = __ffs((int)left) - 1, r = t / 3, s = t - 3 * r;
-            int iy = oy * g.lstep + r - 1, ix = ox * g.lstep + s - 1;
-            if (g.back) {
-                iy = oy + 1 - r;
-                ix = ox + 1 - s;
-                if ((iy | ix) & (g.oscale - 1)) continue;
-                iy >>= g.oscale - 1;
-                ix >>= g.oscale - 1;
+    for (int k0 = 0; k0 < g.in_CH && acc == acc; k0 += 4) {
+        uint32_t info[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) info[i] = g.kinfo[m * g.k_row + (k0 + i < g.in_CH ? k0 + i : k0) * g.k_red];
+        for (int i = 0; i < 4 && k0 + i < g.in_CH; ++i) {
+            const uint32_t u = i == 0 ? info[0] : i == 1 ? info[1] : i == 2 ? info[2] : info[3];
+            if (u == 0xFFFFFFFFu) continue;
+            const int k = k0 + i;
+            const float *wk = wrow + (k >> 3) * 256 + (k >> 2 & 1) * 128 + (k & 3);
+            uint32_t left = u & 511u;
+            float x[4], w[4];
+            bool on[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j, left &= left - 1u) {
+                const int t = __ffs((int)left) - 1, r = t / 3, s = t - 3 * r;
+                int iy = oy * g.lstep + r - 1, ix = ox * g.lstep + s - 1;
+                bool hit = true;
+                if (g.back) {
+                    iy = oy + 1 - r;
+                    ix = ox + 1 - s;
+                    hit = ((iy | ix) & (g.oscale - 1)) == 0;
+                    iy >>= g.oscale - 1;
+                    ix >>= g.oscale - 1;
+                }
+                on[j] = hit && (unsigned)iy < (unsigned)g.in_H && (unsigned)ix < (unsigned)g.in_W;
+                x[j] = img[on[j] ? ((int64_t)iy * g.in_W + ix) * g.in_CH + k : 0];
+                w[j] = wk[(int64_t)t * g.KS * 256];
             }
-            if ((unsigned)iy >= (unsigned)g.in_H || (unsigned)ix >= (unsigned)g.in_W) continue;
-            const float w = wz[((int64_t)((m >> 5) * 9 + t) * g.KS + (k >> 3)) * 256 + ((k >> 2 & 1) * 32 + (m & 31)) * 4 + (k & 3)];
-            acc = fmaf(img[((int64_t)iy * g.in_W + ix) * g.in_CH + k], w, acc);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc = on[j] ? fmaf(x[j], w[j], acc) : acc;
         }
     }
     return acc;
@@ -792,25 +806,50 @@ pc_f32_wgrad_kernel(const float *__restrict__ x, const float *__restrict__ dy, F
         redo |= z == z ? 0u : 1u << r;
     }
     // The matrix instructions multiplied the zeros around the maps and past the tile too, and 0 x Inf = NaN: these sums again,
-    // over the pixels of this wavefront that exist. (The check costs a launch 0.3 us at most: 8 x 32 x 32, 16 -> 16 13.7 -> 14.0 us.)
+    // over the pixels of this wavefront that exist. (Finite data pays for the check only: 8 x 32 x 32, 16 -> 16 all three passes
+    // 25.9 us without and with it. One infinity in 1000 elements of x: 28 x 28, 128 -> 128, batch 64 2.1 ms forward, 3.6 ms here.)
     for (; redo; redo &= redo - 1u) {
         const int r = __ffs((int)redo) - 1, f = f0 + wf * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
         const uint32_t info = kinfo[(int64_t)f * a.C + e_c], mask = info & 511u;
-        for (uint32_t left = THIN ? 1u << e_tap : mask; left; left &= left - 1u) {
-            const int t = __ffs((int)left) - 1, dr = t / 3 - 1, dc = t % 3 - 1;
-            float sum = 0.0f;
-            for (int k = split; k < a.n_tiles && sum == sum; k += a.ksplit) {
-                const int tc = k % a.tiles_c, q = k / a.tiles_c, tr = q % a.tiles_r, n = q / a.tiles_r;
-                const float *dimg = dy + (int64_t)n * a.Ho * a.Wo * a.F + f, *ximg = x + (int64_t)n * a.H * a.W * a.C + e_c;
-                for (int s = 2 * wk; s < 2 * steps; s += (s & 1) ? 2 * WK - 1 : 1) {   // both pixels of every WK-th pair
-                    const int y = s / a.TCe, col = s - y * a.TCe, oy = tr * a.TR + y, ox = tc * a.TC + col;
-                    const int iy = oy * a.stride + dr, ix = ox * a.stride + dc;
-                    if (col < a.TC && oy < a.Ho && ox < a.Wo && (unsigned)iy < (unsigned)a.H && (unsigned)ix < (unsigned)a.W)
-                        sum = fmaf(dimg[((int64_t)oy * a.Wo + ox) * a.F], ximg[((int64_t)iy * a.W + ix) * a.C], sum);
+        constexpr int NK = THIN ? 1 : 4;          // kept taps of this lane's kernel
+        int dr[NK], dc[NK];
+        float sum[NK];
+        uint32_t left = THIN ? 1u << e_tap : mask;
+#pragma unroll
+        for (int j = 0; j < NK; ++j, left &= left - 1u) {
+            const int t = __ffs((int)left) - 1;
+            dr[j] = t / 3 - 1;
+            dc[j] = t % 3 - 1;
+            sum[j] = 0.0f;
+        }
+        bool dead = false;                        // all NaN already
+        for (int k = split; k < a.n_tiles && !dead; k += a.ksplit) {
+            const int tc = k % a.tiles_c, q = k / a.tiles_c, tr = q % a.tiles_r, n = q / a.tiles_r;
+            const float *dimg = dy + (int64_t)n * a.Ho * a.Wo * a.F + f, *ximg = x + (int64_t)n * a.H * a.W * a.C + e_c;
+#pragma unroll 2
+            for (int s = wk; s < steps; s += WK) {
+                const int y = s / half, oy = tr * a.TR + y;
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const int col = (s - y * half) * 2 + i, ox = tc * a.TC + col;
+                    const bool on = col < a.TC && oy < a.Ho && ox < a.Wo;
+                    const float d = dimg[on ? ((int64_t)oy * a.Wo + ox) * a.F : 0];
+#pragma unroll
+                    for (int j = 0; j < NK; ++j) {
+                        const int iy = oy * a.stride + dr[j], ix = ox * a.stride + dc[j];
+                        const bool in = on && (unsigned)iy < (unsigned)a.H && (unsigned)ix < (unsigned)a.W;
+                        const float v = ximg[in ? ((int64_t)iy * a.W + ix) * a.C : 0];
+                        sum[j] = in ? fmaf(d, v, sum[j]) : sum[j];
+                    }
                 }
             }
-            reinterpret_cast<float *>(pout + (info >> 9))[__popc(mask & ((1u << t) - 1u))] = sum;
+            dead = true;
+#pragma unroll
+            for (int j = 0; j < NK; ++j) dead = dead && sum[j] != sum[j];
         }
+#pragma unroll
+        for (int j = 0; j < NK; ++j)
+            reinterpret_cast<float *>(pout + (info >> 9))[THIN ? __popc(mask & ((1u << e_tap) - 1u)) : j] = sum[j];
     }
 }
 
