@@ -564,19 +564,20 @@ def test_bwd_weight_on_a_second_context_and_stream(B, oracle):
 
 def test_select_and_pack_batch(B, ctx, oracle):
     """pc_pattern_select_batch and pc_pack_batch over layers of mixed shapes, dtypes and kernel families (one row too
-    long for the one-workgroup kernel, one float32 layer on the gather kernels): masks bit-exact against the oracle,
+    long for the one-workgroup kernel, float32 layers on the matrix cores and on the gather kernels): masks bit-exact against the oracle,
     the re-packed handles hold W (.) M, their kept-kernel counts are right and a forward pass through each is within
     tolerance. The handles were first packed with other masks (selection with gradients), so a stale table would show."""
     import torch
     shapes = [(2, 6, 6, 3, 64, "bf16"), (2, 6, 6, 64, 64, "bf16"), (2, 5, 4, 64, 128, "bf16"), (2, 4, 4, 24, 40, "f32"),
-              (1, 4, 4, 256, 256, "bf16"), (1, 2, 2, 9000, 8, "bf16"), (3, 3, 3, 40, 72, "bf16")]
+              (1, 4, 4, 256, 256, "bf16"), (1, 2, 2, 9000, 8, "bf16"), (3, 3, 3, 40, 72, "bf16"), (2, 4, 5, 24, 40, "f32 gather")]
     gs, cases = [], []
     try:
         for li, (N, H, W_, C, F, dtype) in enumerate(shapes):
             layer = I.Layer(N, H, W_, C, F, 1)
-            case = Case(layer, dtype, 8, I.kept_per_filter(0.3, C), tag=("batch", li))
+            case = Case(layer, dtype.split()[0], 8, I.kept_per_filter(0.3, C), tag=("batch", li))
             cases.append(case)
-            gs.append(GpuLayer(B, ctx, case))                       # select with gradients + pack, one layer at a time
+            gs.append(GpuLayer(B, ctx, case, variant=B.PC_VARIANT_VALU if "gather" in dtype else B.PC_VARIANT_AUTO))   # select with gradients + pack, one layer at a time
+        assert [g.variant for g in gs] == [B.PC_VARIANT_VALU if "gather" in s[-1] else B.PC_VARIANT_MFMA for s in shapes]
         for g in gs:
             g.pid.fill_(255); g.keep.fill_(255)
         lib = cases[0].lib
@@ -646,19 +647,20 @@ def test_select_and_pack_batch_of_many_layers(B, ctx, oracle):
 
 def test_bwd_weight_batch_equals_the_single_calls(B, ctx, oracle):
     """pc_conv_bwd_weight_batch over layers of every kind (3 input channels: padded copy; a filter count the
-    wave-specialised kernel does not take; a float32 layer on the gather kernels; stride 2; a layer with as many tiles
+    wave-specialised kernel does not take; float32 layers on the matrix cores and on the gather kernels; stride 2; a layer with as many tiles
     as CUs, i.e. no split; a pack whose count is not known on the host): within tolerance of the oracle and of
     pc_conv_bwd_weight layer by layer (the split of a layer, hence the float32 order of additions, may differ), and
     the same bits from call to call."""
     import torch
     shapes = [(8, 8, 8, 3, 64, 1, "bf16"), (8, 8, 8, 64, 64, 1, "bf16"), (4, 6, 6, 40, 36, 1, "bf16"), (2, 5, 5, 16, 24, 1, "f32"),
-              (8, 9, 9, 64, 128, 2, "bf16"), (2, 2, 2, 1024, 1024, 1, "bf16"), (16, 4, 4, 256, 128, 1, "bf16")]
+              (2, 5, 6, 16, 24, 1, "f32 gather"), (8, 9, 9, 64, 128, 2, "bf16"), (2, 2, 2, 1024, 1024, 1, "bf16"), (16, 4, 4, 256, 128, 1, "bf16")]
     gs, cases = [], []
     try:
         for li, (N, H, W_, C, F, st, dtype) in enumerate(shapes):
-            case = Case(I.Layer(N, H, W_, C, F, st), dtype, 8, I.kept_per_filter(0.3, C), tag=("wgb", li))
+            case = Case(I.Layer(N, H, W_, C, F, st), dtype.split()[0], 8, I.kept_per_filter(0.3, C), tag=("wgb", li))
             cases.append(case)
-            gs.append(GpuLayer(B, ctx, case))
+            gs.append(GpuLayer(B, ctx, case, variant=B.PC_VARIANT_VALU if "gather" in dtype else B.PC_VARIANT_AUTO))
+        assert [g.variant for g in gs] == [B.PC_VARIANT_VALU if "gather" in s[-1] else B.PC_VARIANT_MFMA for s in shapes]
         single = []
         for g in gs:
             dw, guard = g.bwd_weight()

@@ -28,11 +28,11 @@ def ctx(B):
     B.pc_destroy(c)
 
 
-def _both(B, ctx, oracle, layer, dtype, P, n_keep, tag):
+def _both(B, ctx, oracle, layer, dtype, P, n_keep, tag, variant=0):
     import torch
     case = Case(layer, dtype, P, n_keep, tag=tag)
     print("no-alloc case", tag, layer, dtype, flush=True)
-    g = GpuLayer(B, ctx, case)
+    g = GpuLayer(B, ctx, case, variant=variant)
     try:
         ref = Guarded(g.nnzk * 4, torch.float32)
         B.pc_conv_bwd_weight(ctx, g.desc, g.pk, g.x, g.dy, ref.ptr)
@@ -54,8 +54,9 @@ def test_two_calls_in_a_row_second_smaller(B, ctx, oracle):
     # matrix-core kernels, several pixel splits: the partial sums of both calls go through the fixed buffer
     _both(B, ctx, oracle, I.Layer(8, 16, 16, 64, 128, 1), "bf16", 8, 19, "noalloc_a")
     _both(B, ctx, oracle, I.Layer(3, 7, 9, 40, 24, 2), "bf16", 8, 12, "noalloc_b")
-    # the gather kernels (float32), and a first layer whose 3 channels are copied to 8-channel rows in the buffer
+    # float32 on the matrix cores and on the gather kernels, and a first layer whose 3 channels are copied to 8-channel rows in the buffer
     _both(B, ctx, oracle, I.Layer(8, 32, 32, 16, 16, 1), "f32", 4, 8, "noalloc_c")
+    _both(B, ctx, oracle, I.Layer(8, 32, 32, 16, 16, 1), "f32", 4, 8, "noalloc_c", B.PC_VARIANT_VALU)
     _both(B, ctx, oracle, I.Layer(2, 16, 16, 3, 64, 1), "bf16", 8, 1, "noalloc_d")
 
 
