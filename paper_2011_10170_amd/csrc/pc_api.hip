@@ -272,7 +272,9 @@ extern "C" pc_status pc_pattern_select_batch(pc_ctx *ctx, int32_t n_layers, cons
 // ------------------------------------------------------------------ pack
 static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
-// Carves the slab. With base == nullptr only the size is computed.
+// Carves the slab. With base == nullptr only the size is computed. The gather tables (about 47 bytes per kernel) are there in
+// every pack and the operand tiles wherever the shape allows them (bf16 36, float32 72 bytes): a handle may be re-packed
+// under another forced variant, which must not allocate.
 static size_t carve(PackView *v, PackView **v_dev, char *base, int F, int C, bool mfma, bool sparse, bool f32)
 {
     size_t off = 0;

@@ -402,7 +402,9 @@ static const F32Shape kF32Shapes[] = {{32, 2, 2, 1, 0.959}, {32, 1, 4, 1, 0.941}
                                       {16, 1, 4, 1, 0.895}, {16, 1, 2, 2, 0.847}, {16, 1, 1, 4, 0.773}};
 
 // Time estimate in us, least squares over 4800 measured launches (240 layers of 1 .. 100 images, 4 .. 224 pixels wide, 3 .. 500 channels,
-// both passes and strides; the choice is 0.8 % behind the best shape on average, on other layers too, the worst one 19 %):
+// both passes and strides; the choice is 0.8 % behind the best shape on average, the worst one 19 %; on 80 layers drawn
+// afterwards, with every shape's time in profiles/plan_timings_f32.csv for a new fit, 0.3 % forward and 2.4 % backward-data (4 % at
+// stride 2, the worst 31 %)):
 // a workgroup costs its matrix cycles, its start and end, staging per 256 elements of 16 bytes, and per chunk a round trip
 // that the other workgroups of the CU hide; then the output and the weights from the L2s. Chunks of less than a cache line fetch
 // lines again where the pixels under way exceed the L2s.

@@ -1150,7 +1150,9 @@ static bool plan_ks(const MfmaArgs &g, int ext, const KsCand &cand, MfmaArgs *ou
     // of 64 bytes. The constants (factor, item and tile cycles per kernel, the shared ones here) are a least-squares fit over
     // the measured times of every kernel on 355 layer shapes (1 to 128 images, 4 x 4 to 224 x 224, 8 to 512 channels, both
     // strides, back to back): 5 % rms over 11 500 timings. The kernel with the least estimate is on average 2 % slower than
-    // the fastest of a shape; the rule it replaces, made for channel counts from 64 up, 22 %.
+    // the fastest of a shape; the rule it replaces, made for channel counts from 64 up, 22 %. On 110 layers drawn afterwards
+    // (profiles/plan_timings_bf16.csv, every kernel on every layer: what a new fit starts from) 1.4 % at stride 1 and 4.7 % at
+    // stride 2, the worst 33 %.
     const double rounds = (double)((total + num_cu - 1) / num_cu);
     const double mfma = 9.0 * (kc / 16) * at * bt * 32.0 / (ksp == 4 ? 4 : 1) * cand.mfma, stage = t.nelem * 16.0 * 0.0418;
     const double end = cand.tile + 2.0 * rows * t.TI * t.TH * t.TW * 0.0143;
@@ -1253,7 +1255,8 @@ pc_status pc_run_mfma_conv_ws(pc_ctx *ctx, int pcfg, const MfmaArgs &g0, int ext
 pc_status pc_run_mfma_conv_mc(pc_ctx *ctx, int pcfg, const MfmaArgs &g0, const uint16_t *in, uint16_t *out, const uint16_t *wz, bool *launched)
 {
     *launched = false;
-    // (constants of the time estimate from the measured times of 171 layer shapes, 7 % rms)
+    // (constants of the time estimate from the measured times of 171 layer shapes, 7 % rms; on 35 others, in the same file as
+    // above, the choice is 3.7 % behind the best on average, the worst 48 %: 40 -> 8 channels, where code 34 would be better)
     static const KsCand kMc[] = {
         {32, 1, 2, 1, 64, 1.24, 321, 3878}, {33, 1, 2, 1, 32, 1.37, 529, 3823}, {34, 1, 2, 1, 16, 1.63, 719, 3829},
         {35, 1, 1, 1, 64, 1.66, 934, 3251}, {36, 1, 1, 1, 32, 1.64, 901, 2974},
