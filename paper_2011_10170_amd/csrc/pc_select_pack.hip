@@ -540,8 +540,7 @@ static pc_status pc_launch_rows(pc_ctx *ctx, SelBatchArg *b, const LibArg &la)
     for (int i = 0; i < b->n; ++i) cmax = b->C[i] > cmax ? b->C[i] : cmax;
     if (cmax > PC_ROW_MAX) {
         const size_t lds = sizeof(uint32_t) * (size_t)cmax;
-        const bool few = rows <= (unsigned)ctx->num_cu;
-        if (few) {
+        if (rows <= (unsigned)ctx->num_cu) {
             static pc_per_device_once attr;
             if (pc_once_pending(attr, ctx->device)) {
                 PC_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&pc_select_long_rows_kernel<true>),
@@ -549,17 +548,20 @@ static pc_status pc_launch_rows(pc_ctx *ctx, SelBatchArg *b, const LibArg &la)
                 pc_once_done(attr, ctx->device);
             }
             hipLaunchKernelGGL(pc_select_long_rows_kernel<true>, dim3(rows), dim3(1024), lds, ctx->stream, *b, la);
+        } else {
+            hipLaunchKernelGGL(pc_select_long_rows_kernel<false>, dim3(rows), dim3(512), lds, ctx->stream, *b, la);
         }
-        else hipLaunchKernelGGL(pc_select_long_rows_kernel<false>, dim3(rows), dim3(512), lds, ctx->stream, *b, la);
-    } else if (rows >= (unsigned)(PC_ROWS_PER_CU * ctx->num_cu))
+    } else if (rows >= (unsigned)(PC_ROWS_PER_CU * ctx->num_cu)) {
         hipLaunchKernelGGL(pc_select_rows_kernel<true>, dim3(rows), dim3(64), 0, ctx->stream, *b, la);
-    else
+    } else {
         hipLaunchKernelGGL(pc_select_rows_kernel<false>, dim3(rows), dim3((unsigned)((cmax + 63) / 64 * 64)), 0, ctx->stream, *b, la);
+    }
     b->n = 0;
     return pc_hip_check(ctx, hipGetLastError(), "select launch");
 }
 
-// Rows longer than PC_ROW_LONG (or few of more than PC_ROW_SPLIT), and layers ranked as a whole: scores to memory, then the ranking of every segment.
+// Rows longer than PC_ROW_LONG (or few of more than PC_ROW_SPLIT), and layers ranked as a whole: scores to memory, then the
+// ranking of every segment.
 static pc_status pc_launch_select_segments(pc_ctx *ctx, const float *W, const float *G, int F, int C, const LibArg &la,
                                            pc_keep_mode km, int64_t n_keep, pc_score_mode sm, uint8_t *pid, uint8_t *keep)
 {

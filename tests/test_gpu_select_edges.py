@@ -27,8 +27,8 @@ def ctx(B):
     B.pc_destroy(c)
 
 
-# (F, C, keep mode): one row per workgroup up to 512 kernels, one per wavefront from 8 rows per CU, scores in memory above;
-# whole layers up to 16384 kernels by one workgroup
+# (F, C, keep mode): one row per workgroup up to 512 kernels, one per wavefront from 8 rows per CU, longer rows by a workgroup with
+# the keys in LDS, or with the scores in memory; whole layers up to 16384 kernels by one workgroup
 SHAPES = [(5, 1, 0), (7, 63, 0), (7, 65, 0), (4, 512, 0), (4, 513, 0), (2, 4097, 0), (1, 16385, 0), (2100, 65, 0), (2060, 3, 0),
           (64, 64, 1), (3, 1366, 1), (128, 128, 1), (113, 146, 1)]
 
