@@ -389,7 +389,7 @@ static pc_status run_mfma_conv(pc_ctx *ctx, MfmaArgs g, int ext, int ntaps, cons
 {
     g.act_mask = nullptr;
     int plan_cfg = (ctx->plan_cfg >= 10 && ctx->plan_cfg < 13) ? -1 : ctx->plan_cfg;   // 10 and 11 select a backward-weight kernel
-    if (ntaps == 9 && plan_cfg >= 32) plan_cfg = -1;   // codes of the stride-2 backward-data kernel
+    if (ntaps == 9 && plan_cfg >= 32 && plan_cfg < 40) plan_cfg = -1;   // codes of the stride-2 backward-data kernel
     if (ntaps == 9 && (plan_cfg < 0 || plan_cfg >= 7) && ctx->plan_split == 0) {
         // The wave-specialised kernel reads and writes whole groups of 8 channels. The first layer's few channels
         // (input of the forward pass, output of the backward-data pass) go through a copy with 8-channel rows.
@@ -432,7 +432,7 @@ static pc_status run_mfma_conv(pc_ctx *ctx, MfmaArgs g, int ext, int ntaps, cons
             }
         }
     }
-    if (pcl && (plan_cfg >= 32 || (plan_cfg < 0 && ctx->plan_split == 0)) && (g.in_CH & 7) == 0) {
+    if (pcl && ((plan_cfg >= 32 && plan_cfg < 40) || (plan_cfg < 0 && ctx->plan_split == 0)) && (g.in_CH & 7) == 0) {
         bool launched = false;
         const pc_status s = pc_run_mfma_conv_mc(ctx, plan_cfg, g, in, out, wz, &launched);
         if (s != PC_OK || launched) return s;

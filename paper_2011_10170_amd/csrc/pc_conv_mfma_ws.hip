@@ -32,20 +32,6 @@ constexpr int pc_ring_depth(int nf, int cap)
     return best;
 }
 
-// Two bf16 values in a word: each one that is negative (or -0) becomes +0.
-__device__ __forceinline__ uint32_t pc_relu_bf16x2(uint32_t u)
-{
-    return u & ~(((u & 0x80008000u) >> 15) * 0xFFFFu);
-}
-
-// Two bf16 values in a word: each one is kept where the matching value of a is positive, else +0.
-__device__ __forceinline__ uint32_t pc_mask_bf16x2(uint32_t u, uint32_t a)
-{
-    const uint32_t lo = ((a & 0xFFFFu) - 1u) < 0x7FFFu ? 0x0000FFFFu : 0u;   // sign clear and not zero
-    const uint32_t hi = ((a >> 16) - 1u) < 0x7FFFu ? 0xFFFF0000u : 0u;
-    return u & (lo | hi);
-}
-
 // The loader wavefronts of the wave-specialised kernels (wavefronts 4..7 of a workgroup of 8): they stage the input
 // halo tile of the NEXT item (tile, chunk of KC channels) into one of two LDS buffers, their global loads KS_DEPTH
 // items ahead in registers, and execute one workgroup barrier after the first staged item and one per item.
@@ -1170,6 +1156,7 @@ pc_status pc_run_mfma_conv_ws(pc_ctx *ctx, int pcfg, const MfmaArgs &g0, int ext
                               const uint16_t *in, uint16_t *out, const uint16_t *wz, const SparseOperand &sp, bool *launched, int act)
 {
     *launched = false;
+    if (pcfg >= 40 && pcfg < 50) return pc_run_mfma_conv_dma(ctx, pcfg, 1e30, g0, tr[0] != 0, in, out, wz, launched, act);
     // The structured-sparse kernel (override code 22; automatic from 64 reduction channels up): 64 x 256 tiles,
     // 64-channel chunks, pixels split over the MFMA wavefronts.
     if (sp.val && g0.lstep == 1 && (pcfg == 22 || (pcfg < 0 && g0.in_CH >= 64))) {
@@ -1207,13 +1194,18 @@ pc_status pc_run_mfma_conv_ws(pc_ctx *ctx, int pcfg, const MfmaArgs &g0, int ext
         if (!plan_ks(g0, ext, kKs[k], &t, &lds, &est, ctx->num_cu)) continue;
         if (best_k < 0 || est < best_est) { best = t; best_lds = lds; best_est = est; best_k = k; }
     }
+    // the tap list is the full 3x3 in tap order, forward (offset (r, s)) or rotated (offset (2-r, 2-s))
+    for (int t = 0; t < 9; ++t)
+        if (g0.tap_w[t] != t || tr[t] != (tr[0] ? 2 - t / 3 : t / 3) || tc[t] != (tc[0] ? 2 - t % 3 : t % 3)) return PC_OK;
+    if (pcfg < 0) {
+        // (5 % less: inside a training step, tensors not in any cache, its loads take longer than where it was measured)
+        const pc_status s = pc_run_mfma_conv_dma(ctx, -1, best_k < 0 ? 1e30 : 0.95 * best_est, g0, tr[0] != 0, in, out, wz, launched, act);
+        if (s != PC_OK || *launched) return s;
+    }
     if (best_k < 0) return PC_OK;
     const KsCand &c = kKs[best_k];
     MfmaArgs g = best;
     const int pitch = 2 * c.kc + 16;
-    // the tap list is the full 3x3 in tap order, forward (offset (r, s)) or rotated (offset (2-r, 2-s))
-    for (int t = 0; t < 9; ++t)
-        if (g.tap_w[t] != t || tr[t] != (tr[0] ? 2 - t / 3 : t / 3) || tc[t] != (tc[0] ? 2 - t % 3 : t % 3)) return PC_OK;
     g.tap_dr = (tr[0] ? -1 : 1) * g.IW * pitch;
     g.tap_ds = (tc[0] ? -1 : 1) * pitch;
     g.tap_o0 = (tr[0] * g.IW + tc[0]) * pitch;

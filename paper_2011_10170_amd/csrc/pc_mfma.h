@@ -45,6 +45,20 @@ enum { PC_ACT_NONE = 0, PC_ACT_RELU = 1, PC_ACT_RELU_MASK = 2 };
 __device__ __forceinline__ uint32_t pc_udiv(uint32_t q, uint32_t mg) { return mg ? __umulhi(q, mg) : q; }
 inline uint32_t pc_udiv_magic(int d) { return d == 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) / (uint64_t)d) + 1); }
 
+// Two bf16 values in a word: each one that is negative (or -0) becomes +0.
+__device__ __forceinline__ uint32_t pc_relu_bf16x2(uint32_t u)
+{
+    return u & ~(((u & 0x80008000u) >> 15) * 0xFFFFu);
+}
+
+// Two bf16 values in a word: each one is kept where the matching value of a is positive, else +0.
+__device__ __forceinline__ uint32_t pc_mask_bf16x2(uint32_t u, uint32_t a)
+{
+    const uint32_t lo = ((a & 0xFFFFu) - 1u) < 0x7FFFu ? 0x0000FFFFu : 0u;   // sign clear and not zero
+    const uint32_t hi = ((a >> 16) - 1u) < 0x7FFFu ? 0xFFFF0000u : 0u;
+    return u & (lo | hi);
+}
+
 // Pixel tile of about BN output pixels (TI images x TH x TW) and its staged input extent; ext = reach of the taps.
 void pc_plan_mfma_tiles(MfmaArgs *g, int BN, int ext);
 
@@ -66,6 +80,8 @@ pc_status pc_run_mfma_conv_ws(pc_ctx *ctx, int pcfg, const MfmaArgs &g0, int ext
                               const uint16_t *in, uint16_t *out, const uint16_t *wz, const SparseOperand &sp, bool *launched,
                               int act = PC_ACT_NONE);
 
+pc_status pc_run_mfma_conv_dma(pc_ctx *ctx, int pcfg, double limit, const MfmaArgs &g0, bool flip, const uint16_t *in, uint16_t *out, const uint16_t *wz,
+                               bool *launched, int act);
 pc_status pc_run_mfma_conv_mc(pc_ctx *ctx, int pcfg, const MfmaArgs &g0, const uint16_t *in, uint16_t *out, const uint16_t *wz, bool *launched);
 
 // Copies between a tensor with C < 8 channels per pixel and one with 8-channel (16-byte) pixel rows.

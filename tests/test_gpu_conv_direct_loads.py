@@ -1,0 +1,105 @@
+"""The stride-1 forward / backward-data kernel that loads both operands straight to LDS (override codes 40 and 41), element by
+element against the oracle, at the edges of its tiles: rows that run across images (one zero row between two of them), columns past
+the map, a last chunk of 8, 16 or 24 channels, partial row tiles, and lists of tiles that continue in narrower ones."""
+import pytest
+
+from paper_2011_10170_amd import inputs as I
+from tests.test_gpu_parity import run_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_2011_10170_amd import binding
+    binding.load()
+    return binding
+
+
+@pytest.fixture(scope="module")
+def ctx(B):
+    import torch
+    c = B.pc_create(0, torch.cuda.current_stream().cuda_stream)
+    yield c
+    B.pc_destroy(c)
+
+
+SHAPES = [
+    (1, 1, 1, 8, 8, 1),          # one pixel, one group of channels
+    (3, 2, 3, 8, 16, 1),         # rows of several images in a tile
+    (1, 33, 47, 40, 72, 1),      # a last chunk of 8 channels, a row and columns past the last tile
+    (2, 31, 17, 56, 24, 1),      # 24 channels in the last chunk; one row short of a tile
+    (7, 16, 9, 80, 136, 1),      # images that divide a tile, 16 channels in the last chunk
+    (5, 13, 8, 64, 200, 1),      # images that do not
+    (1, 64, 5, 32, 64, 1),       # whole chunks and row tiles
+    (9, 96, 95, 16, 200, 1),     # more tiles than workgroups: the list ends in narrower tiles
+    (6, 96, 95, 40, 264, 1),
+]
+
+
+@pytest.mark.parametrize("cfg", [40, 41])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_every_element(B, ctx, oracle, cfg, shape):
+    B.pc_set_plan_override(ctx, cfg, 0)
+    try:
+        run_case(B, ctx, oracle, shape, "bf16", 8, 0.3, B.PC_VARIANT_MFMA, ("direct", cfg))
+    finally:
+        B.pc_set_plan_override(ctx, -1, 0)
+
+
+def test_many_small_images(B, ctx, oracle):
+    """A zero row between every four: only the narrower tile has the LDS for it."""
+    B.pc_set_plan_override(ctx, 40, 0)
+    try:
+        run_case(B, ctx, oracle, (70, 4, 4, 72, 64, 1), "bf16", 8, 0.3, B.PC_VARIANT_MFMA, ("direct", 40))
+    finally:
+        B.pc_set_plan_override(ctx, -1, 0)
+
+
+def test_taken_by_the_automatic_choice(B, ctx, oracle):
+    """A layer of the size it is for: sampled by the plain kernels of the other family, which add in another order."""
+    import torch
+    from tests._harness import Case, GpuLayer
+    layer = I.Layer(16, 56, 56, 64, 128, 1)
+    g = GpuLayer(B, ctx, Case(layer, "bf16", 8, I.kept_per_filter(0.3, layer.C), tag=("direct", "auto")))
+    try:
+        out = []
+        for cfg in (-1, 20):
+            B.pc_set_plan_override(ctx, cfg, 0)
+            y = torch.full((layer.N, layer.Ho, layer.Wo, layer.F), float("nan"), dtype=torch.bfloat16, device="cuda")
+            B.pc_conv_fwd(ctx, g.desc, g.pk, g.x, y)
+            out.append((B.pc_last_kernel(ctx), y.double()))
+        assert "pc_mfma_conv_dma_kernel" in out[0][0] and "pc_mfma_conv_ks_kernel" in out[1][0]
+        # two roundings to bf16 of sums that differ in the order of float32 additions: at most one unit in the last place apart
+        a, b = out[0][1], out[1][1]
+        assert bool((a - b).abs().le(2.0 ** -7 * torch.maximum(a.abs(), b.abs()) + 2.0 ** -12 * b.abs().max()).all())
+    finally:
+        B.pc_set_plan_override(ctx, -1, 0)
+        g.close()
+
+
+@pytest.mark.parametrize("cfg", [40, 41])
+@pytest.mark.parametrize("dims", [(6, 10, 9, 128, 160), (2, 33, 70, 24, 72), (9, 96, 95, 16, 200)])
+def test_fused_relu(B, ctx, cfg, dims):
+    """Bit-identical to the plain launch followed by the step."""
+    import torch
+    from tests._harness import Case, GpuLayer
+    L = I.Layer(*dims, 1)
+    g = GpuLayer(B, ctx, Case(L, "bf16", 8, I.kept_per_filter(0.3, L.C), tag=("direct_relu", cfg)))
+    try:
+        B.pc_set_plan_override(ctx, cfg, 0)
+        y = torch.empty((L.N, L.Ho, L.Wo, L.F), dtype=torch.bfloat16, device="cuda")
+        a, dx = torch.full_like(y, float("nan")), torch.empty((L.N, L.H, L.W, L.C), dtype=torch.bfloat16, device="cuda")
+        dz = torch.full_like(dx, float("nan"))
+        B.pc_conv_fwd(ctx, g.desc, g.pk, g.x, y)
+        B.pc_conv_fwd_relu(ctx, g.desc, g.pk, g.x, a)
+        B.pc_conv_bwd_data(ctx, g.desc, g.pk, g.dy, dx)
+        B.pc_conv_bwd_data_relu(ctx, g.desc, g.pk, g.dy, g.x, dz)
+        torch.cuda.synchronize()
+        assert torch.equal(a.view(torch.int16), torch.where(y > 0, y, torch.zeros_like(y)).view(torch.int16))
+        assert torch.equal(dz.view(torch.int16), torch.where(g.x > 0, dx, torch.zeros_like(dx)).view(torch.int16))
+    finally:
+        B.pc_set_plan_override(ctx, -1, 0)
+        g.close()
