@@ -127,13 +127,13 @@ pc_status pc_set_variant(pc_ctx *ctx, pc_variant v);
  *   30, 31 with tiles of 128 output channels x 128 and 256 pixels, 32- and 16-channel chunks
  *   32..36 stride-2 backward-data (the other passes stay automatic): the four parity classes of input pixels in one
  *          pass, tiles of 32 channels x 4 x 256 pixels with 64-, 32-, 16-channel chunks, x 4 x 128 with 64 and 32
- *   40, 41 stride 1: the kernel that loads both operands straight to LDS, tiles of 64 output channels x 32 rows of 2 and of 4
- *          columns per wavefront
+ *   40..43 stride 1: the kernel that loads both operands straight to LDS, tiles of 64 output channels x 64 x 8, 4, 7 and 2
+ *          pixels; the last with three buffers
  *   10, 11 backward-weight: the cooperative / the wave-specialised kernel (the other passes stay automatic)
  *   22     forward/backward-data: the structured-sparse kernel (packs made under PC_VARIANT_MFMA_SPARSE only)
  *   23     the first-layer kernels (stride 1, at most 4 input channels): the automatic choice takes them wherever
  *          they apply; any other code here keeps such a layer on the general kernels
- * The wave-specialised forward/backward-data kernel (7..9, 13..21, 24..31) takes 9-tap launches only, and so do 40 and 41: a stride-2
+ * The wave-specialised forward/backward-data kernel (7..9, 13..21, 24..31) takes 9-tap launches only, and so do 40..43: a stride-2
  * backward-data pass takes 0..6 (the cooperative kernel over the four parity classes of input pixels) and 32..36 and
  * uses the automatic choice otherwise. split_k > 0 forces that many splits of the reduction in the
  * cooperative forward/backward-data kernel (0 = automatic). A configuration that does not fit a layer makes

@@ -3,30 +3,33 @@
 #include "pc_mfma.h"
 #include <math.h>
 
-// A workgroup of 4 wavefronts owns 64 output channels x (32 rows x 1, 2 or 4 columns per wavefront); two workgroups share a CU.
-// The reduction runs in chunks of 32 input channels: the weights of a chunk (36 KiB) and the input tile with its border are
-// loaded straight into the workgroup's one LDS buffer, and all of the chunk's matrix instructions follow from there. One
-// workgroup loads (or stores a finished tile) while the other multiplies; a wavefront's priority rises through a chunk, so
-// that of two workgroups that multiply at the same time the one ahead finishes first and the two fall out of step by
-// themselves.
+// A workgroup of 4 wavefronts owns 64 output channels x 64 columns of 16 rows (fewer columns in the narrower forms). The reduction runs
+// in chunks of 32 input channels: the weights of a chunk (36 KiB) and the input tile with its border are loaded straight into an
+// LDS buffer, and all of the chunk's matrix instructions follow from there.
+//   Instruction: v_mfma_f32_16x16x32_bf16. The rate the chip holds depends on what the operands and sums toggle: fed from LDS with
+//     pruned weights and ReLU outputs 2.28 PFLOP/s against 2.0 with v_mfma_f32_32x32x16_bf16 (2.38 for both on zeros).
+//   Two ways of hiding the loads (NBUF). With one buffer two workgroups share a CU: one loads (or stores a finished tile) while the
+//     other multiplies; a wavefront's priority rises through a chunk, so that of two workgroups that multiply at the same time
+//     the one ahead finishes first and the two fall out of step by themselves. With two buffers a workgroup has the CU to itself
+//     and loads the next chunk while it multiplies: for launches of about one tile per CU.
 //   Rows: the rows of all images, N * H of them, in order. The staged tile is rows of "padded images" of H + 1 rows (one zero
-//     row between two images), so a tile covers any 32, 64 or 128 rows without a gap, whatever the map's height.
-//   Columns: the 32 lanes of a B fragment are 32 rows of one column, so the fragment of column j is the operand of tap column s
-//     for output column j - s: a tap row of a wavefront's 4 columns reads 6 fragments for its 24 matrix instructions beside the 6 of
-//     the weights.
+//     row between two images), so a tile covers any 16, 32 or 64 rows without a gap, whatever the map's height.
+//   Columns: the 16 columns of a B operand are 16 rows of one column of the map, so the fragment of column j is the operand of tap
+//     column s for output column j - s: the three taps of a row read BT + 2 fragments for BT columns.
 //   LDS: a staged row is its columns' 64 bytes and one 16-byte element more, so lanes a row apart start in different banks.
 // In the kernel that keeps the weights in registers (pc_conv_mfma_ws.hip) each of the four multiplying wavefronts requests the same
 // fragments, 64 B/clk of vector-cache hits, and nothing is multiplied while a tile is stored.
 
 #define DM_KC 32                     // input channels per chunk
-#define DM_NA 36                     // direct loads (1 KiB) of the weights per chunk: 2 row tiles x 9 taps x 2 k-steps
+#define DM_NA 36                     // direct loads (1 KiB) of the weights per chunk: 9 taps x 4 fragments of 16 output channels
 #define DM_NB 11                     // of the input tile per wavefront at most
+#define DM_NBW 4                     // the same where every wavefront has as many
 #define DM_A_BYTES (DM_NA * 1024)
 #define DM_OOB 0x80000000u           // past the end of any tensor taken here, also with a chunk's offset added
-#define DM_LDS_MAX (80 * 1024)       // two workgroups per CU
+#define DM_LDS_MAX (160 * 1024)
 #define DM_STG 144                   // bytes per pixel (64 channels) where a finished tile passes through LDS
 
-// The tile's columns and staged columns for 1, 2 or 4 columns per wavefront.
+// Staged columns for a tile width
 struct DmaGeo {
     int32_t IW, EPR, nB;             // staged columns, 16-byte elements per staged row, direct loads of the input tile
     uint32_t mg_EPR;
@@ -38,13 +41,13 @@ struct DmaArgs {
     int32_t flip;                    // position t of the 3 x 3 neighbourhood takes weight tap 8 - t (backward-data)
     int32_t lgCG;                    // log2 of the wavefronts side by side in a tile's columns; the others lie below each other
     int32_t TR, nrow, rows;          // rows of a tile, staged rows, N * H
-    int32_t m_fast, fdiv, tiles_x;   // tile index = slow * fdiv + fast, as in MfmaArgs; column tiles of the widest part
-    // Parts of the list of tiles: end[2], end[1], end[0] are the tiles of 4, 2 and 1 columns per wavefront up to which a part
-    // runs; tile t of a part lies where tile t >> 1 of the part with twice the columns would.
-    int32_t lgB, end[3];
-    uint32_t in_bytes, out_bytes, wz_bytes;
+    int32_t m_fast, fdiv, tiles_x;   // tile index = slow * fdiv + fast, as in MfmaArgs; column tiles
+    // The list of tiles: `rounds` whole rounds (a tile for every workgroup), then `last` tiles, one each for the first workgroups, and
+    // the remaining tiles cut into 1 << lgP pieces of their columns, one each for the workgroups after those
+    int32_t rounds, last, pieces, lgP;
+    uint32_t in_bytes, out_bytes, wz_bytes, buf_bytes;
     uint32_t mg_fd, mg_tx, mg_H, mg_H1;
-    DmaGeo geo[3];                   // by log2 of the columns per wavefront
+    DmaGeo geo[3];                   // whole tiles, halves, quarters
     const uint16_t *act_mask;
 };
 
@@ -55,6 +58,12 @@ __device__ __forceinline__ void dm_load(const v4u32 &rsrc, int voff, int soff, i
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                  :: "s"(lds_off), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+}
+
+// All but the last N vector memory operations of this wavefront are complete, and every wavefront has come here.
+template <int N> __device__ __forceinline__ void dm_wait_barrier()
+{
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"(N) : "memory");
 }
 
 // The words of a buffer resource (what __builtin_amdgcn_make_buffer_rsrc builds, as an operand of inline assembly).
@@ -70,17 +79,17 @@ __device__ __forceinline__ v4u32 dm_rsrc(const void *p, uint32_t bytes)
 struct DmaTile { int mt, r0, x0; };  // tile of 64 output channels, first row, first column
 
 struct DmaWave {
-    int lane, w, cg, rg, G;
+    int lane, w, cg, rg;
     v4u32 xs, ws;
     int a_voff;
     uint32_t voff[DM_NB];            // byte offsets of this lane's elements of the input tile, first chunk
     uint32_t part;                   // two bits per element: which 8 of the chunk's 32 channels
 };
 
-// Tile t of the part with 1 << lg columns per wavefront.
-__device__ __forceinline__ DmaTile dm_tile(const DmaArgs &g, int t, int lg)
+// Piece t of tiles of BT columns per wavefront cut into 1 << sh pieces.
+template <int BT>
+__device__ __forceinline__ DmaTile dm_tile(const DmaArgs &g, int t, int sh)
 {
-    const int sh = g.lgB - lg;
     const uint32_t p = (uint32_t)t >> sh;
     const uint32_t tq = pc_udiv(p, g.mg_fd), trm = p - tq * g.fdiv;
     const uint32_t pt = g.m_fast ? tq : trm;
@@ -88,7 +97,7 @@ __device__ __forceinline__ DmaTile dm_tile(const DmaArgs &g, int t, int lg)
     DmaTile o;
     o.mt = (int)(g.m_fast ? trm : tq);
     o.r0 = (int)rt * g.TR;
-    o.x0 = (int)(((pt - rt * g.tiles_x) << sh) + ((uint32_t)t & ((1u << sh) - 1u))) << (lg + g.lgCG);
+    o.x0 = (int)(((pt - rt * g.tiles_x) * BT + ((uint32_t)t & ((1u << sh) - 1u)) * (BT >> sh)) << g.lgCG);
     return o;
 }
 
@@ -97,9 +106,11 @@ __device__ __forceinline__ void dm_offsets(DmaWave &s, const DmaArgs &g, const D
 {
     const int V0 = t.r0 + (int)pc_udiv((uint32_t)t.r0, g.mg_H);
     s.part = 0;
+    int lane = s.lane;      // (hidden from the compiler: it would keep the quotients of all elements from tile to tile, in scratch)
+    asm volatile("" : "+v"(lane));
 #pragma unroll
     for (int k = 0; k < DM_NB; ++k) {
-        const uint32_t e = (uint32_t)((s.w + 4 * k) * 64 + s.lane);
+        const uint32_t e = (uint32_t)((s.w + 4 * k) * 64 + lane);
         const uint32_t row = pc_udiv(e, q.mg_EPR), rem = e - row * q.EPR;
         const uint32_t v = V0 + row;
         const int n = (int)pc_udiv(v, g.mg_H1);
@@ -110,142 +121,157 @@ __device__ __forceinline__ void dm_offsets(DmaWave &s, const DmaArgs &g, const D
     }
 }
 
-__device__ __forceinline__ void dm_issue(const DmaWave &s, const DmaArgs &g, int nB, int mt, int ch)
+// The direct loads of chunk ch of a tile (its offsets are in s) into the buffer at lb, in 9 steps: step t brings this wavefront's
+// fragment of tap position t and its loads t and t + 9 of the input tile (nB of them in the workgroup; NBW > 0: NBW for every wavefront).
+//   Fragment (position t, a): row m of it is output channel 16 * (m / 4) + 4 * a + m % 4 of the tile, so that a lane's sums are 16
+//   consecutive channels. Wavefront w loads fragment w of every position.
+template <int NBW>
+__device__ __forceinline__ void dm_issue(const DmaWave &s, const DmaArgs &g, int nB, int mt, int ch, int lb, int t)
 {
-    // Fragment f of the chunk: row tile f & 1, tap position (f / 2) % 9, k-step f / 18. A lane takes the row whose number has bits 2
-    // and 3 exchanged: 8 of its 16 accumulators are then 8 consecutive output channels.
     // (the wavefront's number is hidden from the compiler here: it would compute all scalar offsets ahead and spill them)
     int w = s.w;
     asm volatile("" : "+s"(w));
-#pragma unroll
-    for (int k = 0; k < DM_NA / 4; ++k) {
-        const int f = w + 4 * k, t = (f >> 1) % 9, kk = f / 18;
-        dm_load(s.ws, s.a_voff, (((mt * 2 + (f & 1)) * 9 + (g.flip ? 8 - t : t)) * g.KS + ch * 2 + kk) * 1024, f * 1024);
-    }
+    dm_load(s.ws, s.a_voff, ((mt * 18 + (g.flip ? 8 - t : t)) * g.KS + ch * 2) * 1024 + w * 64, lb + (t * 4 + w) * 1024);
     const bool cut = ch == g.nch - 1 && (g.in_CH & (DM_KC - 1));      // channels past the last one are zeros
     const uint32_t parts = (uint32_t)(g.in_CH & (DM_KC - 1)) >> 3;
 #pragma unroll
-    for (int k = 0; k < DM_NB; ++k) {
+    for (int k = t; k < (NBW ? NBW : DM_NB); k += 9) {
         const int b = w + 4 * k;
-        if (b < nB) {
+        if (NBW || b < nB) {
             uint32_t vo = s.voff[k];
             if (cut) vo = ((s.part >> (2 * k)) & 3u) >= parts ? DM_OOB : vo;
-            dm_load(s.xs, (int)vo, ch * (DM_KC * 2), DM_A_BYTES + b * 1024);
+            dm_load(s.xs, (int)vo, ch * (DM_KC * 2), lb + DM_A_BYTES + b * 1024);
         }
     }
 }
 
-// The matrix instructions of one chunk; pa, pb: this lane's first weight and input fragment, RP: bytes per staged row. The
-// fragments of a tap are read during the one before it, the input fragments of a tap row during the one before.
-template <int BT>
-__device__ __forceinline__ void dm_chunk(f32x16 (&acc)[2][BT], const unsigned char *pa, const unsigned char *pb, int RP)
+// The matrix instructions of one chunk; pa, pb: this lane's first weight and input fragment, RP: bytes per staged row. The weight
+// fragments of a tap are read during the one before it; the input fragments of the next tap row replace those of this one as its last
+// tap has used them. loads(t): called at the start of tap t.
+template <int BT, class Loads>
+__device__ __forceinline__ void dm_chunk(f32x4 (&acc)[4][BT], const unsigned char *pa, const unsigned char *pb, int RP, Loads loads)
 {
-    constexpr int HB = (BT + 3) / 2;   // the fragments of the next tap row are read in two parts
-    bf16x8 aq[2][2], bq[2][BT + 2];
+    bf16x8 aq[2][4], bq[BT + 2];
 #pragma unroll
-    for (int c = 0; c < BT + 2; ++c) bq[0][c] = *reinterpret_cast<const bf16x8 *>(pb + c * 64);
+    for (int a = 0; a < 4; ++a) aq[0][a] = *reinterpret_cast<const bf16x8 *>(pa + a * 1024);
 #pragma unroll
-    for (int ii = 0; ii < 2; ++ii) aq[0][ii] = *reinterpret_cast<const bf16x8 *>(pa + ii * 1024);
+    for (int c = 0; c < BT + 2; ++c) bq[c] = *reinterpret_cast<const bf16x8 *>(pb + c * 64);
 #pragma unroll
-    for (int t = 0; t < 18; ++t) {
-        const int rr = t / 3, s = t % 3;
-        if (t == 6) __builtin_amdgcn_s_setprio(1);
-        if (t == 12) __builtin_amdgcn_s_setprio(2);
-        if (t < 17) {
-#pragma unroll
-            for (int ii = 0; ii < 2; ++ii) aq[(t + 1) & 1][ii] = *reinterpret_cast<const bf16x8 *>(pa + ((t + 1) * 2 + ii) * 1024);
-        }
-        if (rr < 5 && s < 2) {
-#pragma unroll
-            for (int c = s * HB; c < (s + 1) * HB && c < BT + 2; ++c)
-                bq[(rr + 1) & 1][c] = *reinterpret_cast<const bf16x8 *>(pb + ((rr + 1) % 3) * RP + c * 64 + ((rr + 1) / 3) * 32);
+    for (int t = 0; t < 9; ++t) {
+        const int r = t / 3, q = t % 3;
+        const bool refill = q == 2 && r < 2;
+        loads(t);
+        if (t == 3) __builtin_amdgcn_s_setprio(1);
+        if (t == 6) __builtin_amdgcn_s_setprio(2);
+        if (refill) {
+            bq[0] = *reinterpret_cast<const bf16x8 *>(pb + (r + 1) * RP);
+            bq[1] = *reinterpret_cast<const bf16x8 *>(pb + (r + 1) * RP + 64);
         }
 #pragma unroll
-        for (int ii = 0; ii < 2; ++ii)
+        for (int j = 0; j < BT; ++j) {
+            if (t < 8) {
 #pragma unroll
-            for (int j = 0; j < BT; ++j)
-                acc[ii][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(aq[t & 1][ii], bq[rr & 1][j + s], acc[ii][j], 0, 0, 0);
+                for (int a = j * 4 / BT; a < (j + 1) * 4 / BT; ++a)
+                    aq[(t + 1) & 1][a] = *reinterpret_cast<const bf16x8 *>(pa + ((t + 1) * 4 + a) * 1024);
+            }
 #pragma unroll
-        for (int m = 0; m < 2 * BT; ++m) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                  // one matrix instruction
-            __builtin_amdgcn_sched_group_barrier(0x100, BT == 1 ? 2 : 1, 0);    // LDS reads
+            for (int a = 0; a < 4; ++a) acc[a][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aq[t & 1][a], bq[j + q], acc[a][j], 0, 0, 0);
+            if (refill) bq[j + 2] = *reinterpret_cast<const bf16x8 *>(pb + (r + 1) * RP + (j + 2) * 64);
+        }
+        // (in program order: reads go into the shadow of the matrix instructions one at a time)
+        if (refill) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+#pragma unroll
+        for (int j = 0; j < BT; ++j) {
+            if (t < 8 && (j + 1) * 4 / BT > j * 4 / BT) __builtin_amdgcn_sched_group_barrier(0x100, BT < 4 ? 4 / BT : 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+            if (refill) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
         }
         __builtin_amdgcn_sched_barrier(0);
     }
 }
 
-// The tiles first, first + G, ... < end of the part with BT = 1 << LG columns per wavefront. fresh: nothing has used LDS yet.
-template <int LG, int ACT>
-__device__ __forceinline__ void dm_part(DmaWave &s, const DmaArgs &g, unsigned char *lds, __amdgpu_buffer_rsrc_t osrc, __amdgpu_buffer_rsrc_t msrc,
-                                        int first, int end, bool &fresh)
+// Where a lane of a wavefront reads a tile, and the wavefront's sums of a finished tile on their way out through the LDS at stg
+// (of this wavefront alone): 64 pixels at a time, so that 8 lanes store the 128 bytes of a pixel.
+__device__ __forceinline__ int dm_lane_row(const DmaWave &s, const DmaArgs &g, const DmaTile &t)
 {
-    constexpr int BT = 1 << LG;
-    const DmaGeo q = g.geo[LG];
-    const int RP = q.EPR * 16;
-    for (int ti = first; ti < end; ti += s.G) {
-        const DmaTile t = dm_tile(g, ti, LG);
-        dm_offsets(s, g, q, t);
-        // rows past the last one are multiplied with the last one's operands and not stored
-        const int row = t.r0 + s.rg * 32 + (s.lane & 31), rowc = row < g.rows ? row : g.rows - 1;
-        const int lrow = rowc + (int)pc_udiv((uint32_t)rowc, g.mg_H) - (t.r0 + (int)pc_udiv((uint32_t)t.r0, g.mg_H));
-        const unsigned char *pa = lds + s.lane * 16, *pb = lds + DM_A_BYTES + lrow * RP + (s.lane >> 5) * 16 + s.cg * (BT * 64);
-        f32x16 acc[2][BT];
+    // rows past the last one are multiplied with the last one's operands and not stored
+    const int row = t.r0 + s.rg * 16 + (s.lane & 15), rowc = row < g.rows ? row : g.rows - 1;
+    return rowc + (int)pc_udiv((uint32_t)rowc, g.mg_H) - (t.r0 + (int)pc_udiv((uint32_t)t.r0, g.mg_H));
+}
+
+template <int BT, int ACT>
+__device__ __forceinline__ void dm_store(const DmaWave &s, const DmaArgs &g, const DmaTile &t, const f32x4 (&acc)[4][BT], unsigned char *stg,
+                                         __amdgpu_buffer_rsrc_t osrc, __amdgpu_buffer_rsrc_t msrc)
+{
 #pragma unroll
-        for (int ii = 0; ii < 2; ++ii)
+    for (int j0 = 0; j0 < BT; j0 += 4) {
+        constexpr int FULL = BT < 4 ? BT : 4;
+        const int NC = BT - j0 < FULL ? BT - j0 : FULL;        // columns of this pass
+        v4u32 mk[FULL * 2];
+        uint32_t off[FULL * 2];
 #pragma unroll
-            for (int j = 0; j < BT; ++j)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[ii][j][r] = 0.0f;
-        for (int ch = 0; ch < g.nch; ++ch) {
-            if (!fresh) asm volatile("s_barrier" ::: "memory");      // every wavefront has read what the loads replace
-            fresh = false;
-            __builtin_amdgcn_s_setprio(3);
-            dm_issue(s, g, q.nB, t.mt, ch);
-            __builtin_amdgcn_s_setprio(0);
-            asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
-            dm_chunk<BT>(acc, pa, pb, RP);
+        for (int it = 0; it < NC * 2; ++it) {
+            const int px = it * 8 + (s.lane >> 3);
+            const int orow = t.r0 + s.rg * 16 + (px & 15), x = t.x0 + s.cg * BT + j0 + (px >> 4), m = t.mt * 64 + (s.lane & 7) * 8;
+            off[it] = orow < g.rows && x < g.W && m < g.out_CH ? (uint32_t)(orow * g.W + x) * (uint32_t)(g.out_CH * 2) + (uint32_t)(m * 2) : DM_OOB;
+            if (ACT == PC_ACT_RELU_MASK) mk[it] = __builtin_amdgcn_raw_buffer_load_b128(msrc, (int)off[it], 0, 0);
         }
-        // The tile leaves through LDS, 32 rows x 2 columns of a wavefront at a time, so that 8 lanes store the 128 bytes of a pixel.
-        __builtin_amdgcn_s_setprio(3);
-        asm volatile("s_barrier" ::: "memory");
-        constexpr int NC = BT == 1 ? 1 : 2, NP = NC * 4;
-        unsigned char *stg = lds + s.w * (64 * DM_STG);
 #pragma unroll
-        for (int h = 0; h < BT / NC; ++h) {
-            v4u32 mk[NP];
-            uint32_t off[NP];
+        for (int j = 0; j < NC; ++j)
 #pragma unroll
-            for (int it = 0; it < NP; ++it) {
-                const int px = it * 8 + (s.lane >> 3);
-                const int orow = t.r0 + s.rg * 32 + (px & 31), x = t.x0 + s.cg * BT + h * NC + (px >> 5), m = t.mt * 64 + (s.lane & 7) * 8;
-                off[it] = orow < g.rows && x < g.W && m < g.out_CH ? (uint32_t)(orow * g.W + x) * (uint32_t)(g.out_CH * 2) + (uint32_t)(m * 2) : DM_OOB;
-                if (ACT == PC_ACT_RELU_MASK) mk[it] = __builtin_amdgcn_raw_buffer_load_b128(msrc, (int)off[it], 0, 0);
+            for (int e = 0; e < 2; ++e) {      // 8 of the lane's 16 channels: 16 * (lane / 16) + 8 * e ..
+                v4u32 pv;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) pv[u] = pc_pack_bf16x2(acc[e * 2 + (u >> 1)][j0 + j][(u & 1) * 2], acc[e * 2 + (u >> 1)][j0 + j][(u & 1) * 2 + 1]);
+                *reinterpret_cast<v4u32 *>(stg + (j * 16 + (s.lane & 15)) * DM_STG + (s.lane >> 4) * 32 + e * 16) = pv;
             }
 #pragma unroll
-            for (int jj = 0; jj < NC; ++jj)
+        for (int it = 0; it < NC * 2; ++it) {
+            v4u32 pv = *reinterpret_cast<const v4u32 *>(stg + (it * 8 + (s.lane >> 3)) * DM_STG + (s.lane & 7) * 16);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {       // accumulators 8 * (e & 1) .. + 7 of row tile e >> 1: channels 16 * e + 8 * (lane / 32) .. + 7
-                    v4u32 pv;
-#pragma unroll
-                    for (int u = 0; u < 4; ++u)
-                        pv[u] = pc_pack_bf16x2(acc[e >> 1][h * NC + jj][(e & 1) * 8 + 2 * u], acc[e >> 1][h * NC + jj][(e & 1) * 8 + 2 * u + 1]);
-                    *reinterpret_cast<v4u32 *>(stg + (jj * 32 + (s.lane & 31)) * DM_STG + e * 32 + (s.lane >> 5) * 16) = pv;
-                }
-#pragma unroll
-            for (int it = 0; it < NP; ++it) {
-                v4u32 pv = *reinterpret_cast<const v4u32 *>(stg + (it * 8 + (s.lane >> 3)) * DM_STG + (s.lane & 7) * 16);
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    if (ACT == PC_ACT_RELU) pv[u] = pc_relu_bf16x2(pv[u]);
-                    if (ACT == PC_ACT_RELU_MASK) pv[u] = pc_mask_bf16x2(pv[u], mk[it][u]);
-                }
-                __builtin_amdgcn_raw_buffer_store_b128(pv, osrc, (int)off[it], 0, 0);
+            for (int u = 0; u < 4; ++u) {
+                if (ACT == PC_ACT_RELU) pv[u] = pc_relu_bf16x2(pv[u]);
+                if (ACT == PC_ACT_RELU_MASK) pv[u] = pc_mask_bf16x2(pv[u], mk[it][u]);
             }
+            __builtin_amdgcn_raw_buffer_store_b128(pv, osrc, (int)off[it], 0, 0);
         }
     }
 }
 
-template <int LG, int ACT>
+template <int BT> __device__ __forceinline__ void dm_zero(f32x4 (&acc)[4][BT])
+{
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int j = 0; j < BT; ++j) acc[a][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+}
+
+// One tile of BT columns per wavefront, one buffer. fresh: nothing has used LDS yet.
+template <int BT, int ACT>
+__device__ __forceinline__ void dm_one_tile(DmaWave &s, const DmaArgs &g, const DmaGeo &q, unsigned char *lds, __amdgpu_buffer_rsrc_t osrc,
+                                            __amdgpu_buffer_rsrc_t msrc, const DmaTile &t, bool &fresh)
+{
+    dm_offsets(s, g, q, t);
+    const unsigned char *pa = lds + s.lane * 16;
+    const unsigned char *pb = lds + DM_A_BYTES + dm_lane_row(s, g, t) * (q.EPR * 16) + (s.lane >> 4) * 16 + s.cg * (BT * 64);
+    f32x4 acc[4][BT];
+    dm_zero<BT>(acc);
+    for (int ch = 0; ch < g.nch; ++ch) {
+        if (!fresh) asm volatile("s_barrier" ::: "memory");      // every wavefront has read what the loads replace
+        fresh = false;
+        __builtin_amdgcn_s_setprio(3);
+#pragma unroll
+        for (int i = 0; i < 9; ++i) dm_issue<0>(s, g, q.nB, t.mt, ch, 0, i);
+        __builtin_amdgcn_s_setprio(0);
+        dm_wait_barrier<0>();
+        dm_chunk<BT>(acc, pa, pb, q.EPR * 16, [](int) {});
+    }
+    __builtin_amdgcn_s_setprio(3);
+    asm volatile("s_barrier" ::: "memory");
+    dm_store<BT, ACT>(s, g, t, acc, lds + s.w * (64 * DM_STG), osrc, msrc);
+}
+
+template <int BT, int NBUF, int ACT>
 __global__ void __launch_bounds__(256, 2)
 pc_mfma_conv_dma_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__ out, const uint16_t *__restrict__ wz, DmaArgs g)
 {
@@ -255,32 +281,97 @@ pc_mfma_conv_dma_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__ 
     s.w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     s.cg = s.w & ((1 << g.lgCG) - 1);
     s.rg = s.w >> g.lgCG;
-    s.G = gridDim.x;
-    int vb = blockIdx.x;
-    if ((s.G & 7) == 0) vb = (blockIdx.x & 7) * (s.G >> 3) + (blockIdx.x >> 3);   // neighbours in the tile order share an XCD
+    const int G = gridDim.x, b = blockIdx.x;
+    // Workgroups go to the XCDs round robin, and to a CU a second time when each has one: neighbours in the tile order share an XCD, and
+    // what does not fill a round has a CU each.
+    const int vb = (G & 7) == 0 ? (b & 7) * (G >> 3) + (b >> 3) : b;
+    const int vl = (g.last & 7) == 0 ? (b & 7) * (g.last >> 3) + (b >> 3) : b;
     s.xs = dm_rsrc(in, g.in_bytes);
     s.ws = dm_rsrc(wz, g.wz_bytes);
-    s.a_voff = ((s.lane & ~12) | ((s.lane & 4) << 1) | ((s.lane & 8) >> 1)) * 16;
+    {
+        const int m = s.lane & 15, kg = s.lane >> 4;
+        s.a_voff = (m >> 3) * (9 * 1024) * g.KS + (kg >> 1) * 1024 + (kg & 1) * 512 + (16 * ((m >> 2) & 1) + (m & 3)) * 16;
+    }
     const __amdgpu_buffer_rsrc_t osrc = __builtin_amdgcn_make_buffer_rsrc(out, 0, g.out_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t msrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint16_t *>(ACT == PC_ACT_RELU_MASK ? g.act_mask : out), 0, g.out_bytes, 0x00020000);
-    bool fresh = true;
-    if constexpr (LG >= 2) dm_part<2, ACT>(s, g, lds, osrc, msrc, vb, g.end[2], fresh);
-    dm_part<1, ACT>(s, g, lds, osrc, msrc, 2 * g.end[2] + vb, g.end[1], fresh);
-    dm_part<0, ACT>(s, g, lds, osrc, msrc, 2 * g.end[1] + vb, g.end[0], fresh);
+    const int ntile = g.rounds + (b < g.last);
+    auto tile_at = [&](int k) { return dm_tile<BT>(g, k < g.rounds ? k * G + vb : g.rounds * G + vl, 0); };
+    if constexpr (NBUF == 1) {
+        bool fresh = true;
+        for (int k = 0; k < ntile; ++k) dm_one_tile<BT, ACT>(s, g, g.geo[0], lds, osrc, msrc, tile_at(k), fresh);
+        if constexpr (BT == 8 || BT == 4) {
+            const int p0 = (g.rounds * G + g.last) << g.lgP;
+            for (int u = (b - g.last + 2 * G) % G; u < g.pieces; u += G) {
+                const DmaTile t = dm_tile<BT>(g, p0 + u, g.lgP);
+                if (g.lgP == 1) dm_one_tile<BT / 2, ACT>(s, g, g.geo[1], lds, osrc, msrc, t, fresh);
+                else if constexpr (BT == 8) dm_one_tile<2, ACT>(s, g, g.geo[2], lds, osrc, msrc, t, fresh);
+            }
+        }
+    } else {
+        // Chunk i of the workgroup's list is loaded during chunk i - AHEAD, a step per tap.
+        constexpr int AHEAD = NBUF - 1, NBW = NBUF == 3 ? DM_NBW : 0;
+        const DmaGeo &q = g.geo[0];
+        const int RP = q.EPR * 16, chunks = ntile * g.nch;
+        DmaTile t = tile_at(0), tl = t;      // the tile being multiplied, the one being loaded
+        int kl = 0, chl = 0, bl = 0;         // cursor of the loads: tile, chunk, buffer
+        dm_offsets(s, g, q, tl);
+        auto advance = [&]() {
+            if (++bl == NBUF) bl = 0;
+            if (++chl == g.nch) {
+                chl = 0;
+                if (++kl < ntile) {
+                    tl = tile_at(kl);
+                    dm_offsets(s, g, q, tl);
+                }
+            }
+        };
+        for (int i = 0; i < AHEAD && i < chunks; ++i) {
+#pragma unroll
+            for (int j = 0; j < 9; ++j) dm_issue<NBW>(s, g, q.nB, tl.mt, chl, bl * g.buf_bytes, j);
+            advance();
+        }
+        int bc = 0;
+        for (int k = 0; k < ntile; ++k) {
+            const int at = s.lane * 16, bt = DM_A_BYTES + dm_lane_row(s, g, t) * RP + (s.lane >> 4) * 16 + s.cg * (BT * 64);
+            f32x4 acc[4][BT];
+            dm_zero<BT>(acc);
+            for (int ch = 0; ch < g.nch; ++ch) {
+                // this chunk's loads are complete: what follows them is the next chunk's loads, and a finished tile's stores
+                if (AHEAD == 2) {
+                    if (k * g.nch + ch + 1 < chunks) dm_wait_barrier<9 + NBW>();
+                    else dm_wait_barrier<0>();
+                } else if (k > 0 && ch == 0) dm_wait_barrier<2 * BT>();
+                else dm_wait_barrier<0>();
+                const unsigned char *lb = lds + bc * g.buf_bytes;
+                const bool more = kl < ntile;
+                dm_chunk<BT>(acc, lb + at, lb + bt, RP, [&](int j) __attribute__((always_inline)) {
+                    if (more) dm_issue<NBW>(s, g, q.nB, tl.mt, chl, bl * g.buf_bytes, j);
+                });
+                if (more) advance();
+                if (++bc == NBUF) bc = 0;
+            }
+            asm volatile("s_barrier" ::: "memory");                   // the buffer just multiplied is free
+            dm_store<BT, ACT>(s, g, t, acc, lds + (bc == 0 ? NBUF - 1 : bc - 1) * g.buf_bytes + s.w * (64 * DM_STG), osrc, msrc);
+            if (k + 1 < ntile) t = tile_at(k + 1);
+        }
+    }
 }
 
 // ---- plan and launch
+struct DmaCand { int code, bt, nbuf; };
+static const DmaCand kDma[] = {{40, 8, 1}, {41, 4, 1}, {42, 7, 1}, {43, 2, 3}};
+static const int kNumDma = sizeof(kDma) / sizeof(kDma[0]);
 
-// Fills the plan for 1 << lgB columns per wavefront and 1 << lgCG wavefronts side by side; false when it does not fit.
-static bool plan_dma(const MfmaArgs &g, bool flip, int lgB, int lgCG, DmaArgs *out, size_t *lds, int *grid, double *est, int num_cu)
+// Fills the plan for a kernel and 1 << lgCG wavefronts side by side; false when it does not fit.
+static bool plan_dma(const MfmaArgs &g, bool flip, const DmaCand &cand, int lgCG, DmaArgs *out, size_t *lds, int *grid, double *est, int num_cu)
 {
     DmaArgs t;
     memset(&t, 0, sizeof(t));
     t.N = g.N; t.H = g.in_H; t.W = g.in_W; t.in_CH = g.in_CH; t.out_CH = g.out_CH;
     t.KS = g.KS; t.nch = (g.in_CH + DM_KC - 1) / DM_KC; t.flip = flip;
-    t.lgCG = lgCG; t.lgB = lgB;
-    t.TR = 32 * (4 >> lgCG);
+    t.lgCG = lgCG;
+    t.TR = 16 * (4 >> lgCG);
     const int64_t rows = (int64_t)g.N * g.in_H;
     if ((rows + g.N + 2 * t.TR) * (g.in_H + 1) >= ((int64_t)1 << 32) || rows >= (1 << 24)) return false;   // multiply-high divisions stay exact
     t.rows = (int)rows;
@@ -288,16 +379,17 @@ static bool plan_dma(const MfmaArgs &g, bool flip, int lgB, int lgCG, DmaArgs *o
     int cross = g.in_H % t.TR == 0 ? 0 : t.TR % g.in_H == 0 ? t.TR / g.in_H - 1 : (t.TR - 1 + g.in_H - 1) / g.in_H;
     if (cross > g.N - 1) cross = g.N - 1;
     t.nrow = t.TR + 2 + cross;
-    for (int l = 0; l <= lgB; ++l) {
+    for (int l = 0; l < 3; ++l) {
         DmaGeo &q = t.geo[l];
-        q.IW = (1 << (l + lgCG)) + 2;
+        q.IW = ((cand.bt >> l) << lgCG) + 2;
         q.EPR = (DM_KC / 8) * q.IW + 1;
         q.mg_EPR = pc_udiv_magic(q.EPR);
         q.nB = (t.nrow * q.EPR + 63) / 64;
     }
-    const int nB = t.geo[lgB].nB, TC = 1 << (lgB + lgCG);
-    *lds = (size_t)DM_A_BYTES + (size_t)nB * 1024;
-    if (nB > 4 * DM_NB || *lds > DM_LDS_MAX) return false;
+    const int nB = t.geo[0].nB, TC = cand.bt << lgCG;
+    t.buf_bytes = DM_A_BYTES + (uint32_t)(cand.nbuf == 3 ? 4 * DM_NBW : nB) * 1024;
+    *lds = (size_t)t.buf_bytes * cand.nbuf;
+    if (nB > 4 * (cand.nbuf == 3 ? DM_NBW : DM_NB) || *lds > (size_t)DM_LDS_MAX / (cand.nbuf == 1 ? 2 : 1)) return false;
     t.tiles_x = (g.in_W + TC - 1) / TC;
     const int64_t p_tiles = (rows + t.TR - 1) / t.TR * t.tiles_x;
     const int m_tiles = (g.out_CH + 63) / 64;
@@ -312,71 +404,68 @@ static bool plan_dma(const MfmaArgs &g, bool flip, int lgB, int lgCG, DmaArgs *o
     t.mg_fd = pc_udiv_magic(t.fdiv); t.mg_tx = pc_udiv_magic(t.tiles_x);
     t.mg_H = pc_udiv_magic(g.in_H); t.mg_H1 = pc_udiv_magic(g.in_H + 1);
     t.act_mask = g.act_mask;
-    // Estimated time (us). A round is one tile for each of the workgroups the chip holds, two per CU; a last round of at most one
-    // tile per CU has each CU's whole rate for its tiles. A tile takes its chunks, each a fixed time and one for its direct loads of
-    // the input, and an end; the tensors take their bytes (the input with its border, in pieces of 64) at 4.5 TB/s, what these
-    // loads reach where the tensors come from memory and not, as in a loop over one layer, from the last cache (there 7). Constants for
-    // 4, 2 and 1 columns per wavefront from 1790 timings of 127 layer shapes (1 to 125 images, 4 x 4 to 224 x 224, 8 to 512
-    // channels; 7 % rms; the plan with the least estimate is on average 2 % slower than the fastest of a shape).
-    // What is left over after whole rounds of the widest tiles goes to narrower ones where that is estimated to end earlier:
-    // 56 x 56, 256 -> 256, batch 32 is 784 tiles of 4 columns for 512 workgroups; 512 of them, 512 of 2 columns and 64 of 1
-    // column take 85.6 us instead of 90.5, 14 x 14, 512 -> 512 32.4 instead of 54.
-    static const double kPair[3][3] = {{1.288, 0.0127, 1.86}, {2.116, 0.0166, 2.111}, {2.082, 0.0672, 3.27}};    // chunk, direct load, tile
-    static const double kOne[3][3] = {{0.977, 0.0134, 0.953}, {1.311, 0.0149, 1.433}, {2.337, 0.0113, 2.546}};
-    const int slots = num_cu * 2;
+    // Estimated time (us). A round is one tile for each of the workgroups the chip holds, two per CU; a workgroup that has its CU to
+    // itself takes its chunks faster. A chunk takes a fixed time and one for its direct loads of the input, a tile an end; the
+    // tensors take their bytes (the input with its border, in pieces of 64) at 6 TB/s (7.9 where they come from the last cache, as
+    // in a loop over one layer). Constants for 8, 7, 4 and 2 columns per wavefront, and for 2 with three buffers, from 4000
+    // timings of 147 layer shapes (1 to 128 images, 4 x 4 to 224 x 224, 8 to 512 channels; 8 % rms; the plan with the
+    // least estimate is on average 3.5 % slower than the fastest of a shape).
+    // What does not fill a round of tiles may be cut in halves or quarters, all of it or what a tile per CU leaves: 56 x 56,
+    // 256 -> 256, batch 32 is 784 tiles of 8 columns for 512 workgroups; 512 + 256 tiles and 16 cut into 64 quarters
+    // take 77 us instead of 85.
+    struct Times { double chunk, load, tile; };
+    static const Times kPair[4] = {{2.627, 0.0391, 2.225}, {2.232, 0.0405, 2.374}, {1.779, 0.0215, 1.669}, {1.047, 0.0361, 1.416}};
+    static const Times kOne[4] = {{2.960, 0.0001, 1.658}, {2.614, 0.0, 1.425}, {1.693, 0.0038, 0.940}, {1.047, 0.0103, 0.671}};
+    static const Times kSolo = {0.949, 0.002, 0.947};
+    auto tile_us = [&](const Times &c, int l) { return t.nch * (c.chunk + c.load * t.geo[l].nB) + c.tile; };
+    const int first = cand.bt == 8 ? 0 : cand.bt == 7 ? 1 : 2;
+    const int slots = num_cu * (cand.nbuf == 1 ? 2 : 1);
+    t.rounds = (int)(total / slots);
+    const int left = (int)(total % slots);
     double best = 1e30;
-    int64_t most = 0;
-    for (int o = 0; o < 4; ++o) {     // o & 1: the first part ends with its last whole round, o & 2: so does the second
-        int64_t n[3] = {0, 0, 0}, left = total, m = 0;
-        double cost = 0.0;
-        for (int l = lgB; l >= 0; --l) {
-            n[l] = l > 0 && (o & (l == lgB ? 1 : 2)) ? left / slots * slots : left;
-            if (n[l] > m) m = n[l];
-            left = (left - n[l]) * 2;
-            const int64_t rem = n[l] % slots;
-            const bool one = rem > 0 && rem <= num_cu;
-            cost += (double)(n[l] / slots + (rem > num_cu)) * (t.nch * (kPair[l][0] + kPair[l][1] * t.geo[l].nB) + kPair[l][2]);
-            if (one) cost += t.nch * (kOne[l][0] + kOne[l][1] * t.geo[l].nB) + kOne[l][2];
-        }
-        if (cost < best) {
-            best = cost;
-            most = m;
-            t.end[2] = (int)n[2];
-            t.end[1] = (int)(2 * n[2] + n[1]);
-            t.end[0] = (int)(2 * t.end[1] + n[0]);
-        }
+    for (int o = 0; o < 5; ++o) {      // 0: whole tiles; 1, 2: a whole tile per CU and the rest in halves, quarters; 3, 4: all of it
+        const int lgP = o == 0 ? 0 : o & 1 ? 1 : 2;
+        if (o && (cand.nbuf > 1 || (cand.bt != 8 && !(cand.bt == 4 && lgP == 1)))) continue;
+        if ((o == 1 || o == 2) && left <= num_cu) continue;
+        const int last = o == 0 ? left : o < 3 ? num_cu : 0, pieces = o == 0 ? 0 : (left - last) << lgP;
+        const Times &pair = cand.nbuf > 1 ? kSolo : kPair[first], &ppair = kPair[cand.bt == 8 && lgP == 1 ? 2 : 3], &pone = kOne[cand.bt == 8 && lgP == 1 ? 2 : 3];
+        double c = (t.rounds + (last > (cand.nbuf > 1 ? 0 : num_cu))) * tile_us(pair, 0);
+        if (cand.nbuf == 1 && last > 0 && last <= num_cu) c += tile_us(kOne[first], 0);
+        if (pieces && last) c += 0.83 * tile_us(ppair, lgP);
+        else if (pieces) c += (pieces / slots + (pieces % slots > num_cu)) * tile_us(ppair, lgP) + (pieces % slots > 0 && pieces % slots <= num_cu ? tile_us(pone, lgP) : 0.0);
+        if (c < best) { best = c; t.last = last; t.pieces = pieces; t.lgP = lgP; }
     }
-    const double move = 2.0 * ((double)p_tiles * t.nrow * (TC + 2) * (g.in_CH < DM_KC ? DM_KC : g.in_CH) + (double)rows * g.in_W * g.out_CH) / 4.5e6;
-    *est = 4.08 + pow(pow(best, 2.22) + pow(move, 2.22), 1.0 / 2.22);
-    *grid = (int)(most < slots ? most : slots);
+    const double move = 2.0 * ((double)p_tiles * t.nrow * (TC + 2) * (g.in_CH < DM_KC ? DM_KC : g.in_CH) + (double)rows * g.in_W * g.out_CH) / 6.0e6;
+    *est = 3.3 + pow(pow(best, 1.5) + pow(move, 1.5), 1.0 / 1.5);
+    const int busy = t.last + t.pieces;
+    *grid = t.rounds > 0 || busy > slots ? slots : busy;
     *out = t;
     return true;
 }
 
-template <int LG, int ACT>
+template <int BT, int NBUF, int ACT>
 static hipError_t launch_dma_act(int device, hipStream_t st, int grid, size_t lds, const uint16_t *in, uint16_t *out, const uint16_t *wz, const DmaArgs &g)
 {
     static pc_per_device_once attr;
     if (pc_once_pending(attr, device)) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&pc_mfma_conv_dma_kernel<LG, ACT>),
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&pc_mfma_conv_dma_kernel<BT, NBUF, ACT>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, DM_LDS_MAX);
         if (e != hipSuccess) return e;
         pc_once_done(attr, device);
     }
-    hipLaunchKernelGGL((pc_mfma_conv_dma_kernel<LG, ACT>), dim3((unsigned)grid), dim3(256), lds, st, in, out, wz, g);
+    hipLaunchKernelGGL((pc_mfma_conv_dma_kernel<BT, NBUF, ACT>), dim3((unsigned)grid), dim3(256), lds, st, in, out, wz, g);
     return hipGetLastError();
 }
 
-template <int LG>
+template <int BT, int NBUF>
 static hipError_t launch_dma(int device, hipStream_t st, int grid, size_t lds, const uint16_t *in, uint16_t *out, const uint16_t *wz, const DmaArgs &g, int act)
 {
-    if (act == PC_ACT_RELU) return launch_dma_act<LG, PC_ACT_RELU>(device, st, grid, lds, in, out, wz, g);
-    if (act == PC_ACT_RELU_MASK) return launch_dma_act<LG, PC_ACT_RELU_MASK>(device, st, grid, lds, in, out, wz, g);
-    return launch_dma_act<LG, PC_ACT_NONE>(device, st, grid, lds, in, out, wz, g);
+    if (act == PC_ACT_RELU) return launch_dma_act<BT, NBUF, PC_ACT_RELU>(device, st, grid, lds, in, out, wz, g);
+    if (act == PC_ACT_RELU_MASK) return launch_dma_act<BT, NBUF, PC_ACT_RELU_MASK>(device, st, grid, lds, in, out, wz, g);
+    return launch_dma_act<BT, NBUF, PC_ACT_NONE>(device, st, grid, lds, in, out, wz, g);
 }
 
-// pcfg: -1 or 40 / 41 (2 / 4 columns per wavefront). *launched stays false where the kernel does not take the launch or its
-// estimate is not below limit (us).
+// pcfg: -1 or a code of kDma. *launched stays false where no kernel takes the launch or no estimate is below limit (us).
 pc_status pc_run_mfma_conv_dma(pc_ctx *ctx, int pcfg, double limit, const MfmaArgs &g0, bool flip, const uint16_t *in, uint16_t *out, const uint16_t *wz,
                                bool *launched, int act)
 {
@@ -384,23 +473,31 @@ pc_status pc_run_mfma_conv_dma(pc_ctx *ctx, int pcfg, double limit, const MfmaAr
     if (g0.lstep != 1 || g0.oscale != 1 || (g0.in_CH & 7) || (g0.out_CH & 7)) return PC_OK;
     DmaArgs best;
     size_t best_lds = 0;
-    int best_grid = 0, best_b = -1;
+    int best_grid = 0, best_k = -1;
     double best_est = limit;
-    for (int b = 1; b <= 2; ++b) {
-        if (pcfg >= 0 && pcfg != 39 + b) continue;
+    for (int k = 0; k < kNumDma; ++k) {
+        if (pcfg >= 0 && pcfg != kDma[k].code) continue;
         for (int lg = 0; lg <= 2; ++lg) {
             DmaArgs t;
             size_t lds;
             int grid;
             double est;
-            if (!plan_dma(g0, flip, b, lg, &t, &lds, &grid, &est, ctx->num_cu)) continue;
-            if (est < best_est) { best = t; best_lds = lds; best_grid = grid; best_b = b; best_est = est; }
+            if (!plan_dma(g0, flip, kDma[k], lg, &t, &lds, &grid, &est, ctx->num_cu)) continue;
+            if (est < best_est) { best = t; best_lds = lds; best_grid = grid; best_k = k; best_est = est; }
         }
     }
-    if (best_b < 0) return PC_OK;
-    const hipError_t e = best_b == 2 ? launch_dma<2>(ctx->device, ctx->stream, best_grid, best_lds, in, out, wz, best, act)
-                                     : launch_dma<1>(ctx->device, ctx->stream, best_grid, best_lds, in, out, wz, best, act);
+    if (best_k < 0) return PC_OK;
+    const DmaCand &c = kDma[best_k];
+    hipError_t e;
+    switch (c.code) {
+#define DM_CASE(CODE, BT, NBUF) case CODE: e = launch_dma<BT, NBUF>(ctx->device, ctx->stream, best_grid, best_lds, in, out, wz, best, act); break;
+    DM_CASE(40, 8, 1)
+    DM_CASE(41, 4, 1)
+    DM_CASE(42, 7, 1)
+    default: e = launch_dma<2, 3>(ctx->device, ctx->stream, best_grid, best_lds, in, out, wz, best, act); break;
+#undef DM_CASE
+    }
     *launched = true;
-    pc_note_kernel(ctx, "pc_mfma_conv_dma_kernel<%d, %d>", best_b, act);
+    pc_note_kernel(ctx, "pc_mfma_conv_dma_kernel<%d, %d, %d>", c.bt, c.nbuf, act);
     return pc_hip_check(ctx, e, "MFMA conv (direct loads) launch");
 }

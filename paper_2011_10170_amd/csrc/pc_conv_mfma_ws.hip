@@ -1198,8 +1198,7 @@ pc_status pc_run_mfma_conv_ws(pc_ctx *ctx, int pcfg, const MfmaArgs &g0, int ext
     for (int t = 0; t < 9; ++t)
         if (g0.tap_w[t] != t || tr[t] != (tr[0] ? 2 - t / 3 : t / 3) || tc[t] != (tc[0] ? 2 - t % 3 : t % 3)) return PC_OK;
     if (pcfg < 0) {
-        // (5 % less: inside a training step, tensors not in any cache, its loads take longer than where it was measured)
-        const pc_status s = pc_run_mfma_conv_dma(ctx, -1, best_k < 0 ? 1e30 : 0.95 * best_est, g0, tr[0] != 0, in, out, wz, launched, act);
+        const pc_status s = pc_run_mfma_conv_dma(ctx, -1, best_k < 0 ? 1e30 : best_est, g0, tr[0] != 0, in, out, wz, launched, act);
         if (s != PC_OK || *launched) return s;
     }
     if (best_k < 0) return PC_OK;

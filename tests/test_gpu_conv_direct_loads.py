@@ -1,4 +1,4 @@
-"""The stride-1 forward / backward-data kernel that loads both operands straight to LDS (override codes 40 and 41), element by
+"""The stride-1 forward / backward-data kernel that loads both operands straight to LDS (override codes 40 to 43), element by
 element against the oracle, at the edges of its tiles: rows that run across images (one zero row between two of them), columns past
 the map, a last chunk of 8, 16 or 24 channels, partial row tiles, and lists of tiles that continue in narrower ones."""
 import pytest
@@ -39,7 +39,7 @@ SHAPES = [
 ]
 
 
-@pytest.mark.parametrize("cfg", [40, 41])
+@pytest.mark.parametrize("cfg", [40, 41, 42, 43])
 @pytest.mark.parametrize("shape", SHAPES)
 def test_every_element(B, ctx, oracle, cfg, shape):
     B.pc_set_plan_override(ctx, cfg, 0)
@@ -49,25 +49,29 @@ def test_every_element(B, ctx, oracle, cfg, shape):
         B.pc_set_plan_override(ctx, -1, 0)
 
 
-def test_many_small_images(B, ctx, oracle):
-    """A zero row between every four: only the narrower tile has the LDS for it."""
-    B.pc_set_plan_override(ctx, 40, 0)
+@pytest.mark.parametrize("cfg", [41, 42, 43])
+def test_many_small_images(B, ctx, oracle, cfg):
+    """A zero row between every four: the widest tile has not the LDS for it."""
+    B.pc_set_plan_override(ctx, cfg, 0)
     try:
-        run_case(B, ctx, oracle, (70, 4, 4, 72, 64, 1), "bf16", 8, 0.3, B.PC_VARIANT_MFMA, ("direct", 40))
+        run_case(B, ctx, oracle, (70, 4, 4, 72, 64, 1), "bf16", 8, 0.3, B.PC_VARIANT_MFMA, ("direct", cfg))
     finally:
         B.pc_set_plan_override(ctx, -1, 0)
 
 
-def test_taken_by_the_automatic_choice(B, ctx, oracle):
-    """A layer of the size it is for: sampled by the plain kernels of the other family, which add in another order."""
+@pytest.mark.parametrize("cfg", [-1, 40, 41, 42])
+@pytest.mark.parametrize("dims", [(16, 56, 56, 64, 128), (32, 56, 56, 40, 256), (24, 57, 50, 32, 192)])
+def test_more_tiles_than_workgroups(B, ctx, cfg, dims):
+    """Layers of the size it is for, whose tiles fill one to three rounds and leave some: against a kernel of the other family,
+    which adds in another order."""
     import torch
     from tests._harness import Case, GpuLayer
-    layer = I.Layer(16, 56, 56, 64, 128, 1)
+    layer = I.Layer(*dims, 1)
     g = GpuLayer(B, ctx, Case(layer, "bf16", 8, I.kept_per_filter(0.3, layer.C), tag=("direct", "auto")))
     try:
         out = []
-        for cfg in (-1, 20):
-            B.pc_set_plan_override(ctx, cfg, 0)
+        for code in (cfg, 20):
+            B.pc_set_plan_override(ctx, code, 0)
             y = torch.full((layer.N, layer.Ho, layer.Wo, layer.F), float("nan"), dtype=torch.bfloat16, device="cuda")
             B.pc_conv_fwd(ctx, g.desc, g.pk, g.x, y)
             out.append((B.pc_last_kernel(ctx), y.double()))
@@ -80,7 +84,7 @@ def test_taken_by_the_automatic_choice(B, ctx, oracle):
         g.close()
 
 
-@pytest.mark.parametrize("cfg", [40, 41])
+@pytest.mark.parametrize("cfg", [40, 41, 42, 43])
 @pytest.mark.parametrize("dims", [(6, 10, 9, 128, 160), (2, 33, 70, 24, 72), (9, 96, 95, 16, 200)])
 def test_fused_relu(B, ctx, cfg, dims):
     """Bit-identical to the plain launch followed by the step."""
