@@ -129,7 +129,8 @@ pc_status pc_set_variant(pc_ctx *ctx, pc_variant v);
  *          pass, tiles of 32 channels x 4 x 256 pixels with 64-, 32-, 16-channel chunks, x 4 x 128 with 64 and 32
  *   40..43 stride 1: the kernel that loads both operands straight to LDS, tiles of 64 output channels x 64 x 8, 4, 7 and 2
  *          pixels; the last with three buffers
- *   10, 11 backward-weight: the cooperative / the wave-specialised kernel (the other passes stay automatic)
+ *   10, 11, 44 backward-weight: the cooperative / the wave-specialised kernel / the kernel with direct loads (the other passes stay
+ *          automatic)
  *   22     forward/backward-data: the structured-sparse kernel (packs made under PC_VARIANT_MFMA_SPARSE only)
  *   23     the first-layer kernels (stride 1, at most 4 input channels): the automatic choice takes them wherever
  *          they apply; any other code here keeps such a layer on the general kernels
@@ -277,7 +278,7 @@ pc_status pc_conv_bwd_weight(pc_ctx *ctx, const pc_conv_desc *desc, const pc_pac
  * pc_conv_bwd_weight with the same pack state; but the partial sums (and the channel-padded copy of a first layer's
  * x) live in a fixed buffer of 32 MiB that the library's code object holds on every GPU it is loaded on until the
  * process ends, and the call makes no hipMalloc / hipFree and grows no context buffer. A layer that needs more
- * (the partial sums take at most 16 MiB; a first layer with C not a multiple of 8 adds N*H*W*16 bytes) is rejected
+ * (the partial sums take at most 32 MiB; a first layer with C not a multiple of 8 adds N*H*W*16 bytes) is rejected
  * with PC_ERR_UNSUPPORTED before anything is launched. All contexts of a GPU share that one buffer and it keeps the
  * last call's contents (nothing in it needs to start at zero): calls that overlap on one GPU, from different
  * contexts or streams, race; the caller serialises them. */

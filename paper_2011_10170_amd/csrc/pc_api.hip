@@ -173,7 +173,7 @@ extern "C" pc_status pc_set_variant(pc_ctx *ctx, pc_variant v)
 extern "C" pc_status pc_set_plan_override(pc_ctx *ctx, int32_t tile_cfg, int32_t split_k)
 {
     if (!ctx) return PC_ERR_INVALID_ARG;
-    if (tile_cfg < -1 || tile_cfg > 43 || (tile_cfg > 36 && tile_cfg < 40) || tile_cfg == 12 || split_k < 0 || split_k > 64)
+    if (tile_cfg < -1 || tile_cfg > 44 || (tile_cfg > 36 && tile_cfg < 40) || tile_cfg == 12 || split_k < 0 || split_k > 64)
         return pc_fail(ctx, PC_ERR_INVALID_ARG, "pc_set_plan_override: tile_cfg %d split_k %d out of range", tile_cfg, split_k);
     ctx->plan_cfg = tile_cfg;
     ctx->plan_split = split_k;
@@ -211,6 +211,17 @@ pc_status pc_scratch(pc_ctx *ctx, size_t bytes, void **out)
     }
     *out = ctx->scratch;
     return PC_OK;
+}
+
+bool pc_scratch_ready(pc_ctx *ctx, size_t bytes)
+{
+    if (ctx->fixed_scratch) return bytes <= PC_FIXED_SCRATCH_BYTES;
+    if (bytes <= ctx->scratch_bytes) return true;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    void *scr;
+    if (hipStreamIsCapturing(ctx->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone && pc_scratch(ctx, bytes, &scr) == PC_OK) return true;
+    (void)hipGetLastError();
+    return false;
 }
 
 // ------------------------------------------------------------------ select

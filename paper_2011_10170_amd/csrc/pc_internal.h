@@ -145,6 +145,9 @@ inline void pc_once_done(pc_per_device_once &o, int device) { if (device >= 0 &&
 pc_status pc_fail(pc_ctx *ctx, pc_status s, const char *fmt, ...);
 pc_status pc_hip_check(pc_ctx *ctx, hipError_t e, const char *what);
 pc_status pc_scratch(pc_ctx *ctx, size_t bytes, void **out);
+// pc_scratch will hand out `bytes`: it holds them, or has been grown to (not during a stream capture, where it cannot be). For kernels
+// that another one, with less scratch or none, can stand in for.
+bool pc_scratch_ready(pc_ctx *ctx, size_t bytes);
 // Records the symbol of the kernel a conv call launched (printf-style), for pc_last_kernel.
 void pc_note_kernel(pc_ctx *ctx, const char *fmt, ...);
 void pc_fill_lib(LibArg *la, const uint16_t *lib, int P);

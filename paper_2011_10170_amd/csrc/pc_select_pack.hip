@@ -612,12 +612,7 @@ static bool pc_rows_through_memory(pc_ctx *ctx, const SelBatchArg &b)
 {
     if (b.n != 1 || b.row0[1] > ctx->num_cu || b.C[0] <= PC_ROW_SPLIT) return false;
     const size_t bytes = sizeof(float) * (size_t)b.row0[1] * (size_t)b.C[0] + 256;
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    void *scr;
-    if (bytes <= ctx->scratch_bytes) return true;
-    if (hipStreamIsCapturing(ctx->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone && pc_scratch(ctx, bytes, &scr) == PC_OK) return true;
-    (void)hipGetLastError();
-    return false;
+    return pc_scratch_ready(ctx, bytes);
 }
 
 // Layers ranked by rows go into launches of up to PC_BATCH_MAX layers, rows of at most PC_ROW_MAX kernels and longer ones apart;

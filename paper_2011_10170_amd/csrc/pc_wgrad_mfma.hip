@@ -1,7 +1,8 @@
 // Backward-weight on the matrix cores (bf16 layers): dW at the kept taps only, in compact slot order
 // (Section 5.3: only the kept positions are needed).
-#include "pc_mfma.h"
+#include "pc_wgrad_dma.h"
 
+#include <math.h>
 #include <algorithm>
 #include <vector>
 
@@ -858,6 +859,43 @@ static pc_status pc_mfma_bwd_weight_ws(pc_ctx *ctx, const pc_conv_desc *d, const
     return pc_launch_wgrad_reduce(ctx, (const float *)scr, ks, nslots, nslots, pk, dw);
 }
 
+// The kernel with direct loads for one layer. *launched stays false when the layer is outside what it takes.
+static pc_status pc_mfma_bwd_weight_dma(pc_ctx *ctx, const pc_conv_desc *d, const pc_packed *pk, const void *x, const void *dy,
+                                        float *dw, int64_t nslots, bool *launched)
+{
+    *launched = false;
+    WgradDmaGroup g;
+    memset(&g, 0, sizeof(g));
+    WgradDmaLayer &y = g.layer[0];
+    size_t lds;
+    double tile_us;
+    if (!pc_wgrad_dma_plan(ctx, d, nslots, &y.a, &y.gx, &y.gy, &lds, &tile_us)) return PC_OK;
+    // (from about 12 us of work for every place on, two per CU, it is faster than the wave-specialised kernel, below it is not: 60 shapes.
+    // 28 x 28, 512 -> 512, batch 32 99 -> 83 us, 112 x 112, 128 -> 128 105 -> 87, 56 x 56, 128 -> 128, stride 2, batch 64 33 -> 30;
+    // 28 x 28, 128 -> 128, batch 64 24 : 26)
+    if (ctx->plan_cfg != 44 && tile_us * y.gx * y.gy * y.a.n_ktiles < 12.0 * 2 * ctx->num_cu) return PC_OK;
+    int ks = 2 * ctx->num_cu / (y.gx * y.gy);
+    if (ks > y.a.n_ktiles) ks = y.a.n_ktiles;
+    if (ks < 1) ks = 1;
+    y.a.ksplit = ks;
+    if (ks > 1) {
+        // (twice the other kernel's partial planes: up to 32 MiB)
+        void *scr = nullptr;
+        const size_t bytes = sizeof(float) * 4 * (size_t)ks * (size_t)nslots;
+        if (ctx->plan_cfg != 44 && !pc_scratch_ready(ctx, bytes)) return PC_OK;
+        const pc_status s = pc_scratch(ctx, bytes, &scr);
+        if (s != PC_OK) return s;
+        y.partial = (float *)scr;
+    }
+    y.x = (const uint16_t *)x; y.dy = (const uint16_t *)dy; y.kinfo = pk->v.kinfo; y.dw = dw;
+    g.n = 1;
+    g.blk0[1] = y.gx * y.gy * ks;
+    pc_status s = pc_wgrad_dma_launch(ctx, g, lds);
+    *launched = true;
+    if (s != PC_OK || ks == 1) return s;
+    return pc_launch_wgrad_reduce(ctx, y.partial, ks, nslots, nslots, pk, dw);
+}
+
 pc_status pc_mfma_bwd_weight(pc_ctx *ctx, const pc_conv_desc *d, const pc_packed *pk, const void *x, const void *dy,
                              float *dw)
 {
@@ -869,6 +907,13 @@ pc_status pc_mfma_bwd_weight(pc_ctx *ctx, const pc_conv_desc *d, const pc_packed
     const int64_t nslots = pk->nnzk >= 0 ? pk->nnzk : (int64_t)pk->v.F * pk->v.C;
     if (nslots == 0) return PC_OK;
     pc_status s = PC_OK;
+    if (ctx->plan_cfg < 0 || ctx->plan_cfg == 44) {
+        bool launched = false;
+        s = pc_mfma_bwd_weight_dma(ctx, d, pk, x, dy, dw, nslots, &launched);
+        if (launched || s != PC_OK) return s;
+        if (ctx->plan_cfg == 44)
+            return pc_fail(ctx, PC_ERR_UNSUPPORTED, "MFMA bwd_weight: the kernel with direct loads does not take this layer");
+    }
     if (ctx->plan_cfg != 10) {   // 10 forces the cooperative kernel
         bool launched = false;
         s = pc_mfma_bwd_weight_ws(ctx, d, pk, x, dy, dw, nslots, &launched);
@@ -957,53 +1002,126 @@ pc_status pc_mfma_bwd_weight(pc_ctx *ctx, const pc_conv_desc *d, const pc_packed
     return pc_launch_wgrad_reduce(ctx, (const float *)scr, ks, nslots, nslots, pk, dw);
 }
 
-// Backward-weight of several layers: the layers the wave-specialised kernel takes run in one launch per
-// WS_GROUP_MAX layers, followed by one grouped reduction; each layer has the tiles of its own call and at most
-// its splits (fixed order of additions: deterministic, but not the bits of the single call when the split differs).
+// One layer of a grouped call: its plan for the wave-specialised kernel (a) or the one with direct loads (q).
+struct GroupItem {
+    int l;
+    bool dma, pad_x;
+    WgradWsArgs a;
+    WgradDmaArgs q;
+    int ct, ft, n_ktiles, ksplit;    // ksplit: at most, until the shares are known
+    double tile_us;
+    size_t lds, part_off, pad_off;
+    int64_t xb, nslots;
+};
+
+// Split counts the XCD-aware re-reading of the workgroup index can use: a multiple of 8, or a divisor of 8
+// (resnet50_imagenet: 317 us against 339 us with arbitrary counts; within 1 % elsewhere).
+static int group_splits(double want, int most)
+{
+    int64_t ks = (int64_t)ceil(want);
+    if (ks < 1) ks = 1;
+    if (ks >= 8) ks = (ks + 7) / 8 * 8;
+    else if (ks > 4) ks = 8;
+    else if (ks == 3) ks = 4;
+    return (int)(ks < most ? ks : most);
+}
+
+// Backward-weight of several layers: one launch per WS_GROUP_MAX layers of the wave-specialised kernel, one per WD_GROUP_MAX of the kernel with
+// direct loads, followed by one grouped reduction; each layer has the tiles of its own call and splits of the group's own
+// (fixed order of additions: deterministic, but not the bits of the single call when the split differs).
 // The other layers go through pc_mfma_bwd_weight first.
 // Every layer has its own region of the context's scratch buffer (partial planes, padded copy of x).
 pc_status pc_mfma_bwd_weight_group(pc_ctx *ctx, int n, const pc_conv_desc *d, const pc_packed *const *pk, const void *const *x,
                                    const void *const *dy, float *const *dw)
 {
-    struct Item { int l; WgradWsArgs a; int ct, ft; size_t lds, part_off, pad_off; bool pad_x; int64_t xb, nslots; };
-    std::vector<Item> items;
+    std::vector<GroupItem> items;
     std::vector<int> single;
     size_t total = 0;
-    for (int l = 0; l < n; ++l) {
-        const int64_t nslots = pk[l]->nnzk >= 0 ? pk[l]->nnzk : (int64_t)pk[l]->v.F * pk[l]->v.C;
-        if (nslots == 0) continue;
-        Item it;
-        it.l = l;
-        it.nslots = nslots;
-        if (ctx->plan_cfg == 10 || !ws_plan(ctx, &d[l], nslots, &it.a, &it.ct, &it.ft, &it.lds, &it.pad_x, &it.xb)) {
-            single.push_back(l);
-            continue;
+    auto plan = [&](bool dma) {
+        items.clear();
+        single.clear();
+        for (int l = 0; l < n; ++l) {
+            const int64_t nslots = pk[l]->nnzk >= 0 ? pk[l]->nnzk : (int64_t)pk[l]->v.F * pk[l]->v.C;
+            if (nslots == 0) continue;
+            GroupItem it;
+            it.l = l;
+            it.nslots = nslots;
+            it.pad_x = false;
+            it.dma = dma && pc_wgrad_dma_plan(ctx, &d[l], nslots, &it.q, &it.ct, &it.ft, &it.lds, &it.tile_us);
+            if (it.dma) {
+                it.n_ktiles = it.q.n_ktiles;
+                it.ksplit = std::max(1, std::min(2 * ctx->num_cu / (it.ct * it.ft), it.n_ktiles));
+            } else if (ctx->plan_cfg != 10 && ws_plan(ctx, &d[l], nslots, &it.a, &it.ct, &it.ft, &it.lds, &it.pad_x, &it.xb)) {
+                it.n_ktiles = it.a.n_ktiles;
+                it.ksplit = it.a.ksplit;
+            } else {
+                single.push_back(l);
+                continue;
+            }
+            items.push_back(it);
         }
-        items.push_back(it);
+    };
+    // The wave-specialised kernel for every layer, or the kernel with direct loads for all it takes, whichever is estimated to be faster
+    // (us; fitted to the four networks below). Launches of their own for few layers, and short workgroups, cost the second more:
+    // VGG-16 / CIFAR 94 : 116, ResNet-18 / CIFAR 144 : 149, ResNet-50 / ImageNet 287 : 232, VGG-16 / ImageNet 901 : 748. The choice is
+    // remembered for the shapes it was made for.
+    auto ws_us = [&]() {
+        double us = 0.0;
+        for (const GroupItem &it : items)
+            if (!it.dma) us += 2.05 * it.ct * it.ft * it.n_ktiles / ctx->num_cu;
+        return us > 0.0 ? us + 12.0 : 0.0;
+    };
+    auto even = [&]() {          // the direct-load layers' share of every place, two per CU
+        double us = 0.0;
+        for (const GroupItem &it : items)
+            if (it.dma) us += it.ct * it.ft * (double)it.n_ktiles * it.tile_us;
+        return us / (2.0 * ctx->num_cu);
+    };
+    bool dma = ctx->plan_cfg == 44;
+    if (ctx->plan_cfg < 0) {
+        uint64_t h = 1469598103934665603ull;
+        for (int l = 0; l < n; ++l)
+            for (int v : {(int)d[l].N, (int)d[l].H, (int)d[l].W, (int)d[l].C, (int)d[l].F, (int)d[l].stride}) h = (h ^ (uint32_t)v) * 1099511628211ull;
+        const int32_t key[PC_CHOICE_KEY] = {4, n, (int32_t)h, (int32_t)(h >> 32), d[0].N, d[0].H, d[n - 1].H, d[n - 1].F, 0, 0};
+        bool hit;
+        int32_t *choice = pc_choice(ctx, key, &hit);
+        if (!hit) {
+            plan(false);
+            const double all = ws_us();
+            plan(true);
+            *choice = even() > 0.0 && 40.0 + 1.15 * even() + ws_us() < all;
+        }
+        dma = *choice != 0;
     }
+    plan(dma);
     // A layer's own call splits its pixel tiles until the layer alone fills the chip; here the layers fill it
     // together, so every workgroup gets about the same share of all (tile, pixel tile) units: fewer splits, longer
-    // main loops per prologue and epilogue, fewer partial planes.
-    int64_t units = 0;
-    for (const Item &it : items) units += (int64_t)it.ct * it.ft * it.a.n_ktiles;
-    int64_t rounds = units / ((int64_t)PC_GROUP_UNITS * ctx->num_cu);
-    if (rounds < 1) rounds = 1;
-    if (rounds > 4) rounds = 4;
-    int64_t share = units / (rounds * (int64_t)ctx->num_cu);
-    if (share < 1) share = 1;
-    for (Item &it : items) {
-        int64_t ks = (it.a.n_ktiles + share - 1) / share;
-        if (ks < 1) ks = 1;
-        // split counts the XCD-aware re-reading of the workgroup index can use: a multiple of 8, or a divisor of 8
-        // (resnet50_imagenet: 317 us against 339 us with arbitrary counts; within 1 % elsewhere)
-        if (ks >= 8) ks = (ks + 7) / 8 * 8;
-        else if (ks > 4) ks = 8;
-        else if (ks == 3) ks = 4;
-        if (ks < it.a.ksplit) it.a.ksplit = (int32_t)ks;
-        it.part_off = total;
-        if (it.a.ksplit > 1) total += (sizeof(float) * 4 * (size_t)it.a.ksplit * (size_t)it.nslots + 255) / 256 * 256;
-        it.pad_off = total;
-        if (it.pad_x) total += ((size_t)it.xb + 255) / 256 * 256;
+    // main loops per prologue and epilogue, fewer partial planes. (The two kernels run one after the other, each with its own shares.)
+    auto shares = [&]() {
+        total = 0;
+        int64_t units = 0;
+        for (const GroupItem &it : items)
+            if (!it.dma) units += (int64_t)it.ct * it.ft * it.n_ktiles;
+        int64_t rounds = units / ((int64_t)PC_GROUP_UNITS * ctx->num_cu);
+        rounds = rounds < 1 ? 1 : rounds > 4 ? 4 : rounds;
+        int64_t share = units / (rounds * (int64_t)ctx->num_cu);
+        if (share < 1) share = 1;
+        // (2.5 workgroups of the direct-load kernel to a place: 1 to 4 measured, within 3 % of the best on each of the four)
+        const double level = dma ? even() / 2.5 : 1.0;
+        for (GroupItem &it : items) {
+            it.ksplit = group_splits(it.dma ? it.n_ktiles * it.tile_us / level : (double)((it.n_ktiles + share - 1) / share), it.ksplit);
+            it.part_off = total;
+            if (it.ksplit > 1) total += (sizeof(float) * 4 * (size_t)it.ksplit * (size_t)it.nslots + 255) / 256 * 256;
+            it.pad_off = total;
+            if (it.pad_x) total += ((size_t)it.xb + 255) / 256 * 256;
+            it.a.ksplit = it.q.ksplit = it.ksplit;
+        }
+    };
+    shares();
+    if (dma && ctx->plan_cfg < 0 && !pc_scratch_ready(ctx, total)) {      // the other kernel needs fewer partial planes
+        dma = false;
+        plan(false);
+        shares();
     }
     void *scr = nullptr;
     pc_status s = PC_OK;
@@ -1026,46 +1144,49 @@ pc_status pc_mfma_bwd_weight_group(pc_ctx *ctx, int n, const pc_conv_desc *d, co
     std::vector<WgradReduceItem> red;
     std::vector<int64_t> red_nslots;
     std::vector<const pc_packed *> red_pk;
-    // whole-image layers and layers in strips run different kernels (the layers of a network share the batch: mostly one)
-    std::stable_partition(items.begin(), items.end(), [](const Item &it) { return it.a.lgS == 0; });
+    // layers of the kernel with direct loads, whole-image layers and layers in strips run different kernels
+    auto kind = [&](const GroupItem &it) { return it.dma ? 2 : it.a.lgS > 0 ? 1 : 0; };
+    auto work = [](const GroupItem &it) { return it.dma ? (it.n_ktiles + it.ksplit - 1) / it.ksplit * it.tile_us : 0.0; };     // the longest workgroups first
+    std::stable_sort(items.begin(), items.end(), [&](const GroupItem &p, const GroupItem &q) { return kind(p) != kind(q) ? kind(p) < kind(q) : work(p) > work(q); });
     for (size_t i0 = 0, m = 0; i0 < items.size(); i0 += m) {
-        const bool strips = items[i0].a.lgS > 0;
-        for (m = 1; m < WS_GROUP_MAX && i0 + m < items.size() && (items[i0 + m].a.lgS > 0) == strips;) ++m;
+        const int kd = kind(items[i0]);
+        for (m = 1; m < WS_GROUP_MAX && i0 + m < items.size() && kind(items[i0 + m]) == kd;) ++m;
         WgradWsGroup g;
-        memset(&g, 0, sizeof(g));
-        g.n = (int)m;
+        WgradDmaGroup gd;
+        g.n = gd.n = (int)m;
+        g.blk0[0] = gd.blk0[0] = 0;
         size_t lds = 0;
         for (size_t i = 0; i < m; ++i) {
-            const Item &it = items[i0 + i];
-            WgradWsLayer &y = g.layer[i];
-            y.a = it.a;
-            y.x = (const uint16_t *)x[it.l];
+            const GroupItem &it = items[i0 + i];
+            const uint16_t *xp = (const uint16_t *)x[it.l], *dyp = (const uint16_t *)dy[it.l];
             if (it.pad_x) {
-                void *xp = base + it.pad_off;
-                pc_launch_pad_channels(ctx, (const uint16_t *)x[it.l], xp, (int64_t)it.a.N * it.a.H * it.a.W, it.a.Creal, it.a.C);
-                y.x = (const uint16_t *)xp;
+                void *cp = base + it.pad_off;
+                pc_launch_pad_channels(ctx, xp, cp, (int64_t)it.a.N * it.a.H * it.a.W, it.a.Creal, it.a.C);
+                xp = (const uint16_t *)cp;
             }
-            y.dy = (const uint16_t *)dy[it.l];
-            y.kinfo = pk[it.l]->v.kinfo;
-            y.partial = it.a.ksplit > 1 ? reinterpret_cast<float *>(base + it.part_off) : nullptr;
-            y.dw = dw[it.l];
-            y.gx = it.ct; y.gy = it.ft;
-            const int nwg = it.ct * it.ft * it.a.ksplit;
-            g.blk0[i + 1] = g.blk0[i] + (nwg + 7) / 8 * 8;
+            float *partial = it.ksplit > 1 ? reinterpret_cast<float *>(base + it.part_off) : nullptr;
+            const int nwg = it.ct * it.ft * it.ksplit;
+            if (it.dma) gd.layer[i] = {it.q, xp, dyp, pk[it.l]->v.kinfo, partial, dw[it.l], it.ct, it.ft};
+            else g.layer[i] = {it.a, xp, dyp, pk[it.l]->v.kinfo, partial, dw[it.l], it.ct, it.ft};
+            g.blk0[i + 1] = gd.blk0[i + 1] = g.blk0[i] + (nwg + 7) / 8 * 8;
             if (it.lds > lds) lds = it.lds;
-            if (it.a.ksplit > 1) {
+            if (it.ksplit > 1) {
                 WgradReduceItem r;
                 memset(&r, 0, sizeof(r));
-                r.partial = y.partial; r.dw = y.dw; r.pstride = it.nslots; r.G = it.a.ksplit;
+                r.partial = partial; r.dw = dw[it.l]; r.pstride = it.nslots; r.G = it.ksplit;
                 red.push_back(r);
                 red_nslots.push_back(it.nslots);
                 red_pk.push_back(pk[it.l]);
             }
         }
-        if (strips) hipLaunchKernelGGL(pc_mfma_wgrad_ws_group_kernel<true>, dim3((unsigned)g.blk0[m]), dim3(512), lds, ctx->stream, g);
-        else hipLaunchKernelGGL(pc_mfma_wgrad_ws_group_kernel<false>, dim3((unsigned)g.blk0[m]), dim3(512), lds, ctx->stream, g);
-        pc_note_kernel(ctx, "pc_mfma_wgrad_ws_group_kernel");
-        s = pc_hip_check(ctx, hipGetLastError(), "MFMA bwd_weight (several layers) launch");
+        if (kd == 2) {
+            s = pc_wgrad_dma_launch(ctx, gd, lds);
+        } else {
+            if (kd == 1) hipLaunchKernelGGL(pc_mfma_wgrad_ws_group_kernel<true>, dim3((unsigned)g.blk0[m]), dim3(512), lds, ctx->stream, g);
+            else hipLaunchKernelGGL(pc_mfma_wgrad_ws_group_kernel<false>, dim3((unsigned)g.blk0[m]), dim3(512), lds, ctx->stream, g);
+            pc_note_kernel(ctx, "pc_mfma_wgrad_ws_group_kernel");
+            s = pc_hip_check(ctx, hipGetLastError(), "MFMA bwd_weight (several layers) launch");
+        }
         if (s != PC_OK) return s;
     }
     if (red.empty()) return PC_OK;
