@@ -8,10 +8,10 @@
 // LDS buffer, and all of the chunk's matrix instructions follow from there.
 //   Instruction: v_mfma_f32_16x16x32_bf16. The rate the chip holds depends on what the operands and sums toggle: fed from LDS with
 //     pruned weights and ReLU outputs 2.28 PFLOP/s against 2.0 with v_mfma_f32_32x32x16_bf16 (2.38 for both on zeros).
-//   Two ways of hiding the loads (NBUF). With one buffer two workgroups share a CU: one loads (or stores a finished tile) while the
-//     other multiplies; a wavefront's priority rises through a chunk, so that of two workgroups that multiply at the same time
-//     the one ahead finishes first and the two fall out of step by themselves. With two buffers a workgroup has the CU to itself
-//     and loads the next chunk while it multiplies: for launches of about one tile per CU.
+//   Two ways of hiding the loads. Large layers (pc_mfma_conv_dma_kernel): one buffer, and two workgroups share a CU: one loads (or
+//     stores a finished tile) while the other multiplies; a wavefront's priority rises through a chunk, so that of two workgroups
+//     that multiply at the same time the one ahead finishes first and the two fall out of step by themselves. Layers of a few tiles
+//     per CU (pc_mfma_conv_solo_kernel): a workgroup has the CU to itself, with two or three buffers and wavefronts that only load.
 //   Rows: the rows of all images, N * H of them, in order. The staged tile is rows of "padded images" of H + 1 rows (one zero
 //     row between two images), so a tile covers any 16, 32 or 64 rows without a gap, whatever the map's height.
 //   Columns: the 16 columns of a B operand are 16 rows of one column of the map, so the fragment of column j is the operand of tap
@@ -23,11 +23,13 @@
 #define DM_KC 32                     // input channels per chunk
 #define DM_NA 36                     // direct loads (1 KiB) of the weights per chunk: 9 taps x 4 fragments of 16 output channels
 #define DM_NB 11                     // of the input tile per wavefront at most
-#define DM_NBW 4                     // the same where every wavefront has as many
 #define DM_A_BYTES (DM_NA * 1024)
 #define DM_OOB 0x80000000u           // past the end of any tensor taken here, also with a chunk's offset added
 #define DM_LDS_MAX (160 * 1024)
 #define DM_STG 144                   // bytes per pixel (64 channels) where a finished tile passes through LDS
+
+// Direct loads of the input tile per wavefront where every wavefront has as many (three buffers)
+constexpr __host__ __device__ int dm_nbw(int bt) { return bt == 2 ? 3 : 4; }
 
 // Staged columns for a tile width
 struct DmaGeo {
@@ -121,21 +123,32 @@ __device__ __forceinline__ void dm_offsets(DmaWave &s, const DmaArgs &g, const D
     }
 }
 
-// The direct loads of chunk ch of a tile (its offsets are in s) into the buffer at lb, in 9 steps: step t brings this wavefront's
-// fragment of tap position t and its loads t and t + 9 of the input tile (nB of them in the workgroup; NBW > 0: NBW for every wavefront).
-//   Fragment (position t, a): row m of it is output channel 16 * (m / 4) + 4 * a + m % 4 of the tile, so that a lane's sums are 16
-//   consecutive channels. Wavefront w loads fragment w of every position.
-template <int NBW>
-__device__ __forceinline__ void dm_issue(const DmaWave &s, const DmaArgs &g, int nB, int mt, int ch, int lb, int t)
+// The direct loads of chunk ch of a tile (its offsets are in s) into the buffer at lb by wavefront s.w of four: fragment s.w of every tap
+// position and every fourth load of the input tile (nB of them; NBW > 0: NBW for every wavefront).
+//   AT = 4: a wavefront multiplies all 64 channels of the tile. Row m of fragment a is output channel 16 * (m / 4) + 4 * a + m % 4 of the
+//     tile, so that a lane's sums are 16 consecutive channels.
+//   AT = 2: half of them. Row m of fragment 2 * h + a is channel 32 * h + 8 * (m / 4) + 4 * a + m % 4: 8 consecutive channels.
+template <int AT>
+__device__ __forceinline__ int dm_weight_offset(const DmaArgs &g, int lane)     // of a lane in a fragment
+{
+    const int m = lane & 15, kg = lane >> 4, at = (kg >> 1) * 1024 + (kg & 1) * 512;
+    return AT == 4 ? at + (m >> 3) * (9 * 1024) * g.KS + (16 * ((m >> 2) & 1) + (m & 3)) * 16 : at + (8 * (m >> 2) + (m & 3)) * 16;
+}
+
+template <int AT, int NBW>
+__device__ __forceinline__ void dm_issue(const DmaWave &s, const DmaArgs &g, int nB, int mt, int ch, int lb)
 {
     // (the wavefront's number is hidden from the compiler here: it would compute all scalar offsets ahead and spill them)
     int w = s.w;
     asm volatile("" : "+s"(w));
-    dm_load(s.ws, s.a_voff, ((mt * 18 + (g.flip ? 8 - t : t)) * g.KS + ch * 2) * 1024 + w * 64, lb + (t * 4 + w) * 1024);
+    const int first = AT == 4 ? w * 64 : (w >> 1) * (9 * 1024) * g.KS + (w & 1) * 64;
+#pragma unroll
+    for (int t = 0; t < 9; ++t)
+        dm_load(s.ws, s.a_voff, ((mt * 18 + (g.flip ? 8 - t : t)) * g.KS + ch * 2) * 1024 + first, lb + (t * 4 + w) * 1024);
     const bool cut = ch == g.nch - 1 && (g.in_CH & (DM_KC - 1));      // channels past the last one are zeros
     const uint32_t parts = (uint32_t)(g.in_CH & (DM_KC - 1)) >> 3;
 #pragma unroll
-    for (int k = t; k < (NBW ? NBW : DM_NB); k += 9) {
+    for (int k = 0; k < (NBW ? NBW : DM_NB); ++k) {
         const int b = w + 4 * k;
         if (NBW || b < nB) {
             uint32_t vo = s.voff[k];
@@ -146,21 +159,23 @@ __device__ __forceinline__ void dm_issue(const DmaWave &s, const DmaArgs &g, int
 }
 
 // The matrix instructions of one chunk; pa, pb: this lane's first weight and input fragment, RP: bytes per staged row. The weight
-// fragments of a tap are read during the one before it; the input fragments of the next tap row replace those of this one as its last
-// tap has used them. loads(t): called at the start of tap t.
-template <int BT, class Loads>
-__device__ __forceinline__ void dm_chunk(f32x4 (&acc)[4][BT], const unsigned char *pa, const unsigned char *pb, int RP, Loads loads)
+// fragments of a tap are read one tap ahead (two where a tap is 8 instructions); the input fragments of the next tap row replace
+// those of this one as its last tap has used them.
+template <int AT, int BT>
+__device__ __forceinline__ void dm_chunk(f32x4 (&acc)[AT][BT], const unsigned char *pa, const unsigned char *pb, int RP)
 {
-    bf16x8 aq[2][4], bq[BT + 2];
+    constexpr int D = AT * BT <= 4 ? 3 : AT * BT <= 8 ? 2 : 1;
+    bf16x8 aq[D + 1][AT], bq[BT + 2];
 #pragma unroll
-    for (int a = 0; a < 4; ++a) aq[0][a] = *reinterpret_cast<const bf16x8 *>(pa + a * 1024);
+    for (int d = 0; d < D; ++d)
+#pragma unroll
+        for (int a = 0; a < AT; ++a) aq[d][a] = *reinterpret_cast<const bf16x8 *>(pa + (d * 4 + a) * 1024);
 #pragma unroll
     for (int c = 0; c < BT + 2; ++c) bq[c] = *reinterpret_cast<const bf16x8 *>(pb + c * 64);
 #pragma unroll
     for (int t = 0; t < 9; ++t) {
         const int r = t / 3, q = t % 3;
         const bool refill = q == 2 && r < 2;
-        loads(t);
         if (t == 3) __builtin_amdgcn_s_setprio(1);
         if (t == 6) __builtin_amdgcn_s_setprio(2);
         if (refill) {
@@ -169,21 +184,21 @@ __device__ __forceinline__ void dm_chunk(f32x4 (&acc)[4][BT], const unsigned cha
         }
 #pragma unroll
         for (int j = 0; j < BT; ++j) {
-            if (t < 8) {
+            if (t + D < 9) {
 #pragma unroll
-                for (int a = j * 4 / BT; a < (j + 1) * 4 / BT; ++a)
-                    aq[(t + 1) & 1][a] = *reinterpret_cast<const bf16x8 *>(pa + ((t + 1) * 4 + a) * 1024);
+                for (int a = j * AT / BT; a < (j + 1) * AT / BT; ++a)
+                    aq[(t + D) % (D + 1)][a] = *reinterpret_cast<const bf16x8 *>(pa + ((t + D) * 4 + a) * 1024);
             }
 #pragma unroll
-            for (int a = 0; a < 4; ++a) acc[a][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aq[t & 1][a], bq[j + q], acc[a][j], 0, 0, 0);
+            for (int a = 0; a < AT; ++a) acc[a][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aq[t % (D + 1)][a], bq[j + q], acc[a][j], 0, 0, 0);
             if (refill) bq[j + 2] = *reinterpret_cast<const bf16x8 *>(pb + (r + 1) * RP + (j + 2) * 64);
         }
         // (in program order: reads go into the shadow of the matrix instructions one at a time)
         if (refill) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
 #pragma unroll
         for (int j = 0; j < BT; ++j) {
-            if (t < 8 && (j + 1) * 4 / BT > j * 4 / BT) __builtin_amdgcn_sched_group_barrier(0x100, BT < 4 ? 4 / BT : 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+            if (t + D < 9 && (j + 1) * AT / BT > j * AT / BT) __builtin_amdgcn_sched_group_barrier(0x100, BT < AT ? AT / BT : 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, AT, 0);
             if (refill) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -199,35 +214,36 @@ __device__ __forceinline__ int dm_lane_row(const DmaWave &s, const DmaArgs &g, c
     return rowc + (int)pc_udiv((uint32_t)rowc, g.mg_H) - (t.r0 + (int)pc_udiv((uint32_t)t.r0, g.mg_H));
 }
 
-template <int BT, int ACT>
-__device__ __forceinline__ void dm_store(const DmaWave &s, const DmaArgs &g, const DmaTile &t, const f32x4 (&acc)[4][BT], unsigned char *stg,
+template <int AT, int BT, int ACT>
+__device__ __forceinline__ void dm_store(const DmaWave &s, const DmaArgs &g, const DmaTile &t, int m0, const f32x4 (&acc)[AT][BT], unsigned char *stg,
                                          __amdgpu_buffer_rsrc_t osrc, __amdgpu_buffer_rsrc_t msrc)
 {
+    constexpr int LPP = 2 * AT, PXI = 64 / LPP, PITCH = 32 * AT + 16;     // lanes per pixel, pixels per store, bytes per pixel in LDS
 #pragma unroll
     for (int j0 = 0; j0 < BT; j0 += 4) {
         constexpr int FULL = BT < 4 ? BT : 4;
         const int NC = BT - j0 < FULL ? BT - j0 : FULL;        // columns of this pass
-        v4u32 mk[FULL * 2];
-        uint32_t off[FULL * 2];
+        v4u32 mk[FULL * 16 / PXI];
+        uint32_t off[FULL * 16 / PXI];
 #pragma unroll
-        for (int it = 0; it < NC * 2; ++it) {
-            const int px = it * 8 + (s.lane >> 3);
-            const int orow = t.r0 + s.rg * 16 + (px & 15), x = t.x0 + s.cg * BT + j0 + (px >> 4), m = t.mt * 64 + (s.lane & 7) * 8;
+        for (int it = 0; it < NC * 16 / PXI; ++it) {
+            const int px = it * PXI + s.lane / LPP;
+            const int orow = t.r0 + s.rg * 16 + (px & 15), x = t.x0 + s.cg * BT + j0 + (px >> 4), m = m0 + (s.lane % LPP) * 8;
             off[it] = orow < g.rows && x < g.W && m < g.out_CH ? (uint32_t)(orow * g.W + x) * (uint32_t)(g.out_CH * 2) + (uint32_t)(m * 2) : DM_OOB;
             if (ACT == PC_ACT_RELU_MASK) mk[it] = __builtin_amdgcn_raw_buffer_load_b128(msrc, (int)off[it], 0, 0);
         }
 #pragma unroll
         for (int j = 0; j < NC; ++j)
 #pragma unroll
-            for (int e = 0; e < 2; ++e) {      // 8 of the lane's 16 channels: 16 * (lane / 16) + 8 * e ..
+            for (int e = 0; e < AT / 2; ++e) {     // 8 of the lane's 4 * AT channels
                 v4u32 pv;
 #pragma unroll
                 for (int u = 0; u < 4; ++u) pv[u] = pc_pack_bf16x2(acc[e * 2 + (u >> 1)][j0 + j][(u & 1) * 2], acc[e * 2 + (u >> 1)][j0 + j][(u & 1) * 2 + 1]);
-                *reinterpret_cast<v4u32 *>(stg + (j * 16 + (s.lane & 15)) * DM_STG + (s.lane >> 4) * 32 + e * 16) = pv;
+                *reinterpret_cast<v4u32 *>(stg + (j * 16 + (s.lane & 15)) * PITCH + (s.lane >> 4) * (8 * AT) + e * 16) = pv;
             }
 #pragma unroll
-        for (int it = 0; it < NC * 2; ++it) {
-            v4u32 pv = *reinterpret_cast<const v4u32 *>(stg + (it * 8 + (s.lane >> 3)) * DM_STG + (s.lane & 7) * 16);
+        for (int it = 0; it < NC * 16 / PXI; ++it) {
+            v4u32 pv = *reinterpret_cast<const v4u32 *>(stg + (it * PXI + s.lane / LPP) * PITCH + (s.lane % LPP) * 16);
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 if (ACT == PC_ACT_RELU) pv[u] = pc_relu_bf16x2(pv[u]);
@@ -238,10 +254,10 @@ __device__ __forceinline__ void dm_store(const DmaWave &s, const DmaArgs &g, con
     }
 }
 
-template <int BT> __device__ __forceinline__ void dm_zero(f32x4 (&acc)[4][BT])
+template <int AT, int BT> __device__ __forceinline__ void dm_zero(f32x4 (&acc)[AT][BT])
 {
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int a = 0; a < AT; ++a)
 #pragma unroll
         for (int j = 0; j < BT; ++j) acc[a][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 }
@@ -255,23 +271,22 @@ __device__ __forceinline__ void dm_one_tile(DmaWave &s, const DmaArgs &g, const 
     const unsigned char *pa = lds + s.lane * 16;
     const unsigned char *pb = lds + DM_A_BYTES + dm_lane_row(s, g, t) * (q.EPR * 16) + (s.lane >> 4) * 16 + s.cg * (BT * 64);
     f32x4 acc[4][BT];
-    dm_zero<BT>(acc);
+    dm_zero<4, BT>(acc);
     for (int ch = 0; ch < g.nch; ++ch) {
         if (!fresh) asm volatile("s_barrier" ::: "memory");      // every wavefront has read what the loads replace
         fresh = false;
         __builtin_amdgcn_s_setprio(3);
-#pragma unroll
-        for (int i = 0; i < 9; ++i) dm_issue<0>(s, g, q.nB, t.mt, ch, 0, i);
+        dm_issue<4, 0>(s, g, q.nB, t.mt, ch, 0);
         __builtin_amdgcn_s_setprio(0);
         dm_wait_barrier<0>();
-        dm_chunk<BT>(acc, pa, pb, q.EPR * 16, [](int) {});
+        dm_chunk<4, BT>(acc, pa, pb, q.EPR * 16);
     }
     __builtin_amdgcn_s_setprio(3);
     asm volatile("s_barrier" ::: "memory");
-    dm_store<BT, ACT>(s, g, t, acc, lds + s.w * (64 * DM_STG), osrc, msrc);
+    dm_store<4, BT, ACT>(s, g, t, t.mt * 64, acc, lds + s.w * (64 * DM_STG), osrc, msrc);
 }
 
-template <int BT, int NBUF, int ACT>
+template <int BT, int ACT>
 __global__ void __launch_bounds__(256, 2)
 pc_mfma_conv_dma_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__ out, const uint16_t *__restrict__ wz, DmaArgs g)
 {
@@ -288,80 +303,116 @@ pc_mfma_conv_dma_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__ 
     const int vl = (g.last & 7) == 0 ? (b & 7) * (g.last >> 3) + (b >> 3) : b;
     s.xs = dm_rsrc(in, g.in_bytes);
     s.ws = dm_rsrc(wz, g.wz_bytes);
-    {
-        const int m = s.lane & 15, kg = s.lane >> 4;
-        s.a_voff = (m >> 3) * (9 * 1024) * g.KS + (kg >> 1) * 1024 + (kg & 1) * 512 + (16 * ((m >> 2) & 1) + (m & 3)) * 16;
-    }
+    s.a_voff = dm_weight_offset<4>(g, s.lane);
     const __amdgpu_buffer_rsrc_t osrc = __builtin_amdgcn_make_buffer_rsrc(out, 0, g.out_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t msrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint16_t *>(ACT == PC_ACT_RELU_MASK ? g.act_mask : out), 0, g.out_bytes, 0x00020000);
     const int ntile = g.rounds + (b < g.last);
-    auto tile_at = [&](int k) { return dm_tile<BT>(g, k < g.rounds ? k * G + vb : g.rounds * G + vl, 0); };
-    if constexpr (NBUF == 1) {
-        bool fresh = true;
-        for (int k = 0; k < ntile; ++k) dm_one_tile<BT, ACT>(s, g, g.geo[0], lds, osrc, msrc, tile_at(k), fresh);
-        if constexpr (BT == 8 || BT == 4) {
-            const int p0 = (g.rounds * G + g.last) << g.lgP;
-            for (int u = (b - g.last + 2 * G) % G; u < g.pieces; u += G) {
-                const DmaTile t = dm_tile<BT>(g, p0 + u, g.lgP);
-                if (g.lgP == 1) dm_one_tile<BT / 2, ACT>(s, g, g.geo[1], lds, osrc, msrc, t, fresh);
-                else if constexpr (BT == 8) dm_one_tile<2, ACT>(s, g, g.geo[2], lds, osrc, msrc, t, fresh);
-            }
-        }
-    } else {
-        // Chunk i of the workgroup's list is loaded during chunk i - AHEAD, a step per tap.
-        constexpr int AHEAD = NBUF - 1, NBW = NBUF == 3 ? DM_NBW : 0;
-        const DmaGeo &q = g.geo[0];
-        const int RP = q.EPR * 16, chunks = ntile * g.nch;
-        DmaTile t = tile_at(0), tl = t;      // the tile being multiplied, the one being loaded
-        int kl = 0, chl = 0, bl = 0;         // cursor of the loads: tile, chunk, buffer
-        dm_offsets(s, g, q, tl);
-        auto advance = [&]() {
-            if (++bl == NBUF) bl = 0;
-            if (++chl == g.nch) {
-                chl = 0;
-                if (++kl < ntile) {
-                    tl = tile_at(kl);
-                    dm_offsets(s, g, q, tl);
-                }
-            }
-        };
-        for (int i = 0; i < AHEAD && i < chunks; ++i) {
-#pragma unroll
-            for (int j = 0; j < 9; ++j) dm_issue<NBW>(s, g, q.nB, tl.mt, chl, bl * g.buf_bytes, j);
-            advance();
-        }
-        int bc = 0;
-        for (int k = 0; k < ntile; ++k) {
-            const int at = s.lane * 16, bt = DM_A_BYTES + dm_lane_row(s, g, t) * RP + (s.lane >> 4) * 16 + s.cg * (BT * 64);
-            f32x4 acc[4][BT];
-            dm_zero<BT>(acc);
-            for (int ch = 0; ch < g.nch; ++ch) {
-                // this chunk's loads are complete: what follows them is the next chunk's loads, and a finished tile's stores
-                if (AHEAD == 2) {
-                    if (k * g.nch + ch + 1 < chunks) dm_wait_barrier<9 + NBW>();
-                    else dm_wait_barrier<0>();
-                } else if (k > 0 && ch == 0) dm_wait_barrier<2 * BT>();
-                else dm_wait_barrier<0>();
-                const unsigned char *lb = lds + bc * g.buf_bytes;
-                const bool more = kl < ntile;
-                dm_chunk<BT>(acc, lb + at, lb + bt, RP, [&](int j) __attribute__((always_inline)) {
-                    if (more) dm_issue<NBW>(s, g, q.nB, tl.mt, chl, bl * g.buf_bytes, j);
-                });
-                if (more) advance();
-                if (++bc == NBUF) bc = 0;
-            }
-            asm volatile("s_barrier" ::: "memory");                   // the buffer just multiplied is free
-            dm_store<BT, ACT>(s, g, t, acc, lds + (bc == 0 ? NBUF - 1 : bc - 1) * g.buf_bytes + s.w * (64 * DM_STG), osrc, msrc);
-            if (k + 1 < ntile) t = tile_at(k + 1);
+    bool fresh = true;
+    for (int k = 0; k < ntile; ++k)
+        dm_one_tile<BT, ACT>(s, g, g.geo[0], lds, osrc, msrc, dm_tile<BT>(g, k < g.rounds ? k * G + vb : g.rounds * G + vl, 0), fresh);
+    if constexpr (BT == 8 || BT == 4) {
+        const int p0 = (g.rounds * G + g.last) << g.lgP;
+        for (int u = (b - g.last + 2 * G) % G; u < g.pieces; u += G) {
+            const DmaTile t = dm_tile<BT>(g, p0 + u, g.lgP);
+            if (g.lgP == 1) dm_one_tile<BT / 2, ACT>(s, g, g.geo[1], lds, osrc, msrc, t, fresh);
+            else if constexpr (BT == 8) dm_one_tile<2, ACT>(s, g, g.geo[2], lds, osrc, msrc, t, fresh);
         }
     }
 }
 
+// One workgroup of 8 wavefronts per CU: four multiply, four issue the direct loads of the chunks ahead, up to NBUF - 1 of them (a
+// wavefront issues in order, and 48 to 77 KiB of loads take 800 to 1200 cycles to be accepted: with the loads in the multiplying
+// wavefronts a chunk of the smaller tiles took twice its matrix instructions). AT = 2: the wavefronts are two halves of the
+// channels x two groups of pixels, tiles of 64 x 128 (BT = 4) and 64 x 64 (BT = 2).
+// What bounds it: a chunk of 64 x 256, 128 and 64 pixels takes 1.03, 0.55 and 0.39 us for 0.96, 0.48 and 0.24 us of matrix
+// instructions; below 64 x 128 the direct loads (48 KiB a chunk, of them 36 KiB weights that all row tiles load again). With a launch and
+// the first loads and last stores around them, 128 images (us, with the kernel that keeps the weights in registers -> here): 16 x 16
+// 128 -> 128 11.2 -> 10.3, 8 x 8 256 -> 256 11.9 -> 9.9, 4 x 4 512 -> 512 12.2 -> 11.2, 4 x 4 256 -> 512 8.3 -> 7.4; 64 images 7 x 7
+// 512 -> 512 17.3 -> 15.6; one image 56 x 56 256 -> 256 7.7 -> 6.8, 224 x 224 64 -> 64 9.4 -> 7.6.
+template <int AT, int BT, int NBUF, int ACT>
+__global__ void __launch_bounds__(512, 2)
+pc_mfma_conv_solo_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__ out, const uint16_t *__restrict__ wz, DmaArgs g)
+{
+    extern __shared__ __align__(16) unsigned char lds[];
+    constexpr int NBW = NBUF == 3 ? dm_nbw(BT) : 0;
+    DmaWave s;
+    s.lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    s.w = wave & 3;
+    const int pw = AT == 2 ? s.w >> 1 : s.w;
+    s.cg = pw & ((1 << g.lgCG) - 1);
+    s.rg = pw >> g.lgCG;
+    const int G = gridDim.x, b = blockIdx.x;
+    const int vb = (G & 7) == 0 ? (b & 7) * (G >> 3) + (b >> 3) : b;
+    const int vl = (g.last & 7) == 0 ? (b & 7) * (g.last >> 3) + (b >> 3) : b;
+    const int ntile = g.rounds + (b < g.last), nch = g.nch;
+    auto tile_at = [&](int k) { return dm_tile<BT>(g, k < g.rounds ? k * G + vb : g.rounds * G + vl, 0); };
+    const DmaGeo &q = g.geo[0];
+    const int buf_bytes = (int)g.buf_bytes;
+
+    if (wave >= 4) {
+        s.xs = dm_rsrc(in, g.in_bytes);
+        s.ws = dm_rsrc(wz, g.wz_bytes);
+        s.a_voff = dm_weight_offset<AT>(g, s.lane);
+        const int nB = q.nB, chunks = ntile * nch;
+        DmaTile t = tile_at(0);
+        dm_offsets(s, g, q, t);
+        int k = 0, ch = 0, at = 0, done = 0;       // cursor: tile, chunk, buffer; chunks issued
+        auto next = [&]() {
+            dm_issue<AT, NBW>(s, g, nB, t.mt, ch, at);
+            at = at + buf_bytes == NBUF * buf_bytes ? 0 : at + buf_bytes;
+            ++done;
+            if (++ch == nch) {
+                ch = 0;
+                if (++k < ntile) {
+                    t = tile_at(k);
+                    dm_offsets(s, g, q, t);
+                }
+            }
+        };
+        for (int i = 0; i < NBUF - 1; ++i)
+            if (done < chunks) next();
+        int left = nch;
+        for (int i = 0; i < chunks; ++i) {
+            // chunk i is complete, and the buffer of chunk i - 1 is free
+            if (NBUF == 3 && done > i + 1) dm_wait_barrier<9 + NBW>();
+            else dm_wait_barrier<0>();
+            if (done < chunks) next();
+            if (--left == 0) {
+                left = nch;
+                asm volatile("s_barrier" ::: "memory");      // (the tile's sums leave through the buffer of its last chunk)
+            }
+        }
+        return;
+    }
+    const __amdgpu_buffer_rsrc_t osrc = __builtin_amdgcn_make_buffer_rsrc(out, 0, g.out_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t msrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint16_t *>(ACT == PC_ACT_RELU_MASK ? g.act_mask : out), 0, g.out_bytes, 0x00020000);
+    const int RP = q.EPR * 16, half = AT == 2 ? s.w & 1 : 0;
+    int at = 0;
+    for (int k = 0; k < ntile; ++k) {
+        const DmaTile t = tile_at(k);
+        const unsigned char *pa = lds + s.lane * 16 + half * 2048;
+        const unsigned char *pb = lds + DM_A_BYTES + dm_lane_row(s, g, t) * RP + (s.lane >> 4) * 16 + s.cg * (BT * 64);
+        f32x4 acc[AT][BT];
+        dm_zero<AT, BT>(acc);
+        int used = 0;
+        for (int ch = 0; ch < nch; ++ch) {
+            asm volatile("s_barrier" ::: "memory");
+            dm_chunk<AT, BT>(acc, pa + at, pb + at, RP);
+            used = at;
+            at = at + buf_bytes == NBUF * buf_bytes ? 0 : at + buf_bytes;
+        }
+        asm volatile("s_barrier" ::: "memory");
+        dm_store<AT, BT, ACT>(s, g, t, t.mt * 64 + half * 32, acc, lds + used + s.w * (64 * (32 * AT + 16)), osrc, msrc);
+    }
+}
+
 // ---- plan and launch
-struct DmaCand { int code, bt, nbuf; };
-static const DmaCand kDma[] = {{40, 8, 1}, {41, 4, 1}, {42, 7, 1}, {43, 2, 3}};
-static const int kNumDma = sizeof(kDma) / sizeof(kDma[0]);
+struct DmaCand { int code, at, bt, nbuf; };       // nbuf 1: two workgroups per CU
+static const DmaCand kDma[] = {{40, 4, 8, 1}, {41, 4, 4, 1}, {42, 4, 7, 1}, {43, 2, 4, 3}, {45, 4, 4, 2}, {46, 2, 2, 3}};
+constexpr int kNumDma = sizeof(kDma) / sizeof(kDma[0]);
 
 // Fills the plan for a kernel and 1 << lgCG wavefronts side by side; false when it does not fit.
 static bool plan_dma(const MfmaArgs &g, bool flip, const DmaCand &cand, int lgCG, DmaArgs *out, size_t *lds, int *grid, double *est, int num_cu)
@@ -371,7 +422,9 @@ static bool plan_dma(const MfmaArgs &g, bool flip, const DmaCand &cand, int lgCG
     t.N = g.N; t.H = g.in_H; t.W = g.in_W; t.in_CH = g.in_CH; t.out_CH = g.out_CH;
     t.KS = g.KS; t.nch = (g.in_CH + DM_KC - 1) / DM_KC; t.flip = flip;
     t.lgCG = lgCG;
-    t.TR = 16 * (4 >> lgCG);
+    const int lgPG = cand.at == 2 ? 1 : 2;       // groups of pixels among the wavefronts (log2)
+    if (lgCG > lgPG) return false;
+    t.TR = 16 << (lgPG - lgCG);
     const int64_t rows = (int64_t)g.N * g.in_H;
     if ((rows + g.N + 2 * t.TR) * (g.in_H + 1) >= ((int64_t)1 << 32) || rows >= (1 << 24)) return false;   // multiply-high divisions stay exact
     t.rows = (int)rows;
@@ -387,9 +440,9 @@ static bool plan_dma(const MfmaArgs &g, bool flip, const DmaCand &cand, int lgCG
         q.nB = (t.nrow * q.EPR + 63) / 64;
     }
     const int nB = t.geo[0].nB, TC = cand.bt << lgCG;
-    t.buf_bytes = DM_A_BYTES + (uint32_t)(cand.nbuf == 3 ? 4 * DM_NBW : nB) * 1024;
+    t.buf_bytes = DM_A_BYTES + (uint32_t)(cand.nbuf == 3 ? 4 * dm_nbw(cand.bt) : nB) * 1024;
     *lds = (size_t)t.buf_bytes * cand.nbuf;
-    if (nB > 4 * (cand.nbuf == 3 ? DM_NBW : DM_NB) || *lds > (size_t)DM_LDS_MAX / (cand.nbuf == 1 ? 2 : 1)) return false;
+    if (nB > 4 * (cand.nbuf == 3 ? dm_nbw(cand.bt) : DM_NB) || *lds > (size_t)DM_LDS_MAX / (cand.nbuf == 1 ? 2 : 1)) return false;
     t.tiles_x = (g.in_W + TC - 1) / TC;
     const int64_t p_tiles = (rows + t.TR - 1) / t.TR * t.tiles_x;
     const int m_tiles = (g.out_CH + 63) / 64;
@@ -407,16 +460,17 @@ static bool plan_dma(const MfmaArgs &g, bool flip, const DmaCand &cand, int lgCG
     // Estimated time (us). A round is one tile for each of the workgroups the chip holds, two per CU; a workgroup that has its CU to
     // itself takes its chunks faster. A chunk takes a fixed time and one for its direct loads of the input, a tile an end; the
     // tensors take their bytes (the input with its border, in pieces of 64) at 6 TB/s (7.9 where they come from the last cache, as
-    // in a loop over one layer). Constants for 8, 7, 4 and 2 columns per wavefront, and for 2 with three buffers, from 4000
-    // timings of 147 layer shapes (1 to 128 images, 4 x 4 to 224 x 224, 8 to 512 channels; 8 % rms; the plan with the
-    // least estimate is on average 3.5 % slower than the fastest of a shape).
+    // in a loop over one layer). Constants for 8, 7, 4 and 2 columns per wavefront, and for the tiles of a lone workgroup, from 5000
+    // timings of 147 layer shapes (1 to 128 images, 4 x 4 to 224 x 224, 8 to 512 channels; 8 % rms). On 160 shapes drawn
+    // afterwards the choice, the register kernels' included, is on average 2.7 % slower than the fastest, the worst 30 % (16 input
+    // channels), and 12 % faster than the fastest of the register kernels.
     // What does not fill a round of tiles may be cut in halves or quarters, all of it or what a tile per CU leaves: 56 x 56,
     // 256 -> 256, batch 32 is 784 tiles of 8 columns for 512 workgroups; 512 + 256 tiles and 16 cut into 64 quarters
-    // take 77 us instead of 85.
+    // take 73 us instead of 81.
     struct Times { double chunk, load, tile; };
     static const Times kPair[4] = {{2.627, 0.0391, 2.225}, {2.232, 0.0405, 2.374}, {1.779, 0.0215, 1.669}, {1.047, 0.0361, 1.416}};
     static const Times kOne[4] = {{2.960, 0.0001, 1.658}, {2.614, 0.0, 1.425}, {1.693, 0.0038, 0.940}, {1.047, 0.0103, 0.671}};
-    static const Times kSolo = {0.949, 0.002, 0.947};
+    static const Times kSolo[3] = {{1.031, 0.0042, 1.038}, {0.440, 0.0137, 0.491}, {0.387, 0.0, 0.445}};
     auto tile_us = [&](const Times &c, int l) { return t.nch * (c.chunk + c.load * t.geo[l].nB) + c.tile; };
     const int first = cand.bt == 8 ? 0 : cand.bt == 7 ? 1 : 2;
     const int slots = num_cu * (cand.nbuf == 1 ? 2 : 1);
@@ -428,7 +482,7 @@ static bool plan_dma(const MfmaArgs &g, bool flip, const DmaCand &cand, int lgCG
         if (o && (cand.nbuf > 1 || (cand.bt != 8 && !(cand.bt == 4 && lgP == 1)))) continue;
         if ((o == 1 || o == 2) && left <= num_cu) continue;
         const int last = o == 0 ? left : o < 3 ? num_cu : 0, pieces = o == 0 ? 0 : (left - last) << lgP;
-        const Times &pair = cand.nbuf > 1 ? kSolo : kPair[first], &ppair = kPair[cand.bt == 8 && lgP == 1 ? 2 : 3], &pone = kOne[cand.bt == 8 && lgP == 1 ? 2 : 3];
+        const Times &pair = cand.nbuf > 1 ? kSolo[cand.at == 4 ? 0 : cand.bt == 4 ? 1 : 2] : kPair[first], &ppair = kPair[cand.bt == 8 && lgP == 1 ? 2 : 3], &pone = kOne[cand.bt == 8 && lgP == 1 ? 2 : 3];
         double c = (t.rounds + (last > (cand.nbuf > 1 ? 0 : num_cu))) * tile_us(pair, 0);
         if (cand.nbuf == 1 && last > 0 && last <= num_cu) c += tile_us(kOne[first], 0);
         if (pieces && last) c += 0.83 * tile_us(ppair, lgP);
@@ -443,33 +497,26 @@ static bool plan_dma(const MfmaArgs &g, bool flip, const DmaCand &cand, int lgCG
     return true;
 }
 
-template <int BT, int NBUF, int ACT>
-static hipError_t launch_dma_act(int device, hipStream_t st, int grid, size_t lds, const uint16_t *in, uint16_t *out, const uint16_t *wz, const DmaArgs &g)
+typedef void (*DmaKernel)(const uint16_t *, uint16_t *, const uint16_t *, DmaArgs);
+
+static hipError_t launch_dma(DmaKernel kernel, pc_per_device_once &attr, int device, hipStream_t st, int grid, int threads, size_t lds, const uint16_t *in,
+                             uint16_t *out, const uint16_t *wz, const DmaArgs &g)
 {
-    static pc_per_device_once attr;
     if (pc_once_pending(attr, device)) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&pc_mfma_conv_dma_kernel<BT, NBUF, ACT>),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, DM_LDS_MAX);
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, DM_LDS_MAX);
         if (e != hipSuccess) return e;
         pc_once_done(attr, device);
     }
-    hipLaunchKernelGGL((pc_mfma_conv_dma_kernel<BT, NBUF, ACT>), dim3((unsigned)grid), dim3(256), lds, st, in, out, wz, g);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3((unsigned)threads), lds, st, in, out, wz, g);
     return hipGetLastError();
 }
 
-template <int BT, int NBUF>
-static hipError_t launch_dma(int device, hipStream_t st, int grid, size_t lds, const uint16_t *in, uint16_t *out, const uint16_t *wz, const DmaArgs &g, int act)
+// pcfg: -1 or a code of kDma; lgCG: -1 or the wavefronts side by side (log2), on return those of the plan taken. *launched stays 0
+// where no kernel takes the launch or no estimate is below limit (us); it becomes the kernel's code.
+pc_status pc_run_mfma_conv_dma(pc_ctx *ctx, int pcfg, int *lgCG, double limit, const MfmaArgs &g0, bool flip, const uint16_t *in, uint16_t *out,
+                               const uint16_t *wz, int *launched, int act)
 {
-    if (act == PC_ACT_RELU) return launch_dma_act<BT, NBUF, PC_ACT_RELU>(device, st, grid, lds, in, out, wz, g);
-    if (act == PC_ACT_RELU_MASK) return launch_dma_act<BT, NBUF, PC_ACT_RELU_MASK>(device, st, grid, lds, in, out, wz, g);
-    return launch_dma_act<BT, NBUF, PC_ACT_NONE>(device, st, grid, lds, in, out, wz, g);
-}
-
-// pcfg: -1 or a code of kDma. *launched stays false where no kernel takes the launch or no estimate is below limit (us).
-pc_status pc_run_mfma_conv_dma(pc_ctx *ctx, int pcfg, double limit, const MfmaArgs &g0, bool flip, const uint16_t *in, uint16_t *out, const uint16_t *wz,
-                               bool *launched, int act)
-{
-    *launched = false;
+    *launched = 0;
     if (g0.lstep != 1 || g0.oscale != 1 || (g0.in_CH & 7) || (g0.out_CH & 7)) return PC_OK;
     DmaArgs best;
     size_t best_lds = 0;
@@ -477,7 +524,7 @@ pc_status pc_run_mfma_conv_dma(pc_ctx *ctx, int pcfg, double limit, const MfmaAr
     double best_est = limit;
     for (int k = 0; k < kNumDma; ++k) {
         if (pcfg >= 0 && pcfg != kDma[k].code) continue;
-        for (int lg = 0; lg <= 2; ++lg) {
+        for (int lg = *lgCG < 0 ? 0 : *lgCG; lg <= (*lgCG < 0 ? 2 : *lgCG); ++lg) {
             DmaArgs t;
             size_t lds;
             int grid;
@@ -488,16 +535,17 @@ pc_status pc_run_mfma_conv_dma(pc_ctx *ctx, int pcfg, double limit, const MfmaAr
     }
     if (best_k < 0) return PC_OK;
     const DmaCand &c = kDma[best_k];
-    hipError_t e;
-    switch (c.code) {
-#define DM_CASE(CODE, BT, NBUF) case CODE: e = launch_dma<BT, NBUF>(ctx->device, ctx->stream, best_grid, best_lds, in, out, wz, best, act); break;
-    DM_CASE(40, 8, 1)
-    DM_CASE(41, 4, 1)
-    DM_CASE(42, 7, 1)
-    default: e = launch_dma<2, 3>(ctx->device, ctx->stream, best_grid, best_lds, in, out, wz, best, act); break;
-#undef DM_CASE
-    }
-    *launched = true;
-    pc_note_kernel(ctx, "pc_mfma_conv_dma_kernel<%d, %d, %d>", c.bt, c.nbuf, act);
+#define DM_ACTS(NAME, ...) {&NAME<__VA_ARGS__, PC_ACT_NONE>, &NAME<__VA_ARGS__, PC_ACT_RELU>, &NAME<__VA_ARGS__, PC_ACT_RELU_MASK>}
+    static const DmaKernel kernels[kNumDma][3] = {
+        DM_ACTS(pc_mfma_conv_dma_kernel, 8), DM_ACTS(pc_mfma_conv_dma_kernel, 4), DM_ACTS(pc_mfma_conv_dma_kernel, 7),
+        DM_ACTS(pc_mfma_conv_solo_kernel, 2, 4, 3), DM_ACTS(pc_mfma_conv_solo_kernel, 4, 4, 2), DM_ACTS(pc_mfma_conv_solo_kernel, 2, 2, 3)};
+#undef DM_ACTS
+    static pc_per_device_once attr[kNumDma][3];
+    const hipError_t e = launch_dma(kernels[best_k][act], attr[best_k][act], ctx->device, ctx->stream, best_grid, c.nbuf == 1 ? 256 : 512, best_lds, in, out,
+                                    wz, best);
+    *launched = c.code;
+    *lgCG = best.lgCG;
+    if (c.nbuf == 1) pc_note_kernel(ctx, "pc_mfma_conv_dma_kernel<%d, %d>", c.bt, act);
+    else pc_note_kernel(ctx, "pc_mfma_conv_solo_kernel<%d, %d, %d, %d>", c.at, c.bt, c.nbuf, act);
     return pc_hip_check(ctx, e, "MFMA conv (direct loads) launch");
 }

@@ -1156,7 +1156,12 @@ pc_status pc_run_mfma_conv_ws(pc_ctx *ctx, int pcfg, const MfmaArgs &g0, int ext
                               const uint16_t *in, uint16_t *out, const uint16_t *wz, const SparseOperand &sp, bool *launched, int act)
 {
     *launched = false;
-    if (pcfg >= 40 && pcfg < 50) return pc_run_mfma_conv_dma(ctx, pcfg, 1e30, g0, tr[0] != 0, in, out, wz, launched, act);
+    int dma = 0, lgCG = -1;
+    if (pcfg >= 40 && pcfg < 50) {
+        const pc_status s = pc_run_mfma_conv_dma(ctx, pcfg, &lgCG, 1e30, g0, tr[0] != 0, in, out, wz, &dma, act);
+        *launched = dma != 0;
+        return s;
+    }
     // The structured-sparse kernel (override code 22; automatic from 64 reduction channels up): 64 x 256 tiles,
     // 64-channel chunks, pixels split over the MFMA wavefronts.
     if (sp.val && g0.lstep == 1 && (pcfg == 22 || (pcfg < 0 && g0.in_CH >= 64))) {
@@ -1198,8 +1203,9 @@ pc_status pc_run_mfma_conv_ws(pc_ctx *ctx, int pcfg, const MfmaArgs &g0, int ext
     for (int t = 0; t < 9; ++t)
         if (g0.tap_w[t] != t || tr[t] != (tr[0] ? 2 - t / 3 : t / 3) || tc[t] != (tc[0] ? 2 - t % 3 : t % 3)) return PC_OK;
     if (pcfg < 0) {
-        const pc_status s = pc_run_mfma_conv_dma(ctx, -1, best_k < 0 ? 1e30 : best_est, g0, tr[0] != 0, in, out, wz, launched, act);
-        if (s != PC_OK || *launched) return s;
+        const pc_status s = pc_run_mfma_conv_dma(ctx, -1, &lgCG, best_k < 0 ? 1e30 : best_est, g0, tr[0] != 0, in, out, wz, &dma, act);
+        *launched = dma != 0;
+        if (s != PC_OK || dma) return s;
     }
     if (best_k < 0) return PC_OK;
     const KsCand &c = kKs[best_k];

@@ -1,4 +1,4 @@
-"""The stride-1 forward / backward-data kernel that loads both operands straight to LDS (override codes 40 to 43), element by
+"""The stride-1 forward / backward-data kernels that load both operands straight to LDS (override codes 40 to 46), element by
 element against the oracle, at the edges of its tiles: rows that run across images (one zero row between two of them), columns past
 the map, a last chunk of 8, 16 or 24 channels, partial row tiles, and lists of tiles that continue in narrower ones."""
 import pytest
@@ -39,7 +39,7 @@ SHAPES = [
 ]
 
 
-@pytest.mark.parametrize("cfg", [40, 41, 42, 43])
+@pytest.mark.parametrize("cfg", [40, 41, 42, 43, 45, 46])
 @pytest.mark.parametrize("shape", SHAPES)
 def test_every_element(B, ctx, oracle, cfg, shape):
     B.pc_set_plan_override(ctx, cfg, 0)
@@ -49,7 +49,7 @@ def test_every_element(B, ctx, oracle, cfg, shape):
         B.pc_set_plan_override(ctx, -1, 0)
 
 
-@pytest.mark.parametrize("cfg", [41, 42, 43])
+@pytest.mark.parametrize("cfg", [41, 42, 43, 45, 46])
 def test_many_small_images(B, ctx, oracle, cfg):
     """A zero row between every four: the widest tile has not the LDS for it."""
     B.pc_set_plan_override(ctx, cfg, 0)
@@ -59,7 +59,7 @@ def test_many_small_images(B, ctx, oracle, cfg):
         B.pc_set_plan_override(ctx, -1, 0)
 
 
-@pytest.mark.parametrize("cfg", [-1, 40, 41, 42])
+@pytest.mark.parametrize("cfg", [-1, 40, 41, 42, 43, 45, 46])
 @pytest.mark.parametrize("dims", [(16, 56, 56, 64, 128), (32, 56, 56, 40, 256), (24, 57, 50, 32, 192)])
 def test_more_tiles_than_workgroups(B, ctx, cfg, dims):
     """Layers of the size it is for, whose tiles fill one to three rounds and leave some: against a kernel of the other family,
@@ -75,7 +75,8 @@ def test_more_tiles_than_workgroups(B, ctx, cfg, dims):
             y = torch.full((layer.N, layer.Ho, layer.Wo, layer.F), float("nan"), dtype=torch.bfloat16, device="cuda")
             B.pc_conv_fwd(ctx, g.desc, g.pk, g.x, y)
             out.append((B.pc_last_kernel(ctx), y.double()))
-        assert "pc_mfma_conv_dma_kernel" in out[0][0] and "pc_mfma_conv_ks_kernel" in out[1][0]
+        assert ("pc_mfma_conv_dma_kernel" if cfg in (40, 41, 42) else "pc_mfma_conv_solo_kernel" if cfg > 0 else "pc_mfma_conv_") in out[0][0]
+        assert "pc_mfma_conv_ks_kernel" in out[1][0]
         # two roundings to bf16 of sums that differ in the order of float32 additions: at most one unit in the last place apart
         a, b = out[0][1], out[1][1]
         assert bool((a - b).abs().le(2.0 ** -7 * torch.maximum(a.abs(), b.abs()) + 2.0 ** -12 * b.abs().max()).all())
@@ -84,7 +85,7 @@ def test_more_tiles_than_workgroups(B, ctx, cfg, dims):
         g.close()
 
 
-@pytest.mark.parametrize("cfg", [40, 41, 42, 43])
+@pytest.mark.parametrize("cfg", [40, 41, 42, 43, 45, 46])
 @pytest.mark.parametrize("dims", [(6, 10, 9, 128, 160), (2, 33, 70, 24, 72), (9, 96, 95, 16, 200)])
 def test_fused_relu(B, ctx, cfg, dims):
     """Bit-identical to the plain launch followed by the step."""
