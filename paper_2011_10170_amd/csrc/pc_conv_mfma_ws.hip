@@ -1187,24 +1187,37 @@ pc_status pc_run_mfma_conv_ws(pc_ctx *ctx, int pcfg, const MfmaArgs &g0, int ext
         if (pcfg == 22) return pc_fail(ctx, PC_ERR_UNSUPPORTED, "MFMA conv: the structured-sparse kernel does not fit this launch");
     }
     if (pcfg == 22) return pc_fail(ctx, PC_ERR_UNSUPPORTED, "MFMA conv: the pack holds no structured-sparse operand");
+    // the tap list is the full 3x3 in tap order, forward (offset (r, s)) or rotated (offset (2-r, 2-s))
+    for (int t = 0; t < 9; ++t)
+        if (g0.tap_w[t] != t || tr[t] != (tr[0] ? 2 - t / 3 : t / 3) || tc[t] != (tc[0] ? 2 - t % 3 : t % 3)) return PC_OK;
+    // The kernel of a shape, as code * 4 + lgCG: the estimates of all candidates take 2 us of host time, more than a small
+    // layer's launch (9 x 38 x 41, 56 -> 64: 6.0 us a call with them, 4.7 without).
+    bool known = false;
+    const int32_t key[PC_CHOICE_KEY] = {5, g0.N, g0.in_H, g0.in_W, g0.in_CH, g0.out_CH, g0.GH, g0.GW, g0.lstep * 16 + g0.oscale, ext * 2 + (tr[0] != 0)};
+    int32_t *choice = pcfg < 0 ? pc_choice(ctx, key, &known) : nullptr;
+    known = known && *choice >= 0;
+    if (known && (*choice >> 2) >= 40) {
+        lgCG = *choice & 3;
+        const pc_status s = pc_run_mfma_conv_dma(ctx, *choice >> 2, &lgCG, 1e30, g0, tr[0] != 0, in, out, wz, &dma, act);
+        *launched = dma != 0;
+        return s;
+    }
     MfmaArgs best;
     size_t best_lds = 0;
     double best_est = 0.0;
     int best_k = -1;
     for (int k = 0; k < kNumKs; ++k) {
-        if (pcfg >= 7 ? pcfg != kKs[k].code : kKs[k].tile == 0 || (kKs[k].ksp == 2 && g0.lstep != 2)) continue;
+        if (known ? *choice >> 2 != kKs[k].code : pcfg >= 7 ? pcfg != kKs[k].code : kKs[k].tile == 0 || (kKs[k].ksp == 2 && g0.lstep != 2)) continue;
         MfmaArgs t;
         size_t lds;
         double est;
         if (!plan_ks(g0, ext, kKs[k], &t, &lds, &est, ctx->num_cu)) continue;
         if (best_k < 0 || est < best_est) { best = t; best_lds = lds; best_est = est; best_k = k; }
     }
-    // the tap list is the full 3x3 in tap order, forward (offset (r, s)) or rotated (offset (2-r, 2-s))
-    for (int t = 0; t < 9; ++t)
-        if (g0.tap_w[t] != t || tr[t] != (tr[0] ? 2 - t / 3 : t / 3) || tc[t] != (tc[0] ? 2 - t % 3 : t % 3)) return PC_OK;
-    if (pcfg < 0) {
+    if (pcfg < 0 && !known) {
         const pc_status s = pc_run_mfma_conv_dma(ctx, -1, &lgCG, best_k < 0 ? 1e30 : best_est, g0, tr[0] != 0, in, out, wz, &dma, act);
         *launched = dma != 0;
+        if (s == PC_OK) *choice = dma ? dma * 4 + lgCG : best_k < 0 ? 0 : kKs[best_k].code * 4;
         if (s != PC_OK || dma) return s;
     }
     if (best_k < 0) return PC_OK;
