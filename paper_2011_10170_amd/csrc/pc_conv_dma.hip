@@ -1,4 +1,4 @@
-// Forward / backward-data at stride 1 on the matrix cores, both operands brought to LDS by direct loads (see pc_conv_mfma.hip
+// Forward / backward-data on the matrix cores, both operands brought to LDS by direct loads (see pc_conv_mfma.hip
 // for the implicit-GEMM formulation, the operand tiles and the MFMA register layout).
 #include "pc_mfma.h"
 #include <math.h>
@@ -31,6 +31,20 @@
 // Direct loads of the input tile per wavefront where every wavefront has as many (three buffers)
 constexpr __host__ __device__ int dm_nbw(int bt) { return bt == 2 ? 3 : 4; }
 
+// What a kernel computes. The tiles of the stride-2 passes lie on the output gradient's map (the forward pass's output).
+//   DM_FWD2: rows 2y, 2y + 1, 2y + 2 of a padded image go into output row y. Even and odd rows are staged apart, so that 16 output rows
+//     still read 16 staged rows next to each other; 2 * BT + 1 fragments serve the three taps of a row.
+//   DM_BWD2: input row 2y takes tap row 1 from output row y, row 2y + 1 tap row 2 from y and tap row 0 from y + 1, columns alike. A tile's
+//     four parity classes of pixels are summed together, from BT + 1 fragments per row.
+enum { DM_S1 = 0, DM_FWD2 = 1, DM_BWD2 = 2 };
+
+// The tap of step t of a chunk, in the order in which the fragments of a row are used up.
+template <int MODE> constexpr __host__ __device__ int dm_tap(int t)
+{
+    constexpr int order[9] = {3, 4, 5, 6, 7, 8, 1, 2, 0};
+    return MODE == DM_BWD2 ? order[t] : t;
+}
+
 // Staged columns for a tile width
 struct DmaGeo {
     int32_t IW, EPR, nB;             // staged columns, 16-byte elements per staged row, direct loads of the input tile
@@ -38,11 +52,12 @@ struct DmaGeo {
 };
 
 struct DmaArgs {
-    int32_t N, H, W, in_CH, out_CH;  // the output map has the input map's extent
+    int32_t N, H, W, in_CH, out_CH;  // H x W: the map of the tiles
+    int32_t in_H, in_W, out_H, out_W;
     int32_t KS, nch;                 // k-steps of 16 per tap in the operand tiles; chunks
     int32_t flip;                    // position t of the 3 x 3 neighbourhood takes weight tap 8 - t (backward-data)
     int32_t lgCG;                    // log2 of the wavefronts side by side in a tile's columns; the others lie below each other
-    int32_t TR, nrow, rows;          // rows of a tile, staged rows, N * H
+    int32_t TR, nrow, rows;          // rows of a tile, staged rows (of a parity at stride 2 forward), N * H
     int32_t m_fast, fdiv, tiles_x;   // tile index = slow * fdiv + fast, as in MfmaArgs; column tiles
     // The list of tiles: `rounds` whole rounds (a tile for every workgroup), then `last` tiles, one each for the first workgroups, and
     // the remaining tiles cut into 1 << lgP pieces of their columns, one each for the workgroups after those
@@ -104,6 +119,7 @@ __device__ __forceinline__ DmaTile dm_tile(const DmaArgs &g, int t, int sh)
 }
 
 // The elements of a tile that this lane loads: element e of the tile is the 16-byte part e % EPR of staged row e / EPR.
+template <int MODE>
 __device__ __forceinline__ void dm_offsets(DmaWave &s, const DmaArgs &g, const DmaGeo &q, const DmaTile &t)
 {
     const int V0 = t.r0 + (int)pc_udiv((uint32_t)t.r0, g.mg_H);
@@ -114,11 +130,16 @@ __device__ __forceinline__ void dm_offsets(DmaWave &s, const DmaArgs &g, const D
     for (int k = 0; k < DM_NB; ++k) {
         const uint32_t e = (uint32_t)((s.w + 4 * k) * 64 + lane);
         const uint32_t row = pc_udiv(e, q.mg_EPR), rem = e - row * q.EPR;
-        const uint32_t v = V0 + row;
-        const int n = (int)pc_udiv(v, g.mg_H1);
-        const int y = (int)v - n * (g.H + 1) - 1, x = t.x0 - 1 + (int)(rem >> 2);
-        const bool ok = (int)row < g.nrow && (int)(rem >> 2) < q.IW && y >= 0 && n < g.N && (unsigned)x < (unsigned)g.W;
-        s.voff[k] = ok ? (uint32_t)((n * g.H + y) * g.W + x) * (uint32_t)(g.in_CH * 2) + (rem & 3u) * 16u : DM_OOB;
+        const int odd = MODE == DM_FWD2 && (int)row >= g.nrow;
+        const uint32_t v = V0 + row - (odd ? g.nrow : 0);
+        const int n = (int)pc_udiv(v, g.mg_H1), c = (int)(rem >> 2);
+        int y = (int)v - n * (g.H + 1);
+        if (MODE == DM_S1) y -= 1;
+        if (MODE == DM_FWD2) y = 2 * y + odd - 1;
+        const int x = MODE == DM_S1 ? t.x0 - 1 + c : MODE == DM_FWD2 ? 2 * t.x0 - 1 + c : t.x0 + c;
+        const bool ok = (int)row < (MODE == DM_FWD2 ? 2 * g.nrow : g.nrow) && c < q.IW && (unsigned)y < (unsigned)g.in_H && n < g.N &&
+                        (unsigned)x < (unsigned)g.in_W;
+        s.voff[k] = ok ? (uint32_t)((n * g.in_H + y) * g.in_W + x) * (uint32_t)(g.in_CH * 2) + (rem & 3u) * 16u : DM_OOB;
         s.part |= (rem & 3u) << (2 * k);
     }
 }
@@ -135,7 +156,7 @@ __device__ __forceinline__ int dm_weight_offset(const DmaArgs &g, int lane)     
     return AT == 4 ? at + (m >> 3) * (9 * 1024) * g.KS + (16 * ((m >> 2) & 1) + (m & 3)) * 16 : at + (8 * (m >> 2) + (m & 3)) * 16;
 }
 
-template <int AT, int NBW>
+template <int MODE, int AT, int NBW>
 __device__ __forceinline__ void dm_issue(const DmaWave &s, const DmaArgs &g, int nB, int mt, int ch, int lb)
 {
     // (the wavefront's number is hidden from the compiler here: it would compute all scalar offsets ahead and spill them)
@@ -144,7 +165,7 @@ __device__ __forceinline__ void dm_issue(const DmaWave &s, const DmaArgs &g, int
     const int first = AT == 4 ? w * 64 : (w >> 1) * (9 * 1024) * g.KS + (w & 1) * 64;
 #pragma unroll
     for (int t = 0; t < 9; ++t)
-        dm_load(s.ws, s.a_voff, ((mt * 18 + (g.flip ? 8 - t : t)) * g.KS + ch * 2) * 1024 + first, lb + (t * 4 + w) * 1024);
+        dm_load(s.ws, s.a_voff, ((mt * 18 + (MODE == DM_S1 && g.flip ? 8 - t : dm_tap<MODE>(t))) * g.KS + ch * 2) * 1024 + first, lb + (t * 4 + w) * 1024);
     const bool cut = ch == g.nch - 1 && (g.in_CH & (DM_KC - 1));      // channels past the last one are zeros
     const uint32_t parts = (uint32_t)(g.in_CH & (DM_KC - 1)) >> 3;
 #pragma unroll
@@ -158,29 +179,32 @@ __device__ __forceinline__ void dm_issue(const DmaWave &s, const DmaArgs &g, int
     }
 }
 
-// The matrix instructions of one chunk; pa, pb: this lane's first weight and input fragment, RP: bytes per staged row. The weight
-// fragments of a tap are read one tap ahead (two where a tap is 8 instructions); the input fragments of the next tap row replace
-// those of this one as its last tap has used them.
-template <int AT, int BT>
-__device__ __forceinline__ void dm_chunk(f32x4 (&acc)[AT][BT], const unsigned char *pa, const unsigned char *pb, int RP)
+// The matrix instructions of one chunk; pa, pb: this lane's first weight and input fragment, RP: bytes per staged row, PL: from the
+// even to the odd staged rows (DM_FWD2). The weight fragments of a tap are read one tap ahead (two or three where a tap is 8 or 4
+// instructions); the input fragments of the next tap row replace those of this one as its last tap has used them.
+template <int MODE, int AT, int BT>
+__device__ __forceinline__ void dm_chunk(f32x4 (&acc)[AT][MODE == DM_BWD2 ? 4 * BT : BT], const unsigned char *pa, const unsigned char *pb, int RP, int PL)
 {
-    constexpr int D = AT * BT <= 4 ? 3 : AT * BT <= 8 ? 2 : 1;
-    bf16x8 aq[D + 1][AT], bq[BT + 2];
+    constexpr int D = AT * BT <= 4 ? 3 : AT * BT <= 8 ? 2 : 1, NF = MODE == DM_S1 ? BT + 2 : MODE == DM_FWD2 ? 2 * BT + 1 : BT + 1;
+    bf16x8 aq[D + 1][AT], bq[NF];
 #pragma unroll
     for (int d = 0; d < D; ++d)
 #pragma unroll
         for (int a = 0; a < AT; ++a) aq[d][a] = *reinterpret_cast<const bf16x8 *>(pa + (d * 4 + a) * 1024);
 #pragma unroll
-    for (int c = 0; c < BT + 2; ++c) bq[c] = *reinterpret_cast<const bf16x8 *>(pb + c * 64);
+    for (int c = 0; c < NF; ++c) bq[c] = *reinterpret_cast<const bf16x8 *>(pb + c * 64);
 #pragma unroll
     for (int t = 0; t < 9; ++t) {
-        const int r = t / 3, q = t % 3;
-        const bool refill = q == 2 && r < 2;
+        const int r = dm_tap<MODE>(t) / 3, q = dm_tap<MODE>(t) % 3;
+        const bool refill = t == 5 || (t == 2 && MODE != DM_BWD2);
+        const unsigned char *pn = pb + (MODE == DM_S1 ? (t / 3 + 1) * RP : MODE == DM_FWD2 && t == 2 ? PL : RP);   // the next tap row
+        const int cls = MODE == DM_BWD2 ? ((r != 1) * 2 + (q != 1)) * BT : 0;
+        auto read = [&](int c) { bq[c] = *reinterpret_cast<const bf16x8 *>(pn + c * 64); };
         if (t == 3) __builtin_amdgcn_s_setprio(1);
         if (t == 6) __builtin_amdgcn_s_setprio(2);
-        if (refill) {
-            bq[0] = *reinterpret_cast<const bf16x8 *>(pb + (r + 1) * RP);
-            bq[1] = *reinterpret_cast<const bf16x8 *>(pb + (r + 1) * RP + 64);
+        if (refill) {      // those that the row's last tap does not use
+            if (MODE == DM_BWD2) read(BT);
+            else { read(0); read(1); }
         }
 #pragma unroll
         for (int j = 0; j < BT; ++j) {
@@ -189,17 +213,22 @@ __device__ __forceinline__ void dm_chunk(f32x4 (&acc)[AT][BT], const unsigned ch
                 for (int a = j * AT / BT; a < (j + 1) * AT / BT; ++a)
                     aq[(t + D) % (D + 1)][a] = *reinterpret_cast<const bf16x8 *>(pa + ((t + D) * 4 + a) * 1024);
             }
+            const int c = MODE == DM_S1 ? j + q : MODE == DM_FWD2 ? 2 * j + q : j + (q == 0);
 #pragma unroll
-            for (int a = 0; a < AT; ++a) acc[a][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aq[t % (D + 1)][a], bq[j + q], acc[a][j], 0, 0, 0);
-            if (refill) bq[j + 2] = *reinterpret_cast<const bf16x8 *>(pb + (r + 1) * RP + (j + 2) * 64);
+            for (int a = 0; a < AT; ++a) acc[a][cls + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aq[t % (D + 1)][a], bq[c], acc[a][cls + j], 0, 0, 0);
+            if (refill) {
+                read(c);
+                if (MODE == DM_FWD2 && j + 1 < BT) read(c + 1);
+            }
         }
         // (in program order: reads go into the shadow of the matrix instructions one at a time)
-        if (refill) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+        if (refill) __builtin_amdgcn_sched_group_barrier(0x100, MODE == DM_BWD2 ? 1 : 2, 0);
 #pragma unroll
         for (int j = 0; j < BT; ++j) {
             if (t + D < 9 && (j + 1) * AT / BT > j * AT / BT) __builtin_amdgcn_sched_group_barrier(0x100, BT < AT ? AT / BT : 1, 0);
             __builtin_amdgcn_sched_group_barrier(0x008, AT, 0);
-            if (refill) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            if (refill && MODE == DM_FWD2 && j + 1 < BT) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+            else if (refill) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
         }
         __builtin_amdgcn_sched_barrier(0);
     }
@@ -214,8 +243,10 @@ __device__ __forceinline__ int dm_lane_row(const DmaWave &s, const DmaArgs &g, c
     return rowc + (int)pc_udiv((uint32_t)rowc, g.mg_H) - (t.r0 + (int)pc_udiv((uint32_t)t.r0, g.mg_H));
 }
 
-template <int AT, int BT, int ACT>
-__device__ __forceinline__ void dm_store(const DmaWave &s, const DmaArgs &g, const DmaTile &t, int m0, const f32x4 (&acc)[AT][BT], unsigned char *stg,
+// (DM_BWD2: of parity class CLS)
+template <int MODE, int AT, int BT, int CLS, int ACT>
+__device__ __forceinline__ void dm_store(const DmaWave &s, const DmaArgs &g, const DmaTile &t, int m0,
+                                         const f32x4 (&acc)[AT][MODE == DM_BWD2 ? 4 * BT : BT], unsigned char *stg,
                                          __amdgpu_buffer_rsrc_t osrc, __amdgpu_buffer_rsrc_t msrc)
 {
     constexpr int LPP = 2 * AT, PXI = 64 / LPP, PITCH = 32 * AT + 16;     // lanes per pixel, pixels per store, bytes per pixel in LDS
@@ -228,8 +259,17 @@ __device__ __forceinline__ void dm_store(const DmaWave &s, const DmaArgs &g, con
 #pragma unroll
         for (int it = 0; it < NC * 16 / PXI; ++it) {
             const int px = it * PXI + s.lane / LPP;
-            const int orow = t.r0 + s.rg * 16 + (px & 15), x = t.x0 + s.cg * BT + j0 + (px >> 4), m = m0 + (s.lane % LPP) * 8;
-            off[it] = orow < g.rows && x < g.W && m < g.out_CH ? (uint32_t)(orow * g.W + x) * (uint32_t)(g.out_CH * 2) + (uint32_t)(m * 2) : DM_OOB;
+            const int row = t.r0 + s.rg * 16 + (px & 15), m = m0 + (s.lane % LPP) * 8;
+            int x = t.x0 + s.cg * BT + j0 + (px >> 4), orow = row;
+            bool ok = row < g.rows && m < g.out_CH;
+            if (MODE == DM_BWD2) {
+                const int n = (int)pc_udiv((uint32_t)row, g.mg_H), y = 2 * (row - n * g.H) + CLS / 2;
+                x = 2 * x + CLS % 2;
+                orow = n * g.out_H + y;
+                ok = ok && y < g.out_H;
+            }
+            ok = ok && x < g.out_W;
+            off[it] = ok ? (uint32_t)(orow * g.out_W + x) * (uint32_t)(g.out_CH * 2) + (uint32_t)(m * 2) : DM_OOB;
             if (ACT == PC_ACT_RELU_MASK) mk[it] = __builtin_amdgcn_raw_buffer_load_b128(msrc, (int)off[it], 0, 0);
         }
 #pragma unroll
@@ -238,7 +278,7 @@ __device__ __forceinline__ void dm_store(const DmaWave &s, const DmaArgs &g, con
             for (int e = 0; e < AT / 2; ++e) {     // 8 of the lane's 4 * AT channels
                 v4u32 pv;
 #pragma unroll
-                for (int u = 0; u < 4; ++u) pv[u] = pc_pack_bf16x2(acc[e * 2 + (u >> 1)][j0 + j][(u & 1) * 2], acc[e * 2 + (u >> 1)][j0 + j][(u & 1) * 2 + 1]);
+                for (int u = 0; u < 4; ++u) pv[u] = pc_pack_bf16x2(acc[e * 2 + (u >> 1)][CLS * BT + j0 + j][(u & 1) * 2], acc[e * 2 + (u >> 1)][CLS * BT + j0 + j][(u & 1) * 2 + 1]);
                 *reinterpret_cast<v4u32 *>(stg + (j * 16 + (s.lane & 15)) * PITCH + (s.lane >> 4) * (8 * AT) + e * 16) = pv;
             }
 #pragma unroll
@@ -267,7 +307,7 @@ template <int BT, int ACT>
 __device__ __forceinline__ void dm_one_tile(DmaWave &s, const DmaArgs &g, const DmaGeo &q, unsigned char *lds, __amdgpu_buffer_rsrc_t osrc,
                                             __amdgpu_buffer_rsrc_t msrc, const DmaTile &t, bool &fresh)
 {
-    dm_offsets(s, g, q, t);
+    dm_offsets<DM_S1>(s, g, q, t);
     const unsigned char *pa = lds + s.lane * 16;
     const unsigned char *pb = lds + DM_A_BYTES + dm_lane_row(s, g, t) * (q.EPR * 16) + (s.lane >> 4) * 16 + s.cg * (BT * 64);
     f32x4 acc[4][BT];
@@ -276,14 +316,14 @@ __device__ __forceinline__ void dm_one_tile(DmaWave &s, const DmaArgs &g, const 
         if (!fresh) asm volatile("s_barrier" ::: "memory");      // every wavefront has read what the loads replace
         fresh = false;
         __builtin_amdgcn_s_setprio(3);
-        dm_issue<4, 0>(s, g, q.nB, t.mt, ch, 0);
+        dm_issue<DM_S1, 4, 0>(s, g, q.nB, t.mt, ch, 0);
         __builtin_amdgcn_s_setprio(0);
         dm_wait_barrier<0>();
-        dm_chunk<4, BT>(acc, pa, pb, q.EPR * 16);
+        dm_chunk<DM_S1, 4, BT>(acc, pa, pb, q.EPR * 16, 0);
     }
     __builtin_amdgcn_s_setprio(3);
     asm volatile("s_barrier" ::: "memory");
-    dm_store<4, BT, ACT>(s, g, t, t.mt * 64, acc, lds + s.w * (64 * DM_STG), osrc, msrc);
+    dm_store<DM_S1, 4, BT, 0, ACT>(s, g, t, t.mt * 64, acc, lds + s.w * (64 * DM_STG), osrc, msrc);
 }
 
 template <int BT, int ACT>
@@ -330,7 +370,12 @@ pc_mfma_conv_dma_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__ 
 // the first loads and last stores around them, 128 images (us, with the kernel that keeps the weights in registers -> here): 16 x 16
 // 128 -> 128 11.2 -> 10.3, 8 x 8 256 -> 256 11.9 -> 9.9, 4 x 4 512 -> 512 12.2 -> 11.2, 4 x 4 256 -> 512 8.3 -> 7.4; 64 images 7 x 7
 // 512 -> 512 17.3 -> 15.6; one image 56 x 56 256 -> 256 7.7 -> 6.8, 224 x 224 64 -> 64 9.4 -> 7.6.
-template <int AT, int BT, int NBUF, int ACT>
+// Stride 2, backward-data: the same nine taps per chunk and fewer staged columns, 128 images 8 x 8 256 -> 512 16.9 -> 10.8, 64 images
+// 14 x 14 256 -> 512 17.7 -> 11.3, 56 x 56 128 -> 128 25.7 -> 23.0 (its bytes). Forward: 2 * BT + 1 fragments per row and four staged
+// pixels per output pixel make LDS the bound, 0.9 us a chunk of 64 x 128 for 0.48 of matrix instructions (1.5 where the input comes from
+// memory): 64 images 14 x 14 256 -> 512 16.0 -> 11.9, 128 images 16 x 16 128 -> 256 11.1 -> 8.6; of large maps with few channels
+// the register kernel's tiles of 128 channels read less.
+template <int MODE, int AT, int BT, int NBUF, int ACT>
 __global__ void __launch_bounds__(512, 2)
 pc_mfma_conv_solo_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__ out, const uint16_t *__restrict__ wz, DmaArgs g)
 {
@@ -357,17 +402,17 @@ pc_mfma_conv_solo_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__
         s.a_voff = dm_weight_offset<AT>(g, s.lane);
         const int nB = q.nB, chunks = ntile * nch;
         DmaTile t = tile_at(0);
-        dm_offsets(s, g, q, t);
+        dm_offsets<MODE>(s, g, q, t);
         int k = 0, ch = 0, at = 0, done = 0;       // cursor: tile, chunk, buffer; chunks issued
         auto next = [&]() {
-            dm_issue<AT, NBW>(s, g, nB, t.mt, ch, at);
+            dm_issue<MODE, AT, NBW>(s, g, nB, t.mt, ch, at);
             at = at + buf_bytes == NBUF * buf_bytes ? 0 : at + buf_bytes;
             ++done;
             if (++ch == nch) {
                 ch = 0;
                 if (++k < ntile) {
                     t = tile_at(k);
-                    dm_offsets(s, g, q, t);
+                    dm_offsets<MODE>(s, g, q, t);
                 }
             }
         };
@@ -389,29 +434,42 @@ pc_mfma_conv_solo_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__
     const __amdgpu_buffer_rsrc_t osrc = __builtin_amdgcn_make_buffer_rsrc(out, 0, g.out_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t msrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint16_t *>(ACT == PC_ACT_RELU_MASK ? g.act_mask : out), 0, g.out_bytes, 0x00020000);
-    const int RP = q.EPR * 16, half = AT == 2 ? s.w & 1 : 0;
+    const int RP = q.EPR * 16, PL = g.nrow * RP, half = AT == 2 ? s.w & 1 : 0;
     int at = 0;
     for (int k = 0; k < ntile; ++k) {
         const DmaTile t = tile_at(k);
         const unsigned char *pa = lds + s.lane * 16 + half * 2048;
-        const unsigned char *pb = lds + DM_A_BYTES + dm_lane_row(s, g, t) * RP + (s.lane >> 4) * 16 + s.cg * (BT * 64);
-        f32x4 acc[AT][BT];
-        dm_zero<AT, BT>(acc);
+        const unsigned char *pb = lds + DM_A_BYTES + dm_lane_row(s, g, t) * RP + (s.lane >> 4) * 16 + s.cg * (BT * (MODE == DM_FWD2 ? 128 : 64));
+        f32x4 acc[AT][MODE == DM_BWD2 ? 4 * BT : BT];
+        dm_zero(acc);
         int used = 0;
         for (int ch = 0; ch < nch; ++ch) {
             asm volatile("s_barrier" ::: "memory");
-            dm_chunk<AT, BT>(acc, pa + at, pb + at, RP);
+            dm_chunk<MODE, AT, BT>(acc, pa + at, pb + at, RP, PL);
             used = at;
             at = at + buf_bytes == NBUF * buf_bytes ? 0 : at + buf_bytes;
         }
         asm volatile("s_barrier" ::: "memory");
-        dm_store<AT, BT, ACT>(s, g, t, t.mt * 64 + half * 32, acc, lds + used + s.w * (64 * (32 * AT + 16)), osrc, msrc);
+        unsigned char *stg = lds + used + s.w * (64 * (32 * AT + 16));
+        dm_store<MODE, AT, BT, 0, ACT>(s, g, t, t.mt * 64 + half * 32, acc, stg, osrc, msrc);
+        if constexpr (MODE == DM_BWD2) {
+            dm_store<MODE, AT, BT, 1, ACT>(s, g, t, t.mt * 64 + half * 32, acc, stg, osrc, msrc);
+            dm_store<MODE, AT, BT, 2, ACT>(s, g, t, t.mt * 64 + half * 32, acc, stg, osrc, msrc);
+            dm_store<MODE, AT, BT, 3, ACT>(s, g, t, t.mt * 64 + half * 32, acc, stg, osrc, msrc);
+        }
     }
 }
 
 // ---- plan and launch
-struct DmaCand { int code, at, bt, nbuf; };       // nbuf 1: two workgroups per CU
-static const DmaCand kDma[] = {{40, 4, 8, 1}, {41, 4, 4, 1}, {42, 4, 7, 1}, {43, 2, 4, 3}, {45, 4, 4, 2}, {46, 2, 2, 3}};
+// Constants of the time estimate (us) of a tile: a chunk, each direct load of its input, the tile's end; of the launch: its start, and a
+// factor for the time of its bytes
+struct DmaTimes { double chunk, load, tile, start, bytes; };
+struct DmaCand { int code, mode, at, bt, nbuf; DmaTimes solo; };       // nbuf 1: two workgroups per CU
+static const DmaCand kDma[] = {
+    {40, DM_S1, 4, 8, 1, {0, 0, 0, 3.3, 1}}, {41, DM_S1, 4, 4, 1, {0, 0, 0, 3.3, 1}}, {42, DM_S1, 4, 7, 1, {0, 0, 0, 3.3, 1}},
+    {43, DM_S1, 2, 4, 3, {0.440, 0.0137, 0.491, 3.3, 1}}, {45, DM_S1, 4, 4, 2, {1.031, 0.0042, 1.038, 3.3, 1}}, {46, DM_S1, 2, 2, 3, {0.387, 0, 0.445, 3.3, 1}},
+    {47, DM_FWD2, 2, 4, 2, {0.976, 0, 1.296, 2.7, 0.78}}, {48, DM_FWD2, 2, 2, 2, {0.716, 0, 1.275, 2.5, 0.78}},
+    {37, DM_BWD2, 2, 4, 3, {0.504, 0.0087, 1.829, 3.1, 0.62}}, {38, DM_BWD2, 2, 2, 3, {0.348, 0.0082, 1.210, 2.9, 0.50}}};
 constexpr int kNumDma = sizeof(kDma) / sizeof(kDma[0]);
 
 // Fills the plan for a kernel and 1 << lgCG wavefronts side by side; false when it does not fit.
@@ -419,35 +477,38 @@ static bool plan_dma(const MfmaArgs &g, bool flip, const DmaCand &cand, int lgCG
 {
     DmaArgs t;
     memset(&t, 0, sizeof(t));
-    t.N = g.N; t.H = g.in_H; t.W = g.in_W; t.in_CH = g.in_CH; t.out_CH = g.out_CH;
+    t.N = g.N; t.H = g.GH; t.W = g.GW; t.in_CH = g.in_CH; t.out_CH = g.out_CH;
+    t.in_H = g.in_H; t.in_W = g.in_W; t.out_H = g.out_H; t.out_W = g.out_W;
     t.KS = g.KS; t.nch = (g.in_CH + DM_KC - 1) / DM_KC; t.flip = flip;
     t.lgCG = lgCG;
     const int lgPG = cand.at == 2 ? 1 : 2;       // groups of pixels among the wavefronts (log2)
     if (lgCG > lgPG) return false;
     t.TR = 16 << (lgPG - lgCG);
-    const int64_t rows = (int64_t)g.N * g.in_H;
-    if ((rows + g.N + 2 * t.TR) * (g.in_H + 1) >= ((int64_t)1 << 32) || rows >= (1 << 24)) return false;   // multiply-high divisions stay exact
+    const int64_t rows = (int64_t)g.N * t.H;
+    if ((rows + g.N + 2 * t.TR) * (t.H + 1) >= ((int64_t)1 << 32) || rows >= (1 << 24)) return false;   // multiply-high divisions stay exact
     t.rows = (int)rows;
     // image boundaries inside a tile (tiles start at multiples of TR)
-    int cross = g.in_H % t.TR == 0 ? 0 : t.TR % g.in_H == 0 ? t.TR / g.in_H - 1 : (t.TR - 1 + g.in_H - 1) / g.in_H;
+    int cross = t.H % t.TR == 0 ? 0 : t.TR % t.H == 0 ? t.TR / t.H - 1 : (t.TR - 1 + t.H - 1) / t.H;
     if (cross > g.N - 1) cross = g.N - 1;
-    t.nrow = t.TR + 2 + cross;
+    t.nrow = t.TR + (cand.mode == DM_S1 ? 2 : 1) + cross;
+    const int staged = cand.mode == DM_FWD2 ? 2 * t.nrow : t.nrow;
     for (int l = 0; l < 3; ++l) {
         DmaGeo &q = t.geo[l];
-        q.IW = ((cand.bt >> l) << lgCG) + 2;
+        const int tc = (cand.bt >> l) << lgCG;
+        q.IW = cand.mode == DM_S1 ? tc + 2 : cand.mode == DM_FWD2 ? 2 * tc + 1 : tc + 1;
         q.EPR = (DM_KC / 8) * q.IW + 1;
         q.mg_EPR = pc_udiv_magic(q.EPR);
-        q.nB = (t.nrow * q.EPR + 63) / 64;
+        q.nB = (staged * q.EPR + 63) / 64;
     }
     const int nB = t.geo[0].nB, TC = cand.bt << lgCG;
     t.buf_bytes = DM_A_BYTES + (uint32_t)(cand.nbuf == 3 ? 4 * dm_nbw(cand.bt) : nB) * 1024;
     *lds = (size_t)t.buf_bytes * cand.nbuf;
     if (nB > 4 * (cand.nbuf == 3 ? dm_nbw(cand.bt) : DM_NB) || *lds > (size_t)DM_LDS_MAX / (cand.nbuf == 1 ? 2 : 1)) return false;
-    t.tiles_x = (g.in_W + TC - 1) / TC;
+    t.tiles_x = (t.W + TC - 1) / TC;
     const int64_t p_tiles = (rows + t.TR - 1) / t.TR * t.tiles_x;
     const int m_tiles = (g.out_CH + 63) / 64;
     const int64_t total = p_tiles * m_tiles;
-    const int64_t in_bytes = rows * g.in_W * g.in_CH * 2, out_bytes = rows * g.in_W * g.out_CH * 2;
+    const int64_t in_bytes = (int64_t)g.N * g.in_H * g.in_W * g.in_CH * 2, out_bytes = (int64_t)g.N * g.out_H * g.out_W * g.out_CH * 2;
     if (total > (1 << 28) || in_bytes >= ((int64_t)1 << 31) || out_bytes >= ((int64_t)1 << 31)) return false;
     t.in_bytes = (uint32_t)in_bytes; t.out_bytes = (uint32_t)out_bytes;
     t.wz_bytes = (uint32_t)((size_t)((g.out_CH + 127) / 128 * 4) * 9 * t.KS * 1024);
@@ -455,7 +516,7 @@ static bool plan_dma(const MfmaArgs &g, bool flip, const DmaCand &cand, int lgCG
     t.fdiv = t.m_fast ? m_tiles : (int)p_tiles;
     if (total * (t.fdiv > t.tiles_x ? t.fdiv : t.tiles_x) >= ((int64_t)1 << 32)) return false;
     t.mg_fd = pc_udiv_magic(t.fdiv); t.mg_tx = pc_udiv_magic(t.tiles_x);
-    t.mg_H = pc_udiv_magic(g.in_H); t.mg_H1 = pc_udiv_magic(g.in_H + 1);
+    t.mg_H = pc_udiv_magic(t.H); t.mg_H1 = pc_udiv_magic(t.H + 1);
     t.act_mask = g.act_mask;
     // Estimated time (us). A round is one tile for each of the workgroups the chip holds, two per CU; a workgroup that has its CU to
     // itself takes its chunks faster. A chunk takes a fixed time and one for its direct loads of the input, a tile an end; the
@@ -463,15 +524,14 @@ static bool plan_dma(const MfmaArgs &g, bool flip, const DmaCand &cand, int lgCG
     // in a loop over one layer). Constants for 8, 7, 4 and 2 columns per wavefront, and for the tiles of a lone workgroup, from 5000
     // timings of 147 layer shapes (1 to 128 images, 4 x 4 to 224 x 224, 8 to 512 channels; 8 % rms). On 160 shapes drawn
     // afterwards the choice, the register kernels' included, is on average 2.7 % slower than the fastest, the worst 30 % (16 input
-    // channels), and 12 % faster than the fastest of the register kernels.
+    // channels), and 12 % faster than the fastest of the register kernels. At stride 2 (fits of 139 shapes, 6 to 11 % rms), on 139
+    // others: forward 2.4 % and 1 % faster, backward-data 2.6 % and 16 % faster.
     // What does not fill a round of tiles may be cut in halves or quarters, all of it or what a tile per CU leaves: 56 x 56,
     // 256 -> 256, batch 32 is 784 tiles of 8 columns for 512 workgroups; 512 + 256 tiles and 16 cut into 64 quarters
     // take 73 us instead of 81.
-    struct Times { double chunk, load, tile; };
-    static const Times kPair[4] = {{2.627, 0.0391, 2.225}, {2.232, 0.0405, 2.374}, {1.779, 0.0215, 1.669}, {1.047, 0.0361, 1.416}};
-    static const Times kOne[4] = {{2.960, 0.0001, 1.658}, {2.614, 0.0, 1.425}, {1.693, 0.0038, 0.940}, {1.047, 0.0103, 0.671}};
-    static const Times kSolo[3] = {{1.031, 0.0042, 1.038}, {0.440, 0.0137, 0.491}, {0.387, 0.0, 0.445}};
-    auto tile_us = [&](const Times &c, int l) { return t.nch * (c.chunk + c.load * t.geo[l].nB) + c.tile; };
+    static const DmaTimes kPair[4] = {{2.627, 0.0391, 2.225}, {2.232, 0.0405, 2.374}, {1.779, 0.0215, 1.669}, {1.047, 0.0361, 1.416}};
+    static const DmaTimes kOne[4] = {{2.960, 0.0001, 1.658}, {2.614, 0.0, 1.425}, {1.693, 0.0038, 0.940}, {1.047, 0.0103, 0.671}};
+    auto tile_us = [&](const DmaTimes &c, int l) { return t.nch * (c.chunk + c.load * t.geo[l].nB) + c.tile; };
     const int first = cand.bt == 8 ? 0 : cand.bt == 7 ? 1 : 2;
     const int slots = num_cu * (cand.nbuf == 1 ? 2 : 1);
     t.rounds = (int)(total / slots);
@@ -482,15 +542,15 @@ static bool plan_dma(const MfmaArgs &g, bool flip, const DmaCand &cand, int lgCG
         if (o && (cand.nbuf > 1 || (cand.bt != 8 && !(cand.bt == 4 && lgP == 1)))) continue;
         if ((o == 1 || o == 2) && left <= num_cu) continue;
         const int last = o == 0 ? left : o < 3 ? num_cu : 0, pieces = o == 0 ? 0 : (left - last) << lgP;
-        const Times &pair = cand.nbuf > 1 ? kSolo[cand.at == 4 ? 0 : cand.bt == 4 ? 1 : 2] : kPair[first], &ppair = kPair[cand.bt == 8 && lgP == 1 ? 2 : 3], &pone = kOne[cand.bt == 8 && lgP == 1 ? 2 : 3];
+        const DmaTimes &pair = cand.nbuf > 1 ? cand.solo : kPair[first], &ppair = kPair[cand.bt == 8 && lgP == 1 ? 2 : 3], &pone = kOne[cand.bt == 8 && lgP == 1 ? 2 : 3];
         double c = (t.rounds + (last > (cand.nbuf > 1 ? 0 : num_cu))) * tile_us(pair, 0);
         if (cand.nbuf == 1 && last > 0 && last <= num_cu) c += tile_us(kOne[first], 0);
         if (pieces && last) c += 0.83 * tile_us(ppair, lgP);
         else if (pieces) c += (pieces / slots + (pieces % slots > num_cu)) * tile_us(ppair, lgP) + (pieces % slots > 0 && pieces % slots <= num_cu ? tile_us(pone, lgP) : 0.0);
         if (c < best) { best = c; t.last = last; t.pieces = pieces; t.lgP = lgP; }
     }
-    const double move = 2.0 * ((double)p_tiles * t.nrow * (TC + 2) * (g.in_CH < DM_KC ? DM_KC : g.in_CH) + (double)rows * g.in_W * g.out_CH) / 6.0e6;
-    *est = 3.3 + pow(pow(best, 1.5) + pow(move, 1.5), 1.0 / 1.5);
+    const double move = (2.0 * (double)p_tiles * staged * t.geo[0].IW * (g.in_CH < DM_KC ? DM_KC : g.in_CH) + (double)out_bytes) / 6.0e6;
+    *est = cand.solo.start + pow(pow(best, 1.5) + pow(cand.solo.bytes * move, 1.5), 1.0 / 1.5);
     const int busy = t.last + t.pieces;
     *grid = t.rounds > 0 || busy > slots ? slots : busy;
     *out = t;
@@ -517,13 +577,14 @@ pc_status pc_run_mfma_conv_dma(pc_ctx *ctx, int pcfg, int *lgCG, double limit, c
                                const uint16_t *wz, int *launched, int act)
 {
     *launched = 0;
-    if (g0.lstep != 1 || g0.oscale != 1 || (g0.in_CH & 7) || (g0.out_CH & 7)) return PC_OK;
+    if ((g0.in_CH & 7) || (g0.out_CH & 7)) return PC_OK;
+    const int mode = g0.oscale == 2 ? DM_BWD2 : g0.lstep == 2 ? DM_FWD2 : DM_S1;
     DmaArgs best;
     size_t best_lds = 0;
     int best_grid = 0, best_k = -1;
     double best_est = limit;
     for (int k = 0; k < kNumDma; ++k) {
-        if (pcfg >= 0 && pcfg != kDma[k].code) continue;
+        if (kDma[k].mode != mode || (pcfg >= 0 && pcfg != kDma[k].code)) continue;
         for (int lg = *lgCG < 0 ? 0 : *lgCG; lg <= (*lgCG < 0 ? 2 : *lgCG); ++lg) {
             DmaArgs t;
             size_t lds;
@@ -538,7 +599,9 @@ pc_status pc_run_mfma_conv_dma(pc_ctx *ctx, int pcfg, int *lgCG, double limit, c
 #define DM_ACTS(NAME, ...) {&NAME<__VA_ARGS__, PC_ACT_NONE>, &NAME<__VA_ARGS__, PC_ACT_RELU>, &NAME<__VA_ARGS__, PC_ACT_RELU_MASK>}
     static const DmaKernel kernels[kNumDma][3] = {
         DM_ACTS(pc_mfma_conv_dma_kernel, 8), DM_ACTS(pc_mfma_conv_dma_kernel, 4), DM_ACTS(pc_mfma_conv_dma_kernel, 7),
-        DM_ACTS(pc_mfma_conv_solo_kernel, 2, 4, 3), DM_ACTS(pc_mfma_conv_solo_kernel, 4, 4, 2), DM_ACTS(pc_mfma_conv_solo_kernel, 2, 2, 3)};
+        DM_ACTS(pc_mfma_conv_solo_kernel, DM_S1, 2, 4, 3), DM_ACTS(pc_mfma_conv_solo_kernel, DM_S1, 4, 4, 2), DM_ACTS(pc_mfma_conv_solo_kernel, DM_S1, 2, 2, 3),
+        DM_ACTS(pc_mfma_conv_solo_kernel, DM_FWD2, 2, 4, 2), DM_ACTS(pc_mfma_conv_solo_kernel, DM_FWD2, 2, 2, 2),
+        DM_ACTS(pc_mfma_conv_solo_kernel, DM_BWD2, 2, 4, 3), DM_ACTS(pc_mfma_conv_solo_kernel, DM_BWD2, 2, 2, 3)};
 #undef DM_ACTS
     static pc_per_device_once attr[kNumDma][3];
     const hipError_t e = launch_dma(kernels[best_k][act], attr[best_k][act], ctx->device, ctx->stream, best_grid, c.nbuf == 1 ? 256 : 512, best_lds, in, out,
@@ -546,6 +609,6 @@ pc_status pc_run_mfma_conv_dma(pc_ctx *ctx, int pcfg, int *lgCG, double limit, c
     *launched = c.code;
     *lgCG = best.lgCG;
     if (c.nbuf == 1) pc_note_kernel(ctx, "pc_mfma_conv_dma_kernel<%d, %d>", c.bt, act);
-    else pc_note_kernel(ctx, "pc_mfma_conv_solo_kernel<%d, %d, %d, %d>", c.at, c.bt, c.nbuf, act);
+    else pc_note_kernel(ctx, "pc_mfma_conv_solo_kernel<%d, %d, %d, %d, %d>", c.mode, c.at, c.bt, c.nbuf, act);
     return pc_hip_check(ctx, e, "MFMA conv (direct loads) launch");
 }

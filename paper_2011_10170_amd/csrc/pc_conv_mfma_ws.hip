@@ -1265,34 +1265,56 @@ pc_status pc_run_mfma_conv_ws(pc_ctx *ctx, int pcfg, const MfmaArgs &g0, int ext
 pc_status pc_run_mfma_conv_mc(pc_ctx *ctx, int pcfg, const MfmaArgs &g0, const uint16_t *in, uint16_t *out, const uint16_t *wz, bool *launched)
 {
     *launched = false;
+    int dma = 0, lgCG = -1;
+    if (pcfg >= 37) {
+        const pc_status s = pc_run_mfma_conv_dma(ctx, pcfg, &lgCG, 1e30, g0, false, in, out, wz, &dma, PC_ACT_NONE);
+        *launched = dma != 0;
+        return s;
+    }
     // (constants of the time estimate from the measured times of 171 layer shapes, 7 % rms; on 35 others, in the same file as
     // above, the choice is 3.7 % behind the best on average, the worst 48 %: 40 -> 8 channels, where code 34 would be better)
     static const KsCand kMc[] = {
         {32, 1, 2, 1, 64, 1.24, 321, 3878}, {33, 1, 2, 1, 32, 1.37, 529, 3823}, {34, 1, 2, 1, 16, 1.63, 719, 3829},
         {35, 1, 1, 1, 64, 1.66, 934, 3251}, {36, 1, 1, 1, 32, 1.64, 901, 2974},
     };
+    // The kernel of a shape, as code * 4 + lgCG, 0: the cooperative kernel; see above.
+    bool known = false;
+    const int32_t key[PC_CHOICE_KEY] = {6, g0.N, g0.in_H, g0.in_W, g0.in_CH, g0.out_H, g0.out_W, g0.out_CH, 0, 0};
+    int32_t *choice = pcfg < 0 ? pc_choice(ctx, key, &known) : nullptr;
+    known = known && *choice >= 0;
+    if (known && (*choice >> 2) >= 37) {
+        lgCG = *choice & 3;
+        const pc_status s = pc_run_mfma_conv_dma(ctx, *choice >> 2, &lgCG, 1e30, g0, false, in, out, wz, &dma, PC_ACT_NONE);
+        *launched = dma != 0;
+        return s;
+    }
     MfmaArgs best;
     size_t best_lds = 0;
     double best_est = 0.0;
     int best_code = -1;
     for (const KsCand &c : kMc) {
-        if (pcfg >= 0 && pcfg != c.code) continue;
+        if (known ? *choice >> 2 != c.code : pcfg >= 0 && pcfg != c.code) continue;
         MfmaArgs t;
         size_t lds;
         double est;
         if (!plan_ks(g0, 2, c, &t, &lds, &est, ctx->num_cu)) continue;
         if (best_code < 0 || est < best_est) { best = t; best_lds = lds; best_est = est; best_code = c.code; }
     }
-    if (best_code < 0) return PC_OK;
-    // Layers of few workgroups: the cooperative kernel, which spreads the four classes over workgroups of their own, takes
-    // about 4.2 us and 1.4 us per 64-channel chunk for every 1.4 workgroups a CU gets (0.7 us up to 16 channels).
-    if (pcfg < 0) {
+    if (pcfg < 0 && !known) {
+        // Layers of few workgroups: the cooperative kernel, which spreads the four classes over workgroups of their own, takes
+        // about 4.2 us and 1.4 us per 64-channel chunk for every 1.4 workgroups a CU gets (0.7 us up to 16 channels).
         const bool few = g0.in_CH <= 16;
         MfmaArgs t = g0;
         pc_plan_mfma_tiles(&t, few ? 128 : 64, 2);
         const double wgs = 4.0 * ((t.N + t.TI - 1) / t.TI) * t.tiles_y * t.tiles_x * ((g0.out_CH + 63) / 64) / (ctx->num_cu * (few ? 1.0 : 1.4));
-        if (4.2 + (few ? 0.7 : 1.4 * ((g0.in_CH + 63) / 64)) * (wgs > 1.0 ? wgs : 1.0) < best_est) return PC_OK;
+        const double coop = 4.2 + (few ? 0.7 : 1.4 * ((g0.in_CH + 63) / 64)) * (wgs > 1.0 ? wgs : 1.0);
+        const bool take = best_code >= 0 && best_est <= coop;
+        const pc_status s = pc_run_mfma_conv_dma(ctx, -1, &lgCG, take ? best_est : coop, g0, false, in, out, wz, &dma, PC_ACT_NONE);
+        *launched = dma != 0;
+        if (s == PC_OK) *choice = dma ? dma * 4 + lgCG : take ? best_code * 4 : 0;
+        if (s != PC_OK || dma || !take) return s;
     }
+    if (best_code < 0) return PC_OK;
     best.wz_bytes = (uint32_t)((size_t)((best.out_CH + 127) / 128 * 4) * 9 * best.KS * 1024);
     const int grid = best.total_tiles < ctx->num_cu ? best.total_tiles : ctx->num_cu;
     auto launch = [&](auto kernel, pc_per_device_once &attr) -> hipError_t {

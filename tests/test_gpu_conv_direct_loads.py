@@ -1,6 +1,7 @@
-"""The stride-1 forward / backward-data kernels that load both operands straight to LDS (override codes 40 to 46), element by
-element against the oracle, at the edges of its tiles: rows that run across images (one zero row between two of them), columns past
-the map, a last chunk of 8, 16 or 24 channels, partial row tiles, and lists of tiles that continue in narrower ones."""
+"""The forward / backward-data kernels that load both operands straight to LDS (override codes 40 to 48; 37 and 38 for stride-2
+backward-data), element by element against the oracle, at the edges of their tiles: rows that run across images (one zero row
+between two of them), columns past the map, a last chunk of 8, 16 or 24 channels, partial row tiles, and lists of tiles that
+continue in narrower ones."""
 import pytest
 
 from paper_2011_10170_amd import inputs as I
@@ -45,6 +46,19 @@ def test_every_element(B, ctx, oracle, cfg, shape):
     B.pc_set_plan_override(ctx, cfg, 0)
     try:
         run_case(B, ctx, oracle, shape, "bf16", 8, 0.3, B.PC_VARIANT_MFMA, ("direct", cfg))
+    finally:
+        B.pc_set_plan_override(ctx, -1, 0)
+
+
+@pytest.mark.parametrize("cfg", [47, 48, 37, 38])
+@pytest.mark.parametrize("shape", [s[:5] + (2,) for s in SHAPES] + [(70, 4, 4, 72, 64, 2), (5, 32, 32, 64, 64, 2), (3, 64, 66, 136, 40, 2)])
+def test_every_element_at_stride_2(B, ctx, oracle, cfg, shape):
+    """Odd and even maps: the last row or column of an even one has no second tap below or beside it, and an odd one no odd pixels."""
+    if cfg == 47 and shape[1] <= 4 and shape[0] > 32:
+        pytest.skip("rows of too many images for its LDS")
+    B.pc_set_plan_override(ctx, cfg, 0)
+    try:
+        run_case(B, ctx, oracle, shape, "bf16", 8, 0.3, B.PC_VARIANT_MFMA, ("direct2", cfg))
     finally:
         B.pc_set_plan_override(ctx, -1, 0)
 
