@@ -62,6 +62,7 @@ struct DmaArgs {
     // The list of tiles: `rounds` whole rounds (a tile for every workgroup), then `last` tiles, one each for the first workgroups, and
     // the remaining tiles cut into 1 << lgP pieces of their columns, one each for the workgroups after those
     int32_t rounds, last, pieces, lgP;
+    int32_t share, apart;            // workgroups that ask an L2 for a row tile's weights ahead, each for its part (0: none do); their distance
     uint32_t in_bytes, out_bytes, wz_bytes, buf_bytes;
     uint32_t mg_fd, mg_tx, mg_H, mg_H1;
     DmaGeo geo[3];                   // whole tiles, halves, quarters
@@ -435,6 +436,20 @@ pc_mfma_conv_solo_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__
     const __amdgpu_buffer_rsrc_t msrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint16_t *>(ACT == PC_ACT_RELU_MASK ? g.act_mask : out), 0, g.out_bytes, 0x00020000);
     const int RP = q.EPR * 16, PL = g.nrow * RP, half = AT == 2 ? s.w & 1 : 0;
+    // Weights come from the last cache or from memory after other layers' work, chunk by chunk, each with that latency and two chunks ahead
+    // at most. These wavefronts wait for the first chunk anyway: together the workgroups of an XCD that share a row tile touch every
+    // 128-byte line of its weights once, so that the chunks come from L2. (In a step of many layers, 128 images 4 x 4 512 -> 512
+    // 15.5 -> 12.2 us, 64 images 7 x 7 512 -> 512 18.2 -> 16.7, stride 2 8 x 8 256 -> 512 15.2 -> 13.6 forward, 16.2 -> 13.2
+    // backward-data. At stride 1 with more input than weights an XCD reads all row tiles and few workgroups share each: 0.2
+    // to 0.5 us slower, not done. The input ahead: 1 us slower.)
+    uint32_t touched[4];
+    const int lines = 18 * g.KS * 8, part = g.share ? (lines + g.share - 1) / g.share : 0, mt0 = tile_at(0).mt;
+    const __amdgpu_buffer_rsrc_t wsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(wz), 0, g.wz_bytes, 0x00020000);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int l = i * 256 + (int)threadIdx.x, line = (b >> 3) / g.apart * part + l;
+        touched[i] = __builtin_amdgcn_raw_buffer_load_b32(wsrc, (int)(l < part && line < lines ? (uint32_t)((mt0 * lines + line) * 128) : DM_OOB), 0, 0);
+    }
     int at = 0;
     for (int k = 0; k < ntile; ++k) {
         const DmaTile t = tile_at(k);
@@ -450,6 +465,8 @@ pc_mfma_conv_solo_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__
             at = at + buf_bytes == NBUF * buf_bytes ? 0 : at + buf_bytes;
         }
         asm volatile("s_barrier" ::: "memory");
+#pragma unroll
+        for (int i = 0; i < 4; ++i) asm volatile("" :: "v"(touched[i]));      // (no earlier: the wait for them stands here)
         unsigned char *stg = lds + used + s.w * (64 * (32 * AT + 16));
         dm_store<MODE, AT, BT, 0, ACT>(s, g, t, t.mt * 64 + half * 32, acc, stg, osrc, msrc);
         if constexpr (MODE == DM_BWD2) {
@@ -553,6 +570,8 @@ static bool plan_dma(const MfmaArgs &g, bool flip, const DmaCand &cand, int lgCG
     *est = cand.solo.start + pow(pow(best, 1.5) + pow(cand.solo.bytes * move, 1.5), 1.0 / 1.5);
     const int busy = t.last + t.pieces;
     *grid = t.rounds > 0 || busy > slots ? slots : busy;
+    t.apart = t.m_fast ? m_tiles : 1;
+    if (*grid % 8 == 0 && (cand.mode != DM_S1 || !t.m_fast)) t.share = *grid / 8 > t.apart ? *grid / 8 / t.apart : 1;
     *out = t;
     return true;
 }
