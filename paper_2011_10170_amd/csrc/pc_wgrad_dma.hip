@@ -16,7 +16,6 @@
 //     covers any TR rows. Rows past the last one are zeros on both sides.
 //   A staged row is its pixels' 128 bytes (64 channels) and a pad, so that the rows a transposing read takes start in different banks.
 #define WD_OOB 0x80000000u
-#define WD_OT (9 * 32 * 64)          // floats of one filter half parked in the epilogue
 
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 
@@ -219,43 +218,27 @@ __device__ __forceinline__ void pc_wgrad_dma_body(const uint16_t *__restrict__ x
         }
     }
     __builtin_amdgcn_s_setprio(3);
-    // Epilogue, one filter half at a time: parked in LDS as out[tap][filter][channel], from where the 4 kept taps of every kept kernel
-    // are gathered and written in compact slot order.
+    // Epilogue: a lane holds all nine taps of its 16 kernels; the 4 kept ones of a kept kernel move down in place and are written in
+    // compact slot order. (Tap by tap from the last: a kept one becomes the first of the kept values and moves the others up.)
     float *pout = a.ksplit > 1 ? partial + (int64_t)bz * a.pstride * 4 : dw;
-    float *ot = reinterpret_cast<float *>(lds);
-    uint32_t info[2][8];
+    uint32_t info[16];
 #pragma unroll
     for (int k = 0; k < 16; ++k) {
-        const int p = threadIdx.x + 256 * (k & 7), f = f0 + (k >> 3) * 32 + (p >> 6), c = c0 + (p & 63);
-        info[k >> 3][k & 7] = f < a.F && c < a.C ? kinfo[(int64_t)f * a.C + c] : 0xFFFFFFFFu;
+        const int f = f0 + fw * 32 + (k >> 3) * 16 + 4 * (lane >> 4) + (k & 3), c = c0 + cw * 32 + ((k >> 2) & 1) * 16 + (lane & 15);
+        info[k] = f < a.F && c < a.C ? kinfo[(int64_t)f * a.C + c] : 0xFFFFFFFFu;
     }
 #pragma unroll
-    for (int fh = 0; fh < 2; ++fh) {
-        __syncthreads();
-        if (fw == fh) {
+    for (int k = 0; k < 16; ++k) {
+        float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-            for (int t = 0; t < 9; ++t)
-#pragma unroll
-                for (int i = 0; i < 16; ++i)      // filter half, channel half, row of the 16 x 16 block
-                    ot[(t * 32 + (i >> 3) * 16 + 4 * (lane >> 4) + (i & 3)) * 64 + cw * 32 + ((i >> 2) & 1) * 16 + (lane & 15)] = acc[t][i >> 3][(i >> 2) & 1][i & 3];
+        for (int t = 8; t >= 0; --t) {
+            const bool kept = info[k] >> t & 1u;
+            o.w = kept ? o.z : o.w;
+            o.z = kept ? o.y : o.z;
+            o.y = kept ? o.x : o.y;
+            o.x = kept ? acc[t][k >> 3][(k >> 2) & 1][k & 3] : o.x;
         }
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            if (info[fh][k] != 0xFFFFFFFFu) {
-                const int p = threadIdx.x + 256 * k;
-                uint32_t m = info[fh][k] & 0x1FFu;
-                const float *ob = ot + (p >> 6) * 64 + (p & 63);
-                float o[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int t = __builtin_ctz(m);
-                    m &= m - 1u;
-                    o[j] = ob[t * (32 * 64)];
-                }
-                *reinterpret_cast<float4 *>(pout + (int64_t)(info[fh][k] >> 9) * 4) = make_float4(o[0], o[1], o[2], o[3]);
-            }
-        }
+        if (info[k] != 0xFFFFFFFFu) *reinterpret_cast<float4 *>(pout + (int64_t)(info[k] >> 9) * 4) = o;
     }
 }
 
@@ -313,7 +296,6 @@ bool pc_wgrad_dma_plan(const pc_ctx *ctx, const pc_conv_desc *d, int64_t nslots,
     *ct = (a.C + 63) / 64;
     *ft = (a.F + 63) / 64;
     *lds = (size_t)a.dy_off + (size_t)a.TR * a.RPd + 128;
-    if (*lds < WD_OT * sizeof(float)) *lds = WD_OT * sizeof(float);
     *out = a;
     return true;
 }
