@@ -2,6 +2,7 @@
 // for the implicit-GEMM formulation, the operand tiles and the MFMA register layout).
 #include "pc_mfma.h"
 #include <math.h>
+#include <type_traits>
 
 // A workgroup of 4 wavefronts owns 64 output channels x 64 columns of 16 rows (fewer columns in the narrower forms). The reduction runs
 // in chunks of 32 input channels: the weights of a chunk (36 KiB) and the input tile with its border are loaded straight into an
@@ -375,7 +376,7 @@ pc_mfma_conv_dma_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__ 
 // 14 x 14 256 -> 512 17.7 -> 11.3, 56 x 56 128 -> 128 25.7 -> 23.0 (its bytes). Forward: 2 * BT + 1 fragments per row and four staged
 // pixels per output pixel make LDS the bound, 0.9 us a chunk of 64 x 128 for 0.48 of matrix instructions (1.5 where the input comes from
 // memory): 64 images 14 x 14 256 -> 512 16.0 -> 11.9, 128 images 16 x 16 128 -> 256 11.1 -> 8.6; of large maps with few channels
-// the register kernel's tiles of 128 channels read less.
+// tiles of 128 channels read less (pc_mfma_conv_ring_kernel below).
 template <int MODE, int AT, int BT, int NBUF, int ACT>
 __global__ void __launch_bounds__(512, 2)
 pc_mfma_conv_solo_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__ out, const uint16_t *__restrict__ wz, DmaArgs g)
@@ -477,6 +478,173 @@ pc_mfma_conv_solo_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__
     }
 }
 
+// The stride-2 forward pass in tiles of 128 output channels x 128 pixels, 8 wavefronts, four of them loading: two input buffers, and the
+// weights, a row of taps at a time, in a ring of three places (72 + 88 KiB: whole chunks of both would not fit twice). A wavefront
+// multiplies 64 channels x 64 pixels, so that a chunk reads 252 KiB of LDS where two tiles of 64 channels read 360, and an input
+// tile is loaded once for 128 channels. 1.56 us a chunk (0.96 of matrix instructions; LDS 1.2 and a wait at every row). 64 images, us,
+// with the best of the other kernels -> here: 56 x 56 64 -> 128 16.1 -> 14.8, 128 -> 128 25.7 -> 23.6, 28 x 28 128 -> 256 12.6 -> 11.7; 11
+// images 52 x 53 232 -> 480 27.6 -> 22.9; fastest of all on 33 of 139 drawn layers.
+#define DR_B 44                      // direct loads of an input tile: 6 and 5 per wavefront in the first two steps of a chunk
+#define DR_W (2 * DR_B * 1024)       // where the ring begins
+#define DR_SLOT (24 * 1024)
+
+template <int ACT>
+__global__ void __launch_bounds__(512, 2)
+pc_mfma_conv_ring_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__ out, const uint16_t *__restrict__ wz, DmaArgs g)
+{
+    extern __shared__ __align__(16) unsigned char lds[];
+    DmaWave s;
+    s.lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    s.w = wave & 3;
+    const int half = s.w & 1;
+    s.cg = (s.w >> 1) & ((1 << g.lgCG) - 1);
+    s.rg = (s.w >> 1) >> g.lgCG;
+    const int G = gridDim.x, b = blockIdx.x;
+    const int vb = (G & 7) == 0 ? (b & 7) * (G >> 3) + (b >> 3) : b;
+    const int vl = (g.last & 7) == 0 ? (b & 7) * (g.last >> 3) + (b >> 3) : b;
+    const int ntile = g.rounds + (b < g.last), nch = g.nch;
+    auto tile_at = [&](int k) { return dm_tile<4>(g, k < g.rounds ? k * G + vb : g.rounds * G + vl, 0); };
+    const DmaGeo &q = g.geo[0];
+
+    if (wave >= 4) {
+        s.xs = dm_rsrc(in, g.in_bytes);
+        s.ws = dm_rsrc(wz, g.wz_bytes);
+        s.a_voff = dm_weight_offset<4>(g, s.lane);
+        const int steps = 3 * nch * ntile;
+        DmaTile tw = tile_at(0);
+        int kw = 0, chw = 0, rw = 0, slot = 0, wdone = 0;      // weights: tile, chunk, row of taps, place, rows issued
+        auto weights = [&]() {
+            int w = s.w;
+            asm volatile("" : "+s"(w));
+#pragma unroll
+            for (int t = 0; t < 3; ++t)
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    dm_load(s.ws, s.a_voff, (((tw.mt * 2 + h) * 18 + rw * 3 + t) * g.KS + chw * 2) * 1024 + w * 64, DR_W + slot + (t * 8 + h * 4 + w) * 1024);
+            slot = slot == 2 * DR_SLOT ? 0 : slot + DR_SLOT;
+            ++wdone;
+            if (++rw == 3) {
+                rw = 0;
+                if (++chw == nch) {
+                    chw = 0;
+                    if (++kw < ntile) tw = tile_at(kw);
+                }
+            }
+        };
+        DmaTile tx = tw;
+        int kx = 0, chx = 0, at = 0;
+        dm_offsets<DM_FWD2>(s, g, q, tx);
+        auto input = [&](auto part) {          // 0: the first 6 loads, 1: the other 5, and on to the next chunk
+            const bool cut = chx == nch - 1 && (g.in_CH & (DM_KC - 1));
+            const uint32_t parts = (uint32_t)(g.in_CH & (DM_KC - 1)) >> 3;
+#pragma unroll
+            for (int i = decltype(part)::value ? 6 : 0; i < (decltype(part)::value ? 11 : 6); ++i) {
+                uint32_t vo = s.voff[i];
+                if (cut) vo = ((s.part >> (2 * i)) & 3u) >= parts ? DM_OOB : vo;
+                dm_load(s.xs, (int)vo, chx * (DM_KC * 2), at + (s.w + 4 * i) * 1024);
+            }
+            if (decltype(part)::value) {
+                at = DR_B * 1024 - at;
+                if (++chx == nch) {
+                    chx = 0;
+                    if (++kx < ntile) {
+                        tx = tile_at(kx);
+                        dm_offsets<DM_FWD2>(s, g, q, tx);
+                    }
+                }
+            }
+        };
+        using first = std::integral_constant<int, 0>;
+        using rest = std::integral_constant<int, 1>;
+        if (steps) {
+            input(first());
+            input(rest());
+            weights();
+            weights();
+        }
+        int newer = 6, r = 0, left = nch;         // newer: loads of the last step, which nothing waits for yet
+        for (int i = 0; i < steps; ++i) {
+            if (newer == 12) dm_wait_barrier<12>();
+            else if (newer == 11) dm_wait_barrier<11>();
+            else if (newer == 6) dm_wait_barrier<6>();
+            else dm_wait_barrier<0>();
+            newer = 0;
+            if (wdone < steps) { weights(); newer = 6; }
+            if (r < 2 && kx < ntile) {
+                if (r == 0) { input(first()); newer += 6; }
+                else { input(rest()); newer += 5; }
+            }
+            if (++r == 3) {
+                r = 0;
+                if (--left == 0) {
+                    left = nch;
+                    asm volatile("s_barrier" ::: "memory");      // (the tile's sums leave through the input buffer of its last chunk)
+                }
+            }
+        }
+        return;
+    }
+    const __amdgpu_buffer_rsrc_t osrc = __builtin_amdgcn_make_buffer_rsrc(out, 0, g.out_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t msrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint16_t *>(ACT == PC_ACT_RELU_MASK ? g.act_mask : out), 0, g.out_bytes, 0x00020000);
+    const int RP = q.EPR * 16, PL = g.nrow * RP;
+    int at = 0, slot = 0;
+    for (int k = 0; k < ntile; ++k) {
+        const DmaTile t = tile_at(k);
+        const unsigned char *pa = lds + DR_W + s.lane * 16 + half * 4096;
+        const unsigned char *pb = lds + dm_lane_row(s, g, t) * RP + (s.lane >> 4) * 16 + s.cg * (4 * 128);
+        f32x4 acc[4][4];
+        dm_zero(acc);
+        int used = 0;
+        for (int ch = 0; ch < nch; ++ch) {
+            bf16x8 aq[2][4], bq[9];
+#pragma unroll
+            for (int r = 0; r < 3; ++r) {
+                asm volatile("s_barrier" ::: "memory");
+                const unsigned char *pw = pa + slot, *pr = pb + at;
+                slot = slot == 2 * DR_SLOT ? 0 : slot + DR_SLOT;
+#pragma unroll
+                for (int a = 0; a < 4; ++a) aq[0][a] = *reinterpret_cast<const bf16x8 *>(pw + a * 1024);
+                if (r == 0) {
+#pragma unroll
+                    for (int c = 0; c < 9; ++c) bq[c] = *reinterpret_cast<const bf16x8 *>(pr + c * 64);
+                }
+                const unsigned char *pn = pr + (r == 0 ? PL : RP);
+#pragma unroll
+                for (int u = 0; u < 3; ++u) {
+                    const bool refill = u == 2 && r < 2;       // (the input is there: the next row's fragments, before its weights)
+                    auto read = [&](int c) { bq[c] = *reinterpret_cast<const bf16x8 *>(pn + c * 64); };
+                    if (refill) { read(0); read(1); }
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        if (u < 2) aq[(u + 1) & 1][j] = *reinterpret_cast<const bf16x8 *>(pw + ((u + 1) * 8 + j) * 1024);
+#pragma unroll
+                        for (int a = 0; a < 4; ++a) acc[a][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aq[u & 1][a], bq[2 * j + u], acc[a][j], 0, 0, 0);
+                        if (refill) {
+                            read(2 * j + 2);
+                            if (j < 3) read(2 * j + 3);
+                        }
+                    }
+                    if (refill) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        if (u < 2) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+                        if (refill && j < 3) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+                        else if (refill) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            used = at;
+            at = DR_B * 1024 - at;
+        }
+        asm volatile("s_barrier" ::: "memory");
+        dm_store<DM_FWD2, 4, 4, 0, ACT>(s, g, t, t.mt * 128 + half * 64, acc, lds + used + s.w * (64 * DM_STG), osrc, msrc);
+    }
+}
+
 // ---- plan and launch
 // Constants of the time estimate (us) of a tile: a chunk, each direct load of its input, the tile's end; of the launch: its start, and a
 // factor for the time of its bytes
@@ -485,7 +653,7 @@ struct DmaCand { int code, mode, at, bt, nbuf; DmaTimes solo; };       // nbuf 1
 static const DmaCand kDma[] = {
     {40, DM_S1, 4, 8, 1, {0, 0, 0, 3.3, 1}}, {41, DM_S1, 4, 4, 1, {0, 0, 0, 3.3, 1}}, {42, DM_S1, 4, 7, 1, {0, 0, 0, 3.3, 1}},
     {43, DM_S1, 2, 4, 3, {0.440, 0.0137, 0.491, 3.3, 1}}, {45, DM_S1, 4, 4, 2, {1.031, 0.0042, 1.038, 3.3, 1}}, {46, DM_S1, 2, 2, 3, {0.387, 0, 0.445, 3.3, 1}},
-    {47, DM_FWD2, 2, 4, 2, {0.976, 0, 1.296, 2.7, 0.78}}, {48, DM_FWD2, 2, 2, 2, {0.716, 0, 1.275, 2.5, 0.78}},
+    {47, DM_FWD2, 2, 4, 2, {0.976, 0, 1.296, 2.7, 0.78}}, {49, DM_FWD2, 8, 4, 2, {1.5, 0, 1.8, 2.6, 0.7}}, {48, DM_FWD2, 2, 2, 2, {0.716, 0, 1.275, 2.5, 0.78}},
     {37, DM_BWD2, 2, 4, 3, {0.504, 0.0087, 1.829, 3.1, 0.62}}, {38, DM_BWD2, 2, 2, 3, {0.348, 0.0082, 1.210, 2.9, 0.50}}};
 constexpr int kNumDma = sizeof(kDma) / sizeof(kDma[0]);
 
@@ -498,7 +666,7 @@ static bool plan_dma(const MfmaArgs &g, bool flip, const DmaCand &cand, int lgCG
     t.in_H = g.in_H; t.in_W = g.in_W; t.out_H = g.out_H; t.out_W = g.out_W;
     t.KS = g.KS; t.nch = (g.in_CH + DM_KC - 1) / DM_KC; t.flip = flip;
     t.lgCG = lgCG;
-    const int lgPG = cand.at == 2 ? 1 : 2;       // groups of pixels among the wavefronts (log2)
+    const int lgPG = cand.at == 4 ? 2 : 1, rows_m = cand.at == 8 ? 128 : 64;       // groups of pixels among the wavefronts (log2)
     if (lgCG > lgPG) return false;
     t.TR = 16 << (lgPG - lgCG);
     const int64_t rows = (int64_t)g.N * t.H;
@@ -518,12 +686,13 @@ static bool plan_dma(const MfmaArgs &g, bool flip, const DmaCand &cand, int lgCG
         q.nB = (staged * q.EPR + 63) / 64;
     }
     const int nB = t.geo[0].nB, TC = cand.bt << lgCG;
-    t.buf_bytes = DM_A_BYTES + (uint32_t)(cand.nbuf == 3 ? 4 * dm_nbw(cand.bt) : nB) * 1024;
+    if (cand.at == 8 && nB > DR_B) return false;
+    t.buf_bytes = cand.at == 8 ? DM_LDS_MAX / 2 : DM_A_BYTES + (uint32_t)(cand.nbuf == 3 ? 4 * dm_nbw(cand.bt) : nB) * 1024;
     *lds = (size_t)t.buf_bytes * cand.nbuf;
     if (nB > 4 * (cand.nbuf == 3 ? dm_nbw(cand.bt) : DM_NB) || *lds > (size_t)DM_LDS_MAX / (cand.nbuf == 1 ? 2 : 1)) return false;
     t.tiles_x = (t.W + TC - 1) / TC;
     const int64_t p_tiles = (rows + t.TR - 1) / t.TR * t.tiles_x;
-    const int m_tiles = (g.out_CH + 63) / 64;
+    const int m_tiles = (g.out_CH + rows_m - 1) / rows_m;
     const int64_t total = p_tiles * m_tiles;
     const int64_t in_bytes = (int64_t)g.N * g.in_H * g.in_W * g.in_CH * 2, out_bytes = (int64_t)g.N * g.out_H * g.out_W * g.out_CH * 2;
     if (total > (1 << 28) || in_bytes >= ((int64_t)1 << 31) || out_bytes >= ((int64_t)1 << 31)) return false;
@@ -541,8 +710,9 @@ static bool plan_dma(const MfmaArgs &g, bool flip, const DmaCand &cand, int lgCG
     // in a loop over one layer). Constants for 8, 7, 4 and 2 columns per wavefront, and for the tiles of a lone workgroup, from 5000
     // timings of 147 layer shapes (1 to 128 images, 4 x 4 to 224 x 224, 8 to 512 channels; 8 % rms). On 160 shapes drawn
     // afterwards the choice, the register kernels' included, is on average 2.7 % slower than the fastest, the worst 30 % (16 input
-    // channels), and 12 % faster than the fastest of the register kernels. At stride 2 (fits of 139 shapes, 6 to 11 % rms), on 139
-    // others: forward 2.4 % and 1 % faster, backward-data 2.6 % and 16 % faster.
+    // channels), and 12 % faster than the fastest of the register kernels. At stride 2 (fits of 139 shapes, 5 to 11 % rms), on 69
+    // others: forward 2 % and 3 % faster, backward-data 3.4 % and 17 % faster (layers of 8 or 16 input channels up to 1.8 times slower
+    // than the best: the cooperative kernel's estimate knows its output channels in blocks of 64 only).
     // What does not fill a round of tiles may be cut in halves or quarters, all of it or what a tile per CU leaves: 56 x 56,
     // 256 -> 256, batch 32 is 784 tiles of 8 columns for 512 workgroups; 512 + 256 tiles and 16 cut into 64 quarters
     // take 73 us instead of 81.
@@ -571,7 +741,7 @@ static bool plan_dma(const MfmaArgs &g, bool flip, const DmaCand &cand, int lgCG
     const int busy = t.last + t.pieces;
     *grid = t.rounds > 0 || busy > slots ? slots : busy;
     t.apart = t.m_fast ? m_tiles : 1;
-    if (*grid % 8 == 0 && (cand.mode != DM_S1 || !t.m_fast)) t.share = *grid / 8 > t.apart ? *grid / 8 / t.apart : 1;
+    if (*grid % 8 == 0 && cand.at != 8 && (cand.mode != DM_S1 || !t.m_fast)) t.share = *grid / 8 > t.apart ? *grid / 8 / t.apart : 1;
     *out = t;
     return true;
 }
@@ -619,7 +789,7 @@ pc_status pc_run_mfma_conv_dma(pc_ctx *ctx, int pcfg, int *lgCG, double limit, c
     static const DmaKernel kernels[kNumDma][3] = {
         DM_ACTS(pc_mfma_conv_dma_kernel, 8), DM_ACTS(pc_mfma_conv_dma_kernel, 4), DM_ACTS(pc_mfma_conv_dma_kernel, 7),
         DM_ACTS(pc_mfma_conv_solo_kernel, DM_S1, 2, 4, 3), DM_ACTS(pc_mfma_conv_solo_kernel, DM_S1, 4, 4, 2), DM_ACTS(pc_mfma_conv_solo_kernel, DM_S1, 2, 2, 3),
-        DM_ACTS(pc_mfma_conv_solo_kernel, DM_FWD2, 2, 4, 2), DM_ACTS(pc_mfma_conv_solo_kernel, DM_FWD2, 2, 2, 2),
+        DM_ACTS(pc_mfma_conv_solo_kernel, DM_FWD2, 2, 4, 2), {&pc_mfma_conv_ring_kernel<PC_ACT_NONE>, &pc_mfma_conv_ring_kernel<PC_ACT_RELU>, &pc_mfma_conv_ring_kernel<PC_ACT_RELU_MASK>}, DM_ACTS(pc_mfma_conv_solo_kernel, DM_FWD2, 2, 2, 2),
         DM_ACTS(pc_mfma_conv_solo_kernel, DM_BWD2, 2, 4, 3), DM_ACTS(pc_mfma_conv_solo_kernel, DM_BWD2, 2, 2, 3)};
 #undef DM_ACTS
     static pc_per_device_once attr[kNumDma][3];
@@ -627,7 +797,8 @@ pc_status pc_run_mfma_conv_dma(pc_ctx *ctx, int pcfg, int *lgCG, double limit, c
                                     wz, best);
     *launched = c.code;
     *lgCG = best.lgCG;
-    if (c.nbuf == 1) pc_note_kernel(ctx, "pc_mfma_conv_dma_kernel<%d, %d>", c.bt, act);
+    if (c.at == 8) pc_note_kernel(ctx, "pc_mfma_conv_ring_kernel<%d>", act);
+    else if (c.nbuf == 1) pc_note_kernel(ctx, "pc_mfma_conv_dma_kernel<%d, %d>", c.bt, act);
     else pc_note_kernel(ctx, "pc_mfma_conv_solo_kernel<%d, %d, %d, %d, %d>", c.mode, c.at, c.bt, c.nbuf, act);
     return pc_hip_check(ctx, e, "MFMA conv (direct loads) launch");
 }

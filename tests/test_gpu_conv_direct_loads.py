@@ -1,4 +1,4 @@
-"""The forward / backward-data kernels that load both operands straight to LDS (override codes 40 to 48; 37 and 38 for stride-2
+"""The forward / backward-data kernels that load both operands straight to LDS (override codes 40 to 49; 37 and 38 for stride-2
 backward-data), element by element against the oracle, at the edges of their tiles: rows that run across images (one zero row
 between two of them), columns past the map, a last chunk of 8, 16 or 24 channels, partial row tiles, and lists of tiles that
 continue in narrower ones."""
@@ -50,17 +50,41 @@ def test_every_element(B, ctx, oracle, cfg, shape):
         B.pc_set_plan_override(ctx, -1, 0)
 
 
-@pytest.mark.parametrize("cfg", [47, 48, 37, 38])
+@pytest.mark.parametrize("cfg", [47, 48, 49, 37, 38])
 @pytest.mark.parametrize("shape", [s[:5] + (2,) for s in SHAPES] + [(70, 4, 4, 72, 64, 2), (5, 32, 32, 64, 64, 2), (3, 64, 66, 136, 40, 2)])
 def test_every_element_at_stride_2(B, ctx, oracle, cfg, shape):
     """Odd and even maps: the last row or column of an even one has no second tap below or beside it, and an odd one no odd pixels."""
-    if cfg == 47 and shape[1] <= 4 and shape[0] > 32:
+    if cfg in (47, 49) and shape[1] <= 4 and shape[0] > 32:
         pytest.skip("rows of too many images for its LDS")
     B.pc_set_plan_override(ctx, cfg, 0)
     try:
         run_case(B, ctx, oracle, shape, "bf16", 8, 0.3, B.PC_VARIANT_MFMA, ("direct2", cfg))
     finally:
         B.pc_set_plan_override(ctx, -1, 0)
+
+
+@pytest.mark.parametrize("cfg", [47, 48, 49])
+@pytest.mark.parametrize("dims", [(20, 56, 56, 104, 200), (48, 33, 31, 32, 264)])
+def test_several_tiles_per_workgroup_at_stride_2(B, ctx, cfg, dims):
+    """The loads run on from tile to tile: against a kernel of the other family; see test_more_tiles_than_workgroups."""
+    import torch
+    from tests._harness import Case, GpuLayer
+    layer = I.Layer(*dims, 2)
+    g = GpuLayer(B, ctx, Case(layer, "bf16", 8, I.kept_per_filter(0.3, layer.C), tag=("direct2", "tiles")))
+    try:
+        out = []
+        for code in (cfg, 30):
+            B.pc_set_plan_override(ctx, code, 0)
+            for fn in (B.pc_conv_fwd, B.pc_conv_fwd_relu):
+                y = torch.full((layer.N, layer.Ho, layer.Wo, layer.F), float("nan"), dtype=torch.bfloat16, device="cuda")
+                fn(ctx, g.desc, g.pk, g.x, y)
+                out.append(y.double())
+        assert torch.equal(out[1], torch.where(out[0] > 0, out[0], torch.zeros_like(out[0])))
+        a, b = out[0], out[2]
+        assert bool((a - b).abs().le(2.0 ** -7 * torch.maximum(a.abs(), b.abs()) + 2.0 ** -12 * b.abs().max()).all())
+    finally:
+        B.pc_set_plan_override(ctx, -1, 0)
+        g.close()
 
 
 @pytest.mark.parametrize("cfg", [41, 42, 43, 45, 46])
