@@ -870,14 +870,35 @@ static pc_status pc_mfma_bwd_weight_dma(pc_ctx *ctx, const pc_conv_desc *d, cons
     size_t lds;
     double tile_us;
     if (!pc_wgrad_dma_plan(ctx, d, nslots, &y.a, &y.gx, &y.gy, &lds, &tile_us)) return PC_OK;
-    // (from about 12 us of work for every place on, two per CU, it is faster than the wave-specialised kernel, below it is not: 60 shapes.
-    // 28 x 28, 512 -> 512, batch 32 99 -> 83 us, 112 x 112, 128 -> 128 105 -> 87, 56 x 56, 128 -> 128, stride 2, batch 64 33 -> 30;
-    // 28 x 28, 128 -> 128, batch 64 24 : 26)
-    if (ctx->plan_cfg != 44 && tile_us * y.gx * y.gy * y.a.n_ktiles < 12.0 * 2 * ctx->num_cu) return PC_OK;
     int ks = 2 * ctx->num_cu / (y.gx * y.gy);
     if (ks > y.a.n_ktiles) ks = y.a.n_ktiles;
     if (ks < 1) ks = 1;
     y.a.ksplit = ks;
+    if (ctx->plan_cfg != 44) {
+        // Either kernel by its estimated time (us): rounds of pixel tiles, rounds of workgroups, the partial planes and whether there are any,
+        // a start. Fitted to 142 layers (12 and 8 % rms); on 138 others the choice is 1.8 % behind the faster of the two on average,
+        // the rule before it (from 12 us of tiles for every place on) 7.7 %. 13 images 33 x 47, 40 -> 72 15.4 -> 13.6, 64 images 7 x 7, 512 -> 512 25.1 -> 23.4; large
+        // layers 28 x 28, 512 -> 512, batch 32 99 -> 82, 56 x 56, 128 -> 128, stride 2, batch 64 33 -> 27.5.
+        const int32_t key[PC_CHOICE_KEY] = {7, d->N, d->H, d->W, d->C, d->F, d->stride, (int32_t)nslots, 0, 0};
+        bool known;
+        int32_t *choice = pc_choice(ctx, key, &known);
+        if (!known || *choice < 0) {
+            const int T = y.gx * y.gy, places = 2 * ctx->num_cu;
+            auto up = [](int p, int q) { return (double)((p + q - 1) / q); };
+            auto planes = [&](int n) { return n > 1 ? 2.9 + 16e-6 * (double)n * (double)nslots : 0.0; };
+            const double own = (0.9 * up(y.a.n_ktiles, ks) * tile_us + 2.5) * up(T * ks, places) + planes(ks) + 2.5;
+            WgradWsArgs a;
+            int ct, ft;
+            size_t l;
+            bool pad_x;
+            int64_t xb;
+            double other = 1e30;
+            if (ws_plan(ctx, d, nslots, &a, &ct, &ft, &l, &pad_x, &xb))
+                other = (1.58 * up(a.n_ktiles, a.ksplit) + 3.6) * up(ct * ft * a.ksplit, ctx->num_cu) + (a.ksplit > 1 ? 0.7 : 0.0) + planes(a.ksplit) + 3.6;
+            *choice = own < other;
+        }
+        if (!*choice) return PC_OK;
+    }
     if (ks > 1) {
         // (twice the other kernel's partial planes: up to 32 MiB)
         void *scr = nullptr;

@@ -90,7 +90,7 @@ def test_capture_without_room_for_the_partial_planes(B):
     from tests._harness import Case, GpuLayer
     stream = torch.cuda.Stream()
     c = B.pc_create(0, stream.cuda_stream)
-    layer = I.Layer(32, 56, 56, 128, 128, 1)
+    layer = I.Layer(64, 56, 56, 128, 128, 2)
     try:
         with torch.cuda.stream(stream):
             g = GpuLayer(B, c, Case(layer, "bf16", 8, I.kept_per_filter(0.5, layer.C), tag=("rows", "capture")))
