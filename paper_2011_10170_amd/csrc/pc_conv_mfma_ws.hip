@@ -36,9 +36,10 @@ constexpr int pc_ring_depth(int nf, int cap)
 // halo tile of the NEXT item (tile, chunk of KC channels) into one of two LDS buffers, their global loads KS_DEPTH
 // items ahead in registers, and execute one workgroup barrier after the first staged item and one per item.
 //   vb, G: index of this workgroup in the tile order and the number of workgroups; ntile_blk tiles of nch chunks each
+//   twice: a second barrier per item (see the end of pc_mfma_conv_ks_kernel)
 template <int KC, int NV>
 __device__ __forceinline__ void pc_ks_loader_role(const uint16_t *__restrict__ in, const MfmaArgs &g, unsigned char *lds, int vb, int G,
-                                                  int ntile_blk, int nch)
+                                                  int ntile_blk, int nch, bool twice = false)
 {
     constexpr int PITCH = 2 * KC + 16;
     constexpr int PARTS = KC / 8;
@@ -115,6 +116,7 @@ __device__ __forceinline__ void pc_ks_loader_role(const uint16_t *__restrict__ i
         put(R, ((i + 1) & 1) * g.xbuf);
         issue(R);
         __syncthreads();
+        if (twice) asm volatile("s_barrier" ::: "memory");
     };
     int i = 0;
     for (; i + 3 <= I; i += 3) {
@@ -242,8 +244,12 @@ pc_mfma_conv_ks_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__ o
     const int nch = g.nchunks;
     const int I = ntile_blk * nch;
 
+    // With one chunk per tile a wavefront that owns no part of a tile is back with the next tile's partial sums before the next barrier:
+    // the owners' reads of the reduction area need one of their own.
+    const bool twice = RED && nch == 1 && ntile_blk > 1;
+
     if (wave >= 4) {
-        pc_ks_loader_role<KC, NV>(in, g, lds, vb, G, ntile_blk, nch);
+        pc_ks_loader_role<KC, NV>(in, g, lds, vb, G, ntile_blk, nch, twice);
         return;
     }
 
@@ -464,6 +470,7 @@ pc_mfma_conv_ks_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__ o
                     }
                 }
             }
+            if (twice) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
         }
         if (ch == nch - 1) {
 #pragma unroll
