@@ -17,7 +17,7 @@
 #define PC_OV_BAD 0xFFFFFFFFu
 
 struct pc_stream_ref;
-#define PC_CHOICES 128
+#define PC_CHOICES 512         // a network of 16 layers has 48 entries
 #define PC_CHOICE_KEY 10
 
 struct pc_ctx {
