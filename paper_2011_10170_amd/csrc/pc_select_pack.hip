@@ -61,7 +61,7 @@ pc_select_score_kernel(const float *__restrict__ W, const float *__restrict__ G,
 // rem-th largest of them joins the prefix. As soon as all keys of that digit are kept the rest of the key does not
 // matter; otherwise, after the last digit, the keys equal to the threshold are kept by index. Counts are integers: the
 // result does not depend on the order of the atomics.
-#define PC_TOPN_WG 16384        // longest layer ranked by one workgroup
+#define PC_TOPN_WG 16384        // longest layer ranked by one workgroup (25600 kernels: 21 us against 16 across workgroups, 65536: 31, 17)
 __device__ __forceinline__ uint32_t pc_order_key(float f)
 {
     const uint32_t b = __float_as_uint(f);
