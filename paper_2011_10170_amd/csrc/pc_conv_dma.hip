@@ -369,7 +369,7 @@ pc_mfma_conv_dma_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__ 
 // channels x two groups of pixels, tiles of 64 x 128 (BT = 4) and 64 x 64 (BT = 2).
 // What bounds it: a chunk of 64 x 256, 128 and 64 pixels takes 1.03, 0.55 and 0.39 us for 0.96, 0.48 and 0.24 us of matrix
 // instructions; below 64 x 128 the direct loads (48 KiB a chunk, of them 36 KiB weights that all row tiles load again). With a launch and
-// the first loads and last stores around them, 128 images (us, with the kernel that keeps the weights in registers -> here): 16 x 16
+// the first loads and last stores around them, 128 images (us, the kernel chosen without this one -> here): 16 x 16
 // 128 -> 128 11.2 -> 10.3, 8 x 8 256 -> 256 11.9 -> 9.9, 4 x 4 512 -> 512 12.2 -> 11.2, 4 x 4 256 -> 512 8.3 -> 7.4; 64 images 7 x 7
 // 512 -> 512 17.3 -> 15.6; one image 56 x 56 256 -> 256 7.7 -> 6.8, 224 x 224 64 -> 64 9.4 -> 7.6.
 // Stride 2, backward-data: the same nine taps per chunk and fewer staged columns, 128 images 8 x 8 256 -> 512 16.9 -> 10.8, 64 images
