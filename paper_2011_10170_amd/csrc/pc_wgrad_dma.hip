@@ -187,7 +187,8 @@ __device__ __forceinline__ void pc_wgrad_dma_body(const uint16_t *__restrict__ x
 #pragma unroll
             for (int X = 0; X <= LAST; ++X) {
                 if (X < IW) {
-                    // (past the tile's last column: the row's pad, the next row or what follows the rows; not used)
+                    // (past the tile's last column, up to three columns on: the row's pad, the next row or the room the plan leaves after
+                    // the last one; not used. The x columns past a row's last one run into the next row, or into dy.)
                     if (X + 1 < 8) read_d(X + 1);
                     if (X == 3) __builtin_amdgcn_s_setprio(1);
                     if (X == 6) __builtin_amdgcn_s_setprio(2);
@@ -276,7 +277,9 @@ bool pc_wgrad_dma_plan(const pc_ctx *ctx, const pc_conv_desc *d, int64_t nslots,
                 const int cross = a.Ho % TR == 0 ? 0 : TR % a.Ho == 0 ? TR / a.Ho - 1 : (TR - 1 + a.Ho - 1) / a.Ho;
                 const int nrow = st * (TR - 1) + 3 + cross * (a.H + 1 - st * a.Ho);
                 const int IW = st * (tcn - 1) + 3, RPx = IW * 128 + (st == 1 ? 32 : 16), RPd = tcn * 128 + pad;
-                if (nrow * RPx + TR * RPd + 128 > WD_LDS_MAX) continue;        // (128: a read of one column past the last row)
+                // columns of dy that are read past the end of a row: three, none past the eighth (stride 1), or the next pair (stride 2)
+                const int past = st == 1 ? (tcn + 3 < 8 ? 3 : 8 - tcn) : tcn < 6 ? 2 : 0, room = past * 128 > pad ? past * 128 - pad : 0;
+                if (nrow * RPx + TR * RPd + room > WD_LDS_MAX) continue;
                 const int tc_n = (a.Wo + tcn - 1) / tcn, tr_n = (int)((rows + TR - 1) / TR);
                 const double fill = (double)rows * a.Wo / ((double)tr_n * TR * tc_n * tcn);
                 const double mfma = TR / 32.0 * tcn * 36 * 16, load = ((double)nrow * IW + (double)TR * tcn) * 128 / 30.0;   // cycles
@@ -285,6 +288,7 @@ bool pc_wgrad_dma_plan(const pc_ctx *ctx, const pc_conv_desc *d, int64_t nslots,
                     best = eff;
                     a.TR = TR; a.TC = tcn; a.IW = IW; a.nrow = nrow; a.RPx = RPx; a.RPd = RPd; a.dy_off = nrow * RPx;
                     a.tiles_c = tc_n; a.n_ktiles = tr_n * tc_n;
+                    *lds = (size_t)(nrow * RPx + TR * RPd + room);
                 }
             }
     if (best < 0.0) return false;
@@ -295,7 +299,6 @@ bool pc_wgrad_dma_plan(const pc_ctx *ctx, const pc_conv_desc *d, int64_t nslots,
     *tile_us = 0.55 * (a.TR / krows) * (a.TC / cstep) + 1.3;
     *ct = (a.C + 63) / 64;
     *ft = (a.F + 63) / 64;
-    *lds = (size_t)a.dy_off + (size_t)a.TR * a.RPd + 128;
     *out = a;
     return true;
 }

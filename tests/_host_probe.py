@@ -1,0 +1,61 @@
+"""Checks of the host side of libpatconv.so that need no GPU: every HIP call goes to tests/_hip_stub.c, so the launches of a call can be
+looked at. Runs as a program of its own (the stub has to be loaded before any HIP library): python -m tests._host_probe STUB CHECK."""
+import ctypes as ct
+import struct
+import sys
+
+stub = ct.CDLL(sys.argv[1], ct.RTLD_GLOBAL)
+
+from paper_2011_10170_amd import binding as B  # noqa: E402
+from paper_2011_10170_amd import inputs as I  # noqa: E402
+
+LIB = I.make_library(8)
+DEV = 1 << 20        # stands for a device address; nothing reads it
+
+
+def watch(name, arg=0, nbytes=0):
+    """The launches of kernels with `name` in their symbol are noted from here on, with the first bytes of one of their arguments."""
+    ct.memmove(ct.addressof(ct.c_char.in_dll(stub, "stub_watch")), name.encode() + b"\0", len(name) + 1)
+    ct.c_int.in_dll(stub, "stub_arg").value = arg
+    ct.c_int.in_dll(stub, "stub_arg_bytes").value = nbytes
+
+
+def seen():
+    n = ct.c_int.in_dll(stub, "stub_arg_bytes").value
+    return (ct.string_at(ct.addressof(ct.c_char.in_dll(stub, "stub_args")), n), ct.c_longlong.in_dll(stub, "stub_grid").value,
+            ct.c_longlong.in_dll(stub, "stub_lds").value)
+
+
+def layer(ctx, shape):
+    N, H, W, C, F, st = shape
+    return B.make_desc(N, H, W, C, F, st, B.PC_BF16), B.pc_pack(ctx, DEV, DEV, DEV, F, C, LIB, B.PC_BF16)
+
+
+def wgrad_lds():
+    """Backward-weight with direct loads: every column that a wavefront reads ahead lies inside the workgroup's LDS."""
+    ctx = B.pc_create(0, None)
+    B.pc_set_plan_override(ctx, 44, 0)
+    tiles = set()
+    for st in (1, 2):
+        for N in (1, 3, 9, 70):
+            for H in (1, 2, 4, 7, 16, 33):
+                for W in (1, 2, 3, 4, 5, 6, 7, 8, 9, 14, 47):
+                    d, pk = layer(ctx, (N, H, W, 64, 64, st))
+                    watch("pc_mfma_wgrad_dma_kernel", 0, 88 + 64)
+                    B.pc_conv_bwd_weight(ctx, d, pk, DEV, DEV, DEV)
+                    arg, _, lds = seen()
+                    TR, TC, IW, nrow, RPx, RPd, dy_off = struct.unpack("<16i", arg[88:])[9:]
+                    tiles.add((st, TC))
+                    # the last column of dy and of x that is asked for, and the bytes of the last staged row up to its end
+                    d_col = min(7, IW) if st == 1 else max([c + 3 for c in (0, 2) if c < TC] + [TC - 1])
+                    x_col = min(9, IW) if st == 1 else max(c + 2 for u in range(8) for c in [4 * (u // 3) + (u % 3 + 1 if u % 3 < 2 else 4)] if 2 * (u // 3) < TC)
+                    assert dy_off + (TR - 1) * RPd + (d_col + 1) * 128 <= lds <= 80 * 1024, (N, H, W, st, TR, TC, lds)
+                    assert (nrow - 1) * RPx + (x_col + 1) * 128 <= lds and nrow * RPx <= dy_off, (N, H, W, st, TR, TC, lds)
+                    B.pc_packed_free(pk)
+    assert len(tiles) >= 9, tiles
+    B.pc_destroy(ctx)
+
+
+if __name__ == "__main__":
+    globals()[sys.argv[2]]()
+    print("ok")

@@ -1,0 +1,26 @@
+"""What the library launches, looked at on the CPU: tests/_host_probe.py over a HIP runtime that notes launches and runs nothing."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+from paper_2011_10170_amd import binding as B
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    if not os.path.exists(B.LIB_PATH):
+        from paper_2011_10170_amd import build
+        build.build()
+    out = str(tmp_path_factory.mktemp("stub") / "hip_stub.so")
+    subprocess.run(["gcc", "-O1", "-Wall", "-shared", "-fPIC", "-I/opt/rocm/include", "-o", out, os.path.join(ROOT, "tests", "_hip_stub.c")], check=True)
+    return out
+
+
+@pytest.mark.parametrize("check", ["wgrad_lds"])
+def test_host_side(stub, check):
+    r = subprocess.run([sys.executable, "-m", "tests._host_probe", stub, check], cwd=ROOT, capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and r.stdout.endswith("ok\n"), r.stdout + r.stderr
