@@ -72,12 +72,16 @@ struct DmaArgs {
 
 // 64 lanes x 16 bytes from a buffer to the 1 KiB of LDS at lds_off; an offset past the buffer's end writes zeros. As inline
 // assembly because the compiler orders every later LDS read behind a direct load it knows of: here the wait is one
-// s_waitcnt in front of a barrier.
+// s_waitcnt in front of a barrier. (The compiler warns that it saves no reserved register for the statement: m0 holds nothing
+// of its own that it would have to.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void dm_load(const v4u32 &rsrc, int voff, int soff, int lds_off)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :: "s"(lds_off), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+                 :: "s"(lds_off), "v"(voff), "s"(rsrc), "s"(soff) : "memory", "m0");
 }
+#pragma clang diagnostic pop
 
 // All but the last N vector memory operations of this wavefront are complete, and every wavefront has come here.
 template <int N> __device__ __forceinline__ void dm_wait_barrier()

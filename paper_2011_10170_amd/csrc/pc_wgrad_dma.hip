@@ -19,13 +19,16 @@
 
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 
-// Lanes of mask x 16 bytes from a buffer to LDS at lds_off + 16 * lane; an offset past the buffer's end writes zeros. All lanes are
-// active before and after.
+// Lanes of mask x 16 bytes from a buffer to LDS at lds_off + 16 * lane; an offset past the buffer's end writes zeros. Only where all
+// lanes are active: exec is as it was afterwards. (m0: see dm_load.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void wd_load(const v4u32 &rsrc, uint32_t voff, int soff, int lds_off, uint64_t mask)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_mov_b64 exec, %4\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds\n\ts_mov_b64 exec, -1"
-                 :: "s"(lds_off), "v"(voff), "s"(rsrc), "s"(soff), "s"(mask) : "memory");
+                 :: "s"(lds_off), "v"(voff), "s"(rsrc), "s"(soff), "s"(mask) : "memory", "m0");
 }
+#pragma clang diagnostic pop
 
 // A launch argument that stays in its register: the compiler would read it again from memory wherever it is used.
 __device__ __forceinline__ int wd_keep(int v)
