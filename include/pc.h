@@ -24,6 +24,9 @@
  *     Activations are NHWC: x, dx [N][H][W][C]; y, dy [N][Ho][Wo][F]; Ho = (H-1)/stride + 1,
  *     Wo likewise (3x3 window, zero padding 1, stride 1 or 2). Their element type is
  *     desc.dtype: float32, or bfloat16 with float32 accumulation.
+ *   - Activations need the alignment of their element type. Some kernels of the bf16 passes (those with direct loads below) take
+ *     tensors whose address is a multiple of 16 only, as every allocation's is; others go to the kernels that load through
+ *     registers.
  *   - Non-finite inputs give unspecified results, except in the passes of float32 layers: there an infinite or NaN element
  *     reaches exactly the sums of the formulas below that it is a term of (kept taps, inside the maps; the gather kernels
  *     may multiply it with a zero around a map as well). In bf16 layers it may reach the sums it would be a pruned term of.

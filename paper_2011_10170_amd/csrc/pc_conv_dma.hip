@@ -770,7 +770,7 @@ pc_status pc_run_mfma_conv_dma(pc_ctx *ctx, int pcfg, int *lgCG, double limit, c
                                const uint16_t *wz, int *launched, int act)
 {
     *launched = 0;
-    if ((g0.in_CH & 7) || (g0.out_CH & 7)) return PC_OK;
+    if ((g0.in_CH & 7) || (g0.out_CH & 7) || !pc_direct_loads(in)) return PC_OK;
     const int mode = g0.oscale == 2 ? DM_BWD2 : g0.lstep == 2 ? DM_FWD2 : DM_S1;
     DmaArgs best;
     size_t best_lds = 0;

@@ -1198,10 +1198,10 @@ pc_status pc_run_mfma_conv_ws(pc_ctx *ctx, int pcfg, const MfmaArgs &g0, int ext
     for (int t = 0; t < 9; ++t)
         if (g0.tap_w[t] != t || tr[t] != (tr[0] ? 2 - t / 3 : t / 3) || tc[t] != (tc[0] ? 2 - t % 3 : t % 3)) return PC_OK;
     // The kernel of a shape, as code * 4 + lgCG: the estimates of all candidates take 2 us of host time, more than a small
-    // layer's launch (9 x 38 x 41, 56 -> 64: 6.0 us a call with them, 4.7 without).
+    // layer's launch (9 x 38 x 41, 56 -> 64: 6.0 us a call with them, 4.7 without). It is that of tensors that direct loads can take.
     bool known = false;
     const int32_t key[PC_CHOICE_KEY] = {5, g0.N, g0.in_H, g0.in_W, g0.in_CH, g0.out_CH, g0.GH, g0.GW, g0.lstep * 16 + g0.oscale, ext * 2 + (tr[0] != 0)};
-    int32_t *choice = pcfg < 0 ? pc_choice(ctx, key, &known) : nullptr;
+    int32_t *choice = pcfg < 0 && pc_direct_loads(in) ? pc_choice(ctx, key, &known) : nullptr;
     known = known && *choice >= 0;
     if (known && (*choice >> 2) >= 40) {
         lgCG = *choice & 3;
@@ -1221,7 +1221,7 @@ pc_status pc_run_mfma_conv_ws(pc_ctx *ctx, int pcfg, const MfmaArgs &g0, int ext
         if (!plan_ks(g0, ext, kKs[k], &t, &lds, &est, ctx->num_cu)) continue;
         if (best_k < 0 || est < best_est) { best = t; best_lds = lds; best_est = est; best_k = k; }
     }
-    if (pcfg < 0 && !known) {
+    if (choice && !known) {
         const pc_status s = pc_run_mfma_conv_dma(ctx, -1, &lgCG, best_k < 0 ? 1e30 : best_est, g0, tr[0] != 0, in, out, wz, &dma, act);
         *launched = dma != 0;
         if (s == PC_OK) *choice = dma ? dma * 4 + lgCG : best_k < 0 ? 0 : kKs[best_k].code * 4;
@@ -1287,7 +1287,7 @@ pc_status pc_run_mfma_conv_mc(pc_ctx *ctx, int pcfg, const MfmaArgs &g0, const u
     // The kernel of a shape, as code * 4 + lgCG, 0: the cooperative kernel; see above.
     bool known = false;
     const int32_t key[PC_CHOICE_KEY] = {6, g0.N, g0.in_H, g0.in_W, g0.in_CH, g0.out_H, g0.out_W, g0.out_CH, 0, 0};
-    int32_t *choice = pcfg < 0 ? pc_choice(ctx, key, &known) : nullptr;
+    int32_t *choice = pcfg < 0 && pc_direct_loads(in) ? pc_choice(ctx, key, &known) : nullptr;
     known = known && *choice >= 0;
     if (known && (*choice >> 2) >= 37) {
         lgCG = *choice & 3;
@@ -1318,7 +1318,7 @@ pc_status pc_run_mfma_conv_mc(pc_ctx *ctx, int pcfg, const MfmaArgs &g0, const u
         const bool take = best_code >= 0 && best_est <= coop;
         const pc_status s = pc_run_mfma_conv_dma(ctx, -1, &lgCG, take ? best_est : coop, g0, false, in, out, wz, &dma, PC_ACT_NONE);
         *launched = dma != 0;
-        if (s == PC_OK) *choice = dma ? dma * 4 + lgCG : take ? best_code * 4 : 0;
+        if (s == PC_OK && choice) *choice = dma ? dma * 4 + lgCG : take ? best_code * 4 : 0;
         if (s != PC_OK || dma || !take) return s;
     }
     if (best_code < 0) return PC_OK;

@@ -75,6 +75,10 @@ struct SparseOperand {
     const uint32_t *ov_col;
 };
 
+// Whether a tensor can be brought to LDS by direct loads, which take 16-byte elements. The kernels that load through registers take any
+// address that the element type may have.
+inline bool pc_direct_loads(const void *p) { return ((uintptr_t)p & 15) == 0; }
+
 // Wave-specialised forward/backward-data kernel for full 3x3 tap lists. pcfg: -1 = take it when the plan says it
 // wins, >= 7 = the forced variant. *launched stays false when the launch is left to the cooperative kernel.
 pc_status pc_run_mfma_conv_ws(pc_ctx *ctx, int pcfg, const MfmaArgs &g0, int ext, const int *tr, const int *tc,

@@ -869,7 +869,7 @@ static pc_status pc_mfma_bwd_weight_dma(pc_ctx *ctx, const pc_conv_desc *d, cons
     WgradDmaLayer &y = g.layer[0];
     size_t lds;
     double tile_us;
-    if (!pc_wgrad_dma_plan(ctx, d, nslots, &y.a, &y.gx, &y.gy, &lds, &tile_us)) return PC_OK;
+    if (!pc_direct_loads(x) || !pc_direct_loads(dy) || !pc_wgrad_dma_plan(ctx, d, nslots, &y.a, &y.gx, &y.gy, &lds, &tile_us)) return PC_OK;
     int ks = 2 * ctx->num_cu / (y.gx * y.gy);
     if (ks > y.a.n_ktiles) ks = y.a.n_ktiles;
     if (ks < 1) ks = 1;
@@ -1068,7 +1068,8 @@ pc_status pc_mfma_bwd_weight_group(pc_ctx *ctx, int n, const pc_conv_desc *d, co
             it.l = l;
             it.nslots = nslots;
             it.pad_x = false;
-            it.dma = dma && pc_wgrad_dma_plan(ctx, &d[l], nslots, &it.q, &it.ct, &it.ft, &it.lds, &it.tile_us);
+            it.dma = dma && pc_direct_loads(x[l]) && pc_direct_loads(dy[l]) &&
+                     pc_wgrad_dma_plan(ctx, &d[l], nslots, &it.q, &it.ct, &it.ft, &it.lds, &it.tile_us);
             if (it.dma) {
                 it.n_ktiles = it.q.n_ktiles;
                 it.ksplit = std::max(1, std::min(2 * ctx->num_cu / (it.ct * it.ft), it.n_ktiles));
@@ -1102,7 +1103,7 @@ pc_status pc_mfma_bwd_weight_group(pc_ctx *ctx, int n, const pc_conv_desc *d, co
     if (ctx->plan_cfg < 0) {
         uint64_t h = 1469598103934665603ull;
         for (int l = 0; l < n; ++l)
-            for (int v : {(int)d[l].N, (int)d[l].H, (int)d[l].W, (int)d[l].C, (int)d[l].F, (int)d[l].stride}) h = (h ^ (uint32_t)v) * 1099511628211ull;
+            for (int v : {(int)d[l].N, (int)d[l].H, (int)d[l].W, (int)d[l].C, (int)d[l].F, (int)d[l].stride * 2 + (pc_direct_loads(x[l]) && pc_direct_loads(dy[l]))}) h = (h ^ (uint32_t)v) * 1099511628211ull;
         const int32_t key[PC_CHOICE_KEY] = {4, n, (int32_t)h, (int32_t)(h >> 32), d[0].N, d[0].H, d[n - 1].H, d[n - 1].F, 0, 0};
         bool hit;
         int32_t *choice = pc_choice(ctx, key, &hit);

@@ -56,6 +56,37 @@ def wgrad_lds():
     B.pc_destroy(ctx)
 
 
+def alignment():
+    """Tensors whose address is no multiple of 16 go to the kernels that load through registers, before and after an aligned call of the
+    same sizes, and back."""
+    ctx = B.pc_create(0, None)
+    direct = 0
+    for shape in [(9, 38, 41, 56, 64, 1), (32, 112, 112, 128, 128, 1), (64, 7, 7, 512, 512, 1), (64, 56, 56, 128, 128, 2), (64, 14, 14, 256, 512, 2), (13, 33, 47, 40, 72, 1)]:
+        d, pk = layer(ctx, shape)
+        calls = [lambda a: B.pc_conv_fwd(ctx, d, pk, a, DEV), lambda a: B.pc_conv_bwd_data(ctx, d, pk, a, DEV), lambda a: B.pc_conv_bwd_data_relu(ctx, d, pk, a, DEV, DEV),
+                 lambda a: B.pc_conv_bwd_weight(ctx, d, pk, a, DEV, DEV), lambda a: B.pc_conv_bwd_weight(ctx, d, pk, DEV, a, DEV),
+                 lambda a: B.pc_conv_bwd_weight_batch(ctx, [d], [pk], [a], [DEV], [DEV]), lambda a: B.pc_conv_bwd_weight_batch(ctx, [d], [pk], [DEV], [a], [DEV])]
+        for call in calls:
+            names = []
+            for off in (2, 0, 8, 0):
+                call(DEV + off)
+                names.append(B.pc_last_kernel(ctx))
+            is_direct = [any(k in n for k in ("conv_dma", "conv_solo", "conv_ring", "wgrad_dma")) for n in names]
+            assert not is_direct[0] and not is_direct[2] and names[0] == names[2] and names[1] == names[3], (shape, names)
+            direct += is_direct[1]
+        for code in (41, 43, 44) if shape[5] == 1 else (44, 48):      # forced, they are refused
+            B.pc_set_plan_override(ctx, code, 0)
+            try:
+                (calls[3] if code == 44 else calls[0])(DEV + 4)
+                assert False, (shape, code)
+            except B.PcError as e:
+                assert e.status == B.PC_ERR_UNSUPPORTED
+            B.pc_set_plan_override(ctx, -1, 0)
+        B.pc_packed_free(pk)
+    assert direct >= 20, direct
+    B.pc_destroy(ctx)
+
+
 if __name__ == "__main__":
     globals()[sys.argv[2]]()
     print("ok")

@@ -146,3 +146,44 @@ def test_fused_relu(B, ctx, cfg, dims):
     finally:
         B.pc_set_plan_override(ctx, -1, 0)
         g.close()
+
+
+@pytest.mark.parametrize("off", [1, 4])
+@pytest.mark.parametrize("shape", [(9, 38, 41, 56, 64, 1), (13, 33, 47, 40, 72, 1), (33, 7, 7, 136, 200, 1), (20, 14, 14, 64, 128, 2), (5, 33, 31, 40, 72, 2)])
+def test_addresses_that_are_no_multiple_of_16(B, ctx, oracle, shape, off):
+    """Tensors that start 2 and 8 bytes past one: the kernels that load through registers take them, with the same bound."""
+    import numpy as np
+    import torch
+    from tests._harness import TOL_L2, TOL_L2_DW, Case, GpuLayer, Guarded, assert_close, from_dev_f32, oracle_masks
+    L = I.Layer(*shape)
+    case = Case(L, "bf16", 8, I.kept_per_filter(0.3, L.C), tag=("address", shape))
+    g = GpuLayer(B, ctx, case)
+
+    def moved(t):
+        b = torch.empty((t.numel() + 8,), dtype=t.dtype, device="cuda")
+        b[off:off + t.numel()] = t.reshape(-1)
+        return b, b.data_ptr() + 2 * off
+
+    try:
+        pid, kp, M, Wm = oracle_masks(oracle, case)
+        (xb, x), (db, dy) = moved(g.x), moved(g.dy)
+        y, dx, dz, dw = Guarded(g.dy.numel() + 8, g.tdt), Guarded(g.x.numel() + 8, g.tdt), Guarded(g.x.numel() + 8, g.tdt), Guarded(g.nnzk * 4, torch.float32)
+        B.pc_conv_fwd(ctx, g.desc, g.pk, x, y.ptr + 2 * off)
+        B.pc_conv_bwd_data(ctx, g.desc, g.pk, dy, dx.ptr + 2 * off)
+        B.pc_conv_bwd_data_relu(ctx, g.desc, g.pk, dy, x, dz.ptr + 2 * off)
+        B.pc_conv_bwd_weight(ctx, g.desc, g.pk, x, dy, dw.ptr)
+        many = Guarded(g.nnzk * 4, torch.float32)
+        B.pc_conv_bwd_weight_batch(ctx, [g.desc], [g.pk], [x], [dy], [many.ptr])
+        torch.cuda.synchronize()
+        for b in (y, dx, dz, dw, many):
+            assert b.margins_intact()
+        cut = lambda b, t: from_dev_f32(b.body[off:off + t.numel()]).reshape(t.shape)
+        assert_close(cut(y, g.dy), oracle.conv_fwd(case.x, Wm, L.stride), oracle.conv_fwd(np.abs(case.x), np.abs(Wm), L.stride), "bf16", TOL_L2["bf16"], "forward")
+        want = oracle.conv_bwd_data(case.dy, Wm, case.x.shape, L.stride)
+        assert_close(cut(dx, g.x), want, oracle.conv_bwd_data(np.abs(case.dy), np.abs(Wm), case.x.shape, L.stride), "bf16", TOL_L2["bf16"], "backward-data")
+        assert np.array_equal(cut(dz, g.x), np.where(case.x > 0, cut(dx, g.x), 0.0))
+        ref = oracle.conv_bwd_weight(case.x, case.dy, M, L.stride), oracle.conv_bwd_weight(np.abs(case.x), np.abs(case.dy), M, L.stride)
+        assert_close(g.scatter(dw.body), *ref, "f32", TOL_L2_DW, "backward-weight")
+        assert_close(g.scatter(many.body), *ref, "f32", TOL_L2_DW, "backward-weight, several layers")
+    finally:
+        g.close()
