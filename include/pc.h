@@ -274,13 +274,17 @@ pc_status pc_conv_bwd_data_relu(pc_ctx *ctx, const pc_conv_desc *desc, const pc_
  * Deterministic: no floating-point atomics (per-split partial sums in the context's scratch buffer, added in a
  * fixed order). The call never reads the kept-kernel count back: until pc_packed_info has been asked for it
  * after the last pack, the partial sums are laid out for F*C slots (16 bytes x splits x F*C of scratch, touched
- * only at kept slots). dw_compact_dev must hold nnz_kernels x 4 floats. */
+ * only at kept slots). dw_compact_dev must hold nnz_kernels x 4 floats.
+ * The order of additions follows from the sizes and from whether that count is known; and, for a bf16 layer, from whether
+ * there is room for the partial sums of the kernel it would go to (at most 32 MiB): where the scratch buffer would have to
+ * grow and cannot, during a stream capture or because the device has no memory left, a kernel that needs less takes the
+ * call, within the same error bound. A layer that has run once outside a capture has its room. */
 pc_status pc_conv_bwd_weight(pc_ctx *ctx, const pc_conv_desc *desc, const pc_packed *pk,
                              const void *x_dev, const void *dy_dev, float *dw_compact_dev);
 
 /* pc_conv_bwd_weight for callers that cannot allocate device memory: code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc. Same arguments, same kernels and the same result, bit for bit, as
- * pc_conv_bwd_weight with the same pack state; but the partial sums (and the channel-padded copy of a first layer's
+ * pc_conv_bwd_weight with the same pack state and room for its partial sums (see there); but the partial sums (and the channel-padded copy of a first layer's
  * x) live in a fixed buffer of 32 MiB that the library's code object holds on every GPU it is loaded on until the
  * process ends, and the call makes no hipMalloc / hipFree and grows no context buffer. A layer that needs more
  * (the partial sums take at most 32 MiB; a first layer with C not a multiple of 8 adds N*H*W*16 bytes) is rejected
@@ -294,7 +298,8 @@ pc_status pc_conv_bwd_weight_noalloc(pc_ctx *ctx, const pc_conv_desc *desc, cons
  * other (dE/dW of a layer needs only its own a_prev and delta, Section 5.2), so once every x and dy exists they can
  * all be computed together: the bf16 matrix-core layers in one launch per 20 layers plus one reduction launch (the
  * layers share the chip, so each is split less than in its own call: deterministic, equal to the single call up
- * to the float32 order of additions); float32 layers and layers on the gather kernels one by one. Every layer's partial sums have their own region of the context's scratch buffer.
+ * to the float32 order of additions); float32 layers and layers on the gather kernels one by one. Every layer's partial sums have their
+ * own region of the context's scratch buffer; which kernel the group goes to depends on the room for them as for a single layer.
  *   descs_host : HOST array [n_layers] of descriptors; packs_host : HOST array [n_layers] of handles
  *   x_dev_host, dy_dev_host, dw_compact_dev_host : HOST arrays [n_layers] of device pointers as in
  *       pc_conv_bwd_weight (the dw buffers all distinct) */

@@ -180,6 +180,30 @@ extern "C" pc_status pc_set_plan_override(pc_ctx *ctx, int32_t tile_cfg, int32_t
     return PC_OK;
 }
 
+// Leaves no message: not every caller fails without the memory.
+static hipError_t grow_scratch(pc_ctx *ctx, size_t bytes)
+{
+    if (bytes <= ctx->scratch_bytes) return hipSuccess;
+    // Work that is enqueued, or captured in a HIP graph, keeps the address it was given: the old buffer is never
+    // freed before pc_destroy. The list of old buffers grows on the host (the buffer grows by at least half each
+    // time, so the list stays short); when it cannot grow, the call fails and the current buffer stays.
+    if (ctx->scratch && ctx->n_retired == ctx->cap_retired) {
+        const int cap = ctx->cap_retired ? 2 * ctx->cap_retired : 16;
+        void **grown = (void **)realloc(ctx->retired, sizeof(void *) * (size_t)cap);
+        if (!grown) return hipErrorOutOfMemory;
+        ctx->retired = grown;
+        ctx->cap_retired = cap;
+    }
+    const size_t want = bytes + bytes / 2 + (1u << 20);
+    void *fresh = nullptr;
+    const hipError_t e = hipMalloc(&fresh, want);
+    if (e != hipSuccess) return e;
+    if (ctx->scratch) ctx->retired[ctx->n_retired++] = ctx->scratch;
+    ctx->scratch = fresh;
+    ctx->scratch_bytes = want;
+    return hipSuccess;
+}
+
 pc_status pc_scratch(pc_ctx *ctx, size_t bytes, void **out)
 {
     if (ctx->fixed_scratch) {
@@ -191,24 +215,8 @@ pc_status pc_scratch(pc_ctx *ctx, size_t bytes, void **out)
         *out = p;
         return PC_OK;
     }
-    if (bytes > ctx->scratch_bytes) {
-        // Work that is enqueued, or captured in a HIP graph, keeps the address it was given: the old buffer is never
-        // freed before pc_destroy. The list of old buffers grows on the host (the buffer grows by at least half each
-        // time, so the list stays short); when it cannot grow, the call fails and the current buffer stays.
-        if (ctx->scratch && ctx->n_retired == ctx->cap_retired) {
-            const int cap = ctx->cap_retired ? 2 * ctx->cap_retired : 16;
-            void **grown = (void **)realloc(ctx->retired, sizeof(void *) * (size_t)cap);
-            if (!grown) return pc_fail(ctx, PC_ERR_NOMEM, "scratch: host allocation failed");
-            ctx->retired = grown;
-            ctx->cap_retired = cap;
-        }
-        size_t want = bytes + bytes / 2 + (1u << 20);
-        void *fresh = nullptr;
-        PC_HIP(ctx, hipMalloc(&fresh, want));
-        if (ctx->scratch) ctx->retired[ctx->n_retired++] = ctx->scratch;
-        ctx->scratch = fresh;
-        ctx->scratch_bytes = want;
-    }
+    const hipError_t e = grow_scratch(ctx, bytes);
+    if (e != hipSuccess) return pc_hip_check(ctx, e, "scratch");
     *out = ctx->scratch;
     return PC_OK;
 }
@@ -218,8 +226,7 @@ bool pc_scratch_ready(pc_ctx *ctx, size_t bytes)
     if (ctx->fixed_scratch) return bytes <= PC_FIXED_SCRATCH_BYTES;
     if (bytes <= ctx->scratch_bytes) return true;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    void *scr;
-    if (hipStreamIsCapturing(ctx->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone && pc_scratch(ctx, bytes, &scr) == PC_OK) return true;
+    if (hipStreamIsCapturing(ctx->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone && grow_scratch(ctx, bytes) == hipSuccess) return true;
     (void)hipGetLastError();
     return false;
 }

@@ -28,7 +28,10 @@ def seen():
 
 def layer(ctx, shape):
     N, H, W, C, F, st = shape
-    return B.make_desc(N, H, W, C, F, st, B.PC_BF16), B.pc_pack(ctx, DEV, DEV, DEV, F, C, LIB, B.PC_BF16)
+    pk = B.pc_pack(ctx, DEV, DEV, DEV, F, C, LIB, B.PC_BF16)
+    ct.c_int.in_dll(stub, "stub_count").value = F * I.kept_per_filter(0.3, C)
+    B.pc_packed_info(ctx, pk)
+    return B.make_desc(N, H, W, C, F, st, B.PC_BF16), pk
 
 
 def wgrad_lds():
@@ -85,6 +88,42 @@ def alignment():
         B.pc_packed_free(pk)
     assert direct >= 20, direct
     B.pc_destroy(ctx)
+
+
+def no_room():
+    """Backward-weight where the scratch buffer cannot grow: another kernel takes the call, which succeeds and leaves no message. The entry
+    point that allocates nothing goes to the kernel of the call that has room."""
+    for dims in ([(32, 28, 28, 512, 512, 1)], [(32, 112, 112, 128, 128, 1), (32, 56, 56, 256, 256, 1), (32, 28, 28, 512, 512, 1)]):
+        ctx = B.pc_create(0, None)
+        ls = [layer(ctx, s) for s in dims]
+        n = [DEV] * len(ls)
+
+        def call(noalloc=False):
+            if noalloc:
+                B.pc_conv_bwd_weight_noalloc(ctx, *ls[0], DEV, DEV, DEV)
+            elif len(ls) == 1:
+                B.pc_conv_bwd_weight(ctx, *ls[0], DEV, DEV, DEV)
+            else:
+                B.pc_conv_bwd_weight_batch(ctx, [d for d, _ in ls], [p for _, p in ls], n, n, [DEV + 64 * i for i in range(len(ls))])
+            return B.pc_last_kernel(ctx)
+
+        B.pc_set_plan_override(ctx, 11, 0)
+        assert "wgrad_ws" in call()
+        B.pc_set_plan_override(ctx, -1, 0)
+        for name in ("stub_malloc_fails", "stub_capturing"):
+            ct.c_int.in_dll(stub, name).value = 1
+            assert "wgrad_ws" in call()
+            assert B.load().pc_last_error(ctx) == b"", B.load().pc_last_error(ctx)
+            if len(ls) == 1:
+                assert "wgrad_dma" in call(noalloc=True)
+            ct.c_int.in_dll(stub, name).value = 0
+        assert "wgrad_dma" in call()
+        ct.c_int.in_dll(stub, "stub_capturing").value = 1
+        assert "wgrad_dma" in call()
+        ct.c_int.in_dll(stub, "stub_capturing").value = 0
+        for _, p in ls:
+            B.pc_packed_free(p)
+        B.pc_destroy(ctx)
 
 
 if __name__ == "__main__":
