@@ -18,6 +18,7 @@
 
 struct pc_stream_ref;
 #define PC_CHOICES 512         // a network of 16 layers has 48 entries
+#define PC_CHOICE_WAYS 4       // places that a shape may take: five of 48 shapes meet in one set once in 150 networks
 #define PC_CHOICE_KEY 10
 
 struct pc_ctx {
@@ -37,8 +38,9 @@ struct pc_ctx {
                            // device's fixed buffer, or fails when the request exceeds it
     char last_kernel[160]; // symbol of the kernel that did the work of the last conv call (pc_last_kernel)
     pc_stream_ref *ref;
-    // kernels chosen for the shapes seen last, direct mapped (an estimate over all candidates takes longer than a launch)
+    // kernels chosen for the shapes seen last (an estimate over all candidates takes longer than a launch)
     struct { int32_t key[PC_CHOICE_KEY]; int32_t kernel; } choice[PC_CHOICES];
+    uint8_t choice_next[PC_CHOICES / PC_CHOICE_WAYS];      // the place that the next new shape takes, in turn
 };
 
 // The entry of a shape in the context's table: *hit when `kernel` holds its choice, else the caller fills it in.
@@ -47,10 +49,19 @@ static inline int32_t *pc_choice(pc_ctx *ctx, const int32_t (&key)[PC_CHOICE_KEY
 {
     uint32_t h = 0;
     for (int i = 0; i < PC_CHOICE_KEY; ++i) h = (h ^ (uint32_t)key[i]) * 0x9E3779B1u;
-    auto &e = ctx->choice[(h >> 16) % PC_CHOICES];
-    *hit = memcmp(e.key, key, sizeof(key)) == 0;
-    if (!*hit) { memcpy(e.key, key, sizeof(key)); e.kernel = -1; }
-    return &e.kernel;
+    const uint32_t set = (h >> 16) % (PC_CHOICES / PC_CHOICE_WAYS);
+    auto *e = &ctx->choice[set * PC_CHOICE_WAYS];
+    for (int w = 0; w < PC_CHOICE_WAYS; ++w)
+        if (memcmp(e[w].key, key, sizeof(key)) == 0) {
+            *hit = true;
+            return &e[w].kernel;
+        }
+    *hit = false;
+    e += ctx->choice_next[set];
+    ctx->choice_next[set] = (uint8_t)((ctx->choice_next[set] + 1) % PC_CHOICE_WAYS);
+    memcpy(e->key, key, sizeof(key));
+    e->kernel = -1;
+    return &e->kernel;
 }
 
 // Device-side view of a packed layer. All pointers point into one slab.

@@ -24,3 +24,12 @@ def stub(tmp_path_factory):
 def test_host_side(stub, check):
     r = subprocess.run([sys.executable, "-m", "tests._host_probe", stub, check], cwd=ROOT, capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and r.stdout.endswith("ok\n"), r.stdout + r.stderr
+
+
+def test_kernels_chosen_for_a_network_are_remembered(tmp_path):
+    exe = str(tmp_path / "choice_table")
+    subprocess.run(["hipcc" if not os.path.exists("/opt/rocm/bin/hipcc") else "/opt/rocm/bin/hipcc", "--cuda-host-only", "-O1", "-std=c++17",
+                    "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2011_10170_amd", "csrc"), "-o", exe, os.path.join(ROOT, "tests", "choice_table.hip")],
+                   check=True, capture_output=True)
+    out = subprocess.run([exe], check=True, capture_output=True, text=True).stdout
+    assert out.split("\n")[:3] == ["0 0"] * 3, out
