@@ -590,8 +590,6 @@ pc_mfma_conv_ring_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__
         return;
     }
     const __amdgpu_buffer_rsrc_t osrc = __builtin_amdgcn_make_buffer_rsrc(out, 0, g.out_bytes, 0x00020000);
-    const __amdgpu_buffer_rsrc_t msrc = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint16_t *>(ACT == PC_ACT_RELU_MASK ? g.act_mask : out), 0, g.out_bytes, 0x00020000);
     const int RP = q.EPR * 16, PL = g.nrow * RP;
     int at = 0, slot = 0;
     for (int k = 0; k < ntile; ++k) {
@@ -645,7 +643,7 @@ pc_mfma_conv_ring_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__
             at = DR_B * 1024 - at;
         }
         asm volatile("s_barrier" ::: "memory");
-        dm_store<DM_FWD2, 4, 4, 0, ACT>(s, g, t, t.mt * 128 + half * 64, acc, lds + used + s.w * (64 * DM_STG), osrc, msrc);
+        dm_store<DM_FWD2, 4, 4, 0, ACT>(s, g, t, t.mt * 128 + half * 64, acc, lds + used + s.w * (64 * DM_STG), osrc, osrc);
     }
 }
 
@@ -752,6 +750,18 @@ static bool plan_dma(const MfmaArgs &g, bool flip, const DmaCand &cand, int lgCG
 
 typedef void (*DmaKernel)(const uint16_t *, uint16_t *, const uint16_t *, DmaArgs);
 
+// The kernels of kDma by fused step. Only stride-1 passes are masked, and a backward pass has no ReLU of its own.
+#define DM_ACTS(...) {&__VA_ARGS__, PC_ACT_NONE>, &__VA_ARGS__, PC_ACT_RELU>, &__VA_ARGS__, PC_ACT_RELU_MASK>}
+static const DmaKernel kDmaKernels[kNumDma][3] = {
+    DM_ACTS(pc_mfma_conv_dma_kernel<8), DM_ACTS(pc_mfma_conv_dma_kernel<4), DM_ACTS(pc_mfma_conv_dma_kernel<7),
+    DM_ACTS(pc_mfma_conv_solo_kernel<DM_S1, 2, 4, 3), DM_ACTS(pc_mfma_conv_solo_kernel<DM_S1, 4, 4, 2), DM_ACTS(pc_mfma_conv_solo_kernel<DM_S1, 2, 2, 3),
+    {&pc_mfma_conv_solo_kernel<DM_FWD2, 2, 4, 2, PC_ACT_NONE>, &pc_mfma_conv_solo_kernel<DM_FWD2, 2, 4, 2, PC_ACT_RELU>, nullptr},
+    {&pc_mfma_conv_ring_kernel<PC_ACT_NONE>, &pc_mfma_conv_ring_kernel<PC_ACT_RELU>, nullptr},
+    {&pc_mfma_conv_solo_kernel<DM_FWD2, 2, 2, 2, PC_ACT_NONE>, &pc_mfma_conv_solo_kernel<DM_FWD2, 2, 2, 2, PC_ACT_RELU>, nullptr},
+    {&pc_mfma_conv_solo_kernel<DM_BWD2, 2, 4, 3, PC_ACT_NONE>, nullptr, nullptr},
+    {&pc_mfma_conv_solo_kernel<DM_BWD2, 2, 2, 3, PC_ACT_NONE>, nullptr, nullptr}};
+#undef DM_ACTS
+
 static hipError_t launch_dma(DmaKernel kernel, pc_per_device_once &attr, int device, hipStream_t st, int grid, int threads, size_t lds, const uint16_t *in,
                              uint16_t *out, const uint16_t *wz, const DmaArgs &g)
 {
@@ -777,7 +787,7 @@ pc_status pc_run_mfma_conv_dma(pc_ctx *ctx, int pcfg, int *lgCG, double limit, c
     int best_grid = 0, best_k = -1;
     double best_est = limit;
     for (int k = 0; k < kNumDma; ++k) {
-        if (kDma[k].mode != mode || (pcfg >= 0 && pcfg != kDma[k].code)) continue;
+        if (kDma[k].mode != mode || !kDmaKernels[k][act] || (pcfg >= 0 && pcfg != kDma[k].code)) continue;
         for (int lg = *lgCG < 0 ? 0 : *lgCG; lg <= (*lgCG < 0 ? 2 : *lgCG); ++lg) {
             DmaArgs t;
             size_t lds;
@@ -789,15 +799,8 @@ pc_status pc_run_mfma_conv_dma(pc_ctx *ctx, int pcfg, int *lgCG, double limit, c
     }
     if (best_k < 0) return PC_OK;
     const DmaCand &c = kDma[best_k];
-#define DM_ACTS(NAME, ...) {&NAME<__VA_ARGS__, PC_ACT_NONE>, &NAME<__VA_ARGS__, PC_ACT_RELU>, &NAME<__VA_ARGS__, PC_ACT_RELU_MASK>}
-    static const DmaKernel kernels[kNumDma][3] = {
-        DM_ACTS(pc_mfma_conv_dma_kernel, 8), DM_ACTS(pc_mfma_conv_dma_kernel, 4), DM_ACTS(pc_mfma_conv_dma_kernel, 7),
-        DM_ACTS(pc_mfma_conv_solo_kernel, DM_S1, 2, 4, 3), DM_ACTS(pc_mfma_conv_solo_kernel, DM_S1, 4, 4, 2), DM_ACTS(pc_mfma_conv_solo_kernel, DM_S1, 2, 2, 3),
-        DM_ACTS(pc_mfma_conv_solo_kernel, DM_FWD2, 2, 4, 2), {&pc_mfma_conv_ring_kernel<PC_ACT_NONE>, &pc_mfma_conv_ring_kernel<PC_ACT_RELU>, &pc_mfma_conv_ring_kernel<PC_ACT_RELU_MASK>}, DM_ACTS(pc_mfma_conv_solo_kernel, DM_FWD2, 2, 2, 2),
-        DM_ACTS(pc_mfma_conv_solo_kernel, DM_BWD2, 2, 4, 3), DM_ACTS(pc_mfma_conv_solo_kernel, DM_BWD2, 2, 2, 3)};
-#undef DM_ACTS
     static pc_per_device_once attr[kNumDma][3];
-    const hipError_t e = launch_dma(kernels[best_k][act], attr[best_k][act], ctx->device, ctx->stream, best_grid, c.nbuf == 1 ? 256 : 512, best_lds, in, out,
+    const hipError_t e = launch_dma(kDmaKernels[best_k][act], attr[best_k][act], ctx->device, ctx->stream, best_grid, c.nbuf == 1 ? 256 : 512, best_lds, in, out,
                                     wz, best);
     *launched = c.code;
     *lgCG = best.lgCG;

@@ -32,7 +32,6 @@ struct WgradDmaGroup {
 
 // Plan of one layer (ksplit left to the caller); false when the layer is outside what the kernel takes. *tile_us: estimated time of a
 // pixel tile (us) while two workgroups share a CU.
-bool pc_wgrad_dma_plan(const pc_ctx *ctx, const pc_conv_desc *d, int64_t nslots, WgradDmaArgs *out, int *ct, int *ft, size_t *lds,
-                       double *tile_us);
+bool pc_wgrad_dma_plan(const pc_conv_desc *d, int64_t nslots, WgradDmaArgs *out, int *ct, int *ft, size_t *lds, double *tile_us);
 pc_status pc_wgrad_dma_launch(pc_ctx *ctx, const WgradDmaGroup &g, size_t lds);
 #endif

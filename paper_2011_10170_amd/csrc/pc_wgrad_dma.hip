@@ -257,10 +257,8 @@ __global__ void __launch_bounds__(256, 2) pc_mfma_wgrad_dma_kernel(WgradDmaGroup
     else pc_wgrad_dma_body<2>(y.x, y.dy, y.a, y.kinfo, y.partial, y.dw, lin, y.gx, y.gy);
 }
 
-bool pc_wgrad_dma_plan(const pc_ctx *ctx, const pc_conv_desc *d, int64_t nslots, WgradDmaArgs *out, int *ct, int *ft, size_t *lds,
-                       double *tile_us)
+bool pc_wgrad_dma_plan(const pc_conv_desc *d, int64_t nslots, WgradDmaArgs *out, int *ct, int *ft, size_t *lds, double *tile_us)
 {
-    (void)ctx;
     WgradDmaArgs a;
     memset(&a, 0, sizeof(a));
     const int st = d->stride;

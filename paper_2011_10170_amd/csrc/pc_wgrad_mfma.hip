@@ -869,7 +869,7 @@ static pc_status pc_mfma_bwd_weight_dma(pc_ctx *ctx, const pc_conv_desc *d, cons
     WgradDmaLayer &y = g.layer[0];
     size_t lds;
     double tile_us;
-    if (!pc_direct_loads(x) || !pc_direct_loads(dy) || !pc_wgrad_dma_plan(ctx, d, nslots, &y.a, &y.gx, &y.gy, &lds, &tile_us)) return PC_OK;
+    if (!pc_direct_loads(x) || !pc_direct_loads(dy) || !pc_wgrad_dma_plan(d, nslots, &y.a, &y.gx, &y.gy, &lds, &tile_us)) return PC_OK;
     int ks = 2 * ctx->num_cu / (y.gx * y.gy);
     if (ks > y.a.n_ktiles) ks = y.a.n_ktiles;
     if (ks < 1) ks = 1;
@@ -1069,7 +1069,7 @@ pc_status pc_mfma_bwd_weight_group(pc_ctx *ctx, int n, const pc_conv_desc *d, co
             it.nslots = nslots;
             it.pad_x = false;
             it.dma = dma && pc_direct_loads(x[l]) && pc_direct_loads(dy[l]) &&
-                     pc_wgrad_dma_plan(ctx, &d[l], nslots, &it.q, &it.ct, &it.ft, &it.lds, &it.tile_us);
+                     pc_wgrad_dma_plan(&d[l], nslots, &it.q, &it.ct, &it.ft, &it.lds, &it.tile_us);
             if (it.dma) {
                 it.n_ktiles = it.q.n_ktiles;
                 it.ksplit = std::max(1, std::min(2 * ctx->num_cu / (it.ct * it.ft), it.n_ktiles));
