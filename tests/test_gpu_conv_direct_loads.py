@@ -87,6 +87,30 @@ def test_several_tiles_per_workgroup_at_stride_2(B, ctx, cfg, dims):
         g.close()
 
 
+@pytest.mark.parametrize("cfg", [37, 38])
+@pytest.mark.parametrize("dims", [(20, 56, 56, 200, 104), (48, 33, 31, 264, 32), (64, 35, 29, 136, 72)])
+def test_several_tiles_per_workgroup_at_stride_2_backward(B, ctx, cfg, dims):
+    """432 to 1020 tiles of 4, 1 and 3 chunks on 256 workgroups: the three buffers run on from tile to tile at every offset. Against a kernel of
+    the other family; see test_more_tiles_than_workgroups."""
+    import torch
+    from tests._harness import Case, GpuLayer
+    layer = I.Layer(*dims, 2)
+    g = GpuLayer(B, ctx, Case(layer, "bf16", 8, I.kept_per_filter(0.3, layer.C), tag=("direct2", "back")))
+    try:
+        out = []
+        for code, name in ((cfg, "pc_mfma_conv_solo_kernel<2"), (33, "pc_mfma_conv_mc_kernel")):
+            B.pc_set_plan_override(ctx, code, 0)
+            dx = torch.full((layer.N, layer.H, layer.W, layer.C), float("nan"), dtype=torch.bfloat16, device="cuda")
+            B.pc_conv_bwd_data(ctx, g.desc, g.pk, g.dy, dx)
+            assert B.pc_last_kernel(ctx).startswith(name)
+            out.append(dx.double())
+        a, b = out
+        assert bool((a - b).abs().le(2.0 ** -7 * torch.maximum(a.abs(), b.abs()) + 2.0 ** -12 * b.abs().max()).all())
+    finally:
+        B.pc_set_plan_override(ctx, -1, 0)
+        g.close()
+
+
 @pytest.mark.parametrize("cfg", [41, 42, 43, 45, 46])
 def test_many_small_images(B, ctx, oracle, cfg):
     """A zero row between every four: the widest tile has not the LDS for it."""

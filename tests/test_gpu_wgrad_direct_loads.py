@@ -84,6 +84,31 @@ def test_several_layers(B, ctx, code, dims):
             g.close()
 
 
+@pytest.mark.parametrize("code", [44, 11, -1])
+def test_several_layers_against_the_oracle(B, ctx, oracle, code):
+    """One call for layers of both strides, whole images and strips of them, and channels that fill no tile; at code 44 also one that is left to the
+    other kernel (3 channels)."""
+    import torch
+    from tests._harness import TOL_L2_DW, Case, GpuLayer, Guarded, assert_close, oracle_masks
+    dims = SMALL + [(33, 8, 8, 64, 136, 1), (3, 15, 16, 72, 128, 2)]
+    gs = [GpuLayer(B, ctx, Case(I.Layer(*s), "bf16", 8, I.kept_per_filter(0.3, s[3]), tag=("group", s))) for s in dims]
+    try:
+        B.pc_set_plan_override(ctx, code, 0)
+        out = [Guarded(g.nnzk * 4, torch.float32) for g in gs]
+        B.pc_conv_bwd_weight_batch(ctx, [g.desc for g in gs], [g.pk for g in gs], [g.x for g in gs], [g.dy for g in gs], [b.ptr for b in out])
+        torch.cuda.synchronize()
+        for g, b, s in zip(gs, out, dims):
+            assert b.margins_intact()
+            c = g.case
+            _, _, M, _ = oracle_masks(oracle, c)
+            assert_close(g.scatter(b.body), oracle.conv_bwd_weight(c.x, c.dy, M, s[5]), oracle.conv_bwd_weight(np.abs(c.x), np.abs(c.dy), M, s[5]), "f32", TOL_L2_DW,
+                         "%s" % (s,))
+    finally:
+        B.pc_set_plan_override(ctx, -1, 0)
+        for g in gs:
+            g.close()
+
+
 def test_capture_without_room_for_the_partial_planes(B):
     """A call whose partial planes would need more scratch than there is, under stream capture: the kernel with fewer planes takes it."""
     import torch

@@ -60,6 +60,27 @@ def test_two_calls_in_a_row_second_smaller(B, ctx, oracle):
     _both(B, ctx, oracle, I.Layer(2, 16, 16, 3, 64, 1), "bf16", 8, 1, "noalloc_d")
 
 
+@pytest.mark.parametrize("code", [-1, 11, 44])
+@pytest.mark.parametrize("dims,n_keep", [((64, 28, 28, 128, 128, 1), 128), ((48, 35, 28, 128, 120, 2), 128), ((32, 28, 28, 256, 256, 1), 250)])
+def test_partial_sums_that_fill_the_fixed_buffer(B, ctx, dims, n_keep, code):
+    """All or nearly all kernels kept: 128 or 32 planes of the kernel with direct loads take up to the buffer's 32 MiB. The same kernel and bits as the
+    allocating call, whose own scratch has that room."""
+    import torch
+    g = GpuLayer(B, ctx, Case(I.Layer(*dims), "bf16", 8, n_keep, tag="noalloc_full"))
+    try:
+        B.pc_set_plan_override(ctx, code, 0)
+        ref, out = Guarded(g.nnzk * 4, torch.float32), Guarded(g.nnzk * 4, torch.float32)
+        B.pc_conv_bwd_weight(ctx, g.desc, g.pk, g.x, g.dy, ref.ptr)
+        kernel = B.pc_last_kernel(ctx)
+        B.pc_conv_bwd_weight_noalloc(ctx, g.desc, g.pk, g.x, g.dy, out.ptr)
+        torch.cuda.synchronize()
+        assert B.pc_last_kernel(ctx) == kernel and out.margins_intact() and torch.isfinite(out.body).all()
+        assert torch.equal(out.body, ref.body)
+    finally:
+        B.pc_set_plan_override(ctx, -1, 0)
+        g.close()
+
+
 def test_a_layer_beyond_the_fixed_buffer_is_rejected(B, ctx):
     """N*H*W*16 bytes for the 8-channel copy of a 3-channel input: 51 MB at N = 64, 224 x 224; nothing is launched."""
     import torch
