@@ -859,6 +859,11 @@ static pc_status pc_mfma_bwd_weight_ws(pc_ctx *ctx, const pc_conv_desc *d, const
     return pc_launch_wgrad_reduce(ctx, (const float *)scr, ks, nslots, nslots, pk, dw);
 }
 
+// Slots of a partial plane that are written and read. Where the count has not been read back the planes are laid out for every kernel, but
+// 15 to 50 % are kept in earnest: with the capacity in its place the choice between the two kernels was 2.9 % behind the faster on
+// the 200 layers below, with 0.3 of it 0.7 % (5 x 69 x 71, 208 -> 232, stride 2 26 -> 18.5 us).
+static double kept_estimate(const pc_packed *pk, int64_t nslots) { return pk->nnzk >= 0 ? (double)nslots : 0.3 * (double)nslots; }
+
 // The kernel with direct loads for one layer. *launched stays false when the layer is outside what it takes.
 static pc_status pc_mfma_bwd_weight_dma(pc_ctx *ctx, const pc_conv_desc *d, const pc_packed *pk, const void *x, const void *dy,
                                         float *dw, int64_t nslots, bool *launched)
@@ -876,16 +881,17 @@ static pc_status pc_mfma_bwd_weight_dma(pc_ctx *ctx, const pc_conv_desc *d, cons
     y.a.ksplit = ks;
     if (ctx->plan_cfg != 44) {
         // Either kernel by its estimated time (us): rounds of pixel tiles, rounds of workgroups, the partial planes and whether there are any,
-        // a start. Fitted to 142 layers (12 and 8 % rms); on 138 others the choice is 1.8 % behind the faster of the two on average,
-        // the rule before it (from 12 us of tiles for every place on) 7.7 %. 13 images 33 x 47, 40 -> 72 15.4 -> 13.6, 64 images 7 x 7, 512 -> 512 25.1 -> 23.4; large
-        // layers 28 x 28, 512 -> 512, batch 32 99 -> 82, 56 x 56, 128 -> 128, stride 2, batch 64 33 -> 27.5.
-        const int32_t key[PC_CHOICE_KEY] = {7, d->N, d->H, d->W, d->C, d->F, d->stride, (int32_t)nslots, 0, 0};
+        // a start. Fitted to 142 layers (12 and 8 % rms); on 200 others (profiles/plan_timings_bf16.csv, bwd_weight: 11 and 44 are the two
+        // kernels) the choice is 0.6 % behind the faster of the two on average, 0.7 % where the count has not been read back, the worst 16 %;
+        // always this kernel 0.7 %, always the other 14 %. 13 images 33 x 47, 40 -> 72 15.4 -> 13.6, 64 images 7 x 7, 512 -> 512 25.1 -> 23.4;
+        // large layers 28 x 28, 512 -> 512, batch 32 99 -> 82, 56 x 56, 128 -> 128, stride 2, batch 64 33 -> 27.5.
+        const int32_t key[PC_CHOICE_KEY] = {7, d->N, d->H, d->W, d->C, d->F, d->stride, (int32_t)nslots, pk->nnzk >= 0, 0};
         bool known;
         int32_t *choice = pc_choice(ctx, key, &known);
         if (!known || *choice < 0) {
             const int T = y.gx * y.gy, places = 2 * ctx->num_cu;
             auto up = [](int p, int q) { return (double)((p + q - 1) / q); };
-            auto planes = [&](int n) { return n > 1 ? 2.9 + 16e-6 * (double)n * (double)nslots : 0.0; };
+            auto planes = [&](int n) { return n > 1 ? 2.9 + 16e-6 * (double)n * kept_estimate(pk, nslots) : 0.0; };
             const double own = (0.9 * up(y.a.n_ktiles, ks) * tile_us + 2.5) * up(T * ks, places) + planes(ks) + 2.5;
             WgradWsArgs a;
             int ct, ft;

@@ -26,11 +26,13 @@ def seen():
             ct.c_longlong.in_dll(stub, "stub_lds").value)
 
 
-def layer(ctx, shape):
+def layer(ctx, shape, read=True):
+    """Descriptor and pack of a layer; read: its kept-kernel count is known on the host, as after a read-back."""
     N, H, W, C, F, st = shape
     pk = B.pc_pack(ctx, DEV, DEV, DEV, F, C, LIB, B.PC_BF16)
     ct.c_int.in_dll(stub, "stub_count").value = F * I.kept_per_filter(0.3, C)
-    B.pc_packed_info(ctx, pk)
+    if read:
+        B.pc_packed_info(ctx, pk)
     return B.make_desc(N, H, W, C, F, st, B.PC_BF16), pk
 
 
@@ -124,6 +126,27 @@ def no_room():
         for _, p in ls:
             B.pc_packed_free(p)
         B.pc_destroy(ctx)
+
+
+def wgrad_choice():
+    """The kernel that a layer's weight gradient goes to against the stored timings of both (11, 44), with the count read back or not."""
+    times = {}
+    for row in open("profiles/plan_timings_bf16.csv"):
+        f = row.strip().split(",")
+        if f[0].startswith("bwd_weight"):
+            times.setdefault((f[0],) + tuple(int(v) for v in f[1:7]), {})[f[7]] = float(f[8])
+    ctx = B.pc_create(0, None)
+    for name in ("bwd_weight", "bwd_weight_unread"):
+        late = []
+        for k, us in times.items():
+            if k[0] == name:
+                d, pk = layer(ctx, k[1:], read=name == "bwd_weight")
+                B.pc_conv_bwd_weight(ctx, d, pk, DEV, DEV, DEV)
+                late.append(us["44" if "wgrad_dma" in B.pc_last_kernel(ctx) else "11"] / min(us.values()))
+                B.pc_packed_free(pk)
+        print(name, len(late), sum(late) / len(late), max(late))
+        assert len(late) >= 200 and sum(late) / len(late) < 1.01 and max(late) < 1.2
+    B.pc_destroy(ctx)
 
 
 if __name__ == "__main__":
