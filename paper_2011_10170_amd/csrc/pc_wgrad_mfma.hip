@@ -1089,16 +1089,6 @@ pc_status pc_mfma_bwd_weight_group(pc_ctx *ctx, int n, const pc_conv_desc *d, co
             items.push_back(it);
         }
     };
-    // The wave-specialised kernel for every layer, or the kernel with direct loads for all it takes, whichever is estimated to be faster
-    // (us; fitted to the four networks below). Launches of their own for few layers, and short workgroups, cost the second more:
-    // VGG-16 / CIFAR 94 : 116, ResNet-18 / CIFAR 144 : 149, ResNet-50 / ImageNet 287 : 232, VGG-16 / ImageNet 901 : 748. The choice is
-    // remembered for the shapes it was made for.
-    auto ws_us = [&]() {
-        double us = 0.0;
-        for (const GroupItem &it : items)
-            if (!it.dma) us += 2.05 * it.ct * it.ft * it.n_ktiles / ctx->num_cu;
-        return us > 0.0 ? us + 12.0 : 0.0;
-    };
     auto even = [&]() {          // the direct-load layers' share of every place, two per CU
         double us = 0.0;
         for (const GroupItem &it : items)
@@ -1106,22 +1096,6 @@ pc_status pc_mfma_bwd_weight_group(pc_ctx *ctx, int n, const pc_conv_desc *d, co
         return us / (2.0 * ctx->num_cu);
     };
     bool dma = ctx->plan_cfg == 44;
-    if (ctx->plan_cfg < 0) {
-        uint64_t h = 1469598103934665603ull;
-        for (int l = 0; l < n; ++l)
-            for (int v : {(int)d[l].N, (int)d[l].H, (int)d[l].W, (int)d[l].C, (int)d[l].F, (int)d[l].stride * 2 + (pc_direct_loads(x[l]) && pc_direct_loads(dy[l]))}) h = (h ^ (uint32_t)v) * 1099511628211ull;
-        const int32_t key[PC_CHOICE_KEY] = {4, n, (int32_t)h, (int32_t)(h >> 32), d[0].N, d[0].H, d[n - 1].H, d[n - 1].F, 0, 0};
-        bool hit;
-        int32_t *choice = pc_choice(ctx, key, &hit);
-        if (!hit) {
-            plan(false);
-            const double all = ws_us();
-            plan(true);
-            *choice = even() > 0.0 && 40.0 + 1.15 * even() + ws_us() < all;
-        }
-        dma = *choice != 0;
-    }
-    plan(dma);
     // A layer's own call splits its pixel tiles until the layer alone fills the chip; here the layers fill it
     // together, so every workgroup gets about the same share of all (tile, pixel tile) units: fewer splits, longer
     // main loops per prologue and epilogue, fewer partial planes. (The two kernels run one after the other, each with its own shares.)
@@ -1145,6 +1119,48 @@ pc_status pc_mfma_bwd_weight_group(pc_ctx *ctx, int n, const pc_conv_desc *d, co
             it.a.ksplit = it.q.ksplit = it.ksplit;
         }
     };
+    // The wave-specialised kernel for every layer, or the kernel with direct loads for all it takes (the rest in launches of their own),
+    // the second where it is estimated to be faster by a tenth (it takes more scratch, and the estimates err by 8 and 6 % rms). Microseconds:
+    // pixel tiles per CU (strips of images cost more), launches, planes, a start. Fitted to 160 whole networks (VGG- and
+    // ResNet-shaped, 1 to 128 images, widths 16 to 64, maps 16 to 224); on 200 drawn afterwards the choice is 0.5 % behind the faster
+    // of the two on average, the worst 19 % (profiles/group_timings_bf16.csv); always direct loads 1.5 %, never 25 %. The rule
+    // before it, made for four networks of width 64, was 20 % behind: 18 images of 101 x 101, width 16 143 us where direct loads take
+    // 71. VGG-16 / CIFAR 91 : 108, ResNet-18 / CIFAR 144 : 148, ResNet-50 / ImageNet 294 : 235, VGG-16 / ImageNet 948 : 774.
+    auto estimate = [&]() {
+        double whole = 0.0, strips = 0.0, planes = 0.0;
+        int n_whole = 0, n_strips = 0;
+        for (const GroupItem &it : items) {
+            if (!it.dma) {
+                (it.a.lgS ? strips : whole) += (double)it.ct * it.ft * it.n_ktiles / ctx->num_cu;
+                ++(it.a.lgS ? n_strips : n_whole);
+            }
+            if (it.ksplit > 1) planes += 16e-6 * it.ksplit * kept_estimate(pk[it.l], it.nslots);
+        }
+        const int launches = (n_whole + WS_GROUP_MAX - 1) / WS_GROUP_MAX + (n_strips + WS_GROUP_MAX - 1) / WS_GROUP_MAX;
+        if (!dma) return 13.4 + 2.01 * whole + 2.52 * strips + 7.7 * launches + 0.36 * planes;
+        return 17.8 + 1.18 * (even() + whole + strips) + (launches ? 9.3 : 0.0) + 0.38 * planes;
+    };
+    if (ctx->plan_cfg < 0) {
+        // (remembered for the shapes it was made for)
+        uint64_t h = 1469598103934665603ull;
+        for (int l = 0; l < n; ++l)
+            for (int v : {(int)d[l].N, (int)d[l].H, (int)d[l].W, (int)d[l].C, (int)d[l].F, (int)d[l].stride * 2 + (pc_direct_loads(x[l]) && pc_direct_loads(dy[l])), (int)pk[l]->nnzk})
+                h = (h ^ (uint32_t)v) * 1099511628211ull;
+        const int32_t key[PC_CHOICE_KEY] = {4, n, (int32_t)h, (int32_t)(h >> 32), d[0].N, d[0].H, d[n - 1].H, d[n - 1].F, 0, 0};
+        bool hit;
+        int32_t *choice = pc_choice(ctx, key, &hit);
+        if (!hit) {
+            plan(false);
+            shares();
+            const double all = estimate();
+            dma = true;
+            plan(true);
+            shares();
+            *choice = even() > 0.0 && 1.1 * estimate() < all;
+        }
+        dma = *choice != 0;
+    }
+    plan(dma);
     shares();
     if (dma && ctx->plan_cfg < 0 && !pc_scratch_ready(ctx, total)) {      // the other kernel needs fewer partial planes
         dma = false;

@@ -26,11 +26,11 @@ def seen():
             ct.c_longlong.in_dll(stub, "stub_lds").value)
 
 
-def layer(ctx, shape, read=True):
+def layer(ctx, shape, read=True, keep=0.3):
     """Descriptor and pack of a layer; read: its kept-kernel count is known on the host, as after a read-back."""
     N, H, W, C, F, st = shape
     pk = B.pc_pack(ctx, DEV, DEV, DEV, F, C, LIB, B.PC_BF16)
-    ct.c_int.in_dll(stub, "stub_count").value = F * I.kept_per_filter(0.3, C)
+    ct.c_int.in_dll(stub, "stub_count").value = F * I.kept_per_filter(keep, C)
     if read:
         B.pc_packed_info(ctx, pk)
     return B.make_desc(N, H, W, C, F, st, B.PC_BF16), pk
@@ -146,6 +146,41 @@ def wgrad_choice():
                 B.pc_packed_free(pk)
         print(name, len(late), sum(late) / len(late), max(late))
         assert len(late) >= 200 and sum(late) / len(late) < 1.01 and max(late) < 1.2
+    B.pc_destroy(ctx)
+
+
+def network(kind, width, images, size, stages):
+    """The 3x3 layers of a VGG- or ResNet-shaped network (basic and bottleneck blocks)."""
+    out, c = [], 3 if kind == "vgg" else width
+    for s in range(stages):
+        f = width * min(8, 1 << s)
+        for k in range((2 if s < 2 else 3) if kind == "vgg" else 4 if kind == "basic" else (3, 4, 6, 3)[s]):
+            st = 2 if kind != "vgg" and s and k == 0 else 1
+            out.append((images, size, size, f if kind == "bottleneck" else c, f, st))
+            size, c = (size - 1) // st + 1, f
+        if kind == "vgg":
+            size //= 2
+    return out
+
+
+def group_choice():
+    """The kernel that the weight gradients of a network go to in one call against the stored timings of both."""
+    ctx = B.pc_create(0, None)
+    for part in ("fit", "check"):
+        late = []
+        for row in open("profiles/group_timings_bf16.csv"):
+            f = row.strip().split(",")
+            if f[0] != part:
+                continue
+            ls = [layer(ctx, s, read=f[7] == "yes", keep=float(f[6])) for s in network(f[1], *(int(v) for v in f[2:6]))]
+            n = [DEV] * len(ls)
+            B.pc_conv_bwd_weight_batch(ctx, [d for d, _ in ls], [p for _, p in ls], n, n, [DEV + 64 * i for i in range(len(ls))])
+            us = [float(v) for v in f[8:]]
+            late.append(us["wgrad_dma" in B.pc_last_kernel(ctx)] / min(us))
+            for _, p in ls:
+                B.pc_packed_free(p)
+        print(part, len(late), sum(late) / len(late), max(late))
+        assert len(late) >= 160 and sum(late) / len(late) < 1.01 and max(late) < 1.25
     B.pc_destroy(ctx)
 
 
