@@ -710,11 +710,10 @@ static bool plan_dma(const MfmaArgs &g, bool flip, const DmaCand &cand, int lgCG
     // itself takes its chunks faster. A chunk takes a fixed time and one for its direct loads of the input, a tile an end; the
     // tensors take their bytes (the input with its border, in pieces of 64) at 6 TB/s (7.9 where they come from the last cache, as
     // in a loop over one layer). Constants for 8, 7, 4 and 2 columns per wavefront, and for the tiles of a lone workgroup, from 5000
-    // timings of 147 layer shapes (1 to 128 images, 4 x 4 to 224 x 224, 8 to 512 channels; 8 % rms). On 160 shapes drawn
-    // afterwards the choice, the register kernels' included, is on average 2.7 % slower than the fastest, the worst 30 % (16 input
-    // channels), and 12 % faster than the fastest of the register kernels. At stride 2 (fits of 139 shapes, 5 to 11 % rms), on 69
-    // others: forward 2 % and 3 % faster, backward-data 3.4 % and 17 % faster (layers of 8 or 16 input channels up to 1.8 times slower
-    // than the best: the cooperative kernel's estimate knows its output channels in blocks of 64 only).
+    // timings of 147 layer shapes (1 to 128 images, 4 x 4 to 224 x 224, 8 to 512 channels; 8 % rms); at stride 2 fits of 139 shapes, 5 to
+    // 11 % rms. On the 713 layers of profiles/plan_timings_bf16.csv, drawn afterwards, the choice, the register and cooperative kernels
+    // included, is 1.5 % behind the fastest at stride 1 (both passes), 1.0 % at stride 2 forward and 0.2 % backward, the worst 20 %;
+    // it is 11 % (stride 1), 4 % and 22 % (stride 2) ahead of the fastest of the kernels without direct loads.
     // What does not fill a round of tiles may be cut in halves or quarters, all of it or what a tile per CU leaves: 56 x 56,
     // 256 -> 256, batch 32 is 784 tiles of 8 columns for 512 workgroups; 512 + 256 tiles and 16 cut into 64 quarters
     // take 73 us instead of 81.

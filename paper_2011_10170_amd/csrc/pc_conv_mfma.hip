@@ -414,16 +414,23 @@ static pc_status run_mfma_conv(pc_ctx *ctx, MfmaArgs g, int ext, int ntaps, cons
                 gw.out_CH = 8;
             }
         }
-        // Up to 16 input channels (one k-step per tap) the cooperative kernel, whose workgroups are short and run several to a
-        // CU, is 0 to 20 % faster while there are at most 10 of its 64 x 64 tiles per CU, and up to 1.7 times slower beyond
-        // (measured on 90 shapes, 8 to 512 output channels).
-        const int64_t coop_tiles = (out_pix + 63) / 64 * ((gw.out_CH + 63) / 64);
-        const bool coop = plan_cfg < 0 && gw.in_CH <= 16 && !pad_in && coop_tiles <= 10 * (int64_t)ctx->num_cu;
-        if ((gw.in_CH & 7) == 0 && !coop) {
+        // Up to 16 input channels (one k-step per tap) the cooperative kernel, whose workgroups are short and run several to a CU, is still
+        // the fastest of some small layers (48 images 45 x 42, 16 -> 16 6.7 us against 7.3): its time (us) is a start, its workgroups per
+        // CU and its output at 4 to 5 TB/s (234 layers, 5 % rms). On 150 drawn afterwards the kernel with the least estimate is 1.3 % behind the
+        // best (profiles/plan_timings_bf16.csv, the cooperative kernel is code 6); the rule before it, at most 10 tiles of 64 x 64 per
+        // CU, was made before there were direct loads and was 11 % behind.
+        double coop_us = 1e30;
+        if (plan_cfg < 0 && gw.in_CH <= 16 && !pad_in) {
+            MfmaArgs t = gw;
+            pc_plan_mfma_tiles(&t, 128, ext);
+            const double wgs = (double)((t.N + t.TI - 1) / t.TI) * t.tiles_y * t.tiles_x * ((gw.out_CH + 63) / 64) / ctx->num_cu, mb = 2e-6 * (double)out_pix * gw.out_CH;
+            coop_us = gw.lstep == 1 ? 3.96 + (wgs > 1.0 ? wgs : 1.0) + 0.208 * mb : 4.4 + 1.09 * (wgs > 1.0 ? wgs : 1.0) + 0.241 * mb;
+        }
+        if ((gw.in_CH & 7) == 0) {
             bool launched = false;
             const int act_here = (fused && !pad_out) ? act : PC_ACT_NONE;
             gw.act_mask = act_here == PC_ACT_RELU_MASK ? act_mask : nullptr;
-            pc_status s = pc_run_mfma_conv_ws(ctx, plan_cfg, gw, ext, tr, tc, inw, outw, wz, sp, &launched, act_here);
+            pc_status s = pc_run_mfma_conv_ws(ctx, plan_cfg, coop_us, gw, ext, tr, tc, inw, outw, wz, sp, &launched, act_here);
             if (s != PC_OK) return s;
             if (launched) {
                 if (fused) *fused = act_here != PC_ACT_NONE;

@@ -1159,7 +1159,7 @@ static bool plan_ks(const MfmaArgs &g, int ext, const KsCand &cand, MfmaArgs *ou
 }
 
 // PC_OK: launched. PC_ERR_UNSUPPORTED without a message: not applicable, the caller uses the other kernel.
-pc_status pc_run_mfma_conv_ws(pc_ctx *ctx, int pcfg, const MfmaArgs &g0, int ext, const int *tr, const int *tc,
+pc_status pc_run_mfma_conv_ws(pc_ctx *ctx, int pcfg, double coop_us, const MfmaArgs &g0, int ext, const int *tr, const int *tc,
                               const uint16_t *in, uint16_t *out, const uint16_t *wz, const SparseOperand &sp, bool *launched, int act)
 {
     *launched = false;
@@ -1219,10 +1219,10 @@ pc_status pc_run_mfma_conv_ws(pc_ctx *ctx, int pcfg, const MfmaArgs &g0, int ext
         size_t lds;
         double est;
         if (!plan_ks(g0, ext, kKs[k], &t, &lds, &est, ctx->num_cu)) continue;
-        if (best_k < 0 || est < best_est) { best = t; best_lds = lds; best_est = est; best_k = k; }
+        if ((best_k < 0 && (pcfg >= 7 || known || est < coop_us)) || (best_k >= 0 && est < best_est)) { best = t; best_lds = lds; best_est = est; best_k = k; }
     }
     if (choice && !known) {
-        const pc_status s = pc_run_mfma_conv_dma(ctx, -1, &lgCG, best_k < 0 ? 1e30 : best_est, g0, tr[0] != 0, in, out, wz, &dma, act);
+        const pc_status s = pc_run_mfma_conv_dma(ctx, -1, &lgCG, best_k < 0 ? coop_us : best_est, g0, tr[0] != 0, in, out, wz, &dma, act);
         *launched = dma != 0;
         if (s == PC_OK) *choice = dma ? dma * 4 + lgCG : best_k < 0 ? 0 : kKs[best_k].code * 4;
         if (s != PC_OK || dma) return s;
@@ -1279,7 +1279,7 @@ pc_status pc_run_mfma_conv_mc(pc_ctx *ctx, int pcfg, const MfmaArgs &g0, const u
         return s;
     }
     // (constants of the time estimate from the measured times of 171 layer shapes, 7 % rms; on 35 others, in the same file as
-    // above, the choice is 3.7 % behind the best on average, the worst 48 %: 40 -> 8 channels, where code 34 would be better)
+    // above, the choice with direct loads is 0.4 % behind the best on average, the worst 10 %)
     static const KsCand kMc[] = {
         {32, 1, 2, 1, 64, 1.24, 321, 3878}, {33, 1, 2, 1, 32, 1.37, 529, 3823}, {34, 1, 2, 1, 16, 1.63, 719, 3829},
         {35, 1, 1, 1, 64, 1.66, 934, 3251}, {36, 1, 1, 1, 32, 1.64, 901, 2974},
@@ -1309,12 +1309,15 @@ pc_status pc_run_mfma_conv_mc(pc_ctx *ctx, int pcfg, const MfmaArgs &g0, const u
     }
     if (pcfg < 0 && !known) {
         // Layers of few workgroups: the cooperative kernel, which spreads the four classes over workgroups of their own, takes
-        // about 4.2 us and 1.4 us per 64-channel chunk for every 1.4 workgroups a CU gets (0.7 us up to 16 channels).
+        // about 4.2 us and 1.4 us per 64-channel chunk for every 1.4 workgroups a CU gets. Up to 16 channels 4.0 us, 0.91 for every
+        // workgroup a CU gets and its output at 6.5 TB/s (66 layers, 6 % rms; on 50 drawn afterwards the choice is 0.3 % behind the best, with
+        // 0.7 us and no output it was 10 %: 73 images 65 x 65, 392 -> 16 107 us where direct loads take 54).
         const bool few = g0.in_CH <= 16;
         MfmaArgs t = g0;
         pc_plan_mfma_tiles(&t, few ? 128 : 64, 2);
         const double wgs = 4.0 * ((t.N + t.TI - 1) / t.TI) * t.tiles_y * t.tiles_x * ((g0.out_CH + 63) / 64) / (ctx->num_cu * (few ? 1.0 : 1.4));
-        const double coop = 4.2 + (few ? 0.7 : 1.4 * ((g0.in_CH + 63) / 64)) * (wgs > 1.0 ? wgs : 1.0);
+        const double busy = wgs > 1.0 ? wgs : 1.0, out_bytes = 2.0 * g0.N * g0.out_H * g0.out_W * g0.out_CH;
+        const double coop = few ? 4.0 + 0.91 * busy + out_bytes / 6.5e6 : 4.2 + 1.4 * ((g0.in_CH + 63) / 64) * busy;
         const bool take = best_code >= 0 && best_est <= coop;
         const pc_status s = pc_run_mfma_conv_dma(ctx, -1, &lgCG, take ? best_est : coop, g0, false, in, out, wz, &dma, PC_ACT_NONE);
         *launched = dma != 0;

@@ -80,8 +80,8 @@ struct SparseOperand {
 inline bool pc_direct_loads(const void *p) { return ((uintptr_t)p & 15) == 0; }
 
 // Wave-specialised forward/backward-data kernel for full 3x3 tap lists. pcfg: -1 = take it when the plan says it
-// wins, >= 7 = the forced variant. *launched stays false when the launch is left to the cooperative kernel.
-pc_status pc_run_mfma_conv_ws(pc_ctx *ctx, int pcfg, const MfmaArgs &g0, int ext, const int *tr, const int *tc,
+// wins, >= 7 = the forced variant. *launched stays false when the launch is left to the cooperative kernel, whose time is coop_us.
+pc_status pc_run_mfma_conv_ws(pc_ctx *ctx, int pcfg, double coop_us, const MfmaArgs &g0, int ext, const int *tr, const int *tc,
                               const uint16_t *in, uint16_t *out, const uint16_t *wz, const SparseOperand &sp, bool *launched,
                               int act = PC_ACT_NONE);
 

@@ -128,6 +128,49 @@ def no_room():
         B.pc_destroy(ctx)
 
 
+def kernel_code(name):
+    """The override code of a forward / backward-data kernel by its symbol."""
+    v = name.split("<")[1].rstrip(">").split(", ")
+    if "conv_ks" in name:
+        return {"2 4 4 64": 7, "2 2 4 64": 8, "2 1 4 64": 9, "2 1 4 128": 14, "1 1 4 128": 15, "2 2 1 32": 16, "2 4 1 16": 17, "2 2 1 16": 18, "1 4 1 32": 19, "2 2 1 64": 20,
+                "2 2 4 128": 21, "1 2 1 64": 24, "1 2 1 32": 25, "1 4 1 16": 26, "1 2 4 128": 27, "1 4 4 64": 28, "1 2 4 64": 29, "2 2 2 32": 30, "2 4 2 16": 31}[" ".join((v[0], v[1], v[4], v[3]))]
+    if "conv_dma" in name:
+        return {"8": 40, "4": 41, "7": 42}[v[0]]
+    if "conv_solo" in name:
+        return {"0 2 4": 43, "0 4 4": 45, "0 2 2": 46, "1 2 4": 47, "1 2 2": 48, "2 2 4": 37, "2 2 2": 38}[" ".join(v[:3])]
+    if "conv_mc" in name:
+        return {"2 64": 32, "2 32": 33, "2 16": 34, "1 64": 35, "1 32": 36}[" ".join(v[:2])]
+    if "conv_ring" in name:
+        return 49
+    return {"2 4 2 2 32": 1, "2 2 2 2 64": 3, "1 2 2 2 64": 4, "1 1 2 2 64": 5, "1 2 2 2 16": 6}[" ".join(v[:4] + v[5:6])]
+
+
+def conv_choice():
+    """The kernel that a forward or backward-data pass goes to against the stored timings of every kernel that takes it; layers of 8 and 16 input
+    channels, where the cooperative kernel (6) is among them, by themselves. Unaligned tensors: against the kernels without direct loads."""
+    times = {}
+    for row in open("profiles/plan_timings_bf16.csv"):
+        f = row.strip().split(",")
+        if f[0] in ("fwd", "bwd_data"):
+            times.setdefault((f[0],) + tuple(int(v) for v in f[1:7]), {})[int(f[7])] = float(f[8])
+    ctx = B.pc_create(0, None)
+    for off in (0, 2):
+        late = {}
+        for k, us in times.items():
+            d, pk = layer(ctx, k[1:])
+            (B.pc_conv_fwd if k[0] == "fwd" else B.pc_conv_bwd_data)(ctx, d, pk, DEV + off, DEV)
+            code = kernel_code(B.pc_last_kernel(ctx))
+            best = min(v for c, v in us.items() if not off or not 37 <= c <= 49)
+            if code in us:      # (what was timed of a layer leaves out kernels that are never near)
+                late.setdefault((k[0], k[6], (k[4] if k[0] == "fwd" else k[5]) <= 16), []).append(us[code] / best)
+            B.pc_packed_free(pk)
+        assert sum(len(v) for v in late.values()) >= 0.95 * len(times)
+        for k, v in late.items():
+            print(off, k, len(v), sum(v) / len(v), max(v))
+            assert len(v) < 10 or (sum(v) / len(v) < (1.025 if off == 0 else 1.05) and max(v) < (1.25 if off == 0 else 1.5)), (off, k)
+    B.pc_destroy(ctx)
+
+
 def wgrad_choice():
     """The kernel that a layer's weight gradient goes to against the stored timings of both (11, 44), with the count read back or not."""
     times = {}
