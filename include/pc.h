@@ -284,13 +284,13 @@ pc_status pc_conv_bwd_weight(pc_ctx *ctx, const pc_conv_desc *desc, const pc_pac
 
 /* pc_conv_bwd_weight for callers that cannot allocate device memory: code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc. Same arguments, same kernels and the same result, bit for bit, as
- * pc_conv_bwd_weight with the same pack state and room for its partial sums (see there); but the partial sums (and the channel-padded copy of a first layer's
- * x) live in a fixed buffer of 32 MiB that the library's code object holds on every GPU it is loaded on until the
- * process ends, and the call makes no hipMalloc / hipFree and grows no context buffer. A layer that needs more
- * (the partial sums take at most 32 MiB; a first layer with C not a multiple of 8 adds N*H*W*16 bytes) is rejected
- * with PC_ERR_UNSUPPORTED before anything is launched. All contexts of a GPU share that one buffer and it keeps the
- * last call's contents (nothing in it needs to start at zero): calls that overlap on one GPU, from different
- * contexts or streams, race; the caller serialises them. */
+ * pc_conv_bwd_weight with the same pack state and room for its partial sums (see there); but the partial sums (and the
+ * channel-padded copy of a first layer's x) live in a fixed buffer of 32 MiB that the library's code object holds on
+ * every GPU it is loaded on until the process ends, and the call makes no hipMalloc / hipFree and grows no context
+ * buffer. A layer that needs more (the partial sums take at most 32 MiB; a first layer with C not a multiple of 8 adds
+ * N*H*W*16 bytes) is rejected with PC_ERR_UNSUPPORTED before anything is launched. All contexts of a GPU share that one
+ * buffer and it keeps the last call's contents (nothing in it needs to start at zero): calls that overlap on one GPU,
+ * from different contexts or streams, race; the caller serialises them. */
 pc_status pc_conv_bwd_weight_noalloc(pc_ctx *ctx, const pc_conv_desc *desc, const pc_packed *pk,
                                      const void *x_dev, const void *dy_dev, float *dw_compact_dev);
 

@@ -487,7 +487,8 @@ pc_mfma_conv_solo_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__
 // multiplies 64 channels x 64 pixels, so that a chunk reads 252 KiB of LDS where two tiles of 64 channels read 360, and an input
 // tile is loaded once for 128 channels. 1.56 us a chunk (0.96 of matrix instructions; LDS 1.2 and a wait at every row). 64 images, us,
 // with the best of the other kernels -> here: 56 x 56 64 -> 128 16.1 -> 14.8, 128 -> 128 25.7 -> 23.6, 28 x 28 128 -> 256 12.6 -> 11.7; 11
-// images 52 x 53 232 -> 480 27.6 -> 22.9; fastest of all on 33 of 139 drawn layers.
+// images 52 x 53 232 -> 480 27.6 -> 22.9; fastest of all on 9 of the 148 drawn layers in
+// profiles/plan_timings_bf16.csv.
 #define DR_B 44                      // direct loads of an input tile: 6 and 5 per wavefront in the first two steps of a chunk
 #define DR_W (2 * DR_B * 1024)       // where the ring begins
 #define DR_SLOT (24 * 1024)

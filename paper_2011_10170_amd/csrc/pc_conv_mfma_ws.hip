@@ -1143,9 +1143,9 @@ static bool plan_ks(const MfmaArgs &g, int ext, const KsCand &cand, MfmaArgs *ou
     // of 64 bytes. The constants (factor, item and tile cycles per kernel, the shared ones here) are a least-squares fit over
     // the measured times of every kernel on 355 layer shapes (1 to 128 images, 4 x 4 to 224 x 224, 8 to 512 channels, both
     // strides, back to back): 5 % rms over 11 500 timings. The kernel with the least estimate is on average 2 % slower than
-    // the fastest of a shape; the rule it replaces, made for channel counts from 64 up, 22 %. On 110 layers drawn afterwards
-    // (profiles/plan_timings_bf16.csv, every kernel on every layer: what a new fit starts from) 1.4 % at stride 1 and 4.7 % at
-    // stride 2, the worst 33 %.
+    // the fastest of a shape; the rule it replaces, made for channel counts from 64 up, 22 %. On the layers of
+    // profiles/plan_timings_bf16.csv, drawn afterwards and timed on every kernel, the choice without direct loads is 1.0 % behind the
+    // best such kernel at stride 1 and 1.9 % at stride 2, the worst 30 %.
     const double rounds = (double)((total + num_cu - 1) / num_cu);
     const double mfma = 9.0 * (kc / 16) * at * bt * 32.0 / (ksp == 4 ? 4 : 1) * cand.mfma, stage = t.nelem * 16.0 * 0.0418;
     const double end = cand.tile + 2.0 * rows * t.TI * t.TH * t.TW * 0.0143;
