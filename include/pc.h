@@ -135,7 +135,7 @@ pc_status pc_set_variant(pc_ctx *ctx, pc_variant v);
  *   47, 48, 49  the same at stride 2, forward: x 128 and 64 pixels; 128 output channels x 128 pixels
  *   37, 38 the same for stride-2 backward-data (the other passes stay automatic): x 4 x 128 and 4 x 64 pixels
  *   10, 11, 44 backward-weight: the cooperative / the wave-specialised kernel / the kernel with direct loads (the other passes stay
- *          automatic)
+ *          automatic); with 44 and one layer, split_k 0 to 3 are tiles of 64 x 64, 32 x 64, 64 x 32 and 32 x 32 (filter, channel)
  *   22     forward/backward-data: the structured-sparse kernel (packs made under PC_VARIANT_MFMA_SPARSE only)
  *   23     the first-layer kernels (stride 1, at most 4 input channels): the automatic choice takes them wherever
  *          they apply; any other code here keeps such a layer on the general kernels

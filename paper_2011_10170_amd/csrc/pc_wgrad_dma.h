@@ -4,7 +4,9 @@
 #include "pc_mfma.h"
 
 #define WD_LDS_MAX (80 * 1024)       // two workgroups per CU
+#define WD_LDS_SUMS (4 * 18 * 1024)  // in which wavefronts that share pixels add their sums
 #define WD_GROUP_MAX 20
+#define WD_WAVES 4                   // arrangements of a workgroup's wavefronts
 
 struct WgradDmaArgs {
     int32_t N, H, W, C, F, Ho, Wo, stride;
@@ -14,7 +16,12 @@ struct WgradDmaArgs {
     int32_t tiles_c, n_ktiles, ksplit, pstride;
     uint32_t x_bytes, dy_bytes;
     uint32_t mg_tc, mg_Ho, mg_H1;
+    int32_t waves, lgPC, NC;         // arrangement of the wavefronts; of those that share pixels side by side (log2), each with NC columns
+    // set at the launch: tiles of the layer, and how a workgroup's index is read, so that those of an XCD share as few pixel splits as possible
+    int32_t T, place, lgks;
+    uint32_t mg_T, mg_gx;
 };
+enum { WD_PLACE_PLAIN, WD_PLACE_MANY, WD_PLACE_FEW };
 
 struct WgradDmaLayer {
     WgradDmaArgs a;
@@ -24,14 +31,27 @@ struct WgradDmaLayer {
     int32_t gx, gy;
 };
 
-struct WgradDmaGroup {
+template <int LAYERS> struct WgradDmaLayers {
     int32_t n;
     int32_t blk0[WD_GROUP_MAX + 1];
-    WgradDmaLayer layer[WD_GROUP_MAX];
+    WgradDmaLayer layer[LAYERS];
+};
+typedef WgradDmaLayers<1> WgradDmaOne;
+typedef WgradDmaLayers<WD_GROUP_MAX> WgradDmaGroup;
+
+struct WgradDmaPlan {
+    WgradDmaArgs a;
+    int ct, ft;                      // tiles of channels and of filters
+    int steps, loads;                // of a pixel tile: steps of 36 matrix instructions and direct loads per wavefront
+    size_t lds;
+    double tile_us;                  // estimated time of a pixel tile (us) while two workgroups share a CU
 };
 
-// Plan of one layer (ksplit left to the caller); false when the layer is outside what the kernel takes. *tile_us: estimated time of a
-// pixel tile (us) while two workgroups share a CU.
-bool pc_wgrad_dma_plan(const pc_conv_desc *d, int64_t nslots, WgradDmaArgs *out, int *ct, int *ft, size_t *lds, double *tile_us);
-pc_status pc_wgrad_dma_launch(pc_ctx *ctx, const WgradDmaGroup &g, size_t lds);
+// Plan of one layer of a grouped call (ksplit left to the caller), and of a layer's own call; false when the layer is outside what the kernel
+// takes. kept: kernels whose partial sums are written and read; waves: the arrangement to take, -1 = any; *choice: the plan made before
+// for this layer, or -1 and the plan's code on return (choice may be null).
+bool pc_wgrad_dma_plan(const pc_conv_desc *d, int64_t nslots, WgradDmaPlan *out);
+bool pc_wgrad_dma_plan_one(const pc_conv_desc *d, int64_t nslots, double kept, int num_cu, int waves, int32_t *choice, WgradDmaPlan *out);
+pc_status pc_wgrad_dma_launch(pc_ctx *ctx, WgradDmaOne &g, size_t lds);
+pc_status pc_wgrad_dma_launch(pc_ctx *ctx, WgradDmaGroup &g, size_t lds);
 #endif

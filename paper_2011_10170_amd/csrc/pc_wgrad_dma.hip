@@ -2,6 +2,8 @@
 // itself, the splits of the pixels and the partial planes).
 #include "pc_wgrad_dma.h"
 
+#include <math.h>
+
 // dW[t][f][c] = sum over output pixels of dy[pixel][f] * x[pixel shifted by tap t][c]. A workgroup of 4 wavefronts owns a tile of 64
 // filters x 64 channels, a wavefront 32 x 32 of it for all nine taps (144 accumulator registers), and walks tiles of TR rows x TC
 // columns of output pixels; two workgroups share a CU, one loads (or writes its sums) while the other multiplies.
@@ -15,6 +17,13 @@
 //   Rows: the output rows of all images in order; the x rows of images of H + 1 rows, one zero row between two of them, so a tile
 //     covers any TR rows. Rows past the last one are zeros on both sides.
 //   A staged row is its pixels' 128 bytes (64 channels) and a pad, so that the rows a transposing read takes start in different banks.
+//   Layers whose last tile of 64 filters or channels would be half empty take tiles of 32: the wavefronts that are then left over share the
+//     tile's pixels (rows or columns of it), and their sums are added in LDS. 34 images 209 x 208, 32 -> 8: 65 -> 38 us; 50 images
+//     80 x 80, 144 -> 80: 98 -> 80.
+//   What a small layer's call spends (5 images 14 x 14, 48 -> 24, 8.5 us; stamps of one lane): arguments and zeros 0.65, first loads 1.9,
+//     products 0.9 to 2.6 (a tile of 64 rows is 16 steps, of 32 x 1 one), look-up table 0.8, pick of the kept taps and stores 2.3. Hence
+//     small tiles and many splits for small layers, the table's lines touched at the start, a pick of 41 instructions a kernel instead
+//     of 54, and arguments of 300 bytes: 13 images 33 x 47, 40 -> 72 13.6 -> 12.4 us with the partial planes added.
 #define WD_OOB 0x80000000u
 
 typedef short i16x4 __attribute__((ext_vector_type(4)));
@@ -57,44 +66,67 @@ __device__ __forceinline__ bf16x8 wd_frag(const unsigned char *p0, const unsigne
     return o;
 }
 
+// (a uniform choice between registers, which cannot be indexed)
+__device__ __forceinline__ f32x4 wd_pick(bool second, const f32x4 &p, const f32x4 &q)
+{
+    f32x4 o;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) o[i] = second ? q[i] : p[i];
+    return o;
+}
+
 // lin: index of the workgroup in the layer's grid of gx x gy tiles x ksplit splits (x fastest).
-template <int ST>
+// FW, CW: wavefronts side by side along the filters and the channels of the workgroup's tile; the other 4 / (FW * CW) share the tile's pixels.
+template <int ST, int FW, int CW>
 __device__ __forceinline__ void pc_wgrad_dma_body(const uint16_t *__restrict__ x, const uint16_t *__restrict__ dy, const WgradDmaArgs &a,
-                                                  const uint32_t *__restrict__ kinfo, float *__restrict__ partial, float *__restrict__ dw, int lin,
-                                                  int gx, int gy)
+                                                  const uint32_t *__restrict__ kinfo, float *__restrict__ partial, float *__restrict__ dw, int lin, int gx)
 {
     extern __shared__ __align__(16) unsigned char lds[];
+    constexpr int PW = 4 / (FW * CW), XB = 64 * CW, DB = 64 * FW;      // bytes per staged pixel of x and of dy
+    constexpr int XL = 4 * CW, DL = 4 * FW;                             // lanes of a direct load per pixel
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // workgroups of an XCD share as few pixel splits as possible (as in pc_mfma_wgrad_ws_body)
-    int bx = lin % gx, by = (lin / gx) % gy, bz = lin / (gx * gy);
-    {
-        const int T = gx * gy, ks = a.ksplit;
-        const int xcd = lin & 7, r = lin >> 3;
-        int tile = -1;
-        if ((ks & 7) == 0) {
-            tile = r % T;
-            bz = (r / T) * 8 + xcd;
-        } else if (ks < 8 && (8 % ks) == 0 && (T % (8 / ks)) == 0) {
-            bz = xcd % ks;
-            tile = r * (8 / ks) + xcd / ks;
-        }
-        if (tile >= 0) { bx = tile % gx; by = tile / gx; }
+    int bz = lin >> 3, tile = lin & 7;
+    if (a.place == WD_PLACE_MANY) {              // 8, 16, .. splits: an XCD's in order
+        const int q = (int)pc_udiv((uint32_t)bz, a.mg_T);
+        const int xcd = tile;
+        tile = bz - q * a.T;
+        bz = q * 8 + xcd;
+    } else if (a.place == WD_PLACE_FEW) {        // 1, 2 or 4 splits: 8 / ksplit XCDs share one
+        const int xcd = tile;
+        tile = ((bz << 3) >> a.lgks) + (xcd >> a.lgks);
+        bz = xcd & (a.ksplit - 1);
+    } else {
+        bz = (int)pc_udiv((uint32_t)lin, a.mg_T);
+        tile = lin - bz * a.T;
     }
-    const int c0 = bx * 64, f0 = by * 64;
-    const int fw = w & 1, cw = w >> 1;
+    const int by = (int)pc_udiv((uint32_t)tile, a.mg_gx), bx = tile - by * gx;
+    const int c0 = bx * (32 * CW), f0 = by * (32 * FW);
+    const int fw = w % FW, cw = w / FW % CW, pw = w / (FW * CW);
     const v4u32 xs = wd_rsrc(x, a.x_bytes), ds = wd_rsrc(dy, a.dy_bytes);
     const int x_row = wd_keep(a.W * a.C * 2), d_row = wd_keep(a.Wo * a.F * 2);       // bytes per row
     const int H1 = wd_keep(a.H + 1), nimg = wd_keep(a.N), rows = wd_keep(a.rows), nrow = wd_keep(a.nrow), TR = wd_keep(a.TR), TC = a.TC, IW = a.IW,
               RPx = wd_keep(a.RPx), RPd = wd_keep(a.RPd), dy_off = a.dy_off, n_ktiles = a.n_ktiles, ksplit = a.ksplit;
-    // lanes of the loads of a row: 8 a pixel
-    const uint64_t mask_a = IW >= 8 ? ~0ull : (1ull << (8 * IW)) - 1, mask_b = IW > 8 ? ~0ull >> (64 - 8 * (IW - 8)) : 0,
-                   mask_d = TC >= 8 ? ~0ull : (1ull << (8 * TC)) - 1;
-    const bool x_ok = c0 + (lane & 7) * 8 < a.C, d_ok = f0 + (lane & 7) * 8 < a.F;
+    // The wavefronts that share pixels: 1 << lgPC side by side, each with NC columns, the others below each other
+    const int col0 = PW > 1 ? (pw & ((1 << a.lgPC) - 1)) * a.NC : 0, left = TC - col0, nc = PW > 1 ? wd_keep(left < a.NC ? left : a.NC) : TC,
+              ncx = PW > 1 ? wd_keep(nc + 2) : IW;      // (two numbers to the compiler)
+    // lanes of the loads of a row
+    const uint64_t mask_a = IW * XL >= 64 ? ~0ull : (1ull << (XL * IW)) - 1, mask_b = IW * XL > 64 ? ~0ull >> (128 - XL * IW) : 0,
+                   mask_d = TC * DL >= 64 ? ~0ull : (1ull << (DL * TC)) - 1;
+    const bool x_ok = c0 + (lane & (XL - 1)) * 8 < a.C, d_ok = f0 + (lane & (DL - 1)) * 8 < a.F;
     // where this lane's transposing reads start inside 4 pixels' rows (4 of 16 channels or filters), and the first row it reads
     // (stride 2: the 32 reduction entries are 16 rows of two columns that follow each other, for less LDS per tile)
     constexpr int KROWS = ST == 1 ? 32 : 16;
     const int sub = (lane & 3) * 8, krow = 8 * ((lane >> 4) & (KROWS / 8 - 1)) + ((lane & 15) >> 2), kcol = ST == 1 ? 0 : lane >> 5;
+    const int h_first = PW > 1 ? (left > 0 ? (pw >> a.lgPC) * KROWS : TR) : 0, h_step = PW > 1 ? wd_keep((PW >> a.lgPC) * KROWS) : KROWS;
+
+    // The look-up table of the epilogue comes from L2 then: every 128-byte line of the tile's rows is touched now.
+    uint32_t touched = 0;
+    if ((int)threadIdx.x < 32 * FW * CW) {
+        const int f = f0 + (int)threadIdx.x / CW, c = c0 + (int)threadIdx.x % CW * 32;
+        if (f < a.F && c < a.C) touched = kinfo[(int64_t)f * a.C + c];
+    }
 
     f32x4 acc[9][2][2];       // tap, filter half, channel half of the wavefront's 32 x 32
 #pragma unroll
@@ -108,15 +140,14 @@ __device__ __forceinline__ void pc_wgrad_dma_body(const uint16_t *__restrict__ x
         if (kt != bz) asm volatile("s_barrier" ::: "memory");      // every wavefront has read what the loads replace
         __builtin_amdgcn_s_setprio(3);
         {
-            // a wavefront's load brings 8 pixels of a row, the x columns past the 8th come in a second one
-            const int col = lane >> 3;
+            // a wavefront's load brings 64 / XL pixels of a row, the x columns past them come in a second one
             uint32_t vx[2];
 #pragma unroll
             for (int p = 0; p < 2; ++p) {
-                const int xx = x0 * ST - 1 + p * 8 + col;
-                vx[p] = x_ok && (unsigned)xx < (unsigned)a.W ? (uint32_t)(xx * a.C + c0 + (lane & 7) * 8) * 2u : WD_OOB;
+                const int xx = x0 * ST - 1 + p * (64 / XL) + lane / XL;
+                vx[p] = x_ok && (unsigned)xx < (unsigned)a.W ? (uint32_t)(xx * a.C + c0 + (lane & (XL - 1)) * 8) * 2u : WD_OOB;
             }
-            const uint32_t vd = d_ok && x0 + col < a.Wo ? (uint32_t)((x0 + col) * a.F + f0 + (lane & 7) * 8) * 2u : WD_OOB;
+            const uint32_t vd = d_ok && x0 + lane / DL < a.Wo ? (uint32_t)((x0 + lane / DL) * a.F + f0 + (lane & (DL - 1)) * 8) * 2u : WD_OOB;
             // row y of an image is row y + 1 of the padded image, row 0 is zeros
             int v = V0 + w, n = (int)pc_udiv((uint32_t)v, a.mg_H1), y1 = v - n * H1, at = w * RPx;
             for (int row = w; row < nrow; row += 4) {
@@ -139,21 +170,21 @@ __device__ __forceinline__ void pc_wgrad_dma_body(const uint16_t *__restrict__ x
         }
         __builtin_amdgcn_s_setprio(0);
         asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
-        for (int hh = 0; hh < TR; hh += KROWS) {
+        for (int hh = h_first; hh < TR; hh += h_step) {
             const unsigned char *pr[3][2], *pd[2];
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
                 const int k = hh + krow + 4 * q, rho = r0 + k, n = (int)pc_udiv((uint32_t)rho, a.mg_Ho);
-                pr[0][q] = lds + (n * H1 + (rho - n * a.Ho) * ST - V0) * RPx + cw * 64 + sub + kcol * (ST * 128);
+                pr[0][q] = lds + (n * H1 + (rho - n * a.Ho) * ST - V0) * RPx + cw * 64 + sub + (kcol + col0) * (ST * XB);
                 pr[1][q] = pr[0][q] + RPx;
                 pr[2][q] = pr[1][q] + RPx;
-                pd[q] = lds + dy_off + k * RPd + fw * 64 + sub + kcol * 128;
+                pd[q] = lds + dy_off + k * RPd + fw * 64 + sub + (kcol + col0) * DB;
             }
             bf16x8 xq[3][2], dq[4][2];
-            auto read_x = [&](int r, int h, int col) __attribute__((always_inline)) { xq[r][h] = wd_frag(pr[r][0] + col * 128 + h * 32, pr[r][1] + col * 128 + h * 32); };
+            auto read_x = [&](int r, int h, int col) __attribute__((always_inline)) { xq[r][h] = wd_frag(pr[r][0] + col * XB + h * 32, pr[r][1] + col * XB + h * 32); };
             auto read_d = [&](int col) __attribute__((always_inline)) {
 #pragma unroll
-                for (int h = 0; h < 2; ++h) dq[col & 3][h] = wd_frag(pd[0] + col * 128 + h * 32, pd[1] + col * 128 + h * 32);
+                for (int h = 0; h < 2; ++h) dq[col & 3][h] = wd_frag(pd[0] + col * DB + h * 32, pd[1] + col * DB + h * 32);
             };
             read_d(0);
 #pragma unroll
@@ -163,7 +194,7 @@ __device__ __forceinline__ void pc_wgrad_dma_body(const uint16_t *__restrict__ x
 #pragma unroll
                 for (int u = 0; u < 9; ++u) {
                     const int c = 2 * (u / 3), q = u % 3;
-                    if (c < TC) {
+                    if (c < nc) {
                         if (q == 0 && u + 3 < 9) read_d(c + 2);
                         if (u == 3) __builtin_amdgcn_s_setprio(1);
                         if (u == 6) __builtin_amdgcn_s_setprio(2);
@@ -186,10 +217,10 @@ __device__ __forceinline__ void pc_wgrad_dma_body(const uint16_t *__restrict__ x
                 }
                 continue;
             }
-            constexpr int LAST = 9;              // last x column of a tile of 8
+            constexpr int LAST = 9;              // last x column of 8 output columns
 #pragma unroll
             for (int X = 0; X <= LAST; ++X) {
-                if (X < IW) {
+                if (X < ncx) {
                     // (past the tile's last column, up to three columns on: the row's pad, the next row or the room the plan leaves after
                     // the last one; not used. The x columns past a row's last one run into the next row, or into dy.)
                     if (X + 1 < 8) read_d(X + 1);
@@ -200,7 +231,7 @@ __device__ __forceinline__ void pc_wgrad_dma_body(const uint16_t *__restrict__ x
                         const int j = X - q;                              // output column X is tap column q of
                         if (j < 0 || j > 7) continue;
                         const bool final = j == 0 || q == 2;              // the last taps column X takes part in: its operands are replaced
-                        if (j < TC) {
+                        if (j < nc) {
 #pragma unroll
                             for (int i = 0; i < 6; ++i) {
 #pragma unroll
@@ -222,21 +253,65 @@ __device__ __forceinline__ void pc_wgrad_dma_body(const uint16_t *__restrict__ x
         }
     }
     __builtin_amdgcn_s_setprio(3);
-    // Epilogue: a lane holds all nine taps of its 16 kernels; the 4 kept ones of a kept kernel move down in place and are written in
-    // compact slot order. (Tap by tap from the last: a kept one becomes the first of the kept values and moves the others up.)
-    float *pout = a.ksplit > 1 ? partial + (int64_t)bz * a.pstride * 4 : dw;
-    uint32_t info[16];
+    asm volatile("" :: "v"(touched));
+    // Wavefronts that shared pixels add their sums through LDS, halves of the 32 x 32 at a time: partners swap the filter halves (a wavefront
+    // keeps one), of four then also the channel halves. What is left to write is 4 / PW blocks of 16 x 16, block b in acc[..][b >> 1][b & 1].
+    int fh = 0, ch = 0;       // the halves kept
+    if constexpr (PW > 1) {
+        f32x4 *mine = reinterpret_cast<f32x4 *>(lds) + w * (18 * 64) + lane;
+        const f32x4 *theirs = reinterpret_cast<const f32x4 *>(lds) + (w ^ (FW * CW)) * (18 * 64) + lane;
+        fh = pw & 1;
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        const int f = f0 + fw * 32 + (k >> 3) * 16 + 4 * (lane >> 4) + (k & 3), c = c0 + cw * 32 + ((k >> 2) & 1) * 16 + (lane & 15);
-        info[k] = f < a.F && c < a.C ? kinfo[(int64_t)f * a.C + c] : 0xFFFFFFFFu;
+        for (int t = 0; t < 9; ++t)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                mine[(t * 2 + c) * 64] = wd_pick(fh == 0, acc[t][0][c], acc[t][1][c]);
+                acc[t][0][c] = wd_pick(fh != 0, acc[t][0][c], acc[t][1][c]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < 9; ++t)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                acc[t][0][c] += theirs[(t * 2 + c) * 64];
+                if (t % 3 == 2) __builtin_amdgcn_sched_barrier(0);
+            }
+    }
+    if constexpr (PW > 2) {
+        f32x4 *mine = reinterpret_cast<f32x4 *>(lds) + w * (9 * 64) + lane;
+        const f32x4 *theirs = reinterpret_cast<const f32x4 *>(lds) + (w ^ 2) * (9 * 64) + lane;
+        ch = pw >> 1;
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < 9; ++t) {
+            mine[t * 64] = wd_pick(ch == 0, acc[t][0][0], acc[t][0][1]);
+            acc[t][0][0] = wd_pick(ch != 0, acc[t][0][0], acc[t][0][1]);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < 9; ++t) acc[t][0][0] += theirs[t * 64];
+    }
+    // Epilogue: a lane holds all nine taps of its 16 / PW kernels; the 4 kept ones of a kept kernel move down in place and are written in
+    // compact slot order. (Tap by tap from the last: a kept one becomes the first of the kept values and moves the others up.)
+    constexpr int NK = 16 / PW;
+    float *pout = a.ksplit > 1 ? partial + (int64_t)bz * a.pstride * 4 : dw;
+    uint32_t info[NK];
+#pragma unroll
+    for (int k = 0; k < NK; ++k) {       // (all loads at once: clamped, not under a condition)
+        const int f = f0 + fw * 32 + (PW > 1 ? fh : k >> 3) * 16 + 4 * (lane >> 4) + (k & 3), c = c0 + cw * 32 + (PW > 2 ? ch : (k >> 2) & 1) * 16 + (lane & 15);
+        const bool in = f < a.F && c < a.C;
+        const uint32_t u = kinfo[in ? (uint32_t)f * (uint32_t)a.C + (uint32_t)c : 0u];
+        info[k] = in ? u : 0xFFFFFFFFu;
     }
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
+    for (int k = 0; k < NK; ++k) {
         float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+        uint32_t m = info[k] << 23;
 #pragma unroll
         for (int t = 8; t >= 0; --t) {
-            const bool kept = info[k] >> t & 1u;
+            const bool kept = __builtin_uadd_overflow(m, m, &m);       // (tap t's bit: one addition that shifts it out)
             o.w = kept ? o.z : o.w;
             o.z = kept ? o.y : o.z;
             o.y = kept ? o.x : o.y;
@@ -246,72 +321,198 @@ __device__ __forceinline__ void pc_wgrad_dma_body(const uint16_t *__restrict__ x
     }
 }
 
+// One layer. Its arguments are 250 bytes; those of a network (below) are 4 KiB, which a launch copies and every workgroup searches.
+template <int ST, int FW, int CW>
+__global__ void __launch_bounds__(256, 2) pc_mfma_wgrad_dma_kernel(WgradDmaOne g)
+{
+    const WgradDmaLayer &y = g.layer[0];
+    pc_wgrad_dma_body<ST, FW, CW>(y.x, y.dy, y.a, y.kinfo, y.partial, y.dw, (int)blockIdx.x, y.gx);
+}
+
 // The layers of a network in one launch: workgroup b serves workgroup b - blk0[l] of layer l (blk0 entries are multiples of 8).
-__global__ void __launch_bounds__(256, 2) pc_mfma_wgrad_dma_kernel(WgradDmaGroup g)
+__global__ void __launch_bounds__(256, 2) pc_mfma_wgrad_dma_group_kernel(WgradDmaGroup g)
 {
     const int l = pc_batch_find(g.blk0, g.n, (int)blockIdx.x);
     const WgradDmaLayer &y = g.layer[l];
     const int lin = (int)blockIdx.x - g.blk0[l];
     if (lin >= y.gx * y.gy * y.a.ksplit) return;
-    if (y.a.stride == 1) pc_wgrad_dma_body<1>(y.x, y.dy, y.a, y.kinfo, y.partial, y.dw, lin, y.gx, y.gy);
-    else pc_wgrad_dma_body<2>(y.x, y.dy, y.a, y.kinfo, y.partial, y.dw, lin, y.gx, y.gy);
+    if (y.a.stride == 1) pc_wgrad_dma_body<1, 2, 2>(y.x, y.dy, y.a, y.kinfo, y.partial, y.dw, lin, y.gx);
+    else pc_wgrad_dma_body<2, 2, 2>(y.x, y.dy, y.a, y.kinfo, y.partial, y.dw, lin, y.gx);
 }
 
-bool pc_wgrad_dma_plan(const pc_conv_desc *d, int64_t nslots, WgradDmaArgs *out, int *ct, int *ft, size_t *lds, double *tile_us)
+// Wavefronts along the filters and the channels of a workgroup's tile
+static const struct { int fw, cw, lgPW; } kWaves[WD_WAVES] = {{2, 2, 0}, {1, 2, 1}, {2, 1, 1}, {1, 1, 2}};     // (lgPW: log2 of those that share pixels)
+
+static int wd_placed(int T, int ks) { return ks % 8 == 0 ? WD_PLACE_MANY : 8 % ks == 0 && T % (8 / ks) == 0 ? WD_PLACE_FEW : WD_PLACE_PLAIN; }
+
+// The part of a layer's plan that does not depend on its tiles; false when the layer is outside what the kernel takes.
+static bool wd_layer(const pc_conv_desc *d, int64_t nslots, WgradDmaArgs &a)
 {
-    WgradDmaArgs a;
     memset(&a, 0, sizeof(a));
     const int st = d->stride;
-    if ((d->C & 7) || (d->F & 7)) return false;
     a.N = d->N; a.H = d->H; a.W = d->W; a.C = d->C; a.F = d->F; a.stride = st;
     a.Ho = (d->H - 1) / st + 1; a.Wo = (d->W - 1) / st + 1;
     const int64_t xb = (int64_t)a.N * a.H * a.W * a.C * 2, db = (int64_t)a.N * a.Ho * a.Wo * a.F * 2, rows = (int64_t)a.N * a.Ho;
-    if (xb >= ((int64_t)1 << 31) || db >= ((int64_t)1 << 31) || rows >= (1 << 24)) return false;
+    if ((d->C & 7) || (d->F & 7) || xb >= ((int64_t)1 << 31) || db >= ((int64_t)1 << 31) || rows >= (1 << 24)) return false;
+    if ((rows + 64) * a.Ho >= ((int64_t)1 << 32) || ((int64_t)a.N + 66) * (a.H + 1) * (a.H + 1) >= ((int64_t)1 << 32)) return false;
     a.x_bytes = (uint32_t)xb; a.dy_bytes = (uint32_t)db;
     a.rows = (int)rows;
-    double best = -1.0;
-    const int krows = st == 1 ? 32 : 16, cstep = st;      // rows and columns of a step
-    for (int TR = krows; TR <= 64; TR += krows)
-        for (int tcn = cstep; tcn <= (st == 1 ? 8 : 6) && tcn < a.Wo + cstep; tcn += cstep)
-            for (int pad = 32; pad >= 0; pad -= 32) {
-                // image boundaries inside a tile (tiles start at multiples of TR); rows past the last image lie as if more images followed
-                const int cross = a.Ho % TR == 0 ? 0 : TR % a.Ho == 0 ? TR / a.Ho - 1 : (TR - 1 + a.Ho - 1) / a.Ho;
-                const int nrow = st * (TR - 1) + 3 + cross * (a.H + 1 - st * a.Ho);
-                const int IW = st * (tcn - 1) + 3, RPx = IW * 128 + (st == 1 ? 32 : 16), RPd = tcn * 128 + pad;
-                // columns of dy that are read past the end of a row: three, none past the eighth (stride 1), or the next pair (stride 2)
-                const int past = st == 1 ? (tcn + 3 < 8 ? 3 : 8 - tcn) : tcn < 6 ? 2 : 0, room = past * 128 > pad ? past * 128 - pad : 0;
-                if (nrow * RPx + TR * RPd + room > WD_LDS_MAX) continue;
-                const int tc_n = (a.Wo + tcn - 1) / tcn, tr_n = (int)((rows + TR - 1) / TR);
-                const double fill = (double)rows * a.Wo / ((double)tr_n * TR * tc_n * tcn);
-                const double mfma = TR / 32.0 * tcn * 36 * 16, load = ((double)nrow * IW + (double)TR * tcn) * 128 / 30.0;   // cycles
-                const double eff = fill * mfma / ((mfma > load ? mfma : load) + 300 + 150.0 * (TR / 16));
-                if (eff > best) {
-                    best = eff;
-                    a.TR = TR; a.TC = tcn; a.IW = IW; a.nrow = nrow; a.RPx = RPx; a.RPd = RPd; a.dy_off = nrow * RPx;
-                    a.tiles_c = tc_n; a.n_ktiles = tr_n * tc_n;
-                    *lds = (size_t)(nrow * RPx + TR * RPd + room);
-                }
-            }
-    if (best < 0.0) return false;
-    if ((rows + 64) * a.Ho >= ((int64_t)1 << 32) || ((int64_t)a.N + 66) * (a.H + 1) * (a.H + 1) >= ((int64_t)1 << 32) ||
-        (int64_t)a.n_ktiles * a.tiles_c >= ((int64_t)1 << 32)) return false;
     a.pstride = (int32_t)nslots;
-    a.mg_tc = pc_udiv_magic(a.tiles_c); a.mg_Ho = pc_udiv_magic(a.Ho); a.mg_H1 = pc_udiv_magic(a.H + 1);
-    *tile_us = 0.55 * (a.TR / krows) * (a.TC / cstep) + 1.3;
-    *ct = (a.C + 63) / 64;
-    *ft = (a.F + 63) / 64;
-    *out = a;
+    a.mg_Ho = pc_udiv_magic(a.Ho); a.mg_H1 = pc_udiv_magic(a.H + 1);
     return true;
 }
 
-pc_status pc_wgrad_dma_launch(pc_ctx *ctx, const WgradDmaGroup &g, size_t lds)
+// The plan with this arrangement of the wavefronts, 1 << lgPC of those that share pixels side by side with nc columns each, in tiles of TR
+// rows; false when it does not fit.
+static bool wd_tile(const WgradDmaArgs &layer, int waves, int lgPC, int TR, int nc, WgradDmaPlan *out)
 {
-    static pc_per_device_once attr;
+    WgradDmaPlan p;
+    p.a = layer;
+    WgradDmaArgs &a = p.a;
+    const int st = a.stride, krows = st == 1 ? 32 : 16, fw = kWaves[waves].fw, cw = kWaves[waves].cw, lgPW = kWaves[waves].lgPW, XB = 64 * cw, DB = 64 * fw;
+    a.waves = waves; a.lgPC = lgPC; a.TR = TR; a.NC = nc;
+    // (columns of wavefronts past the map's last one are not staged)
+    const int wide = (a.Wo + st - 1) / st * st;
+    a.TC = nc << lgPC < wide ? nc << lgPC : wide;
+    a.IW = st * (a.TC - 1) + 3;
+    if (a.TC * DB > 1024 || a.IW * XB > 2048) return false;       // a row of dy is one direct load, a row of x at most two
+    // image boundaries inside a tile (tiles start at multiples of TR); rows past the last image lie as if more images followed
+    const int cross = a.Ho % TR == 0 ? 0 : TR % a.Ho == 0 ? TR / a.Ho - 1 : (TR - 1 + a.Ho - 1) / a.Ho;
+    a.nrow = st * (TR - 1) + 3 + cross * (a.H + 1 - st * a.Ho);
+    a.RPx = a.IW * XB + (st == 1 ? 32 : 16);
+    a.dy_off = a.nrow * a.RPx;
+    // columns of dy that are read past the end of a row: three, none past a wavefront's eighth (stride 1), or the next pair (stride 2)
+    const int past = st == 1 ? (nc + 3 < 8 ? 3 : 8 - nc) : nc < 6 ? 2 : 0;
+    for (int pad = 32;; pad = 0) {
+        a.RPd = a.TC * DB + pad;
+        p.lds = (size_t)(a.dy_off + TR * a.RPd + (past * DB > pad ? past * DB - pad : 0));
+        if (p.lds <= WD_LDS_MAX) break;
+        if (pad == 0) return false;
+    }
+    if (lgPW && p.lds < WD_LDS_SUMS) p.lds = WD_LDS_SUMS;
+    a.tiles_c = (a.Wo + a.TC - 1) / a.TC;
+    a.n_ktiles = (a.rows + TR - 1) / TR * a.tiles_c;
+    if ((int64_t)a.n_ktiles * a.tiles_c >= ((int64_t)1 << 32)) return false;
+    a.mg_tc = pc_udiv_magic(a.tiles_c);
+    p.ct = (a.C + 32 * cw - 1) / (32 * cw);
+    p.ft = (a.F + 32 * fw - 1) / (32 * fw);
+    p.steps = (TR / krows >> (lgPW - lgPC)) * (nc / st);
+    p.loads = (a.nrow * (a.IW * XB > 1024 ? 2 : 1) + TR + 3) / 4;
+    *out = p;
+    return true;
+}
+
+// `use` is called with every plan that fits (of one arrangement of the wavefronts: only >= 0). Tiles of 32 filters or channels are for layers
+// whose last tile of 64 would be half empty: elsewhere they were the fastest by 0.6 % on average.
+template <class Use> static void wd_plans(const WgradDmaArgs &layer, int only, Use use)
+{
+    const int st = layer.stride, krows = st == 1 ? 32 : 16;
+    WgradDmaPlan p;
+    for (int w = 0; w < WD_WAVES; ++w) {
+        if (only >= 0 ? w != only : (kWaves[w].cw == 1 && (-layer.C & 63) < 32) || (kWaves[w].fw == 1 && (-layer.F & 63) < 32)) continue;
+        const int lgPW = kWaves[w].lgPW;
+        for (int lgPC = 0; lgPC <= lgPW; ++lgPC)
+            for (int TR = krows << (lgPW - lgPC); TR <= (lgPW ? 128 : 64); TR += krows << (lgPW - lgPC))
+                for (int nc = st; nc <= (st == 1 ? 8 : 6) && (nc - st) << lgPC < layer.Wo; nc += st)
+                    if (wd_tile(layer, w, lgPC, TR, nc, &p)) use(p);
+    }
+}
+
+bool pc_wgrad_dma_plan(const pc_conv_desc *d, int64_t nslots, WgradDmaPlan *out)
+{
+    WgradDmaArgs layer;
+    if (!wd_layer(d, nslots, layer)) return false;
+    double best = 1e30;
+    wd_plans(layer, 0, [&](const WgradDmaPlan &p) {
+        const double mfma = p.steps * 36 * 16, load = ((double)p.a.nrow * p.a.IW + (double)p.a.TR * p.a.TC) * 128 / 30.0;   // cycles
+        const double t = p.a.n_ktiles * ((mfma > load ? mfma : load) + 300 + 150.0 * (p.a.TR / 16));
+        if (t < best) { best = t; *out = p; }
+    });
+    out->tile_us = 0.55 * out->steps + 1.3;
+    return best < 1e30;
+}
+
+bool pc_wgrad_dma_plan_one(const pc_conv_desc *d, int64_t nslots, double kept, int num_cu, int waves, int32_t *choice, WgradDmaPlan *out)
+{
+    WgradDmaArgs layer;
+    if (!wd_layer(d, nslots, layer)) return false;
+    if (choice && *choice >= 0) {
+        const int c = *choice;
+        if (!wd_tile(layer, c & 3, (c >> 2) & 3, ((c >> 4) & 15) * 16, (c >> 8) & 15, out)) return false;
+        out->a.ksplit = c >> 12;
+        return true;
+    }
+    // Estimated time (us): a start, the pixel tiles of a workgroup one after the other (a lone one on its CU: a wait, loads and products in
+    // sequence; two sharing it: loads and products overlap), the sums of wavefronts that share pixels and the pick of the kept taps of
+    // 16 x 16 blocks, the tensors' bytes; the partial planes and their launch. Of splits that leave the workgroups of an XCD without shared
+    // pixels (WD_PLACE_PLAIN) every staged byte comes from beyond its L2: 144 -> 80, 50 images of 80 x 80, 34 splits of tiles of 32 x 32 186 us,
+    // 32 splits 95. Fitted to 25000 timings of 160 layers (7 % rms), on which the choice is 3.5 % behind the fastest, the worst 17 %;
+    // one tile of 64 x 64, the pixel tile of the best throughput and as many splits as fill the chip were 12 % behind.
+    const double bytes = (double)layer.x_bytes + layer.dy_bytes;
+    double best = 1e30;
+    wd_plans(layer, waves, [&](const WgradDmaPlan &p) {
+        const int T = p.ct * p.ft, lgPW = kWaves[p.a.waves].lgPW;
+        const double sums = 0.28 * (4 >> lgPW) + (lgPW == 0 ? 0.0 : lgPW == 1 ? 1.25 : 1.87), lone = 0.526 + 0.068 * p.loads + 0.319 * p.steps,
+                     load = 0.0893 * p.loads, mul = 0.498 * p.steps, pair = 0.574 + sqrt(load * load + mul * mul);
+        const double staged = ((double)p.a.nrow * p.a.IW * kWaves[p.a.waves].cw + (double)p.a.TR * p.a.TC * kWaves[p.a.waves].fw) * 64.0;
+        int last = 0;
+        for (int places = 2 * num_cu; places >= num_cu / 4; places >>= 1)
+            for (int even = 0; even < 2; ++even) {
+                int ks = places / T < p.a.n_ktiles ? places / T : p.a.n_ktiles;
+                if (ks < 1) ks = 1;
+                if (even) ks = ks >= 8 ? ks & ~7 : ks >= 4 ? 4 : ks >= 2 ? 2 : 1;
+                if (ks == last) continue;
+                last = ks;
+                const int u = (p.a.n_ktiles + ks - 1) / ks, rounds = (T * ks + 2 * num_cu - 1) / (2 * num_cu);
+                const double t = 3.25 + (T * ks <= num_cu ? u * lone + sums : rounds * (u * pair + 2.2 * sums));
+                const double moved = 0.168e-6 * bytes + (wd_placed(T, ks) == WD_PLACE_PLAIN ? 0.112e-6 * staged * T * ks * u : 0.0);
+                const double us = cbrt(t * t * t + moved * moved * moved) + (ks > 1 ? 2.5 + 10.7e-6 * ks * kept : 0.0);
+                if (us < best) { best = us; *out = p; out->a.ksplit = ks; }
+            }
+    });
+    if (best < 1e30 && choice) *choice = out->a.waves | out->a.lgPC << 2 | out->a.TR / 16 << 4 | out->a.NC << 8 | out->a.ksplit << 12;
+    return best < 1e30;
+}
+
+// Where the workgroups of a layer find their tile and split.
+static void wd_place(WgradDmaLayer &y)
+{
+    WgradDmaArgs &a = y.a;
+    a.T = y.gx * y.gy;
+    a.mg_T = pc_udiv_magic(a.T);
+    a.mg_gx = pc_udiv_magic(y.gx);
+    a.lgks = a.ksplit >= 4 ? 2 : a.ksplit == 2;
+    a.place = wd_placed(a.T, a.ksplit);
+}
+
+template <class Args>
+static pc_status wd_launch(pc_ctx *ctx, void (*kernel)(Args), pc_per_device_once &attr, const Args &g, size_t lds)
+{
     if (pc_once_pending(attr, ctx->device)) {
-        PC_HIP(ctx, hipFuncSetAttribute((const void *)pc_mfma_wgrad_dma_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, WD_LDS_MAX));
+        PC_HIP(ctx, hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, WD_LDS_MAX));
         pc_once_done(attr, ctx->device);
     }
-    hipLaunchKernelGGL(pc_mfma_wgrad_dma_kernel, dim3((unsigned)g.blk0[g.n]), dim3(256), lds, ctx->stream, g);
-    pc_note_kernel(ctx, "pc_mfma_wgrad_dma_kernel");
+    hipLaunchKernelGGL(kernel, dim3((unsigned)g.blk0[g.n]), dim3(256), lds, ctx->stream, g);
     return pc_hip_check(ctx, hipGetLastError(), "MFMA bwd_weight (direct loads) launch");
+}
+
+pc_status pc_wgrad_dma_launch(pc_ctx *ctx, WgradDmaOne &g, size_t lds)
+{
+    wd_place(g.layer[0]);
+    typedef void (*One)(WgradDmaOne);
+#define WD_ONES(st) {&pc_mfma_wgrad_dma_kernel<st, 2, 2>, &pc_mfma_wgrad_dma_kernel<st, 1, 2>, &pc_mfma_wgrad_dma_kernel<st, 2, 1>, &pc_mfma_wgrad_dma_kernel<st, 1, 1>}
+    static const One kernels[2][WD_WAVES] = {WD_ONES(1), WD_ONES(2)};
+#undef WD_ONES
+    static pc_per_device_once attr[2][WD_WAVES];
+    const WgradDmaArgs &a = g.layer[0].a;
+    pc_note_kernel(ctx, "pc_mfma_wgrad_dma_kernel<%d, %d, %d>", a.stride, kWaves[a.waves].fw, kWaves[a.waves].cw);
+    return wd_launch(ctx, kernels[a.stride - 1][a.waves], attr[a.stride - 1][a.waves], g, lds);
+}
+
+pc_status pc_wgrad_dma_launch(pc_ctx *ctx, WgradDmaGroup &g, size_t lds)
+{
+    for (int l = 0; l < g.n; ++l) wd_place(g.layer[l]);
+    static pc_per_device_once attr;
+    pc_note_kernel(ctx, "pc_mfma_wgrad_dma_group_kernel");
+    return wd_launch(ctx, &pc_mfma_wgrad_dma_group_kernel, attr, g, lds);
 }

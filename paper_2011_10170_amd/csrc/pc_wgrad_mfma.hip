@@ -869,42 +869,22 @@ static pc_status pc_mfma_bwd_weight_dma(pc_ctx *ctx, const pc_conv_desc *d, cons
                                         float *dw, int64_t nslots, bool *launched)
 {
     *launched = false;
-    WgradDmaGroup g;
-    memset(&g, 0, sizeof(g));
-    WgradDmaLayer &y = g.layer[0];
-    size_t lds;
-    double tile_us;
-    if (!pc_direct_loads(x) || !pc_direct_loads(dy) || !pc_wgrad_dma_plan(d, nslots, &y.a, &y.gx, &y.gy, &lds, &tile_us)) return PC_OK;
-    int ks = 2 * ctx->num_cu / (y.gx * y.gy);
-    if (ks > y.a.n_ktiles) ks = y.a.n_ktiles;
-    if (ks < 1) ks = 1;
-    y.a.ksplit = ks;
-    if (ctx->plan_cfg != 44) {
-        // Either kernel by its estimated time (us): rounds of pixel tiles, rounds of workgroups, the partial planes and whether there are any,
-        // a start. Fitted to 142 layers (12 and 8 % rms); on 200 others (profiles/plan_timings_bf16.csv, bwd_weight: 11 and 44 are the two
-        // kernels) the choice is 0.6 % behind the faster of the two on average, 0.7 % where the count has not been read back, the worst 16 %;
-        // always this kernel 0.7 %, always the other 14 %. 13 images 33 x 47, 40 -> 72 15.4 -> 13.6, 64 images 7 x 7, 512 -> 512 25.1 -> 23.4;
-        // large layers 28 x 28, 512 -> 512, batch 32 99 -> 82, 56 x 56, 128 -> 128, stride 2, batch 64 33 -> 27.5.
+    if (!pc_direct_loads(x) || !pc_direct_loads(dy)) return PC_OK;
+    // (remembered for the layer)
+    WgradDmaPlan p;
+    const bool forced = ctx->plan_cfg == 44;
+    int32_t *choice = nullptr;
+    if (!forced) {
         const int32_t key[PC_CHOICE_KEY] = {7, d->N, d->H, d->W, d->C, d->F, d->stride, (int32_t)nslots, pk->nnzk >= 0, 0};
         bool known;
-        int32_t *choice = pc_choice(ctx, key, &known);
-        if (!known || *choice < 0) {
-            const int T = y.gx * y.gy, places = 2 * ctx->num_cu;
-            auto up = [](int p, int q) { return (double)((p + q - 1) / q); };
-            auto planes = [&](int n) { return n > 1 ? 2.9 + 16e-6 * (double)n * kept_estimate(pk, nslots) : 0.0; };
-            const double own = (0.9 * up(y.a.n_ktiles, ks) * tile_us + 2.5) * up(T * ks, places) + planes(ks) + 2.5;
-            WgradWsArgs a;
-            int ct, ft;
-            size_t l;
-            bool pad_x;
-            int64_t xb;
-            double other = 1e30;
-            if (ws_plan(ctx, d, nslots, &a, &ct, &ft, &l, &pad_x, &xb))
-                other = (1.58 * up(a.n_ktiles, a.ksplit) + 3.6) * up(ct * ft * a.ksplit, ctx->num_cu) + (a.ksplit > 1 ? 0.7 : 0.0) + planes(a.ksplit) + 3.6;
-            *choice = own < other;
-        }
-        if (!*choice) return PC_OK;
+        choice = pc_choice(ctx, key, &known);
     }
+    if (!pc_wgrad_dma_plan_one(d, nslots, kept_estimate(pk, nslots), ctx->num_cu, !forced ? -1 : ctx->plan_split > 0 && ctx->plan_split < WD_WAVES ? ctx->plan_split : 0, choice, &p)) return PC_OK;
+    const int ks = p.a.ksplit;
+    WgradDmaOne g;
+    memset(&g, 0, sizeof(g));
+    WgradDmaLayer &y = g.layer[0];
+    y.a = p.a; y.gx = p.ct; y.gy = p.ft;
     if (ks > 1) {
         // (twice the other kernel's partial planes: up to 32 MiB)
         void *scr = nullptr;
@@ -917,7 +897,7 @@ static pc_status pc_mfma_bwd_weight_dma(pc_ctx *ctx, const pc_conv_desc *d, cons
     y.x = (const uint16_t *)x; y.dy = (const uint16_t *)dy; y.kinfo = pk->v.kinfo; y.dw = dw;
     g.n = 1;
     g.blk0[1] = y.gx * y.gy * ks;
-    pc_status s = pc_wgrad_dma_launch(ctx, g, lds);
+    pc_status s = pc_wgrad_dma_launch(ctx, g, p.lds);
     *launched = true;
     if (s != PC_OK || ks == 1) return s;
     return pc_launch_wgrad_reduce(ctx, y.partial, ks, nslots, nslots, pk, dw);
@@ -1074,9 +1054,10 @@ pc_status pc_mfma_bwd_weight_group(pc_ctx *ctx, int n, const pc_conv_desc *d, co
             it.l = l;
             it.nslots = nslots;
             it.pad_x = false;
-            it.dma = dma && pc_direct_loads(x[l]) && pc_direct_loads(dy[l]) &&
-                     pc_wgrad_dma_plan(&d[l], nslots, &it.q, &it.ct, &it.ft, &it.lds, &it.tile_us);
+            WgradDmaPlan q;
+            it.dma = dma && pc_direct_loads(x[l]) && pc_direct_loads(dy[l]) && pc_wgrad_dma_plan(&d[l], nslots, &q);
             if (it.dma) {
+                it.q = q.a; it.ct = q.ct; it.ft = q.ft; it.lds = q.lds; it.tile_us = q.tile_us;
                 it.n_ktiles = it.q.n_ktiles;
                 it.ksplit = std::max(1, std::min(2 * ctx->num_cu / (it.ct * it.ft), it.n_ktiles));
             } else if (ctx->plan_cfg != 10 && ws_plan(ctx, &d[l], nslots, &it.a, &it.ct, &it.ft, &it.lds, &it.pad_x, &it.xb)) {

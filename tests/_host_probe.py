@@ -61,6 +61,41 @@ def wgrad_lds():
     B.pc_destroy(ctx)
 
 
+def wgrad_lds_narrow():
+    """The same where wavefronts share the pixels of a tile (split_k 1 to 3): every wavefront's columns, and the sums they add in LDS."""
+    ctx = B.pc_create(0, None)
+    tiles = set()
+    for waves, (fw, cw) in ((1, (1, 2)), (2, (2, 1)), (3, (1, 1))):
+        B.pc_set_plan_override(ctx, 44, waves)
+        for st in (1, 2):
+            for N in (1, 9, 70):
+                for H in (1, 4, 7, 33, 200):
+                    for W in (1, 2, 3, 5, 8, 14, 47, 190):
+                        d, pk = layer(ctx, (N, H, W, 24, 40, st))
+                        watch("pc_mfma_wgrad_dma_kernel", 0, 88 + 112)
+                        B.pc_conv_bwd_weight(ctx, d, pk, DEV, DEV, DEV)
+                        arg, grid, lds = seen()
+                        a = struct.unpack("<28i", arg[88:])
+                        TR, TC, IW, nrow, RPx, RPd, dy_off = a[9:16]
+                        assert a[25] == waves and a[18] >= 1 and grid == -(-24 // (32 * cw)) * -(-40 // (32 * fw)) * a[18]
+                        lgPC, NC, XB, DB = a[26], a[27], 64 * cw, 64 * fw
+                        tiles.add((st, waves, lgPC, TR, NC))
+                        assert 4 * 18 * 1024 <= lds <= 80 * 1024 and nrow * RPx <= dy_off and TC * DB <= min(1024, RPd) and IW * XB <= min(2048, RPx)
+                        assert TR % (((32 if st == 1 else 16) * 4 // (fw * cw)) >> lgPC) == 0
+                        for p in range(1 << lgPC):
+                            nc = min(NC, TC - p * NC)
+                            if nc <= 0:
+                                continue
+                            d_col = p * NC + (min(7, nc + 2) if st == 1 else max([c + 3 for c in (0, 2) if c < nc] + [nc - 1]))
+                            x_col = p * NC * st + (min(9, nc + 2) if st == 1 else
+                                                   max(c + 2 for u in range(8) for c in [4 * (u // 3) + (u % 3 + 1 if u % 3 < 2 else 4)] if 2 * (u // 3) < nc))
+                            assert dy_off + (TR - 1) * RPd + (d_col + 1) * DB <= lds, (N, H, W, st, waves, a)
+                            assert (nrow - 1) * RPx + (x_col + 1) * XB <= lds, (N, H, W, st, waves, a)
+                        B.pc_packed_free(pk)
+    assert len(tiles) >= 30, len(tiles)
+    B.pc_destroy(ctx)
+
+
 def alignment():
     """Tensors whose address is no multiple of 16 go to the kernels that load through registers, before and after an aligned call of the
     same sizes, and back."""

@@ -41,6 +41,20 @@ def test_backward_weight(B, ctx, oracle, shape):
         B.pc_set_plan_override(ctx, -1, 0)
 
 
+@pytest.mark.parametrize("waves", [1, 2, 3])
+@pytest.mark.parametrize("shape", [
+    (1, 1, 1, 8, 8, 1), (40, 1, 2, 8, 8, 1), (3, 5, 3, 40, 32, 1), (9, 7, 7, 32, 200, 1), (1, 33, 47, 40, 72, 1), (5, 31, 15, 64, 24, 1), (4, 64, 40, 32, 32, 1),
+    (1, 1, 1, 8, 8, 2), (33, 2, 3, 8, 16, 2), (9, 7, 7, 136, 32, 2), (1, 33, 47, 40, 72, 2), (2, 64, 47, 24, 16, 2)])
+def test_wavefronts_that_share_pixels(B, ctx, oracle, waves, shape):
+    """Tiles of 32 filters or channels (split_k names the arrangement): the wavefronts' sums are added in LDS."""
+    B.pc_set_plan_override(ctx, 44, waves)
+    try:
+        run_case(B, ctx, oracle, shape, "bf16", 8, 0.4, B.PC_VARIANT_MFMA, ("rows", shape))
+        assert B.pc_last_kernel(ctx) == "pc_mfma_wgrad_dma_kernel<%d, %s>" % (shape[5], ("1, 2", "2, 1", "1, 1")[waves - 1])
+    finally:
+        B.pc_set_plan_override(ctx, -1, 0)
+
+
 SMALL = [(6, 14, 14, 64, 72, 1), (6, 14, 14, 3, 64, 1), (6, 27, 28, 40, 24, 2), (6, 7, 7, 136, 64, 1)]
 
 
