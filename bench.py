@@ -382,7 +382,8 @@ def main() -> int:
     helpers = {"pc_mfma_wgrad_ws_kernel": ("pc_wgrad_reduce", "pc_pad_channels_kernel"),
                "pc_mfma_wgrad_ws_group_kernel": ("pc_wgrad_reduce", "pc_pad_channels_kernel"),
                "pc_mfma_wgrad_dma_kernel": ("pc_wgrad_reduce", "pc_pad_channels_kernel"),
-               "pc_mfma_wgrad_dma_group_kernel": ("pc_wgrad_reduce", "pc_pad_channels_kernel"),
+               "pc_mfma_wgrad_dma_group_kernel": ("pc_wgrad_reduce", "pc_thin_wgrad_kernel"),
+               "pc_thin_wgrad_kernel": ("pc_wgrad_reduce",),
                "pc_mfma_wgrad_kernel": ("pc_wgrad_reduce",), "pc_wgrad_valu_kernel": ("pc_wgrad_reduce",),
                "pc_mfma_conv_ks_kernel": (), "pc_mfma_conv_kernel": ("pc_mfma_splitk_reduce_kernel",)}.get(dk, ())
     if os.path.exists(prof):

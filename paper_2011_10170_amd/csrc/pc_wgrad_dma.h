@@ -44,14 +44,31 @@ struct WgradDmaPlan {
     int ct, ft;                      // tiles of channels and of filters
     int steps, loads;                // of a pixel tile: steps of 36 matrix instructions and direct loads per wavefront
     size_t lds;
-    double tile_us;                  // estimated time of a pixel tile (us) while two workgroups share a CU
+    double tile_us, end_us;          // estimated time of a pixel tile (us) while two workgroups share a CU, and of a workgroup's end
 };
 
 // Plan of one layer of a grouped call (ksplit left to the caller), and of a layer's own call; false when the layer is outside what the kernel
 // takes. kept: kernels whose partial sums are written and read; waves: the arrangement to take, -1 = any; *choice: the plan made before
-// for this layer, or -1 and the plan's code on return (choice may be null).
-bool pc_wgrad_dma_plan(const pc_conv_desc *d, int64_t nslots, WgradDmaPlan *out);
+// for this layer, or -1 and the plan's code on return (plan_one: may be null).
+bool pc_wgrad_dma_plan(const pc_conv_desc *d, int64_t nslots, int32_t *choice, WgradDmaPlan *out);
 bool pc_wgrad_dma_plan_one(const pc_conv_desc *d, int64_t nslots, double kept, int num_cu, int waves, int32_t *choice, WgradDmaPlan *out);
 pc_status pc_wgrad_dma_launch(pc_ctx *ctx, WgradDmaOne &g, size_t lds);
 pc_status pc_wgrad_dma_launch(pc_ctx *ctx, WgradDmaGroup &g, size_t lds);
+
+// A layer with at most 4 input channels.
+struct ThinWgradArgs {
+    int32_t N, H, W, C, F, Ho, Wo, stride;
+    int32_t rows, TC, IW, nx;        // N * Ho; columns of a tile, staged x columns and pixels
+    int32_t RPx, RPd, x_off, buf_bytes;
+    int32_t tiles_c, n_tiles, pstride;
+    uint32_t x_bytes, dy_bytes;
+    uint32_t mg_tc, mg_Ho, mg_H1, mg_IW;
+};
+struct ThinWgradPlan {
+    ThinWgradArgs a;
+    int nf, xp, blocks_f, ksplit;    // blocks of 16 filters per workgroup, pixels of x per thread, blocks of 64 filters, workgroups that share the tiles
+    size_t lds;
+};
+bool pc_thin_wgrad_plan(const pc_conv_desc *d, int64_t nslots, int num_cu, ThinWgradPlan *out);
+pc_status pc_thin_wgrad_launch(pc_ctx *ctx, const ThinWgradPlan &p, const uint16_t *x, const uint16_t *dy, const uint32_t *kinfo, float *out);
 #endif

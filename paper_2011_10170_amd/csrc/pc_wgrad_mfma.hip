@@ -903,6 +903,32 @@ static pc_status pc_mfma_bwd_weight_dma(pc_ctx *ctx, const pc_conv_desc *d, cons
     return pc_launch_wgrad_reduce(ctx, y.partial, ks, nslots, nslots, pk, dw);
 }
 
+// Whether the kernel for few input channels takes a layer (the tensor of the output's gradient by direct loads).
+static bool thin_plan(pc_ctx *ctx, const pc_conv_desc *d, int64_t nslots, const void *dy, ThinWgradPlan *p)
+{
+    return (ctx->plan_cfg < 0 || ctx->plan_cfg == 23) && pc_direct_loads(dy) && pc_thin_wgrad_plan(d, nslots, ctx->num_cu, p);
+}
+
+static pc_status pc_mfma_bwd_weight_thin(pc_ctx *ctx, const pc_conv_desc *d, const pc_packed *pk, const void *x, const void *dy,
+                                         float *dw, int64_t nslots, bool *launched)
+{
+    *launched = false;
+    ThinWgradPlan p;
+    if (!thin_plan(ctx, d, nslots, dy, &p)) return PC_OK;
+    void *scr = nullptr;
+    if (p.ksplit > 1) {
+        // (the entry that allocates nothing counts the 8-channel copy of x, which the other kernel needs, against its limit: it refuses the same layers)
+        const size_t bytes = sizeof(float) * 4 * (size_t)p.ksplit * (size_t)nslots, copy = ctx->fixed_scratch ? (size_t)16 * d->N * d->H * d->W : 0;
+        if (!pc_scratch_ready(ctx, bytes + copy)) return PC_OK;
+        const pc_status s = pc_scratch(ctx, bytes, &scr);
+        if (s != PC_OK) return s;
+    }
+    pc_status s = pc_thin_wgrad_launch(ctx, p, (const uint16_t *)x, (const uint16_t *)dy, pk->v.kinfo, p.ksplit > 1 ? (float *)scr : dw);
+    *launched = true;
+    if (s != PC_OK || p.ksplit == 1) return s;
+    return pc_launch_wgrad_reduce(ctx, (const float *)scr, p.ksplit, nslots, nslots, pk, dw);
+}
+
 pc_status pc_mfma_bwd_weight(pc_ctx *ctx, const pc_conv_desc *d, const pc_packed *pk, const void *x, const void *dy,
                              float *dw)
 {
@@ -914,6 +940,11 @@ pc_status pc_mfma_bwd_weight(pc_ctx *ctx, const pc_conv_desc *d, const pc_packed
     const int64_t nslots = pk->nnzk >= 0 ? pk->nnzk : (int64_t)pk->v.F * pk->v.C;
     if (nslots == 0) return PC_OK;
     pc_status s = PC_OK;
+    {
+        bool launched = false;
+        s = pc_mfma_bwd_weight_thin(ctx, d, pk, x, dy, dw, nslots, &launched);
+        if (launched || s != PC_OK) return s;
+    }
     if (ctx->plan_cfg < 0 || ctx->plan_cfg == 44) {
         bool launched = false;
         s = pc_mfma_bwd_weight_dma(ctx, d, pk, x, dy, dw, nslots, &launched);
@@ -1015,8 +1046,8 @@ struct GroupItem {
     bool dma, pad_x;
     WgradWsArgs a;
     WgradDmaArgs q;
-    int ct, ft, n_ktiles, ksplit;    // ksplit: at most, until the shares are known
-    double tile_us;
+    int ct, ft, n_ktiles, ksplit, most;    // most: splits that fill the chip
+    double tile_us, end_us;
     size_t lds, part_off, pad_off;
     int64_t xb, nslots;
 };
@@ -1043,26 +1074,43 @@ pc_status pc_mfma_bwd_weight_group(pc_ctx *ctx, int n, const pc_conv_desc *d, co
 {
     std::vector<GroupItem> items;
     std::vector<int> single;
-    size_t total = 0;
+    size_t total = 0, thin_total = 0;
+    struct ThinItem { int l; int64_t nslots; size_t part_off; ThinWgradPlan p; };
+    std::vector<ThinItem> thin;          // layers with few input channels: a launch of their own each, one reduction with the others
+    std::vector<char> is_thin(n, 0);
+    for (int l = 0; l < n; ++l) {
+        const int64_t nslots = pk[l]->nnzk >= 0 ? pk[l]->nnzk : (int64_t)pk[l]->v.F * pk[l]->v.C;
+        ThinItem t;
+        if (nslots == 0 || !thin_plan(ctx, &d[l], nslots, dy[l], &t.p)) continue;
+        t.l = l; t.nslots = nslots; t.part_off = thin_total;
+        if (t.p.ksplit > 1) thin_total += (sizeof(float) * 4 * (size_t)t.p.ksplit * (size_t)nslots + 255) / 256 * 256;
+        thin.push_back(t);
+        is_thin[l] = 1;
+    }
     auto plan = [&](bool dma) {
         items.clear();
         single.clear();
         for (int l = 0; l < n; ++l) {
             const int64_t nslots = pk[l]->nnzk >= 0 ? pk[l]->nnzk : (int64_t)pk[l]->v.F * pk[l]->v.C;
-            if (nslots == 0) continue;
+            if (nslots == 0 || is_thin[l]) continue;
             GroupItem it;
             it.l = l;
             it.nslots = nslots;
             it.pad_x = false;
             WgradDmaPlan q;
-            it.dma = dma && pc_direct_loads(x[l]) && pc_direct_loads(dy[l]) && pc_wgrad_dma_plan(&d[l], nslots, &q);
+            it.dma = dma && pc_direct_loads(x[l]) && pc_direct_loads(dy[l]);
             if (it.dma) {
-                it.q = q.a; it.ct = q.ct; it.ft = q.ft; it.lds = q.lds; it.tile_us = q.tile_us;
+                const int32_t key[PC_CHOICE_KEY] = {8, d[l].N, d[l].H, d[l].W, d[l].C, d[l].F, d[l].stride, 0, 0, 0};
+                bool known;
+                it.dma = pc_wgrad_dma_plan(&d[l], nslots, pc_choice(ctx, key, &known), &q);
+            }
+            if (it.dma) {
+                it.q = q.a; it.ct = q.ct; it.ft = q.ft; it.lds = q.lds; it.tile_us = q.tile_us; it.end_us = q.end_us;
                 it.n_ktiles = it.q.n_ktiles;
-                it.ksplit = std::max(1, std::min(2 * ctx->num_cu / (it.ct * it.ft), it.n_ktiles));
+                it.most = std::max(1, std::min(2 * ctx->num_cu / (it.ct * it.ft), it.n_ktiles));
             } else if (ctx->plan_cfg != 10 && ws_plan(ctx, &d[l], nslots, &it.a, &it.ct, &it.ft, &it.lds, &it.pad_x, &it.xb)) {
                 it.n_ktiles = it.a.n_ktiles;
-                it.ksplit = it.a.ksplit;
+                it.most = it.a.ksplit;
             } else {
                 single.push_back(l);
                 continue;
@@ -1070,18 +1118,14 @@ pc_status pc_mfma_bwd_weight_group(pc_ctx *ctx, int n, const pc_conv_desc *d, co
             items.push_back(it);
         }
     };
-    auto even = [&]() {          // the direct-load layers' share of every place, two per CU
-        double us = 0.0;
-        for (const GroupItem &it : items)
-            if (it.dma) us += it.ct * it.ft * (double)it.n_ktiles * it.tile_us;
-        return us / (2.0 * ctx->num_cu);
-    };
-    bool dma = ctx->plan_cfg == 44;
+    // The kernel with direct loads for all layers it takes: on 360 whole networks (VGG- and ResNet-shaped, 1 to 128 images, widths 16 to 64, maps 16
+    // to 224; profiles/group_timings_bf16.csv) it takes 0.6 of the wave-specialised kernel's time, and more on none (by 3 %).
+    bool dma = ctx->plan_cfg < 0 || ctx->plan_cfg == 44;
     // A layer's own call splits its pixel tiles until the layer alone fills the chip; here the layers fill it
     // together, so every workgroup gets about the same share of all (tile, pixel tile) units: fewer splits, longer
     // main loops per prologue and epilogue, fewer partial planes. (The two kernels run one after the other, each with its own shares.)
-    auto shares = [&]() {
-        total = 0;
+    auto shares = [&](double level) {
+        total = thin_total;
         int64_t units = 0;
         for (const GroupItem &it : items)
             if (!it.dma) units += (int64_t)it.ct * it.ft * it.n_ktiles;
@@ -1089,10 +1133,8 @@ pc_status pc_mfma_bwd_weight_group(pc_ctx *ctx, int n, const pc_conv_desc *d, co
         rounds = rounds < 1 ? 1 : rounds > 4 ? 4 : rounds;
         int64_t share = units / (rounds * (int64_t)ctx->num_cu);
         if (share < 1) share = 1;
-        // (2.5 workgroups of the direct-load kernel to a place: 1 to 4 measured, within 3 % of the best on each of the four)
-        const double level = dma ? even() / 2.5 : 1.0;
         for (GroupItem &it : items) {
-            it.ksplit = group_splits(it.dma ? it.n_ktiles * it.tile_us / level : (double)((it.n_ktiles + share - 1) / share), it.ksplit);
+            it.ksplit = group_splits(it.dma ? it.n_ktiles * it.tile_us / level : (double)((it.n_ktiles + share - 1) / share), it.most);
             it.part_off = total;
             if (it.ksplit > 1) total += (sizeof(float) * 4 * (size_t)it.ksplit * (size_t)it.nslots + 255) / 256 * 256;
             it.pad_off = total;
@@ -1100,53 +1142,59 @@ pc_status pc_mfma_bwd_weight_group(pc_ctx *ctx, int n, const pc_conv_desc *d, co
             it.a.ksplit = it.q.ksplit = it.ksplit;
         }
     };
-    // The wave-specialised kernel for every layer, or the kernel with direct loads for all it takes (the rest in launches of their own),
-    // the second where it is estimated to be faster by a tenth (it takes more scratch, and the estimates err by 8 and 6 % rms). Microseconds:
-    // pixel tiles per CU (strips of images cost more), launches, planes, a start. Fitted to 160 whole networks (VGG- and
-    // ResNet-shaped, 1 to 128 images, widths 16 to 64, maps 16 to 224); on 200 drawn afterwards the choice is 0.5 % behind the faster
-    // of the two on average, the worst 19 % (profiles/group_timings_bf16.csv); always direct loads 1.5 %, never 25 %. The rule
-    // before it, made for four networks of width 64, was 20 % behind: 18 images of 101 x 101, width 16 143 us where direct loads take
-    // 71. VGG-16 / CIFAR 91 : 108, ResNet-18 / CIFAR 144 : 148, ResNet-50 / ImageNet 294 : 235, VGG-16 / ImageNet 948 : 774.
-    auto estimate = [&]() {
-        double whole = 0.0, strips = 0.0, planes = 0.0;
-        int n_whole = 0, n_strips = 0;
-        for (const GroupItem &it : items) {
-            if (!it.dma) {
-                (it.a.lgS ? strips : whole) += (double)it.ct * it.ft * it.n_ktiles / ctx->num_cu;
-                ++(it.a.lgS ? n_strips : n_whole);
+    plan(dma);
+    // The direct-load layers' workgroups go to two places per CU in order, the longest first. Of a few shares of a workgroup (us) the one is taken
+    // whose last place ends first, with the partial planes' time (3.9 % behind the best share of a network on average, a fixed rule on the total 6 %);
+    // large networks take two rounds or more, which even out what the estimates miss (VGG-16 / ImageNet 720 against 780 us in one).
+    auto share_of = [&]() {
+        double all = 0.0;
+        for (const GroupItem &it : items)
+            if (it.dma) all += it.ct * it.ft * (it.n_ktiles * it.tile_us + it.end_us);
+        all /= 2.0 * ctx->num_cu;
+        double best = 1e30, level = 1.0;
+        for (double n : {0.6, 0.8, 1.0, 1.25, 1.5, 2.0, 2.5, 3.0}) {
+            if (n < std::min(2.0, all / 60.0)) continue;
+            shares(all / n);
+            std::vector<std::pair<double, int>> places(1, {0.0, 2 * ctx->num_cu}), runs;      // (time, how many)
+            double planes = 0.0;
+            for (const GroupItem &it : items) {
+                if (it.ksplit > 1) planes += 6e-6 * it.ksplit * kept_estimate(pk[it.l], it.nslots);
+                if (it.dma) runs.push_back({(it.n_ktiles + it.ksplit - 1) / it.ksplit * it.tile_us + it.end_us, it.ct * it.ft * it.ksplit});
             }
-            if (it.ksplit > 1) planes += 16e-6 * it.ksplit * kept_estimate(pk[it.l], it.nslots);
+            std::sort(runs.begin(), runs.end(), [](const std::pair<double, int> &p, const std::pair<double, int> &q) { return p.first > q.first; });
+            for (auto &r : runs)
+                while (r.second > 0) {
+                    const auto first = std::min_element(places.begin(), places.end());
+                    const double at = first->first;
+                    const int m = std::min(first->second, r.second);
+                    first->second -= m;
+                    if (first->second == 0) places.erase(first);
+                    places.push_back({at + r.first, m});
+                    r.second -= m;
+                }
+            const double end = std::max_element(places.begin(), places.end())->first + planes;
+            if (end < best) { best = end; level = all / n; }
         }
-        const int launches = (n_whole + WS_GROUP_MAX - 1) / WS_GROUP_MAX + (n_strips + WS_GROUP_MAX - 1) / WS_GROUP_MAX;
-        if (!dma) return 13.4 + 2.01 * whole + 2.52 * strips + 7.7 * launches + 0.36 * planes;
-        return 17.8 + 1.18 * (even() + whole + strips) + (launches ? 9.3 : 0.0) + 0.38 * planes;
+        return level;
     };
-    if (ctx->plan_cfg < 0) {
+    double level = 1.0;
+    if (dma) {
         // (remembered for the shapes it was made for)
         uint64_t h = 1469598103934665603ull;
         for (int l = 0; l < n; ++l)
             for (int v : {(int)d[l].N, (int)d[l].H, (int)d[l].W, (int)d[l].C, (int)d[l].F, (int)d[l].stride * 2 + (pc_direct_loads(x[l]) && pc_direct_loads(dy[l])), (int)pk[l]->nnzk})
                 h = (h ^ (uint32_t)v) * 1099511628211ull;
-        const int32_t key[PC_CHOICE_KEY] = {4, n, (int32_t)h, (int32_t)(h >> 32), d[0].N, d[0].H, d[n - 1].H, d[n - 1].F, 0, 0};
+        const int32_t key[PC_CHOICE_KEY] = {4, n, (int32_t)h, (int32_t)(h >> 32), d[0].N, d[0].H, d[n - 1].H, d[n - 1].F, ctx->plan_cfg, 0};
         bool hit;
         int32_t *choice = pc_choice(ctx, key, &hit);
-        if (!hit) {
-            plan(false);
-            shares();
-            const double all = estimate();
-            dma = true;
-            plan(true);
-            shares();
-            *choice = even() > 0.0 && 1.1 * estimate() < all;
-        }
-        dma = *choice != 0;
+        if (!hit || *choice < 0) *choice = (int32_t)(share_of() * 100.0) + 1;
+        level = *choice / 100.0;
     }
-    plan(dma);
-    shares();
+    shares(level);
     if (dma && ctx->plan_cfg < 0 && !pc_scratch_ready(ctx, total)) {      // the other kernel needs fewer partial planes
         dma = false;
         plan(false);
-        shares();
+        shares(1.0);
     }
     void *scr = nullptr;
     pc_status s = PC_OK;
@@ -1158,17 +1206,30 @@ pc_status pc_mfma_bwd_weight_group(pc_ctx *ctx, int n, const pc_conv_desc *d, co
         s = pc_mfma_bwd_weight(ctx, &d[l], pk[l], x[l], dy[l], dw[l]);
         if (s != PC_OK) return s;
     }
-    if (items.empty()) return PC_OK;
     if (total) {
         s = pc_scratch(ctx, total, &scr);      // the base may have moved if one of the calls above needed more
         if (s != PC_OK) return s;
     }
-    s = ws_set_lds_attr(ctx);
+    if (!items.empty()) s = ws_set_lds_attr(ctx);
     if (s != PC_OK) return s;
     unsigned char *base = static_cast<unsigned char *>(scr);
     std::vector<WgradReduceItem> red;
     std::vector<int64_t> red_nslots;
     std::vector<const pc_packed *> red_pk;
+    auto reduce = [&](int l, const float *partial, int64_t nslots, int planes) {
+        WgradReduceItem r;
+        memset(&r, 0, sizeof(r));
+        r.partial = partial; r.dw = dw[l]; r.pstride = nslots; r.G = planes;
+        red.push_back(r);
+        red_nslots.push_back(nslots);
+        red_pk.push_back(pk[l]);
+    };
+    for (const ThinItem &t : thin) {
+        float *partial = t.p.ksplit > 1 ? reinterpret_cast<float *>(base + t.part_off) : dw[t.l];
+        s = pc_thin_wgrad_launch(ctx, t.p, (const uint16_t *)x[t.l], (const uint16_t *)dy[t.l], pk[t.l]->v.kinfo, partial);
+        if (s != PC_OK) return s;
+        if (t.p.ksplit > 1) reduce(t.l, partial, t.nslots, t.p.ksplit);
+    }
     // layers of the kernel with direct loads, whole-image layers and layers in strips run different kernels
     auto kind = [&](const GroupItem &it) { return it.dma ? 2 : it.a.lgS > 0 ? 1 : 0; };
     auto work = [](const GroupItem &it) { return it.dma ? (it.n_ktiles + it.ksplit - 1) / it.ksplit * it.tile_us : 0.0; };     // the longest workgroups first
@@ -1195,14 +1256,7 @@ pc_status pc_mfma_bwd_weight_group(pc_ctx *ctx, int n, const pc_conv_desc *d, co
             else g.layer[i] = {it.a, xp, dyp, pk[it.l]->v.kinfo, partial, dw[it.l], it.ct, it.ft};
             g.blk0[i + 1] = gd.blk0[i + 1] = g.blk0[i] + (nwg + 7) / 8 * 8;
             if (it.lds > lds) lds = it.lds;
-            if (it.ksplit > 1) {
-                WgradReduceItem r;
-                memset(&r, 0, sizeof(r));
-                r.partial = partial; r.dw = dw[it.l]; r.pstride = it.nslots; r.G = it.ksplit;
-                red.push_back(r);
-                red_nslots.push_back(it.nslots);
-                red_pk.push_back(pk[it.l]);
-            }
+            if (it.ksplit > 1) reduce(it.l, partial, it.nslots, it.ksplit);
         }
         if (kd == 2) {
             s = pc_wgrad_dma_launch(ctx, gd, lds);

@@ -88,3 +88,28 @@ def test_first_layer_kernels_are_the_automatic_choice_and_fuse_the_relu(B, ctx):
     finally:
         B.pc_set_plan_override(ctx, -1, 0)
         g.close()
+
+
+@pytest.mark.parametrize("shape", [
+    (1, 1, 2, 4, 8, 1), (40, 2, 2, 3, 16, 1), (2, 64, 31, 2, 48, 1), (1, 224, 9, 3, 136, 1), (3, 9, 11, 3, 24, 2), (7, 5, 3, 4, 64, 2), (5, 33, 35, 1, 72, 2),
+    (9, 32, 32, 3, 32, 1)])
+def test_backward_weight_of_few_channels(B, ctx, oracle, shape):
+    """Rows across images, columns past the map, blocks of 16 and of 64 filters that are not full, both strides, and x at an address that is a multiple
+    of 2 only (its last pixel is read with the bytes before it)."""
+    import torch
+    from tests._harness import Case, GpuLayer
+    run_case(B, ctx, oracle, shape, "bf16", 8, 0.5, B.PC_VARIANT_MFMA, "few_channels")
+    assert B.pc_last_kernel(ctx).startswith("pc_thin_wgrad_kernel")
+    g = GpuLayer(B, ctx, Case(I.Layer(*shape), "bf16", 8, I.kept_per_filter(0.5, shape[3]), tag=("few", shape)))
+    try:
+        want = g.bwd_weight()[0]
+        moved = torch.zeros(g.x.numel() + 8, dtype=g.x.dtype, device="cuda")
+        for off in (1, 2, 3):
+            moved.fill_(float("nan"))
+            moved[off:off + g.x.numel()].copy_(g.x.reshape(-1))
+            got = torch.full((g.nnzk, 4), float("nan"), device="cuda")
+            B.pc_conv_bwd_weight(ctx, g.desc, g.pk, moved[off:], g.dy, got)
+            assert B.pc_last_kernel(ctx).startswith("pc_thin_wgrad_kernel")
+            assert np.array_equal(got.cpu().numpy(), want)
+    finally:
+        g.close()
