@@ -17,6 +17,7 @@
 // the padding, and copy no operand registers.
 #include "pc_mfma.h"
 #include <math.h>
+#include <algorithm>
 #include <type_traits>
 
 // ------------------------------------------------------------------ forward / backward-data
@@ -611,10 +612,10 @@ pc_status pc_f32_bwd_data(pc_ctx *ctx, const pc_conv_desc *d, const pc_packed *p
 // dW[t][f][c] = sum over output pixels of dy[pixel][f] * x[pixel shifted by tap t][c]. The pixels are the reduction and a
 // lane holds one float of one pixel, so NHWC rows in LDS are the operands as they are: no transpose. A wavefront holds a
 // 32 x 32 (filter, channel) tile of all 9 taps (144 accumulators) and reads 10 words per 9 matrix instructions.
-// WF x WC wavefronts cover 32*WF filters x 32*WC channels; where a layer needs fewer than four, the 4 / (WF*WC)
-// remaining ones take every WK-th pixel pair and write partial planes of their own. Pixel tiles are split over the
-// workgroups (two per CU); every split writes the kept taps in compact slot order, pc_wgrad_reduce adds the planes in
-// a fixed order.
+// WF x WC wavefronts cover 32*WF filters x 32*WC channels; of fewer than four, the WK = 4 / (WF*WC) that are left over take every WK-th
+// pixel pair, and their sums are added in LDS (halves of the tile at a time, a wavefront keeps 16 / WK of its kernels). Pixel tiles are
+// split over the workgroups (two per CU); every split writes the kept taps in compact slot order, pc_wgrad_reduce adds the planes in a
+// fixed order.
 // THIN (at most 3 channels): the 9 * C (tap, channel) pairs are the columns of one tile, one instruction instead of 9.
 #define F32W_ND 2       // 16-byte elements of dy, and
 #define F32W_NX 6       // of x, staged per thread and pixel tile
@@ -624,7 +625,9 @@ struct F32WgradArgs {
     int32_t TR, TC, TCe, IR, IW;          // pixel tile, its columns rounded up to even, staged extent of x
     int32_t tiles_r, tiles_c, n_tiles, ksplit, ct, ft;
     int32_t nd, nx;                       // elements per tile
-    uint32_t mg_half;                     // division by TCe / 2
+    // multiply-high divisions by TCe / 2, TCe and IW; where `exact` also those of the tile's index and the workgroup's
+    uint32_t mg_half, mg_TCe, mg_IW, mg_tc, mg_tr, mg_ks, mg_ct;
+    int32_t exact;
     int64_t pstride;                      // slots per partial plane
 };
 
@@ -640,8 +643,9 @@ pc_f32_wgrad_kernel(const float *__restrict__ x, const float *__restrict__ dy, F
     const int lane = threadIdx.x & 63, h = lane >> 5, n32 = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wk = wave % WK, wc = (wave / WK) % WC, wf = wave / WK / WC;
-    const int b = (int)blockIdx.x, split = b % a.ksplit, tile = b / a.ksplit;
-    const int c0 = (tile % a.ct) * CD, f0 = (tile / a.ct) * FD;
+    auto divide = [&](int q, int d, uint32_t mg) { return a.exact ? (int)pc_udiv((uint32_t)q, mg) : q / d; };
+    const int b = (int)blockIdx.x, tile = divide(b, a.ksplit, a.mg_ks), split = b - tile * a.ksplit;
+    const int tf = divide(tile, a.ct, a.mg_ct), c0 = (tile - tf * a.ct) * CD, f0 = tf * FD;
     float *sd = smem, *sx = smem + a.TR * a.TCe * PD;
 
     // staged elements: a thread takes the same 4 filters (channels) of several positions; position inside the tile (or
@@ -651,13 +655,13 @@ pc_f32_wgrad_kernel(const float *__restrict__ x, const float *__restrict__ dy, F
     int dpos[F32W_ND], xpos[F32W_NX], doff[F32W_ND], xoff[F32W_NX];
 #pragma unroll
     for (int i = 0; i < F32W_ND; ++i) {
-        const int q = dq + i * (1024 / FD), r = q / a.TCe, col = q - r * a.TCe;
+        const int q = dq + i * (1024 / FD), r = (int)pc_udiv((uint32_t)q, a.mg_TCe), col = q - r * a.TCe;
         dpos[i] = r < a.TR && col < a.TC && dleft > 0 ? (r << 16) | col : -1;
         doff[i] = (r * a.Wo + col) * a.F + f0 + dp * 4;
     }
 #pragma unroll
     for (int i = 0; i < F32W_NX; ++i) {
-        const int q = xq + i * (1024 / CD), r = q / a.IW, col = q - r * a.IW;
+        const int q = xq + i * (1024 / CD), r = (int)pc_udiv((uint32_t)q, a.mg_IW), col = q - r * a.IW;
         xpos[i] = r < a.IR && xleft > 0 ? (r << 16) | col : -1;
         xoff[i] = (r * a.W + col) * a.C + c0 + xp * 4;
     }
@@ -675,9 +679,7 @@ pc_f32_wgrad_kernel(const float *__restrict__ x, const float *__restrict__ dy, F
     // select behind a load would wait for it); VEC: rows of whole quads, an image within 2 GiB
     uint32_t okd = 0, okx = 0;
     auto issue = [&](int kt) {
-        int q = kt;
-        const int tc = q % a.tiles_c; q /= a.tiles_c;
-        const int tr = q % a.tiles_r, n = q / a.tiles_r;
+        const int q = divide(kt, a.tiles_c, a.mg_tc), tc = kt - q * a.tiles_c, n = divide(q, a.tiles_r, a.mg_tr), tr = q - n * a.tiles_r;
         const int oy = tr * a.TR, ox = tc * a.TC, iy = oy * a.stride - 1, ix = ox * a.stride - 1;
         const float *dimg = dy + (int64_t)n * a.Ho * a.Wo * a.F, *ximg = x + (int64_t)n * a.H * a.W * a.C;
         const int db = (oy * a.Wo + ox) * a.F, xb = (iy * a.W + ix) * a.C;
@@ -756,10 +758,12 @@ pc_f32_wgrad_kernel(const float *__restrict__ x, const float *__restrict__ dy, F
     const int e_tap = THIN && n32 < 9 * a.C ? n32 / a.C : 0;
     const int e_c = THIN ? n32 - e_tap * a.C : c0 + wc * 32 + n32;
     const bool e_on = THIN ? n32 < 9 * a.C : e_c < a.C;
-    uint32_t kinf[16];
+    constexpr int NKER = 16 / WK;                 // kernels of a lane at the end, and the first of its groups of 4 filters
+    const int quad0 = WK == 1 ? 0 : WK == 2 ? 2 * wk : 2 * (wk & 1) + (wk >> 1);
+    uint32_t kinf[NKER];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int f = f0 + wf * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
+    for (int r = 0; r < NKER; ++r) {
+        const int f = f0 + wf * 32 + 8 * (quad0 + (r >> 2)) + 4 * h + (r & 3);
         const bool on = e_on && f < a.F;
         const uint32_t u = kinfo[on ? (int64_t)f * a.C + e_c : 0];
         kinf[r] = on ? u : 0xFFFFFFFFu;
@@ -782,11 +786,66 @@ pc_f32_wgrad_kernel(const float *__restrict__ x, const float *__restrict__ dy, F
         }
         if (s < steps) multiply(0);
     }
-    // kept taps in compact order, straight from the accumulators: a lane holds one channel and 16 filters
-    float4 *pout = partial + (int64_t)(split * WK + wk) * a.pstride;
+    // Sums of wavefronts that shared pixels: partners swap halves of their groups of filters (a wavefront keeps one), of four then quarters.
+    if constexpr (WK > 1) {
+        f32x4 *mine = reinterpret_cast<f32x4 *>(smem) + wave * (2 * NT * 64) + lane;
+        const f32x4 *theirs = reinterpret_cast<const f32x4 *>(smem) + (wave ^ 1) * (2 * NT * 64) + lane;
+        const bool high = wk & 1;
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                f32x4 give;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float lo = acc[t][4 * j + i], hi = acc[t][8 + 4 * j + i];
+                    give[i] = high ? lo : hi;
+                    acc[t][4 * j + i] = high ? hi : lo;
+                }
+                mine[(t * 2 + j) * 64] = give;
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const f32x4 got = theirs[(t * 2 + j) * 64];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[t][4 * j + i] += got[i];
+                if (t % 3 == 2) __builtin_amdgcn_sched_barrier(0);
+            }
+    }
+    if constexpr (WK > 2) {
+        f32x4 *mine = reinterpret_cast<f32x4 *>(smem) + wave * (NT * 64) + lane;
+        const f32x4 *theirs = reinterpret_cast<const f32x4 *>(smem) + (wave ^ 2) * (NT * 64) + lane;
+        const bool high = wk >> 1;
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            f32x4 give;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float lo = acc[t][i], hi = acc[t][4 + i];
+                give[i] = high ? lo : hi;
+                acc[t][i] = high ? hi : lo;
+            }
+            mine[t * 64] = give;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const f32x4 got = theirs[t * 64];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[t][i] += got[i];
+        }
+    }
+    // kept taps in compact order, straight from the accumulators: a lane holds one channel and NKER filters
+    float4 *pout = partial + (int64_t)split * a.pstride;
     uint32_t redo = 0u;                           // kernels with a sum that is not finite
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
+    for (int r = 0; r < NKER; ++r) {
         const uint32_t info = kinf[r];
         if (info == 0xFFFFFFFFu) continue;
         if (THIN) {
@@ -797,9 +856,10 @@ pc_f32_wgrad_kernel(const float *__restrict__ x, const float *__restrict__ dy, F
             continue;
         }
         float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+        uint32_t bits = info << (32 - NT);
 #pragma unroll
         for (int t = NT - 1; t >= 0; --t) {           // the four set bits of the mask, ascending
-            const bool on = (info >> t) & 1u;
+            const bool on = __builtin_uadd_overflow(bits, bits, &bits);       // (tap t's: one addition that shifts it out)
             o.w = on ? o.z : o.w; o.z = on ? o.y : o.z; o.y = on ? o.x : o.y;
             o.x = on ? acc[t][r] : o.x;
         }
@@ -808,10 +868,10 @@ pc_f32_wgrad_kernel(const float *__restrict__ x, const float *__restrict__ dy, F
         redo |= z == z ? 0u : 1u << r;
     }
     // The matrix instructions multiplied the zeros around the maps and past the tile too, and 0 x Inf = NaN: these sums again,
-    // over the pixels of this wavefront that exist. (Finite data pays for the check only: 8 x 32 x 32, 16 -> 16 all three passes
+    // over the pixels of this workgroup that exist. (Finite data pays for the check only: 8 x 32 x 32, 16 -> 16 all three passes
     // 25.9 us without and with it. One infinity in 1000 elements of x: 28 x 28, 128 -> 128, batch 64 2.1 ms forward, 3.6 ms here.)
     for (; redo; redo &= redo - 1u) {
-        const int r = __ffs((int)redo) - 1, f = f0 + wf * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
+        const int r = __ffs((int)redo) - 1, f = f0 + wf * 32 + 8 * (quad0 + (r >> 2)) + 4 * h + (r & 3);
         const uint32_t info = kinfo[(int64_t)f * a.C + e_c], mask = info & 511u;
         constexpr int NK = THIN ? 1 : 4;          // kept taps of this lane's kernel
         int dr[NK], dc[NK];
@@ -829,7 +889,7 @@ pc_f32_wgrad_kernel(const float *__restrict__ x, const float *__restrict__ dy, F
             const int tc = k % a.tiles_c, q = k / a.tiles_c, tr = q % a.tiles_r, n = q / a.tiles_r;
             const float *dimg = dy + (int64_t)n * a.Ho * a.Wo * a.F + f, *ximg = x + (int64_t)n * a.H * a.W * a.C + e_c;
 #pragma unroll 2
-            for (int s = wk; s < steps; s += WK) {
+            for (int s = 0; s < steps; ++s) {
                 const int y = s / half, oy = tr * a.TR + y;
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
@@ -864,69 +924,100 @@ pc_status pc_f32_bwd_weight(pc_ctx *ctx, const pc_conv_desc *d, const pc_packed 
     a.N = d->N; a.H = d->H; a.W = d->W; a.C = d->C; a.F = d->F; a.stride = d->stride;
     a.Ho = (d->H - 1) / d->stride + 1; a.Wo = (d->W - 1) / d->stride + 1;
     const bool thin = d->C <= 3;
-    const int wf = d->F > 32 ? 2 : 1, wc = !thin && d->C > 32 ? 2 : 1, wk = 4 / (wf * wc);
-    const int FD = 32 * wf, CD = thin ? 4 : 32 * wc;
-    a.ft = (d->F + FD - 1) / FD;
-    a.ct = thin ? 1 : (d->C + CD - 1) / CD;
-    // pixel tile: the staging registers bound it; fewest matrix steps over the map, then fewest staged pixels
-    double best = -1.0;
-    const int max_pos = 256 * F32W_ND / (FD / 4);
-    for (int tr = 1; tr <= max_pos && tr <= a.Ho; ++tr)
-        for (int tc = 1; tr * tc <= max_pos && tc <= a.Wo; ++tc) {
-            const int tce = (tc + 1) / 2 * 2;
-            if (tr * tce > max_pos) break;
-            const int ir = (tr - 1) * d->stride + 3, iw = (tce - 1) * d->stride + 3;
-            if (ir * iw * (CD / 4) > 256 * F32W_NX) continue;
-            const int nr = (a.Ho + tr - 1) / tr, nc = (a.Wo + tc - 1) / tc;
-            const double steps = (double)((tr * tce / 2 + wk - 1) / wk);
-            const double cost = (double)nr * nc * (steps * 576.0 + 400.0 + 6.0 * (ir * iw * (CD / 4) + tr * tce * (FD / 4)) / 4);
-            if (best < 0.0 || cost < best) {
-                best = cost;
-                a.TR = tr; a.TC = tc; a.TCe = tce; a.IR = ir; a.IW = iw; a.tiles_r = nr; a.tiles_c = nc;
-            }
+    // The tile of an arrangement of the wavefronts; false when the staging registers do not hold it.
+    auto tile = [&](F32WgradArgs &t, int wf, int wc, int TR, int TC) {
+        const int FD = 32 * wf, CD = thin ? 4 : 32 * wc, max_pos = 256 * F32W_ND / (FD / 4);
+        t.ft = (d->F + FD - 1) / FD;
+        t.ct = thin ? 1 : (d->C + CD - 1) / CD;
+        t.TR = TR; t.TC = TC; t.TCe = (TC + 1) / 2 * 2;
+        t.IR = (TR - 1) * d->stride + 3; t.IW = (t.TCe - 1) * d->stride + 3;
+        t.nd = TR * t.TCe * (FD / 4);
+        t.nx = t.IR * t.IW * (CD / 4);
+        t.tiles_r = (t.Ho + TR - 1) / TR; t.tiles_c = (t.Wo + TC - 1) / TC;
+        return TR * t.TCe <= max_pos && t.nx <= 256 * F32W_NX;
+    };
+    // Arrangement, pixel tile and splits by an estimate of the time (us): a start, the tiles of a workgroup (a wait, staging, matrix steps; two
+    // workgroups share a CU from 256 up, two rounds from 512), the sums of wavefronts that share pixels and the pick of the kept taps, the
+    // tensors' bytes, the partial planes. Fitted to 10000 timings of 70 layers (9 % rms): 2.5 % behind the fastest, the worst 15 %; the widest
+    // tile that the channels fill and the pixel tile of the best throughput were 9 % behind (9 images 73 x 74, 416 -> 16 181 -> 153 us; 1 x 64 x 64,
+    // 48 -> 256 30 -> 22). The partial planes stay within 16 MiB. (The choice of a layer is remembered: kernel tile, pixel tile, splits.)
+    int wf = 1, wc = 1, ks = 1;
+    const int32_t key[PC_CHOICE_KEY] = {9, d->N, d->H, d->W, d->C, d->F, d->stride, (int32_t)nslots, pk->nnzk >= 0, 0};
+    bool known;
+    int32_t *choice = pc_choice(ctx, key, &known);
+    if (!known || *choice < 0) {
+        const int64_t cap = std::max((int64_t)1, ((int64_t)1 << 20) / nslots);
+        const double kept = pk->nnzk >= 0 ? (double)nslots : 0.3 * (double)nslots;
+        const double moved = 0.491e-6 * 4.0 * ((double)a.N * a.H * a.W * a.C + (double)a.N * a.Ho * a.Wo * a.F), moved3 = moved * moved * moved;
+        double best = 1e30;
+        *choice = -1;
+        for (int v = 0; v < 4; ++v) {
+            const int vf = v & 1 ? 1 : 2, vc = v & 2 || thin ? 1 : 2, wk = 4 / (vf * vc);
+            if (thin && (v & 2)) continue;
+            const double end = wk == 1 ? 0.78 : wk == 2 ? 0.39 : 1.2;
+            F32WgradArgs t = a;
+            for (int TR = 1; TR <= 64 && TR <= a.Ho; ++TR)
+                for (int TC = 1; TC <= 64 && TC <= a.Wo && tile(t, vf, vc, TR, TC); ++TC) {
+                    const int64_t nkt = (int64_t)t.N * t.tiles_r * t.tiles_c, T = (int64_t)t.ft * t.ct;
+                    const double steps = (double)((TR * t.TCe / 2 + wk - 1) / wk), staged = (t.nd + t.nx) / 256.0;
+                    const double lone = 0.514 + 0.314 * (thin ? 0.25 : 1.0) * steps, pair = 0.618 + 0.0194 * staged + 0.468 * (thin ? 0.25 : 1.0) * steps;
+                    for (int places = 2 * ctx->num_cu; places >= ctx->num_cu / 2; places >>= 1) {
+                        const int64_t k = std::max((int64_t)1, std::min(std::min(cap, nkt), (places + T - 1) / T)), G = T * k;
+                        const double u = (double)((nkt + k - 1) / k);
+                        const double us = 6.65 + (G <= ctx->num_cu ? u * lone + end : (double)((G + 2 * ctx->num_cu - 1) / (2 * ctx->num_cu)) * (u * pair + 1.7 * end));
+                        const double c = cbrt(us * us * us + moved3) + (k > 1 ? 2.2 + 11.5e-6 * (double)k * kept : 0.0);
+                        if (c < best) {
+                            best = c;
+                            *choice = (vf - 1) | (vc - 1) << 1 | TR << 2 | TC << 9 | (int32_t)k << 16;
+                        }
+                    }
+                }
         }
-    if (best < 0.0) return pc_fail(ctx, PC_ERR_UNSUPPORTED, "float32 bwd_weight: no pixel tile fits");
+        if (*choice < 0) return pc_fail(ctx, PC_ERR_UNSUPPORTED, "float32 bwd_weight: no pixel tile fits");
+    }
+    wf = 1 + (*choice & 1); wc = 1 + (*choice >> 1 & 1); ks = *choice >> 16;
+    tile(a, wf, wc, *choice >> 2 & 127, *choice >> 9 & 127);
+    const int wk = 4 / (wf * wc), FD = 32 * wf, CD = thin ? 4 : 32 * wc;
     const int64_t nkt = (int64_t)a.N * a.tiles_r * a.tiles_c;
     if (nkt >= ((int64_t)1 << 31)) return pc_fail(ctx, PC_ERR_UNSUPPORTED, "float32 bwd_weight: too many pixel tiles");
     a.n_tiles = (int)nkt;
-    a.nd = a.TR * a.TCe * (FD / 4);
-    a.nx = a.IR * a.IW * (CD / 4);
-    a.mg_half = pc_udiv_magic(a.TCe / 2);
+    a.mg_half = pc_udiv_magic(a.TCe / 2); a.mg_TCe = pc_udiv_magic(a.TCe); a.mg_IW = pc_udiv_magic(a.IW);
     a.pstride = nslots;
-    // two workgroups per CU; the partial planes stay within 16 MiB
-    int64_t ks = (2 * (int64_t)ctx->num_cu + a.ft * a.ct - 1) / ((int64_t)a.ft * a.ct);
-    const int64_t cap = ((int64_t)1 << 20) / (nslots * wk);
-    if (ks > cap) ks = cap;
-    if (ks > a.n_tiles) ks = a.n_tiles;
-    if (ks < 1) ks = 1;
-    a.ksplit = (int)ks;
-    const int planes = a.ksplit * wk;
+    a.ksplit = ks;
+    const int64_t wgs = (int64_t)a.ft * a.ct * ks;
+    a.exact = nkt * (a.tiles_c > a.tiles_r ? a.tiles_c : a.tiles_r) < ((int64_t)1 << 32) && wgs * (ks > a.ct ? ks : a.ct) < ((int64_t)1 << 32);
+    a.mg_tc = pc_udiv_magic(a.tiles_c); a.mg_tr = pc_udiv_magic(a.tiles_r); a.mg_ks = pc_udiv_magic(a.ksplit); a.mg_ct = pc_udiv_magic(a.ct);
+    const int planes = a.ksplit;
     void *scr = nullptr;
     if (planes > 1) {
         pc_status s = pc_scratch(ctx, sizeof(float4) * (size_t)planes * (size_t)nslots, &scr);
         if (s != PC_OK) return s;
     }
     const int PD = FD + 4, PX = thin ? 4 : CD + 4;
-    const size_t lds = sizeof(float) * ((size_t)a.TR * a.TCe * PD + (size_t)a.IR * a.IW * PX);
+    size_t lds = sizeof(float) * ((size_t)a.TR * a.TCe * PD + (size_t)a.IR * a.IW * PX);
+    if (wk > 1 && lds < (size_t)(thin ? 1 : 9) * 8 * 1024) lds = (size_t)(thin ? 1 : 9) * 8 * 1024;      // in which the sums of wavefronts are added
     const dim3 grid((unsigned)(a.ft * a.ct * a.ksplit)), blk(256);
     float4 *po = planes > 1 ? (float4 *)scr : (float4 *)dw;
     const float *xp = (const float *)x, *dp = (const float *)dy;
     hipStream_t st = ctx->stream;
     const bool vec = (d->F & 3) == 0 && (d->C & 3) == 0 && (int64_t)a.H * a.W * a.C * 4 < ((int64_t)1 << 31) &&
                      (int64_t)a.Ho * a.Wo * a.F * 4 < ((int64_t)1 << 31);
-#define F32W_LAUNCH(WF, WC)                                                                                                              \
-    do {                                                                                                                                 \
-        if (vec) hipLaunchKernelGGL((pc_f32_wgrad_kernel<WF, WC, false, true>), grid, blk, lds, st, xp, dp, a, pk->v.kinfo, po);         \
-        else hipLaunchKernelGGL((pc_f32_wgrad_kernel<WF, WC, false, false>), grid, blk, lds, st, xp, dp, a, pk->v.kinfo, po);            \
-    } while (0)
-    if (thin && wf == 2) hipLaunchKernelGGL((pc_f32_wgrad_kernel<2, 1, true, false>), grid, blk, lds, st, xp, dp, a, pk->v.kinfo, po);
-    else if (thin) hipLaunchKernelGGL((pc_f32_wgrad_kernel<1, 1, true, false>), grid, blk, lds, st, xp, dp, a, pk->v.kinfo, po);
-    else if (wf == 2 && wc == 2) F32W_LAUNCH(2, 2);
-    else if (wf == 2) F32W_LAUNCH(2, 1);
-    else if (wc == 2) F32W_LAUNCH(1, 2);
-    else F32W_LAUNCH(1, 1);
-#undef F32W_LAUNCH
-    pc_note_kernel(ctx, "pc_f32_wgrad_kernel<%d, %d, %s, %s>", wf, wc, thin ? "true" : "false", vec ? "true" : "false");
+    typedef void (*Kernel)(const float *, const float *, F32WgradArgs, const uint32_t *, float4 *);
+    static const struct { Kernel f; int wf, wc; bool thin, vec; } kernels[] = {
+#define F32W(A, B, T, V) {&pc_f32_wgrad_kernel<A, B, T, V>, A, B, T, V}
+        F32W(2, 1, true, false), F32W(1, 1, true, false), F32W(2, 2, false, true), F32W(2, 2, false, false), F32W(2, 1, false, true), F32W(2, 1, false, false),
+        F32W(1, 2, false, true), F32W(1, 2, false, false), F32W(1, 1, false, true), F32W(1, 1, false, false)};
+#undef F32W
+    constexpr int n_kernels = sizeof(kernels) / sizeof(kernels[0]);
+    static pc_per_device_once attr[n_kernels];
+    int k = 0;
+    while (kernels[k].wf != wf || kernels[k].wc != wc || kernels[k].thin != thin || (!thin && kernels[k].vec != vec)) ++k;
+    if (lds > 64 * 1024 && pc_once_pending(attr[k], ctx->device)) {
+        PC_HIP(ctx, hipFuncSetAttribute((const void *)kernels[k].f, hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024));
+        pc_once_done(attr[k], ctx->device);
+    }
+    hipLaunchKernelGGL(kernels[k].f, grid, blk, lds, st, xp, dp, a, pk->v.kinfo, po);
+    pc_note_kernel(ctx, "pc_f32_wgrad_kernel<%d, %d, %s, %s>", wf, wc, thin ? "true" : "false", kernels[k].vec ? "true" : "false");
     pc_status s = pc_hip_check(ctx, hipGetLastError(), "float32 bwd_weight launch");
     if (s != PC_OK || planes == 1) return s;
     return pc_launch_wgrad_reduce(ctx, (const float *)scr, planes, nslots, nslots, pk, dw);

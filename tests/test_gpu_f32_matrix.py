@@ -38,3 +38,12 @@ def test_edges(B, ctx, oracle, shape):
 def test_gather_kernels_still_take_float32(B, ctx, oracle, shape):
     run_case(B, ctx, oracle, shape, "f32", 8, 0.4, B.PC_VARIANT_VALU, "f32_gather")
     assert B.pc_last_kernel(ctx).startswith("pc_wgrad_valu_kernel")
+
+
+@pytest.mark.parametrize("waves,shape", [
+    ("1, 1", (1, 12, 1, 8, 200, 1)), ("1, 1", (1, 28, 3, 32, 8, 2)), ("1, 2", (2, 3, 2, 8, 16, 2)), ("1, 2", (3, 9, 11, 40, 24, 1)), ("1, 2", (4, 13, 13, 100, 66, 2)),
+    ("2, 1", (14, 21, 1, 8, 64, 1)), ("2, 1", (4, 10, 15, 8, 33, 1)), ("2, 1", (3, 30, 31, 2, 50, 2)), ("1, 1", (1, 15, 6, 33, 33, 2))])
+def test_wavefronts_that_share_pixels(B, ctx, oracle, waves, shape):
+    """Weight gradients whose wavefronts add their sums in LDS: two and four of them, rows of quads and not, the (tap, channel) columns of a first layer."""
+    run_case(B, ctx, oracle, shape, "f32", 8, 0.4, B.PC_VARIANT_AUTO, "f32_shared")
+    assert B.pc_last_kernel(ctx).startswith("pc_f32_wgrad_kernel<%s, " % waves)
