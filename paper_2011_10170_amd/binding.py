@@ -1,4 +1,5 @@
-"""ctypes binding of libpatconv.so: the same entry points as include/pc.h, argument marshalling only.
+"""Binding of libpatconv.so: the same entry points as include/pc.h, argument marshalling only. The calls of a training or serving loop
+are marshalled by _native (csrc/pc_python.cpp), the others by ctypes.
 
 Device buffers are passed as anything with a ``data_ptr()`` method (torch tensors on the context's
 GPU) or as integer addresses. Nothing here computes: every step runs in the library's kernels.
@@ -7,6 +8,7 @@ There is no fallback: if the library is missing, load() raises.
 from __future__ import annotations
 
 import ctypes as ct
+import importlib
 import os
 from typing import Optional, Sequence
 
@@ -45,12 +47,23 @@ class PcError(RuntimeError):
 _lib = None
 
 
+class _Unloaded:
+    """Stands for _native until the library is loaded."""
+
+    def __getattr__(self, name):
+        load()
+        return getattr(_native, name)
+
+
+_native = _Unloaded()
+
+
 def load():
     """Loads libpatconv.so. Raises if it has not been built (paper_2011_10170_amd/build.py)."""
-    global _lib
+    global _lib, _native
     if _lib is not None:
         return _lib
-    if not os.path.exists(LIB_PATH):
+    if not os.path.exists(LIB_PATH) or not os.path.exists(os.path.join(HERE, "_native.so")):
         raise RuntimeError("libpatconv.so is not built: run `python -m paper_2011_10170_amd.build` "
                            "(there is no CPU fallback)")
     lib = ct.CDLL(LIB_PATH)
@@ -101,7 +114,9 @@ def load():
         fn = getattr(lib, name)
         if name not in ("pc_destroy", "pc_packed_free", "pc_status_str", "pc_last_error", "pc_last_kernel"):
             fn.restype = ct.c_int
-    _lib = lib
+    native = importlib.import_module("paper_2011_10170_amd._native")
+    native.bind({name: ct.cast(getattr(lib, name), vp).value for name in EXPORTS})
+    _lib, _native = lib, native
     return lib
 
 
@@ -164,12 +179,17 @@ def pc_check_conv_desc(desc: pc_conv_desc) -> int:
 
 
 def pc_pattern_select(ctx, W, G, F, C, masks, keep_mode, n_keep, score_mode, pid, keep) -> None:
-    arr = _lib_arr(masks)
-    _check(ctx, load().pc_pattern_select(ctx, _ptr(W), _ptr(G), int(F), int(C), ct.cast(arr, ct.c_void_p), len(masks),
-                                         int(keep_mode), int(n_keep), int(score_mode), _ptr(pid), _ptr(keep)))
+    status = _native.pattern_select(ctx, W, G, F, C, masks, keep_mode, n_keep, score_mode, pid, keep)
+    if status:
+        _check(ctx, status)
 
 
 def pc_pack(ctx, W, pid, keep, F, C, masks, compute_dtype, reuse: Optional[int] = None) -> int:
+    if reuse:
+        status = _native.pack(ctx, W, pid, keep, F, C, masks, compute_dtype, reuse)
+        if status:
+            _check(ctx, status)
+        return reuse
     arr = _lib_arr(masks)
     out = ct.c_void_p(reuse)
     _check(ctx, load().pc_pack(ctx, _ptr(W), _ptr(pid), _ptr(keep), int(F), int(C), ct.cast(arr, ct.c_void_p),
@@ -178,7 +198,9 @@ def pc_pack(ctx, W, pid, keep, F, C, masks, compute_dtype, reuse: Optional[int] 
 
 
 def pc_update_values(ctx, pk, W) -> None:
-    _check(ctx, load().pc_update_values(ctx, pk, _ptr(W)))
+    status = _native.update_values(ctx, pk, W)
+    if status:
+        _check(ctx, status)
 
 
 def pc_packed_info(ctx, pk):
@@ -193,23 +215,33 @@ def pc_packed_free(pk) -> None:
 
 
 def pc_scatter_dense(ctx, pk, compact, dense) -> None:
-    _check(ctx, load().pc_scatter_dense(ctx, pk, _ptr(compact), _ptr(dense)))
+    status = _native.scatter_dense(ctx, pk, compact, dense)
+    if status:
+        _check(ctx, status)
 
 
 def pc_unpack_dense(ctx, pk, dense) -> None:
-    _check(ctx, load().pc_unpack_dense(ctx, pk, _ptr(dense)))
+    status = _native.unpack_dense(ctx, pk, dense)
+    if status:
+        _check(ctx, status)
 
 
 def pc_conv_fwd(ctx, desc, pk, x, y) -> None:
-    _check(ctx, load().pc_conv_fwd(ctx, ct.byref(desc), pk, _ptr(x), _ptr(y)))
+    status = _native.conv_fwd(ctx, desc, pk, x, y)
+    if status:
+        _check(ctx, status)
 
 
 def pc_conv_bwd_data(ctx, desc, pk, dy, dx) -> None:
-    _check(ctx, load().pc_conv_bwd_data(ctx, ct.byref(desc), pk, _ptr(dy), _ptr(dx)))
+    status = _native.conv_bwd_data(ctx, desc, pk, dy, dx)
+    if status:
+        _check(ctx, status)
 
 
 def pc_conv_bwd_weight(ctx, desc, pk, x, dy, dw_compact) -> None:
-    _check(ctx, load().pc_conv_bwd_weight(ctx, ct.byref(desc), pk, _ptr(x), _ptr(dy), _ptr(dw_compact)))
+    status = _native.conv_bwd_weight(ctx, desc, pk, x, dy, dw_compact)
+    if status:
+        _check(ctx, status)
 
 
 def pc_conv_bwd_weight_noalloc(ctx, desc, pk, x, dy, dw_compact) -> None:
@@ -231,11 +263,15 @@ def pc_dppg_pool(ctx, hist, n_patterns: int):
 
 
 def pc_finalize_count(ctx, pid, F, C, P, counts) -> None:
-    _check(ctx, load().pc_finalize_count(ctx, _ptr(pid), int(F), int(C), int(P), _ptr(counts)))
+    status = _native.finalize_count(ctx, pid, F, C, P, counts)
+    if status:
+        _check(ctx, status)
 
 
 def pc_finalize_pick(ctx, counts, F, C, P, pid) -> None:
-    _check(ctx, load().pc_finalize_pick(ctx, _ptr(counts), int(F), int(C), int(P), _ptr(pid)))
+    status = _native.finalize_pick(ctx, counts, F, C, P, pid)
+    if status:
+        _check(ctx, status)
 
 
 def pc_group_lasso_grad(ctx, W, pid, keep, F, C, masks, lambda_p, lambda_i, dW, penalty=None) -> None:
@@ -245,11 +281,15 @@ def pc_group_lasso_grad(ctx, W, pid, keep, F, C, masks, lambda_p, lambda_i, dW, 
 
 
 def pc_act_pool_fwd(ctx, z, N, H, W, C, dtype, pool, a, sel) -> None:
-    _check(ctx, load().pc_act_pool_fwd(ctx, _ptr(z), int(N), int(H), int(W), int(C), int(dtype), int(pool), _ptr(a), _ptr(sel)))
+    status = _native.act_pool_fwd(ctx, z, N, H, W, C, dtype, pool, a, sel)
+    if status:
+        _check(ctx, status)
 
 
 def pc_act_pool_bwd(ctx, da, sel, N, H, W, C, dtype, pool, dz) -> None:
-    _check(ctx, load().pc_act_pool_bwd(ctx, _ptr(da), _ptr(sel), int(N), int(H), int(W), int(C), int(dtype), int(pool), _ptr(dz)))
+    status = _native.act_pool_bwd(ctx, da, sel, N, H, W, C, dtype, pool, dz)
+    if status:
+        _check(ctx, status)
 
 
 def _ptr_array(items):
@@ -258,25 +298,22 @@ def _ptr_array(items):
 
 def pc_pattern_select_batch(ctx, W, G, F, C, masks, keep_mode, n_keep, score_mode, pid, keep) -> None:
     """W, G (or None), pid, keep: lists of device tensors; F, C, n_keep: lists of ints."""
-    n = len(W)
-    arr = _lib_arr(masks)
-    _check(ctx, load().pc_pattern_select_batch(
-        ctx, n, _ptr_array(W), _ptr_array(G) if G is not None else None, (ct.c_int32 * n)(*[int(v) for v in F]),
-        (ct.c_int32 * n)(*[int(v) for v in C]), ct.cast(arr, ct.c_void_p), len(masks), int(keep_mode),
-        (ct.c_int64 * n)(*[int(v) for v in n_keep]), int(score_mode), _ptr_array(pid), _ptr_array(keep)))
+    status = _native.pattern_select_batch(ctx, W, G, F, C, masks, keep_mode, n_keep, score_mode, pid, keep)
+    if status:
+        _check(ctx, status)
 
 
 def pc_pack_batch(ctx, W, pid, keep, masks, packs) -> None:
     """Re-packs the existing handles `packs` (a list) from lists of device tensors."""
-    n = len(W)
-    arr = _lib_arr(masks)
-    _check(ctx, load().pc_pack_batch(ctx, n, _ptr_array(W), _ptr_array(pid), _ptr_array(keep), ct.cast(arr, ct.c_void_p),
-                                     len(masks), (ct.c_void_p * n)(*[int(p) for p in packs])))
+    status = _native.pack_batch(ctx, W, pid, keep, masks, packs)
+    if status:
+        _check(ctx, status)
 
 
 def pc_update_values_batch(ctx, packs, W) -> None:
-    n = len(packs)
-    _check(ctx, load().pc_update_values_batch(ctx, n, (ct.c_void_p * n)(*[int(p) for p in packs]), _ptr_array(W)))
+    status = _native.update_values_batch(ctx, packs, W)
+    if status:
+        _check(ctx, status)
 
 
 def _i32_array(vals):
@@ -284,37 +321,43 @@ def _i32_array(vals):
 
 
 def pc_dppg_accumulate_batch(ctx, W, G, F, C, hist, masks=None) -> None:
-    _check(ctx, load().pc_dppg_accumulate_batch(ctx, len(W), _ptr_array(W), _ptr_array(G) if G is not None else None,
-                                                _i32_array(F), _i32_array(C), _ptr(hist),
-                                                _ptr_array(masks) if masks is not None else None))
+    status = _native.dppg_accumulate_batch(ctx, W, G, F, C, hist, masks)
+    if status:
+        _check(ctx, status)
 
 
 def pc_finalize_count_batch(ctx, pid, F, C, P, counts) -> None:
-    _check(ctx, load().pc_finalize_count_batch(ctx, len(pid), _ptr_array(pid), _i32_array(F), _i32_array(C), int(P), _ptr_array(counts)))
+    status = _native.finalize_count_batch(ctx, pid, F, C, P, counts)
+    if status:
+        _check(ctx, status)
 
 
 def pc_finalize_pick_batch(ctx, counts, F, C, P, pid) -> None:
-    _check(ctx, load().pc_finalize_pick_batch(ctx, len(pid), _ptr_array(counts), _i32_array(F), _i32_array(C), int(P), _ptr_array(pid)))
+    status = _native.finalize_pick_batch(ctx, counts, F, C, P, pid)
+    if status:
+        _check(ctx, status)
 
 
 def pc_group_lasso_grad_batch(ctx, W, pid, keep, F, C, masks, lambda_p, lambda_i, dW, penalty=None) -> None:
-    arr = _lib_arr(masks)
-    _check(ctx, load().pc_group_lasso_grad_batch(ctx, len(W), _ptr_array(W), _ptr_array(pid), _ptr_array(keep), _i32_array(F),
-                                                 _i32_array(C), ct.cast(arr, ct.c_void_p), len(masks), float(lambda_p),
-                                                 float(lambda_i), _ptr_array(dW), _ptr(penalty)))
+    status = _native.group_lasso_grad_batch(ctx, W, pid, keep, F, C, masks, lambda_p, lambda_i, dW, penalty)
+    if status:
+        _check(ctx, status)
 
 
 def pc_conv_bwd_weight_batch(ctx, descs, packs, x, dy, dw) -> None:
     """descs: list of pc_conv_desc; packs: list of handles; x, dy, dw: lists of device tensors."""
-    n = len(descs)
-    darr = (pc_conv_desc * n)(*descs)
-    _check(ctx, load().pc_conv_bwd_weight_batch(ctx, n, ct.cast(darr, ct.c_void_p), (ct.c_void_p * n)(*[int(p) for p in packs]),
-                                                _ptr_array(x), _ptr_array(dy), _ptr_array(dw)))
+    status = _native.conv_bwd_weight_batch(ctx, descs, packs, x, dy, dw)
+    if status:
+        _check(ctx, status)
 
 
 def pc_conv_fwd_relu(ctx, desc, pk, x, a) -> None:
-    _check(ctx, load().pc_conv_fwd_relu(ctx, ct.byref(desc), pk, _ptr(x), _ptr(a)))
+    status = _native.conv_fwd_relu(ctx, desc, pk, x, a)
+    if status:
+        _check(ctx, status)
 
 
 def pc_conv_bwd_data_relu(ctx, desc, pk, dy, x, dx) -> None:
-    _check(ctx, load().pc_conv_bwd_data_relu(ctx, ct.byref(desc), pk, _ptr(dy), _ptr(x), _ptr(dx)))
+    status = _native.conv_bwd_data_relu(ctx, desc, pk, dy, x, dx)
+    if status:
+        _check(ctx, status)

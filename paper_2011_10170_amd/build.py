@@ -1,15 +1,17 @@
-"""Builds libpatconv.so (HIP, gfx950 only) in-tree with hipcc."""
+"""Builds libpatconv.so (HIP, gfx950 only) with hipcc and the binding's marshalling (_native.so) with g++, in-tree."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpatconv.so")
+NATIVE = os.path.join(HERE, "_native.so")
 SOURCES = ["pc_api.hip", "pc_select_pack.hip", "pc_conv_valu.hip", "pc_conv_mfma.hip", "pc_conv_mfma_ws.hip",
            "pc_wgrad_mfma.hip", "pc_train_steps.hip", "pc_act_pool.hip", "pc_conv_thin.hip",
            "pc_conv_f32.hip", "pc_conv_dma.hip", "pc_wgrad_dma.hip"]
@@ -53,6 +55,11 @@ def build(verbose: bool = False) -> str:
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n%s\n%s" % (r.stdout, r.stderr))
+    cmd = ["g++", "-O2", "-std=c++17", "-Wall", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"),
+           os.path.join(CSRC, "pc_python.cpp"), "-o", NATIVE]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed for pc_python.cpp:\n%s\n%s" % (r.stdout, r.stderr))
     return LIB
 
 

@@ -44,15 +44,37 @@ extern "C" const char *pc_status_str(pc_status s)
 
 extern "C" const char *pc_last_error(const pc_ctx *ctx) { return ctx ? ctx->err : "no context"; }
 
+// The symbol is made when it is asked for: printing it took a tenth of a call's host time. (%d and %s only, strings that outlive the context.)
 void pc_note_kernel(pc_ctx *ctx, const char *fmt, ...)
 {
     va_list ap;
     va_start(ap, fmt);
-    vsnprintf(ctx->last_kernel, sizeof(ctx->last_kernel), fmt, ap);
+    int n = 0;
+    for (const char *p = fmt; *p; ++p)
+        if (*p == '%' && n < PC_NOTE_ARGS) {
+            if (*++p == 's') ctx->note_arg[n++] = (intptr_t)va_arg(ap, const char *);
+            else ctx->note_arg[n++] = va_arg(ap, int);
+        }
     va_end(ap);
+    ctx->note = fmt;
 }
 
-extern "C" const char *pc_last_kernel(const pc_ctx *ctx) { return ctx ? ctx->last_kernel : ""; }
+extern "C" const char *pc_last_kernel(const pc_ctx *ctx)
+{
+    if (!ctx || !ctx->note) return "";
+    pc_ctx *c = const_cast<pc_ctx *>(ctx);
+    size_t at = 0;
+    int n = 0;
+    for (const char *p = ctx->note; *p && at + 1 < sizeof(c->last_kernel); ++p) {
+        if (*p != '%') { c->last_kernel[at++] = *p; continue; }
+        const size_t room = sizeof(c->last_kernel) - at;
+        const int w = *++p == 's' ? snprintf(c->last_kernel + at, room, "%s", (const char *)ctx->note_arg[n]) : snprintf(c->last_kernel + at, room, "%d", (int)ctx->note_arg[n]);
+        ++n;
+        at += w < 0 ? 0 : (size_t)w < room ? (size_t)w : room - 1;
+    }
+    c->last_kernel[at] = 0;
+    return c->last_kernel;
+}
 
 // ------------------------------------------------------------------ host-only checks
 extern "C" pc_status pc_check_library(const uint16_t *lib, int32_t P)

@@ -17,6 +17,7 @@
 #define PC_OV_BAD 0xFFFFFFFFu
 
 struct pc_stream_ref;
+#define PC_NOTE_ARGS 8
 #define PC_CHOICES 512         // a network of 16 layers has 48 entries
 #define PC_CHOICE_WAYS 4       // places that a shape may take: five of 48 shapes meet in one set once in 150 networks
 #define PC_CHOICE_KEY 10
@@ -36,7 +37,9 @@ struct pc_ctx {
     int n_retired, cap_retired;
     bool fixed_scratch;    // set for the duration of an entry point that must not allocate: pc_scratch then hands out the
                            // device's fixed buffer, or fails when the request exceeds it
-    char last_kernel[160]; // symbol of the kernel that did the work of the last conv call (pc_last_kernel)
+    char last_kernel[160]; // symbol of the kernel that did the work of the last conv call (pc_last_kernel), made from
+    const char *note;      // its format and
+    intptr_t note_arg[PC_NOTE_ARGS];
     pc_stream_ref *ref;
     // kernels chosen for the shapes seen last (an estimate over all candidates takes longer than a launch)
     struct { int32_t key[PC_CHOICE_KEY]; int32_t kernel; } choice[PC_CHOICES];

@@ -1,0 +1,72 @@
+"""The native argument marshalling of the binding, on the CPU: what it takes for tensors, integers and lists, and what it refuses."""
+import numpy as np
+import pytest
+
+from paper_2011_10170_amd import binding as B
+
+
+class Tensor:
+    def data_ptr(self):
+        return 1 << 63 | 4096
+
+
+class Broken:
+    def data_ptr(self):
+        raise RuntimeError("no storage")
+
+
+DESC = B.make_desc(1, 4, 4, 8, 8, 1, B.PC_BF16)
+MASKS = [0x1B0, 0x0D8]
+
+
+def refused(call):
+    """The library is reached and refuses the null context."""
+    with pytest.raises(B.PcError) as e:
+        call()
+    assert e.value.status == B.PC_ERR_INVALID_ARG
+
+
+def test_arguments_reach_the_library():
+    t = Tensor()
+    refused(lambda: B.pc_conv_fwd(None, DESC, None, t, 64))
+    refused(lambda: B.pc_conv_bwd_weight(None, DESC, 0, t, np.int64(64), t))
+    refused(lambda: B.pc_act_pool_fwd(None, t, np.int32(1), 2.0, 2, 8, B.PC_BF16, 2, t, t))
+    refused(lambda: B.pc_pattern_select(None, t, None, 8, 8, MASKS, 0, 4, 0, t, t))
+    refused(lambda: B.pc_pattern_select_batch(None, [t, 64], None, [8, 8], (8, np.int64(8)), MASKS, 0, [4, 4], 0, [t, t], [t, t]))
+    refused(lambda: B.pc_pack_batch(None, [t], [t], [t], MASKS, [64]))
+    refused(lambda: B.pc_conv_bwd_weight_batch(None, [DESC, DESC], [64, 64], [t, t], [t, t], [t, t]))
+    refused(lambda: B.pc_group_lasso_grad_batch(None, [t], [t], [t], [8], [8], MASKS, 1, 1e-4, [t], penalty=None))
+    refused(lambda: B.pc_finalize_pick_batch(None, [t, t], [8], [8], 4, [t]))      # (one layer: what goes beyond is not read)
+
+
+def test_what_is_no_argument():
+    t = Tensor()
+    with pytest.raises(RuntimeError, match="no storage"):
+        B.pc_conv_fwd(None, DESC, None, Broken(), t)
+    for bad in (object(), "x"):
+        with pytest.raises((TypeError, ValueError)):
+            B.pc_conv_fwd(None, DESC, None, bad, t)
+    with pytest.raises(TypeError):
+        B.pc_conv_fwd(None, None, None, t, t)
+    with pytest.raises(TypeError):
+        B.pc_conv_fwd(None, np.zeros(3, np.int32), None, t, t)
+    with pytest.raises(TypeError):
+        B.pc_update_values_batch(None, 5, [t])
+    with pytest.raises(OverflowError):
+        B.pc_conv_fwd(None, DESC, 1 << 70, t, t)
+
+
+@pytest.mark.parametrize("call", [
+    lambda t: B.pc_pattern_select_batch(None, [t, t], [t], [8, 8], [8, 8], MASKS, 0, [4, 4], 0, [t, t], [t, t]),
+    lambda t: B.pc_pattern_select_batch(None, [t, t], [t, t], [8], [8, 8], MASKS, 0, [4, 4], 0, [t, t], [t, t]),
+    lambda t: B.pc_pattern_select_batch(None, [t, t], [t, t], [8, 8], [8, 8], MASKS, 0, [4, 4, 4], 0, [t, t], [t, t]),
+    lambda t: B.pc_pack_batch(None, [t], [t], [t], MASKS, [64, 64]),
+    lambda t: B.pc_update_values_batch(None, [64, 64], [t]),
+    lambda t: B.pc_conv_bwd_weight_batch(None, [DESC, DESC], [64, 64], [t, t], [t], [t, t]),
+    lambda t: B.pc_finalize_count_batch(None, [t, t], [8, 8], [8], 4, [t, t]),
+    lambda t: B.pc_finalize_pick_batch(None, [t], [8, 8], [8, 8], 4, [t, t]),
+    lambda t: B.pc_dppg_accumulate_batch(None, [t, t], [t, t], [8, 8], [8, 8], t, [t]),
+    lambda t: B.pc_group_lasso_grad_batch(None, [t], [t], [], [8], [8], MASKS, 1e-4, 1e-4, [t])])
+def test_lists_of_different_lengths(call):
+    with pytest.raises(ValueError):
+        call(Tensor())
