@@ -19,7 +19,7 @@
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 struct ThinArgs {
-    int32_t N, H, W, C, F;       // C: the thin side (<= 4 channels), F: the wide side (a multiple of 32)
+    int32_t N, H, W, C, F;       // C: the thin side (<= 4 channels), F: the wide side (a multiple of 8; backward-data: 32 or 64)
     int32_t TH, TW, LW;          // output tile, and pixels per staged row (TW + 2)
     int32_t tiles_y, tiles_x;
     int32_t KS;                  // k-steps of 16 per tap in the operand tiles
@@ -30,7 +30,8 @@ struct ThinArgs {
 constexpr uint32_t THIN_OOB = 0x80000000u;   // past any tensor these kernels accept: loads return zero, stores are dropped
 
 // ------------------------------------------------------------------ forward
-// NFT: row tiles of 32 filters. Workgroup: TH output rows x TW (a multiple of 32) columns of one image.
+// NFT: row tiles of 32 filters (the last may be partly empty: zero rows of the operand, not stored; before it took such widths, 7 images 139 x 139,
+// 3 -> 56 went through the cooperative kernel and a launch for the ReLU). Workgroup: TH output rows x TW (a multiple of 32) columns of one image.
 // wz: the forward operand tiles [F/32][9][KS][64 lanes][8] (lane = (filter % 32, half), 8 channels each).
 template <int NFT, int ACT>
 __global__ void __launch_bounds__(256) pc_thin_fwd_kernel(const uint16_t *__restrict__ x, uint16_t *__restrict__ y,
@@ -120,7 +121,7 @@ __global__ void __launch_bounds__(256) pc_thin_fwd_kernel(const uint16_t *__rest
                     for (int e = 0; e < 4; ++e) pv[e] &= ~(((pv[e] & 0x80008000u) >> 15) * 0xFFFFu);   // negative (or -0) -> +0
                 }
                 // filters 32 t + 16 h + 8 g + (0..7)
-                __builtin_amdgcn_raw_buffer_store_b128(pv, ysrc, (int)(ok ? obase + (uint32_t)((32 * t + 16 * h + 8 * g) * 2) : THIN_OOB), 0, 0);
+                __builtin_amdgcn_raw_buffer_store_b128(pv, ysrc, (int)(ok && 32 * t + 16 * h + 8 * g < a.F ? obase + (uint32_t)((32 * t + 16 * h + 8 * g) * 2) : THIN_OOB), 0, 0);
             }
         }
     }
@@ -268,7 +269,7 @@ static void thin_fwd_launch(hipStream_t st, unsigned grid, size_t lds, const uin
 pc_status pc_thin_fwd(pc_ctx *ctx, const pc_conv_desc *d, const pc_packed *pk, const void *x, void *y, int act, bool *launched)
 {
     *launched = false;
-    if (d->stride != 1 || d->C > 4 || (d->F & 31) || d->F > 128 || (act != PC_ACT_NONE && act != PC_ACT_RELU)) return PC_OK;
+    if (d->stride != 1 || d->C > 4 || (d->F & 7) || d->F > 128 || (act != PC_ACT_NONE && act != PC_ACT_RELU)) return PC_OK;
     int TW = (d->W + 31) / 32 * 32;
     if (TW > 256) TW = 256;
     // Tiles of 8 rows of up to 256 pixels read their border least, but a small batch has too few of them: cut down to a workgroup
@@ -287,14 +288,15 @@ pc_status pc_thin_fwd(pc_ctx *ctx, const pc_conv_desc *d, const pc_packed *pk, c
     const unsigned grid = (unsigned)((int64_t)d->N * a.tiles_y * a.tiles_x);
     const uint16_t *xs = static_cast<const uint16_t *>(x);
     uint16_t *ys = static_cast<uint16_t *>(y);
-    switch (d->F / 32) {
+    const int nft = (d->F + 31) / 32;
+    switch (nft) {
     case 1: thin_fwd_launch<1>(ctx->stream, grid, lds, xs, ys, pk->v.wz_fwd, a, act); break;
     case 2: thin_fwd_launch<2>(ctx->stream, grid, lds, xs, ys, pk->v.wz_fwd, a, act); break;
     case 3: thin_fwd_launch<3>(ctx->stream, grid, lds, xs, ys, pk->v.wz_fwd, a, act); break;
     default: thin_fwd_launch<4>(ctx->stream, grid, lds, xs, ys, pk->v.wz_fwd, a, act); break;
     }
     *launched = true;
-    pc_note_kernel(ctx, "pc_thin_fwd_kernel<%d, %d>", d->F / 32, act);
+    pc_note_kernel(ctx, "pc_thin_fwd_kernel<%d, %d>", nft, act);
     return pc_hip_check(ctx, hipGetLastError(), "first-layer forward launch");
 }
 

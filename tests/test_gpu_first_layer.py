@@ -113,3 +113,24 @@ def test_backward_weight_of_few_channels(B, ctx, oracle, shape):
             assert np.array_equal(got.cpu().numpy(), want)
     finally:
         g.close()
+
+
+@pytest.mark.parametrize("shape", [(2, 9, 37, 3, 8, 1), (1, 5, 300, 4, 24, 1), (3, 16, 32, 1, 56, 1), (2, 17, 33, 2, 104, 1)])
+def test_forward_with_a_row_tile_that_is_not_full(B, ctx, oracle, shape):
+    """Filter counts that are multiples of 8 only: nothing is stored past the last filter, with and without the fused ReLU."""
+    import torch
+    from tests._harness import Case, GpuLayer, Guarded
+    run_case(B, ctx, oracle, shape, "bf16", 8, 0.4, B.PC_VARIANT_MFMA, "first_layer_rows")
+    L = I.Layer(*shape)
+    g = GpuLayer(B, ctx, Case(L, "bf16", 8, I.kept_per_filter(0.4, L.C), tag=("rows", shape)))
+    try:
+        y, a = (Guarded(L.N * L.Ho * L.Wo * L.F, torch.bfloat16) for _ in range(2))
+        B.pc_conv_fwd(ctx, g.desc, g.pk, g.x, y.ptr)
+        assert B.pc_last_kernel(ctx).startswith("pc_thin_fwd_kernel")
+        B.pc_conv_fwd_relu(ctx, g.desc, g.pk, g.x, a.ptr)
+        assert B.pc_last_kernel(ctx).startswith("pc_thin_fwd_kernel")
+        torch.cuda.synchronize()
+        assert y.margins_intact() and a.margins_intact()
+        assert torch.equal(a.body.view(torch.int16), torch.where(y.body > 0, y.body, torch.zeros_like(y.body)).view(torch.int16))
+    finally:
+        g.close()
