@@ -1,14 +1,24 @@
-// Float32 layers on the matrix cores (Section 5.2, forward and backward phase): v_mfma_f32_32x32x2_f32, float32 products
-// and sums throughout.
+// Float32 layers on the matrix cores (Section 5.2, forward and backward phase). Tiles of 32 of the forward and backward-data passes:
+// v_mfma_f32_32x32x16_bf16 over operands split in three; tiles of 16 and the weight gradients: v_mfma_f32_16x16x4_f32 / 32x32x2_f32.
+//
+// Three parts. A float32 value is the sum of three bfloat16 values (8 significant bits each, round to nearest, the remainder
+// goes on; |a1| <= 2^-8 |a0|, |a2| <= 2^-16 |a0|), and of the nine products of two such sums the six of 2^-16 and above are formed: a
+// product of two bfloat16 values is exact in float32, what is left out is 2^-26 of a product. a0 b0 is summed in one accumulator, the
+// five small ones in another, and the two are added once at the end. Error against 64 bits, root mean square relative to the
+// result's (normal data; 89 % zero weights in brackets): 64 products 1.43e-7 with v_mfma_f32_32x32x2_f32, 0.50e-7 in parts (0.57,
+// 0.29); 1152 products 5.99e-7, 2.00e-7 (2.16, 0.81); 4608 products 11.9e-7, 4.2e-7 (4.2, 1.7): the float32 instruction rounds its sum
+// after every two products, this one after sixteen. (All six in one accumulator: 5.2e-7 for 1152, 3.9e-7 with zeros, so two.) Parts
+// below 2^-133 vanish: operands under 2^-109 lose bits that float32 would hold. Infinities and NaN come out NaN: see pc_f32_kept_taps.
+// Six products take 192 cycles where the float32 instruction takes 512 for the same tile and depth. 64 x 28 x 28, 128 -> 128:
+// forward 132.5 -> 65.6 us, backward-data 133.2 -> 67.3 us (1.3 PFLOP/s of bfloat16 products); bound now by the splitting of
+// the weights (44 vector instructions per 12 matrix instructions) and by the barriers of the staging with two workgroups per CU.
 //
 // The gather kernels of pc_conv_valu.hip multiply kept taps only, but every multiply-add takes an LDS word and every kept
-// kernel a chain of scalar loads: they reach 2 % of the vector rate. The matrix instruction needs 256 bytes of operand per
-// 64 cycles, so the zero-filled contraction runs at the matrix rate (the same as the vector rate, 157 TFLOP/s) with one
-// LDS read per four instructions, whatever the density. 28 x 28, 128 -> 128, batch 64, keep 0.25: see the kernels below.
+// kernel a chain of scalar loads: they reach 2 % of the vector rate. The zero-filled contraction runs at the matrix rate whatever the density.
 //
-// Operand layout: lane l holds row (A) / column (B) l % 32 and k = l / 32; accumulator register r of lane l is row
-// 8*(r/4) + 4*(l/32) + r%4, column l % 32. A fragment is 8 reduction entries: lane half h holds entries 4h .. 4h+3 in one
-// 16-byte load, and instruction j of the fragment multiplies entries j and 4 + j.
+// Operand layout: of 32x32x2_f32, lane l holds row (A) / column (B) l % 32 and k = l / 32; of 32x32x16_bf16, the same row and k = 8 (l / 32)
+// .. + 7; accumulator register r of lane l is row 8*(r/4) + 4*(l/32) + r%4, column l % 32. The packed operand holds fragments of 8
+// reduction entries: 64 pieces of 16 bytes, piece l the entries 4 (l / 32) .. + 3 of row l % 32 (so a lane's eight entries are two pieces).
 //
 // The float32 matrix instructions occupy the vector units: a vector instruction of any wavefront of the SIMD adds its four
 // cycles to the kernel's time (measured: taking out the loads, the LDS writes and the LDS reads of the weight-gradient loop
@@ -24,11 +34,12 @@
 // A workgroup computes 32*WM output channels x 32*WN pixels, one 32 x 32 tile per wavefront (WK = 4: one tile, the four
 // wavefronts split the reduction and add up in wavefront order). The pixels of a tile are consecutive in raster order
 // over (image, row, column of a strip of Ws columns), so a tile is full whatever the map size; what it reads is a
-// range of rows of the "virtual" image in which the images follow each other with one zero row between them.
+// range of rows of the "virtual" image in which the images follow each other with one zero row between them. (NT = 2: a wavefront has
+// two tiles of pixels and splits its weights once for both.) Staged pixels of tiles of 32: per 16 channels the three parts, 32 bytes each.
 // Several workgroups share a CU: the staging of one runs under the matrix instructions of the others.
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 // 16-byte elements staged per thread and chunk, tiles of T = 32 or 16
-__host__ __device__ constexpr int f32_ne(int T) { return T == 32 ? 6 : 8; }
+__host__ __device__ constexpr int f32_ne(int T, int NT) { return T == 32 && NT == 1 ? 6 : 8; }
 
 struct F32Class {
     int32_t GH, GW, ooff_y, ooff_x;   // pixel grid of this launch part; output pixel = grid * oscale + ooff
@@ -43,7 +54,7 @@ struct F32Class {
 struct F32ConvArgs {
     int32_t N, in_H, in_W, in_CH, out_H, out_W, out_CH;
     int32_t oscale, lstep, HP, ioff;  // virtual row v is input row v % HP + ioff (HP = in_H + 1)
-    int32_t KC, lparts, nchunk, KS;   // channels per chunk (8, 16 or 32), log2(KC / 4), chunks, fragments of 8 per tap in the operand
+    int32_t KC, lparts, nchunk, KS;   // channels per chunk (16 to 128), log2(KC / 4), chunks, fragments of 8 per tap in the operand
     int32_t pitch;                    // bytes per staged pixel
     int32_t m_tiles, ncls;
     int32_t tail_first, tail_R;       // tiles and workgroups from tail_first on: a workgroup per part of 32 x 32; its staged rows
@@ -56,7 +67,9 @@ struct F32ConvArgs {
 
 // Output channel m of output pixel (oy, ox) of image n, over kept taps inside the map only. The matrix instructions multiply the
 // pruned taps of the zero-filled operand too, and 0 x Inf = 0 x NaN = NaN: an element that did not come out finite is computed
-// again here, so that what lies under a pruned tap never reaches it. (The check of finite tiles is 16 multiply-adds per lane:
+// again here, so that what lies under a pruned tap never reaches it.
+// (So does the split of an infinity, a NaN or a value that rounds up to a bfloat16 infinity: Inf - Inf and Inf x 0 in the small parts are
+// NaN.) (The check of finite tiles is 16 multiply-adds per lane:
 // 28 x 28, 128 -> 128, batch 64 takes 115.5 us without and 115.4 us with it.)
 __device__ __forceinline__ float pc_f32_kept_taps(const float *__restrict__ in, const float *__restrict__ wz, const F32ConvArgs &g, int n, int oy, int ox, int m)
 {
@@ -97,12 +110,40 @@ __device__ __forceinline__ float pc_f32_kept_taps(const float *__restrict__ in, 
     return acc;
 }
 
-template <int T, int NTAPS, int WM, int WN, int WK, bool VEC>
+// x = s[0] + s[1] + s[2], each bfloat16 (round to nearest: the parts below have either sign), of two values per word
+__device__ __forceinline__ void f32_split(float a, float b, uint32_t s[3])
+{
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        s[k] = pc_pack_bf16x2(a, b);
+        a -= __uint_as_float(s[k] << 16);
+        b -= __uint_as_float(s[k] & 0xFFFF0000u);
+    }
+}
+
+struct F32Parts { bf16x8 p[3]; };   // eight values in three parts
+__device__ __forceinline__ F32Parts f32_split8(const float4 &u, const float4 &v)
+{
+    uint32_t s[4][3];
+    f32_split(u.x, u.y, s[0]);
+    f32_split(u.z, u.w, s[1]);
+    f32_split(v.x, v.y, s[2]);
+    f32_split(v.z, v.w, s[3]);
+    F32Parts r;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const v4u32 w = {s[0][k], s[1][k], s[2][k], s[3][k]};
+        __builtin_memcpy(&r.p[k], &w, 16);
+    }
+    return r;
+}
+
+template <int T, int NTAPS, int WM, int WN, int WK, int NT, bool VEC>
 __device__ __forceinline__ void pc_f32_conv_body(const float *__restrict__ in, float *__restrict__ out, const float *__restrict__ wz,
                                                  const F32ConvArgs &g, const F32Class &c, int rows, int mt, int strip, int p0,
                                                  unsigned char *lds)
 {
-    constexpr int FR = T == 32 ? 8 : 16, F32_NE = f32_ne(T);   // FR: channels per fragment
+    constexpr int FR = 16, F32_NE = f32_ne(T, NT);             // FR: channels per fragment
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wk = wave % WK, wn = (wave / WK) % WN, wm = wave / WK / WN;
@@ -110,11 +151,19 @@ __device__ __forceinline__ void pc_f32_conv_body(const float *__restrict__ in, f
     const int np = g.N * c.GH * c.Ws;
     const int r0 = p0 / c.Ws, n0 = r0 / c.GH, v0 = n0 * g.HP + (r0 - n0 * c.GH) * g.lstep;
 
-    // this lane's pixel
-    const int p = p0 + wn * T + (lane & (T - 1));
-    const int pr = (p < np ? p : np - 1) / c.Ws, px = (p < np ? p : np - 1) - pr * c.Ws;
-    const int pn = pr / c.GH, py = pr - pn * c.GH;
-    const unsigned char *bp = lds + ((pn * g.HP + py * g.lstep - v0) * c.IW + px * g.lstep) * g.pitch + lane / T * 16;
+    // this lane's pixels: image, row and column of the strip (found again at the end: the registers are needed between)
+    struct Pixel { int n, y, x; };
+    const int pl = p0 + wn * NT * T + (lane & (T - 1));
+    auto pixel = [&](int p) -> Pixel {
+        const int r = p / c.Ws, n = r / c.GH;
+        return Pixel{n, r - n * c.GH, p - r * c.Ws};
+    };
+    const unsigned char *bp[NT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+        const Pixel q = pixel(pl + j * T < np ? pl + j * T : np - 1);
+        bp[j] = lds + ((q.n * g.HP + q.y * g.lstep - v0) * c.IW + q.x * g.lstep) * g.pitch + lane / T * 16;
+    }
 
     // elements this thread stages: 16 bytes (4 channels, the same ones of every pixel) of a pixel each; pix = the input
     // pixel counted from the first image of the tile
@@ -161,7 +210,7 @@ __device__ __forceinline__ void pc_f32_conv_body(const float *__restrict__ in, f
         }
     };
     auto put = [&](int ch) {
-        unsigned char *dst = lds + q0 * g.pitch + part * 16;
+        unsigned char *dst = lds + q0 * g.pitch + (T == 32 ? (part >> 2) * 96 + (part & 3) * 8 : part * 16);
         const int left = g.in_CH - ch * g.KC - part * 4;
 #pragma unroll
         for (int i = 0; i < F32_NE; ++i)
@@ -171,7 +220,15 @@ __device__ __forceinline__ void pc_f32_conv_body(const float *__restrict__ in, f
 #pragma unroll
                     for (int k = 0; k < 4; ++k) R[i][k] = ok && left > k ? R[i][k] : 0u;
                 }
-                *reinterpret_cast<v4u32 *>(dst + i * dq * g.pitch) = R[i];
+                if (T == 32) {
+                    uint32_t s[2][3];
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) f32_split(__uint_as_float(R[i][2 * e]), __uint_as_float(R[i][2 * e + 1]), s[e]);
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) *reinterpret_cast<v2u32 *>(dst + i * dq * g.pitch + k * 32) = v2u32{s[0][k], s[1][k]};
+                } else {
+                    *reinterpret_cast<v4u32 *>(dst + i * dq * g.pitch) = R[i];
+                }
             }
     };
 
@@ -183,87 +240,156 @@ __device__ __forceinline__ void pc_f32_conv_body(const float *__restrict__ in, f
     if (rt > rt_last) rt = rt_last;
     const __amdgpu_buffer_rsrc_t wsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<float *>(wz + (int64_t)(T == 32 ? rt : rt >> 1) * 9 * g.KS * 256), 0, 9 * g.KS * 1024, 0x00020000);
-    const int KSF = T == 32 ? g.KS : (g.KS + 1) >> 1;
-    const uint32_t wvo = T == 32 ? lane * 16u : (lane >> 5) * 1024u + ((rt & 1) * 16 + (lane & 15) + (lane & 16) * 2) * 16u;
-    const uint32_t wvo_last = T == 32 || !(g.KS & 1) || lane < 32 ? wvo : OOB;
-    auto a_load = [&](int tap, int kf) -> float4 {
+    const int KSF = (g.KS + 1) >> 1;
+    const uint32_t wvo = T == 32 ? (lane >> 5) * 1024u + (lane & 31) * 16u : (lane >> 5) * 1024u + ((rt & 1) * 16 + (lane & 15) + (lane & 16) * 2) * 16u;
+    const uint32_t wvo_last = !(g.KS & 1) || lane < 32 ? wvo : OOB;
+    auto a_load = [&](int tap, int kf, int half) -> float4 {
         const int tw = NTAPS == 9 ? tap : c.tap_w[tap & 3];
         const int k = kf < KSF - 1 ? kf : KSF - 1;
-        const uint32_t vo = T == 32 ? wvo : kf < KSF - 1 ? wvo : wvo_last;
-        const v4u32 u = __builtin_amdgcn_raw_buffer_load_b128(wsrc, (int)vo, (tw * g.KS + k * (FR / 8)) * 1024, 0);
+        const uint32_t vo = (kf < KSF - 1 ? wvo : wvo_last) + half * 512u;
+        const v4u32 u = __builtin_amdgcn_raw_buffer_load_b128(wsrc, (int)vo, (tw * g.KS + k * 2) * 1024, 0);
         float4 r;
         __builtin_memcpy(&r, &u, 16);
         return r;
     };
     auto tap_off = [&](int tap) -> int { return NTAPS == 9 ? c.o0 + tap / 3 * c.dr + tap % 3 * c.ds : c.tap_off[tap & 3]; };
-    typename std::conditional<T == 32, f32x16, f32x4>::type acc;
-#pragma unroll
-    for (int i = 0; i < T * T / 64; ++i) acc[i] = 0.0f;
-    auto mma = [&](float a, float bv) {
-        if constexpr (T == 32) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a, bv, acc, 0, 0, 0);
-        else acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a, bv, acc, 0, 0, 0);
-    };
     issue(0);
-    // One fragment of weights per tap is in flight (a wavefront's loads retire in order: the nine cover the round trip of
-    // the next chunk's pixels, which are requested in front of them); LDS reads run one tap ahead. The scheduling barriers
-    // keep the loads ahead of the matrix instructions they are to overlap.
-    float4 ar[NTAPS];
-#pragma unroll
-    for (int t = 0; t < NTAPS; ++t) ar[t] = a_load(t, wk);
     const int KF = g.KC / FR;
-    constexpr int RB = NTAPS % 3 == 0 ? 3 : NTAPS % 2 == 0 ? 2 : 1;   // the pixel fragments rotate without copies from one fragment to the next
-    float4 bq[RB];
-    const unsigned char *bt[NTAPS];
+    typename std::conditional<T == 32, f32x16, f32x4>::type acc[NT];
 #pragma unroll
-    for (int t = 0; t < NTAPS; ++t) bt[t] = bp + tap_off(t);
-    for (int ch = 0; ch < g.nchunk; ++ch) {
-        if (ch) __syncthreads();
-        put(ch);
-        __syncthreads();
-        if (ch + 1 < g.nchunk) issue(ch + 1);
-        const int left = (g.in_CH - ch * g.KC + FR - 1) / FR, nf = left < KF ? left : KF;
-        if (wk >= nf) continue;
-        bq[0] = *reinterpret_cast<const float4 *>(bt[0] + wk * FR * 4);
-        for (int f = wk; f < nf; f += WK) {
-            const int fn = f + WK < nf ? f + WK : f;
-            const int kn = f + WK < nf ? ch * KF + fn : (ch + 1) * KF + wk;   // the fragment after this one
+    for (int j = 0; j < NT; ++j)
 #pragma unroll
-            for (int t = 0; t < NTAPS; ++t) {
-                const float4 a = ar[t], bv = bq[t % RB];
-                if (RB > 1) bq[(t + 1) % RB] = *reinterpret_cast<const float4 *>(t + 1 < NTAPS ? bt[t + 1 < NTAPS ? t + 1 : 0] + f * FR * 4 : bt[0] + fn * FR * 4);
-                __builtin_amdgcn_sched_barrier(0);
-                mma(a.x, bv.x);
-                mma(a.y, bv.y);
-                mma(a.z, bv.z);
-                mma(a.w, bv.w);
-                __builtin_amdgcn_sched_barrier(0);
-                ar[t] = a_load(t, kn);        // behind its last use: the register is free
-                if (RB == 1) bq[0] = *reinterpret_cast<const float4 *>(bt[0] + fn * FR * 4);
+        for (int i = 0; i < T * T / 64; ++i) acc[j][i] = 0.0f;
+    if constexpr (T == 32) {
+        // WK = 4: wavefronts 0, 1 take the even fragments of 16 channels and 2, 3 the odd ones, each the first or the last taps
+        constexpr int HT = WK == 4 ? (NTAPS + 1) / 2 : NTAPS, FS = WK == 4 ? 2 : 1;
+        constexpr int RB = HT % 3 == 0 ? 3 : HT % 2 == 0 ? 2 : HT, PD = HT == 9 ? 3 : HT;   // rings of operands and of weights on their way
+        const int wf = WK == 4 ? wk >> 1 : 0, t0 = WK == 4 ? (wk & 1) * HT : 0, nt = WK == 4 ? (wk & 1 ? NTAPS - HT : HT) : HT;
+        f32x16 low[NT];
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) low[j][i] = 0.0f;
+        const auto tap = [&](int i) -> int { return WK == 4 ? (t0 + i < NTAPS ? t0 + i : NTAPS - 1) : i; };
+        int to[HT];
+#pragma unroll
+        for (int i = 0; i < HT; ++i) to[i] = tap_off(tap(i));
+        float4 ar[PD][2];
+#pragma unroll
+        for (int i = 0; i < PD; ++i) {
+            ar[i][0] = a_load(tap(i), wf, 0);
+            ar[i][1] = a_load(tap(i), wf, 1);
+        }
+        F32Parts ap[RB], bq[RB][NT];
+        auto b_load = [&](F32Parts *b, int i, int f) {
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+                for (int k = 0; k < 3; ++k) b[j].p[k] = *reinterpret_cast<const bf16x8 *>(bp[j] + f * 96 + to[i] + k * 32);
+        };
+        auto a_split = [&](int i) -> F32Parts { return f32_split8(ar[i][0], ar[i][1]); };
+        ap[0] = a_split(0);
+        for (int ch = 0; ch < g.nchunk; ++ch) {
+            if (ch) __syncthreads();
+            put(ch);
+            __syncthreads();
+            if (ch + 1 < g.nchunk) issue(ch + 1);
+            const int left = (g.in_CH - ch * g.KC + FR - 1) / FR, nf = left < KF ? left : KF;
+            if (wf >= nf) continue;
+            b_load(bq[0], 0, wf);
+            for (int f = wf; f < nf; f += FS) {
+                const int fn = f + FS < nf ? f + FS : f;
+                const int kc = ch * KF + f, kn = f + FS < nf ? ch * KF + fn : (ch + 1) * KF + wf;   // this fragment, the one after it
+#pragma unroll
+                for (int i = 0; i < HT; ++i) {
+                    if (RB > 1) b_load(bq[(i + 1) % RB], i + 1 < HT ? i + 1 : 0, i + 1 < HT ? f : fn);
+                    const int slot = i % PD;           // (its weights are split: the registers are free)
+                    ar[slot][0] = a_load(tap((i + PD) % HT), i + PD < HT ? kc : kn, 0);
+                    ar[slot][1] = a_load(tap((i + PD) % HT), i + PD < HT ? kc : kn, 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (WK == 1 || i < nt) {
+#pragma unroll
+                        for (int m = 0; m < 6; ++m)
+#pragma unroll
+                            for (int j = 0; j < NT; ++j) {
+                                constexpr int PA[6] = {0, 0, 1, 1, 0, 2}, PB[6] = {0, 1, 0, 1, 2, 0};
+                                f32x16 &s = m == 0 ? acc[j] : low[j];
+                                s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ap[i % RB].p[PA[m]], bq[i % RB][j].p[PB[m]], s, 0, 0, 0);
+                            }
+                    }
+                    ap[(i + 1) % RB] = a_split((i + 1) % PD);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (RB == 1) b_load(bq[0], 0, fn);
+                }
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[j][i] += low[j][i];
+    } else {
+        // One fragment of weights per tap is in flight (a wavefront's loads retire in order: the nine cover the round trip of
+        // the next chunk's pixels, which are requested in front of them); LDS reads run one tap ahead. The scheduling barriers
+        // keep the loads ahead of the matrix instructions they are to overlap.
+        auto mma = [&](float a, float bv) { acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, bv, acc[0], 0, 0, 0); };
+        float4 ar[NTAPS];
+#pragma unroll
+        for (int t = 0; t < NTAPS; ++t) ar[t] = a_load(t, wk, 0);
+        constexpr int RB = NTAPS % 3 == 0 ? 3 : NTAPS % 2 == 0 ? 2 : 1;   // the pixel fragments rotate without copies from one fragment to the next
+        float4 bq[RB];
+        const unsigned char *bt[NTAPS];
+#pragma unroll
+        for (int t = 0; t < NTAPS; ++t) bt[t] = bp[0] + tap_off(t);
+        for (int ch = 0; ch < g.nchunk; ++ch) {
+            if (ch) __syncthreads();
+            put(ch);
+            __syncthreads();
+            if (ch + 1 < g.nchunk) issue(ch + 1);
+            const int left = (g.in_CH - ch * g.KC + FR - 1) / FR, nf = left < KF ? left : KF;
+            if (wk >= nf) continue;
+            bq[0] = *reinterpret_cast<const float4 *>(bt[0] + wk * FR * 4);
+            for (int f = wk; f < nf; f += WK) {
+                const int fn = f + WK < nf ? f + WK : f;
+                const int kn = f + WK < nf ? ch * KF + fn : (ch + 1) * KF + wk;   // the fragment after this one
+#pragma unroll
+                for (int t = 0; t < NTAPS; ++t) {
+                    const float4 a = ar[t], bv = bq[t % RB];
+                    if (RB > 1) bq[(t + 1) % RB] = *reinterpret_cast<const float4 *>(t + 1 < NTAPS ? bt[t + 1 < NTAPS ? t + 1 : 0] + f * FR * 4 : bt[0] + fn * FR * 4);
+                    __builtin_amdgcn_sched_barrier(0);
+                    mma(a.x, bv.x);
+                    mma(a.y, bv.y);
+                    mma(a.z, bv.z);
+                    mma(a.w, bv.w);
+                    __builtin_amdgcn_sched_barrier(0);
+                    ar[t] = a_load(t, kn, 0);     // behind its last use: the register is free
+                    if (RB == 1) bq[0] = *reinterpret_cast<const float4 *>(bt[0] + fn * FR * 4);
+                }
             }
         }
     }
-    float4 o[4];
+    constexpr int NQ = T == 16 || WK > 1 ? 1 : 4;
+    float4 o[NT][NQ];
     if constexpr (T == 16) {
         if (WK > 1) {
             // the first wavefront of each pixel tile adds the partial tiles in wavefront order
             float4 *red = reinterpret_cast<float4 *>(lds);
             __syncthreads();
-            if (wk) red[(wk * WM * WN + wave / WK) * 64 + lane] = make_float4(acc[0], acc[1], acc[2], acc[3]);
+            if (wk) red[(wk * WM * WN + wave / WK) * 64 + lane] = make_float4(acc[0][0], acc[0][1], acc[0][2], acc[0][3]);
             __syncthreads();
             if (wk) return;
 #pragma unroll
             for (int k = 1; k < WK; ++k) {
                 const float4 u = red[(k * WM * WN + wave / WK) * 64 + lane];
-                acc[0] += u.x; acc[1] += u.y; acc[2] += u.z; acc[3] += u.w;
+                acc[0][0] += u.x; acc[0][1] += u.y; acc[0][2] += u.z; acc[0][3] += u.w;
             }
         }
-        o[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
+        o[0][0] = make_float4(acc[0][0], acc[0][1], acc[0][2], acc[0][3]);
     } else if constexpr (WK > 1) {
         // partial tiles added in wavefront order, wavefront w finishes rows 8w .. 8w+7
         float4 *red = reinterpret_cast<float4 *>(lds);
         __syncthreads();
 #pragma unroll
-        for (int q = 0; q < 4; ++q) red[(wave * 4 + q) * 64 + lane] = make_float4(acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]);
+        for (int q = 0; q < 4; ++q) red[(wave * 4 + q) * 64 + lane] = make_float4(acc[0][4 * q], acc[0][4 * q + 1], acc[0][4 * q + 2], acc[0][4 * q + 3]);
         __syncthreads();
         float4 s = red[wk * 64 + lane];
 #pragma unroll
@@ -271,60 +397,68 @@ __device__ __forceinline__ void pc_f32_conv_body(const float *__restrict__ in, f
             const float4 u = red[(k * 4 + wk) * 64 + lane];
             s.x += u.x; s.y += u.y; s.z += u.z; s.w += u.w;
         }
-        o[0] = s;
+        o[0][0] = s;
     } else {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) o[q] = make_float4(acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]);
-    }
-    if (p >= np || x0 + px >= c.GW) return;
-    constexpr int NQ = T == 16 || WK > 1 ? 1 : 4;
-    const int oy = py * g.oscale + c.ooff_y, ox = (x0 + px) * g.oscale + c.ooff_x;
-    const int m0 = (mt * WM + wm) * T + (T == 32 && WK > 1 ? wk : 0) * 8 + lane / T * 4;
-    const int64_t opix = ((int64_t)pn * g.out_H + oy) * g.out_W + ox;
-    float z = 0.0f;                   // NaN when one of the elements is not finite
-    uint32_t redo = 0u;
+        for (int j = 0; j < NT; ++j)
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) z = fmaf(o[q].x, 0.0f, fmaf(o[q].y, 0.0f, fmaf(o[q].z, 0.0f, fmaf(o[q].w, 0.0f, z))));
-    if (__builtin_expect(z != z, 0)) {
+            for (int q = 0; q < 4; ++q) o[j][q] = make_float4(acc[j][4 * q], acc[j][4 * q + 1], acc[j][4 * q + 2], acc[j][4 * q + 3]);
+    }
+    const int m0 = (mt * WM + wm) * T + (T == 32 && WK > 1 ? wk : 0) * 8 + lane / T * 4;
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+        int p = pl + j * T;
+        asm volatile("" : "+v"(p));   // (the compiler would keep the pixels of the start)
+        if (p >= np) break;
+        const Pixel px = pixel(p);
+        if (x0 + px.x >= c.GW) continue;
+        const int oy = px.y * g.oscale + c.ooff_y, ox = (x0 + px.x) * g.oscale + c.ooff_x;
+        const int64_t opix = ((int64_t)px.n * g.out_H + oy) * g.out_W + ox;
+        float z = 0.0f;               // NaN when one of the elements is not finite
+        uint32_t redo = 0u;
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) z = fmaf(o[j][q].x, 0.0f, fmaf(o[j][q].y, 0.0f, fmaf(o[j][q].z, 0.0f, fmaf(o[j][q].w, 0.0f, z))));
+        if (__builtin_expect(z != z, 0)) {
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                const float v[4] = {o[j][q].x, o[j][q].y, o[j][q].z, o[j][q].w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) redo |= fabsf(v[e]) < INFINITY ? 0u : 1u << (4 * q + e);
+            }
+        }
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
-            const float v[4] = {o[q].x, o[q].y, o[q].z, o[q].w};
+            const int m = m0 + 8 * q;
+            if (m >= g.out_CH) continue;
+            const int64_t at = opix * g.out_CH + m;
+            float v[4] = {o[j][q].x, o[j][q].y, o[j][q].z, o[j][q].w};
+            const int ne = (g.out_CH & 3) == 0 ? 4 : (g.out_CH - m < 4 ? g.out_CH - m : 4);
+            if (g.act == PC_ACT_RELU) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) redo |= fabsf(v[e]) < INFINITY ? 0u : 1u << (4 * q + e);
+                for (int e = 0; e < 4; ++e) v[e] = v[e] > 0.0f ? v[e] : 0.0f;
+            } else if (g.act == PC_ACT_RELU_MASK) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = (e < ne && g.act_mask[at + e] > 0.0f) ? v[e] : 0.0f;
+            }
+            if ((g.out_CH & 3) == 0) *reinterpret_cast<float4 *>(out + at) = make_float4(v[0], v[1], v[2], v[3]);
+            else
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (e < ne) out[at + e] = v[e];
         }
-    }
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-        const int m = m0 + 8 * q;
-        if (m >= g.out_CH) continue;
-        const int64_t at = opix * g.out_CH + m;
-        float v[4] = {o[q].x, o[q].y, o[q].z, o[q].w};
-        const int ne = (g.out_CH & 3) == 0 ? 4 : (g.out_CH - m < 4 ? g.out_CH - m : 4);
-        if (g.act == PC_ACT_RELU) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = v[e] > 0.0f ? v[e] : 0.0f;
-        } else if (g.act == PC_ACT_RELU_MASK) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = (e < ne && g.act_mask[at + e] > 0.0f) ? v[e] : 0.0f;
+        for (; redo; redo &= redo - 1u) {
+            const int i = __ffs((int)redo) - 1, m = m0 + (i >> 2) * 8 + (i & 3);
+            if (m >= g.out_CH) continue;
+            float v = pc_f32_kept_taps(in, wz, g, px.n, oy, ox, m);
+            if (g.act == PC_ACT_RELU || g.act == PC_ACT_RELU_MASK) v = (g.act == PC_ACT_RELU ? v : g.act_mask[opix * g.out_CH + m]) > 0.0f ? v : 0.0f;
+            out[opix * g.out_CH + m] = v;
         }
-        if ((g.out_CH & 3) == 0) *reinterpret_cast<float4 *>(out + at) = make_float4(v[0], v[1], v[2], v[3]);
-        else
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (e < ne) out[at + e] = v[e];
-    }
-    for (; redo; redo &= redo - 1u) {
-        const int i = __ffs((int)redo) - 1, m = m0 + (i >> 2) * 8 + (i & 3);
-        if (m >= g.out_CH) continue;
-        float v = pc_f32_kept_taps(in, wz, g, pn, oy, ox, m);
-        if (g.act == PC_ACT_RELU || g.act == PC_ACT_RELU_MASK) v = (g.act == PC_ACT_RELU ? v : g.act_mask[opix * g.out_CH + m]) > 0.0f ? v : 0.0f;
-        out[opix * g.out_CH + m] = v;
     }
 }
 
 // MC: the four parity classes of a stride-2 backward-data pass (4, 2, 2 and 1 taps), each a range of workgroups.
-template <int T, int WM, int WN, int WK, bool MC, bool VEC>
-__global__ void __launch_bounds__(256, 4)
+template <int T, int WM, int WN, int WK, int NT, bool MC, bool VEC>
+__global__ void __launch_bounds__(256, T == 16 ? 4 : NT == 1 ? 3 : 2)
 pc_f32_conv_kernel(const float *__restrict__ in, float *__restrict__ out, const float *__restrict__ wz, F32ConvArgs g)
 {
     extern __shared__ __align__(16) unsigned char lds[];
@@ -334,30 +468,30 @@ pc_f32_conv_kernel(const float *__restrict__ in, float *__restrict__ out, const 
         while (k + 1 < g.ncls && b >= g.cls[k + 1].first) ++k;
         const F32Class &c = g.cls[k];
         b -= c.first;
-        const int mt = b % g.m_tiles, pt = b / g.m_tiles, strip = pt / c.tiles, p0 = (pt - strip * c.tiles) * T * WN;
-        if (c.ntaps == 4) pc_f32_conv_body<T, 4, WM, WN, WK, VEC>(in, out, wz, g, c, c.R, mt, strip, p0, lds);
-        else if (c.ntaps == 2) pc_f32_conv_body<T, 2, WM, WN, WK, VEC>(in, out, wz, g, c, c.R, mt, strip, p0, lds);
-        else pc_f32_conv_body<T, 1, WM, WN, WK, VEC>(in, out, wz, g, c, c.R, mt, strip, p0, lds);
+        const int mt = b % g.m_tiles, pt = b / g.m_tiles, strip = pt / c.tiles, p0 = (pt - strip * c.tiles) * T * WN * NT;
+        if (c.ntaps == 4) pc_f32_conv_body<T, 4, WM, WN, WK, NT, VEC>(in, out, wz, g, c, c.R, mt, strip, p0, lds);
+        else if (c.ntaps == 2) pc_f32_conv_body<T, 2, WM, WN, WK, NT, VEC>(in, out, wz, g, c, c.R, mt, strip, p0, lds);
+        else pc_f32_conv_body<T, 1, WM, WN, WK, NT, VEC>(in, out, wz, g, c, c.R, mt, strip, p0, lds);
     } else {
         const F32Class &c = g.cls[0];
         const bool tail = T == 32 && WK == 1 && b >= g.tail_first;
         int sub = 0;
         if (tail) {
             b -= g.tail_first;
-            sub = b % (WM * WN);
-            b = g.tail_first + b / (WM * WN);
+            sub = b % (WM * WN * NT);
+            b = g.tail_first + b / (WM * WN * NT);
         } else if ((g.tail_first & 7) == 0) {
             b = (b & 7) * (g.tail_first >> 3) + (b >> 3);   // workgroups that share pixels share an XCD
         }
-        const int mt = b % g.m_tiles, pt = b / g.m_tiles, strip = pt / c.tiles, p0 = (pt - strip * c.tiles) * T * WN;
+        const int mt = b % g.m_tiles, pt = b / g.m_tiles, strip = pt / c.tiles, p0 = (pt - strip * c.tiles) * T * WN * NT;
         if constexpr (T == 32 && WK == 1) {
             if (tail) {
                 if (p0 + sub / WM * 32 >= g.N * c.GH * c.Ws || (mt * WM + sub % WM) * 32 >= g.out_CH) return;
-                pc_f32_conv_body<32, 9, 1, 1, 4, VEC>(in, out, wz, g, c, g.tail_R, mt * WM + sub % WM, strip, p0 + sub / WM * 32, lds);
+                pc_f32_conv_body<32, 9, 1, 1, 4, 1, VEC>(in, out, wz, g, c, g.tail_R, mt * WM + sub % WM, strip, p0 + sub / WM * 32, lds);
                 return;
             }
         }
-        pc_f32_conv_body<T, 9, WM, WN, WK, VEC>(in, out, wz, g, c, c.R, mt, strip, p0, lds);
+        pc_f32_conv_body<T, 9, WM, WN, WK, NT, VEC>(in, out, wz, g, c, c.R, mt, strip, p0, lds);
     }
 }
 
@@ -398,61 +532,69 @@ static bool f32_plan_class(const F32ConvArgs &g, F32Class *c, int ext, int BN, i
 // with few pixels fill the chip (2 x 11 x 13, 360 -> 24 forward: 9 tiles of 32 took 21.9 us, 42 of 16 take 9.3), and
 // layers of up to 16 output channels do half the matrix work (45 x 44, 384 -> 16: 21.7 -> 9.2 us). The larger tiles read
 // fewer weights and pixels per multiply-add and win where there are enough of them.
-struct F32Shape { int t, wm, wn, wk; double mma; };
-static const F32Shape kF32Shapes[] = {{32, 2, 2, 1, 0.959}, {32, 1, 4, 1, 0.941}, {32, 4, 1, 1, 0.937}, {32, 1, 1, 4, 0.830},
-                                      {16, 1, 4, 1, 0.895}, {16, 1, 2, 2, 0.847}, {16, 1, 1, 4, 0.773}};
+// Tiles of 32: nt = 2 pixel tiles per wavefront halve the splitting of the weights and their loads and win where two workgroups per CU
+// are enough of them (64 x 28 x 28, 128 -> 128 forward 75.4 -> 65.7 us), nt = 1 has three per CU.
+struct F32Shape { int t, wm, wn, wk, nt; double mma; };
+static const F32Shape kF32Shapes[] = {{32, 2, 2, 1, 2, 0.803}, {32, 4, 1, 1, 2, 0.781}, {32, 1, 4, 1, 2, 0.836},
+                                      {32, 2, 2, 1, 1, 0.901}, {32, 4, 1, 1, 1, 0.856}, {32, 1, 4, 1, 1, 0.937}, {32, 1, 1, 4, 1, 1.066},
+                                      {16, 1, 4, 1, 1, 0.733}, {16, 1, 2, 2, 1, 0.658}, {16, 1, 1, 4, 1, 0.567}};
+// The rest of the estimate, by kind: tiles of 16; of 32 with one and with two pixel tiles per wavefront; of 32 along the reduction
+struct F32Kind { int occ; double alone, part_round, stage, start, trip; };
+static const F32Kind kF32Kinds[] = {{4, 0.495, 0.962, 141.0, 1243.0, 740.0}, {3, 0.469, 0.613, 218.0, 1777.0, 1247.0},
+                                    {2, 0.928, 0.816, 218.0, 1777.0, 1247.0}, {3, 0.469, 0.476, 218.0, 1777.0, 1247.0}};
+static const F32Kind &f32_kind(const F32Shape &s) { return kF32Kinds[s.t == 16 ? 0 : s.wk > 1 ? 3 : s.nt]; }
 
-// Time estimate in us, least squares over 4800 measured launches (240 layers of 1 .. 100 images, 4 .. 224 pixels wide, 3 .. 500 channels,
-// both passes and strides; the choice is 0.8 % behind the best shape on average, the worst one 19 %; on 80 layers drawn
-// afterwards, with every shape's time in profiles/plan_timings_f32.csv for a new fit, 0.3 % forward and 2.4 % backward-data (4 % at
-// stride 2, the worst 31 %)):
-// a workgroup costs its matrix cycles, its start and end, staging per 256 elements of 16 bytes, and per chunk a round trip
-// that the other workgroups of the CU hide; then the output and the weights from the L2s. Chunks of less than a cache line fetch
-// lines again where the pixels under way exceed the L2s.
+// Time estimate in us, least squares over 14000 measured launches (400 layers of 1 .. 128 images, 4 .. 224 pixels wide, 1 .. 512 channels,
+// both passes and strides; the choice is 1.3 % behind the best shape on average, 2.7 % in backward-data passes of stride 2, the worst
+// one 31 %; a part of the layers with every shape's time in profiles/plan_timings_f32.csv for a new fit): a workgroup costs its
+// matrix cycles (more per cycle the fewer workgroups share the CU), its start and end, staging per 256 elements of 16 bytes, and per
+// chunk a round trip that the other workgroups of the CU hide; then the output and the weights from the L2s.
+static int f32_occ(const F32Shape &s, size_t lds)
+{
+    const int occ = (int)(160 * 1024 / lds), most = f32_kind(s).occ;
+    return occ < most ? occ : most;
+}
+
 // Cycles of one workgroup; rounds = workgroups per CU.
 static double f32_cycles(const F32Shape &s, const F32ConvArgs &t, double taps, double staged, double rounds, size_t lds)
 {
-    const int fr = s.t == 32 ? 8 : 16, left = t.in_CH - (t.nchunk - 1) * t.KC;
-    const int frags = (t.nchunk - 1) * (t.KC / fr / s.wk) + ((left + fr - 1) / fr + s.wk - 1) / s.wk;
-    int occ = (int)(160 * 1024 / lds);
-    if (occ > 4) occ = 4;
-    const double up = ceil(rounds), conc = up < occ ? up : occ;
-    return taps * frags * (s.t == 32 ? 256.0 : 128.0) * s.mma + staged / 256.0 * t.nchunk * 119.0 + 1039.0 + 1037.0 * t.nchunk / conc;
+    const F32Kind &q = f32_kind(s);
+    const int left = t.in_CH - (t.nchunk - 1) * t.KC, wf = s.t == 32 && s.wk == 4 ? 2 : s.wk;
+    const int frags = (t.nchunk - 1) * (t.KC / 16 / wf) + ((left + 15) / 16 + wf - 1) / wf;
+    if (s.t == 32 && s.wk == 4) taps = (taps + 1.0) / 2.0;
+    const double up = ceil(rounds), occ = f32_occ(s, lds), conc = up < occ ? up : occ;
+    return taps * frags * (s.t == 32 ? 192.0 * s.nt : 128.0) * s.mma * (1.0 + q.alone / conc) + staged / 256.0 * t.nchunk * q.stage + q.start +
+           q.trip * t.nchunk / conc;
 }
 
-static double f32_rounds(double n) { return n <= 4.0 ? ceil(n) : n + 0.68; }
+static double f32_rounds(const F32Shape &s, double n) { return n <= f32_kind(s).occ ? ceil(n) : n + f32_kind(s).part_round; }
 
 static double f32_time(const pc_ctx *ctx, const F32Shape &s, const F32ConvArgs &t, int64_t blocks, double taps, double staged, size_t lds, int64_t out_bytes)
 {
     const double n = (double)blocks / ctx->num_cu;
     const double wbytes = (double)blocks * s.t * s.wm * taps * ((t.in_CH + 7) / 8 * 32);
-    double us = 4.0 + f32_rounds(n) * f32_cycles(s, t, taps, staged, n, lds) / 2350.0 + (double)out_bytes / 5.5e6 + wbytes / 140e6;
-    int occ = (int)(160 * 1024 / lds);
-    if (occ > 4) occ = 4;
-    const double res = n < occ ? (double)blocks : (double)occ * ctx->num_cu;
-    if (t.KC < 32 && staged * 16.0 * t.nchunk * res / 8 > 4e6) us += (double)blocks * staged * 16.0 * t.nchunk * (32 / t.KC - 1) / 80e6;
-    return us;
+    return 3.6 + f32_rounds(s, n) * f32_cycles(s, t, taps, staged, n, lds) / 2350.0 + (double)out_bytes / 5.5e6 + wbytes / 90e6;
 }
 
 // The last, partly filled round of a launch: its tiles are cut into parts of 32 x 32, one workgroup each, four wavefronts along the
 // reduction. What bounds such a launch is the time of whole tiles on the CUs that have one more than the others; a part takes
 // a quarter of a tile's time or less, so the CUs end that much closer together. Taken where the estimate is at least 2 % shorter
-// (parts stage and read more per multiply-add, and LDS for their sums may cost a workgroup per CU). 34 layers, in us: 64 x 28 x 28,
+// (parts stage and read more per multiply-add, and LDS for their sums may cost a workgroup per CU). 34 layers, with float32 instructions, in us: 64 x 28 x 28,
 // 128 -> 128 forward 128.9 -> 119.7 (6.1 tiles per CU), backward-data 125.1 -> 111.8; 117 x 119, 72 -> 136 68.8 -> 53.1;
 // geometric mean 1.08 and 1.06, the least 0.96. Tiles of 16 end in small steps by themselves, and launches of the parity classes of
 // stride 2 mix short and long workgroups, so neither is cut.
 static void f32_plan_tail(const pc_ctx *ctx, const F32Shape &s, F32ConvArgs *t, int ext, int64_t *blocks, double staged, size_t *lds, double *us)
 {
-    static const F32Shape part = {32, 1, 1, 4, 0.830};
+    static const F32Shape part = {32, 1, 1, 4, 1, 1.066};
     const F32Class &c = t->cls[0];
-    const int sub = s.wm * s.wn;
+    const int sub = s.wm * s.wn * s.nt;
     const int64_t whole = *blocks / ctx->num_cu * ctx->num_cu, rest = *blocks - whole;
     const int R = f32_rows(*t, c.GH, c.Ws, ext, 32);
-    if (whole == 0 || rest == 0 || R * c.IW * 8 > 256 * f32_ne(32) || R > c.R || whole + rest * sub >= ((int64_t)1 << 31)) return;
+    if (whole == 0 || rest == 0 || R * c.IW * 8 > 256 * f32_ne(32, 1) || R > c.R || whole + rest * sub >= ((int64_t)1 << 31)) return;
     const size_t need = *lds < 16384 ? 16384 : *lds;   // (the parts add their four sums there)
     const double n = (double)*blocks / ctx->num_cu, k = (double)(whole / ctx->num_cu), m = (double)(rest * sub) / ctx->num_cu;
-    const double now = f32_rounds(n) * f32_cycles(s, *t, 9.0, staged, n, *lds);
-    const double cut = k * f32_cycles(s, *t, 9.0, staged, n, need) + f32_rounds(m) * f32_cycles(part, *t, 9.0, (double)R * c.IW * 8, n, need);
+    const double now = f32_rounds(s, n) * f32_cycles(s, *t, 9.0, staged, n, *lds);
+    const double cut = k * f32_cycles(s, *t, 9.0, staged, n, need) + f32_rounds(part, m) * f32_cycles(part, *t, 9.0, (double)R * c.IW * 8, n, need);
     if (cut >= 0.98 * now) return;
     *us -= (now - cut) / 2350.0;
     t->tail_first = (int32_t)whole;
@@ -478,14 +620,14 @@ static pc_status f32_run(pc_ctx *ctx, F32ConvArgs g, bool mc, int ext, const int
     for (int k = 0; k < (int)(sizeof(kF32Shapes) / sizeof(kF32Shapes[0])); ++k) {
         const F32Shape &s = kF32Shapes[k];
         // chunks of 32 (128) channels, shorter ones where the staged tile would not fit, down to one fragment per wavefront
-        const int kc_min = (s.t == 16 ? 16 : 8) * s.wk;
+        const int kc_min = 16 * (s.t == 32 && s.wk == 4 ? 2 : s.wk);
         for (int kc = s.t == 16 ? 128 : 32; kc >= kc_min; kc >>= 1) {
             if (known ? *choice != k * 256 + kc : kc >= 2 * c8 && kc > kc_min) continue;
             F32ConvArgs t = g;
             t.KC = kc;
             t.lparts = 0;
             while ((4 << t.lparts) < kc) ++t.lparts;
-            t.pitch = t.KC * 4 + 16;
+            t.pitch = t.KC * (s.t == 32 ? 6 : 4) + 16;
             t.nchunk = (g.in_CH + t.KC - 1) / t.KC;
             t.m_tiles = (g.out_CH + s.t * s.wm - 1) / (s.t * s.wm);
             int64_t blocks = 0;
@@ -494,7 +636,7 @@ static pc_status f32_run(pc_ctx *ctx, F32ConvArgs g, bool mc, int ext, const int
             size_t need = s.wk > 1 ? 16384 : 0;
             for (int i = 0; i < g.ncls && ok; ++i) {
                 F32Class &c = t.cls[i];
-                ok = f32_plan_class(t, &c, ext, s.t * s.wn, f32_ne(s.t));
+                ok = f32_plan_class(t, &c, ext, s.t * s.wn * s.nt, f32_ne(s.t, s.nt));
                 if (!ok) break;
                 const int64_t nb = (int64_t)c.tiles * ((c.GW + c.Ws - 1) / c.Ws) * t.m_tiles;
                 c.first = (int32_t)blocks;
@@ -525,30 +667,33 @@ static pc_status f32_run(pc_ctx *ctx, F32ConvArgs g, bool mc, int ext, const int
     int64_t span = 0;
     for (int i = 0; i < best.ncls; ++i) {
         const F32Class &c = best.cls[i];
-        const int64_t n = 2 + (kF32Shapes[best_k].t * kF32Shapes[best_k].wn + c.Ws - 1) / c.Ws / c.GH;
+        const int64_t n = 2 + (kF32Shapes[best_k].t * kF32Shapes[best_k].wn * kF32Shapes[best_k].nt + c.Ws - 1) / c.Ws / c.GH;
         if (n > span) span = n;
     }
     const bool vec = (g.in_CH & 3) == 0 && span * g.in_H * g.in_W * g.in_CH * 4 < ((int64_t)1 << 31);
     hipStream_t st = ctx->stream;
-#define F32_LAUNCH(T, WM, WN, WK)                                                                                            \
+#define F32_LAUNCH(T, WM, WN, WK, NT)                                                                                        \
     do {                                                                                                                    \
-        if (mc && vec) hipLaunchKernelGGL((pc_f32_conv_kernel<T, WM, WN, WK, true, true>), grid, blk, lds, st, in, out, wz, best);   \
-        else if (mc) hipLaunchKernelGGL((pc_f32_conv_kernel<T, WM, WN, WK, true, false>), grid, blk, lds, st, in, out, wz, best);    \
-        else if (vec) hipLaunchKernelGGL((pc_f32_conv_kernel<T, WM, WN, WK, false, true>), grid, blk, lds, st, in, out, wz, best);   \
-        else hipLaunchKernelGGL((pc_f32_conv_kernel<T, WM, WN, WK, false, false>), grid, blk, lds, st, in, out, wz, best);           \
+        if (mc && vec) hipLaunchKernelGGL((pc_f32_conv_kernel<T, WM, WN, WK, NT, true, true>), grid, blk, lds, st, in, out, wz, best);   \
+        else if (mc) hipLaunchKernelGGL((pc_f32_conv_kernel<T, WM, WN, WK, NT, true, false>), grid, blk, lds, st, in, out, wz, best);    \
+        else if (vec) hipLaunchKernelGGL((pc_f32_conv_kernel<T, WM, WN, WK, NT, false, true>), grid, blk, lds, st, in, out, wz, best);   \
+        else hipLaunchKernelGGL((pc_f32_conv_kernel<T, WM, WN, WK, NT, false, false>), grid, blk, lds, st, in, out, wz, best);           \
     } while (0)
     switch (best_k) {
-    case 0: F32_LAUNCH(32, 2, 2, 1); break;
-    case 1: F32_LAUNCH(32, 1, 4, 1); break;
-    case 2: F32_LAUNCH(32, 4, 1, 1); break;
-    case 3: F32_LAUNCH(32, 1, 1, 4); break;
-    case 4: F32_LAUNCH(16, 1, 4, 1); break;
-    case 5: F32_LAUNCH(16, 1, 2, 2); break;
-    default: F32_LAUNCH(16, 1, 1, 4); break;
+    case 0: F32_LAUNCH(32, 2, 2, 1, 2); break;
+    case 1: F32_LAUNCH(32, 4, 1, 1, 2); break;
+    case 2: F32_LAUNCH(32, 1, 4, 1, 2); break;
+    case 3: F32_LAUNCH(32, 2, 2, 1, 1); break;
+    case 4: F32_LAUNCH(32, 4, 1, 1, 1); break;
+    case 5: F32_LAUNCH(32, 1, 4, 1, 1); break;
+    case 6: F32_LAUNCH(32, 1, 1, 4, 1); break;
+    case 7: F32_LAUNCH(16, 1, 4, 1, 1); break;
+    case 8: F32_LAUNCH(16, 1, 2, 2, 1); break;
+    default: F32_LAUNCH(16, 1, 1, 4, 1); break;
     }
 #undef F32_LAUNCH
-    pc_note_kernel(ctx, "pc_f32_conv_kernel<%d, %d, %d, %d, %s, %s>", kF32Shapes[best_k].t, kF32Shapes[best_k].wm, kF32Shapes[best_k].wn, kF32Shapes[best_k].wk,
-                   mc ? "true" : "false", vec ? "true" : "false");
+    const F32Shape &bs = kF32Shapes[best_k];
+    pc_note_kernel(ctx, "pc_f32_conv_kernel<%d, %d, %d, %d, %d, %s, %s>", bs.t, bs.wm, bs.wn, bs.wk, bs.nt, mc ? "true" : "false", vec ? "true" : "false");
     return pc_hip_check(ctx, hipGetLastError(), "float32 conv launch");
 }
 

@@ -47,3 +47,33 @@ def test_wavefronts_that_share_pixels(B, ctx, oracle, waves, shape):
     """Weight gradients whose wavefronts add their sums in LDS: two and four of them, rows of quads and not, the (tap, channel) columns of a first layer."""
     run_case(B, ctx, oracle, shape, "f32", 8, 0.4, B.PC_VARIANT_AUTO, "f32_shared")
     assert B.pc_last_kernel(ctx).startswith("pc_f32_wgrad_kernel<%s, " % waves)
+
+
+@pytest.mark.parametrize("kernel,shape", [
+    ("2, 2, 1, 2", (6, 55, 55, 8, 40, 1)), ("2, 2, 1, 2", (2, 94, 97, 3, 48, 1)), ("4, 1, 1, 2", (11, 33, 32, 16, 96, 1)), ("4, 1, 1, 2", (2, 111, 113, 3, 136, 2)),
+    ("1, 4, 1, 2", (43, 30, 32, 8, 24, 1)), ("1, 4, 1, 2", (12, 60, 58, 3, 24, 1)), ("2, 2, 1, 1", (10, 34, 32, 8, 24, 1)), ("4, 1, 1, 1", (15, 6, 7, 32, 464, 1)),
+    ("4, 1, 1, 1", (88, 8, 10, 3, 48, 1)), ("1, 4, 1, 1", (1, 138, 139, 32, 24, 1)), ("1, 4, 1, 1", (117, 27, 25, 3, 24, 1))])
+def test_three_parts(B, ctx, oracle, kernel, shape):
+    """Tiles of 32, operands split in three: every shape of workgroup, half a fragment of 16 channels, rows that are no whole quads. Next to the
+    element-wise bound of float32: the error over the whole tensor is that of sums rounded after sixteen products, not after two."""
+    import numpy as np
+    from paper_2011_10170_amd import inputs as I
+    from tests._harness import Case, GpuLayer, oracle_masks
+    run_case(B, ctx, oracle, shape, "f32", 8, 0.4, B.PC_VARIANT_AUTO, "f32_parts")
+    L = I.Layer(*shape)
+    case = Case(L, "f32", 8, I.kept_per_filter(0.4, L.C), tag=("parts", shape))
+    Wm = oracle_masks(oracle, case)[3]
+    g = GpuLayer(B, ctx, case)
+    try:
+        y = g.fwd()
+        assert B.pc_last_kernel(ctx).startswith("pc_f32_conv_kernel<32, %s, " % kernel)
+    finally:
+        g.close()
+    ref = oracle.conv_fwd(case.x, Wm, L.stride)
+    # n additions that each round the running sum by at most 2^-24 of it (0.58 of that in the mean square) and of which the sum
+    # has half its final square on average, and the final rounding; n = the groups of 16 channels of every tap, twice for the hardware's own halves
+    n = 9 * -(-L.C // 16) * 2
+    bound = 2.0 ** -24 * (1.0 + 0.58 * np.sqrt(n / 2.0))
+    rel = float(np.linalg.norm(y.astype(np.float64) - ref) / np.linalg.norm(ref))
+    print("error over the tensor: %.2e, bound %.2e" % (rel, bound))
+    assert rel <= bound, (rel, bound)
