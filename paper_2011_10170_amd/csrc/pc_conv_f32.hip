@@ -1,5 +1,6 @@
-// Float32 layers on the matrix cores (Section 5.2, forward and backward phase). Tiles of 32 of the forward and backward-data passes:
-// v_mfma_f32_32x32x16_bf16 over operands split in three; tiles of 16 and the weight gradients: v_mfma_f32_16x16x4_f32 / 32x32x2_f32.
+// Float32 layers on the matrix cores (Section 5.2, forward and backward phase). Tiles of 32 of the forward and backward-data passes
+// and the weight gradients: bfloat16 instructions over operands split in three; tiles of 16 and the first layer's weight gradients:
+// v_mfma_f32_16x16x4_f32 / 32x32x2_f32.
 //
 // Three parts. A float32 value is the sum of three bfloat16 values (8 significant bits each, round to nearest, the remainder
 // goes on; |a1| <= 2^-8 |a0|, |a2| <= 2^-16 |a0|), and of the nine products of two such sums the six of 2^-16 and above are formed: a
@@ -38,6 +39,7 @@
 // two tiles of pixels and splits its weights once for both.) Staged pixels of tiles of 32: per 16 channels the three parts, 32 bytes each.
 // Several workgroups share a CU: the staging of one runs under the matrix instructions of the others.
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef short i16x4 __attribute__((ext_vector_type(4)));
 // 16-byte elements staged per thread and chunk, tiles of T = 32 or 16
 __host__ __device__ constexpr int f32_ne(int T, int NT) { return T == 32 && NT == 1 ? 6 : 8; }
 
@@ -291,9 +293,11 @@ __device__ __forceinline__ void pc_f32_conv_body(const float *__restrict__ in, f
         ap[0] = a_split(0);
         for (int ch = 0; ch < g.nchunk; ++ch) {
             if (ch) __syncthreads();
+            __builtin_amdgcn_s_setprio(0);        // a wavefront that multiplies goes first (4 x 71 x 74, 96 -> 96: 25.2 -> 24.6 us)
             put(ch);
             __syncthreads();
             if (ch + 1 < g.nchunk) issue(ch + 1);
+            __builtin_amdgcn_s_setprio(1);
             const int left = (g.in_CH - ch * g.KC + FR - 1) / FR, nf = left < KF ? left : KF;
             if (wf >= nf) continue;
             b_load(bq[0], 0, wf);
@@ -754,16 +758,21 @@ pc_status pc_f32_bwd_data(pc_ctx *ctx, const pc_conv_desc *d, const pc_packed *p
 }
 
 // ------------------------------------------------------------------ backward-weight
-// dW[t][f][c] = sum over output pixels of dy[pixel][f] * x[pixel shifted by tap t][c]. The pixels are the reduction and a
-// lane holds one float of one pixel, so NHWC rows in LDS are the operands as they are: no transpose. A wavefront holds a
-// 32 x 32 (filter, channel) tile of all 9 taps (144 accumulators) and reads 10 words per 9 matrix instructions.
-// WF x WC wavefronts cover 32*WF filters x 32*WC channels; of fewer than four, the WK = 4 / (WF*WC) that are left over take every WK-th
-// pixel pair, and their sums are added in LDS (halves of the tile at a time, a wavefront keeps 16 / WK of its kernels). Pixel tiles are
+// dW[t][f][c] = sum over output pixels of dy[pixel][f] * x[pixel shifted by tap t][c]. The pixels are the reduction. Both sides are split
+// in three parts (see above) when they are staged, 4 channels of a pixel at a time, and gfx950's transposing LDS reads make operands of 8
+// pixels of one channel per lane from the pixel rows, so a tap is an offset. A wavefront holds 32 filters x 16 channels of all 9 taps (72
+// sums, v_mfma_f32_16x16x32_bf16) and multiplies 32 pixels at a time: 66 reads of 8 bytes per 108 matrix instructions of 16 cycles, of the
+// LDS's bandwidth 60 %. The small products of 32 pixels start from zero and are added to the sums once: an accumulator of their own for
+// every tap does not fit, and in one accumulator with the leading product the error is larger than that of float32 instructions.
+// WF x WC wavefronts cover 32*WF filters x 16*WC channels; of fewer than four, the WK = 4 / (WF*WC) that are left over take other
+// pixels, and their sums are added in LDS (halves of the tile at a time, a wavefront keeps 8 / WK of its kernels). Pixel tiles are
 // split over the workgroups (two per CU); every split writes the kept taps in compact slot order, pc_wgrad_reduce adds the planes in a
-// fixed order.
-// THIN (at most 3 channels): the 9 * C (tap, channel) pairs are the columns of one tile, one instruction instead of 9.
-#define F32W_ND 2       // 16-byte elements of dy, and
-#define F32W_NX 6       // of x, staged per thread and pixel tile
+// fixed order. 64 x 28 x 28, 128 -> 128, with the sum of the planes: 151 -> 80 us (32 x 32 tiles of v_mfma_f32_32x32x2_f32 before); matrix
+// cores busy 53 % of the time, the LDS 40 %. A third wavefront per SIMD would need 168 registers, this takes 195.
+// THIN (at most 3 channels): the 9 * C (tap, channel) pairs are the columns of one tile of float32 instructions, one instead of 9.
+// 16-byte elements of dy and of x staged per thread and pixel tile (three parts: 32 pixels of dy per wavefront that shares them)
+__host__ __device__ constexpr int f32w_nd(int wc, bool thin) { return thin || wc == 2 ? 2 : 4; }
+__host__ __device__ constexpr int f32w_nx(bool thin) { return thin ? 6 : 4; }
 
 struct F32WgradArgs {
     int32_t N, H, W, C, F, Ho, Wo, stride;
@@ -776,22 +785,26 @@ struct F32WgradArgs {
     int64_t pstride;                      // slots per partial plane
 };
 
+// Words per staged pixel of n channels in three parts: rows of 64 bytes of four pixels in a row stand in different banks
+__host__ __device__ constexpr int f32w_pitch(int n) { return n == 64 ? 104 : n == 32 ? 56 : 24; }
+
 template <int WF, int WC, bool THIN, bool VEC>
 __global__ void __launch_bounds__(256, 2)
 pc_f32_wgrad_kernel(const float *__restrict__ x, const float *__restrict__ dy, F32WgradArgs a, const uint32_t *__restrict__ kinfo,
                     float4 *__restrict__ partial)
 {
     extern __shared__ __align__(16) float smem[];
-    constexpr int WK = 4 / (WF * WC), FD = 32 * WF, CD = THIN ? 4 : 32 * WC;
-    constexpr int PD = FD + 4, PX = THIN ? 4 : CD + 4;       // floats per staged pixel
+    constexpr int WK = 4 / (WF * WC), FD = 32 * WF, CT = THIN ? 32 : 16, CD = THIN ? 4 : CT * WC;   // CT: columns of a wavefront
+    constexpr int F32W_ND = f32w_nd(WC, THIN), F32W_NX = f32w_nx(THIN);
+    constexpr int PD = THIN ? FD + 4 : f32w_pitch(FD), PX = THIN ? 4 : f32w_pitch(CD);   // words per staged pixel
     constexpr int NT = THIN ? 1 : 9;
-    const int lane = threadIdx.x & 63, h = lane >> 5, n32 = lane & 31;
+    const int lane = threadIdx.x & 63, h = lane / CT, n32 = lane % CT;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wk = wave % WK, wc = (wave / WK) % WC, wf = wave / WK / WC;
     auto divide = [&](int q, int d, uint32_t mg) { return a.exact ? (int)pc_udiv((uint32_t)q, mg) : q / d; };
     const int b = (int)blockIdx.x, tile = divide(b, a.ksplit, a.mg_ks), split = b - tile * a.ksplit;
     const int tf = divide(tile, a.ct, a.mg_ct), c0 = (tile - tf * a.ct) * CD, f0 = tf * FD;
-    float *sd = smem, *sx = smem + a.TR * a.TCe * PD;
+    float *sd = smem, *sx = smem + (THIN ? a.TR * a.TCe : 256 * F32W_ND / (FD / 4)) * PD;
 
     // staged elements: a thread takes the same 4 filters (channels) of several positions; position inside the tile (or
     // its x region) and offset inside an image
@@ -839,11 +852,23 @@ pc_f32_wgrad_kernel(const float *__restrict__ x, const float *__restrict__ dy, F
         }
 #pragma unroll
         for (int i = 0; i < F32W_NX; ++i) {
+            if (256 * i >= a.nx) break;           // (the same for all)
             const int yy = iy + (xpos[i] >> 16), xx = ix + (xpos[i] & 0xFFFF);
             const bool ok = xpos[i] >= 0 && (unsigned)yy < (unsigned)a.H && (unsigned)xx < (unsigned)a.W;
             if (VEC) RX[i] = __builtin_amdgcn_raw_buffer_load_b128(xsrc, (int)(ok ? (uint32_t)(xb + xoff[i]) * 4u : OOB), 0, 0);
             else { RX[i] = load4(ximg, (int64_t)xb + xoff[i], ok, xleft); okx |= ok ? 1u << i : 0u; }
         }
+    };
+    auto store = [&](float *at, int part, int channels, const v4u32 &v) __attribute__((always_inline)) {   // 4 channels of a pixel
+        if (THIN) {
+            *reinterpret_cast<v4u32 *>(at + part * 4) = v;
+            return;
+        }
+        uint32_t s[2][3];
+        f32_split(__uint_as_float(v[0]), __uint_as_float(v[1]), s[0]);
+        f32_split(__uint_as_float(v[2]), __uint_as_float(v[3]), s[1]);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) *reinterpret_cast<v2u32 *>(at + k * (channels / 2) + part * 2) = v2u32{s[0][k], s[1][k]};
     };
     auto put = [&]() {
 #pragma unroll
@@ -852,7 +877,7 @@ pc_f32_wgrad_kernel(const float *__restrict__ x, const float *__restrict__ dy, F
                 if (!VEC)
 #pragma unroll
                     for (int k = 0; k < 4; ++k) RD[i][k] = ((okd >> i) & 1u) && dleft > k ? RD[i][k] : 0u;
-                *reinterpret_cast<v4u32 *>(sd + (dq + i * (1024 / FD)) * PD + dp * 4) = RD[i];
+                store(sd + (dq + i * (1024 / FD)) * PD, dp, FD, RD[i]);
             }
 #pragma unroll
         for (int i = 0; i < F32W_NX; ++i)
@@ -860,130 +885,189 @@ pc_f32_wgrad_kernel(const float *__restrict__ x, const float *__restrict__ dy, F
                 if (!VEC)
 #pragma unroll
                     for (int k = 0; k < 4; ++k) RX[i][k] = ((okx >> i) & 1u) && xleft > k ? RX[i][k] : 0u;
-                *reinterpret_cast<v4u32 *>(sx + (xq + i * (1024 / CD)) * PX + xp * 4) = RX[i];
+                store(sx + (xq + i * (1024 / CD)) * PX, xp, CD, RX[i]);
             }
     };
 
-    f32x16 acc[NT];
+    // sums of a lane: NV filters of each tap
+    constexpr int NV = THIN ? 16 : 8;
+    f32x4 acc[NT][NV / 4];
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[t][r] = 0.0f;
-    const int half = a.TCe >> 1, steps = a.TR * half;
-    const int a_base = h * PD + wf * 32 + n32;
-    int b_base;
-    if (THIN) {
-        const int tap = n32 < 9 * a.C ? n32 / a.C : 0, cn = n32 < 9 * a.C ? n32 - tap * a.C : 0;
-        b_base = (h * a.stride + tap / 3 * a.IW + tap % 3) * PX + cn;
-    } else {
-        b_base = h * a.stride * PX + wc * 32 + n32;
-    }
-    const int row = a.IW * PX;
-    // operands of two pixel pairs, used in turn
-    float fa[2], fb[2][NT];
-    auto read = [&](int s, int k) __attribute__((always_inline)) {
-        const int y = (int)pc_udiv((uint32_t)s, a.mg_half), xs = (s - y * half) * 2;
-        fa[k] = sd[a_base + (y * a.TCe + xs) * PD];
-        const float *q = sx + b_base + (y * a.IW + xs) * a.stride * PX;
-        if (THIN) fb[k][0] = q[0];
-        else
-#pragma unroll
-            for (int t = 0; t < NT; ++t) fb[k][t] = q[t / 3 * row + t % 3 * PX];
-    };
-    auto multiply = [&](int k) __attribute__((always_inline)) {
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[k], fb[k][t], acc[t], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-    };
+        for (int q = 0; q < NV / 4; ++q) acc[t][q] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    const int half = a.TCe >> 1, steps = THIN ? a.TR * half : (a.TR * a.TC + 31) >> 5;     // pixel pairs, or groups of 32 pixels
     int kt = split;
     if (kt < a.n_tiles) issue(kt);
-    // (compact slot, pattern mask) of the 16 kernels this lane writes at the end, requested here: behind the loop they
-    // would cost 16 memory round trips in a row
+    // (compact slot, pattern mask) of the NKER kernels that this lane writes at the end: requested under the last tile, in the registers
+    // of its staged elements; behind the loop they would cost a memory round trip
     const int e_tap = THIN && n32 < 9 * a.C ? n32 / a.C : 0;
-    const int e_c = THIN ? n32 - e_tap * a.C : c0 + wc * 32 + n32;
+    const int e_c = THIN ? n32 - e_tap * a.C : c0 + wc * CT + n32;
     const bool e_on = THIN ? n32 < 9 * a.C : e_c < a.C;
-    constexpr int NKER = 16 / WK;                 // kernels of a lane at the end, and the first of its groups of 4 filters
-    const int quad0 = WK == 1 ? 0 : WK == 2 ? 2 * wk : 2 * (wk & 1) + (wk >> 1);
-    uint32_t kinf[NKER];
+    constexpr int NKER = NV / WK;                 // kernels of a lane at the end, and the first of them
+    const int v0 = WK == 1 ? 0 : WK == 2 ? wk * (NV / 2) : (wk & 1) * (NV / 2) + (wk >> 1) * (NV / 4);
+    auto filter = [&](int r) __attribute__((always_inline)) { return f0 + wf * 32 + (THIN ? 8 : 16) * ((v0 + r) >> 2) + 4 * h + ((v0 + r) & 3); };
+    auto kernels = [&]() {
 #pragma unroll
-    for (int r = 0; r < NKER; ++r) {
-        const int f = f0 + wf * 32 + 8 * (quad0 + (r >> 2)) + 4 * h + (r & 3);
-        const bool on = e_on && f < a.F;
-        const uint32_t u = kinfo[on ? (int64_t)f * a.C + e_c : 0];
-        kinf[r] = on ? u : 0xFFFFFFFFu;
-    }
-    for (bool first = true; kt < a.n_tiles; kt += a.ksplit, first = false) {
-        if (!first) __syncthreads();
-        put();
-        __syncthreads();
-        if (kt + a.ksplit < a.n_tiles) issue(kt + a.ksplit);
-        // operands of a pixel pair are read one pair ahead (past the last pair: this one again, unused, so that the reads
-        // stand under no condition and the waits count them)
-        if (wk >= steps) continue;
-        read(wk, 0);
-        int s = wk;
-        for (; s + WK < steps; s += 2 * WK) {
-            read(s + WK, 1);
-            multiply(0);
-            read(s + 2 * WK < steps ? s + 2 * WK : s, 0);
-            multiply(1);
+        for (int r = 0; r < NKER; ++r) RX[r >> 2][r & 3] = kinfo[e_on && filter(r) < a.F ? (int64_t)filter(r) * a.C + e_c : 0];
+    };
+    if (kt >= a.n_tiles) kernels();
+    if constexpr (THIN) {
+        f32x16 sum;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sum[r] = 0.0f;
+        const int a_base = h * PD + wf * 32 + n32;
+        const int tap = n32 < 9 * a.C ? n32 / a.C : 0, cn = n32 < 9 * a.C ? n32 - tap * a.C : 0;
+        const int b_base = (h * a.stride + tap / 3 * a.IW + tap % 3) * PX + cn;
+        // operands of two pixel pairs, used in turn
+        float fa[2], fb[2];
+        auto read = [&](int s, int k) __attribute__((always_inline)) {
+            const int y = (int)pc_udiv((uint32_t)s, a.mg_half), xs = (s - y * half) * 2;
+            fa[k] = sd[a_base + (y * a.TCe + xs) * PD];
+            fb[k] = sx[b_base + (y * a.IW + xs) * a.stride * PX];
+        };
+        auto multiply = [&](int k) __attribute__((always_inline)) {
+            __builtin_amdgcn_sched_barrier(0);
+            sum = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[k], fb[k], sum, 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        for (bool first = true; kt < a.n_tiles; kt += a.ksplit, first = false) {
+            if (!first) __syncthreads();
+            put();
+            __syncthreads();
+            if (kt + a.ksplit < a.n_tiles) issue(kt + a.ksplit);
+            else kernels();
+            // operands of a pixel pair are read one pair ahead (past the last pair: this one again, unused, so that the reads
+            // stand under no condition and the waits count them)
+            if (wk >= steps) continue;
+            read(wk, 0);
+            int s = wk;
+            for (; s + WK < steps; s += 2 * WK) {
+                read(s + WK, 1);
+                multiply(0);
+                read(s + 2 * WK < steps ? s + 2 * WK : s, 0);
+                multiply(1);
+            }
+            if (s < steps) multiply(0);
         }
-        if (s < steps) multiply(0);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[0][r >> 2][r & 3] = sum[r];
+    } else {
+        // Transposing reads: 16 lanes take 4 pixels of 16 channels, lane l gets 4 pixels of channel l % 16; two reads make the lane's 8
+        // pixels 8 (l / 16) .. + 7 of the wavefront's 32. Pixels past the tile: zeros of dy, x of pixel 0.
+        const int chan = (lane & 3) * 8;
+        typedef __attribute__((address_space(3))) i16x4 *lds4;
+        int pa[2], pb[2];                         // bytes
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int p = wk * 32 + 8 * h + 4 * j + (n32 >> 2), q = p < a.TR * a.TC ? p : 0, y = (int)pc_udiv((uint32_t)q, a.mg_TCe);
+            pa[j] = (p * PD + wf * 16) * 4 + chan;
+            pb[j] = (256 * F32W_ND / (FD / 4) * PD + (y * a.IW + q - y * a.TCe) * a.stride * PX + wc * (CT / 2)) * 4 + chan;
+        }
+        auto parts = [&](int q0, int q1, int channels) __attribute__((always_inline)) -> F32Parts {
+            F32Parts o;
+            const unsigned char *p0 = reinterpret_cast<const unsigned char *>(smem) + q0, *p1 = reinterpret_cast<const unsigned char *>(smem) + q1;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4)(p0 + k * channels * 2)), hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4)(p1 + k * channels * 2));
+                const short __attribute__((ext_vector_type(8))) v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+                __builtin_memcpy(&o.p[k], &v, 16);
+            }
+            return o;
+        };
+        const int row = a.IW * PX * 4;
+        for (bool begin = true; kt < a.n_tiles; kt += a.ksplit, begin = false) {
+            if (!begin) __syncthreads();
+            __builtin_amdgcn_s_setprio(0);        // a wavefront that multiplies goes first (9 x 73 x 74, 416 -> 16: 122.7 -> 110.8 us)
+            put();
+            __syncthreads();
+            if (kt + a.ksplit < a.n_tiles) issue(kt + a.ksplit);
+            else kernels();
+            __builtin_amdgcn_s_setprio(1);
+            if (wk >= steps) continue;
+#pragma unroll
+            for (int j = 0; j < 2; ++j) asm volatile("" : "+v"(pb[j]));   // (else the addresses of all taps are held in registers)
+            F32Parts A[2], Bq[3];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) A[i] = parts(pa[0] + i * 32, pa[1] + i * 32, FD);
+            Bq[0] = parts(pb[0], pb[1], CD);
+            // The small products of a tile start from zero and are added to its sums once: they round below the last bit of these.
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                if (t + 1 < NT) {
+                    const int at = (t + 1) / 3 * row + (t + 1) % 3 * (PX * 4);
+                    Bq[(t + 1) % 3] = parts(pb[0] + at, pb[1] + at, CD);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                f32x4 low[2] = {{0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}};
+#pragma unroll
+                for (int m = 0; m < 6; ++m)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        constexpr int PA[6] = {0, 1, 1, 0, 2, 0}, PB[6] = {1, 0, 1, 2, 0, 0};
+                        f32x4 &to = m == 5 ? acc[t][i] : low[i];
+                        to = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[i].p[PA[m]], Bq[t % 3].p[PB[m]], to, 0, 0, 0);
+                    }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int i = 0; i < 2; ++i) acc[t][i] += low[i];
+            }
+        }
     }
-    // Sums of wavefronts that shared pixels: partners swap halves of their groups of filters (a wavefront keeps one), of four then quarters.
+    // Sums of wavefronts that shared pixels: partners swap halves of their filters (a wavefront keeps one), of four then quarters.
     if constexpr (WK > 1) {
-        f32x4 *mine = reinterpret_cast<f32x4 *>(smem) + wave * (2 * NT * 64) + lane;
-        const f32x4 *theirs = reinterpret_cast<const f32x4 *>(smem) + (wave ^ 1) * (2 * NT * 64) + lane;
+        constexpr int G = NV / 8;
+        f32x4 *mine = reinterpret_cast<f32x4 *>(smem) + wave * (G * NT * 64) + lane;
+        const f32x4 *theirs = reinterpret_cast<const f32x4 *>(smem) + (wave ^ 1) * (G * NT * 64) + lane;
         const bool high = wk & 1;
         __syncthreads();
 #pragma unroll
         for (int t = 0; t < NT; ++t)
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
+            for (int j = 0; j < G; ++j) {
                 f32x4 give;
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const float lo = acc[t][4 * j + i], hi = acc[t][8 + 4 * j + i];
+                    const float lo = acc[t][j][i], hi = acc[t][G + j][i];
                     give[i] = high ? lo : hi;
-                    acc[t][4 * j + i] = high ? hi : lo;
+                    acc[t][j][i] = high ? hi : lo;
                 }
-                mine[(t * 2 + j) * 64] = give;
+                mine[(t * G + j) * 64] = give;
                 __builtin_amdgcn_sched_barrier(0);
             }
         __syncthreads();
 #pragma unroll
         for (int t = 0; t < NT; ++t)
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const f32x4 got = theirs[(t * 2 + j) * 64];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) acc[t][4 * j + i] += got[i];
+            for (int j = 0; j < G; ++j) {
+                acc[t][j] += theirs[(t * G + j) * 64];
                 if (t % 3 == 2) __builtin_amdgcn_sched_barrier(0);
             }
     }
     if constexpr (WK > 2) {
-        f32x4 *mine = reinterpret_cast<f32x4 *>(smem) + wave * (NT * 64) + lane;
-        const f32x4 *theirs = reinterpret_cast<const f32x4 *>(smem) + (wave ^ 2) * (NT * 64) + lane;
+        constexpr int G = NV / 4;                 // values given away
+        typedef float give_t __attribute__((ext_vector_type(G)));
+        give_t *mine = reinterpret_cast<give_t *>(smem) + wave * (NT * 64) + lane;
+        const give_t *theirs = reinterpret_cast<const give_t *>(smem) + (wave ^ 2) * (NT * 64) + lane;
         const bool high = wk >> 1;
         __syncthreads();
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
-            f32x4 give;
+            give_t give;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float lo = acc[t][i], hi = acc[t][4 + i];
+            for (int i = 0; i < G; ++i) {
+                const float lo = acc[t][i >> 2][i & 3], hi = acc[t][(G + i) >> 2][(G + i) & 3];
                 give[i] = high ? lo : hi;
-                acc[t][i] = high ? hi : lo;
+                acc[t][i >> 2][i & 3] = high ? hi : lo;
             }
             mine[t * 64] = give;
         }
         __syncthreads();
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
-            const f32x4 got = theirs[t * 64];
+            const give_t got = theirs[t * 64];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) acc[t][i] += got[i];
+            for (int i = 0; i < G; ++i) acc[t][i >> 2][i & 3] += got[i];
         }
     }
     // kept taps in compact order, straight from the accumulators: a lane holds one channel and NKER filters
@@ -991,12 +1075,12 @@ pc_f32_wgrad_kernel(const float *__restrict__ x, const float *__restrict__ dy, F
     uint32_t redo = 0u;                           // kernels with a sum that is not finite
 #pragma unroll
     for (int r = 0; r < NKER; ++r) {
-        const uint32_t info = kinf[r];
-        if (info == 0xFFFFFFFFu) continue;
+        const uint32_t info = RX[r >> 2][r & 3];
+        if (!e_on || filter(r) >= a.F || info == 0xFFFFFFFFu) continue;
         if (THIN) {
             if ((info >> e_tap) & 1u) {
-                reinterpret_cast<float *>(pout + (info >> 9))[__popc(info & ((1u << e_tap) - 1u))] = acc[0][r];
-                redo |= fabsf(acc[0][r]) < INFINITY ? 0u : 1u << r;
+                reinterpret_cast<float *>(pout + (info >> 9))[__popc(info & ((1u << e_tap) - 1u))] = acc[0][r >> 2][r & 3];
+                redo |= fabsf(acc[0][r >> 2][r & 3]) < INFINITY ? 0u : 1u << r;
             }
             continue;
         }
@@ -1006,7 +1090,7 @@ pc_f32_wgrad_kernel(const float *__restrict__ x, const float *__restrict__ dy, F
         for (int t = NT - 1; t >= 0; --t) {           // the four set bits of the mask, ascending
             const bool on = __builtin_uadd_overflow(bits, bits, &bits);       // (tap t's: one addition that shifts it out)
             o.w = on ? o.z : o.w; o.z = on ? o.y : o.z; o.y = on ? o.x : o.y;
-            o.x = on ? acc[t][r] : o.x;
+            o.x = on ? acc[t][r >> 2][r & 3] : o.x;
         }
         pout[info >> 9] = o;
         const float z = fmaf(o.x, 0.0f, fmaf(o.y, 0.0f, fmaf(o.z, 0.0f, o.w * 0.0f)));   // NaN when one of them is not finite
@@ -1016,7 +1100,7 @@ pc_f32_wgrad_kernel(const float *__restrict__ x, const float *__restrict__ dy, F
     // over the pixels of this workgroup that exist. (Finite data pays for the check only: 8 x 32 x 32, 16 -> 16 all three passes
     // 25.9 us without and with it. One infinity in 1000 elements of x: 28 x 28, 128 -> 128, batch 64 2.1 ms forward, 3.6 ms here.)
     for (; redo; redo &= redo - 1u) {
-        const int r = __ffs((int)redo) - 1, f = f0 + wf * 32 + 8 * (quad0 + (r >> 2)) + 4 * h + (r & 3);
+        const int r = __ffs((int)redo) - 1, f = filter(r);
         const uint32_t info = kinfo[(int64_t)f * a.C + e_c], mask = info & 511u;
         constexpr int NK = THIN ? 1 : 4;          // kept taps of this lane's kernel
         int dr[NK], dc[NK];
@@ -1034,20 +1118,16 @@ pc_f32_wgrad_kernel(const float *__restrict__ x, const float *__restrict__ dy, F
             const int tc = k % a.tiles_c, q = k / a.tiles_c, tr = q % a.tiles_r, n = q / a.tiles_r;
             const float *dimg = dy + (int64_t)n * a.Ho * a.Wo * a.F + f, *ximg = x + (int64_t)n * a.H * a.W * a.C + e_c;
 #pragma unroll 2
-            for (int s = 0; s < steps; ++s) {
-                const int y = s / half, oy = tr * a.TR + y;
+            for (int s = 0; s < a.TR * a.TC; ++s) {
+                const int y = s / a.TC, col = s - y * a.TC, oy = tr * a.TR + y, ox = tc * a.TC + col;
+                const bool on = oy < a.Ho && ox < a.Wo;
+                const float d = dimg[on ? ((int64_t)oy * a.Wo + ox) * a.F : 0];
 #pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    const int col = (s - y * half) * 2 + i, ox = tc * a.TC + col;
-                    const bool on = col < a.TC && oy < a.Ho && ox < a.Wo;
-                    const float d = dimg[on ? ((int64_t)oy * a.Wo + ox) * a.F : 0];
-#pragma unroll
-                    for (int j = 0; j < NK; ++j) {
-                        const int iy = oy * a.stride + dr[j], ix = ox * a.stride + dc[j];
-                        const bool in = on && (unsigned)iy < (unsigned)a.H && (unsigned)ix < (unsigned)a.W;
-                        const float v = ximg[in ? ((int64_t)iy * a.W + ix) * a.C : 0];
-                        sum[j] = in ? fmaf(d, v, sum[j]) : sum[j];
-                    }
+                for (int j = 0; j < NK; ++j) {
+                    const int iy = oy * a.stride + dr[j], ix = ox * a.stride + dc[j];
+                    const bool in = on && (unsigned)iy < (unsigned)a.H && (unsigned)ix < (unsigned)a.W;
+                    const float v = ximg[in ? ((int64_t)iy * a.W + ix) * a.C : 0];
+                    sum[j] = in ? fmaf(d, v, sum[j]) : sum[j];
                 }
             }
             dead = true;
@@ -1071,21 +1151,21 @@ pc_status pc_f32_bwd_weight(pc_ctx *ctx, const pc_conv_desc *d, const pc_packed 
     const bool thin = d->C <= 3;
     // The tile of an arrangement of the wavefronts; false when the staging registers do not hold it.
     auto tile = [&](F32WgradArgs &t, int wf, int wc, int TR, int TC) {
-        const int FD = 32 * wf, CD = thin ? 4 : 32 * wc, max_pos = 256 * F32W_ND / (FD / 4);
+        const int FD = 32 * wf, CD = thin ? 4 : 16 * wc, nd = 256 * f32w_nd(wc, thin), max_pos = nd / (FD / 4);
         t.ft = (d->F + FD - 1) / FD;
         t.ct = thin ? 1 : (d->C + CD - 1) / CD;
-        t.TR = TR; t.TC = TC; t.TCe = (TC + 1) / 2 * 2;
+        t.TR = TR; t.TC = TC; t.TCe = thin ? (TC + 1) / 2 * 2 : TC;
         t.IR = (TR - 1) * d->stride + 3; t.IW = (t.TCe - 1) * d->stride + 3;
-        t.nd = TR * t.TCe * (FD / 4);
+        t.nd = thin ? TR * t.TCe * (FD / 4) : nd;     // (three parts: zeros up to the last group of 32 pixels)
         t.nx = t.IR * t.IW * (CD / 4);
         t.tiles_r = (t.Ho + TR - 1) / TR; t.tiles_c = (t.Wo + TC - 1) / TC;
-        return TR * t.TCe <= max_pos && t.nx <= 256 * F32W_NX;
+        return TR * t.TCe <= max_pos && t.nx <= 256 * f32w_nx(thin);
     };
     // Arrangement, pixel tile and splits by an estimate of the time (us): a start, the tiles of a workgroup (a wait, staging, matrix steps; two
     // workgroups share a CU from 256 up, two rounds from 512), the sums of wavefronts that share pixels and the pick of the kept taps, the
-    // tensors' bytes, the partial planes. Fitted to 10000 timings of 70 layers (9 % rms): 2.5 % behind the fastest, the worst 15 %; the widest
-    // tile that the channels fill and the pixel tile of the best throughput were 9 % behind (9 images 73 x 74, 416 -> 16 181 -> 153 us; 1 x 64 x 64,
-    // 48 -> 256 30 -> 22). The partial planes stay within 16 MiB. (The choice of a layer is remembered: kernel tile, pixel tile, splits.)
+    // tensors' bytes, the partial planes. Fitted to 5700 timings of 160 layers (8 % rms): 3 % behind the fastest, the worst 20 % (the
+    // first layer's: 10000 timings, 2.5 %); the widest tile that the channels fill and the pixel tile of the best throughput were 9 %
+    // behind. The partial planes stay within 16 MiB. (The choice of a layer is remembered: kernel tile, pixel tile, splits.)
     int wf = 1, wc = 1, ks = 1;
     const int32_t key[PC_CHOICE_KEY] = {9, d->N, d->H, d->W, d->C, d->F, d->stride, (int32_t)nslots, pk->nnzk >= 0, 0};
     bool known;
@@ -1093,24 +1173,24 @@ pc_status pc_f32_bwd_weight(pc_ctx *ctx, const pc_conv_desc *d, const pc_packed 
     if (!known || *choice < 0) {
         const int64_t cap = std::max((int64_t)1, ((int64_t)1 << 20) / nslots);
         const double kept = pk->nnzk >= 0 ? (double)nslots : 0.3 * (double)nslots;
-        const double moved = 0.491e-6 * 4.0 * ((double)a.N * a.H * a.W * a.C + (double)a.N * a.Ho * a.Wo * a.F), moved3 = moved * moved * moved;
+        const double moved = (thin ? 0.491e-6 : 0.466e-6) * 4.0 * ((double)a.N * a.H * a.W * a.C + (double)a.N * a.Ho * a.Wo * a.F), moved3 = moved * moved * moved;
         double best = 1e30;
         *choice = -1;
         for (int v = 0; v < 4; ++v) {
             const int vf = v & 1 ? 1 : 2, vc = v & 2 || thin ? 1 : 2, wk = 4 / (vf * vc);
             if (thin && (v & 2)) continue;
-            const double end = wk == 1 ? 0.78 : wk == 2 ? 0.39 : 1.2;
+            const double end = !thin ? 0.305 : wk == 2 ? 0.39 : 1.2;
             F32WgradArgs t = a;
             for (int TR = 1; TR <= 64 && TR <= a.Ho; ++TR)
                 for (int TC = 1; TC <= 64 && TC <= a.Wo && tile(t, vf, vc, TR, TC); ++TC) {
                     const int64_t nkt = (int64_t)t.N * t.tiles_r * t.tiles_c, T = (int64_t)t.ft * t.ct;
                     const double steps = (double)((TR * t.TCe / 2 + wk - 1) / wk), staged = (t.nd + t.nx) / 256.0;
-                    const double lone = 0.514 + 0.314 * (thin ? 0.25 : 1.0) * steps, pair = 0.618 + 0.0194 * staged + 0.468 * (thin ? 0.25 : 1.0) * steps;
+                    const double lone = thin ? 0.514 + 0.0785 * steps : 1.661 + 0.106 * staged, pair = thin ? 0.618 + 0.0194 * staged + 0.117 * steps : 1.776 + 0.117 * staged;
                     for (int places = 2 * ctx->num_cu; places >= ctx->num_cu / 2; places >>= 1) {
                         const int64_t k = std::max((int64_t)1, std::min(std::min(cap, nkt), (places + T - 1) / T)), G = T * k;
                         const double u = (double)((nkt + k - 1) / k);
-                        const double us = 6.65 + (G <= ctx->num_cu ? u * lone + end : (double)((G + 2 * ctx->num_cu - 1) / (2 * ctx->num_cu)) * (u * pair + 1.7 * end));
-                        const double c = cbrt(us * us * us + moved3) + (k > 1 ? 2.2 + 11.5e-6 * (double)k * kept : 0.0);
+                        const double us = (thin ? 6.65 : 5.0) + (G <= ctx->num_cu ? u * lone + (thin ? end : 0.0) : (double)((G + 2 * ctx->num_cu - 1) / (2 * ctx->num_cu)) * (u * pair + 1.7 * end));
+                        const double c = cbrt(us * us * us + moved3) + (k > 1 ? (thin ? 2.2 : 3.5) + (thin ? 11.5e-6 : 14.1e-6) * (double)k * kept : 0.0);
                         if (c < best) {
                             best = c;
                             *choice = (vf - 1) | (vc - 1) << 1 | TR << 2 | TC << 9 | (int32_t)k << 16;
@@ -1122,11 +1202,11 @@ pc_status pc_f32_bwd_weight(pc_ctx *ctx, const pc_conv_desc *d, const pc_packed 
     }
     wf = 1 + (*choice & 1); wc = 1 + (*choice >> 1 & 1); ks = *choice >> 16;
     tile(a, wf, wc, *choice >> 2 & 127, *choice >> 9 & 127);
-    const int wk = 4 / (wf * wc), FD = 32 * wf, CD = thin ? 4 : 32 * wc;
+    const int wk = 4 / (wf * wc), FD = 32 * wf, CD = thin ? 4 : 16 * wc;
     const int64_t nkt = (int64_t)a.N * a.tiles_r * a.tiles_c;
     if (nkt >= ((int64_t)1 << 31)) return pc_fail(ctx, PC_ERR_UNSUPPORTED, "float32 bwd_weight: too many pixel tiles");
     a.n_tiles = (int)nkt;
-    a.mg_half = pc_udiv_magic(a.TCe / 2); a.mg_TCe = pc_udiv_magic(a.TCe); a.mg_IW = pc_udiv_magic(a.IW);
+    a.mg_half = pc_udiv_magic(thin ? a.TCe / 2 : 1); a.mg_TCe = pc_udiv_magic(a.TCe); a.mg_IW = pc_udiv_magic(a.IW);
     a.pstride = nslots;
     a.ksplit = ks;
     const int64_t wgs = (int64_t)a.ft * a.ct * ks;
@@ -1138,9 +1218,9 @@ pc_status pc_f32_bwd_weight(pc_ctx *ctx, const pc_conv_desc *d, const pc_packed 
         pc_status s = pc_scratch(ctx, sizeof(float4) * (size_t)planes * (size_t)nslots, &scr);
         if (s != PC_OK) return s;
     }
-    const int PD = FD + 4, PX = thin ? 4 : CD + 4;
-    size_t lds = sizeof(float) * ((size_t)a.TR * a.TCe * PD + (size_t)a.IR * a.IW * PX);
-    if (wk > 1 && lds < (size_t)(thin ? 1 : 9) * 8 * 1024) lds = (size_t)(thin ? 1 : 9) * 8 * 1024;      // in which the sums of wavefronts are added
+    const int PD = thin ? FD + 4 : f32w_pitch(FD), PX = thin ? 4 : f32w_pitch(CD);
+    size_t lds = sizeof(float) * ((size_t)a.nd / (FD / 4) * PD + (size_t)a.IR * a.IW * PX);
+    if (wk > 1 && lds < (size_t)(thin ? 8 : 36) * 1024) lds = (size_t)(thin ? 8 : 36) * 1024;      // in which the sums of wavefronts are added
     const dim3 grid((unsigned)(a.ft * a.ct * a.ksplit)), blk(256);
     float4 *po = planes > 1 ? (float4 *)scr : (float4 *)dw;
     const float *xp = (const float *)x, *dp = (const float *)dy;

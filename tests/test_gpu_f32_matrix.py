@@ -41,8 +41,9 @@ def test_gather_kernels_still_take_float32(B, ctx, oracle, shape):
 
 
 @pytest.mark.parametrize("waves,shape", [
-    ("1, 1", (1, 12, 1, 8, 200, 1)), ("1, 1", (1, 28, 3, 32, 8, 2)), ("1, 2", (2, 3, 2, 8, 16, 2)), ("1, 2", (3, 9, 11, 40, 24, 1)), ("1, 2", (4, 13, 13, 100, 66, 2)),
-    ("2, 1", (14, 21, 1, 8, 64, 1)), ("2, 1", (4, 10, 15, 8, 33, 1)), ("2, 1", (3, 30, 31, 2, 50, 2)), ("1, 1", (1, 15, 6, 33, 33, 2))])
+    ("1, 1", (1, 29, 3, 100, 40, 1)), ("1, 1", (1, 4, 22, 24, 66, 1)), ("1, 1", (8, 45, 2, 130, 64, 1)), ("1, 2", (6, 2, 19, 100, 64, 1)), ("1, 2", (1, 13, 4, 40, 130, 1)),
+    ("1, 2", (4, 6, 22, 40, 33, 1)), ("2, 1", (1, 3, 34, 24, 40, 2)), ("2, 1", (1, 18, 12, 130, 130, 2)), ("2, 1", (11, 8, 49, 33, 40, 1)), ("2, 1", (3, 30, 31, 2, 50, 2)),
+    ("2, 2", (1, 3, 5, 8, 66, 2)), ("2, 2", (2, 12, 1, 33, 66, 1))])
 def test_wavefronts_that_share_pixels(B, ctx, oracle, waves, shape):
     """Weight gradients whose wavefronts add their sums in LDS: two and four of them, rows of quads and not, the (tap, channel) columns of a first layer."""
     run_case(B, ctx, oracle, shape, "f32", 8, 0.4, B.PC_VARIANT_AUTO, "f32_shared")
