@@ -31,13 +31,31 @@ struct WgradDmaLayer {
     int32_t gx, gy;
 };
 
+// A layer with at most 4 input channels.
+struct ThinWgradArgs {
+    int32_t N, H, W, C, F, Ho, Wo, stride;
+    int32_t rows, TC, IW, nx;        // N * Ho; columns of a tile, staged x columns and pixels
+    int32_t RPx, RPd, x_off, buf_bytes;
+    int32_t tiles_c, n_tiles, pstride;
+    uint32_t x_bytes, dy_bytes;
+    uint32_t mg_tc, mg_Ho, mg_H1, mg_IW;
+};
+struct ThinWgradLayer {
+    ThinWgradArgs a;
+    const uint16_t *x, *dy;
+    const uint32_t *kinfo;
+    float *out;
+    int32_t ksplit, blocks_f;             // ksplit = 0: none
+};
+
 template <int LAYERS> struct WgradDmaLayers {
     int32_t n;
     int32_t blk0[WD_GROUP_MAX + 1];
     WgradDmaLayer layer[LAYERS];
 };
 typedef WgradDmaLayers<1> WgradDmaOne;
-typedef WgradDmaLayers<WD_GROUP_MAX> WgradDmaGroup;
+struct WgradDmaGroup : WgradDmaLayers<WD_GROUP_MAX> { ThinWgradLayer thin; };
+static_assert(sizeof(WgradDmaGroup) <= 4096, "kernel arguments");
 
 struct WgradDmaPlan {
     WgradDmaArgs a;
@@ -55,15 +73,6 @@ bool pc_wgrad_dma_plan_one(const pc_conv_desc *d, int64_t nslots, double kept, i
 pc_status pc_wgrad_dma_launch(pc_ctx *ctx, WgradDmaOne &g, size_t lds);
 pc_status pc_wgrad_dma_launch(pc_ctx *ctx, WgradDmaGroup &g, size_t lds);
 
-// A layer with at most 4 input channels.
-struct ThinWgradArgs {
-    int32_t N, H, W, C, F, Ho, Wo, stride;
-    int32_t rows, TC, IW, nx;        // N * Ho; columns of a tile, staged x columns and pixels
-    int32_t RPx, RPd, x_off, buf_bytes;
-    int32_t tiles_c, n_tiles, pstride;
-    uint32_t x_bytes, dy_bytes;
-    uint32_t mg_tc, mg_Ho, mg_H1, mg_IW;
-};
 struct ThinWgradPlan {
     ThinWgradArgs a;
     int nf, xp, blocks_f, ksplit;    // blocks of 16 filters per workgroup, pixels of x per thread, blocks of 64 filters, workgroups that share the tiles

@@ -346,17 +346,6 @@ __global__ void __launch_bounds__(256, 2) pc_mfma_wgrad_dma_kernel(WgradDmaOne g
     pc_wgrad_dma_body<ST, FW, CW>(y.x, y.dy, y.a, y.kinfo, y.partial, y.dw, (int)blockIdx.x, y.gx);
 }
 
-// The layers of a network in one launch: workgroup b serves workgroup b - blk0[l] of layer l (blk0 entries are multiples of 8).
-__global__ void __launch_bounds__(256, 2) pc_mfma_wgrad_dma_group_kernel(WgradDmaGroup g)
-{
-    const int l = pc_batch_find(g.blk0, g.n, (int)blockIdx.x);
-    const WgradDmaLayer &y = g.layer[l];
-    const int lin = (int)blockIdx.x - g.blk0[l];
-    if (lin >= y.gx * y.gy * y.a.ksplit) return;
-    if (y.a.stride == 1) pc_wgrad_dma_layer<1>(y, lin);
-    else pc_wgrad_dma_layer<2>(y, lin);
-}
-
 // Wavefronts along the filters and the channels of a workgroup's tile
 static const struct { int fw, cw, lgPW; } kWaves[WD_WAVES] = {{2, 2, 0}, {1, 2, 1}, {2, 1, 1}, {1, 1, 2}};     // (lgPW: log2 of those that share pixels)
 
@@ -509,13 +498,13 @@ static void wd_place(WgradDmaLayer &y)
 }
 
 template <class Args>
-static pc_status wd_launch(pc_ctx *ctx, void (*kernel)(Args), pc_per_device_once &attr, const Args &g, size_t lds)
+static pc_status wd_launch(pc_ctx *ctx, void (*kernel)(Args), pc_per_device_once &attr, const Args &g, size_t lds, int more = 0)
 {
     if (pc_once_pending(attr, ctx->device)) {
         PC_HIP(ctx, hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, WD_LDS_MAX));
         pc_once_done(attr, ctx->device);
     }
-    hipLaunchKernelGGL(kernel, dim3((unsigned)g.blk0[g.n]), dim3(256), lds, ctx->stream, g);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(g.blk0[g.n] + more)), dim3(256), lds, ctx->stream, g);
     return pc_hip_check(ctx, hipGetLastError(), "MFMA bwd_weight (direct loads) launch");
 }
 
@@ -532,14 +521,6 @@ pc_status pc_wgrad_dma_launch(pc_ctx *ctx, WgradDmaOne &g, size_t lds)
     return wd_launch(ctx, kernels[a.stride - 1][a.waves], attr[a.stride - 1][a.waves], g, lds);
 }
 
-pc_status pc_wgrad_dma_launch(pc_ctx *ctx, WgradDmaGroup &g, size_t lds)
-{
-    for (int l = 0; l < g.n; ++l) wd_place(g.layer[l]);
-    static pc_per_device_once attr;
-    pc_note_kernel(ctx, "pc_mfma_wgrad_dma_group_kernel");
-    return wd_launch(ctx, &pc_mfma_wgrad_dma_group_kernel, attr, g, lds);
-}
-
 // ------------------------------------------------------------------ few input channels
 // Backward-weight of a layer with at most 4 input channels (the first of a network). The taps and channels of one tap row are the 16 columns of one
 // matrix operand: the input is staged as pixels of 4 channels (8 bytes), so the 4 x 4 values of 4 pixels side by side are 32 consecutive
@@ -553,14 +534,12 @@ pc_status pc_wgrad_dma_launch(pc_ctx *ctx, WgradDmaGroup &g, size_t lds)
 
 // NF: blocks of 16 filters, XP: pixels of x per thread and tile at most
 template <int NF, int XP>
-__global__ void __launch_bounds__(256, 4)
-pc_thin_wgrad_kernel(const uint16_t *__restrict__ x, const uint16_t *__restrict__ dy, ThinWgradArgs a, const uint32_t *__restrict__ kinfo, float *__restrict__ out)
+__device__ __forceinline__ void pc_thin_wgrad_body(const uint16_t *__restrict__ x, const uint16_t *__restrict__ dy, const ThinWgradArgs &a,
+                                                   const uint32_t *__restrict__ kinfo, float *__restrict__ out, int wg, int G, int f0, unsigned char *lds)
 {
-    extern __shared__ __align__(16) unsigned char lds[];
     constexpr int DB = NF > 2 ? 128 : 64, DL = DB / 16;      // bytes and lanes of a direct load per pixel of dy
     const int lane = threadIdx.x & 63, tid = (int)threadIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int f0 = (int)blockIdx.y * 64;
     const v4u32 ds = wd_rsrc(dy, a.dy_bytes);
     const int d_row = a.Wo * a.F * 2, H1 = a.H + 1;
     const uint64_t mask_c = a.C == 4 ? ~0ull : (1ull << (16 * a.C)) - 1;
@@ -606,11 +585,10 @@ pc_thin_wgrad_kernel(const uint16_t *__restrict__ x, const uint16_t *__restrict_
     for (int r = 0; r < 3; ++r)
 #pragma unroll
         for (int k = 0; k < NF; ++k) acc[r][k] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int G = (int)gridDim.x;      // (at least one tile for each)
     int buf = 0;
-    issue((int)blockIdx.x, 0);
+    issue(wg, 0);                      // (at least one tile for each)
     put(0);
-    for (int t = (int)blockIdx.x; t < a.n_tiles; t += G) {
+    for (int t = wg; t < a.n_tiles; t += G) {
         const bool more = t + G < a.n_tiles;
         if (more) issue(t + G, a.buf_bytes - buf);
         const int tr = (int)pc_udiv((uint32_t)t, a.mg_tc), r0 = tr * TW_ROWS, n0 = (int)pc_udiv((uint32_t)r0, a.mg_Ho), V0 = n0 * H1 + (r0 - n0 * a.Ho) * a.stride;
@@ -673,8 +651,50 @@ pc_thin_wgrad_kernel(const uint16_t *__restrict__ x, const uint16_t *__restrict_
             o.y = kept ? o.x : o.y;
             o.x = kept ? v[t] : o.x;
         }
-        *reinterpret_cast<float4 *>(out + ((int64_t)blockIdx.x * a.pstride + (info >> 9)) * 4) = o;
+        *reinterpret_cast<float4 *>(out + ((int64_t)wg * a.pstride + (info >> 9)) * 4) = o;
     }
+}
+
+template <int NF, int XP>
+__global__ void __launch_bounds__(256, 4)
+pc_thin_wgrad_kernel(const uint16_t *__restrict__ x, const uint16_t *__restrict__ dy, ThinWgradArgs a, const uint32_t *__restrict__ kinfo, float *__restrict__ out)
+{
+    extern __shared__ __align__(16) unsigned char lds[];
+    pc_thin_wgrad_body<NF, XP>(x, dy, a, kinfo, out, (int)blockIdx.x, (int)gridDim.x, (int)blockIdx.y * 64, lds);
+}
+
+__device__ __forceinline__ void pc_thin_wgrad_layer(const ThinWgradLayer &y, int lin)
+{
+    extern __shared__ __align__(16) unsigned char lds[];
+    const int fb = __builtin_amdgcn_readfirstlane(lin / y.ksplit), wg = lin - fb * y.ksplit;
+    pc_thin_wgrad_body<4, 3>(y.x, y.dy, y.a, y.kinfo, y.out, wg, y.ksplit, fb * 64, lds);   // (three and four blocks of 16 filters have the same layout)
+}
+
+// The layers of a network in one launch: workgroup b serves workgroup b - blk0[l] of layer l (blk0 entries are multiples of 8), and behind
+// them the network's first layer: its workgroups, short and bound by memory, fill the places that the others
+// leave at the end (128 images 32 x 32, 13 layers of VGG-16, all of a training step 458 -> 446 us).
+__global__ void __launch_bounds__(256, 2) pc_mfma_wgrad_dma_group_kernel(WgradDmaGroup g)
+{
+    const int first = g.blk0[g.n];
+    if ((int)blockIdx.x < first) {
+        const int l = pc_batch_find(g.blk0, g.n, (int)blockIdx.x);
+        const WgradDmaLayer &y = g.layer[l];
+        const int lin = (int)blockIdx.x - g.blk0[l];
+        if (lin < y.gx * y.gy * y.a.ksplit) {
+            if (y.a.stride == 1) pc_wgrad_dma_layer<1>(y, lin);
+            else pc_wgrad_dma_layer<2>(y, lin);
+        }
+    } else {
+        pc_thin_wgrad_layer(g.thin, (int)blockIdx.x - first);
+    }
+}
+
+pc_status pc_wgrad_dma_launch(pc_ctx *ctx, WgradDmaGroup &g, size_t lds)
+{
+    for (int l = 0; l < g.n; ++l) wd_place(g.layer[l]);
+    static pc_per_device_once attr;
+    pc_note_kernel(ctx, "pc_mfma_wgrad_dma_group_kernel");
+    return wd_launch(ctx, &pc_mfma_wgrad_dma_group_kernel, attr, g, lds, g.thin.ksplit * g.thin.blocks_f);
 }
 
 bool pc_thin_wgrad_plan(const pc_conv_desc *d, int64_t nslots, int num_cu, ThinWgradPlan *out)

@@ -1076,7 +1076,7 @@ pc_status pc_mfma_bwd_weight_group(pc_ctx *ctx, int n, const pc_conv_desc *d, co
     std::vector<int> single;
     size_t total = 0, thin_total = 0;
     struct ThinItem { int l; int64_t nslots; size_t part_off; ThinWgradPlan p; };
-    std::vector<ThinItem> thin;          // layers with few input channels: a launch of their own each, one reduction with the others
+    std::vector<ThinItem> thin;          // layers with few input channels: one goes with the others' launch, more have their own
     std::vector<char> is_thin(n, 0);
     for (int l = 0; l < n; ++l) {
         const int64_t nslots = pk[l]->nnzk >= 0 ? pk[l]->nnzk : (int64_t)pk[l]->v.F * pk[l]->v.C;
@@ -1162,6 +1162,8 @@ pc_status pc_mfma_bwd_weight_group(pc_ctx *ctx, int n, const pc_conv_desc *d, co
                 if (it.dma) runs.push_back({(it.n_ktiles + it.ksplit - 1) / it.ksplit * it.tile_us + it.end_us, it.ct * it.ft * it.ksplit});
             }
             std::sort(runs.begin(), runs.end(), [](const std::pair<double, int> &p, const std::pair<double, int> &q) { return p.first > q.first; });
+            if (!thin.empty())           // (16 KiB of dy per tile and place)
+                runs.push_back({1.5 + 1.7 * thin[0].p.a.n_tiles / thin[0].p.ksplit, thin[0].p.ksplit * thin[0].p.blocks_f});
             for (auto &r : runs)
                 while (r.second > 0) {
                     const auto first = std::min_element(places.begin(), places.end());
@@ -1224,9 +1226,12 @@ pc_status pc_mfma_bwd_weight_group(pc_ctx *ctx, int n, const pc_conv_desc *d, co
         red_nslots.push_back(nslots);
         red_pk.push_back(pk[l]);
     };
-    for (const ThinItem &t : thin) {
+    // the last launch of direct-load layers takes the first of the thin ones along (more than 32 filters: one form of its kernel in theirs)
+    const bool along = !thin.empty() && thin[0].p.nf > 2 && std::any_of(items.begin(), items.end(), [](const GroupItem &it) { return it.dma; });
+    for (size_t i = 0; i < thin.size(); ++i) {
+        const ThinItem &t = thin[i];
         float *partial = t.p.ksplit > 1 ? reinterpret_cast<float *>(base + t.part_off) : dw[t.l];
-        s = pc_thin_wgrad_launch(ctx, t.p, (const uint16_t *)x[t.l], (const uint16_t *)dy[t.l], pk[t.l]->v.kinfo, partial);
+        if (i > 0 || !along) s = pc_thin_wgrad_launch(ctx, t.p, (const uint16_t *)x[t.l], (const uint16_t *)dy[t.l], pk[t.l]->v.kinfo, partial);
         if (s != PC_OK) return s;
         if (t.p.ksplit > 1) reduce(t.l, partial, t.nslots, t.p.ksplit);
     }
@@ -1259,6 +1264,13 @@ pc_status pc_mfma_bwd_weight_group(pc_ctx *ctx, int n, const pc_conv_desc *d, co
             if (it.ksplit > 1) reduce(it.l, partial, it.nslots, it.ksplit);
         }
         if (kd == 2) {
+            memset(&gd.thin, 0, sizeof(gd.thin));
+            if (along && i0 + m == items.size()) {          // (the direct-load layers come last)
+                const ThinItem &t = thin[0];
+                gd.thin = {t.p.a, (const uint16_t *)x[t.l], (const uint16_t *)dy[t.l], pk[t.l]->v.kinfo,
+                           t.p.ksplit > 1 ? reinterpret_cast<float *>(base + t.part_off) : dw[t.l], t.p.ksplit, t.p.blocks_f};
+                lds = std::max(lds, std::max(t.p.lds, (size_t)24 * 1024));     // (sums of four blocks of 16 filters)
+            }
             s = pc_wgrad_dma_launch(ctx, gd, lds);
         } else {
             if (kd == 1) hipLaunchKernelGGL(pc_mfma_wgrad_ws_group_kernel<true>, dim3((unsigned)g.blk0[m]), dim3(512), lds, ctx->stream, g);

@@ -134,3 +134,27 @@ def test_forward_with_a_row_tile_that_is_not_full(B, ctx, oracle, shape):
         assert torch.equal(a.body.view(torch.int16), torch.where(y.body > 0, y.body, torch.zeros_like(y.body)).view(torch.int16))
     finally:
         g.close()
+
+
+@pytest.mark.parametrize("shape", [(3, 9, 11, 3, 40, 1), (1, 224, 9, 3, 136, 1), (2, 64, 31, 2, 48, 1), (5, 33, 35, 1, 72, 2), (7, 5, 3, 4, 64, 2), (9, 32, 32, 3, 32, 1)])
+def test_backward_weight_of_few_channels_in_a_group(B, ctx, oracle, shape):
+    """Behind the workgroups of other layers in their launch (more than 32 filters) and in its own: the sums of a call of its own, of which
+    every workgroup takes the same tiles."""
+    import torch
+    from tests._harness import Case, GpuLayer, rel_l2
+    shapes = [(2, 14, 14, 64, 64, 1), shape, (3, 8, 8, 64, 128, 1)]
+    gs = [GpuLayer(B, ctx, Case(I.Layer(*s), "bf16", 8, I.kept_per_filter(0.5, s[3]), tag=("group", s))) for s in shapes]
+    try:
+        want = gs[1].bwd_weight()[0]
+        assert B.pc_last_kernel(ctx).startswith("pc_thin_wgrad_kernel")
+        for _ in range(2):
+            outs = [torch.full((g.nnzk, 4), float("nan"), device="cuda") for g in gs]
+            B.pc_conv_bwd_weight_batch(ctx, [g.desc for g in gs], [g.pk for g in gs], [g.x for g in gs], [g.dy for g in gs], outs)
+            assert B.pc_last_kernel(ctx).startswith("pc_mfma_wgrad_dma_group_kernel")
+            torch.cuda.synchronize()
+            assert np.array_equal(outs[1].cpu().numpy(), want)
+            for g, o in zip(gs, outs):
+                assert rel_l2(o.cpu().numpy(), g.bwd_weight()[0]) <= 1e-5
+    finally:
+        for g in gs:
+            g.close()
