@@ -1,6 +1,8 @@
 // Forward / backward-data on the matrix cores, both operands brought to LDS by direct loads (see pc_conv_mfma.hip
 // for the implicit-GEMM formulation, the operand tiles and the MFMA register layout).
 #include "pc_mfma.h"
+#include <algorithm>
+
 #include <math.h>
 #include <type_traits>
 
@@ -162,16 +164,24 @@ __device__ __forceinline__ int dm_weight_offset(const DmaArgs &g, int lane)     
     return AT == 4 ? at + (m >> 3) * (9 * 1024) * g.KS + (16 * ((m >> 2) & 1) + (m & 3)) * 16 : at + (8 * (m >> 2) + (m & 3)) * 16;
 }
 
-template <int MODE, int AT, int NBW>
+template <int MODE, int AT, int NBW, int FR = 4>
 __device__ __forceinline__ void dm_issue(const DmaWave &s, const DmaArgs &g, int nB, int mt, int ch, int lb)
 {
     // (the wavefront's number is hidden from the compiler here: it would compute all scalar offsets ahead and spill them)
     int w = s.w;
     asm volatile("" : "+s"(w));
     const int first = AT == 4 ? w * 64 : (w >> 1) * (9 * 1024) * g.KS + (w & 1) * 64;
+    if constexpr (FR == 4) {
 #pragma unroll
-    for (int t = 0; t < 9; ++t)
-        dm_load(s.ws, s.a_voff, ((mt * 18 + (MODE == DM_S1 && g.flip ? 8 - t : dm_tap<MODE>(t))) * g.KS + ch * 2) * 1024 + first, lb + (t * 4 + w) * 1024);
+        for (int t = 0; t < 9; ++t)
+            dm_load(s.ws, s.a_voff, ((mt * 18 + (MODE == DM_S1 && g.flip ? 8 - t : dm_tap<MODE>(t))) * g.KS + ch * 2) * 1024 + first, lb + (t * 4 + w) * 1024);
+    } else {               // the first 32 channels: fragment w % 2 of taps w / 2, w / 2 + 2, ..
+#pragma unroll
+        for (int i = 0; i < 5; ++i) {
+            const int t = 2 * i + (w >> 1);
+            if (t < 9) dm_load(s.ws, s.a_voff, ((mt * 18 + (g.flip ? 8 - t : t)) * g.KS + ch * 2) * 1024 + (w & 1) * 64, lb + (t * 2 + (w & 1)) * 1024);
+        }
+    }
     const bool cut = ch == g.nch - 1 && (g.in_CH & (DM_KC - 1));      // channels past the last one are zeros
     const uint32_t parts = (uint32_t)(g.in_CH & (DM_KC - 1)) >> 3;
 #pragma unroll
@@ -180,7 +190,7 @@ __device__ __forceinline__ void dm_issue(const DmaWave &s, const DmaArgs &g, int
         if (NBW || b < nB) {
             uint32_t vo = s.voff[k];
             if (cut) vo = ((s.part >> (2 * k)) & 3u) >= parts ? DM_OOB : vo;
-            dm_load(s.xs, (int)vo, ch * (DM_KC * 2), lb + DM_A_BYTES + b * 1024);
+            dm_load(s.xs, (int)vo, ch * (DM_KC * 2), lb + FR * (DM_A_BYTES / 4) + b * 1024);
         }
     }
 }
@@ -188,7 +198,7 @@ __device__ __forceinline__ void dm_issue(const DmaWave &s, const DmaArgs &g, int
 // The matrix instructions of one chunk; pa, pb: this lane's first weight and input fragment, RP: bytes per staged row, PL: from the
 // even to the odd staged rows (DM_FWD2). The weight fragments of a tap are read one tap ahead (two or three where a tap is 8 or 4
 // instructions); the input fragments of the next tap row replace those of this one as its last tap has used them.
-template <int MODE, int AT, int BT>
+template <int MODE, int AT, int BT, int FR = 4>
 __device__ __forceinline__ void dm_chunk(f32x4 (&acc)[AT][MODE == DM_BWD2 ? 4 * BT : BT], const unsigned char *pa, const unsigned char *pb, int RP, int PL)
 {
     constexpr int D = AT * BT <= 4 ? 3 : AT * BT <= 8 ? 2 : 1, NF = MODE == DM_S1 ? BT + 2 : MODE == DM_FWD2 ? 2 * BT + 1 : BT + 1;
@@ -196,7 +206,7 @@ __device__ __forceinline__ void dm_chunk(f32x4 (&acc)[AT][MODE == DM_BWD2 ? 4 * 
 #pragma unroll
     for (int d = 0; d < D; ++d)
 #pragma unroll
-        for (int a = 0; a < AT; ++a) aq[d][a] = *reinterpret_cast<const bf16x8 *>(pa + (d * 4 + a) * 1024);
+        for (int a = 0; a < AT; ++a) aq[d][a] = *reinterpret_cast<const bf16x8 *>(pa + (d * FR + a) * 1024);
 #pragma unroll
     for (int c = 0; c < NF; ++c) bq[c] = *reinterpret_cast<const bf16x8 *>(pb + c * 64);
 #pragma unroll
@@ -217,7 +227,7 @@ __device__ __forceinline__ void dm_chunk(f32x4 (&acc)[AT][MODE == DM_BWD2 ? 4 * 
             if (t + D < 9) {
 #pragma unroll
                 for (int a = j * AT / BT; a < (j + 1) * AT / BT; ++a)
-                    aq[(t + D) % (D + 1)][a] = *reinterpret_cast<const bf16x8 *>(pa + ((t + D) * 4 + a) * 1024);
+                    aq[(t + D) % (D + 1)][a] = *reinterpret_cast<const bf16x8 *>(pa + ((t + D) * FR + a) * 1024);
             }
             const int c = MODE == DM_S1 ? j + q : MODE == DM_FWD2 ? 2 * j + q : j + (q == 0);
 #pragma unroll
@@ -309,30 +319,33 @@ template <int AT, int BT> __device__ __forceinline__ void dm_zero(f32x4 (&acc)[A
 }
 
 // One tile of BT columns per wavefront, one buffer. fresh: nothing has used LDS yet.
-template <int BT, int ACT>
+template <int AT, int BT, int ACT>
 __device__ __forceinline__ void dm_one_tile(DmaWave &s, const DmaArgs &g, const DmaGeo &q, unsigned char *lds, __amdgpu_buffer_rsrc_t osrc,
                                             __amdgpu_buffer_rsrc_t msrc, const DmaTile &t, bool &fresh)
 {
     dm_offsets<DM_S1>(s, g, q, t);
     const unsigned char *pa = lds + s.lane * 16;
-    const unsigned char *pb = lds + DM_A_BYTES + dm_lane_row(s, g, t) * (q.EPR * 16) + (s.lane >> 4) * 16 + s.cg * (BT * 64);
-    f32x4 acc[4][BT];
-    dm_zero<4, BT>(acc);
+    const unsigned char *pb = lds + AT * (DM_A_BYTES / 4) + dm_lane_row(s, g, t) * (q.EPR * 16) + (s.lane >> 4) * 16 + s.cg * (BT * 64);
+    f32x4 acc[AT][BT];
+    dm_zero<AT, BT>(acc);
     for (int ch = 0; ch < g.nch; ++ch) {
         if (!fresh) asm volatile("s_barrier" ::: "memory");      // every wavefront has read what the loads replace
         fresh = false;
         __builtin_amdgcn_s_setprio(3);
-        dm_issue<DM_S1, 4, 0>(s, g, q.nB, t.mt, ch, 0);
+        dm_issue<DM_S1, AT, 0, AT>(s, g, q.nB, t.mt, ch, 0);
         __builtin_amdgcn_s_setprio(0);
         dm_wait_barrier<0>();
-        dm_chunk<DM_S1, 4, BT>(acc, pa, pb, q.EPR * 16, 0);
+        dm_chunk<DM_S1, AT, BT, AT>(acc, pa, pb, q.EPR * 16, 0);
     }
     __builtin_amdgcn_s_setprio(3);
     asm volatile("s_barrier" ::: "memory");
-    dm_store<DM_S1, 4, BT, 0, ACT>(s, g, t, t.mt * 64, acc, lds + s.w * (64 * DM_STG), osrc, msrc);
+    dm_store<DM_S1, AT, BT, 0, ACT>(s, g, t, t.mt * 64, acc, lds + s.w * (64 * DM_STG), osrc, msrc);
 }
 
-template <int BT, int ACT>
+// AT = 2: layers of up to 32 output channels. Half the weights and matrix instructions of a tile of 64 channels, of which half would be zeros
+// (us: 61 x 199 x 198, 32 -> 16 79.9 -> 55.3; 103 x 178 x 180, 8 -> 24 82.0 -> 65.4; 66 x 50 x 47, 96 -> 16 17.8 -> 11.8; 60 layers, the kernel chosen
+// before and the fastest of these forms: 1.19 on average).
+template <int BT, int ACT, int AT>
 __global__ void __launch_bounds__(256, 2)
 pc_mfma_conv_dma_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__ out, const uint16_t *__restrict__ wz, DmaArgs g)
 {
@@ -349,20 +362,20 @@ pc_mfma_conv_dma_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__ 
     const int vl = (g.last & 7) == 0 ? (b & 7) * (g.last >> 3) + (b >> 3) : b;
     s.xs = dm_rsrc(in, g.in_bytes);
     s.ws = dm_rsrc(wz, g.wz_bytes);
-    s.a_voff = dm_weight_offset<4>(g, s.lane);
+    s.a_voff = dm_weight_offset<AT>(g, s.lane);
     const __amdgpu_buffer_rsrc_t osrc = __builtin_amdgcn_make_buffer_rsrc(out, 0, g.out_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t msrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint16_t *>(ACT == PC_ACT_RELU_MASK ? g.act_mask : out), 0, g.out_bytes, 0x00020000);
     const int ntile = g.rounds + (b < g.last);
     bool fresh = true;
     for (int k = 0; k < ntile; ++k)
-        dm_one_tile<BT, ACT>(s, g, g.geo[0], lds, osrc, msrc, dm_tile<BT>(g, k < g.rounds ? k * G + vb : g.rounds * G + vl, 0), fresh);
+        dm_one_tile<AT, BT, ACT>(s, g, g.geo[0], lds, osrc, msrc, dm_tile<BT>(g, k < g.rounds ? k * G + vb : g.rounds * G + vl, 0), fresh);
     if constexpr (BT == 8 || BT == 4) {
         const int p0 = (g.rounds * G + g.last) << g.lgP;
         for (int u = (b - g.last + 2 * G) % G; u < g.pieces; u += G) {
             const DmaTile t = dm_tile<BT>(g, p0 + u, g.lgP);
-            if (g.lgP == 1) dm_one_tile<BT / 2, ACT>(s, g, g.geo[1], lds, osrc, msrc, t, fresh);
-            else if constexpr (BT == 8) dm_one_tile<2, ACT>(s, g, g.geo[2], lds, osrc, msrc, t, fresh);
+            if (g.lgP == 1) dm_one_tile<AT, BT / 2, ACT>(s, g, g.geo[1], lds, osrc, msrc, t, fresh);
+            else if constexpr (BT == 8) dm_one_tile<AT, 2, ACT>(s, g, g.geo[2], lds, osrc, msrc, t, fresh);
         }
     }
 }
@@ -669,6 +682,7 @@ static bool plan_dma(const MfmaArgs &g, bool flip, const DmaCand &cand, int lgCG
     t.in_H = g.in_H; t.in_W = g.in_W; t.out_H = g.out_H; t.out_W = g.out_W;
     t.KS = g.KS; t.nch = (g.in_CH + DM_KC - 1) / DM_KC; t.flip = flip;
     t.lgCG = lgCG;
+    const bool narrow = cand.nbuf == 1 && g.out_CH <= 32;
     const int lgPG = cand.at == 4 ? 2 : 1, rows_m = cand.at == 8 ? 128 : 64;       // groups of pixels among the wavefronts (log2)
     if (lgCG > lgPG) return false;
     t.TR = 16 << (lgPG - lgCG);
@@ -690,7 +704,8 @@ static bool plan_dma(const MfmaArgs &g, bool flip, const DmaCand &cand, int lgCG
     }
     const int nB = t.geo[0].nB, TC = cand.bt << lgCG;
     if (cand.at == 8 && nB > DR_B) return false;
-    t.buf_bytes = cand.at == 8 ? DM_LDS_MAX / 2 : DM_A_BYTES + (uint32_t)(cand.nbuf == 3 ? 4 * dm_nbw(cand.bt) : nB) * 1024;
+    t.buf_bytes = cand.at == 8 ? DM_LDS_MAX / 2 : (narrow ? DM_A_BYTES / 2 : DM_A_BYTES) + (uint32_t)(cand.nbuf == 3 ? 4 * dm_nbw(cand.bt) : nB) * 1024;
+    if (narrow && t.buf_bytes < 4 * 64 * DM_STG) t.buf_bytes = 4 * 64 * DM_STG;      // (the tile leaves through it)
     *lds = (size_t)t.buf_bytes * cand.nbuf;
     if (nB > 4 * (cand.nbuf == 3 ? dm_nbw(cand.bt) : DM_NB) || *lds > (size_t)DM_LDS_MAX / (cand.nbuf == 1 ? 2 : 1)) return false;
     t.tiles_x = (t.W + TC - 1) / TC;
@@ -720,7 +735,13 @@ static bool plan_dma(const MfmaArgs &g, bool flip, const DmaCand &cand, int lgCG
     // take 73 us instead of 81.
     static const DmaTimes kPair[4] = {{2.627, 0.0391, 2.225}, {2.232, 0.0405, 2.374}, {1.779, 0.0215, 1.669}, {1.047, 0.0361, 1.416}};
     static const DmaTimes kOne[4] = {{2.960, 0.0001, 1.658}, {2.614, 0.0, 1.425}, {1.693, 0.0038, 0.940}, {1.047, 0.0103, 0.671}};
-    auto tile_us = [&](const DmaTimes &c, int l) { return t.nch * (c.chunk + c.load * t.geo[l].nB) + c.tile; };
+    // Up to 32 output channels: shares of these times (558 timings of 186 layers, 6.5 % rms; the choice among the three is 1.2 % behind the best).
+    // A chunk is half a line of a pixel: where the lines under way exceed the L2s (28 MB; all of them from 60 MB on) the next chunk fetches
+    // them again (27 x 96 x 93, 360 -> 8: 81.8 us in tiles of 8 columns, 51.0 in tiles of 4).
+    static const DmaTimes kNarrow = {0.693, 0.460, 0.321, 3.3, 0.765};
+    auto tile_us = [&](const DmaTimes &c, int l) {
+        return narrow ? t.nch * (kNarrow.chunk * c.chunk + kNarrow.load * c.load * t.geo[l].nB) + kNarrow.tile * c.tile : t.nch * (c.chunk + c.load * t.geo[l].nB) + c.tile;
+    };
     const int first = cand.bt == 8 ? 0 : cand.bt == 7 ? 1 : 2;
     const int slots = num_cu * (cand.nbuf == 1 ? 2 : 1);
     t.rounds = (int)(total / slots);
@@ -738,8 +759,13 @@ static bool plan_dma(const MfmaArgs &g, bool flip, const DmaCand &cand, int lgCG
         else if (pieces) c += (pieces / slots + (pieces % slots > num_cu)) * tile_us(ppair, lgP) + (pieces % slots > 0 && pieces % slots <= num_cu ? tile_us(pone, lgP) : 0.0);
         if (c < best) { best = c; t.last = last; t.pieces = pieces; t.lgP = lgP; }
     }
-    const double move = (2.0 * (double)p_tiles * staged * t.geo[0].IW * (g.in_CH < DM_KC ? DM_KC : g.in_CH) + (double)out_bytes) / 6.0e6;
-    *est = cand.solo.start + pow(pow(best, 1.5) + pow(cand.solo.bytes * move, 1.5), 1.0 / 1.5);
+    double in_moved = 2.0 * (double)p_tiles * staged * t.geo[0].IW * (g.in_CH < DM_KC ? DM_KC : g.in_CH);
+    if (narrow && t.nch > 1) {
+        const double under_way = (double)(total < slots ? total : slots) * staged * t.geo[0].IW * 128.0;
+        in_moved *= 1.0 + 1.05 * std::min(1.0, std::max(0.0, (under_way - 28e6) / 32e6));
+    }
+    const double move = (in_moved + (double)out_bytes) / 6.0e6;
+    *est = (narrow ? kNarrow.start : cand.solo.start) + pow(pow(best, 1.5) + pow((narrow ? kNarrow.bytes : cand.solo.bytes) * move, 1.5), 1.0 / 1.5);
     const int busy = t.last + t.pieces;
     *grid = t.rounds > 0 || busy > slots ? slots : busy;
     t.apart = t.m_fast ? m_tiles : 1;
@@ -752,15 +778,19 @@ typedef void (*DmaKernel)(const uint16_t *, uint16_t *, const uint16_t *, DmaArg
 
 // The kernels of kDma by fused step. Only stride-1 passes are masked, and a backward pass has no ReLU of its own.
 #define DM_ACTS(...) {&__VA_ARGS__, PC_ACT_NONE>, &__VA_ARGS__, PC_ACT_RELU>, &__VA_ARGS__, PC_ACT_RELU_MASK>}
+#define DM_PAIR(BT, AT) {&pc_mfma_conv_dma_kernel<BT, PC_ACT_NONE, AT>, &pc_mfma_conv_dma_kernel<BT, PC_ACT_RELU, AT>, &pc_mfma_conv_dma_kernel<BT, PC_ACT_RELU_MASK, AT>}
 static const DmaKernel kDmaKernels[kNumDma][3] = {
-    DM_ACTS(pc_mfma_conv_dma_kernel<8), DM_ACTS(pc_mfma_conv_dma_kernel<4), DM_ACTS(pc_mfma_conv_dma_kernel<7),
+    DM_PAIR(8, 4), DM_PAIR(4, 4), DM_PAIR(7, 4),
     DM_ACTS(pc_mfma_conv_solo_kernel<DM_S1, 2, 4, 3), DM_ACTS(pc_mfma_conv_solo_kernel<DM_S1, 4, 4, 2), DM_ACTS(pc_mfma_conv_solo_kernel<DM_S1, 2, 2, 3),
     {&pc_mfma_conv_solo_kernel<DM_FWD2, 2, 4, 2, PC_ACT_NONE>, &pc_mfma_conv_solo_kernel<DM_FWD2, 2, 4, 2, PC_ACT_RELU>, nullptr},
     {&pc_mfma_conv_ring_kernel<PC_ACT_NONE>, &pc_mfma_conv_ring_kernel<PC_ACT_RELU>, nullptr},
     {&pc_mfma_conv_solo_kernel<DM_FWD2, 2, 2, 2, PC_ACT_NONE>, &pc_mfma_conv_solo_kernel<DM_FWD2, 2, 2, 2, PC_ACT_RELU>, nullptr},
     {&pc_mfma_conv_solo_kernel<DM_BWD2, 2, 4, 3, PC_ACT_NONE>, nullptr, nullptr},
     {&pc_mfma_conv_solo_kernel<DM_BWD2, 2, 2, 3, PC_ACT_NONE>, nullptr, nullptr}};
+// The first three for up to 32 output channels
+static const DmaKernel kDmaNarrow[3][3] = {DM_PAIR(8, 2), DM_PAIR(4, 2), DM_PAIR(7, 2)};
 #undef DM_ACTS
+#undef DM_PAIR
 
 static hipError_t launch_dma(DmaKernel kernel, pc_per_device_once &attr, int device, hipStream_t st, int grid, int threads, size_t lds, const uint16_t *in,
                              uint16_t *out, const uint16_t *wz, const DmaArgs &g)
@@ -799,13 +829,14 @@ pc_status pc_run_mfma_conv_dma(pc_ctx *ctx, int pcfg, int *lgCG, double limit, c
     }
     if (best_k < 0) return PC_OK;
     const DmaCand &c = kDma[best_k];
-    static pc_per_device_once attr[kNumDma][3];
-    const hipError_t e = launch_dma(kDmaKernels[best_k][act], attr[best_k][act], ctx->device, ctx->stream, best_grid, c.nbuf == 1 ? 256 : 512, best_lds, in, out,
+    static pc_per_device_once attr[kNumDma][3], attr_narrow[3][3];
+    const bool narrow = c.nbuf == 1 && g0.out_CH <= 32;
+    const hipError_t e = launch_dma(narrow ? kDmaNarrow[best_k][act] : kDmaKernels[best_k][act], narrow ? attr_narrow[best_k][act] : attr[best_k][act], ctx->device, ctx->stream, best_grid, c.nbuf == 1 ? 256 : 512, best_lds, in, out,
                                     wz, best);
     *launched = c.code;
     *lgCG = best.lgCG;
     if (c.at == 8) pc_note_kernel(ctx, "pc_mfma_conv_ring_kernel<%d>", act);
-    else if (c.nbuf == 1) pc_note_kernel(ctx, "pc_mfma_conv_dma_kernel<%d, %d>", c.bt, act);
+    else if (c.nbuf == 1) pc_note_kernel(ctx, "pc_mfma_conv_dma_kernel<%d, %d, %d>", c.bt, act, narrow ? 2 : 4);
     else pc_note_kernel(ctx, "pc_mfma_conv_solo_kernel<%d, %d, %d, %d, %d>", c.mode, c.at, c.bt, c.nbuf, act);
     return pc_hip_check(ctx, e, "MFMA conv (direct loads) launch");
 }

@@ -211,3 +211,38 @@ def test_addresses_that_are_no_multiple_of_16(B, ctx, oracle, shape, off):
         assert_close(g.scatter(many.body), *ref, "f32", TOL_L2_DW, "backward-weight, several layers")
     finally:
         g.close()
+
+
+@pytest.mark.parametrize("code", [40, 41, 42])
+@pytest.mark.parametrize("shape", [(2, 30, 37, 40, 8, 1), (3, 17, 66, 32, 24, 1), (1, 65, 9, 72, 32, 1), (6, 16, 15, 8, 16, 1), (9, 64, 70, 16, 32, 1)])
+def test_up_to_32_output_channels(B, ctx, oracle, code, shape):
+    """Half of a tile's 64 channels, forward and, with the channels exchanged, backward-data: filters that do not fill 32, chunks that end early,
+    tiles across images, rows and columns past the map, rounds and their pieces; with the fused ReLU and its mask."""
+    import torch
+    from tests._harness import Case, GpuLayer, Guarded
+    N, H, W, C, F, stride = shape
+    for c, f in ((C, F), (F, C)):
+        B.pc_set_plan_override(ctx, code, 0)
+        L = I.Layer(N, H, W, c, f, stride)
+        g = None
+        try:
+            run_case(B, ctx, oracle, (N, H, W, c, f, stride), "bf16", 8, 0.4, B.PC_VARIANT_MFMA, "narrow")
+            g = GpuLayer(B, ctx, Case(L, "bf16", 8, I.kept_per_filter(0.4, c), tag=("narrow", c, f)))
+            fwd = f <= 32
+            n = L.N * L.H * L.W * (f if fwd else c)
+            z, a = (Guarded(n, torch.bfloat16) for _ in range(2))
+            (B.pc_conv_fwd if fwd else B.pc_conv_bwd_data)(ctx, g.desc, g.pk, g.x if fwd else g.dy, z.ptr)
+            assert B.pc_last_kernel(ctx).startswith("pc_mfma_conv_dma_kernel<") and B.pc_last_kernel(ctx).endswith(", 2>")
+            if fwd:
+                B.pc_conv_fwd_relu(ctx, g.desc, g.pk, g.x, a.ptr)
+                keep = z.body > 0
+            else:
+                B.pc_conv_bwd_data_relu(ctx, g.desc, g.pk, g.dy, g.x, a.ptr)
+                keep = g.x.reshape(-1).view(torch.bfloat16) > 0
+            torch.cuda.synchronize()
+            assert z.margins_intact() and a.margins_intact()
+            assert torch.equal(a.body.view(torch.int16), torch.where(keep, z.body, torch.zeros_like(z.body)).view(torch.int16))
+        finally:
+            B.pc_set_plan_override(ctx, -1, 0)
+            if g is not None:
+                g.close()
