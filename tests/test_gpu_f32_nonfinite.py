@@ -99,3 +99,32 @@ def test_three_passes(B, ctx, oracle, shape):
         check(g.bwd_data(), oracle.conv_bwd_data(case.dy, Wm2, x.shape, stride), dx_mag, TOL_L2["f32"], "bwd_data, infinite weight")
     finally:
         g.close()
+
+
+@pytest.mark.parametrize("shape", [(8, 80, 78, 33, 32, 1), (12, 28, 28, 64, 128, 1), (9, 56, 57, 24, 100, 2)])
+def test_values_that_round_up_to_a_bfloat16_infinity(B, ctx, oracle, shape):
+    """3.4e38 is finite in float32 and its leading part of 8 bits is not: the sums that hold such an element are float32's all the same."""
+    N, H, W, C, F, stride = shape
+    case = Case(I.Layer(N, H, W, C, F, stride), "f32", 8, I.kept_per_filter(0.3, C), tag=("huge", shape))
+    rng = np.random.default_rng(sum(shape))
+    pid, kp, M, Wm = oracle_masks(oracle, case)
+    x, dy = case.x.copy(), (case.dy * np.float32(2.0 ** -10)).astype(np.float32)
+    flat = x.reshape(-1, C)
+    for p in [0, len(flat) - 1] + list(rng.integers(0, len(flat), size=4)):
+        flat[p, rng.integers(0, C)] = np.float32(3.4e38)
+    small = np.float32(2.0 ** -10)
+    g = GpuLayer(B, ctx, case)
+    try:
+        g.x, g.dy = to_dev(x), to_dev(dy)
+        B.pc_update_values(ctx, g.pk, to_dev((case.W * small).astype(np.float32)))
+        y_ref = oracle.conv_fwd(x, (Wm * small).astype(np.float32), stride)
+        y_mag = oracle.conv_fwd(np.abs(x), np.abs(Wm * small).astype(np.float32), stride)
+        assert np.isfinite(y_ref).all()
+        check(g.fwd(), y_ref, y_mag, TOL_L2["f32"], "fwd, huge")
+        sf, sc = oracle.compact_order(pid, kp, case.P)
+        ref = oracle.gather_compact(oracle.conv_bwd_weight(x, dy, M, stride), pid, case.lib, sf, sc)
+        mag = oracle.gather_compact(oracle.conv_bwd_weight(np.abs(x), np.abs(dy), M, stride), pid, case.lib, sf, sc)
+        assert np.isfinite(ref).all()
+        check(g.bwd_weight()[0], ref, mag, TOL_L2_DW, "bwd_weight, huge")
+    finally:
+        g.close()
