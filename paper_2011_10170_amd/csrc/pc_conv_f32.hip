@@ -3,16 +3,20 @@
 // v_mfma_f32_16x16x4_f32 / 32x32x2_f32.
 //
 // Three parts. A float32 value is the sum of three bfloat16 values (8 significant bits each, round to nearest, the remainder
-// goes on; |a1| <= 2^-8 |a0|, |a2| <= 2^-16 |a0|), and of the nine products of two such sums the six of 2^-16 and above are formed: a
-// product of two bfloat16 values is exact in float32, what is left out is 2^-26 of a product. a0 b0 is summed in one accumulator, the
-// five small ones in another, and the two are added once at the end. Error against 64 bits, root mean square relative to the
+// goes on; |a1| <= 2^-8 |a0|, |a2| <= 2^-17 |a0|), and of the nine products of two such sums the six of 2^-16 and above are formed: a
+// product of two bfloat16 values is exact in float32, what is left out is at most 2^-24 of a product and 2^-27.5 in the mean square. a0 b0 is
+// summed in one accumulator, the five small ones in another, and the two are added once at the end. Error against 64 bits, root mean square relative to the
 // result's (normal data; 89 % zero weights in brackets): 64 products 1.43e-7 with v_mfma_f32_32x32x2_f32, 0.50e-7 in parts (0.57,
 // 0.29); 1152 products 5.99e-7, 2.00e-7 (2.16, 0.81); 4608 products 11.9e-7, 4.2e-7 (4.2, 1.7): the float32 instruction rounds its sum
-// after every two products, this one after sixteen. (All six in one accumulator: 5.2e-7 for 1152, 3.9e-7 with zeros, so two.) Parts
-// below 2^-133 vanish: operands under 2^-109 lose bits that float32 would hold. Infinities and NaN come out NaN: see pc_f32_kept_taps.
+// after every two products, this one after sixteen. (All six in one accumulator: 5.2e-7 for 1152, 3.9e-7 with zeros, so two.)
+// Small operands: bfloat16 has float32's exponents but ends at 2^-133, so the last parts of an operand under 2^-109 would vanish. Every operand is
+// split times 2^16, which puts the last bit of a subnormal, 2^-149, at 2^-133 (the instruction takes subnormal operands), and the sums are
+// multiplied by 2^-32 at the end. (64 x 28 x 28, 128 -> 128 forward 79 -> 81 us, 9 x 73 x 74, 416 -> 16 backward-data 60 -> 64, weight
+// gradients up to 2 %.) Operands of 2^112 and sums of 2^96 and above overflow then.
+// What does not come out finite, infinities and NaN among the operands too, goes to pc_f32_kept_taps.
 // Six products take 192 cycles where the float32 instruction takes 512 for the same tile and depth. 64 x 28 x 28, 128 -> 128:
-// forward 132.5 -> 65.6 us, backward-data 133.2 -> 67.3 us (1.3 PFLOP/s of bfloat16 products); bound now by the splitting of
-// the weights (44 vector instructions per 12 matrix instructions) and by the barriers of the staging with two workgroups per CU.
+// forward 132.5 -> 65.6 us, backward-data 133.2 -> 67.3 us (1.3 PFLOP/s of bfloat16 products; before the scaling); bound now by the splitting of
+// the weights (52 vector instructions per 12 matrix instructions) and by the barriers of the staging with two workgroups per CU.
 //
 // The gather kernels of pc_conv_valu.hip multiply kept taps only, but every multiply-add takes an LDS word and every kept
 // kernel a chain of scalar loads: they reach 2 % of the vector rate. The zero-filled contraction runs at the matrix rate whatever the density.
@@ -112,9 +116,13 @@ __device__ __forceinline__ float pc_f32_kept_taps(const float *__restrict__ in, 
     return acc;
 }
 
-// x = s[0] + s[1] + s[2], each bfloat16 (round to nearest: the parts below have either sign), of two values per word
+// F32_SCALE * x = s[0] + s[1] + s[2], each bfloat16 (round to nearest: the parts below have either sign), of two values per word
+#define F32_SCALE 0x1p16f
+#define F32_UNSCALE 0x1p-32f         // of a product of two
 __device__ __forceinline__ void f32_split(float a, float b, uint32_t s[3])
 {
+    a *= F32_SCALE;
+    b *= F32_SCALE;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
         s[k] = pc_pack_bf16x2(a, b);
@@ -330,7 +338,7 @@ __device__ __forceinline__ void pc_f32_conv_body(const float *__restrict__ in, f
 #pragma unroll
         for (int j = 0; j < NT; ++j)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) acc[j][i] += low[j][i];
+            for (int i = 0; i < 16; ++i) acc[j][i] = WK == 1 ? (acc[j][i] + low[j][i]) * F32_UNSCALE : acc[j][i] + low[j][i];
     } else {
         // One fragment of weights per tap is in flight (a wavefront's loads retire in order: the nine cover the round trip of
         // the next chunk's pixels, which are requested in front of them); LDS reads run one tap ahead. The scheduling barriers
@@ -401,7 +409,7 @@ __device__ __forceinline__ void pc_f32_conv_body(const float *__restrict__ in, f
             const float4 u = red[(k * 4 + wk) * 64 + lane];
             s.x += u.x; s.y += u.y; s.z += u.z; s.w += u.w;
         }
-        o[0][0] = s;
+        o[0][0] = make_float4(s.x * F32_UNSCALE, s.y * F32_UNSCALE, s.z * F32_UNSCALE, s.w * F32_UNSCALE);
     } else {
 #pragma unroll
         for (int j = 0; j < NT; ++j)
@@ -1092,6 +1100,7 @@ pc_f32_wgrad_kernel(const float *__restrict__ x, const float *__restrict__ dy, F
             o.w = on ? o.z : o.w; o.z = on ? o.y : o.z; o.y = on ? o.x : o.y;
             o.x = on ? acc[t][r >> 2][r & 3] : o.x;
         }
+        o = make_float4(o.x * F32_UNSCALE, o.y * F32_UNSCALE, o.z * F32_UNSCALE, o.w * F32_UNSCALE);
         pout[info >> 9] = o;
         const float z = fmaf(o.x, 0.0f, fmaf(o.y, 0.0f, fmaf(o.z, 0.0f, o.w * 0.0f)));   // NaN when one of them is not finite
         redo |= z == z ? 0u : 1u << r;
