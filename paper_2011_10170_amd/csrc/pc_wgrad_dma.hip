@@ -735,7 +735,12 @@ bool pc_thin_wgrad_plan(const pc_conv_desc *d, int64_t nslots, int num_cu, ThinW
     if (tiles * a.tiles_c >= ((int64_t)1 << 32)) return false;
     a.n_tiles = (int)tiles;
     a.mg_tc = pc_udiv_magic(a.tiles_c); a.mg_Ho = pc_udiv_magic(a.Ho); a.mg_H1 = pc_udiv_magic(a.H + 1); a.mg_IW = pc_udiv_magic(a.IW);
-    p.ksplit = a.n_tiles < 2 * num_cu ? a.n_tiles : 2 * num_cu;      // (4 per CU: 45.2 us for 43.5, and 11.5 for 9.9 on 128 images 32 x 32)
+    // Two workgroups per CU, the blocks of 64 filters together (4 per CU: 45.2 us for 43.5, and 11.5 for 9.9 on 128 images 32 x 32), so the
+    // partial planes of any number of filters stay within 2 MiB (two per CU for each block: 32 x 224 x 224, 3 -> 128 82.8 us for 73.0; 8 x 64 x 64,
+    // 3 -> 512 15.2 for 11.7).
+    p.ksplit = 2 * num_cu / p.blocks_f;
+    if (p.ksplit > a.n_tiles) p.ksplit = a.n_tiles;
+    if (p.ksplit < 1) p.ksplit = 1;
     *out = p;
     return true;
 }

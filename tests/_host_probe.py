@@ -127,6 +127,26 @@ def alignment():
     B.pc_destroy(ctx)
 
 
+def thin_planes():
+    """The first layer's weight gradient: about two workgroups per CU however many filters there are, and partial planes within 32 MiB."""
+    ctx = B.pc_create(0, None)
+    for st in (1, 2):
+        for N, H, W in ((1, 1, 2), (3, 33, 47), (32, 224, 224)):
+            for C, F in ((3, 8), (3, 64), (4, 72), (3, 512), (4, 1024), (3, 2048), (4, 65528)):
+                if N * H * W * F >= 1 << 30:
+                    continue
+                d, pk = layer(ctx, (N, H, W, C, F, st), read=False)
+                watch("pc_thin_wgrad_kernel")
+                B.pc_conv_bwd_weight(ctx, d, pk, DEV, DEV, DEV)
+                assert B.pc_last_kernel(ctx).startswith("pc_thin_wgrad_kernel")
+                grid, blocks = seen()[1], (F + 63) // 64
+                splits = grid // blocks
+                assert splits * blocks == grid and splits >= 1 and (splits == 1 or grid <= 2 * 256), (N, H, W, C, F, st, grid)
+                assert splits == 1 or splits * F * C * 16 <= 32 << 20, (N, H, W, C, F, st, grid)
+                B.pc_packed_free(pk)
+    B.pc_destroy(ctx)
+
+
 def no_room():
     """Backward-weight where the scratch buffer cannot grow: another kernel takes the call, which succeeds and leaves no message. The entry
     point that allocates nothing goes to the kernel of the call that has room."""
