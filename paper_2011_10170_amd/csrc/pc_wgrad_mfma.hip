@@ -1193,8 +1193,11 @@ pc_status pc_mfma_bwd_weight_group(pc_ctx *ctx, int n, const pc_conv_desc *d, co
         level = *choice / 100.0;
     }
     shares(level);
-    if (dma && ctx->plan_cfg < 0 && !pc_scratch_ready(ctx, total)) {      // the other kernel needs fewer partial planes
+    if (dma && ctx->plan_cfg < 0 && !pc_scratch_ready(ctx, total)) {      // the other kernel needs fewer partial planes, of a first layer too
         dma = false;
+        thin.clear();
+        is_thin.assign(n, 0);
+        thin_total = 0;
         plan(false);
         shares(1.0);
     }

@@ -183,6 +183,32 @@ def no_room():
         B.pc_destroy(ctx)
 
 
+def no_room_first_layer():
+    """The same for first layers, alone and beside other layers: their partial planes, too, make way for the kernel that needs less."""
+    for dims in ([(8, 64, 64, 3, 512, 1)], [(8, 64, 64, 3, 512, 1), (8, 64, 64, 64, 64, 1)], [(4, 64, 64, 4, 1024, 1)], [(8, 64, 64, 64, 64, 1), (2, 33, 9, 3, 2048, 2), (5, 40, 41, 3, 64, 1)]):
+        for read in (True, False):
+            ctx = B.pc_create(0, None)
+            ls = [layer(ctx, s, read=read) for s in dims]
+            n = [DEV] * len(ls)
+
+            def call():
+                B.pc_conv_bwd_weight_batch(ctx, [d for d, _ in ls], [p for _, p in ls], n, n, [DEV + 64 * i for i in range(len(ls))])
+                return B.pc_last_kernel(ctx)
+
+            B.pc_set_plan_override(ctx, 11, 0)
+            assert "wgrad_ws" in call()
+            B.pc_set_plan_override(ctx, -1, 0)
+            for name in ("stub_malloc_fails", "stub_capturing"):
+                ct.c_int.in_dll(stub, name).value = 1
+                kernel = call()
+                assert "wgrad" in kernel and B.load().pc_last_error(ctx) == b"", (dims, kernel)
+                ct.c_int.in_dll(stub, name).value = 0
+            assert "wgrad_dma" in call() or "thin_wgrad" in B.pc_last_kernel(ctx)
+            for _, p in ls:
+                B.pc_packed_free(p)
+            B.pc_destroy(ctx)
+
+
 def kernel_code(name):
     """The override code of a forward / backward-data kernel by its symbol."""
     v = name.split("<")[1].rstrip(">").split(", ")
