@@ -810,6 +810,12 @@ static bool ws_plan(const pc_ctx *ctx, const pc_conv_desc *d, int64_t nslots, Wg
     return true;
 }
 
+// Scratch of that kernel: the partial planes, then the padded copy.
+static size_t ws_scratch(int ks, int64_t nslots, bool pad_x, int64_t xb)
+{
+    return (ks > 1 ? (sizeof(float) * 4 * (size_t)ks * (size_t)nslots + 255) / 256 * 256 : 0) + (pad_x ? (size_t)xb : 0);
+}
+
 static pc_status ws_set_lds_attr(pc_ctx *ctx)
 {
     static pc_per_device_once attr;
@@ -836,9 +842,9 @@ static pc_status pc_mfma_bwd_weight_ws(pc_ctx *ctx, const pc_conv_desc *d, const
     if (!ws_plan(ctx, d, nslots, &a, &ct, &ft, &lds, &pad_x, &xb)) return PC_OK;
     const int ks = a.ksplit;
     void *scr = nullptr;
-    const size_t part_bytes = ks > 1 ? (sizeof(float) * 4 * (size_t)ks * (size_t)nslots + 255) / 256 * 256 : 0;
+    const size_t part_bytes = ws_scratch(ks, nslots, false, 0);
     if (part_bytes || pad_x) {
-        pc_status s = pc_scratch(ctx, part_bytes + (pad_x ? (size_t)xb : 0), &scr);
+        pc_status s = pc_scratch(ctx, ws_scratch(ks, nslots, pad_x, xb), &scr);
         if (s != PC_OK) return s;
     }
     if (pad_x) {
@@ -915,11 +921,20 @@ static pc_status pc_mfma_bwd_weight_thin(pc_ctx *ctx, const pc_conv_desc *d, con
     *launched = false;
     ThinWgradPlan p;
     if (!thin_plan(ctx, d, nslots, dy, &p)) return PC_OK;
+    if (ctx->fixed_scratch) {
+        // The entry that allocates nothing refuses a layer whose 8-channel copy of x, which the wave-specialised kernel reads, exceeds its buffer with
+        // that kernel's planes (it does so on its way); what it takes goes to this kernel, whose planes always fit.
+        WgradWsArgs a;
+        int ct, ft;
+        size_t lds;
+        bool pad_x;
+        int64_t xb;
+        if (ws_plan(ctx, d, nslots, &a, &ct, &ft, &lds, &pad_x, &xb) && !pc_scratch_ready(ctx, ws_scratch(a.ksplit, nslots, pad_x, xb))) return PC_OK;
+    }
     void *scr = nullptr;
     if (p.ksplit > 1) {
-        // (the entry that allocates nothing counts the 8-channel copy of x, which the other kernel needs, against its limit: it refuses the same layers)
-        const size_t bytes = sizeof(float) * 4 * (size_t)p.ksplit * (size_t)nslots, copy = ctx->fixed_scratch ? (size_t)16 * d->N * d->H * d->W : 0;
-        if (!pc_scratch_ready(ctx, bytes + copy)) return PC_OK;
+        const size_t bytes = sizeof(float) * 4 * (size_t)p.ksplit * (size_t)nslots;
+        if (!pc_scratch_ready(ctx, bytes)) return PC_OK;
         const pc_status s = pc_scratch(ctx, bytes, &scr);
         if (s != PC_OK) return s;
     }

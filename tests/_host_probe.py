@@ -147,6 +147,27 @@ def thin_planes():
     B.pc_destroy(ctx)
 
 
+def noalloc_first_layer():
+    """The entry point that allocates nothing: the kernel of the call that does, or a refusal where the partial planes of the wave-specialised
+    kernel and the 8-channel copy of x that it reads exceed 32 MiB."""
+    ctx = B.pc_create(0, None)
+    for shape, fits in (((32, 208, 208, 3, 512, 1), True), ((40, 224, 224, 3, 64, 1), True), ((43, 224, 224, 3, 64, 1), False), ((43, 224, 224, 4, 128, 1), False),
+                        ((8, 64, 64, 3, 512, 1), True), ((32, 208, 208, 1, 2048, 2), True), ((128, 32, 32, 3, 64, 1), True)):
+        for read in (True, False):
+            d, pk = layer(ctx, shape, read=read)
+            B.pc_conv_bwd_weight(ctx, d, pk, DEV, DEV, DEV)
+            want = B.pc_last_kernel(ctx)
+            watch("wgrad", 0, 0)
+            ct.c_longlong.in_dll(stub, "stub_grid").value = 0
+            try:
+                B.pc_conv_bwd_weight_noalloc(ctx, d, pk, DEV, DEV, DEV)
+                assert fits and B.pc_last_kernel(ctx) == want and want.startswith("pc_thin_wgrad_kernel"), (shape, want, B.pc_last_kernel(ctx))
+            except B.PcError as e:
+                assert not fits and e.status == B.PC_ERR_UNSUPPORTED and seen()[1] == 0, (shape, e)
+            B.pc_packed_free(pk)
+    B.pc_destroy(ctx)
+
+
 def no_room():
     """Backward-weight where the scratch buffer cannot grow: another kernel takes the call, which succeeds and leaves no message. The entry
     point that allocates nothing goes to the kernel of the call that has room."""
