@@ -115,7 +115,7 @@ def load():
         if name not in ("pc_destroy", "pc_packed_free", "pc_status_str", "pc_last_error", "pc_last_kernel"):
             fn.restype = ct.c_int
     native = importlib.import_module("paper_2011_10170_amd._native")
-    native.bind({name: ct.cast(getattr(lib, name), vp).value for name in EXPORTS})
+    native.bind({name: ct.cast(getattr(lib, name), vp).value for name in EXPORTS}, pc_conv_desc, lambda handle: ct.cast(handle, vp).value)
     _lib, _native = lib, native
     return lib
 
