@@ -128,10 +128,14 @@ template <class E, class F> bool fill(PyObject *o, std::vector<E> &v, F one)
 {
     PyObject *s = PySequence_Fast(o, "a list is wanted");
     if (!s) return false;
-    const Py_ssize_t n = PySequence_Fast_GET_SIZE(s);
-    v.resize((size_t)n);
+    v.reserve((size_t)PySequence_Fast_GET_SIZE(s));
     bool ok = true;
-    for (Py_ssize_t i = 0; i < n && ok; ++i) v[(size_t)i] = one(PySequence_Fast_GET_ITEM(s, i), &ok);
+    for (Py_ssize_t i = 0; i < PySequence_Fast_GET_SIZE(s) && ok; ++i) {      // (an entry's code may change the caller's list)
+        PyObject *o = PySequence_Fast_GET_ITEM(s, i);
+        Py_INCREF(o);
+        v.push_back(one(o, &ok));
+        Py_DECREF(o);
+    }
     Py_DECREF(s);
     return ok;
 }

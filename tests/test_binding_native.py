@@ -130,3 +130,16 @@ def test_descriptors_are_of_their_type():
 def test_numbers_are_what_float_takes():
     t = Tensor()
     refused(lambda: B.pc_group_lasso_grad_batch(None, [t], [t], [t], [8], [8], MASKS, "1e-4", np.float32(1e-4), [t]))
+
+
+def test_a_list_that_shrinks_while_it_is_read():
+    items = []
+
+    class Shrinks:
+        def data_ptr(self):
+            items.clear()
+            return 64
+
+    items += [Shrinks() for _ in range(1000)]
+    with pytest.raises((ValueError, RuntimeError)):
+        B.pc_update_values_batch(None, [64] * 1000, items)
