@@ -669,10 +669,9 @@ extern "C" pc_status pc_conv_bwd_weight_noalloc(pc_ctx *ctx, const pc_conv_desc 
     return s;
 }
 
-extern "C" pc_status pc_conv_bwd_weight_batch(pc_ctx *ctx, int32_t n_layers, const pc_conv_desc *descs, const pc_packed *const *packs,
-                                              const void *const *x, const void *const *dy, float *const *dw)
+static pc_status bwd_weight_batch(pc_ctx *ctx, int32_t n_layers, const pc_conv_desc *descs, const pc_packed *const *packs, const void *const *x,
+                                  const void *const *dy, float *const *dw)
 {
-    if (!ctx) return PC_ERR_INVALID_ARG;
     if (n_layers < 0) return pc_fail(ctx, PC_ERR_INVALID_ARG, "pc_conv_bwd_weight_batch: n_layers %d", n_layers);
     if (n_layers == 0) return PC_OK;
     if (!descs || !packs || !x || !dy || !dw) return pc_fail(ctx, PC_ERR_INVALID_ARG, "pc_conv_bwd_weight_batch: null pointer");
@@ -700,4 +699,15 @@ extern "C" pc_status pc_conv_bwd_weight_batch(pc_ctx *ctx, int32_t n_layers, con
     }
     if (md.empty()) return PC_OK;
     return pc_mfma_bwd_weight_group(ctx, (int)md.size(), md.data(), mp.data(), mx.data(), mdy.data(), mdw.data());
+}
+
+extern "C" pc_status pc_conv_bwd_weight_batch(pc_ctx *ctx, int32_t n_layers, const pc_conv_desc *descs, const pc_packed *const *packs,
+                                              const void *const *x, const void *const *dy, float *const *dw)
+{
+    if (!ctx) return PC_ERR_INVALID_ARG;
+    try {      // (the lists of layers are std::vector's)
+        return bwd_weight_batch(ctx, n_layers, descs, packs, x, dy, dw);
+    } catch (const std::bad_alloc &) {
+        return pc_fail(ctx, PC_ERR_NOMEM, "pc_conv_bwd_weight_batch: no host memory");
+    }
 }

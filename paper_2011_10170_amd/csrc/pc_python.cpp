@@ -225,11 +225,11 @@ template <int MAIN, class... K, class Go> PyObject *call(int entry, PyObject *co
         std::tuple<K...> t;
         if (!set_all(t, a, std::index_sequence_for<K...>()) || !lengths<MAIN>(t)) return nullptr;
         int status;
-        Py_BEGIN_ALLOW_THREADS
+        Py_BEGIN_ALLOW_THREADS              // (nothing is thrown from here: the lists are made, the library's entry points return errors)
         status = std::apply(go, t);
         Py_END_ALLOW_THREADS
         return PyLong_FromLong(status);
-    } catch (const std::bad_alloc &) {      // (of the lists above: the library's entry points throw nothing)
+    } catch (const std::bad_alloc &) {      // (of the lists above)
         return PyErr_NoMemory();
     }
 }

@@ -7,7 +7,6 @@
 #include "pc_importance.h"
 
 #include <algorithm>
-#include <vector>
 
 #define TS_BLOCK 256
 
@@ -222,14 +221,14 @@ extern "C" pc_status pc_dppg_pool(pc_ctx *ctx, const uint32_t *hist, int32_t n_p
     if (n_patterns < 1 || n_patterns > PC_MAX_P)
         return pc_fail(ctx, PC_ERR_INVALID_ARG, "pc_dppg_pool: n_patterns=%d outside 1..%d", n_patterns, PC_MAX_P);
     PC_HIP(ctx, hipSetDevice(ctx->device));
-    std::vector<uint32_t> h(512);
-    PC_HIP(ctx, hipMemcpyAsync(h.data(), hist, 512 * sizeof(uint32_t), hipMemcpyDeviceToHost, ctx->stream));
+    uint32_t h[512] = {};
+    PC_HIP(ctx, hipMemcpyAsync(h, hist, sizeof(h), hipMemcpyDeviceToHost, ctx->stream));
     PC_HIP(ctx, hipStreamSynchronize(ctx->stream));
-    std::vector<int> order;
+    int order[512], found = 0;
     for (int m = 0; m < 512; ++m)
-        if (h[m]) order.push_back(m);
-    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return h[a] > h[b]; });   // stable: lower mask first
-    const int n = (int)order.size() < n_patterns ? (int)order.size() : n_patterns;
+        if (h[m]) order[found++] = m;
+    std::sort(order, order + found, [&](int a, int b) { return h[a] != h[b] ? h[a] > h[b] : a < b; });   // (allocates nothing)
+    const int n = found < n_patterns ? found : n_patterns;
     for (int i = 0; i < n; ++i) {
         lib_host[i] = (uint16_t)order[i];
         if (score_host) score_host[i] = h[order[i]];

@@ -18,6 +18,16 @@ char stub_args[8192], stub_name[256];  /* of the last launch whose kernel's name
 char stub_watch[64];
 long long stub_grid, stub_lds;
 
+/* operator new of what is loaded after this file: from the time stub_new_left is set to n > 0, the n-th call fails */
+int stub_new_left;
+extern void _ZSt17__throw_bad_allocv(void);
+void *_Znwm(size_t n)
+{
+    void *p = stub_new_left > 0 && --stub_new_left == 0 ? NULL : malloc(n ? n : 1);
+    if (!p) _ZSt17__throw_bad_allocv();
+    return p;
+}
+
 void **__hipRegisterFatBinary(const void *d) { static void *h; (void)d; return &h; }
 void __hipUnregisterFatBinary(void **h) { (void)h; }
 void __hipRegisterVar(void **h, void *v, char *hn, const char *dn, int e, size_t s, int c, int g) { (void)h; (void)v; (void)hn; (void)dn; (void)e; (void)s; (void)c; (void)g; }

@@ -168,6 +168,36 @@ def noalloc_first_layer():
     B.pc_destroy(ctx)
 
 
+def no_host_memory():
+    """No C++ exception leaves a C entry or the binding: an allocation on the host that fails, whichever it is, is an error of the call."""
+    ctx = B.pc_create(0, None)
+    ls = [layer(ctx, s) for s in [(8, 32, 32, 3, 64, 1), (8, 32, 32, 64, 64, 1), (8, 16, 16, 64, 128, 1), (8, 16, 16, 12, 20, 1)]]
+    n = [DEV] * len(ls)
+    hist = (ct.c_uint32 * 512)(*range(512))
+    left = ct.c_int.in_dll(stub, "stub_new_left")
+    for name, call in (("batch", lambda: B.pc_conv_bwd_weight_batch(ctx, [d for d, _ in ls], [p for _, p in ls], n, n, [DEV + 64 * i for i in range(len(ls))])),
+                       ("fallback", lambda: B.pc_conv_bwd_weight_batch(ctx, [d for d, _ in ls[1:]], [p for _, p in ls[1:]], n[1:], n[1:], [DEV + 64 * i for i in range(1, len(ls))])),
+                       ("one", lambda: B.pc_conv_bwd_weight(ctx, *ls[0], DEV, DEV, DEV)), ("pool", lambda: B.pc_dppg_pool(ctx, ct.addressof(hist), 8))):
+        for k in range(1, 1000):
+            left.value = k
+            try:
+                call()
+                if left.value > 0:          # fewer allocations than k
+                    left.value = 0
+                    break
+            except MemoryError:
+                left.value = 0
+            except B.PcError as e:
+                left.value = 0
+                assert e.status == B.PC_ERR_NOMEM, (name, k, e)
+        print(name, k)
+        assert k < 999 and (k > 10) == (name in ("batch", "fallback"))
+        call()
+    for _, p in ls:
+        B.pc_packed_free(p)
+    B.pc_destroy(ctx)
+
+
 def no_room():
     """Backward-weight where the scratch buffer cannot grow: another kernel takes the call, which succeeds and leaves no message. The entry
     point that allocates nothing goes to the kernel of the call that has room."""

@@ -16,11 +16,11 @@ def stub(tmp_path_factory):
         from paper_2011_10170_amd import build
         build.build()
     out = str(tmp_path_factory.mktemp("stub") / "hip_stub.so")
-    subprocess.run(["gcc", "-O1", "-Wall", "-shared", "-fPIC", "-I/opt/rocm/include", "-o", out, os.path.join(ROOT, "tests", "_hip_stub.c")], check=True)
+    subprocess.run(["gcc", "-O1", "-Wall", "-shared", "-fPIC", "-I/opt/rocm/include", "-o", out, os.path.join(ROOT, "tests", "_hip_stub.c"), "-l:libstdc++.so.6"], check=True)
     return out
 
 
-@pytest.mark.parametrize("check", ["wgrad_lds", "wgrad_lds_narrow", "thin_planes", "alignment", "noalloc_first_layer", "no_room", "no_room_first_layer", "wgrad_choice", "group_choice", "conv_choice"])
+@pytest.mark.parametrize("check", ["wgrad_lds", "wgrad_lds_narrow", "thin_planes", "alignment", "noalloc_first_layer", "no_host_memory", "no_room", "no_room_first_layer", "wgrad_choice", "group_choice", "conv_choice"])
 def test_host_side(stub, check):
     r = subprocess.run([sys.executable, "-m", "tests._host_probe", stub, check], cwd=ROOT, capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and r.stdout.endswith("ok\n"), r.stdout + r.stderr
