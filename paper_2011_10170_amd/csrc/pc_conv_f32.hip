@@ -1158,55 +1158,85 @@ pc_status pc_f32_bwd_weight(pc_ctx *ctx, const pc_conv_desc *d, const pc_packed 
     a.N = d->N; a.H = d->H; a.W = d->W; a.C = d->C; a.F = d->F; a.stride = d->stride;
     a.Ho = (d->H - 1) / d->stride + 1; a.Wo = (d->W - 1) / d->stride + 1;
     const bool thin = d->C <= 3;
-    // The tile of an arrangement of the wavefronts; false when the staging registers do not hold it.
+    // The elements of x that a tile stages, and whether the staging registers hold a tile.
+    auto staged_x = [&](int wc, int TR, int TC) {
+        return ((TR - 1) * d->stride + 3) * (((thin ? (TC + 1) / 2 * 2 : TC) - 1) * d->stride + 3) * (thin ? 1 : 4 * wc);
+    };
+    auto fits = [&](int wf, int wc, int TR, int TC) {
+        return TR * (thin ? (TC + 1) / 2 * 2 : TC) <= 256 * f32w_nd(wc, thin) / (8 * wf) && staged_x(wc, TR, TC) <= 256 * f32w_nx(thin);
+    };
+    // The tile of an arrangement of the wavefronts.
     auto tile = [&](F32WgradArgs &t, int wf, int wc, int TR, int TC) {
-        const int FD = 32 * wf, CD = thin ? 4 : 16 * wc, nd = 256 * f32w_nd(wc, thin), max_pos = nd / (FD / 4);
+        const int FD = 32 * wf, CD = thin ? 4 : 16 * wc;
         t.ft = (d->F + FD - 1) / FD;
         t.ct = thin ? 1 : (d->C + CD - 1) / CD;
         t.TR = TR; t.TC = TC; t.TCe = thin ? (TC + 1) / 2 * 2 : TC;
         t.IR = (TR - 1) * d->stride + 3; t.IW = (t.TCe - 1) * d->stride + 3;
-        t.nd = thin ? TR * t.TCe * (FD / 4) : nd;     // (three parts: zeros up to the last group of 32 pixels)
-        t.nx = t.IR * t.IW * (CD / 4);
+        t.nd = thin ? TR * t.TCe * (FD / 4) : 256 * f32w_nd(wc, false);     // (three parts: zeros up to the last group of 32 pixels)
+        t.nx = staged_x(wc, TR, TC);
         t.tiles_r = (t.Ho + TR - 1) / TR; t.tiles_c = (t.Wo + TC - 1) / TC;
-        return TR * t.TCe <= max_pos && t.nx <= 256 * f32w_nx(thin);
     };
     // Arrangement, pixel tile and splits by an estimate of the time (us): a start, the tiles of a workgroup (a wait, staging, matrix steps; two
     // workgroups share a CU from 256 up, two rounds from 512), the sums of wavefronts that share pixels and the pick of the kept taps, the
     // tensors' bytes, the partial planes. Fitted to 5700 timings of 160 layers (8 % rms): 3 % behind the fastest, the worst 20 % (the
     // first layer's: 10000 timings, 2.5 %); the widest tile that the channels fill and the pixel tile of the best throughput were 9 %
-    // behind. The partial planes stay within 16 MiB. (The choice of a layer is remembered: kernel tile, pixel tile, splits.)
+    // behind. The partial planes stay within 16 MiB. (The choice of a layer and share of kept kernels is remembered: kernel tile, pixel
+    // tile, splits. Making it takes 10 to 50 us of host time.)
     int wf = 1, wc = 1, ks = 1;
-    const int32_t key[PC_CHOICE_KEY] = {9, d->N, d->H, d->W, d->C, d->F, d->stride, (int32_t)nslots, pk->nnzk >= 0, 0};
+    const int64_t all = (int64_t)pk->v.F * pk->v.C;
+    const int share = pc_kept_share(pk);
+    const int32_t key[PC_CHOICE_KEY] = {9, d->N, d->H, d->W, d->C, d->F, d->stride, share, 0, 0};
     bool known;
     int32_t *choice = pc_choice(ctx, key, &known);
     if (!known || *choice < 0) {
-        const int64_t cap = std::max((int64_t)1, ((int64_t)1 << 20) / nslots);
-        const double kept = pk->nnzk >= 0 ? (double)nslots : 0.3 * (double)nslots;
+        const int64_t most = share ? (share * all + 31) / 32 : all;      // slots of a plane at most
+        const int64_t cap = std::max((int64_t)1, ((int64_t)1 << 20) / most);
+        const double kept = pc_kept_estimate(pk);
         const double moved = (thin ? 0.491e-6 : 0.466e-6) * 4.0 * ((double)a.N * a.H * a.W * a.C + (double)a.N * a.Ho * a.Wo * a.F), moved3 = moved * moved * moved;
-        double best = 1e30;
+        const double start = thin ? 6.65 : 5.0, plane0 = thin ? 2.2 : 3.5, plane = (thin ? 11.5e-6 : 14.1e-6) * kept;
+        int tiles_c[65];
+        for (int TC = 1; TC <= 64; ++TC) tiles_c[TC] = (a.Wo + TC - 1) / TC;
+        double best = 1e30, bound = 1e30;
         *choice = -1;
-        for (int v = 0; v < 4; ++v) {
-            const int vf = v & 1 ? 1 : 2, vc = v & 2 || thin ? 1 : 2, wk = 4 / (vf * vc);
-            if (thin && (v & 2)) continue;
-            const double end = !thin ? 0.305 : wk == 2 ? 0.39 : 1.2;
-            F32WgradArgs t = a;
-            for (int TR = 1; TR <= 64 && TR <= a.Ho; ++TR)
-                for (int TC = 1; TC <= 64 && TC <= a.Wo && tile(t, vf, vc, TR, TC); ++TC) {
-                    const int64_t nkt = (int64_t)t.N * t.tiles_r * t.tiles_c, T = (int64_t)t.ft * t.ct;
-                    const double steps = (double)((TR * t.TCe / 2 + wk - 1) / wk), staged = (t.nd + t.nx) / 256.0;
-                    const double lone = thin ? 0.514 + 0.0785 * steps : 1.661 + 0.106 * staged, pair = thin ? 0.618 + 0.0194 * staged + 0.117 * steps : 1.776 + 0.117 * staged;
-                    for (int places = 2 * ctx->num_cu; places >= ctx->num_cu / 2; places >>= 1) {
-                        const int64_t k = std::max((int64_t)1, std::min(std::min(cap, nkt), (places + T - 1) / T)), G = T * k;
-                        const double u = (double)((nkt + k - 1) / k);
-                        const double us = (thin ? 6.65 : 5.0) + (G <= ctx->num_cu ? u * lone + (thin ? end : 0.0) : (double)((G + 2 * ctx->num_cu - 1) / (2 * ctx->num_cu)) * (u * pair + 1.7 * end));
-                        const double c = cbrt(us * us * us + moved3) + (k > 1 ? (thin ? 2.2 : 3.5) + (thin ? 11.5e-6 : 14.1e-6) * (double)k * kept : 0.0);
-                        if (c < best) {
-                            best = c;
-                            *choice = (vf - 1) | (vc - 1) << 1 | TR << 2 | TC << 9 | (int32_t)k << 16;
+        // The first walk looks at the longest tile of each number of rows and leaves a bound, which most tiles of the second exceed at once.
+        for (int walk = 0; walk < 2; ++walk)
+            for (int v = 0; v < 4; ++v) {
+                const int vf = v & 1 ? 1 : 2, vc = v & 2 || thin ? 1 : 2, wk = 4 / (vf * vc);
+                if (thin && (v & 2)) continue;
+                const double end = !thin ? 0.305 : wk == 2 ? 0.39 : 1.2;
+                F32WgradArgs t = a;
+                tile(t, vf, vc, 1, 1);
+                const int64_t T = (int64_t)t.ft * t.ct;
+                int64_t splits[3];
+                for (int p = 0; p < 3; ++p) splits[p] = std::min(cap, ((2 * ctx->num_cu >> p) + T - 1) / T);
+                for (int TR = 1; TR <= 64 && TR <= a.Ho; ++TR) {
+                    const int tiles_r = (a.Ho + TR - 1) / TR;
+                    int last = 0;
+                    if (walk == 0)
+                        while (last < 64 && last < a.Wo && fits(vf, vc, TR, last + 1)) ++last;
+                    for (int TC = walk == 0 ? std::max(1, last) : 1; TC <= 64 && TC <= a.Wo && fits(vf, vc, TR, TC); ++TC) {
+                        const int TCe = thin ? (TC + 1) / 2 * 2 : TC, nd = thin ? TR * TCe * (8 * vf) : 256 * f32w_nd(vc, false);
+                        const int64_t nkt = (int64_t)a.N * tiles_r * tiles_c[TC];
+                        const double steps = (double)((TR * TCe / 2 + wk - 1) / wk), staged = (nd + staged_x(vc, TR, TC)) / 256.0;
+                        const double lone = thin ? 0.514 + 0.0785 * steps : 1.661 + 0.106 * staged, pair = thin ? 0.618 + 0.0194 * staged + 0.117 * steps : 1.776 + 0.117 * staged;
+                        // (at least one tile, and every place busy all the time, whichever the splits)
+                        if (start + std::max(std::min(lone, pair), (double)nkt * (double)T / (2.0 * ctx->num_cu) * std::min(2.0 * lone, pair)) > bound) continue;
+                        for (int p = 0; p < 3; ++p) {
+                            const int64_t k = std::max((int64_t)1, std::min(splits[p], nkt)), G = T * k;
+                            const double u = (double)((nkt + k - 1) / k);
+                            const double us = start + (G <= ctx->num_cu ? u * lone + (thin ? end : 0.0) : (double)((G + 2 * ctx->num_cu - 1) / (2 * ctx->num_cu)) * (u * pair + 1.7 * end));
+                            const double planes = k > 1 ? plane0 + plane * (double)k : 0.0;
+                            if (std::max(us, moved) + planes > bound) continue;
+                            const double c = cbrt(us * us * us + moved3) + planes;
+                            if (c < bound) bound = c;
+                            if (walk == 1 && c < best) {
+                                best = c;
+                                *choice = (vf - 1) | (vc - 1) << 1 | TR << 2 | TC << 9 | (int32_t)k << 16;
+                            }
                         }
                     }
                 }
-        }
+            }
         if (*choice < 0) return pc_fail(ctx, PC_ERR_UNSUPPORTED, "float32 bwd_weight: no pixel tile fits");
     }
     wf = 1 + (*choice & 1); wc = 1 + (*choice >> 1 & 1); ks = *choice >> 16;

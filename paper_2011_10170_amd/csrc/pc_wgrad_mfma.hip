@@ -865,11 +865,6 @@ static pc_status pc_mfma_bwd_weight_ws(pc_ctx *ctx, const pc_conv_desc *d, const
     return pc_launch_wgrad_reduce(ctx, (const float *)scr, ks, nslots, nslots, pk, dw);
 }
 
-// Slots of a partial plane that are written and read. Where the count has not been read back the planes are laid out for every kernel, but
-// 15 to 50 % are kept in earnest: with the capacity in its place the choice between the two kernels was 2.9 % behind the faster on
-// the 200 layers below, with 0.3 of it 0.7 % (5 x 69 x 71, 208 -> 232, stride 2 26 -> 18.5 us).
-static double kept_estimate(const pc_packed *pk, int64_t nslots) { return pk->nnzk >= 0 ? (double)nslots : 0.3 * (double)nslots; }
-
 // The kernel with direct loads for one layer. *launched stays false when the layer is outside what it takes.
 static pc_status pc_mfma_bwd_weight_dma(pc_ctx *ctx, const pc_conv_desc *d, const pc_packed *pk, const void *x, const void *dy,
                                         float *dw, int64_t nslots, bool *launched)
@@ -881,11 +876,11 @@ static pc_status pc_mfma_bwd_weight_dma(pc_ctx *ctx, const pc_conv_desc *d, cons
     const bool forced = ctx->plan_cfg == 44;
     int32_t *choice = nullptr;
     if (!forced) {
-        const int32_t key[PC_CHOICE_KEY] = {7, d->N, d->H, d->W, d->C, d->F, d->stride, (int32_t)nslots, pk->nnzk >= 0, 0};
+        const int32_t key[PC_CHOICE_KEY] = {7, d->N, d->H, d->W, d->C, d->F, d->stride, pc_kept_share(pk), 0, 0};
         bool known;
         choice = pc_choice(ctx, key, &known);
     }
-    if (!pc_wgrad_dma_plan_one(d, nslots, kept_estimate(pk, nslots), ctx->num_cu, !forced ? -1 : ctx->plan_split > 0 && ctx->plan_split < WD_WAVES ? ctx->plan_split : 0, choice, &p)) return PC_OK;
+    if (!pc_wgrad_dma_plan_one(d, nslots, pc_kept_estimate(pk), ctx->num_cu, !forced ? -1 : ctx->plan_split > 0 && ctx->plan_split < WD_WAVES ? ctx->plan_split : 0, choice, &p)) return PC_OK;
     const int ks = p.a.ksplit;
     WgradDmaOne g;
     memset(&g, 0, sizeof(g));
@@ -1173,7 +1168,7 @@ pc_status pc_mfma_bwd_weight_group(pc_ctx *ctx, int n, const pc_conv_desc *d, co
             std::vector<std::pair<double, int>> places(1, {0.0, 2 * ctx->num_cu}), runs;      // (time, how many)
             double planes = 0.0;
             for (const GroupItem &it : items) {
-                if (it.ksplit > 1) planes += 6e-6 * it.ksplit * kept_estimate(pk[it.l], it.nslots);
+                if (it.ksplit > 1) planes += 6e-6 * it.ksplit * pc_kept_estimate(pk[it.l]);
                 if (it.dma) runs.push_back({(it.n_ktiles + it.ksplit - 1) / it.ksplit * it.tile_us + it.end_us, it.ct * it.ft * it.ksplit});
             }
             std::sort(runs.begin(), runs.end(), [](const std::pair<double, int> &p, const std::pair<double, int> &q) { return p.first > q.first; });
@@ -1199,7 +1194,7 @@ pc_status pc_mfma_bwd_weight_group(pc_ctx *ctx, int n, const pc_conv_desc *d, co
         // (remembered for the shapes it was made for)
         uint64_t h = 1469598103934665603ull;
         for (int l = 0; l < n; ++l)
-            for (int v : {(int)d[l].N, (int)d[l].H, (int)d[l].W, (int)d[l].C, (int)d[l].F, (int)d[l].stride * 2 + (pc_direct_loads(x[l]) && pc_direct_loads(dy[l])), (int)pk[l]->nnzk})
+            for (int v : {(int)d[l].N, (int)d[l].H, (int)d[l].W, (int)d[l].C, (int)d[l].F, (int)d[l].stride * 2 + (pc_direct_loads(x[l]) && pc_direct_loads(dy[l])), pc_kept_share(pk[l])})
                 h = (h ^ (uint32_t)v) * 1099511628211ull;
         const int32_t key[PC_CHOICE_KEY] = {4, n, (int32_t)h, (int32_t)(h >> 32), d[0].N, d[0].H, d[n - 1].H, d[n - 1].F, ctx->plan_cfg, 0};
         bool hit;

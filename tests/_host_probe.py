@@ -3,6 +3,7 @@ looked at. Runs as a program of its own (the stub has to be loaded before any HI
 import ctypes as ct
 import struct
 import sys
+import time
 
 stub = ct.CDLL(sys.argv[1], ct.RTLD_GLOBAL)
 
@@ -258,6 +259,32 @@ def no_room_first_layer():
             for _, p in ls:
                 B.pc_packed_free(p)
             B.pc_destroy(ctx)
+
+
+def changing_counts():
+    """A layer whose kept count differs after every re-pack is not planned again in every call: such calls cost about what calls of one count do."""
+    ctx = B.pc_create(0, None)
+    for dtype in (B.PC_F32, B.PC_BF16):
+        for N, H, W, C, F, st in ((64, 28, 28, 128, 128, 1), (13, 33, 47, 40, 72, 1), (32, 64, 64, 3, 64, 1)):
+            d, pk = B.make_desc(N, H, W, C, F, st, dtype), B.pc_pack(ctx, DEV, DEV, DEV, F, C, LIB, dtype)
+
+            def median(counts):
+                us = []
+                for n in counts:
+                    ct.c_int.in_dll(stub, "stub_count").value = n
+                    B.pc_pack(ctx, DEV, DEV, DEV, F, C, LIB, dtype, reuse=pk)
+                    B.pc_packed_info(ctx, pk)
+                    t = time.perf_counter()
+                    B.pc_conv_bwd_weight(ctx, d, pk, DEV, DEV, DEV)
+                    us.append((time.perf_counter() - t) * 1e6)
+                return sorted(us)[len(us) // 2]
+
+            n0 = F * C * 5 // 16
+            same, new = median([n0] * 101), median([n0 - i for i in range(1, 102)])
+            print((dtype, N, H, W, C, F), "%.1f %.1f us" % (same, new))
+            assert new <= 2.0 * same + 2.0, (dtype, N, H, W, C, F, same, new)
+            B.pc_packed_free(pk)
+    B.pc_destroy(ctx)
 
 
 def kernel_code(name):
