@@ -330,24 +330,80 @@ def conv_choice():
     B.pc_destroy(ctx)
 
 
-def wgrad_choice():
-    """The kernel that a layer's weight gradient goes to against the stored timings of both (11, 44), with the count read back or not."""
+def stored(path, n_key, n_plan, words=0):
+    """{what the plan is made for: {plan: us}} of a file of stored timings; words: leading columns that are no numbers."""
     times = {}
-    for row in open("profiles/plan_timings_bf16.csv"):
+    for row in list(open(path))[1:]:
         f = row.strip().split(",")
-        if f[0].startswith("bwd_weight"):
-            times.setdefault((f[0],) + tuple(int(v) for v in f[1:7]), {})[f[7]] = float(f[8])
+        v = tuple(f[:words]) + tuple(int(x) for x in f[words:-1])
+        times.setdefault(v[:n_key], {})[v[n_key:n_key + n_plan]] = float(f[-1])
+    return times
+
+
+def compare(what, late, mean, worst, missing):
+    """late: the chosen plan's stored time over the least one of each layer, None where that plan was not timed. Bounds: what these layers
+    show, and as much again as two runs of a time differ by (2 % in the mean, 5 % of one layer)."""
+    got = [v for v in late if v is not None]
+    print(what, len(late), len(late) - len(got), sum(got) / len(got), max(got))
+    assert len(late) - len(got) <= missing * len(late) and sum(got) / len(got) < mean and max(got) < worst, what
+
+
+def wgrad_choice():
+    """A layer's weight gradient goes to the kernel with direct loads, and its arrangement of the wavefronts, pixel tile and splits are held against the
+    stored times of those and others."""
     ctx = B.pc_create(0, None)
-    for name in ("bwd_weight", "bwd_weight_unread"):
-        late = []
-        for k, us in times.items():
-            if k[0] == name:
-                d, pk = layer(ctx, k[1:], read=name == "bwd_weight")
-                B.pc_conv_bwd_weight(ctx, d, pk, DEV, DEV, DEV)
-                late.append(us["44" if "wgrad_dma" in B.pc_last_kernel(ctx) else "11"] / min(us.values()))
-                B.pc_packed_free(pk)
-        print(name, len(late), sum(late) / len(late), max(late))
-        assert len(late) >= 200 and sum(late) / len(late) < 1.01 and max(late) < 1.2
+    late = []
+    for k, us in stored("profiles/wgrad_plan_timings_bf16.csv", 6, 5).items():
+        d, pk = layer(ctx, k)
+        watch("pc_mfma_wgrad_dma_kernel", 0, 88 + 112)
+        B.pc_conv_bwd_weight(ctx, d, pk, DEV, DEV, DEV)
+        assert "wgrad_dma" in B.pc_last_kernel(ctx), k
+        a = struct.unpack("<28i", seen()[0][88:])
+        plan = (a[25], a[26], a[9], a[27], a[18])
+        late.append(us[plan] / min(us.values()) if plan in us else None)
+        B.pc_packed_free(pk)
+    compare("bwd_weight", late, 1.057, 1.24, 0.05)      # 1.037, 1.19
+    B.pc_destroy(ctx)
+
+
+def f32_wgrad_choice():
+    """The same for float32 layers, those with few input channels by themselves."""
+    ctx = B.pc_create(0, None)
+    late = {}
+    for k, us in stored("profiles/wgrad_plan_timings_f32.csv", 6, 5).items():
+        N, H, W, C, F, st = k
+        pk = B.pc_pack(ctx, DEV, DEV, DEV, F, C, LIB, B.PC_F32)
+        ct.c_int.in_dll(stub, "stub_count").value = F * I.kept_per_filter(0.3, C)
+        B.pc_packed_info(ctx, pk)
+        watch("pc_f32_wgrad_kernel", 2, 17 * 4)
+        B.pc_conv_bwd_weight(ctx, B.make_desc(N, H, W, C, F, st, B.PC_F32), pk, DEV, DEV, DEV)
+        a = struct.unpack("<17i", seen()[0])
+        plan = tuple(int(v) for v in B.pc_last_kernel(ctx).split("<")[1].split(",")[:2]) + (a[8], a[9], a[16])
+        late.setdefault(C <= 3, []).append(us[plan] / min(us.values()) if plan in us else None)
+        B.pc_packed_free(pk)
+    compare("bwd_weight", late[False], 1.053, 1.2, 0.05)            # 1.033, 1.15
+    compare("few channels", late[True], 1.117, 1.29, 0.05)          # 1.097, 1.24
+    B.pc_destroy(ctx)
+
+
+def f32_conv_choice():
+    """The shape and chunk length of float32 forward and backward-data passes against the stored times of all that take the layer."""
+    ctx = B.pc_create(0, None)
+    late = {}
+    times = {}
+    for row in list(open("profiles/plan_timings_f32.csv"))[1:]:
+        f = row.strip().split(",")
+        times.setdefault((f[0],) + tuple(int(v) for v in f[1:7]), {})[f[7]] = float(f[8])
+    for k, us in times.items():
+        N, H, W, C, F, st = k[1:]
+        pk = B.pc_pack(ctx, DEV, DEV, DEV, F, C, LIB, B.PC_F32)
+        watch("pc_f32_conv_kernel", 3, 12 * 4)
+        (B.pc_conv_fwd if k[0] == "fwd" else B.pc_conv_bwd_data)(ctx, B.make_desc(N, H, W, C, F, st, B.PC_F32), pk, DEV, DEV)
+        plan = "x".join(B.pc_last_kernel(ctx).split("<")[1].split(", ")[:5]) + "/%d" % struct.unpack("<12i", seen()[0])[11]
+        late.setdefault((k[0], st), []).append(us.get(plan, 1e9) / min(us.values()))
+        B.pc_packed_free(pk)
+    for k, v in late.items():                                        # 1.021 and 1.029, 1.25; stride 2 1.027 and 1.041, 1.18
+        compare(k, v, 1.049 if k[1] == 1 else 1.061, 1.3, 0.0)
     B.pc_destroy(ctx)
 
 
@@ -366,23 +422,24 @@ def network(kind, width, images, size, stages):
 
 
 def group_choice():
-    """The kernel that the weight gradients of a network go to in one call against the stored timings of both."""
+    """The weight gradients of a network in one call go to the kernel with direct loads, and the share of a workgroup (told by how many there are)
+    is held against the stored times of eight."""
+    times = {}
+    for row in list(open("profiles/group_share_timings_bf16.csv"))[1:]:
+        f = row.strip().split(",")
+        times.setdefault(tuple(f[:7]), {})[int(f[8])] = float(f[9])
     ctx = B.pc_create(0, None)
-    for part in ("fit", "check"):
-        late = []
-        for row in open("profiles/group_timings_bf16.csv"):
-            f = row.strip().split(",")
-            if f[0] != part:
-                continue
-            ls = [layer(ctx, s, read=f[7] == "yes", keep=float(f[6])) for s in network(f[1], *(int(v) for v in f[2:6]))]
-            n = [DEV] * len(ls)
-            B.pc_conv_bwd_weight_batch(ctx, [d for d, _ in ls], [p for _, p in ls], n, n, [DEV + 64 * i for i in range(len(ls))])
-            us = [float(v) for v in f[8:]]
-            late.append(us["wgrad_dma" in B.pc_last_kernel(ctx)] / min(us))
-            for _, p in ls:
-                B.pc_packed_free(p)
-        print(part, len(late), sum(late) / len(late), max(late))
-        assert len(late) >= 160 and sum(late) / len(late) < 1.01 and max(late) < 1.25
+    late = []
+    for k, us in times.items():
+        ls = [layer(ctx, s, read=k[6] == "yes", keep=float(k[5])) for s in network(k[0], *(int(v) for v in k[1:5]))]
+        n = [DEV] * len(ls)
+        watch("pc_mfma_wgrad_dma_group_kernel")
+        B.pc_conv_bwd_weight_batch(ctx, [d for d, _ in ls], [p for _, p in ls], n, n, [DEV + 64 * i for i in range(len(ls))])
+        assert "wgrad_dma_group" in B.pc_last_kernel(ctx), k
+        late.append(us[seen()[1]] / min(us.values()) if seen()[1] in us else None)
+        for _, p in ls:
+            B.pc_packed_free(p)
+    compare("group", late, 1.044, 1.29, 0.05)           # 1.024, 1.24
     B.pc_destroy(ctx)
 
 
