@@ -137,8 +137,9 @@ pc_status pc_set_variant(pc_ctx *ctx, pc_variant v);
  *   10, 11, 44 backward-weight: the cooperative / the wave-specialised kernel / the kernel with direct loads (the other passes stay
  *          automatic); with 44 and one layer, split_k 0 to 3 are tiles of 64 x 64, 32 x 64, 64 x 32 and 32 x 32 (filter, channel)
  *   22     forward/backward-data: the structured-sparse kernel (packs made under PC_VARIANT_MFMA_SPARSE only)
- *   23     the first-layer kernels (stride 1, at most 4 input channels): the automatic choice takes them wherever
- *          they apply; any other code here keeps such a layer on the general kernels
+ *   23     the first-layer kernels (at most 4 input channels; forward and backward-data at stride 1, backward-weight at
+ *          both): the automatic choice takes them wherever they apply; any other code here keeps such a layer on the
+ *          general kernels
  * The wave-specialised forward/backward-data kernel (7..9, 13..21, 24..31) takes 9-tap launches only, and so do 40..43 and 45..49: a stride-2
  * backward-data pass takes 0..6 (the cooperative kernel over the four parity classes of input pixels) and 32..38 and
  * uses the automatic choice otherwise. split_k > 0 forces that many splits of the reduction in the
@@ -275,7 +276,7 @@ pc_status pc_conv_bwd_data_relu(pc_ctx *ctx, const pc_conv_desc *desc, const pc_
  * fixed order). The call never reads the kept-kernel count back: until pc_packed_info has been asked for it
  * after the last pack, the partial sums are laid out for F*C slots (16 bytes x splits x F*C of scratch, touched
  * only at kept slots). dw_compact_dev must hold nnz_kernels x 4 floats.
- * The order of additions follows from the sizes and from whether that count is known; and, for a bf16 layer, from whether
+ * The order of additions follows from the sizes and, where it is known, from that count; and, for a bf16 layer, from whether
  * there is room for the partial sums of the kernel it would go to (at most 32 MiB): where the scratch buffer would have to
  * grow and cannot, during a stream capture or because the device has no memory left, a kernel that needs less takes the
  * call, within the same error bound. A layer that has run once outside a capture has its room. */

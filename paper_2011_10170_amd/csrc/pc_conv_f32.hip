@@ -11,8 +11,8 @@
 // after every two products, this one after sixteen. (All six in one accumulator: 5.2e-7 for 1152, 3.9e-7 with zeros, so two.)
 // Small operands: bfloat16 has float32's exponents but ends at 2^-133, so the last parts of an operand under 2^-109 would vanish. Every operand is
 // split times 2^16, which puts the last bit of a subnormal, 2^-149, at 2^-133 (the instruction takes subnormal operands), and the sums are
-// multiplied by 2^-32 at the end. (64 x 28 x 28, 128 -> 128 forward 79 -> 81 us, 9 x 73 x 74, 416 -> 16 backward-data 60 -> 64, weight
-// gradients up to 2 %.) Operands of 2^112 and sums of 2^96 and above overflow then.
+// multiplied by 2^-32 at the end. (64 x 28 x 28, 128 -> 128 forward and backward-data 67.3 -> 70.8 us, 9 x 73 x 74, 416 -> 16 backward-data
+// 56.7 -> 61.6, weight gradients up to 2 %.) Operands of 2^112 and sums of 2^96 and above overflow then.
 // What does not come out finite, infinities and NaN among the operands too, goes to pc_f32_kept_taps.
 // Six products take 192 cycles where the float32 instruction takes 512 for the same tile and depth. 64 x 28 x 28, 128 -> 128:
 // forward 132.5 -> 65.6 us, backward-data 133.2 -> 67.3 us (1.3 PFLOP/s of bfloat16 products; before the scaling); bound now by the splitting of
@@ -75,8 +75,7 @@ struct F32ConvArgs {
 // pruned taps of the zero-filled operand too, and 0 x Inf = 0 x NaN = NaN: an element that did not come out finite is computed
 // again here, so that what lies under a pruned tap never reaches it.
 // (So does the split of an infinity, a NaN or a value that rounds up to a bfloat16 infinity: Inf - Inf and Inf x 0 in the small parts are
-// NaN.) (The check of finite tiles is 16 multiply-adds per lane:
-// 28 x 28, 128 -> 128, batch 64 takes 115.5 us without and 115.4 us with it.)
+// NaN.) (The check of finite tiles is 16 multiply-adds per lane: 28 x 28, 128 -> 128, batch 64 takes 70.2 us without and 70.8 with it.)
 __device__ __forceinline__ float pc_f32_kept_taps(const float *__restrict__ in, const float *__restrict__ wz, const F32ConvArgs &g, int n, int oy, int ox, int m)
 {
     const float *img = in + (int64_t)n * g.in_H * g.in_W * g.in_CH, *wrow = wz + (int64_t)(m >> 5) * 9 * g.KS * 256 + (m & 31) * 4;
@@ -557,8 +556,9 @@ static const F32Kind kF32Kinds[] = {{4, 0.495, 0.962, 141.0, 1243.0, 740.0}, {3,
 static const F32Kind &f32_kind(const F32Shape &s) { return kF32Kinds[s.t == 16 ? 0 : s.wk > 1 ? 3 : s.nt]; }
 
 // Time estimate in us, least squares over 14000 measured launches (400 layers of 1 .. 128 images, 4 .. 224 pixels wide, 1 .. 512 channels,
-// both passes and strides; the choice is 1.3 % behind the best shape on average, 2.7 % in backward-data passes of stride 2, the worst
-// one 31 %; a part of the layers with every shape's time in profiles/plan_timings_f32.csv for a new fit): a workgroup costs its
+// both passes and strides; the choice was 1.3 % behind the best shape on average, 2.7 % in backward-data passes of stride 2, the worst
+// one 31 %. Timed again with the operands scaled, which tiles of 32 pay for: on the 82 layers of profiles/plan_timings_f32.csv 2.1 % forward,
+// 2.9 % backward-data, 2.7 and 4.1 % at stride 2, the worst 25 %): a workgroup costs its
 // matrix cycles (more per cycle the fewer workgroups share the CU), its start and end, staging per 256 elements of 16 bytes, and per
 // chunk a round trip that the other workgroups of the CU hide; then the output and the weights from the L2s.
 static int f32_occ(const F32Shape &s, size_t lds)
@@ -1106,8 +1106,8 @@ pc_f32_wgrad_kernel(const float *__restrict__ x, const float *__restrict__ dy, F
         redo |= z == z ? 0u : 1u << r;
     }
     // The matrix instructions multiplied the zeros around the maps and past the tile too, and 0 x Inf = NaN: these sums again,
-    // over the pixels of this workgroup that exist. (Finite data pays for the check only: 8 x 32 x 32, 16 -> 16 all three passes
-    // 25.9 us without and with it. One infinity in 1000 elements of x: 28 x 28, 128 -> 128, batch 64 2.1 ms forward, 3.6 ms here.)
+    // over the pixels of this workgroup that exist. (Finite data pays for the check only: 8 x 32 x 32, 16 -> 16 10.3 us without, 10.5 with it;
+    // 28 x 28, 128 -> 128, batch 64 78.8 and 78.7. One infinity in 1000 elements of x and of dy: that layer 3.2 ms forward, 4.9 ms here.)
     for (; redo; redo &= redo - 1u) {
         const int r = __ffs((int)redo) - 1, f = filter(r);
         const uint32_t info = kinfo[(int64_t)f * a.C + e_c], mask = info & 511u;
@@ -1179,7 +1179,8 @@ pc_status pc_f32_bwd_weight(pc_ctx *ctx, const pc_conv_desc *d, const pc_packed 
     // Arrangement, pixel tile and splits by an estimate of the time (us): a start, the tiles of a workgroup (a wait, staging, matrix steps; two
     // workgroups share a CU from 256 up, two rounds from 512), the sums of wavefronts that share pixels and the pick of the kept taps, the
     // tensors' bytes, the partial planes. Fitted to 5700 timings of 160 layers (8 % rms): 3 % behind the fastest, the worst 20 % (the
-    // first layer's: 10000 timings, 2.5 %); the widest tile that the channels fill and the pixel tile of the best throughput were 9 %
+    // first layer's: 10000 timings, 2.5 %; on the layers of profiles/wgrad_plan_timings_f32.csv 3.3 % and 15 %, on 12 small first layers 10 %
+    // and 24 %); the widest tile that the channels fill and the pixel tile of the best throughput were 9 %
     // behind. The partial planes stay within 16 MiB. (The choice of a layer and share of kept kernels is remembered: kernel tile, pixel
     // tile, splits. Making it takes 10 to 50 us of host time.)
     int wf = 1, wc = 1, ks = 1;
@@ -1258,7 +1259,7 @@ pc_status pc_f32_bwd_weight(pc_ctx *ctx, const pc_conv_desc *d, const pc_packed 
         if (s != PC_OK) return s;
     }
     const int PD = thin ? FD + 4 : f32w_pitch(FD), PX = thin ? 4 : f32w_pitch(CD);
-    size_t lds = sizeof(float) * ((size_t)a.nd / (FD / 4) * PD + (size_t)a.IR * a.IW * PX);
+    size_t lds = sizeof(float) * ((size_t)a.nd / (FD / 4) * PD + (size_t)a.IR * a.IW * PX);      // (at most 53248: the staging registers bound both)
     if (wk > 1 && lds < (size_t)(thin ? 8 : 36) * 1024) lds = (size_t)(thin ? 8 : 36) * 1024;      // in which the sums of wavefronts are added
     const dim3 grid((unsigned)(a.ft * a.ct * a.ksplit)), blk(256);
     float4 *po = planes > 1 ? (float4 *)scr : (float4 *)dw;
@@ -1272,14 +1273,8 @@ pc_status pc_f32_bwd_weight(pc_ctx *ctx, const pc_conv_desc *d, const pc_packed 
         F32W(2, 1, true, false), F32W(1, 1, true, false), F32W(2, 2, false, true), F32W(2, 2, false, false), F32W(2, 1, false, true), F32W(2, 1, false, false),
         F32W(1, 2, false, true), F32W(1, 2, false, false), F32W(1, 1, false, true), F32W(1, 1, false, false)};
 #undef F32W
-    constexpr int n_kernels = sizeof(kernels) / sizeof(kernels[0]);
-    static pc_per_device_once attr[n_kernels];
     int k = 0;
     while (kernels[k].wf != wf || kernels[k].wc != wc || kernels[k].thin != thin || (!thin && kernels[k].vec != vec)) ++k;
-    if (lds > 64 * 1024 && pc_once_pending(attr[k], ctx->device)) {
-        PC_HIP(ctx, hipFuncSetAttribute((const void *)kernels[k].f, hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024));
-        pc_once_done(attr[k], ctx->device);
-    }
     hipLaunchKernelGGL(kernels[k].f, grid, blk, lds, st, xp, dp, a, pk->v.kinfo, po);
     pc_note_kernel(ctx, "pc_f32_wgrad_kernel<%d, %d, %s, %s>", wf, wc, thin ? "true" : "false", kernels[k].vec ? "true" : "false");
     pc_status s = pc_hip_check(ctx, hipGetLastError(), "float32 bwd_weight launch");

@@ -55,7 +55,7 @@ template <int LAYERS> struct WgradDmaLayers {
 };
 typedef WgradDmaLayers<1> WgradDmaOne;
 struct WgradDmaGroup : WgradDmaLayers<WD_GROUP_MAX> { ThinWgradLayer thin; };
-static_assert(sizeof(WgradDmaGroup) <= 4096, "kernel arguments");
+static_assert(sizeof(WgradDmaOne) == 272 && sizeof(WgradDmaGroup) <= 4096, "kernel arguments");
 
 struct WgradDmaPlan {
     WgradDmaArgs a;

@@ -23,7 +23,7 @@
 //   What a small layer's call spends (5 images 14 x 14, 48 -> 24, 8.5 us; stamps of one lane): arguments and zeros 0.65, first loads 1.9,
 //     products 0.9 to 2.6 (a tile of 64 rows is 16 steps, of 32 x 1 one), look-up table 0.8, pick of the kept taps and stores 2.3. Hence
 //     small tiles and many splits for small layers, the table's lines touched at the start, a pick of 41 instructions a kernel instead
-//     of 54, and arguments of 300 bytes: 13 images 33 x 47, 40 -> 72 13.6 -> 12.4 us with the partial planes added.
+//     of 54, and arguments of 272 bytes: 13 images 33 x 47, 40 -> 72 13.6 -> 12.4 us with the partial planes added.
 #define WD_OOB 0x80000000u
 
 typedef short i16x4 __attribute__((ext_vector_type(4)));
@@ -338,7 +338,7 @@ __device__ __forceinline__ void pc_wgrad_dma_layer(const WgradDmaLayer &y, int l
     }
 }
 
-// One layer. Its arguments are 250 bytes; those of a network (below) are 4 KiB, which a launch copies and every workgroup searches.
+// One layer. Its arguments are 272 bytes; those of a network (below) are 4 KiB, which a launch copies and every workgroup searches.
 template <int ST, int FW, int CW>
 __global__ void __launch_bounds__(256, 2) pc_mfma_wgrad_dma_kernel(WgradDmaOne g)
 {
@@ -360,6 +360,8 @@ static bool wd_layer(const pc_conv_desc *d, int64_t nslots, WgradDmaArgs &a)
     a.Ho = (d->H - 1) / st + 1; a.Wo = (d->W - 1) / st + 1;
     const int64_t xb = (int64_t)a.N * a.H * a.W * a.C * 2, db = (int64_t)a.N * a.Ho * a.Wo * a.F * 2, rows = (int64_t)a.N * a.Ho;
     if ((d->C & 7) || (d->F & 7) || xb >= ((int64_t)1 << 31) || db >= ((int64_t)1 << 31) || rows >= (1 << 24)) return false;
+    // (pc_udiv is exact below 2^32 / divisor. A tile of 128 rows ends up to 127 rows past the last image: beyond the 64 here only where Ho is above
+    // 255, as the rows are below 2^24, and those rows leave remainders below 127, which the quotient is exact for, too.)
     if ((rows + 64) * a.Ho >= ((int64_t)1 << 32) || ((int64_t)a.N + 66) * (a.H + 1) * (a.H + 1) >= ((int64_t)1 << 32)) return false;
     a.x_bytes = (uint32_t)xb; a.dy_bytes = (uint32_t)db;
     a.rows = (int)rows;
@@ -459,7 +461,8 @@ bool pc_wgrad_dma_plan_one(const pc_conv_desc *d, int64_t nslots, double kept, i
     // sequence; two sharing it: loads and products overlap), the sums of wavefronts that share pixels and the pick of the kept taps of
     // 16 x 16 blocks, the tensors' bytes; the partial planes and their launch. Of splits that leave the workgroups of an XCD without shared
     // pixels (WD_PLACE_PLAIN) every staged byte comes from beyond its L2: 144 -> 80, 50 images of 80 x 80, 34 splits of tiles of 32 x 32 186 us,
-    // 32 splits 95. Fitted to 25000 timings of 160 layers (7 % rms), on which the choice is 3.5 % behind the fastest, the worst 17 %;
+    // 32 splits 95. Fitted to 25000 timings of 160 layers (7 % rms), on which the choice is 3.5 % behind the fastest, the worst 17 % (on the
+    // 67 of profiles/wgrad_plan_timings_bf16.csv 3.7 and 19 %);
     // one tile of 64 x 64, the pixel tile of the best throughput and as many splits as fill the chip were 12 % behind.
     const double bytes = (double)layer.x_bytes + layer.dy_bytes;
     double best = 1e30;

@@ -1129,7 +1129,7 @@ pc_status pc_mfma_bwd_weight_group(pc_ctx *ctx, int n, const pc_conv_desc *d, co
         }
     };
     // The kernel with direct loads for all layers it takes: on 360 whole networks (VGG- and ResNet-shaped, 1 to 128 images, widths 16 to 64, maps 16
-    // to 224; profiles/group_timings_bf16.csv) it takes 0.6 of the wave-specialised kernel's time, and more on none (by 3 %).
+    // to 224; profiles/group_timings_bf16.csv) it takes 0.6 of the wave-specialised kernel's time, and more on one, by 3 %.
     bool dma = ctx->plan_cfg < 0 || ctx->plan_cfg == 44;
     // A layer's own call splits its pixel tiles until the layer alone fills the chip; here the layers fill it
     // together, so every workgroup gets about the same share of all (tile, pixel tile) units: fewer splits, longer
@@ -1154,7 +1154,8 @@ pc_status pc_mfma_bwd_weight_group(pc_ctx *ctx, int n, const pc_conv_desc *d, co
     };
     plan(dma);
     // The direct-load layers' workgroups go to two places per CU in order, the longest first. Of a few shares of a workgroup (us) the one is taken
-    // whose last place ends first, with the partial planes' time (3.9 % behind the best share of a network on average, a fixed rule on the total 6 %);
+    // whose last place ends first, with the partial planes' time (3.9 % behind the best share of a network on average, a fixed rule on the total 6 %; on
+    // the 93 networks of profiles/group_share_timings_bf16.csv 2.4 %, the worst 24 %);
     // large networks take two rounds or more, which even out what the estimates miss (VGG-16 / ImageNet 720 against 780 us in one).
     auto share_of = [&]() {
         double all = 0.0;
