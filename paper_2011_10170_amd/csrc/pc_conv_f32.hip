@@ -15,7 +15,8 @@
 // 56.7 -> 61.6, weight gradients up to 2 %.) Operands of 2^112 and sums of 2^96 and above overflow then.
 // What does not come out finite, infinities and NaN among the operands too, goes to pc_f32_kept_taps.
 // Six products take 192 cycles where the float32 instruction takes 512 for the same tile and depth. 64 x 28 x 28, 128 -> 128:
-// forward 132.5 -> 65.6 us, backward-data 133.2 -> 67.3 us (1.3 PFLOP/s of bfloat16 products; before the scaling); bound now by the splitting of
+// forward 132.5 -> 65.6 us, backward-data 133.2 -> 67.3 us (1.3 PFLOP/s of bfloat16 products), 70.8 with the scaling (matrix cores busy
+// 58 % of the time, 64 % without it); bound now by the splitting of
 // the weights (52 vector instructions per 12 matrix instructions) and by the barriers of the staging with two workgroups per CU.
 //
 // The gather kernels of pc_conv_valu.hip multiply kept taps only, but every multiply-add takes an LDS word and every kept
@@ -776,7 +777,7 @@ pc_status pc_f32_bwd_data(pc_ctx *ctx, const pc_conv_desc *d, const pc_packed *p
 // pixels, and their sums are added in LDS (halves of the tile at a time, a wavefront keeps 8 / WK of its kernels). Pixel tiles are
 // split over the workgroups (two per CU); every split writes the kept taps in compact slot order, pc_wgrad_reduce adds the planes in a
 // fixed order. 64 x 28 x 28, 128 -> 128, with the sum of the planes: 151 -> 80 us (32 x 32 tiles of v_mfma_f32_32x32x2_f32 before); matrix
-// cores busy 53 % of the time, the LDS 40 %. A third wavefront per SIMD would need 168 registers, this takes 195.
+// cores busy 54 % of the time, the LDS 40 %. A third wavefront per SIMD would need 168 registers, this takes 195.
 // THIN (at most 3 channels): the 9 * C (tap, channel) pairs are the columns of one tile of float32 instructions, one instead of 9.
 // 16-byte elements of dy and of x staged per thread and pixel tile (three parts: 32 pixels of dy per wavefront that shares them)
 __host__ __device__ constexpr int f32w_nd(int wc, bool thin) { return thin || wc == 2 ? 2 : 4; }
