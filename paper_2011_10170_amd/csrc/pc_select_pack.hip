@@ -61,7 +61,7 @@ pc_select_score_kernel(const float *__restrict__ W, const float *__restrict__ G,
 // rem-th largest of them joins the prefix. As soon as all keys of that digit are kept the rest of the key does not
 // matter; otherwise, after the last digit, the keys equal to the threshold are kept by index. Counts are integers: the
 // result does not depend on the order of the atomics.
-#define PC_TOPN_WG 16384        // longest layer ranked by one workgroup (25600 kernels: 21 us against 16 across workgroups, 65536: 31, 17)
+#define PC_TOPN_WG 16384        // longest layer ranked by one workgroup (16384 kernels: 9.9 us; 16640 by the binned ranking 10.7)
 __device__ __forceinline__ uint32_t pc_order_key(float f)
 {
     const uint32_t b = __float_as_uint(f);
@@ -523,6 +523,176 @@ pc_topn_write_kernel(const float *__restrict__ R, int64_t L, int64_t chunk, int 
     }
 }
 
+// Layers of PC_TOPN_WG + 1 .. PC_TOPN_BINNED kernels ranked as a whole, two launches. The scoring launch leaves, for every 1024 kernels
+// ("row"), the keys grouped by bin (sign, exponent and first bit of the mantissa, largest first) and where each bin begins. A workgroup of
+// the second launch adds up the rows' bin starts, which names the bin of the threshold, and walks that bin's keys of all rows, a tenth of
+// the layer, itself; then it flags its own row. So nothing is handed from one workgroup to another but through the end of a launch, and no
+// histogram has to be cleared. What bounds both is latency: the walk is a chain of bin starts, keys and two counting passes in LDS.
+// Selection of 256 x 256 kernels: 17.3 us with the three counting launches and the writing one above, each waiting for the one before,
+// 11.8 here; 130 x 128 16.3, 10.7; with four times the rows (320 x 320) 18.5, 19.9: there the walk outlasts the launches it saves.
+#define PC_TOPN_BINNED 65536
+#define PC_BIN_ROW 1024
+#define PC_BINS 512
+#define PC_BIN_PITCH 520        // starts of a row's bins: PC_BINS + 1, a multiple of 8
+// Bin of a key, 0 for the largest: the upper 10 bits of positive scores; the last bin holds every other key too.
+__device__ __forceinline__ int pc_key_bin(uint32_t key)
+{
+    const uint32_t top = key >> 22;
+    return 1023 - (int)(top < 512u ? 512u : top);
+}
+
+__global__ void __launch_bounds__(PC_BIN_ROW)
+pc_select_bins_kernel(const float *__restrict__ W, const float *__restrict__ G, int nk, LibArg la, int score_mode,
+                      uint8_t *__restrict__ pid, uint32_t *__restrict__ R, uint32_t *__restrict__ K, uint16_t *__restrict__ start)
+{
+    __shared__ __align__(16) float s[16][64 * 9];
+    __shared__ int cnt[PC_BINS], part[PC_BINS / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, row0 = (int)blockIdx.x * PC_BIN_ROW, k0 = row0 + wave * 64;
+    const int n = nk - k0 < 64 ? nk - k0 : 64;  // kernels of this wavefront, none where negative
+    PcImpRegs r;
+    if (n > 0) pc_imp_issue(W, G, k0, n, r);
+    if (tid < PC_BINS) cnt[tid] = 0;
+    __syncthreads();
+    uint32_t key = 0u;
+    int rank = 0;
+    if (n > 0) {
+        pc_imp_put(r, G != nullptr, n, s[wave]);
+        if (lane < n) {
+            int best;
+            float sc;
+            pc_score_taps(s[wave] + lane * 9, la, score_mode, &best, &sc);
+            key = pc_order_key(sc);
+            pid[k0 + lane] = (uint8_t)best;
+            R[k0 + lane] = key;
+            rank = atomicAdd(&cnt[pc_key_bin(key)], 1);   // the order inside a bin does not matter: it is counted only
+        }
+    }
+    __syncthreads();
+    int incl = 0, mine = 0;
+    if (tid < PC_BINS) {
+        incl = mine = cnt[tid];
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int t = __shfl_up(incl, off);
+            if (lane >= off) incl += t;
+        }
+        if (lane == 63) part[wave] = incl;
+    }
+    __syncthreads();
+    if (tid < PC_BINS) {
+        int first = incl - mine;
+#pragma unroll
+        for (int w = 0; w < PC_BINS / 64; ++w) first += w < wave ? part[w] : 0;
+        cnt[tid] = first;
+        uint16_t *to = start + (int64_t)blockIdx.x * PC_BIN_PITCH;
+        to[tid] = (uint16_t)first;
+        if (tid == PC_BINS - 1) to[PC_BINS] = (uint16_t)(first + mine);
+    }
+    __syncthreads();
+    if (lane < n) K[row0 + cnt[pc_key_bin(key)] + rank] = key;
+}
+
+// The first 128 keys of a row's bin stay in registers; what follows is read in every pass.
+__global__ void __launch_bounds__(PC_BIN_ROW)
+pc_topn_bins_kernel(const uint32_t *__restrict__ R, const uint32_t *__restrict__ K, const uint16_t *__restrict__ start, int nk, int n_keep,
+                    uint8_t *__restrict__ keep)
+{
+    constexpr int NR = PC_TOPN_BINNED / PC_BIN_ROW / 16;   // rows a wavefront walks, at most
+    __shared__ int cum[PC_BINS + 1];            // keys of the layer in the bins before
+    __shared__ uint32_t hist[2048];
+    __shared__ int part[16], dig[3], s_bin, s_base;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int rows = (int)gridDim.x, own = (int)blockIdx.x * PC_BIN_ROW + tid;
+    const uint32_t mykey = R[own < nk ? own : nk - 1];
+    if (tid <= PC_BINS) cum[tid] = 0;
+    hist[tid] = 0u;
+    hist[tid + 1024] = 0u;
+    __syncthreads();
+    {
+        const int col = tid & 255;
+        const uint32_t *src = reinterpret_cast<const uint32_t *>(start) + col;
+        int lo = 0, hi = 0;
+#pragma unroll 8
+        for (int r = tid >> 8; r < rows; r += 4) {
+            const uint32_t u = src[r * (PC_BIN_PITCH / 2)];
+            lo += (int)(u & 0xFFFFu);
+            hi += (int)(u >> 16);
+        }
+        atomicAdd(&cum[2 * col], lo);           // integers: order-free
+        atomicAdd(&cum[2 * col + 1], hi);
+        if (tid == 0) cum[PC_BINS] = nk;
+    }
+    __syncthreads();
+    if (tid < PC_BINS && cum[tid] < n_keep && n_keep <= cum[tid + 1]) s_bin = tid;   // exactly one thread: 0 < n_keep < nk
+    __syncthreads();
+    const int bin = s_bin, mybin = pc_key_bin(mykey);
+    int rem = n_keep - cum[bin];
+    if (rem == cum[bin + 1] - cum[bin]) {       // the whole bin is kept
+        if (own < nk) keep[own] = mybin <= bin ? 1 : 0;
+        return;
+    }
+    // the bin's keys of rows wave, wave + 16, ...: lane i holds the bounds of the i-th
+    int b0 = 0, b1 = 0;
+    if (lane < NR && wave + 16 * lane < rows) {
+        const uint16_t *at = start + (wave + 16 * lane) * PC_BIN_PITCH + bin;
+        b0 = at[0];
+        b1 = at[1];
+    }
+    uint32_t q[NR][2];
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+        const int f = __builtin_amdgcn_readlane(b0, i), n = __builtin_amdgcn_readlane(b1, i) - f, row = wave + 16 * i < rows ? wave + 16 * i : 0;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) q[i][j] = K[row * PC_BIN_ROW + (j * 64 + lane < n ? f + j * 64 + lane : 0)];
+    }
+    auto walk = [&](auto &&use) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+            const int f = __builtin_amdgcn_readlane(b0, i), n = __builtin_amdgcn_readlane(b1, i) - f;
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                if (j * 64 + lane < n) use(q[i][j], i);
+            for (int j = 128 + lane; j < n; j += 64) use(K[(wave + 16 * i) * PC_BIN_ROW + f + j], i);
+        }
+    };
+    // digits of up to 11 bits of the keys of the bin: 22 bits are open, 32 in the last bin
+    uint32_t prefix = bin == PC_BINS - 1 ? 0u : (uint32_t)(1023 - bin) << 22;
+    int shift = bin == PC_BINS - 1 ? 32 : 22;
+    bool all;
+    for (;;) {
+        const int width = shift < 11 ? shift : 11;
+        const uint32_t himask = shift == 32 ? 0u : 0xFFFFFFFFu << shift;
+        shift -= width;
+        walk([&](uint32_t k, int) __attribute__((always_inline)) {
+            if ((k & himask) == prefix) atomicAdd(&hist[(k >> shift) & ((1u << width) - 1u)], 1u);
+        });
+        __syncthreads();
+        const uint32_t h[2] = {hist[2 * tid], hist[2 * tid + 1]};
+        pc_topn_digit<1024, 2>(h, rem, part, dig);
+        prefix |= (uint32_t)dig[0] << shift;
+        rem -= dig[1];
+        all = dig[2] == rem;
+        if (all || shift == 0) break;
+        hist[tid] = 0u;                         // read before the barrier that ended pc_topn_digit
+        hist[tid + 1024] = 0u;
+        __syncthreads();
+    }
+    if (all) {                                  // (keys below the bin are below its prefix, keys above it above)
+        if (own < nk) keep[own] = (mykey & (0xFFFFFFFFu << shift)) >= prefix ? 1 : 0;
+        return;
+    }
+    // of the keys equal to the threshold the first rem by index
+    if (tid == 0) s_base = 0;
+    __syncthreads();
+    int before = 0;
+    walk([&](uint32_t k, int i) __attribute__((always_inline)) { before += k == prefix && wave + 16 * i < (int)blockIdx.x; });
+    if (before) atomicAdd(&s_base, before);
+    const bool eq = own < nk && mykey == prefix;
+    int total;
+    const int rank = pc_block_rank(eq, part, 16, &total);   // (its barriers come after the additions)
+    if (own < nk) keep[own] = mykey > prefix || (eq && s_base + rank < rem) ? 1 : 0;
+}
+
 __global__ void __launch_bounds__(256) pc_fill_u8_kernel(uint8_t *__restrict__ p, int64_t n, uint8_t v)
 {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -575,6 +745,19 @@ static pc_status pc_launch_select_segments(pc_ctx *ctx, const float *W, const fl
     chunk = chunk < 1024 ? 1024 : (chunk + 255) / 256 * 256;
     const unsigned nchunks = (unsigned)((L + chunk - 1) / chunk);
     const size_t r_bytes = (sizeof(float) * (size_t)nk + 255) / 256 * 256;
+    const unsigned bin_rows = (unsigned)((nk + PC_BIN_ROW - 1) / PC_BIN_ROW);
+    const size_t bin_bytes = r_bytes + (size_t)bin_rows * (PC_BIN_ROW * sizeof(uint32_t) + PC_BIN_PITCH * sizeof(uint16_t));
+    // (a capture whose scratch holds the counting passes below only takes these)
+    if (across && L <= PC_TOPN_BINNED && pc_scratch_ready(ctx, bin_bytes)) {
+        void *scr = nullptr;
+        const pc_status s = pc_scratch(ctx, bin_bytes, &scr);
+        if (s != PC_OK) return s;
+        uint32_t *R = (uint32_t *)scr, *K = reinterpret_cast<uint32_t *>(static_cast<unsigned char *>(scr) + r_bytes);
+        uint16_t *start = reinterpret_cast<uint16_t *>(K + (size_t)bin_rows * PC_BIN_ROW);
+        hipLaunchKernelGGL(pc_select_bins_kernel, dim3(bin_rows), dim3(PC_BIN_ROW), 0, ctx->stream, W, G, (int)nk, la, (int)sm, pid, R, K, start);
+        hipLaunchKernelGGL(pc_topn_bins_kernel, dim3(bin_rows), dim3(PC_BIN_ROW), 0, ctx->stream, R, K, start, (int)nk, (int)n_keep, keep);
+        return pc_hip_check(ctx, hipGetLastError(), "select launch");
+    }
     const int nzero = across ? 3 * PC_TOPN_BINS : 0;
     void *scr = nullptr;
     pc_status s = pc_scratch(ctx, r_bytes + (across ? sizeof(uint32_t) * ((size_t)nzero + 1024 * (size_t)nchunks) : 0), &scr);
@@ -660,7 +843,7 @@ pc_status pc_launch_select(pc_ctx *ctx, const float *W, const float *G, int F, i
 // Table rows are filters (row stride C, element stride 1 in the [F][C] maps) for the
 // filter-major table, channels (row stride 1, element stride C) for the channel-major one.
 //
-// A pack is two launches. The first counts the kept kernels of every table row per pattern id and, for the
+// A pack of a small layer is one launch (pc_pack_one_kernel). Others are two. The first counts the kept kernels of every table row per pattern id and, for the
 // matrix-core variant, writes the operand tiles (they depend on W and the masks only). The second places the
 // kernels: every workgroup adds up the totals of the rows before its own, so no separate scan is needed.
 
@@ -1198,6 +1381,103 @@ template <int KIND> __global__ void __launch_bounds__(256) pc_pack_place_batch_k
         pc_pack_place_row<KIND>(b.W[l], b.pid[l], b.keep[l], v.F, v.C, (int64_t)v.C, (int64_t)1, la, b.bf16[l], v, row);
 }
 
+// A pack of the matrix-core kernels in one launch: the first F workgroups place a row each, the rest write the operand tiles. A row of
+// up to 512 kernels is ranked at once, so its pattern groups are known without a counting launch, and the kept kernels before it are
+// counted from the masks themselves, 16 at a time, by every workgroup again (128 KiB of each mask at most, from L2).
+// Bound by latency: 256 x 256 8.5 us in two launches, 5.9 in one; 256 x 512 9.3, 7.8; 400 x 400 10.1, 9.8; 512 x 512 10.7, 13.5.
+#define PC_PACK_ONE 131072
+__device__ __forceinline__ int pc_count_kept(uint32_t keep, uint32_t pid, uint32_t ge)
+{
+    const uint32_t kept = ((keep & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | keep, past = ((pid & 0x7F7F7F7Fu) + ge) | pid;   // bit 7 of every byte
+    return __popc(kept & ~past & 0x80808080u);
+}
+
+__device__ __forceinline__ void pc_pack_place_counted(const uint8_t *__restrict__ pid, const uint8_t *__restrict__ keep, const LibArg &la,
+                                                      const PackView &v, int row)
+{
+    __shared__ int start[128], wcnt[4][128], red[4];
+    __shared__ uint16_t lmask[128];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int P = la.P, C = v.C, idbits = P > 1 ? 32 - __builtin_clz(P - 1) : 0;
+    int code[2], rank[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int e = (wave * 2 + j) * 64 + lane, k = row * C + (e < C ? e : C - 1);
+        const int kp = keep[k], pd = pid[k];
+        code[j] = e < C && kp && pd < P ? pd : 255;
+    }
+    if (tid < P) lmask[tid] = la.mask[tid];
+    const int before = row * C, whole = before >> 4;
+    const uint32_t ge = (uint32_t)(128 - P) * 0x01010101u;
+    int part = 0;
+#pragma unroll 4
+    for (int i = tid; i < whole; i += 256) {
+        const uint4 k = reinterpret_cast<const uint4 *>(keep)[i], p = reinterpret_cast<const uint4 *>(pid)[i];
+        part += pc_count_kept(k.x, p.x, ge) + pc_count_kept(k.y, p.y, ge) + pc_count_kept(k.z, p.z, ge) + pc_count_kept(k.w, p.w, ge);
+    }
+    if (16 * whole + tid < before) part += keep[16 * whole + tid] && pid[16 * whole + tid] < P;
+    wcnt[wave][lane] = 0;
+    wcnt[wave][lane + 64] = 0;
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        unsigned long long same = __ballot(code[j] != 255);   // lanes of the same pattern, bit by bit of its id
+        for (int bit = 0; bit < idbits; ++bit) {
+            const bool on = (code[j] >> bit) & 1;
+            const unsigned long long b = __ballot(on);
+            same &= on ? b : ~b;
+        }
+        rank[j] = (int)__popcll(same & ((1ull << lane) - 1ull));
+        const int ahead = code[j] != 255 ? wcnt[wave][code[j]] : 0;
+        const bool first = rank[j] == 0;
+        rank[j] += ahead;
+        __builtin_amdgcn_wave_barrier();
+        if (code[j] != 255 && first) wcnt[wave][code[j]] = ahead + (int)__popcll(same);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+    for (int off = 32; off > 0; off >>= 1) part += __shfl_down(part, off);
+    if (lane == 0) red[wave] = part;
+    __syncthreads();
+    const int base = (red[0] + red[1]) + (red[2] + red[3]);
+    if (wave == 0) {
+        const int n0 = (wcnt[0][lane] + wcnt[1][lane]) + (wcnt[2][lane] + wcnt[3][lane]);
+        const int n1 = (wcnt[0][lane + 64] + wcnt[1][lane + 64]) + (wcnt[2][lane + 64] + wcnt[3][lane + 64]);
+        int s0 = n0, s1 = n1;                    // inclusive sums over the patterns
+        for (int off = 1; off < 64; off <<= 1) {
+            const int t0 = __shfl_up(s0, off), t1 = __shfl_up(s1, off);
+            if (lane >= off) { s0 += t0; s1 += t1; }
+        }
+        const int half = __shfl(s0, 63), end = base + half + __shfl(s1, 63);
+        start[lane] = s0 - n0;
+        start[lane + 64] = half + s1 - n1;
+        if (lane == 0) {
+            v.fm_rowptr[row] = base;
+            if (row == v.F - 1) v.fm_rowptr[v.F] = end;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int e = (wave * 2 + j) * 64 + lane;
+        if (e >= C) continue;
+        const bool kept = code[j] != 255;
+        const int c = kept ? code[j] : 0;
+        int slot = base + start[c] + rank[j];
+        for (int w = 0; w < wave; ++w) slot += wcnt[w][c];
+        v.kinfo[row * C + e] = kept ? ((uint32_t)slot << 9) | lmask[c] : 0xFFFFFFFFu;
+    }
+}
+
+__global__ void __launch_bounds__(256)
+pc_pack_one_kernel(const float *__restrict__ W, const uint8_t *__restrict__ pid, const uint8_t *__restrict__ keep, LibArg la, PackView v,
+                   int tiles_c)
+{
+    const int b = (int)blockIdx.x;
+    if (b < v.F) pc_pack_place_counted(pid, keep, la, v, b);
+    else pc_pack_tile_block<false>(W, pid, keep, la, v, (b - v.F) / tiles_c, (b - v.F) % tiles_c);
+}
+
 // Re-gathers values with unchanged tables (one thread per kernel (f,c)).
 __global__ void __launch_bounds__(256)
 pc_pack_regather_fm_kernel(const float *__restrict__ W, LibArg la, int bf16, PackView v)
@@ -1254,6 +1534,11 @@ pc_status pc_launch_pack(pc_ctx *ctx, pc_packed *pk, const float *W, const uint8
     // the channel-major table serves the gather kernels' backward-data pass (the matrix-core kernels read operand tiles)
     const int nfm = pc_pack_row_wgs(v.F), ncm = mfma ? 0 : pc_pack_row_wgs(v.C);
     const int tiles_c = v.Cp / 32, ntiles = mfma ? (v.Fp / 32) * tiles_c : 0;
+    if (mfma && v.C <= 512 && (int64_t)v.F * v.C <= PC_PACK_ONE && (((uintptr_t)pid | (uintptr_t)keep) & 15) == 0) {
+        hipLaunchKernelGGL(pc_pack_one_kernel, dim3((unsigned)(v.F + ntiles)), dim3(256), 0, st, W, pid, keep, la, v, tiles_c);
+        pc_launch_ovf_merge(ctx, v);
+        return pc_hip_check(ctx, hipGetLastError(), "pack launch");
+    }
     hipLaunchKernelGGL(pc_pack_stage1_kernel, dim3((unsigned)(nfm + ncm + ntiles)), dim3(256), 0, st, W, pid, keep, la, v, ncm,
                        tiles_c);
     if (mfma) {
