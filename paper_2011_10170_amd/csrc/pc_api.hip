@@ -313,7 +313,7 @@ extern "C" pc_status pc_pattern_select_batch(pc_ctx *ctx, int32_t n_layers, cons
 static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // Carves the slab. With base == nullptr only the size is computed. The gather tables (about 47 bytes per kernel) are there in
-// every pack and the operand tiles wherever the shape allows them (bf16 36, float32 72 bytes): a handle may be re-packed
+// every pack and the operand tiles wherever the shape allows them (bf16 36, float32 72 bytes, 108 more with the parts): a handle may be re-packed
 // under another forced variant, which must not allocate.
 static size_t carve(PackView *v, PackView **v_dev, char *base, int F, int C, bool mfma, bool sparse, bool f32)
 {
@@ -355,6 +355,9 @@ static size_t carve(PackView *v, PackView **v_dev, char *base, int F, int C, boo
     } else {
         v->wz_fwd = v->wz_bwd = nullptr;
     }
+    const size_t parts = mfma && f32 && cap <= PC_F32_PARTS ? sizeof(uint16_t) * 3 : 0;
+    v->w3_fwd = parts ? (uint16_t *)take(parts * 9 * (size_t)v->Fp * v->Ck) : nullptr;
+    v->w3_bwd = parts ? (uint16_t *)take(parts * 9 * (size_t)v->Cp * v->Fk) : nullptr;
     if (mfma && sparse) {
         v->ws_fwd_val = (uint16_t *)take(sizeof(uint16_t) * 9 * (size_t)v->Fp * v->Ck);
         v->ws_bwd_val = (uint16_t *)take(sizeof(uint16_t) * 9 * (size_t)v->Cp * v->Fk);

@@ -15,16 +15,19 @@
 // 56.7 -> 61.6, weight gradients up to 2 %.) Operands of 2^112 and sums of 2^96 and above overflow then.
 // What does not come out finite, infinities and NaN among the operands too, goes to pc_f32_kept_taps.
 // Six products take 192 cycles where the float32 instruction takes 512 for the same tile and depth. 64 x 28 x 28, 128 -> 128:
-// forward 132.5 -> 65.6 us, backward-data 133.2 -> 67.3 us (1.3 PFLOP/s of bfloat16 products), 70.8 with the scaling (matrix cores busy
-// 58 % of the time, 64 % without it); bound now by the splitting of
-// the weights (52 vector instructions per 12 matrix instructions) and by the barriers of the staging with two workgroups per CU.
+// forward 132.5 -> 65.6 us, backward-data 133.2 -> 67.3 us (1.3 PFLOP/s of bfloat16 products), 69.0 and 71.9 with the scaling. A wavefront that split its weights itself
+// spent 52 vector instructions per 12 matrix instructions on it, and matrix and vector instructions hardly overlap here (busy 58 and 54 % of the
+// time, sum 1.12): layers of up to PC_F32_PARTS kernels have their weights split when they are packed, 61.6 and 64.9 us (matrix cores busy 69 %;
+// 7.5 -> 3.0 vector instructions per matrix instruction; 16 x 14 x 14, 256 -> 256 31 -> 24 us). Bound now by the barriers of the staging with two
+// workgroups per CU and by the split of the pixels. (Tiles of 16 over split weights, with 16x16x32_bf16: 0.6 % on 215 layers, not kept.)
 //
 // The gather kernels of pc_conv_valu.hip multiply kept taps only, but every multiply-add takes an LDS word and every kept
 // kernel a chain of scalar loads: they reach 2 % of the vector rate. The zero-filled contraction runs at the matrix rate whatever the density.
 //
 // Operand layout: of 32x32x2_f32, lane l holds row (A) / column (B) l % 32 and k = l / 32; of 32x32x16_bf16, the same row and k = 8 (l / 32)
-// .. + 7; accumulator register r of lane l is row 8*(r/4) + 4*(l/32) + r%4, column l % 32. The packed operand holds fragments of 8
-// reduction entries: 64 pieces of 16 bytes, piece l the entries 4 (l / 32) .. + 3 of row l % 32 (so a lane's eight entries are two pieces).
+// .. + 7; accumulator register r of lane l is row 8*(r/4) + 4*(l/32) + r%4, column l % 32. The packed float32 operand holds fragments of 8
+// reduction entries: 64 pieces of 16 bytes, piece l the entries 4 (l / 32) .. + 3 of row l % 32; the one in three parts fragments of 16: per
+// part 64 pieces of 16 bytes, piece l the lane's eight entries.
 //
 // The float32 matrix instructions occupy the vector units: a vector instruction of any wavefront of the SIMD adds its four
 // cycles to the kernel's time (measured: taking out the loads, the LDS writes and the LDS reads of the weight-gradient loop
@@ -70,6 +73,7 @@ struct F32ConvArgs {
     const float *act_mask;
     const uint32_t *kinfo;            // pattern masks of the kernels
     F32Class cls[4];
+    const uint16_t *w3;               // the weights in three parts, or none
 };
 
 // Output channel m of output pixel (oy, ox) of image n, over kept taps inside the map only. The matrix instructions multiply the
@@ -116,39 +120,7 @@ __device__ __forceinline__ float pc_f32_kept_taps(const float *__restrict__ in, 
     return acc;
 }
 
-// F32_SCALE * x = s[0] + s[1] + s[2], each bfloat16 (round to nearest: the parts below have either sign), of two values per word
-#define F32_SCALE 0x1p16f
-#define F32_UNSCALE 0x1p-32f         // of a product of two
-__device__ __forceinline__ void f32_split(float a, float b, uint32_t s[3])
-{
-    a *= F32_SCALE;
-    b *= F32_SCALE;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        s[k] = pc_pack_bf16x2(a, b);
-        a -= __uint_as_float(s[k] << 16);
-        b -= __uint_as_float(s[k] & 0xFFFF0000u);
-    }
-}
-
-struct F32Parts { bf16x8 p[3]; };   // eight values in three parts
-__device__ __forceinline__ F32Parts f32_split8(const float4 &u, const float4 &v)
-{
-    uint32_t s[4][3];
-    f32_split(u.x, u.y, s[0]);
-    f32_split(u.z, u.w, s[1]);
-    f32_split(v.x, v.y, s[2]);
-    f32_split(v.z, v.w, s[3]);
-    F32Parts r;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const v4u32 w = {s[0][k], s[1][k], s[2][k], s[3][k]};
-        __builtin_memcpy(&r.p[k], &w, 16);
-    }
-    return r;
-}
-
-template <int T, int NTAPS, int WM, int WN, int WK, int NT, bool VEC>
+template <int T, int NTAPS, int WM, int WN, int WK, int NT, bool VEC, bool PARTS>
 __device__ __forceinline__ void pc_f32_conv_body(const float *__restrict__ in, float *__restrict__ out, const float *__restrict__ wz,
                                                  const F32ConvArgs &g, const F32Class &c, int rows, int mt, int strip, int p0,
                                                  unsigned char *lds)
@@ -242,26 +214,11 @@ __device__ __forceinline__ void pc_f32_conv_body(const float *__restrict__ in, f
             }
     };
 
-    // weight fragments: [row tile][tap][fragment][64 lanes][4], a row tile past the last reads the last (not stored)
-    // (tiles of 16 rows: lane l holds row l % 16 and entries 4 * (l / 16) .. + 3 of 16, two fragments of the 32-row operand;
-    // where the second one does not exist its lanes read zeros)
+    // a row tile past the last reads the last (not stored)
     int rt = mt * WM + wm;
     const int rt_last = (g.out_CH - 1) / T;
     if (rt > rt_last) rt = rt_last;
-    const __amdgpu_buffer_rsrc_t wsrc = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<float *>(wz + (int64_t)(T == 32 ? rt : rt >> 1) * 9 * g.KS * 256), 0, 9 * g.KS * 1024, 0x00020000);
     const int KSF = (g.KS + 1) >> 1;
-    const uint32_t wvo = T == 32 ? (lane >> 5) * 1024u + (lane & 31) * 16u : (lane >> 5) * 1024u + ((rt & 1) * 16 + (lane & 15) + (lane & 16) * 2) * 16u;
-    const uint32_t wvo_last = !(g.KS & 1) || lane < 32 ? wvo : OOB;
-    auto a_load = [&](int tap, int kf, int half) -> float4 {
-        const int tw = NTAPS == 9 ? tap : c.tap_w[tap & 3];
-        const int k = kf < KSF - 1 ? kf : KSF - 1;
-        const uint32_t vo = (kf < KSF - 1 ? wvo : wvo_last) + half * 512u;
-        const v4u32 u = __builtin_amdgcn_raw_buffer_load_b128(wsrc, (int)vo, (tw * g.KS + k * 2) * 1024, 0);
-        float4 r;
-        __builtin_memcpy(&r, &u, 16);
-        return r;
-    };
     auto tap_off = [&](int tap) -> int { return NTAPS == 9 ? c.o0 + tap / 3 * c.dr + tap % 3 * c.ds : c.tap_off[tap & 3]; };
     issue(0);
     const int KF = g.KC / FR;
@@ -284,21 +241,41 @@ __device__ __forceinline__ void pc_f32_conv_body(const float *__restrict__ in, f
         int to[HT];
 #pragma unroll
         for (int i = 0; i < HT; ++i) to[i] = tap_off(tap(i));
-        float4 ar[PD][2];
+        // PARTS: weights split at pack time. HT >= 4: a tap's registers are loaded again as soon as its matrix instructions have read them;
+        // fewer taps come through registers of their own, for the lead of a whole tap. Else: weights split here, the registers of
+        // a tap are free once its parts are made.
+        const __amdgpu_buffer_rsrc_t wsrc = PARTS ?
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(g.w3 + (int64_t)rt * 9 * KSF * 1536), 0, 9 * KSF * 3072, 0x00020000) :
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(wz + (int64_t)rt * 9 * KSF * 512), 0, 9 * KSF * 2048, 0x00020000);
+        struct Whole { float4 h[2]; };
+        typedef typename std::conditional<PARTS, F32Parts, Whole>::type Weights;
+        auto a_load = [&](int tap, int kf) -> Weights {
+            constexpr int NB = (int)sizeof(Weights) / 16;
+            const int tw = NTAPS == 9 ? tap : c.tap_w[tap & 3], at = (tw * KSF + (kf < KSF ? kf : KSF - 1)) * NB * 1024;
+            v4u32 u[NB];
 #pragma unroll
-        for (int i = 0; i < PD; ++i) {
-            ar[i][0] = a_load(tap(i), wf, 0);
-            ar[i][1] = a_load(tap(i), wf, 1);
-        }
-        F32Parts ap[RB], bq[RB][NT];
+            for (int k = 0; k < NB; ++k)
+                u[k] = __builtin_amdgcn_raw_buffer_load_b128(wsrc, PARTS ? lane * 16 + k * 1024 : (lane >> 5) * 1024 + (lane & 31) * 16 + k * 512, at, 0);
+            Weights r;
+            __builtin_memcpy(&r, u, sizeof(r));
+            return r;
+        };
+        auto parts = [&](const Weights &w) -> F32Parts {
+            if constexpr (PARTS) return w;
+            else return f32_split8(w.h[0], w.h[1]);
+        };
+        constexpr bool IN_PLACE = PARTS && HT >= 4;
+        Weights ar[PD];
+        F32Parts cur, bq[RB][NT];
+#pragma unroll
+        for (int i = 0; i < PD; ++i) ar[i] = a_load(tap(i), wf);
         auto b_load = [&](F32Parts *b, int i, int f) {
 #pragma unroll
             for (int j = 0; j < NT; ++j)
 #pragma unroll
                 for (int k = 0; k < 3; ++k) b[j].p[k] = *reinterpret_cast<const bf16x8 *>(bp[j] + f * 96 + to[i] + k * 32);
         };
-        auto a_split = [&](int i) -> F32Parts { return f32_split8(ar[i][0], ar[i][1]); };
-        ap[0] = a_split(0);
+        if (!IN_PLACE) cur = parts(ar[0]);
         for (int ch = 0; ch < g.nchunk; ++ch) {
             if (ch) __syncthreads();
             __builtin_amdgcn_s_setprio(0);        // a wavefront that multiplies goes first (4 x 71 x 74, 96 -> 96: 25.2 -> 24.6 us)
@@ -315,21 +292,22 @@ __device__ __forceinline__ void pc_f32_conv_body(const float *__restrict__ in, f
 #pragma unroll
                 for (int i = 0; i < HT; ++i) {
                     if (RB > 1) b_load(bq[(i + 1) % RB], i + 1 < HT ? i + 1 : 0, i + 1 < HT ? f : fn);
-                    const int slot = i % PD;           // (its weights are split: the registers are free)
-                    ar[slot][0] = a_load(tap((i + PD) % HT), i + PD < HT ? kc : kn, 0);
-                    ar[slot][1] = a_load(tap((i + PD) % HT), i + PD < HT ? kc : kn, 1);
+                    if (!IN_PLACE) ar[i % PD] = a_load(tap((i + PD) % HT), i + PD < HT ? kc : kn);
                     __builtin_amdgcn_sched_barrier(0);
                     if (WK == 1 || i < nt) {
+                        const F32Parts *ap = &cur;
+                        if constexpr (IN_PLACE) ap = &ar[i % PD];
 #pragma unroll
                         for (int m = 0; m < 6; ++m)
 #pragma unroll
                             for (int j = 0; j < NT; ++j) {
                                 constexpr int PA[6] = {0, 0, 1, 1, 0, 2}, PB[6] = {0, 1, 0, 1, 2, 0};
                                 f32x16 &s = m == 0 ? acc[j] : low[j];
-                                s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ap[i % RB].p[PA[m]], bq[i % RB][j].p[PB[m]], s, 0, 0, 0);
+                                s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ap->p[PA[m]], bq[i % RB][j].p[PB[m]], s, 0, 0, 0);
                             }
                     }
-                    ap[(i + 1) % RB] = a_split((i + 1) % PD);
+                    if (!IN_PLACE) cur = parts(ar[(i + 1) % PD]);
+                    else ar[i % PD] = a_load(tap((i + PD) % HT), i + PD < HT ? kc : kn);
                     __builtin_amdgcn_sched_barrier(0);
                     if (RB == 1) b_load(bq[0], 0, fn);
                 }
@@ -343,10 +321,24 @@ __device__ __forceinline__ void pc_f32_conv_body(const float *__restrict__ in, f
         // One fragment of weights per tap is in flight (a wavefront's loads retire in order: the nine cover the round trip of
         // the next chunk's pixels, which are requested in front of them); LDS reads run one tap ahead. The scheduling barriers
         // keep the loads ahead of the matrix instructions they are to overlap.
+        // weights: [row tile of 32][tap][fragment][64 lanes][4]; lane l holds row l % 16 and entries 4 * (l / 16) .. + 3 of 16, two fragments
+        // of the 32-row operand; where the second one does not exist its lanes read zeros
+        const __amdgpu_buffer_rsrc_t wsrc = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<float *>(wz + (int64_t)(rt >> 1) * 9 * g.KS * 256), 0, 9 * g.KS * 1024, 0x00020000);
+        const uint32_t wvo = (lane >> 5) * 1024u + ((rt & 1) * 16 + (lane & 15) + (lane & 16) * 2) * 16u;
+        const uint32_t wvo_last = !(g.KS & 1) || lane < 32 ? wvo : OOB;
+        auto a_load = [&](int tap, int kf) -> float4 {
+            const int tw = NTAPS == 9 ? tap : c.tap_w[tap & 3];
+            const int k = kf < KSF - 1 ? kf : KSF - 1;
+            const v4u32 u = __builtin_amdgcn_raw_buffer_load_b128(wsrc, (int)(kf < KSF - 1 ? wvo : wvo_last), (tw * g.KS + k * 2) * 1024, 0);
+            float4 r;
+            __builtin_memcpy(&r, &u, 16);
+            return r;
+        };
         auto mma = [&](float a, float bv) { acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, bv, acc[0], 0, 0, 0); };
         float4 ar[NTAPS];
 #pragma unroll
-        for (int t = 0; t < NTAPS; ++t) ar[t] = a_load(t, wk, 0);
+        for (int t = 0; t < NTAPS; ++t) ar[t] = a_load(t, wk);
         constexpr int RB = NTAPS % 3 == 0 ? 3 : NTAPS % 2 == 0 ? 2 : 1;   // the pixel fragments rotate without copies from one fragment to the next
         float4 bq[RB];
         const unsigned char *bt[NTAPS];
@@ -373,7 +365,7 @@ __device__ __forceinline__ void pc_f32_conv_body(const float *__restrict__ in, f
                     mma(a.z, bv.z);
                     mma(a.w, bv.w);
                     __builtin_amdgcn_sched_barrier(0);
-                    ar[t] = a_load(t, kn, 0);     // behind its last use: the register is free
+                    ar[t] = a_load(t, kn);     // behind its last use: the register is free
                     if (RB == 1) bq[0] = *reinterpret_cast<const float4 *>(bt[0] + fn * FR * 4);
                 }
             }
@@ -469,7 +461,7 @@ __device__ __forceinline__ void pc_f32_conv_body(const float *__restrict__ in, f
 }
 
 // MC: the four parity classes of a stride-2 backward-data pass (4, 2, 2 and 1 taps), each a range of workgroups.
-template <int T, int WM, int WN, int WK, int NT, bool MC, bool VEC>
+template <int T, int WM, int WN, int WK, int NT, bool MC, bool VEC, bool PARTS>
 __global__ void __launch_bounds__(256, T == 16 ? 4 : NT == 1 ? 3 : 2)
 pc_f32_conv_kernel(const float *__restrict__ in, float *__restrict__ out, const float *__restrict__ wz, F32ConvArgs g)
 {
@@ -481,9 +473,9 @@ pc_f32_conv_kernel(const float *__restrict__ in, float *__restrict__ out, const 
         const F32Class &c = g.cls[k];
         b -= c.first;
         const int mt = b % g.m_tiles, pt = b / g.m_tiles, strip = pt / c.tiles, p0 = (pt - strip * c.tiles) * T * WN * NT;
-        if (c.ntaps == 4) pc_f32_conv_body<T, 4, WM, WN, WK, NT, VEC>(in, out, wz, g, c, c.R, mt, strip, p0, lds);
-        else if (c.ntaps == 2) pc_f32_conv_body<T, 2, WM, WN, WK, NT, VEC>(in, out, wz, g, c, c.R, mt, strip, p0, lds);
-        else pc_f32_conv_body<T, 1, WM, WN, WK, NT, VEC>(in, out, wz, g, c, c.R, mt, strip, p0, lds);
+        if (c.ntaps == 4) pc_f32_conv_body<T, 4, WM, WN, WK, NT, VEC, PARTS>(in, out, wz, g, c, c.R, mt, strip, p0, lds);
+        else if (c.ntaps == 2) pc_f32_conv_body<T, 2, WM, WN, WK, NT, VEC, PARTS>(in, out, wz, g, c, c.R, mt, strip, p0, lds);
+        else pc_f32_conv_body<T, 1, WM, WN, WK, NT, VEC, PARTS>(in, out, wz, g, c, c.R, mt, strip, p0, lds);
     } else {
         const F32Class &c = g.cls[0];
         const bool tail = T == 32 && WK == 1 && b >= g.tail_first;
@@ -499,11 +491,11 @@ pc_f32_conv_kernel(const float *__restrict__ in, float *__restrict__ out, const 
         if constexpr (T == 32 && WK == 1) {
             if (tail) {
                 if (p0 + sub / WM * 32 >= g.N * c.GH * c.Ws || (mt * WM + sub % WM) * 32 >= g.out_CH) return;
-                pc_f32_conv_body<32, 9, 1, 1, 4, 1, VEC>(in, out, wz, g, c, g.tail_R, mt * WM + sub % WM, strip, p0 + sub / WM * 32, lds);
+                pc_f32_conv_body<32, 9, 1, 1, 4, 1, VEC, PARTS>(in, out, wz, g, c, g.tail_R, mt * WM + sub % WM, strip, p0 + sub / WM * 32, lds);
                 return;
             }
         }
-        pc_f32_conv_body<T, 9, WM, WN, WK, NT, VEC>(in, out, wz, g, c, c.R, mt, strip, p0, lds);
+        pc_f32_conv_body<T, 9, WM, WN, WK, NT, VEC, PARTS>(in, out, wz, g, c, c.R, mt, strip, p0, lds);
     }
 }
 
@@ -546,47 +538,52 @@ static bool f32_plan_class(const F32ConvArgs &g, F32Class *c, int ext, int BN, i
 // fewer weights and pixels per multiply-add and win where there are enough of them.
 // Tiles of 32: nt = 2 pixel tiles per wavefront halve the splitting of the weights and their loads and win where two workgroups per CU
 // are enough of them (64 x 28 x 28, 128 -> 128 forward 75.4 -> 65.7 us), nt = 1 has three per CU.
-struct F32Shape { int t, wm, wn, wk, nt; double mma; };
-static const F32Shape kF32Shapes[] = {{32, 2, 2, 1, 2, 0.803}, {32, 4, 1, 1, 2, 0.781}, {32, 1, 4, 1, 2, 0.836},
-                                      {32, 2, 2, 1, 1, 0.901}, {32, 4, 1, 1, 1, 0.856}, {32, 1, 4, 1, 1, 0.937}, {32, 1, 1, 4, 1, 1.066},
-                                      {16, 1, 4, 1, 1, 0.733}, {16, 1, 2, 2, 1, 0.658}, {16, 1, 1, 4, 1, 0.567}};
-// The rest of the estimate, by kind: tiles of 16; of 32 with one and with two pixel tiles per wavefront; of 32 along the reduction
+struct F32Shape { int t, wm, wn, wk, nt; double mma, mma_parts; };   // mma_parts: over weights split at pack time
+static const F32Shape kF32Shapes[] = {{32, 2, 2, 1, 2, 0.803, 0.762}, {32, 4, 1, 1, 2, 0.781, 0.695}, {32, 1, 4, 1, 2, 0.836, 0.698},
+                                      {32, 2, 2, 1, 1, 0.901, 0.683}, {32, 4, 1, 1, 1, 0.856, 0.586}, {32, 1, 4, 1, 1, 0.937, 0.656},
+                                      {32, 1, 1, 4, 1, 1.066, 0.922},
+                                      {16, 1, 4, 1, 1, 0.733, 0.0}, {16, 1, 2, 2, 1, 0.658, 0.0}, {16, 1, 1, 4, 1, 0.567, 0.0}};
+// The rest of the estimate, by kind: tiles of 16; of 32 with one and with two pixel tiles per wavefront; of 32 along the reduction; and
+// those of 32 again over weights split at pack time
 struct F32Kind { int occ; double alone, part_round, stage, start, trip; };
 static const F32Kind kF32Kinds[] = {{4, 0.495, 0.962, 141.0, 1243.0, 740.0}, {3, 0.469, 0.613, 218.0, 1777.0, 1247.0},
-                                    {2, 0.928, 0.816, 218.0, 1777.0, 1247.0}, {3, 0.469, 0.476, 218.0, 1777.0, 1247.0}};
-static const F32Kind &f32_kind(const F32Shape &s) { return kF32Kinds[s.t == 16 ? 0 : s.wk > 1 ? 3 : s.nt]; }
+                                    {2, 0.928, 0.816, 218.0, 1777.0, 1247.0}, {3, 0.469, 0.476, 218.0, 1777.0, 1247.0},
+                                    {3, 0.318, 0.669, 223.0, 1866.0, 1290.0}, {2, 0.347, 0.730, 247.0, 2466.0, 1788.0},
+                                    {3, 1.361, 0.771, 190.0, 1437.0, 739.0}};
+static const F32Kind &f32_kind(const F32Shape &s, bool parts) { return kF32Kinds[s.t == 16 ? 0 : (s.wk > 1 ? 3 : s.nt) + (parts ? 3 : 0)]; }
 
 // Time estimate in us, least squares over 14000 measured launches (400 layers of 1 .. 128 images, 4 .. 224 pixels wide, 1 .. 512 channels,
 // both passes and strides; the choice was 1.3 % behind the best shape on average, 2.7 % in backward-data passes of stride 2, the worst
-// one 31 %. Timed again with the operands scaled, which tiles of 32 pay for: on the 82 layers of profiles/plan_timings_f32.csv 2.1 % forward,
-// 2.9 % backward-data, 2.7 and 4.1 % at stride 2, the worst 25 %): a workgroup costs its
+// one 31 %), and for weights split at pack time over 7500 more (494 layers and passes: 1.5 % forward, 1.3 % backward-data, 1.8 and 3.8 % at stride 2,
+// the worst 25 %; with the figures of weights split in the kernel 2.8, 2.6, 1.8, 5.0 and 34 %. profiles/plan_timings_f32.csv has 82 of the
+// layers): a workgroup costs its
 // matrix cycles (more per cycle the fewer workgroups share the CU), its start and end, staging per 256 elements of 16 bytes, and per
 // chunk a round trip that the other workgroups of the CU hide; then the output and the weights from the L2s.
 static int f32_occ(const F32Shape &s, size_t lds)
 {
-    const int occ = (int)(160 * 1024 / lds), most = f32_kind(s).occ;
+    const int occ = (int)(160 * 1024 / lds), most = f32_kind(s, false).occ;
     return occ < most ? occ : most;
 }
 
 // Cycles of one workgroup; rounds = workgroups per CU.
 static double f32_cycles(const F32Shape &s, const F32ConvArgs &t, double taps, double staged, double rounds, size_t lds)
 {
-    const F32Kind &q = f32_kind(s);
+    const F32Kind &q = f32_kind(s, t.w3);
     const int left = t.in_CH - (t.nchunk - 1) * t.KC, wf = s.t == 32 && s.wk == 4 ? 2 : s.wk;
     const int frags = (t.nchunk - 1) * (t.KC / 16 / wf) + ((left + 15) / 16 + wf - 1) / wf;
     if (s.t == 32 && s.wk == 4) taps = (taps + 1.0) / 2.0;
     const double up = ceil(rounds), occ = f32_occ(s, lds), conc = up < occ ? up : occ;
-    return taps * frags * (s.t == 32 ? 192.0 * s.nt : 128.0) * s.mma * (1.0 + q.alone / conc) + staged / 256.0 * t.nchunk * q.stage + q.start +
+    return taps * frags * (s.t == 16 ? 128.0 * s.mma : 192.0 * s.nt * (t.w3 ? s.mma_parts : s.mma)) * (1.0 + q.alone / conc) + staged / 256.0 * t.nchunk * q.stage + q.start +
            q.trip * t.nchunk / conc;
 }
 
-static double f32_rounds(const F32Shape &s, double n) { return n <= f32_kind(s).occ ? ceil(n) : n + f32_kind(s).part_round; }
+static double f32_rounds(const F32Shape &s, bool parts, double n) { return n <= f32_kind(s, parts).occ ? ceil(n) : n + f32_kind(s, parts).part_round; }
 
 static double f32_time(const pc_ctx *ctx, const F32Shape &s, const F32ConvArgs &t, int64_t blocks, double taps, double staged, size_t lds, int64_t out_bytes)
 {
     const double n = (double)blocks / ctx->num_cu;
-    const double wbytes = (double)blocks * s.t * s.wm * taps * ((t.in_CH + 7) / 8 * 32);
-    return 3.6 + f32_rounds(s, n) * f32_cycles(s, t, taps, staged, n, lds) / 2350.0 + (double)out_bytes / 5.5e6 + wbytes / 90e6;
+    const double wbytes = (double)blocks * s.t * s.wm * taps * ((t.in_CH + 7) / 8 * 32) * (s.t == 32 && t.w3 ? 1.5 : 1.0);
+    return 3.6 + f32_rounds(s, t.w3, n) * f32_cycles(s, t, taps, staged, n, lds) / 2350.0 + (double)out_bytes / 5.5e6 + wbytes / 90e6;
 }
 
 // The last, partly filled round of a launch: its tiles are cut into parts of 32 x 32, one workgroup each, four wavefronts along the
@@ -598,7 +595,7 @@ static double f32_time(const pc_ctx *ctx, const F32Shape &s, const F32ConvArgs &
 // stride 2 mix short and long workgroups, so neither is cut.
 static void f32_plan_tail(const pc_ctx *ctx, const F32Shape &s, F32ConvArgs *t, int ext, int64_t *blocks, double staged, size_t *lds, double *us)
 {
-    static const F32Shape part = {32, 1, 1, 4, 1, 1.066};
+    static const F32Shape part = {32, 1, 1, 4, 1, 1.066, 0.922};
     const F32Class &c = t->cls[0];
     const int sub = s.wm * s.wn * s.nt;
     const int64_t whole = *blocks / ctx->num_cu * ctx->num_cu, rest = *blocks - whole;
@@ -606,8 +603,8 @@ static void f32_plan_tail(const pc_ctx *ctx, const F32Shape &s, F32ConvArgs *t, 
     if (whole == 0 || rest == 0 || R * c.IW * 8 > 256 * f32_ne(32, 1) || R > c.R || whole + rest * sub >= ((int64_t)1 << 31)) return;
     const size_t need = *lds < 16384 ? 16384 : *lds;   // (the parts add their four sums there)
     const double n = (double)*blocks / ctx->num_cu, k = (double)(whole / ctx->num_cu), m = (double)(rest * sub) / ctx->num_cu;
-    const double now = f32_rounds(s, n) * f32_cycles(s, *t, 9.0, staged, n, *lds);
-    const double cut = k * f32_cycles(s, *t, 9.0, staged, n, need) + f32_rounds(part, m) * f32_cycles(part, *t, 9.0, (double)R * c.IW * 8, n, need);
+    const double now = f32_rounds(s, t->w3, n) * f32_cycles(s, *t, 9.0, staged, n, *lds);
+    const double cut = k * f32_cycles(s, *t, 9.0, staged, n, need) + f32_rounds(part, t->w3, m) * f32_cycles(part, *t, 9.0, (double)R * c.IW * 8, n, need);
     if (cut >= 0.98 * now) return;
     *us -= (now - cut) / 2350.0;
     t->tail_first = (int32_t)whole;
@@ -685,12 +682,18 @@ static pc_status f32_run(pc_ctx *ctx, F32ConvArgs g, bool mc, int ext, const int
     }
     const bool vec = (g.in_CH & 3) == 0 && span * g.in_H * g.in_W * g.in_CH * 4 < ((int64_t)1 << 31);
     hipStream_t st = ctx->stream;
+    const bool parts = best.w3 != nullptr && kF32Shapes[best_k].t == 32;
+#define F32_LAUNCH_(T, WM, WN, WK, NT, PARTS)                                                                                \
+    do {                                                                                                                    \
+        if (mc && vec) hipLaunchKernelGGL((pc_f32_conv_kernel<T, WM, WN, WK, NT, true, true, PARTS>), grid, blk, lds, st, in, out, wz, best);   \
+        else if (mc) hipLaunchKernelGGL((pc_f32_conv_kernel<T, WM, WN, WK, NT, true, false, PARTS>), grid, blk, lds, st, in, out, wz, best);    \
+        else if (vec) hipLaunchKernelGGL((pc_f32_conv_kernel<T, WM, WN, WK, NT, false, true, PARTS>), grid, blk, lds, st, in, out, wz, best);   \
+        else hipLaunchKernelGGL((pc_f32_conv_kernel<T, WM, WN, WK, NT, false, false, PARTS>), grid, blk, lds, st, in, out, wz, best);           \
+    } while (0)
 #define F32_LAUNCH(T, WM, WN, WK, NT)                                                                                        \
     do {                                                                                                                    \
-        if (mc && vec) hipLaunchKernelGGL((pc_f32_conv_kernel<T, WM, WN, WK, NT, true, true>), grid, blk, lds, st, in, out, wz, best);   \
-        else if (mc) hipLaunchKernelGGL((pc_f32_conv_kernel<T, WM, WN, WK, NT, true, false>), grid, blk, lds, st, in, out, wz, best);    \
-        else if (vec) hipLaunchKernelGGL((pc_f32_conv_kernel<T, WM, WN, WK, NT, false, true>), grid, blk, lds, st, in, out, wz, best);   \
-        else hipLaunchKernelGGL((pc_f32_conv_kernel<T, WM, WN, WK, NT, false, false>), grid, blk, lds, st, in, out, wz, best);           \
+        if (T == 32 && parts) F32_LAUNCH_(T, WM, WN, WK, NT, (T == 32));                                                    \
+        else F32_LAUNCH_(T, WM, WN, WK, NT, false);                                                                         \
     } while (0)
     switch (best_k) {
     case 0: F32_LAUNCH(32, 2, 2, 1, 2); break;
@@ -705,8 +708,10 @@ static pc_status f32_run(pc_ctx *ctx, F32ConvArgs g, bool mc, int ext, const int
     default: F32_LAUNCH(16, 1, 1, 4, 1); break;
     }
 #undef F32_LAUNCH
+#undef F32_LAUNCH_
     const F32Shape &bs = kF32Shapes[best_k];
-    pc_note_kernel(ctx, "pc_f32_conv_kernel<%d, %d, %d, %d, %d, %s, %s>", bs.t, bs.wm, bs.wn, bs.wk, bs.nt, mc ? "true" : "false", vec ? "true" : "false");
+    pc_note_kernel(ctx, "pc_f32_conv_kernel<%d, %d, %d, %d, %d, %s, %s, %s>", bs.t, bs.wm, bs.wn, bs.wk, bs.nt, mc ? "true" : "false", vec ? "true" : "false",
+                   parts ? "true" : "false");
     return pc_hip_check(ctx, hipGetLastError(), "float32 conv launch");
 }
 
@@ -718,7 +723,7 @@ pc_status pc_f32_fwd(pc_ctx *ctx, const pc_conv_desc *d, const pc_packed *pk, co
     g.out_H = (d->H - 1) / d->stride + 1; g.out_W = (d->W - 1) / d->stride + 1; g.out_CH = d->F;
     g.oscale = 1; g.lstep = d->stride; g.HP = d->H + 1; g.ioff = -1;
     g.KS = pk->v.Ck / 8;
-    g.kinfo = pk->v.kinfo; g.k_row = d->C; g.k_red = 1;
+    g.kinfo = pk->v.kinfo; g.k_row = d->C; g.k_red = 1; g.w3 = pk->v.w3_fwd;
     g.act = act; g.ncls = 1;
     F32Class &c = g.cls[0];
     c.GH = g.out_H; c.GW = g.out_W; c.ntaps = 9;
@@ -735,7 +740,7 @@ pc_status pc_f32_bwd_data(pc_ctx *ctx, const pc_conv_desc *d, const pc_packed *p
     g.out_H = d->H; g.out_W = d->W; g.out_CH = d->C;
     g.oscale = d->stride; g.lstep = 1; g.HP = g.in_H + 1;
     g.KS = pk->v.Fk / 8;
-    g.back = 1; g.kinfo = pk->v.kinfo; g.k_row = 1; g.k_red = d->C;
+    g.back = 1; g.kinfo = pk->v.kinfo; g.k_row = 1; g.k_red = d->C; g.w3 = pk->v.w3_bwd;
     g.act = act; g.act_mask = (const float *)act_mask;
     int tr[4][9], tc[4][9];
     if (d->stride == 1) {

@@ -67,6 +67,10 @@ static inline int32_t *pc_choice(pc_ctx *ctx, const int32_t (&key)[PC_CHOICE_KEY
     return &e->kernel;
 }
 
+// Float32 layers whose weights are split when they are packed. Their conv passes save the split of every workgroup (5 to 25 % of a pass), the
+// pack writes 108 bytes a kernel more, which is what a larger one is bound by (320 x 320 8.9 us with the parts and 8.0 without; 512 x 512 17.2, 11.9).
+#define PC_F32_PARTS 102400
+
 // Device-side view of a packed layer. All pointers point into one slab.
 struct PackView {
     int32_t F, C, P;
@@ -90,6 +94,7 @@ struct PackView {
     // MFMA operand tiles (bf16 bit patterns, or float32 of a float32 pack; zero at every pruned position), fragment order
     uint16_t *wz_fwd;     // A operand of the forward pass
     uint16_t *wz_bwd;     // A operand of the backward-data pass
+    uint16_t *w3_fwd, *w3_bwd;   // float32 packs of up to PC_F32_PARTS kernels: the same in three bfloat16 parts ([row tile of 32][tap][entry / 16][part][64 lanes][8])
     // The same operands for the structured-sparse matrix instruction (at most 2 nonzeros in every 4 consecutive
     // reduction entries of a row): row tile rt of 32 rows, tap, step ss of 32 reduction entries.
     //   ws_*_val [rt][tap][ss][2][64 lanes][8]: part 0 holds the first two nonzeros of every group of 4, part 1 the

@@ -75,6 +75,38 @@ struct SparseOperand {
     const uint32_t *ov_col;
 };
 
+// F32_SCALE * x = s[0] + s[1] + s[2], each bfloat16 (round to nearest: the parts below have either sign), of two values per word
+#define F32_SCALE 0x1p16f
+#define F32_UNSCALE 0x1p-32f         // of a product of two
+__device__ __forceinline__ void f32_split(float a, float b, uint32_t s[3])
+{
+    a *= F32_SCALE;
+    b *= F32_SCALE;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        s[k] = pc_pack_bf16x2(a, b);
+        a -= __uint_as_float(s[k] << 16);
+        b -= __uint_as_float(s[k] & 0xFFFF0000u);
+    }
+}
+
+struct F32Parts { bf16x8 p[3]; };   // eight values in three parts
+__device__ __forceinline__ F32Parts f32_split8(const float4 &u, const float4 &v)
+{
+    uint32_t s[4][3];
+    f32_split(u.x, u.y, s[0]);
+    f32_split(u.z, u.w, s[1]);
+    f32_split(v.x, v.y, s[2]);
+    f32_split(v.z, v.w, s[3]);
+    F32Parts r;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const v4u32 w = {s[0][k], s[1][k], s[2][k], s[3][k]};
+        __builtin_memcpy(&r.p[k], &w, 16);
+    }
+    return r;
+}
+
 // Whether a tensor can be brought to LDS by direct loads, which take 16-byte elements. The kernels that load through registers take any
 // address that the element type may have.
 inline bool pc_direct_loads(const void *p) { return ((uintptr_t)p & 15) == 0; }

@@ -3,6 +3,7 @@
 // Selection is bit-reproducible: float32, fixed operation order, no fused multiply-add
 // (this file must be compiled with -ffp-contract=off).
 #include "pc_importance.h"
+#include "pc_mfma.h"
 
 // ------------------------------------------------------------------ selection
 // Tap importances of one kernel -> best pattern of the pool and the ranking score. Every sum is taken in ascending tap
@@ -979,11 +980,13 @@ __device__ __forceinline__ void pc_pack_tile_load(const float *__restrict__ W, c
 }
 
 // The float32 form: [row tile][tap][entry / 8][lane][4], lane l of a fragment holds row l % 32 and entries
-// 4 * (l / 32) .. + 3. The block's weights are masked into LDS as they lie in W and read in both orientations.
+// 4 * (l / 32) .. + 3; and in three parts, [row tile][tap][entry / 16][part][lane][8], lane l holds row l % 32 and entries 8 * (l / 32) .. + 7.
+// The block's weights are masked into LDS as they lie in W and read in both orientations. With the parts, whose stores bound it, a block has
+// a workgroup for each (128 x 128 4.9 us with one, 4.8 with two; 256 x 256 9.0, 7.0).
 template <bool FROM_KINFO>
 __device__ __forceinline__ void pc_pack_tile_block_f32(const float *__restrict__ W, const uint8_t *__restrict__ pid,
                                                        const uint8_t *__restrict__ keep, const LibArg &la, const PackView &v,
-                                                       int fb, int cb)
+                                                       int fb, int cb, int odd)
 {
     constexpr int PITCH = 289;                    // odd: rows and columns spread over the banks
     float *tw = reinterpret_cast<float *>(pc_tile_lds());
@@ -995,15 +998,23 @@ __device__ __forceinline__ void pc_pack_tile_block_f32(const float *__restrict__
 #pragma unroll
         for (int j = 0; j < 9; ++j) tw[(r0 + i) * PITCH + cl * 9 + j] = ((t.m[i] >> j) & 1u) ? t.w[i][j] : 0.0f;
     __syncthreads();
-    const int KSf = v.Ck / 8, KSb = v.Fk / 8;
-    float4 *of = reinterpret_cast<float4 *>(v.wz_fwd), *ob = reinterpret_cast<float4 *>(v.wz_bwd);
-    for (int o = tid; o < 9 * 4 * 64; o += 256) {
-        const int lane = o & 63, q = o >> 6, tap = q >> 2, ks = q & 3;
-        const int row = lane & 31, e = ks * 8 + 4 * (lane >> 5);
-        const float *p = tw + row * PITCH + e * 9 + tap;
-        of[((int64_t)(fb * 9 + tap) * KSf + cb * 4 + ks) * 64 + lane] = make_float4(p[0], p[9], p[18], p[27]);
-        const float *s = tw + e * PITCH + row * 9 + tap;
-        ob[((int64_t)(cb * 9 + tap) * KSb + fb * 4 + ks) * 64 + lane] = make_float4(s[0], s[PITCH], s[2 * PITCH], s[3 * PITCH]);
+    // both orientations, or (with the parts) the workgroup's own
+    for (int o = tid + (v.w3_fwd && odd ? 9 * 128 : 0); o < (v.w3_fwd && !odd ? 1 : 2) * 9 * 128; o += 256) {
+        const int lane = o & 63, u = o >> 6, bwd = u >= 18, tap = (bwd ? u - 18 : u) >> 1, half = u & 1;
+        const int row = lane & 31, e = half * 16 + 8 * (lane >> 5);
+        const float *p = bwd ? tw + e * PITCH + row * 9 + tap : tw + row * PITCH + e * 9 + tap;
+        const int step = bwd ? PITCH : 9, kf = (bwd ? fb : cb) * 2 + half;
+        const int64_t fr = (int64_t)((bwd ? cb : fb) * 9 + tap) * ((bwd ? v.Fk : v.Ck) / 16) + kf;
+        const float4 a = make_float4(p[0], p[step], p[2 * step], p[3 * step]);
+        const float4 b = make_float4(p[4 * step], p[5 * step], p[6 * step], p[7 * step]);
+        float4 *to = reinterpret_cast<float4 *>(bwd ? v.wz_bwd : v.wz_fwd) + fr * 128 + (lane >> 5) * 64 + row;
+        to[0] = a;
+        to[32] = b;
+        if (!v.w3_fwd) continue;              // uniform
+        const F32Parts s = f32_split8(a, b);
+        bf16x8 *to3 = reinterpret_cast<bf16x8 *>(bwd ? v.w3_bwd : v.w3_fwd) + fr * 192 + lane;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) to3[k * 64] = s.p[k];
     }
 }
 
@@ -1012,7 +1023,7 @@ __device__ __forceinline__ void pc_pack_tile_block(const float *__restrict__ W, 
                                                    const uint8_t *__restrict__ keep, const LibArg &la, const PackView &v,
                                                    int fb, int cb)
 {
-    if (v.f32) return pc_pack_tile_block_f32<FROM_KINFO>(W, pid, keep, la, v, fb, cb);
+    if (v.f32) return pc_pack_tile_block_f32<FROM_KINFO>(W, pid, keep, la, v, fb, v.w3_fwd ? cb >> 1 : cb, cb & 1);
     uint16_t (*tA)[32][PC_TILE_PITCH] = reinterpret_cast<uint16_t (*)[32][PC_TILE_PITCH]>(pc_tile_lds());   // [tap][filter][channel]
     uint16_t (*tB)[32][PC_TILE_PITCH] = tA + 9;                   // [tap][channel][filter]
     const int tid = threadIdx.x, cl = tid & 31, r0 = 4 * (tid >> 5);
@@ -1154,7 +1165,8 @@ __global__ void __launch_bounds__(64) pc_pack_ovf_merge_kernel(PackView v) { pc_
 
 
 // First launch of a pack: the first workgroups count the filter rows, the next ncm the channel rows (gather variant, else
-// none), the rest write the operand tiles (matrix-core variant), one 32 x 32 block each.
+// none), the rest write the operand tiles (matrix-core variant), one 32 x 32 block each (with the parts of float32 weights: one orientation of it).
+static int pc_tile_cols(const PackView &v) { return v.Cp / 32 * (v.w3_fwd ? 2 : 1); }
 static int pc_pack_row_wgs(int rows) { return (rows + PC_PACK_ROWS - 1) / PC_PACK_ROWS; }
 __device__ __forceinline__ void pc_pack_stage1_body(const float *__restrict__ W, const uint8_t *__restrict__ pid,
                                                     const uint8_t *__restrict__ keep, const LibArg &la, const PackView &v, int ncm,
@@ -1533,7 +1545,7 @@ pc_status pc_launch_pack(pc_ctx *ctx, pc_packed *pk, const float *W, const uint8
     const bool mfma = pk->variant == PC_VARIANT_MFMA;
     // the channel-major table serves the gather kernels' backward-data pass (the matrix-core kernels read operand tiles)
     const int nfm = pc_pack_row_wgs(v.F), ncm = mfma ? 0 : pc_pack_row_wgs(v.C);
-    const int tiles_c = v.Cp / 32, ntiles = mfma ? (v.Fp / 32) * tiles_c : 0;
+    const int tiles_c = pc_tile_cols(v), ntiles = mfma ? (v.Fp / 32) * tiles_c : 0;
     if (mfma && v.C <= 512 && (int64_t)v.F * v.C <= PC_PACK_ONE && (((uintptr_t)pid | (uintptr_t)keep) & 15) == 0) {
         hipLaunchKernelGGL(pc_pack_one_kernel, dim3((unsigned)(v.F + ntiles)), dim3(256), 0, st, W, pid, keep, la, v, tiles_c);
         pc_launch_ovf_merge(ctx, v);
@@ -1570,7 +1582,7 @@ pc_status pc_launch_pack_batch(pc_ctx *ctx, int n, pc_packed *const *pk, const f
             s1.W[i] = W[l0 + i]; s1.pid[i] = pid[l0 + i]; s1.keep[i] = keep[l0 + i];
             s1.view[i] = p->v_dev;
             s1.ncm[i] = mfma ? 0 : pc_pack_row_wgs(p->v.C);
-            s1.tiles_c[i] = p->v.Cp / 32;
+            s1.tiles_c[i] = pc_tile_cols(p->v);
             s1.bf16[i] = p->dtype == PC_BF16;
         }
         sl = s1;
@@ -1622,7 +1634,7 @@ pc_status pc_launch_update_values_batch(pc_ctx *ctx, int n, pc_packed *const *pk
         bpk[i] = p;
         b.W[i] = W[l];
         b.view[i] = p->v_dev;
-        b.tiles_c[i] = p->v.Cp / 32;
+        b.tiles_c[i] = pc_tile_cols(p->v);
         b.blk0[i + 1] = b.blk0[i] + (p->v.Fp / 32) * b.tiles_c[i];
         if (++b.n == PC_BATCH_MAX) {
             pc_status s = flush();
@@ -1636,7 +1648,7 @@ pc_status pc_launch_update_values(pc_ctx *ctx, pc_packed *pk, const float *W)
 {
     PackView v = pk->v;
     if (pk->variant == PC_VARIANT_MFMA) {
-        const int tiles_c = v.Cp / 32, ntiles = (v.Fp / 32) * tiles_c;
+        const int tiles_c = pc_tile_cols(v), ntiles = (v.Fp / 32) * tiles_c;
         hipLaunchKernelGGL(pc_pack_revalue_kernel, dim3((unsigned)ntiles), dim3(256), 0, ctx->stream, W, v, tiles_c);
         pc_launch_ovf_merge(ctx, v);
     } else {
