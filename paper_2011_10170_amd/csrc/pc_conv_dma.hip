@@ -164,12 +164,9 @@ __device__ __forceinline__ int dm_weight_offset(const DmaArgs &g, int lane)     
     return AT == 4 ? at + (m >> 3) * (9 * 1024) * g.KS + (16 * ((m >> 2) & 1) + (m & 3)) * 16 : at + (8 * (m >> 2) + (m & 3)) * 16;
 }
 
-template <int MODE, int AT, int NBW, int FR = 4>
-__device__ __forceinline__ void dm_issue(const DmaWave &s, const DmaArgs &g, int nB, int mt, int ch, int lb)
+template <int MODE, int AT, int FR>
+__device__ __forceinline__ void dm_issue_weights(const DmaWave &s, const DmaArgs &g, int w, int mt, int ch, int lb)
 {
-    // (the wavefront's number is hidden from the compiler here: it would compute all scalar offsets ahead and spill them)
-    int w = s.w;
-    asm volatile("" : "+s"(w));
     const int first = AT == 4 ? w * 64 : (w >> 1) * (9 * 1024) * g.KS + (w & 1) * 64;
     if constexpr (FR == 4) {
 #pragma unroll
@@ -182,6 +179,11 @@ __device__ __forceinline__ void dm_issue(const DmaWave &s, const DmaArgs &g, int
             if (t < 9) dm_load(s.ws, s.a_voff, ((mt * 18 + (g.flip ? 8 - t : t)) * g.KS + ch * 2) * 1024 + (w & 1) * 64, lb + (t * 2 + (w & 1)) * 1024);
         }
     }
+}
+
+template <int NBW>
+__device__ __forceinline__ void dm_issue_input(const DmaWave &s, const DmaArgs &g, int w, int nB, int ch, int lb)
+{
     const bool cut = ch == g.nch - 1 && (g.in_CH & (DM_KC - 1));      // channels past the last one are zeros
     const uint32_t parts = (uint32_t)(g.in_CH & (DM_KC - 1)) >> 3;
 #pragma unroll
@@ -190,9 +192,19 @@ __device__ __forceinline__ void dm_issue(const DmaWave &s, const DmaArgs &g, int
         if (NBW || b < nB) {
             uint32_t vo = s.voff[k];
             if (cut) vo = ((s.part >> (2 * k)) & 3u) >= parts ? DM_OOB : vo;
-            dm_load(s.xs, (int)vo, ch * (DM_KC * 2), lb + FR * (DM_A_BYTES / 4) + b * 1024);
+            dm_load(s.xs, (int)vo, ch * (DM_KC * 2), lb + b * 1024);
         }
     }
+}
+
+template <int MODE, int AT, int NBW, int FR = 4>
+__device__ __forceinline__ void dm_issue(const DmaWave &s, const DmaArgs &g, int nB, int mt, int ch, int lb)
+{
+    // (the wavefront's number is hidden from the compiler here: it would compute all scalar offsets ahead and spill them)
+    int w = s.w;
+    asm volatile("" : "+s"(w));
+    dm_issue_weights<MODE, AT, FR>(s, g, w, mt, ch, lb);
+    dm_issue_input<NBW>(s, g, w, nB, ch, lb + FR * (DM_A_BYTES / 4));
 }
 
 // The matrix instructions of one chunk; pa, pb: this lane's first weight and input fragment, RP: bytes per staged row, PL: from the
@@ -495,6 +507,131 @@ pc_mfma_conv_solo_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__
     }
 }
 
+// Layers of up to 64 input and 16 * AT output channels, 64 and 32, whose weights stay in LDS: a workgroup of 8 wavefronts per CU, four multiply, four
+// load tiles of 16 * AT channels x 64 * BT pixels a chunk of 32 channels at a time into three buffers. A tile's sums leave through LDS of their
+// own, so the loads of the next tiles go on meanwhile. What bounds these layers is memory: with the kernels above a chunk loads 36 KiB of
+// weights again beside 20 to 40 KiB of input, and loads, products and stores of a CU's two workgroups overlap in part. us, the fastest of the
+// others -> here: 32 x 224 x 224, 64 -> 64 114 -> 99 forward and backward (4.1 TB/s; in a training step 124 -> 95 and, with the mask, 149 -> 130), 32 x
+// 112 x 112 31.5 -> 29.3, one 224 x 224 image 7.6 -> 7.0, 61 x 199 x 198, 32 -> 16 53.5 -> 48.5; 64 x 56 x 56 (three tiles a CU and 16 left) 18.5
+// -> 19.5: by the estimate.
+template <int AT, int BT, int NBW, int ACT>
+__global__ void __launch_bounds__(512, 2)
+pc_mfma_conv_keep_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__ out, const uint16_t *__restrict__ wz, DmaArgs g)
+{
+    extern __shared__ __align__(16) unsigned char lds[];
+    constexpr int WB = AT * (DM_A_BYTES / 4), BUF = 4 * NBW * 1024;      // bytes of a chunk's weights and of an input buffer
+    DmaWave s;
+    s.lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    s.w = wave & 3;
+    s.cg = s.w & ((1 << g.lgCG) - 1);
+    s.rg = s.w >> g.lgCG;
+    const int G = gridDim.x, b = blockIdx.x;
+    const int vb = (G & 7) == 0 ? (b & 7) * (G >> 3) + (b >> 3) : b;
+    const int vl = (g.last & 7) == 0 ? (b & 7) * (g.last >> 3) + (b >> 3) : b;
+    const int ntile = g.rounds + (b < g.last), nch = g.nch, x0 = nch * WB;
+    auto tile_at = [&](int k) { return dm_tile<BT>(g, k < g.rounds ? k * G + vb : g.rounds * G + vl, 0); };
+    const DmaGeo &q = g.geo[0];
+
+    if (wave >= 4) {
+        s.xs = dm_rsrc(in, g.in_bytes);
+        s.ws = dm_rsrc(wz, g.wz_bytes);
+        s.a_voff = dm_weight_offset<AT>(g, s.lane);
+        const int chunks = ntile * nch;
+        DmaTile t = tile_at(0);
+        dm_offsets<DM_S1>(s, g, q, t);
+        int k = 0, ch = 0, at = x0, done = 0;      // cursor: tile, chunk, buffer; chunks issued
+        auto next = [&]() {
+            int w = s.w;
+            asm volatile("" : "+s"(w));
+            dm_issue_input<NBW>(s, g, w, 0, ch, at);
+            at = at == x0 + 2 * BUF ? x0 : at + BUF;
+            ++done;
+            if (++ch == nch) {
+                ch = 0;
+                if (++k < ntile) {
+                    t = tile_at(k);
+                    dm_offsets<DM_S1>(s, g, q, t);
+                }
+            }
+        };
+        dm_issue_weights<DM_S1, AT, AT>(s, g, s.w, 0, 0, 0);
+        next();
+        if (nch == 2) dm_issue_weights<DM_S1, AT, AT>(s, g, s.w, 0, 1, WB);
+        if (done < chunks) next();
+        for (int i = 0; i < chunks; ++i) {
+            // chunk i is complete, and the buffer of chunk i - 1 is free
+            if (i == 0 && nch == 2) dm_wait_barrier<(AT == 4 ? 9 : 4) + NBW>();
+            else if (done > i + 1) dm_wait_barrier<NBW>();
+            else dm_wait_barrier<0>();
+            if (done < chunks) next();
+        }
+        return;
+    }
+    constexpr int LPP = 2 * AT, PXI = 64 / LPP, IT = 16 / PXI, PITCH = AT == 4 ? 128 : 80;   // lanes per pixel, pixels per store, stores per column, bytes per pixel in LDS
+    const __amdgpu_buffer_rsrc_t osrc = __builtin_amdgcn_make_buffer_rsrc(out, 0, g.out_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t msrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint16_t *>(ACT == PC_ACT_RELU_MASK ? g.act_mask : out), 0, g.out_bytes, 0x00020000);
+    const int RP = q.EPR * 16, pix = g.out_CH * 2;
+    unsigned char *stg = lds + x0 + 3 * BUF + s.w * (2 * 16 * PITCH);
+    // (rows of 128 bytes: their 16-byte pieces are stored in turned order, or all pixels' would stand in the same banks)
+    auto piece = [&](int px, int i) { return AT == 4 ? i ^ (px & 7) : i; };
+    int at = x0;
+    for (int k = 0; k < ntile; ++k) {
+        const DmaTile t = tile_at(k);
+        const unsigned char *pa = lds + s.lane * 16;
+        const unsigned char *pb = lds + dm_lane_row(s, g, t) * RP + (s.lane >> 4) * 16 + s.cg * (BT * 64);
+        uint32_t off[IT];                          // of this lane's pixels in column 0 of the map
+        v4u32 mk[BT][IT];
+#pragma unroll
+        for (int i = 0; i < IT; ++i) {
+            const int row = t.r0 + s.rg * 16 + i * PXI + s.lane / LPP, m = (s.lane % LPP) * 8;
+            off[i] = row < g.rows && m < g.out_CH ? (uint32_t)(row * g.out_W) * (uint32_t)pix + (uint32_t)(m * 2) : DM_OOB;
+        }
+        const int xw = t.x0 + s.cg * BT;
+        if (ACT == PC_ACT_RELU_MASK) {
+#pragma unroll
+            for (int j = 0; j < BT; ++j)
+#pragma unroll
+                for (int i = 0; i < IT; ++i) mk[j][i] = __builtin_amdgcn_raw_buffer_load_b128(msrc, (int)(xw + j < g.out_W ? off[i] : DM_OOB), xw + j < g.out_W ? (xw + j) * pix : 0, 0);
+        }
+        f32x4 acc[AT][BT];
+        dm_zero<AT, BT>(acc);
+        for (int ch = 0; ch < nch; ++ch) {
+            asm volatile("s_barrier" ::: "memory");
+            dm_chunk<DM_S1, AT, BT, AT>(acc, pa + ch * WB, pb + at, RP, 0);
+            at = at == x0 + 2 * BUF ? x0 : at + BUF;
+        }
+#pragma unroll
+        for (int j0 = 0; j0 < BT; j0 += 2) {
+            const int NC = BT - j0 < 2 ? BT - j0 : 2;
+#pragma unroll
+            for (int j = 0; j < NC; ++j)
+#pragma unroll
+                for (int e = 0; e < AT / 2; ++e) {     // 8 of the lane's 4 * AT channels
+                    v4u32 pv;
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) pv[u] = pc_pack_bf16x2(acc[e * 2 + (u >> 1)][j0 + j][(u & 1) * 2], acc[e * 2 + (u >> 1)][j0 + j][(u & 1) * 2 + 1]);
+                    const int px = s.lane & 15;
+                    *reinterpret_cast<v4u32 *>(stg + (j * 16 + px) * PITCH + piece(px, (s.lane >> 4) * (AT / 2) + e) * 16) = pv;
+                }
+#pragma unroll
+            for (int j = 0; j < NC; ++j)
+#pragma unroll
+                for (int i = 0; i < IT; ++i) {
+                    const int px = i * PXI + s.lane / LPP, x = xw + j0 + j;
+                    v4u32 pv = *reinterpret_cast<const v4u32 *>(stg + (j * 16 + px) * PITCH + piece(px, s.lane % LPP) * 16);
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        if (ACT == PC_ACT_RELU) pv[u] = pc_relu_bf16x2(pv[u]);
+                        if (ACT == PC_ACT_RELU_MASK) pv[u] = pc_mask_bf16x2(pv[u], mk[j0 + j][i][u]);
+                    }
+                    __builtin_amdgcn_raw_buffer_store_b128(pv, osrc, (int)(x < g.out_W ? off[i] : DM_OOB), x < g.out_W ? x * pix : 0, 0);
+                }
+        }
+    }
+}
+
 // The stride-2 forward pass in tiles of 128 output channels x 128 pixels, 8 wavefronts, four of them loading: two input buffers, and the
 // weights, a row of taps at a time, in a ring of three places (72 + 88 KiB: whole chunks of both would not fit twice). A wavefront
 // multiplies 64 channels x 64 pixels, so that a chunk reads 252 KiB of LDS where two tiles of 64 channels read 360, and an input
@@ -665,11 +802,13 @@ pc_mfma_conv_ring_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__
 // Constants of the time estimate (us) of a tile: a chunk, each direct load of its input, the tile's end; of the launch: its start, and a
 // factor for the time of its bytes
 struct DmaTimes { double chunk, load, tile, start, bytes; };
-struct DmaCand { int code, mode, at, bt, nbuf; DmaTimes solo; };       // nbuf 1: two workgroups per CU
+#define DM_KEEP_NBW 6                // direct loads of a chunk per loading wavefront where the weights stay in LDS
+struct DmaCand { int code, mode, at, bt, nbuf; DmaTimes solo; };       // nbuf 1: two workgroups per CU; 4: the weights stay in LDS beside three
 static const DmaCand kDma[] = {
     {40, DM_S1, 4, 8, 1, {0, 0, 0, 3.3, 1}}, {41, DM_S1, 4, 4, 1, {0, 0, 0, 3.3, 1}}, {42, DM_S1, 4, 7, 1, {0, 0, 0, 3.3, 1}},
     {43, DM_S1, 2, 4, 3, {0.440, 0.0137, 0.491, 3.3, 1}}, {45, DM_S1, 4, 4, 2, {1.031, 0.0042, 1.038, 3.3, 1}}, {46, DM_S1, 2, 2, 3, {0.387, 0, 0.445, 3.3, 1}},
     {47, DM_FWD2, 2, 4, 2, {0.976, 0, 1.296, 2.7, 0.78}}, {49, DM_FWD2, 8, 4, 2, {1.5, 0, 1.8, 2.6, 0.7}}, {48, DM_FWD2, 2, 2, 2, {0.716, 0, 1.275, 2.5, 0.78}},
+    {50, DM_S1, 4, 4, 4, {0, 0, 0, 0, 0}},
     {37, DM_BWD2, 2, 4, 3, {0.504, 0.0087, 1.829, 3.1, 0.62}}, {38, DM_BWD2, 2, 2, 3, {0.348, 0.0082, 1.210, 2.9, 0.50}}};
 constexpr int kNumDma = sizeof(kDma) / sizeof(kDma[0]);
 
@@ -682,7 +821,9 @@ static bool plan_dma(const MfmaArgs &g, bool flip, const DmaCand &cand, int lgCG
     t.in_H = g.in_H; t.in_W = g.in_W; t.out_H = g.out_H; t.out_W = g.out_W;
     t.KS = g.KS; t.nch = (g.in_CH + DM_KC - 1) / DM_KC; t.flip = flip;
     t.lgCG = lgCG;
-    const bool narrow = cand.nbuf == 1 && g.out_CH <= 32;
+    const bool keep = cand.nbuf == 4;
+    if (keep && (g.in_CH > 64 || g.out_CH > 64)) return false;
+    const bool narrow = (cand.nbuf == 1 || keep) && g.out_CH <= 32;
     const int lgPG = cand.at == 4 ? 2 : 1, rows_m = cand.at == 8 ? 128 : 64;       // groups of pixels among the wavefronts (log2)
     if (lgCG > lgPG) return false;
     t.TR = 16 << (lgPG - lgCG);
@@ -705,9 +846,14 @@ static bool plan_dma(const MfmaArgs &g, bool flip, const DmaCand &cand, int lgCG
     const int nB = t.geo[0].nB, TC = cand.bt << lgCG;
     if (cand.at == 8 && nB > DR_B) return false;
     t.buf_bytes = cand.at == 8 ? DM_LDS_MAX / 2 : (narrow ? DM_A_BYTES / 2 : DM_A_BYTES) + (uint32_t)(cand.nbuf == 3 ? 4 * dm_nbw(cand.bt) : nB) * 1024;
-    if (narrow && t.buf_bytes < 4 * 64 * DM_STG) t.buf_bytes = 4 * 64 * DM_STG;      // (the tile leaves through it)
-    *lds = (size_t)t.buf_bytes * cand.nbuf;
-    if (nB > 4 * (cand.nbuf == 3 ? dm_nbw(cand.bt) : DM_NB) || *lds > (size_t)DM_LDS_MAX / (cand.nbuf == 1 ? 2 : 1)) return false;
+    if (keep) {
+        t.buf_bytes = 4 * DM_KEEP_NBW * 1024;
+        *lds = t.nch * (size_t)(narrow ? DM_A_BYTES / 2 : DM_A_BYTES) + 3 * (size_t)t.buf_bytes + 4 * 2 * 16 * (narrow ? 80 : 128);
+        if (nB > 4 * DM_KEEP_NBW || *lds > (size_t)DM_LDS_MAX) return false;
+    }
+    if (!keep && narrow && t.buf_bytes < 4 * 64 * DM_STG) t.buf_bytes = 4 * 64 * DM_STG;      // (the tile leaves through it)
+    if (!keep) *lds = (size_t)t.buf_bytes * cand.nbuf;
+    if (!keep && (nB > 4 * (cand.nbuf == 3 ? dm_nbw(cand.bt) : DM_NB) || *lds > (size_t)DM_LDS_MAX / (cand.nbuf == 1 ? 2 : 1))) return false;
     t.tiles_x = (t.W + TC - 1) / TC;
     const int64_t p_tiles = (rows + t.TR - 1) / t.TR * t.tiles_x;
     const int m_tiles = (g.out_CH + rows_m - 1) / rows_m;
@@ -760,12 +906,21 @@ static bool plan_dma(const MfmaArgs &g, bool flip, const DmaCand &cand, int lgCG
         if (c < best) { best = c; t.last = last; t.pieces = pieces; t.lgP = lgP; }
     }
     double in_moved = 2.0 * (double)p_tiles * staged * t.geo[0].IW * (g.in_CH < DM_KC ? DM_KC : g.in_CH);
-    if (narrow && t.nch > 1) {
+    if (narrow && !keep && t.nch > 1) {
         const double under_way = (double)(total < slots ? total : slots) * staged * t.geo[0].IW * 128.0;
         in_moved *= 1.0 + 1.05 * std::min(1.0, std::max(0.0, (under_way - 28e6) / 32e6));
     }
     const double move = (in_moved + (double)out_bytes) / 6.0e6;
-    *est = (narrow ? kNarrow.start : cand.solo.start) + pow(pow(best, 1.5) + pow((narrow ? kNarrow.bytes : cand.solo.bytes) * move, 1.5), 1.0 / 1.5);
+    if (keep) {
+        // Weights in LDS: tiles one after the other and the tensors' bytes, by whether there are more than 32 output channels and more than one
+        // chunk (656 timings of 328 layers of up to 64 channels, 6 % rms; of two sets it is the
+        // fastest in 30 and 42 % of the passes, by up to 26 %; of one chunk 3 % more than the fit, the other kernels' own estimates are high)
+        static const DmaTimes kKeep[2][2] = {{{0.885, 0, 0, 3.55, 0.394}, {1.556, 0, 0, 3.48, 0.250}}, {{1.432, 0, 0, 3.74, 0.490}, {2.844, 0, 0, 3.46, 0.415}}};
+        const DmaTimes &c = kKeep[!narrow][t.nch - 1];
+        *est = c.start + (t.rounds + (t.last > 0)) * c.chunk + c.bytes * move;
+    } else {
+        *est = (narrow ? kNarrow.start : cand.solo.start) + pow(pow(best, 1.5) + pow((narrow ? kNarrow.bytes : cand.solo.bytes) * move, 1.5), 1.0 / 1.5);
+    }
     const int busy = t.last + t.pieces;
     *grid = t.rounds > 0 || busy > slots ? slots : busy;
     t.apart = t.m_fast ? m_tiles : 1;
@@ -785,9 +940,11 @@ static const DmaKernel kDmaKernels[kNumDma][3] = {
     {&pc_mfma_conv_solo_kernel<DM_FWD2, 2, 4, 2, PC_ACT_NONE>, &pc_mfma_conv_solo_kernel<DM_FWD2, 2, 4, 2, PC_ACT_RELU>, nullptr},
     {&pc_mfma_conv_ring_kernel<PC_ACT_NONE>, &pc_mfma_conv_ring_kernel<PC_ACT_RELU>, nullptr},
     {&pc_mfma_conv_solo_kernel<DM_FWD2, 2, 2, 2, PC_ACT_NONE>, &pc_mfma_conv_solo_kernel<DM_FWD2, 2, 2, 2, PC_ACT_RELU>, nullptr},
+    DM_ACTS(pc_mfma_conv_keep_kernel<4, 4, DM_KEEP_NBW),
     {&pc_mfma_conv_solo_kernel<DM_BWD2, 2, 4, 3, PC_ACT_NONE>, nullptr, nullptr},
     {&pc_mfma_conv_solo_kernel<DM_BWD2, 2, 2, 3, PC_ACT_NONE>, nullptr, nullptr}};
 // The first three for up to 32 output channels
+static const DmaKernel kDmaKeepNarrow[3] = DM_ACTS(pc_mfma_conv_keep_kernel<2, 4, DM_KEEP_NBW);
 static const DmaKernel kDmaNarrow[3][3] = {DM_PAIR(8, 2), DM_PAIR(4, 2), DM_PAIR(7, 2)};
 #undef DM_ACTS
 #undef DM_PAIR
@@ -829,14 +986,16 @@ pc_status pc_run_mfma_conv_dma(pc_ctx *ctx, int pcfg, int *lgCG, double limit, c
     }
     if (best_k < 0) return PC_OK;
     const DmaCand &c = kDma[best_k];
-    static pc_per_device_once attr[kNumDma][3], attr_narrow[3][3];
-    const bool narrow = c.nbuf == 1 && g0.out_CH <= 32;
-    const hipError_t e = launch_dma(narrow ? kDmaNarrow[best_k][act] : kDmaKernels[best_k][act], narrow ? attr_narrow[best_k][act] : attr[best_k][act], ctx->device, ctx->stream, best_grid, c.nbuf == 1 ? 256 : 512, best_lds, in, out,
+    static pc_per_device_once attr[kNumDma][3], attr_narrow[4][3];
+    const bool narrow = (c.nbuf == 1 || c.nbuf == 4) && g0.out_CH <= 32;
+    const int row = c.nbuf == 4 ? 3 : best_k;
+    const hipError_t e = launch_dma(!narrow ? kDmaKernels[best_k][act] : c.nbuf == 4 ? kDmaKeepNarrow[act] : kDmaNarrow[best_k][act], narrow ? attr_narrow[row][act] : attr[best_k][act], ctx->device, ctx->stream, best_grid, c.nbuf == 1 ? 256 : 512, best_lds, in, out,
                                     wz, best);
     *launched = c.code;
     *lgCG = best.lgCG;
     if (c.at == 8) pc_note_kernel(ctx, "pc_mfma_conv_ring_kernel<%d>", act);
     else if (c.nbuf == 1) pc_note_kernel(ctx, "pc_mfma_conv_dma_kernel<%d, %d, %d>", c.bt, act, narrow ? 2 : 4);
+    else if (c.nbuf == 4) pc_note_kernel(ctx, "pc_mfma_conv_keep_kernel<%d, %d, %d, %d>", narrow ? 2 : 4, c.bt, DM_KEEP_NBW, act);
     else pc_note_kernel(ctx, "pc_mfma_conv_solo_kernel<%d, %d, %d, %d, %d>", c.mode, c.at, c.bt, c.nbuf, act);
     return pc_hip_check(ctx, e, "MFMA conv (direct loads) launch");
 }

@@ -1164,7 +1164,7 @@ pc_status pc_run_mfma_conv_ws(pc_ctx *ctx, int pcfg, double coop_us, const MfmaA
 {
     *launched = false;
     int dma = 0, lgCG = -1;
-    if (pcfg >= 40 && pcfg < 50) {
+    if (pcfg >= 40 && pcfg <= 50) {
         const pc_status s = pc_run_mfma_conv_dma(ctx, pcfg, &lgCG, 1e30, g0, tr[0] != 0, in, out, wz, &dma, act);
         *launched = dma != 0;
         return s;
