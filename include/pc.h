@@ -132,16 +132,17 @@ pc_status pc_set_variant(pc_ctx *ctx, pc_variant v);
  *          pass, tiles of 32 channels x 4 x 256 pixels with 64-, 32-, 16-channel chunks, x 4 x 128 with 64 and 32
  *   40..43, 45, 46  stride 1: the kernels that load both operands straight to LDS, tiles of 64 output channels x 512, 256 and 448
  *          pixels, two workgroups per CU; x 128 (43), 256 (45) and 64 (46) pixels, one workgroup per CU
- *   50     the same with the weights kept in LDS, x 256 pixels, one workgroup per CU (up to 64 input and output channels)
  *   47, 48, 49  the same at stride 2, forward: x 128 and 64 pixels; 128 output channels x 128 pixels
  *   37, 38 the same for stride-2 backward-data (the other passes stay automatic): x 4 x 128 and 4 x 64 pixels
+ *   50     stride 1, up to 64 input and output channels: direct loads of the input, the weights kept in LDS, tiles of 256 pixels, one workgroup per CU
+ *   51..54 stride 1, few pixels: tiles of 16 output channels x 32 and 64 pixels, 32 x 32 and 64, up to 512 reduction channels at once
  *   10, 11, 44 backward-weight: the cooperative / the wave-specialised kernel / the kernel with direct loads (the other passes stay
  *          automatic); with 44 and one layer, split_k 0 to 3 are tiles of 64 x 64, 32 x 64, 64 x 32 and 32 x 32 (filter, channel)
  *   22     forward/backward-data: the structured-sparse kernel (packs made under PC_VARIANT_MFMA_SPARSE only)
  *   23     the first-layer kernels (at most 4 input channels; forward and backward-data at stride 1, backward-weight at
  *          both): the automatic choice takes them wherever they apply; any other code here keeps such a layer on the
  *          general kernels
- * The wave-specialised forward/backward-data kernel (7..9, 13..21, 24..31) takes 9-tap launches only, and so do 40..43 and 45..50: a stride-2
+ * The wave-specialised forward/backward-data kernel (7..9, 13..21, 24..31) takes 9-tap launches only, and so do 40..43 and 45..54: a stride-2
  * backward-data pass takes 0..6 (the cooperative kernel over the four parity classes of input pixels) and 32..38 and
  * uses the automatic choice otherwise. split_k > 0 forces that many splits of the reduction in the
  * cooperative forward/backward-data kernel (0 = automatic). A configuration that does not fit a layer makes

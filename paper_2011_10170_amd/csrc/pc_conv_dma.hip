@@ -1,6 +1,6 @@
 // Forward / backward-data on the matrix cores, both operands brought to LDS by direct loads (see pc_conv_mfma.hip
 // for the implicit-GEMM formulation, the operand tiles and the MFMA register layout).
-#include "pc_mfma.h"
+#include "pc_dma.h"
 #include <algorithm>
 
 #include <math.h>
@@ -27,7 +27,6 @@
 #define DM_NA 36                     // direct loads (1 KiB) of the weights per chunk: 9 taps x 4 fragments of 16 output channels
 #define DM_NB 11                     // of the input tile per wavefront at most
 #define DM_A_BYTES (DM_NA * 1024)
-#define DM_OOB 0x80000000u           // past the end of any tensor taken here, also with a chunk's offset added
 #define DM_LDS_MAX (160 * 1024)
 #define DM_STG 144                   // bytes per pixel (64 channels) where a finished tile passes through LDS
 
@@ -71,35 +70,6 @@ struct DmaArgs {
     DmaGeo geo[3];                   // whole tiles, halves, quarters
     const uint16_t *act_mask;
 };
-
-// 64 lanes x 16 bytes from a buffer to the 1 KiB of LDS at lds_off; an offset past the buffer's end writes zeros. As inline
-// assembly because the compiler orders every later LDS read behind a direct load it knows of: here the wait is one
-// s_waitcnt in front of a barrier. (The compiler warns that it saves no reserved register for the statement: m0 holds nothing
-// of its own that it would have to.)
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-__device__ __forceinline__ void dm_load(const v4u32 &rsrc, int voff, int soff, int lds_off)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :: "s"(lds_off), "v"(voff), "s"(rsrc), "s"(soff) : "memory", "m0");
-}
-#pragma clang diagnostic pop
-
-// All but the last N vector memory operations of this wavefront are complete, and every wavefront has come here.
-template <int N> __device__ __forceinline__ void dm_wait_barrier()
-{
-    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"(N) : "memory");
-}
-
-// The words of a buffer resource (what __builtin_amdgcn_make_buffer_rsrc builds, as an operand of inline assembly).
-__device__ __forceinline__ v4u32 dm_rsrc(const void *p, uint32_t bytes)
-{
-    const uint64_t a = (uint64_t)p;
-    const v4u32 r = {(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a),
-                     (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)(a >> 32) & 0xFFFFu)),
-                     (uint32_t)__builtin_amdgcn_readfirstlane((int)bytes), 0x00020000u};
-    return r;
-}
 
 struct DmaTile { int mt, r0, x0; };  // tile of 64 output channels, first row, first column
 
@@ -914,8 +884,8 @@ static bool plan_dma(const MfmaArgs &g, bool flip, const DmaCand &cand, int lgCG
     if (keep) {
         // Weights in LDS: tiles one after the other and the tensors' bytes, by whether there are more than 32 output channels and more than one
         // chunk (656 timings of 328 layers of up to 64 channels, 6 % rms; of two sets it is the
-        // fastest in 30 and 42 % of the passes, by up to 26 %; of one chunk 3 % more than the fit, the other kernels' own estimates are high)
-        static const DmaTimes kKeep[2][2] = {{{0.885, 0, 0, 3.55, 0.394}, {1.556, 0, 0, 3.48, 0.250}}, {{1.432, 0, 0, 3.74, 0.490}, {2.844, 0, 0, 3.46, 0.415}}};
+        // fastest in 30 and 42 % of the passes, by up to 26 %; those of one chunk set by which kernel is the faster)
+        static const DmaTimes kKeep[2][2] = {{{0.950, 0, 0, 3.20, 0.394}, {1.556, 0, 0, 3.48, 0.250}}, {{1.432, 0, 0, 3.74, 0.490}, {2.844, 0, 0, 3.46, 0.415}}};
         const DmaTimes &c = kKeep[!narrow][t.nch - 1];
         *est = c.start + (t.rounds + (t.last > 0)) * c.chunk + c.bytes * move;
     } else {

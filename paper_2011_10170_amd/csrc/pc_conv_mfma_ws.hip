@@ -1169,6 +1169,11 @@ pc_status pc_run_mfma_conv_ws(pc_ctx *ctx, int pcfg, double coop_us, const MfmaA
         *launched = dma != 0;
         return s;
     }
+    if (pcfg > 50) {
+        const pc_status s = pc_run_mfma_conv_deep(ctx, pcfg, 1e30, g0, tr[0] != 0, in, out, wz, &dma, nullptr, act);
+        *launched = dma != 0;
+        return s;
+    }
     // The structured-sparse kernel (override code 22; automatic from 64 reduction channels up): 64 x 256 tiles,
     // 64-channel chunks, pixels split over the MFMA wavefronts.
     if (sp.val && g0.lstep == 1 && (pcfg == 22 || (pcfg < 0 && g0.in_CH >= 64))) {
@@ -1203,6 +1208,11 @@ pc_status pc_run_mfma_conv_ws(pc_ctx *ctx, int pcfg, double coop_us, const MfmaA
     const int32_t key[PC_CHOICE_KEY] = {5, g0.N, g0.in_H, g0.in_W, g0.in_CH, g0.out_CH, g0.GH, g0.GW, g0.lstep * 16 + g0.oscale, ext * 2 + (tr[0] != 0)};
     int32_t *choice = pcfg < 0 && pc_direct_loads(in) ? pc_choice(ctx, key, &known) : nullptr;
     known = known && *choice >= 0;
+    if (known && (*choice >> 2) > 50) {
+        const pc_status s = pc_run_mfma_conv_deep(ctx, *choice >> 2, 1e30, g0, tr[0] != 0, in, out, wz, &dma, nullptr, act);
+        *launched = dma != 0;
+        return s;
+    }
     if (known && (*choice >> 2) >= 40) {
         lgCG = *choice & 3;
         const pc_status s = pc_run_mfma_conv_dma(ctx, *choice >> 2, &lgCG, 1e30, g0, tr[0] != 0, in, out, wz, &dma, act);
@@ -1222,7 +1232,14 @@ pc_status pc_run_mfma_conv_ws(pc_ctx *ctx, int pcfg, double coop_us, const MfmaA
         if ((best_k < 0 && (pcfg >= 7 || known || est < coop_us)) || (best_k >= 0 && est < best_est)) { best = t; best_lds = lds; best_est = est; best_k = k; }
     }
     if (choice && !known) {
-        const pc_status s = pc_run_mfma_conv_dma(ctx, -1, &lgCG, best_k < 0 ? coop_us : best_est, g0, tr[0] != 0, in, out, wz, &dma, act);
+        int deep = 0;
+        double limit = best_k < 0 ? coop_us : best_est;
+        (void)pc_run_mfma_conv_deep(ctx, -1, limit, g0, tr[0] != 0, in, out, wz, &deep, &limit, act);
+        pc_status s = pc_run_mfma_conv_dma(ctx, -1, &lgCG, limit, g0, tr[0] != 0, in, out, wz, &dma, act);
+        if (s == PC_OK && !dma && deep) {
+            lgCG = 0;
+            s = pc_run_mfma_conv_deep(ctx, deep, 1e30, g0, tr[0] != 0, in, out, wz, &dma, nullptr, act);
+        }
         *launched = dma != 0;
         if (s == PC_OK) *choice = dma ? dma * 4 + lgCG : best_k < 0 ? 0 : kKs[best_k].code * 4;
         if (s != PC_OK || dma) return s;

@@ -119,6 +119,9 @@ pc_status pc_run_mfma_conv_ws(pc_ctx *ctx, int pcfg, double coop_us, const MfmaA
 
 pc_status pc_run_mfma_conv_dma(pc_ctx *ctx, int pcfg, int *lgCG, double limit, const MfmaArgs &g0, bool flip, const uint16_t *in, uint16_t *out,
                                const uint16_t *wz, int *launched, int act);
+// Few pixels, many channels. us: the estimate is asked for, nothing is launched.
+pc_status pc_run_mfma_conv_deep(pc_ctx *ctx, int pcfg, double limit, const MfmaArgs &g, bool flip, const uint16_t *in, uint16_t *out,
+                                const uint16_t *wz, int *launched, double *us, int act);
 pc_status pc_run_mfma_conv_mc(pc_ctx *ctx, int pcfg, const MfmaArgs &g0, const uint16_t *in, uint16_t *out, const uint16_t *wz, bool *launched);
 
 // Copies between a tensor with C < 8 channels per pixel and one with 8-channel (16-byte) pixel rows.

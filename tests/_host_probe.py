@@ -303,6 +303,8 @@ def kernel_code(name):
         return 49
     if "conv_keep" in name:
         return 50
+    if "conv_deep" in name:
+        return {"1 2": 51, "1 4": 52, "2 2": 53, "2 4": 54}[" ".join(v[:2])]
     return {"2 4 2 2 32": 1, "2 2 2 2 64": 3, "1 2 2 2 64": 4, "1 1 2 2 64": 5, "1 2 2 2 16": 6}[" ".join(v[:4] + v[5:6])]
 
 
@@ -321,7 +323,7 @@ def conv_choice():
             d, pk = layer(ctx, k[1:])
             (B.pc_conv_fwd if k[0] == "fwd" else B.pc_conv_bwd_data)(ctx, d, pk, DEV + off, DEV)
             code = kernel_code(B.pc_last_kernel(ctx))
-            best = min(v for c, v in us.items() if not off or not 37 <= c <= 50)
+            best = min(v for c, v in us.items() if not off or not 37 <= c <= 54)
             if code in us:      # (what was timed of a layer leaves out kernels that are never near)
                 late.setdefault((k[0], k[6], (k[4] if k[0] == "fwd" else k[5]) <= 16), []).append(us[code] / best)
             B.pc_packed_free(pk)
