@@ -138,6 +138,7 @@ pc_status pc_set_variant(pc_ctx *ctx, pc_variant v);
  *   51..54 stride 1, few pixels: tiles of 16 output channels x 32 and 64 pixels, 32 x 32 and 64, up to 512 reduction channels at once
  *   10, 11, 44 backward-weight: the cooperative / the wave-specialised kernel / the kernel with direct loads (the other passes stay
  *          automatic); with 44 and one layer, split_k 0 to 3 are tiles of 64 x 64, 32 x 64, 64 x 32 and 32 x 32 (filter, channel)
+ *   55     backward-weight at stride 1: the kernel for few pixels (one launch); split_k 0 to 3 are tiles of 16 x 16, 16 x 32, 32 x 16 and 32 x 32
  *   22     forward/backward-data: the structured-sparse kernel (packs made under PC_VARIANT_MFMA_SPARSE only)
  *   23     the first-layer kernels (at most 4 input channels; forward and backward-data at stride 1, backward-weight at
  *          both): the automatic choice takes them wherever they apply; any other code here keeps such a layer on the

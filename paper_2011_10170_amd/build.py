@@ -14,7 +14,7 @@ LIB = os.path.join(HERE, "libpatconv.so")
 NATIVE = os.path.join(HERE, "_native.so")
 SOURCES = ["pc_api.hip", "pc_select_pack.hip", "pc_conv_valu.hip", "pc_conv_mfma.hip", "pc_conv_mfma_ws.hip",
            "pc_wgrad_mfma.hip", "pc_train_steps.hip", "pc_act_pool.hip", "pc_conv_thin.hip",
-           "pc_conv_f32.hip", "pc_conv_dma.hip", "pc_conv_deep.hip", "pc_wgrad_dma.hip"]
+           "pc_conv_f32.hip", "pc_conv_dma.hip", "pc_conv_deep.hip", "pc_wgrad_dma.hip", "pc_wgrad_few.hip"]
 
 # Contraction is off so that the selection arithmetic keeps its written order; the conv kernels
 # call fmaf explicitly. Packed fp32 instructions are disabled for the device pass.

@@ -388,7 +388,7 @@ static pc_status run_mfma_conv(pc_ctx *ctx, MfmaArgs g, int ext, int ntaps, cons
                                bool *fused = nullptr)
 {
     g.act_mask = nullptr;
-    int plan_cfg = (ctx->plan_cfg >= 10 && ctx->plan_cfg < 13) || ctx->plan_cfg == 44 ? -1 : ctx->plan_cfg;   // 10, 11 and 44 select a backward-weight kernel
+    int plan_cfg = (ctx->plan_cfg >= 10 && ctx->plan_cfg < 13) || ctx->plan_cfg == 44 || ctx->plan_cfg == 55 ? -1 : ctx->plan_cfg;   // 10, 11, 44 and 55 select a backward-weight kernel
     if (ntaps == 9 && plan_cfg >= 32 && plan_cfg < 40) plan_cfg = -1;   // codes of the stride-2 backward-data kernel
     if (ntaps == 9 && (plan_cfg < 0 || plan_cfg >= 7) && ctx->plan_split == 0) {
         // The wave-specialised kernel reads and writes whole groups of 8 channels. The first layer's few channels

@@ -63,6 +63,7 @@ struct WgradDmaPlan {
     int steps, loads;                // of a pixel tile: steps of 36 matrix instructions and direct loads per wavefront
     size_t lds;
     double tile_us, end_us;          // estimated time of a pixel tile (us) while two workgroups share a CU, and of a workgroup's end
+    double us;                       // plan_one, not of a remembered choice: of the layer
 };
 
 // Plan of one layer of a grouped call (ksplit left to the caller), and of a layer's own call; false when the layer is outside what the kernel
@@ -72,6 +73,11 @@ bool pc_wgrad_dma_plan(const pc_conv_desc *d, int64_t nslots, int32_t *choice, W
 bool pc_wgrad_dma_plan_one(const pc_conv_desc *d, int64_t nslots, double kept, int num_cu, int waves, int32_t *choice, WgradDmaPlan *out);
 pc_status pc_wgrad_dma_launch(pc_ctx *ctx, WgradDmaOne &g, size_t lds);
 pc_status pc_wgrad_dma_launch(pc_ctx *ctx, WgradDmaGroup &g, size_t lds);
+
+// A layer of few pixels in one launch, without scratch: the tile (16 x 16, 16 x 32, 32 x 16, 32 x 32 filters x channels) of the least estimated
+// time below limit (us) or -1, and its launch.
+int pc_wgrad_few_tile(const pc_conv_desc *d, int num_cu, double limit);
+pc_status pc_mfma_bwd_weight_few(pc_ctx *ctx, const pc_conv_desc *d, const pc_packed *pk, const void *x, const void *dy, float *dw, int tile, bool *launched);
 
 struct ThinWgradPlan {
     ThinWgradArgs a;

@@ -482,7 +482,7 @@ bool pc_wgrad_dma_plan_one(const pc_conv_desc *d, int64_t nslots, double kept, i
                 const double t = 3.25 + (T * ks <= num_cu ? u * lone + p.end_us / 2.2 : rounds * (u * p.tile_us + p.end_us));
                 const double moved = 0.168e-6 * bytes + (wd_placed(T, ks) == WD_PLACE_PLAIN ? 0.112e-6 * staged * T * ks * u : 0.0);
                 const double us = cbrt(t * t * t + moved * moved * moved) + (ks > 1 ? 2.5 + 10.7e-6 * ks * kept : 0.0);
-                if (us < best) { best = us; *out = p; out->a.ksplit = ks; }
+                if (us < best) { best = us; *out = p; out->a.ksplit = ks; out->us = us; }
             }
     });
     if (best < 1e30 && choice) *choice = wd_code(*out);

@@ -362,6 +362,10 @@ def wgrad_choice():
         watch("pc_mfma_wgrad_dma_kernel", 0, 88 + 112)
         B.pc_conv_bwd_weight(ctx, d, pk, DEV, DEV, DEV)
         assert "wgrad_dma" in B.pc_last_kernel(ctx), k
+        if "wgrad_dma_few" in B.pc_last_kernel(ctx):      # (another kernel: few pixels)
+            assert k[0] * k[1] * k[2] <= 8192 and k[5] == 1, k
+            B.pc_packed_free(pk)
+            continue
         a = struct.unpack("<28i", seen()[0][88:])
         plan = (a[25], a[26], a[9], a[27], a[18])
         late.append(us[plan] / min(us.values()) if plan in us else None)
