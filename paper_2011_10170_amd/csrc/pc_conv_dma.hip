@@ -15,11 +15,18 @@
 //     stores a finished tile) while the other multiplies; a wavefront's priority rises through a chunk, so that of two workgroups
 //     that multiply at the same time the one ahead finishes first and the two fall out of step by themselves. Layers of a few tiles
 //     per CU (pc_mfma_conv_solo_kernel): a workgroup has the CU to itself, with two or three buffers and wavefronts that only load.
-//   Rows: the rows of all images, N * H of them, in order. The staged tile is rows of "padded images" of H + 1 rows (one zero
-//     row between two images), so a tile covers any 16, 32 or 64 rows without a gap, whatever the map's height.
+//   Rows: the rows of all images, N * H of them, in order, so a tile covers any 16, 32 or 64 rows without a gap, whatever the map's
+//     height. Stride 1: they are staged as they follow each other, and where a row's neighbour lies outside its image the lane reads
+//     zeros behind the staged rows. Stride 2: the staged tile is rows of "padded images" of H + 1 rows (one zero row between two images).
 //   Columns: the 16 columns of a B operand are 16 rows of one column of the map, so the fragment of column j is the operand of tap
 //     column s for output column j - s: the three taps of a row read BT + 2 fragments for BT columns.
-//   LDS: a staged row is its columns' 64 bytes and one 16-byte element more, so lanes a row apart start in different banks.
+//   LDS: a staged row is its columns' 64 bytes and two 16-byte elements more where there is room. ds_read_b128 takes 16 lanes at a time,
+//     0 to 3, 12 to 15 and 20 to 27 first: those rows of one 16-byte group of channels and the other rows of the next group, which stand in
+//     16 different places of 256 bytes exactly if a row is twice an odd number of elements long. (With one element more every read took twice the
+//     time, with an image's end among the 16 rows and a row of zeros there three times. A zero is read from the place of the
+//     256 bytes where the row would have stood.) us with one element and rows of
+//     zeros -> here, tiles of 64 x 128: 64 images 7 x 7 512 -> 512 16.1 -> 14.1, 128 images 8 x 8 256 -> 256 10.2 -> 9.3; of 64 x 256: 64 images 14 x 14
+//     256 -> 256 15.5 -> 14.3, 32 images 512 -> 512 27.3 -> 26.1; tiles of two workgroups per CU, where LDS was busy half of the time, 1 to 3 %.
 // In the kernel that keeps the weights in registers (pc_conv_mfma_ws.hip) each of the four multiplying wavefronts requests the same
 // fragments, 64 B/clk of vector-cache hits, and nothing is multiplied while a tile is stored.
 
@@ -49,7 +56,7 @@ template <int MODE> constexpr __host__ __device__ int dm_tap(int t)
 
 // Staged columns for a tile width
 struct DmaGeo {
-    int32_t IW, EPR, nB;             // staged columns, 16-byte elements per staged row, direct loads of the input tile
+    int32_t IW, EPR, nB, zero;       // staged columns, 16-byte elements per staged row, direct loads of the input tile, where zeros stand behind it (bytes)
     uint32_t mg_EPR;
 };
 
@@ -72,6 +79,8 @@ struct DmaArgs {
 };
 
 struct DmaTile { int mt, r0, x0; };  // tile of 64 output channels, first row, first column
+
+struct DmaRows { const unsigned char *p[3]; };
 
 struct DmaWave {
     int lane, w, cg, rg;
@@ -96,28 +105,35 @@ __device__ __forceinline__ DmaTile dm_tile(const DmaArgs &g, int t, int sh)
     return o;
 }
 
-// The elements of a tile that this lane loads: element e of the tile is the 16-byte part e % EPR of staged row e / EPR.
-template <int MODE>
+// The elements of a tile that this lane loads (NBW > 0: NBW of them): element e of the tile is the 16-byte part e % EPR of staged row e / EPR.
+template <int MODE, int NBW>
 __device__ __forceinline__ void dm_offsets(DmaWave &s, const DmaArgs &g, const DmaGeo &q, const DmaTile &t)
 {
-    const int V0 = t.r0 + (int)pc_udiv((uint32_t)t.r0, g.mg_H);
+    const int V0 = MODE == DM_S1 ? t.r0 - 1 : t.r0 + (int)pc_udiv((uint32_t)t.r0, g.mg_H);
     s.part = 0;
     int lane = s.lane;      // (hidden from the compiler: it would keep the quotients of all elements from tile to tile, in scratch)
     asm volatile("" : "+v"(lane));
 #pragma unroll
-    for (int k = 0; k < DM_NB; ++k) {
+    for (int k = 0; k < (NBW ? NBW : DM_NB); ++k) {
+        if (!NBW && s.w + 4 * k >= q.nB) break;
         const uint32_t e = (uint32_t)((s.w + 4 * k) * 64 + lane);
         const uint32_t row = pc_udiv(e, q.mg_EPR), rem = e - row * q.EPR;
-        const int odd = MODE == DM_FWD2 && (int)row >= g.nrow;
-        const uint32_t v = V0 + row - (odd ? g.nrow : 0);
-        const int n = (int)pc_udiv(v, g.mg_H1), c = (int)(rem >> 2);
-        int y = (int)v - n * (g.H + 1);
-        if (MODE == DM_S1) y -= 1;
-        if (MODE == DM_FWD2) y = 2 * y + odd - 1;
-        const int x = MODE == DM_S1 ? t.x0 - 1 + c : MODE == DM_FWD2 ? 2 * t.x0 - 1 + c : t.x0 + c;
-        const bool ok = (int)row < (MODE == DM_FWD2 ? 2 * g.nrow : g.nrow) && c < q.IW && (unsigned)y < (unsigned)g.in_H && n < g.N &&
-                        (unsigned)x < (unsigned)g.in_W;
-        s.voff[k] = ok ? (uint32_t)((n * g.in_H + y) * g.in_W + x) * (uint32_t)(g.in_CH * 2) + (rem & 3u) * 16u : DM_OOB;
+        const int c = (int)(rem >> 2);
+        if (MODE == DM_S1) {
+            const int v = V0 + (int)row, x = t.x0 - 1 + c;
+            const bool ok = (int)row < g.nrow && c < q.IW && (unsigned)v < (unsigned)g.rows && (unsigned)x < (unsigned)g.in_W;
+            s.voff[k] = ok ? (uint32_t)(v * g.in_W + x) * (uint32_t)(g.in_CH * 2) + (rem & 3u) * 16u : DM_OOB;
+        } else {
+            const int odd = MODE == DM_FWD2 && (int)row >= g.nrow;
+            const uint32_t v = V0 + row - (odd ? g.nrow : 0);
+            const int n = (int)pc_udiv(v, g.mg_H1);
+            int y = (int)v - n * (g.H + 1);
+            if (MODE == DM_FWD2) y = 2 * y + odd - 1;
+            const int x = MODE == DM_FWD2 ? 2 * t.x0 - 1 + c : t.x0 + c;
+            const bool ok = (int)row < (MODE == DM_FWD2 ? 2 * g.nrow : g.nrow) && c < q.IW && (unsigned)y < (unsigned)g.in_H && n < g.N &&
+                            (unsigned)x < (unsigned)g.in_W;
+            s.voff[k] = ok ? (uint32_t)((n * g.in_H + y) * g.in_W + x) * (uint32_t)(g.in_CH * 2) + (rem & 3u) * 16u : DM_OOB;
+        }
         s.part |= (rem & 3u) << (2 * k);
     }
 }
@@ -167,21 +183,11 @@ __device__ __forceinline__ void dm_issue_input(const DmaWave &s, const DmaArgs &
     }
 }
 
-template <int MODE, int AT, int NBW, int FR = 4>
-__device__ __forceinline__ void dm_issue(const DmaWave &s, const DmaArgs &g, int nB, int mt, int ch, int lb)
-{
-    // (the wavefront's number is hidden from the compiler here: it would compute all scalar offsets ahead and spill them)
-    int w = s.w;
-    asm volatile("" : "+s"(w));
-    dm_issue_weights<MODE, AT, FR>(s, g, w, mt, ch, lb);
-    dm_issue_input<NBW>(s, g, w, nB, ch, lb + FR * (DM_A_BYTES / 4));
-}
-
-// The matrix instructions of one chunk; pa, pb: this lane's first weight and input fragment, RP: bytes per staged row, PL: from the
-// even to the odd staged rows (DM_FWD2). The weight fragments of a tap are read one tap ahead (two or three where a tap is 8 or 4
+// The matrix instructions of one chunk; pa: this lane's first weight fragment, pb: its first input fragments in the order in which the
+// tap rows are used. The weight fragments of a tap are read one tap ahead (two or three where a tap is 8 or 4
 // instructions); the input fragments of the next tap row replace those of this one as its last tap has used them.
 template <int MODE, int AT, int BT, int FR = 4>
-__device__ __forceinline__ void dm_chunk(f32x4 (&acc)[AT][MODE == DM_BWD2 ? 4 * BT : BT], const unsigned char *pa, const unsigned char *pb, int RP, int PL)
+__device__ __forceinline__ void dm_chunk(f32x4 (&acc)[AT][MODE == DM_BWD2 ? 4 * BT : BT], const unsigned char *pa, const DmaRows &pb)
 {
     constexpr int D = AT * BT <= 4 ? 3 : AT * BT <= 8 ? 2 : 1, NF = MODE == DM_S1 ? BT + 2 : MODE == DM_FWD2 ? 2 * BT + 1 : BT + 1;
     bf16x8 aq[D + 1][AT], bq[NF];
@@ -190,12 +196,12 @@ __device__ __forceinline__ void dm_chunk(f32x4 (&acc)[AT][MODE == DM_BWD2 ? 4 * 
 #pragma unroll
         for (int a = 0; a < AT; ++a) aq[d][a] = *reinterpret_cast<const bf16x8 *>(pa + (d * FR + a) * 1024);
 #pragma unroll
-    for (int c = 0; c < NF; ++c) bq[c] = *reinterpret_cast<const bf16x8 *>(pb + c * 64);
+    for (int c = 0; c < NF; ++c) bq[c] = *reinterpret_cast<const bf16x8 *>(pb.p[0] + c * 64);
 #pragma unroll
     for (int t = 0; t < 9; ++t) {
         const int r = dm_tap<MODE>(t) / 3, q = dm_tap<MODE>(t) % 3;
         const bool refill = t == 5 || (t == 2 && MODE != DM_BWD2);
-        const unsigned char *pn = pb + (MODE == DM_S1 ? (t / 3 + 1) * RP : MODE == DM_FWD2 && t == 2 ? PL : RP);   // the next tap row
+        const unsigned char *pn = pb.p[t < 3 ? 1 : 2];                      // the next tap row
         const int cls = MODE == DM_BWD2 ? ((r != 1) * 2 + (q != 1)) * BT : 0;
         auto read = [&](int c) { bq[c] = *reinterpret_cast<const bf16x8 *>(pn + c * 64); };
         if (t == 3) __builtin_amdgcn_s_setprio(1);
@@ -232,20 +238,53 @@ __device__ __forceinline__ void dm_chunk(f32x4 (&acc)[AT][MODE == DM_BWD2 ? 4 * 
     }
 }
 
-// Where a lane of a wavefront reads a tile, and the wavefront's sums of a finished tile on their way out through the LDS at stg
-// (of this wavefront alone): 64 pixels at a time, so that 8 lanes store the 128 bytes of a pixel.
-__device__ __forceinline__ int dm_lane_row(const DmaWave &s, const DmaArgs &g, const DmaTile &t)
+// Where a lane of a wavefront reads a tile: byte offsets in an input buffer of the three tap rows (stride 2: of the staged row).
+template <int MODE, int BT>
+__device__ __forceinline__ void dm_lane_rows(const DmaWave &s, const DmaArgs &g, const DmaGeo &q, const DmaTile &t, int (&at)[3])
 {
     // rows past the last one are multiplied with the last one's operands and not stored
-    const int row = t.r0 + s.rg * 16 + (s.lane & 15), rowc = row < g.rows ? row : g.rows - 1;
-    return rowc + (int)pc_udiv((uint32_t)rowc, g.mg_H) - (t.r0 + (int)pc_udiv((uint32_t)t.r0, g.mg_H));
+    const int row = t.r0 + s.rg * 16 + (s.lane & 15), rowc = row < g.rows ? row : g.rows - 1, RP = q.EPR * 16;
+    const int n = (int)pc_udiv((uint32_t)rowc, g.mg_H), left = (s.lane >> 4) * 16 + s.cg * (BT * (MODE == DM_FWD2 ? 128 : 64));
+    if (MODE == DM_S1) {
+        const int y = rowc - n * g.H;
+        at[0] = (rowc - t.r0) * RP + left; at[1] = at[0] + RP; at[2] = at[1] + RP;
+        if (y == 0) at[0] = q.zero + (at[0] & 255);
+        if (y == g.H - 1) at[2] = q.zero + (at[2] & 255);
+    } else {
+        at[0] = (rowc + n - (t.r0 + (int)pc_udiv((uint32_t)t.r0, g.mg_H))) * RP + left;
+        at[1] = at[0] + (MODE == DM_FWD2 ? g.nrow * RP : RP);
+        at[2] = at[0] + RP;
+    }
 }
 
-// (DM_BWD2: of parity class CLS)
+__device__ __forceinline__ DmaRows dm_rows(const unsigned char *buf, const int (&at)[3]) { return {{buf + at[0], buf + at[1], buf + at[2]}}; }
+
+// A wavefront's sums of a finished tile go out through the LDS at stg (of this wavefront alone): 64 pixels at a time, so that 8 lanes
+// store the 128 bytes of a pixel.
+// Output offset of the 16 bytes that this lane stores in step it of the columns from j0 on (DM_BWD2: of parity class CLS).
+template <int MODE, int AT, int BT, int CLS>
+__device__ __forceinline__ uint32_t dm_out_offset(const DmaWave &s, const DmaArgs &g, const DmaTile &t, int m0, int j0, int it)
+{
+    constexpr int LPP = 2 * AT, PXI = 64 / LPP;
+    const int px = it * PXI + s.lane / LPP;
+    const int row = t.r0 + s.rg * 16 + (px & 15), m = m0 + (s.lane % LPP) * 8;
+    int x = t.x0 + s.cg * BT + j0 + (px >> 4), orow = row;
+    bool ok = row < g.rows && m < g.out_CH;
+    if (MODE == DM_BWD2) {
+        const int n = (int)pc_udiv((uint32_t)row, g.mg_H), y = 2 * (row - n * g.H) + CLS / 2;
+        x = 2 * x + CLS % 2;
+        orow = n * g.out_H + y;
+        ok = ok && y < g.out_H;
+    }
+    ok = ok && x < g.out_W;
+    return ok ? (uint32_t)(orow * g.out_W + x) * (uint32_t)(g.out_CH * 2) + (uint32_t)(m * 2) : DM_OOB;
+}
+
+// ahead: the mask elements of the tile (BT <= 4), or null
 template <int MODE, int AT, int BT, int CLS, int ACT>
 __device__ __forceinline__ void dm_store(const DmaWave &s, const DmaArgs &g, const DmaTile &t, int m0,
                                          const f32x4 (&acc)[AT][MODE == DM_BWD2 ? 4 * BT : BT], unsigned char *stg,
-                                         __amdgpu_buffer_rsrc_t osrc, __amdgpu_buffer_rsrc_t msrc)
+                                         __amdgpu_buffer_rsrc_t osrc, __amdgpu_buffer_rsrc_t msrc, const v4u32 *ahead = nullptr)
 {
     constexpr int LPP = 2 * AT, PXI = 64 / LPP, PITCH = 32 * AT + 16;     // lanes per pixel, pixels per store, bytes per pixel in LDS
 #pragma unroll
@@ -256,19 +295,8 @@ __device__ __forceinline__ void dm_store(const DmaWave &s, const DmaArgs &g, con
         uint32_t off[FULL * 16 / PXI];
 #pragma unroll
         for (int it = 0; it < NC * 16 / PXI; ++it) {
-            const int px = it * PXI + s.lane / LPP;
-            const int row = t.r0 + s.rg * 16 + (px & 15), m = m0 + (s.lane % LPP) * 8;
-            int x = t.x0 + s.cg * BT + j0 + (px >> 4), orow = row;
-            bool ok = row < g.rows && m < g.out_CH;
-            if (MODE == DM_BWD2) {
-                const int n = (int)pc_udiv((uint32_t)row, g.mg_H), y = 2 * (row - n * g.H) + CLS / 2;
-                x = 2 * x + CLS % 2;
-                orow = n * g.out_H + y;
-                ok = ok && y < g.out_H;
-            }
-            ok = ok && x < g.out_W;
-            off[it] = ok ? (uint32_t)(orow * g.out_W + x) * (uint32_t)(g.out_CH * 2) + (uint32_t)(m * 2) : DM_OOB;
-            if (ACT == PC_ACT_RELU_MASK) mk[it] = __builtin_amdgcn_raw_buffer_load_b128(msrc, (int)off[it], 0, 0);
+            off[it] = dm_out_offset<MODE, AT, BT, CLS>(s, g, t, m0, j0, it);
+            if (ACT == PC_ACT_RELU_MASK) mk[it] = ahead ? ahead[it] : __builtin_amdgcn_raw_buffer_load_b128(msrc, (int)off[it], 0, 0);
         }
 #pragma unroll
         for (int j = 0; j < NC; ++j)
@@ -305,19 +333,24 @@ template <int AT, int BT, int ACT>
 __device__ __forceinline__ void dm_one_tile(DmaWave &s, const DmaArgs &g, const DmaGeo &q, unsigned char *lds, __amdgpu_buffer_rsrc_t osrc,
                                             __amdgpu_buffer_rsrc_t msrc, const DmaTile &t, bool &fresh)
 {
-    dm_offsets<DM_S1>(s, g, q, t);
+    dm_offsets<DM_S1, 0>(s, g, q, t);
     const unsigned char *pa = lds + s.lane * 16;
-    const unsigned char *pb = lds + AT * (DM_A_BYTES / 4) + dm_lane_row(s, g, t) * (q.EPR * 16) + (s.lane >> 4) * 16 + s.cg * (BT * 64);
+    int rows[3];
+    dm_lane_rows<DM_S1, BT>(s, g, q, t, rows);
+    const DmaRows pb = dm_rows(lds + AT * (DM_A_BYTES / 4), rows);
     f32x4 acc[AT][BT];
     dm_zero<AT, BT>(acc);
     for (int ch = 0; ch < g.nch; ++ch) {
         if (!fresh) asm volatile("s_barrier" ::: "memory");      // every wavefront has read what the loads replace
         fresh = false;
         __builtin_amdgcn_s_setprio(3);
-        dm_issue<DM_S1, AT, 0, AT>(s, g, q.nB, t.mt, ch, 0);
+        int w = s.w;       // (hidden from the compiler here and below: it would compute all scalar offsets ahead and spill them)
+        asm volatile("" : "+s"(w));
+        dm_issue_weights<DM_S1, AT, AT>(s, g, w, t.mt, ch, 0);
+        dm_issue_input<0>(s, g, w, q.nB, ch, AT * (DM_A_BYTES / 4));
         __builtin_amdgcn_s_setprio(0);
         dm_wait_barrier<0>();
-        dm_chunk<DM_S1, AT, BT, AT>(acc, pa, pb, q.EPR * 16, 0);
+        dm_chunk<DM_S1, AT, BT, AT>(acc, pa, pb);
     }
     __builtin_amdgcn_s_setprio(3);
     asm volatile("s_barrier" ::: "memory");
@@ -403,17 +436,21 @@ pc_mfma_conv_solo_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__
         s.a_voff = dm_weight_offset<AT>(g, s.lane);
         const int nB = q.nB, chunks = ntile * nch;
         DmaTile t = tile_at(0);
-        dm_offsets<MODE>(s, g, q, t);
+        dm_issue_weights<MODE, AT, 4>(s, g, s.w, t.mt, 0, 0);      // (on their way while the offsets are made)
+        dm_offsets<MODE, NBW>(s, g, q, t);
         int k = 0, ch = 0, at = 0, done = 0;       // cursor: tile, chunk, buffer; chunks issued
         auto next = [&]() {
-            dm_issue<MODE, AT, NBW>(s, g, nB, t.mt, ch, at);
+            int w = s.w;
+            asm volatile("" : "+s"(w));
+            if (done) dm_issue_weights<MODE, AT, 4>(s, g, w, t.mt, ch, at);
+            dm_issue_input<NBW>(s, g, w, nB, ch, at + DM_A_BYTES);
             at = at + buf_bytes == NBUF * buf_bytes ? 0 : at + buf_bytes;
             ++done;
             if (++ch == nch) {
                 ch = 0;
                 if (++k < ntile) {
                     t = tile_at(k);
-                    dm_offsets<MODE>(s, g, q, t);
+                    dm_offsets<MODE, NBW>(s, g, q, t);
                 }
             }
         };
@@ -435,7 +472,7 @@ pc_mfma_conv_solo_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__
     const __amdgpu_buffer_rsrc_t osrc = __builtin_amdgcn_make_buffer_rsrc(out, 0, g.out_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t msrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint16_t *>(ACT == PC_ACT_RELU_MASK ? g.act_mask : out), 0, g.out_bytes, 0x00020000);
-    const int RP = q.EPR * 16, PL = g.nrow * RP, half = AT == 2 ? s.w & 1 : 0;
+    const int half = AT == 2 ? s.w & 1 : 0;
     // Weights come from the last cache or from memory after other layers' work, chunk by chunk, each with that latency and two chunks ahead
     // at most. These wavefronts wait for the first chunk anyway: together the workgroups of an XCD that share a row tile touch every
     // 128-byte line of its weights once, so that the chunks come from L2. (In a step of many layers, 128 images 4 x 4 512 -> 512
@@ -454,13 +491,20 @@ pc_mfma_conv_solo_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__
     for (int k = 0; k < ntile; ++k) {
         const DmaTile t = tile_at(k);
         const unsigned char *pa = lds + s.lane * 16 + half * 2048;
-        const unsigned char *pb = lds + DM_A_BYTES + dm_lane_row(s, g, t) * RP + (s.lane >> 4) * 16 + s.cg * (BT * (MODE == DM_FWD2 ? 128 : 64));
+        int rows[3];
+        dm_lane_rows<MODE, BT>(s, g, q, t, rows);
+        v4u32 mk[BT * AT / 2];
+        if (ACT == PC_ACT_RELU_MASK) {
+#pragma unroll
+            for (int i = 0; i < BT * AT / 2; ++i)
+                mk[i] = __builtin_amdgcn_raw_buffer_load_b128(msrc, (int)dm_out_offset<MODE, AT, BT, 0>(s, g, t, t.mt * 64 + half * 32, 0, i), 0, 0);
+        }
         f32x4 acc[AT][MODE == DM_BWD2 ? 4 * BT : BT];
         dm_zero(acc);
         int used = 0;
         for (int ch = 0; ch < nch; ++ch) {
             asm volatile("s_barrier" ::: "memory");
-            dm_chunk<MODE, AT, BT>(acc, pa + at, pb + at, RP, PL);
+            dm_chunk<MODE, AT, BT>(acc, pa + at, dm_rows(lds + DM_A_BYTES + at, rows));
             used = at;
             at = at + buf_bytes == NBUF * buf_bytes ? 0 : at + buf_bytes;
         }
@@ -468,7 +512,7 @@ pc_mfma_conv_solo_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__
 #pragma unroll
         for (int i = 0; i < 4; ++i) asm volatile("" :: "v"(touched[i]));      // (no earlier: the wait for them stands here)
         unsigned char *stg = lds + used + s.w * (64 * (32 * AT + 16));
-        dm_store<MODE, AT, BT, 0, ACT>(s, g, t, t.mt * 64 + half * 32, acc, stg, osrc, msrc);
+        dm_store<MODE, AT, BT, 0, ACT>(s, g, t, t.mt * 64 + half * 32, acc, stg, osrc, msrc, ACT == PC_ACT_RELU_MASK ? mk : nullptr);
         if constexpr (MODE == DM_BWD2) {
             dm_store<MODE, AT, BT, 1, ACT>(s, g, t, t.mt * 64 + half * 32, acc, stg, osrc, msrc);
             dm_store<MODE, AT, BT, 2, ACT>(s, g, t, t.mt * 64 + half * 32, acc, stg, osrc, msrc);
@@ -509,7 +553,7 @@ pc_mfma_conv_keep_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__
         s.a_voff = dm_weight_offset<AT>(g, s.lane);
         const int chunks = ntile * nch;
         DmaTile t = tile_at(0);
-        dm_offsets<DM_S1>(s, g, q, t);
+        dm_offsets<DM_S1, NBW>(s, g, q, t);
         int k = 0, ch = 0, at = x0, done = 0;      // cursor: tile, chunk, buffer; chunks issued
         auto next = [&]() {
             int w = s.w;
@@ -521,7 +565,7 @@ pc_mfma_conv_keep_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__
                 ch = 0;
                 if (++k < ntile) {
                     t = tile_at(k);
-                    dm_offsets<DM_S1>(s, g, q, t);
+                    dm_offsets<DM_S1, NBW>(s, g, q, t);
                 }
             }
         };
@@ -542,7 +586,7 @@ pc_mfma_conv_keep_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__
     const __amdgpu_buffer_rsrc_t osrc = __builtin_amdgcn_make_buffer_rsrc(out, 0, g.out_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t msrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint16_t *>(ACT == PC_ACT_RELU_MASK ? g.act_mask : out), 0, g.out_bytes, 0x00020000);
-    const int RP = q.EPR * 16, pix = g.out_CH * 2;
+    const int pix = g.out_CH * 2;
     unsigned char *stg = lds + x0 + 3 * BUF + s.w * (2 * 16 * PITCH);
     // (rows of 128 bytes: their 16-byte pieces are stored in turned order, or all pixels' would stand in the same banks)
     auto piece = [&](int px, int i) { return AT == 4 ? i ^ (px & 7) : i; };
@@ -550,7 +594,8 @@ pc_mfma_conv_keep_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__
     for (int k = 0; k < ntile; ++k) {
         const DmaTile t = tile_at(k);
         const unsigned char *pa = lds + s.lane * 16;
-        const unsigned char *pb = lds + dm_lane_row(s, g, t) * RP + (s.lane >> 4) * 16 + s.cg * (BT * 64);
+        int rows[3];
+        dm_lane_rows<DM_S1, BT>(s, g, q, t, rows);
         uint32_t off[IT];                          // of this lane's pixels in column 0 of the map
         v4u32 mk[BT][IT];
 #pragma unroll
@@ -569,7 +614,7 @@ pc_mfma_conv_keep_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__
         dm_zero<AT, BT>(acc);
         for (int ch = 0; ch < nch; ++ch) {
             asm volatile("s_barrier" ::: "memory");
-            dm_chunk<DM_S1, AT, BT, AT>(acc, pa + ch * WB, pb + at, RP, 0);
+            dm_chunk<DM_S1, AT, BT, AT>(acc, pa + ch * WB, dm_rows(lds + at, rows));
             at = at == x0 + 2 * BUF ? x0 : at + BUF;
         }
 #pragma unroll
@@ -659,7 +704,8 @@ pc_mfma_conv_ring_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__
         };
         DmaTile tx = tw;
         int kx = 0, chx = 0, at = 0;
-        dm_offsets<DM_FWD2>(s, g, q, tx);
+        weights();                                // (on their way while the offsets are made)
+        dm_offsets<DM_FWD2, 11>(s, g, q, tx);
         auto input = [&](auto part) {          // 0: the first 6 loads, 1: the other 5, and on to the next chunk
             const bool cut = chx == nch - 1 && (g.in_CH & (DM_KC - 1));
             const uint32_t parts = (uint32_t)(g.in_CH & (DM_KC - 1)) >> 3;
@@ -675,19 +721,16 @@ pc_mfma_conv_ring_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__
                     chx = 0;
                     if (++kx < ntile) {
                         tx = tile_at(kx);
-                        dm_offsets<DM_FWD2>(s, g, q, tx);
+                        dm_offsets<DM_FWD2, 11>(s, g, q, tx);
                     }
                 }
             }
         };
         using first = std::integral_constant<int, 0>;
         using rest = std::integral_constant<int, 1>;
-        if (steps) {
-            input(first());
-            input(rest());
-            weights();
-            weights();
-        }
+        input(first());
+        input(rest());
+        weights();
         int newer = 6, r = 0, left = nch;         // newer: loads of the last step, which nothing waits for yet
         for (int i = 0; i < steps; ++i) {
             if (newer == 12) dm_wait_barrier<12>();
@@ -711,12 +754,12 @@ pc_mfma_conv_ring_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__
         return;
     }
     const __amdgpu_buffer_rsrc_t osrc = __builtin_amdgcn_make_buffer_rsrc(out, 0, g.out_bytes, 0x00020000);
-    const int RP = q.EPR * 16, PL = g.nrow * RP;
     int at = 0, slot = 0;
     for (int k = 0; k < ntile; ++k) {
         const DmaTile t = tile_at(k);
         const unsigned char *pa = lds + DR_W + s.lane * 16 + half * 4096;
-        const unsigned char *pb = lds + dm_lane_row(s, g, t) * RP + (s.lane >> 4) * 16 + s.cg * (4 * 128);
+        int rows[3];
+        dm_lane_rows<DM_FWD2, 4>(s, g, q, t, rows);
         f32x4 acc[4][4];
         dm_zero(acc);
         int used = 0;
@@ -725,7 +768,7 @@ pc_mfma_conv_ring_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__
 #pragma unroll
             for (int r = 0; r < 3; ++r) {
                 asm volatile("s_barrier" ::: "memory");
-                const unsigned char *pw = pa + slot, *pr = pb + at;
+                const unsigned char *pw = pa + slot, *pr = lds + at + rows[0];
                 slot = slot == 2 * DR_SLOT ? 0 : slot + DR_SLOT;
 #pragma unroll
                 for (int a = 0; a < 4; ++a) aq[0][a] = *reinterpret_cast<const bf16x8 *>(pw + a * 1024);
@@ -733,7 +776,7 @@ pc_mfma_conv_ring_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__
 #pragma unroll
                     for (int c = 0; c < 9; ++c) bq[c] = *reinterpret_cast<const bf16x8 *>(pr + c * 64);
                 }
-                const unsigned char *pn = pr + (r == 0 ? PL : RP);
+                const unsigned char *pn = lds + at + rows[r == 0 ? 1 : 2];
 #pragma unroll
                 for (int u = 0; u < 3; ++u) {
                     const bool refill = u == 2 && r < 2;       // (the input is there: the next row's fragments, before its weights)
@@ -803,27 +846,37 @@ static bool plan_dma(const MfmaArgs &g, bool flip, const DmaCand &cand, int lgCG
     // image boundaries inside a tile (tiles start at multiples of TR)
     int cross = t.H % t.TR == 0 ? 0 : t.TR % t.H == 0 ? t.TR / t.H - 1 : (t.TR - 1 + t.H - 1) / t.H;
     if (cross > g.N - 1) cross = g.N - 1;
-    t.nrow = t.TR + (cand.mode == DM_S1 ? 2 : 1) + cross;
+    t.nrow = cand.mode == DM_S1 ? t.TR + 2 : t.TR + 1 + cross;
     const int staged = cand.mode == DM_FWD2 ? 2 * t.nrow : t.nrow;
+    const int most = cand.at == 8 ? DR_B : 4 * (keep ? DM_KEEP_NBW : cand.nbuf == 3 ? dm_nbw(cand.bt) : DM_NB);
     for (int l = 0; l < 3; ++l) {
         DmaGeo &q = t.geo[l];
-        const int tc = (cand.bt >> l) << lgCG;
+        const int bt = cand.bt >> l, tc = bt << lgCG;
         q.IW = cand.mode == DM_S1 ? tc + 2 : cand.mode == DM_FWD2 ? 2 * tc + 1 : tc + 1;
-        q.EPR = (DM_KC / 8) * q.IW + 1;
+        for (int pad = 2; pad >= 1; --pad) {       // (one element where two do not fit)
+            q.EPR = (DM_KC / 8) * q.IW + pad;
+            int elements = staged * q.EPR;
+            if (cand.mode == DM_S1) {              // zeros: 256 bytes and the fragments of a row
+                elements = (elements + 15) / 16 * 16;
+                q.zero = elements * 16;
+                elements += 16 + 4 * (bt + 2);
+            }
+            q.nB = (elements + 63) / 64;
+            if (q.nB <= most && (keep || cand.at == 8 || ((narrow ? DM_A_BYTES / 2 : DM_A_BYTES) + q.nB * 1024) * (cand.nbuf == 3 ? 1 : cand.nbuf) <= DM_LDS_MAX / (cand.nbuf == 1 ? 2 : 1))) break;
+        }
         q.mg_EPR = pc_udiv_magic(q.EPR);
-        q.nB = (staged * q.EPR + 63) / 64;
     }
     const int nB = t.geo[0].nB, TC = cand.bt << lgCG;
-    if (cand.at == 8 && nB > DR_B) return false;
+    if (nB > most) return false;
     t.buf_bytes = cand.at == 8 ? DM_LDS_MAX / 2 : (narrow ? DM_A_BYTES / 2 : DM_A_BYTES) + (uint32_t)(cand.nbuf == 3 ? 4 * dm_nbw(cand.bt) : nB) * 1024;
     if (keep) {
         t.buf_bytes = 4 * DM_KEEP_NBW * 1024;
         *lds = t.nch * (size_t)(narrow ? DM_A_BYTES / 2 : DM_A_BYTES) + 3 * (size_t)t.buf_bytes + 4 * 2 * 16 * (narrow ? 80 : 128);
-        if (nB > 4 * DM_KEEP_NBW || *lds > (size_t)DM_LDS_MAX) return false;
+        if (*lds > (size_t)DM_LDS_MAX) return false;
     }
     if (!keep && narrow && t.buf_bytes < 4 * 64 * DM_STG) t.buf_bytes = 4 * 64 * DM_STG;      // (the tile leaves through it)
     if (!keep) *lds = (size_t)t.buf_bytes * cand.nbuf;
-    if (!keep && (nB > 4 * (cand.nbuf == 3 ? dm_nbw(cand.bt) : DM_NB) || *lds > (size_t)DM_LDS_MAX / (cand.nbuf == 1 ? 2 : 1))) return false;
+    if (!keep && *lds > (size_t)DM_LDS_MAX / (cand.nbuf == 1 ? 2 : 1)) return false;
     t.tiles_x = (t.W + TC - 1) / TC;
     const int64_t p_tiles = (rows + t.TR - 1) / t.TR * t.tiles_x;
     const int m_tiles = (g.out_CH + rows_m - 1) / rows_m;
