@@ -106,9 +106,12 @@ __device__ __forceinline__ DmaTile dm_tile(const DmaArgs &g, int t, int sh)
 }
 
 // The elements of a tile that this lane loads (NBW > 0: NBW of them): element e of the tile is the 16-byte part e % EPR of staged row e / EPR.
-template <int MODE, int NBW>
-__device__ __forceinline__ void dm_offsets(DmaWave &s, const DmaArgs &g, const DmaGeo &q, const DmaTile &t)
+// ASK: and asks for the first chunk of each at once, into the buffer at lb (with all offsets made first a launch's first pixels were asked for 0.4
+// to 1 us later).
+template <int MODE, int NBW, bool ASK = false>
+__device__ __forceinline__ void dm_offsets(DmaWave &s, const DmaArgs &g, const DmaGeo &q, const DmaTile &t, int lb = 0)
 {
+    const uint32_t parts = g.nch == 1 && (g.in_CH & (DM_KC - 1)) ? (uint32_t)(g.in_CH & (DM_KC - 1)) >> 3 : 4u;
     const int V0 = MODE == DM_S1 ? t.r0 - 1 : t.r0 + (int)pc_udiv((uint32_t)t.r0, g.mg_H);
     s.part = 0;
     int lane = s.lane;      // (hidden from the compiler: it would keep the quotients of all elements from tile to tile, in scratch)
@@ -135,6 +138,7 @@ __device__ __forceinline__ void dm_offsets(DmaWave &s, const DmaArgs &g, const D
             s.voff[k] = ok ? (uint32_t)((n * g.in_H + y) * g.in_W + x) * (uint32_t)(g.in_CH * 2) + (rem & 3u) * 16u : DM_OOB;
         }
         s.part |= (rem & 3u) << (2 * k);
+        if (ASK) dm_load(s.xs, (int)((rem & 3u) >= parts ? DM_OOB : s.voff[k]), 0, lb + (s.w + 4 * k) * 1024);
     }
 }
 
@@ -437,13 +441,15 @@ pc_mfma_conv_solo_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__
         const int nB = q.nB, chunks = ntile * nch;
         DmaTile t = tile_at(0);
         dm_issue_weights<MODE, AT, 4>(s, g, s.w, t.mt, 0, 0);      // (on their way while the offsets are made)
-        dm_offsets<MODE, NBW>(s, g, q, t);
+        dm_offsets<MODE, NBW, true>(s, g, q, t, DM_A_BYTES);
         int k = 0, ch = 0, at = 0, done = 0;       // cursor: tile, chunk, buffer; chunks issued
         auto next = [&]() {
             int w = s.w;
             asm volatile("" : "+s"(w));
-            if (done) dm_issue_weights<MODE, AT, 4>(s, g, w, t.mt, ch, at);
-            dm_issue_input<NBW>(s, g, w, nB, ch, at + DM_A_BYTES);
+            if (done) {
+                dm_issue_weights<MODE, AT, 4>(s, g, w, t.mt, ch, at);
+                dm_issue_input<NBW>(s, g, w, nB, ch, at + DM_A_BYTES);
+            }
             at = at + buf_bytes == NBUF * buf_bytes ? 0 : at + buf_bytes;
             ++done;
             if (++ch == nch) {
@@ -553,12 +559,13 @@ pc_mfma_conv_keep_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__
         s.a_voff = dm_weight_offset<AT>(g, s.lane);
         const int chunks = ntile * nch;
         DmaTile t = tile_at(0);
-        dm_offsets<DM_S1, NBW>(s, g, q, t);
+        dm_issue_weights<DM_S1, AT, AT>(s, g, s.w, 0, 0, 0);
+        dm_offsets<DM_S1, NBW, true>(s, g, q, t, x0);
         int k = 0, ch = 0, at = x0, done = 0;      // cursor: tile, chunk, buffer; chunks issued
         auto next = [&]() {
             int w = s.w;
             asm volatile("" : "+s"(w));
-            dm_issue_input<NBW>(s, g, w, 0, ch, at);
+            if (done) dm_issue_input<NBW>(s, g, w, 0, ch, at);
             at = at == x0 + 2 * BUF ? x0 : at + BUF;
             ++done;
             if (++ch == nch) {
@@ -569,7 +576,6 @@ pc_mfma_conv_keep_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__
                 }
             }
         };
-        dm_issue_weights<DM_S1, AT, AT>(s, g, s.w, 0, 0, 0);
         next();
         if (nch == 2) dm_issue_weights<DM_S1, AT, AT>(s, g, s.w, 0, 1, WB);
         if (done < chunks) next();
@@ -705,7 +711,8 @@ pc_mfma_conv_ring_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__
         DmaTile tx = tw;
         int kx = 0, chx = 0, at = 0;
         weights();                                // (on their way while the offsets are made)
-        dm_offsets<DM_FWD2, 11>(s, g, q, tx);
+        dm_offsets<DM_FWD2, 11, true>(s, g, q, tx, 0);
+        bool ask = false;                         // (the first chunk: on its way)
         auto input = [&](auto part) {          // 0: the first 6 loads, 1: the other 5, and on to the next chunk
             const bool cut = chx == nch - 1 && (g.in_CH & (DM_KC - 1));
             const uint32_t parts = (uint32_t)(g.in_CH & (DM_KC - 1)) >> 3;
@@ -713,7 +720,7 @@ pc_mfma_conv_ring_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__
             for (int i = decltype(part)::value ? 6 : 0; i < (decltype(part)::value ? 11 : 6); ++i) {
                 uint32_t vo = s.voff[i];
                 if (cut) vo = ((s.part >> (2 * i)) & 3u) >= parts ? DM_OOB : vo;
-                dm_load(s.xs, (int)vo, chx * (DM_KC * 2), at + (s.w + 4 * i) * 1024);
+                if (ask) dm_load(s.xs, (int)vo, chx * (DM_KC * 2), at + (s.w + 4 * i) * 1024);
             }
             if (decltype(part)::value) {
                 at = DR_B * 1024 - at;
@@ -730,6 +737,7 @@ pc_mfma_conv_ring_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__
         using rest = std::integral_constant<int, 1>;
         input(first());
         input(rest());
+        ask = true;
         weights();
         int newer = 6, r = 0, left = nch;         // newer: loads of the last step, which nothing waits for yet
         for (int i = 0; i < steps; ++i) {
