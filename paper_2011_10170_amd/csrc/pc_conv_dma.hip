@@ -403,11 +403,11 @@ pc_mfma_conv_dma_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__ 
 // wavefront issues in order, and 48 to 77 KiB of loads take 800 to 1200 cycles to be accepted: with the loads in the multiplying
 // wavefronts a chunk of the smaller tiles took twice its matrix instructions). AT = 2: the wavefronts are two halves of the
 // channels x two groups of pixels, tiles of 64 x 128 (BT = 4) and 64 x 64 (BT = 2).
-// What bounds it: a chunk of 64 x 256, 128 and 64 pixels takes 1.03, 0.55 and 0.39 us for 0.96, 0.48 and 0.24 us of matrix
+// What bounds it: a chunk of 64 x 256, 128 and 64 pixels takes 1.15, 0.64 and 0.39 us for 0.96, 0.48 and 0.24 us of matrix
 // instructions; below 64 x 128 the direct loads (48 KiB a chunk, of them 36 KiB weights that all row tiles load again). With a launch and
-// the first loads and last stores around them, 128 images (us, the kernel chosen without this one -> here): 16 x 16
-// 128 -> 128 11.2 -> 10.3, 8 x 8 256 -> 256 11.9 -> 9.9, 4 x 4 512 -> 512 12.2 -> 11.2, 4 x 4 256 -> 512 8.3 -> 7.4; 64 images 7 x 7
-// 512 -> 512 17.3 -> 15.6; one image 56 x 56 256 -> 256 7.7 -> 6.8, 224 x 224 64 -> 64 9.4 -> 7.6.
+// the first loads (2 us) and last stores around them, 128 images (us, the kernel chosen without this one -> here): 16 x 16
+// 128 -> 128 11.2 -> 9.9, 8 x 8 256 -> 256 11.9 -> 9.2, 4 x 4 512 -> 512 12.2 -> 10.3, 4 x 4 256 -> 512 8.3 -> 7.0; 64 images 7 x 7
+// 512 -> 512 17.3 -> 14.0; one image 56 x 56 256 -> 256 7.7 -> 6.7, 224 x 224 64 -> 64 9.4 -> 7.6.
 // Stride 2, backward-data: the same nine taps per chunk and fewer staged columns, 128 images 8 x 8 256 -> 512 16.9 -> 10.8, 64 images
 // 14 x 14 256 -> 512 17.7 -> 11.3, 56 x 56 128 -> 128 25.7 -> 23.0 (its bytes). Forward: 2 * BT + 1 fragments per row and four staged
 // pixels per output pixel make LDS the bound, 0.9 us a chunk of 64 x 128 for 0.48 of matrix instructions (1.5 where the input comes from
@@ -826,8 +826,8 @@ struct DmaTimes { double chunk, load, tile, start, bytes; };
 #define DM_KEEP_NBW 6                // direct loads of a chunk per loading wavefront where the weights stay in LDS
 struct DmaCand { int code, mode, at, bt, nbuf; DmaTimes solo; };       // nbuf 1: two workgroups per CU; 4: the weights stay in LDS beside three
 static const DmaCand kDma[] = {
-    {40, DM_S1, 4, 8, 1, {0, 0, 0, 3.3, 1}}, {41, DM_S1, 4, 4, 1, {0, 0, 0, 3.3, 1}}, {42, DM_S1, 4, 7, 1, {0, 0, 0, 3.3, 1}},
-    {43, DM_S1, 2, 4, 3, {0.440, 0.0137, 0.491, 3.3, 1}}, {45, DM_S1, 4, 4, 2, {1.031, 0.0042, 1.038, 3.3, 1}}, {46, DM_S1, 2, 2, 3, {0.387, 0, 0.445, 3.3, 1}},
+    {40, DM_S1, 4, 8, 1, {0, 0, 0, 2.93, 1.07}}, {41, DM_S1, 4, 4, 1, {0, 0, 0, 2.73, 1.04}}, {42, DM_S1, 4, 7, 1, {0, 0, 0, 2.90, 0.89}},
+    {43, DM_S1, 2, 4, 3, {0.639, 0, 0.530, 2.72, 0.70}}, {45, DM_S1, 4, 4, 2, {1.152, 0.0009, 0.80, 2.95, 0.85}}, {46, DM_S1, 2, 2, 3, {0.368, 0.0037, 0.487, 2.65, 0.69}},
     {47, DM_FWD2, 2, 4, 2, {0.976, 0, 1.296, 2.7, 0.78}}, {49, DM_FWD2, 8, 4, 2, {1.5, 0, 1.8, 2.6, 0.7}}, {48, DM_FWD2, 2, 2, 2, {0.716, 0, 1.275, 2.5, 0.78}},
     {50, DM_S1, 4, 4, 4, {0, 0, 0, 0, 0}},
     {37, DM_BWD2, 2, 4, 3, {0.504, 0.0087, 1.829, 3.1, 0.62}}, {38, DM_BWD2, 2, 2, 3, {0.348, 0.0082, 1.210, 2.9, 0.50}}};
@@ -902,24 +902,23 @@ static bool plan_dma(const MfmaArgs &g, bool flip, const DmaCand &cand, int lgCG
     // Estimated time (us). A round is one tile for each of the workgroups the chip holds, two per CU; a workgroup that has its CU to
     // itself takes its chunks faster. A chunk takes a fixed time and one for its direct loads of the input, a tile an end; the
     // tensors take their bytes (the input with its border, in pieces of 64) at 6 TB/s (7.9 where they come from the last cache, as
-    // in a loop over one layer). Constants for 8, 7, 4 and 2 columns per wavefront, and for the tiles of a lone workgroup, from 5000
-    // timings of 147 layer shapes (1 to 128 images, 4 x 4 to 224 x 224, 8 to 512 channels; 8 % rms); at stride 2 fits of 139 shapes, 5 to
-    // 11 % rms. On the 713 layers of profiles/plan_timings_bf16.csv, drawn afterwards, the choice, the register and cooperative kernels
-    // included, is 1.5 % behind the fastest at stride 1 (both passes), 1.0 % at stride 2 forward and 0.2 % backward, the worst 20 %;
-    // it is 11 % (stride 1), 4 % and 22 % (stride 2) ahead of the fastest of the kernels without direct loads.
+    // in a loop over one layer). Constants from 4700 timings of 485 layer shapes at stride 1 (1 to 128 images, 4 x 4 to
+    // 224 x 224, 8 to 512 channels, a half of them layers of networks; 5 to 8 % rms) and of 139 at stride 2. On the layers of
+    // profiles/plan_timings_bf16.csv the choice, the register and cooperative kernels included, is 1.4 % behind the fastest at stride 1 (both
+    // passes), 1.0 % at stride 2 forward and 0.3 % backward, the worst 22 %; on the 540 passes of networks 0.4 %.
     // What does not fill a round of tiles may be cut in halves or quarters, all of it or what a tile per CU leaves: 56 x 56,
     // 256 -> 256, batch 32 is 784 tiles of 8 columns for 512 workgroups; 512 + 256 tiles and 16 cut into 64 quarters
     // take 73 us instead of 81.
-    static const DmaTimes kPair[4] = {{2.627, 0.0391, 2.225}, {2.232, 0.0405, 2.374}, {1.779, 0.0215, 1.669}, {1.047, 0.0361, 1.416}};
-    static const DmaTimes kOne[4] = {{2.960, 0.0001, 1.658}, {2.614, 0.0, 1.425}, {1.693, 0.0038, 0.940}, {1.047, 0.0103, 0.671}};
-    // Up to 32 output channels: shares of these times (558 timings of 186 layers, 6.5 % rms; the choice among the three is 1.2 % behind the best).
+    static const DmaTimes kPair[4] = {{2.663, 0.0396, 2.256}, {2.151, 0.0391, 2.288}, {1.605, 0.0194, 1.506}, {0.996, 0.0344, 1.348}};
+    static const DmaTimes kOne[4] = {{3.001, 0.0001, 1.680}, {2.519, 0.0000, 1.373}, {1.527, 0.0034, 0.848}, {0.996, 0.0099, 0.638}};
+    // Up to 32 output channels: shares of these times, by tile width (660 timings of 220 layers, 4 to 6 % rms).
     // A chunk is half a line of a pixel: where the lines under way exceed the L2s (28 MB; all of them from 60 MB on) the next chunk fetches
     // them again (27 x 96 x 93, 360 -> 8: 81.8 us in tiles of 8 columns, 51.0 in tiles of 4).
-    static const DmaTimes kNarrow = {0.693, 0.460, 0.321, 3.3, 0.765};
-    auto tile_us = [&](const DmaTimes &c, int l) {
-        return narrow ? t.nch * (kNarrow.chunk * c.chunk + kNarrow.load * c.load * t.geo[l].nB) + kNarrow.tile * c.tile : t.nch * (c.chunk + c.load * t.geo[l].nB) + c.tile;
-    };
+    static const DmaTimes kNarrow[3] = {{0.669, 0.444, 0.310, 3.13, 0.833}, {0.614, 0.407, 0.285, 2.86, 0.75}, {0.645, 0.428, 0.299, 2.87, 0.809}};
     const int first = cand.bt == 8 ? 0 : cand.bt == 7 ? 1 : 2;
+    auto tile_us = [&](const DmaTimes &c, int l) {
+        return narrow ? t.nch * (kNarrow[first].chunk * c.chunk + kNarrow[first].load * c.load * t.geo[l].nB) + kNarrow[first].tile * c.tile : t.nch * (c.chunk + c.load * t.geo[l].nB) + c.tile;
+    };
     const int slots = num_cu * (cand.nbuf == 1 ? 2 : 1);
     t.rounds = (int)(total / slots);
     const int left = (int)(total % slots);
@@ -944,13 +943,13 @@ static bool plan_dma(const MfmaArgs &g, bool flip, const DmaCand &cand, int lgCG
     const double move = (in_moved + (double)out_bytes) / 6.0e6;
     if (keep) {
         // Weights in LDS: tiles one after the other and the tensors' bytes, by whether there are more than 32 output channels and more than one
-        // chunk (656 timings of 328 layers of up to 64 channels, 6 % rms; of two sets it is the
+        // chunk (376 timings of 188 layers of up to 64 channels, 3 to 7 % rms; of two sets it is the
         // fastest in 30 and 42 % of the passes, by up to 26 %; those of one chunk set by which kernel is the faster)
-        static const DmaTimes kKeep[2][2] = {{{0.950, 0, 0, 3.20, 0.394}, {1.556, 0, 0, 3.48, 0.250}}, {{1.432, 0, 0, 3.74, 0.490}, {2.844, 0, 0, 3.46, 0.415}}};
+        static const DmaTimes kKeep[2][2] = {{{0.857, 0, 0, 2.83, 0.426}, {1.330, 0, 0, 2.86, 0.419}}, {{0.64, 0, 0, 3.5, 0.9}, {2.72, 0, 0, 3.12, 0.447}}};
         const DmaTimes &c = kKeep[!narrow][t.nch - 1];
         *est = c.start + (t.rounds + (t.last > 0)) * c.chunk + c.bytes * move;
     } else {
-        *est = (narrow ? kNarrow.start : cand.solo.start) + pow(pow(best, 1.5) + pow((narrow ? kNarrow.bytes : cand.solo.bytes) * move, 1.5), 1.0 / 1.5);
+        *est = (narrow ? kNarrow[first].start : cand.solo.start) + pow(pow(best, 1.5) + pow((narrow ? kNarrow[first].bytes : cand.solo.bytes) * move, 1.5), 1.0 / 1.5);
     }
     const int busy = t.last + t.pieces;
     *grid = t.rounds > 0 || busy > slots ? slots : busy;
