@@ -69,7 +69,7 @@ def test_same_bits_without_scratch(B, dims):
         for _ in range(3):
             with torch.cuda.stream(stream):
                 got.fill_(float("nan"))
-            graph.replay()
+                graph.replay()            # (on this stream: behind the fill)
             torch.cuda.synchronize()
             assert torch.equal(got, want) and torch.equal(other, want)
         g.close()
