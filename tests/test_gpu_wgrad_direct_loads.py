@@ -145,7 +145,7 @@ def test_capture_without_room_for_the_partial_planes(B):
         for _ in range(3):
             with torch.cuda.stream(stream):
                 got.fill_(float("nan"))
-            graph.replay()
+                graph.replay()            # (on this stream: behind the fill)
             torch.cuda.synchronize()
             assert torch.equal(got, want)
         with torch.cuda.stream(stream):
