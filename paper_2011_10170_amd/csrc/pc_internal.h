@@ -67,8 +67,9 @@ static inline int32_t *pc_choice(pc_ctx *ctx, const int32_t (&key)[PC_CHOICE_KEY
     return &e->kernel;
 }
 
-// Float32 layers whose weights are split when they are packed. Their conv passes save the split of every workgroup (5 to 25 % of a pass), the
-// pack writes 108 bytes a kernel more, which is what a larger one is bound by (320 x 320 8.9 us with the parts and 8.0 without; 512 x 512 17.2, 11.9).
+// Float32 layers whose weights are split when they are packed. A forward or backward-data pass in tiles of 32 saves the split of every
+// workgroup (5 to 25 %); the pack writes 108 bytes a kernel more. New values cost no more with the parts up to 192 x 192 kernels, 0.8 us more
+// at 256 x 256 (3.9 -> 4.7) and 1.7 at 320 x 320 (4.2 -> 5.9); a pack 8.0 -> 8.7 there, and 11.9 -> 17.2 at 512 x 512.
 #define PC_F32_PARTS 102400
 
 // Device-side view of a packed layer. All pointers point into one slab.

@@ -937,10 +937,11 @@ __device__ __forceinline__ void pc_sparse_compress16(const uint16_t *src, uint4 
     *idx = ix;
     *n_ovf = no;
 }
-// LDS of a tile block, shared by the bf16 and the float32 form.
+// LDS of a tile block, shared by the bf16 and the float32 forms.
+#define PC_TILE_LDS (2 * 9 * 32 * PC_TILE_PITCH * 2)
 __device__ __forceinline__ unsigned char *pc_tile_lds()
 {
-    __shared__ __align__(16) unsigned char buf[2 * 9 * 32 * PC_TILE_PITCH * 2];
+    __shared__ __align__(16) unsigned char buf[PC_TILE_LDS];
     return buf;
 }
 
@@ -980,13 +981,11 @@ __device__ __forceinline__ void pc_pack_tile_load(const float *__restrict__ W, c
 }
 
 // The float32 form: [row tile][tap][entry / 8][lane][4], lane l of a fragment holds row l % 32 and entries
-// 4 * (l / 32) .. + 3; and in three parts, [row tile][tap][entry / 16][part][lane][8], lane l holds row l % 32 and entries 8 * (l / 32) .. + 7.
-// The block's weights are masked into LDS as they lie in W and read in both orientations. With the parts, whose stores bound it, a block has
-// a workgroup for each (128 x 128 4.9 us with one, 4.8 with two; 256 x 256 9.0, 7.0).
+// 4 * (l / 32) .. + 3. The block's weights are masked into LDS as they lie in W and read in both orientations.
 template <bool FROM_KINFO>
 __device__ __forceinline__ void pc_pack_tile_block_f32(const float *__restrict__ W, const uint8_t *__restrict__ pid,
                                                        const uint8_t *__restrict__ keep, const LibArg &la, const PackView &v,
-                                                       int fb, int cb, int odd)
+                                                       int fb, int cb)
 {
     constexpr int PITCH = 289;                    // odd: rows and columns spread over the banks
     float *tw = reinterpret_cast<float *>(pc_tile_lds());
@@ -998,32 +997,102 @@ __device__ __forceinline__ void pc_pack_tile_block_f32(const float *__restrict__
 #pragma unroll
         for (int j = 0; j < 9; ++j) tw[(r0 + i) * PITCH + cl * 9 + j] = ((t.m[i] >> j) & 1u) ? t.w[i][j] : 0.0f;
     __syncthreads();
-    // both orientations, or (with the parts) the workgroup's own
-    for (int o = tid + (v.w3_fwd && odd ? 9 * 128 : 0); o < (v.w3_fwd && !odd ? 1 : 2) * 9 * 128; o += 256) {
-        const int lane = o & 63, u = o >> 6, bwd = u >= 18, tap = (bwd ? u - 18 : u) >> 1, half = u & 1;
-        const int row = lane & 31, e = half * 16 + 8 * (lane >> 5);
-        const float *p = bwd ? tw + e * PITCH + row * 9 + tap : tw + row * PITCH + e * 9 + tap;
-        const int step = bwd ? PITCH : 9, kf = (bwd ? fb : cb) * 2 + half;
-        const int64_t fr = (int64_t)((bwd ? cb : fb) * 9 + tap) * ((bwd ? v.Fk : v.Ck) / 16) + kf;
-        const float4 a = make_float4(p[0], p[step], p[2 * step], p[3 * step]);
-        const float4 b = make_float4(p[4 * step], p[5 * step], p[6 * step], p[7 * step]);
-        float4 *to = reinterpret_cast<float4 *>(bwd ? v.wz_bwd : v.wz_fwd) + fr * 128 + (lane >> 5) * 64 + row;
-        to[0] = a;
-        to[32] = b;
-        if (!v.w3_fwd) continue;              // uniform
-        const F32Parts s = f32_split8(a, b);
-        bf16x8 *to3 = reinterpret_cast<bf16x8 *>(bwd ? v.w3_bwd : v.w3_fwd) + fr * 192 + lane;
+    const int KSf = v.Ck / 8, KSb = v.Fk / 8;
+    float4 *of = reinterpret_cast<float4 *>(v.wz_fwd), *ob = reinterpret_cast<float4 *>(v.wz_bwd);
+    for (int o = tid; o < 9 * 4 * 64; o += 256) {
+        const int lane = o & 63, q = o >> 6, tap = q >> 2, ks = q & 3;
+        const int row = lane & 31, e = ks * 8 + 4 * (lane >> 5);
+        const float *p = tw + row * PITCH + e * 9 + tap;
+        of[((int64_t)(fb * 9 + tap) * KSf + cb * 4 + ks) * 64 + lane] = make_float4(p[0], p[9], p[18], p[27]);
+        const float *s = tw + e * PITCH + row * 9 + tap;
+        ob[((int64_t)(cb * 9 + tap) * KSb + fb * 4 + ks) * 64 + lane] = make_float4(s[0], s[PITCH], s[2 * PITCH], s[3 * PITCH]);
+    }
+}
+
+// The same, and in three parts: [row tile][tap][entry / 16][part][lane][8], lane l holds row l % 32 and entries 8 * (l / 32) .. + 7. The
+// workgroups of a block have NT taps each, and with SIDES one orientation; those that share its weights follow each other on one XCD (the
+// eight take workgroups in turn). Small layers are bound by the chain of a wavefront: load, LDS, split, store; large ones by their bytes, 180 a
+// kernel with the float32 values (4.7 TB/s at 320 x 320). us of new values, without the parts / a workgroup per orientation / per tap / per
+// three taps: 16 x 16 3.1, 4.0, 2.4, 3.0; 128 x 128 3.5, 4.4, 2.8, 3.4; 192 x 192 3.6, 4.8, 3.6, 3.9; 256 x 256 3.9, 5.4, 4.8, 4.7; 320 x 320 4.2, 6.3,
+// 6.2, 5.9 (taps of a block on eight XCDs 8.1). In a pack of one launch workgroups that place rows run beside them, per orientation / tap / three
+// taps: 16 x 16 4.1, 3.4, 3.5; 192 x 192 5.3, 5.8, 5.4; 256 x 256 6.8, 7.5, 7.0; 320 x 320 8.7, 8.8, 9.2.
+template <bool FROM_KINFO, int NT, bool SIDES>
+__device__ __forceinline__ void pc_pack_tile_parts(const float *__restrict__ W, const uint8_t *__restrict__ pid,
+                                                   const uint8_t *__restrict__ keep, const LibArg &la, const PackView &v, int b)
+{
+    constexpr int PITCH = 33, NG = 9 / NT * (SIDES ? 2 : 1), UNITS = NT * (SIDES ? 2 : 4);    // a unit: tap, half a fragment row's entries, orientation
+    static_assert(NT * 32 * PITCH * 4 <= PC_TILE_LDS, "tile");
+    float *tw = reinterpret_cast<float *>(pc_tile_lds());       // [tap][filter][channel]
+    const int cols = v.Cp >> 5, blocks = (v.Fp >> 5) * cols, g8 = b / (8 * NG), r8 = b - g8 * (8 * NG), n8 = blocks - 8 * g8 < 8 ? blocks - 8 * g8 : 8;
+    const int part = r8 / n8, t0 = (SIDES ? part >> 1 : part) * NT, blk = 8 * g8 + r8 - part * n8, fb = blk / cols, cb = blk - fb * cols;
+    const int tid = threadIdx.x, cl = tid & 31, r0 = 4 * (tid >> 5), c = cb * 32 + cl;
+    __shared__ uint16_t lm[PC_MAX_P + 2];         // the pool's masks
+    if (!FROM_KINFO && tid < la.P) lm[tid] = la.mask[tid];
+    uint32_t u[4];
+    float w[4][NT];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int f = fb * 32 + r0 + i;
+        const int64_t k = f < v.F && c < v.C ? (int64_t)f * v.C + c : 0;
+        if (FROM_KINFO) u[i] = v.kinfo[k];
+        else {
+            const uint32_t kp = keep[k], pd = pid[k];
+            u[i] = kp ? pd : 255u;                // (no id of a pool)
+        }
+#pragma unroll
+        for (int j = 0; j < NT; ++j) w[i][j] = W[k * 9 + t0 + j];
+    }
+    if (!FROM_KINFO) __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        uint32_t m = 0u;
+        if (fb * 32 + r0 + i < v.F && c < v.C) {
+            if (FROM_KINFO) m = u[i] != 0xFFFFFFFFu ? u[i] : 0u;
+            else if ((int)u[i] < la.P) m = lm[u[i]];
+        }
+#pragma unroll
+        for (int j = 0; j < NT; ++j) tw[(j * 32 + r0 + i) * PITCH + cl] = ((m >> (t0 + j)) & 1u) ? w[i][j] : 0.0f;
+    }
+    __syncthreads();
+    const int lane = tid & 63, row = lane & 31, KF[2] = {v.Ck / 16, v.Fk / 16};
+    uint16_t *const wz[2] = {v.wz_fwd, v.wz_bwd}, *const w3[2] = {v.w3_fwd, v.w3_bwd};
+#pragma unroll
+    for (int i = 0; i < (UNITS + 3) / 4; ++i) {
+        const int q = i * 4 + (tid >> 6);
+        if (UNITS % 4 && q >= UNITS) break;
+        const int half = q & 1, j = SIDES ? q >> 1 : q >> 2;
+        const bool bwd = SIDES ? part & 1 : (q >> 1) & 1;
+        const int e = half * 16 + 8 * (lane >> 5), step = bwd ? PITCH : 1;
+        const float *p = tw + j * 32 * PITCH + (bwd ? e * PITCH + row : row * PITCH + e);
+        const int64_t fr = (int64_t)((bwd ? cb : fb) * 9 + t0 + j) * (bwd ? KF[1] : KF[0]) + (bwd ? fb : cb) * 2 + half;
+        const float4 x = make_float4(p[0], p[step], p[2 * step], p[3 * step]), y = make_float4(p[4 * step], p[5 * step], p[6 * step], p[7 * step]);
+        float4 *to = reinterpret_cast<float4 *>(bwd ? wz[1] : wz[0]) + fr * 128 + (lane >> 5) * 64 + row;
+        to[0] = x;
+        to[32] = y;
+        const F32Parts s = f32_split8(x, y);
+        bf16x8 *to3 = reinterpret_cast<bf16x8 *>(bwd ? w3[1] : w3[0]) + fr * 192 + lane;
 #pragma unroll
         for (int k = 0; k < 3; ++k) to3[k * 64] = s.p[k];
     }
 }
 
-template <bool FROM_KINFO>
+// How many workgroups share a block of a pack with the parts (the figures above): two, the orientations, where workgroups that place rows run
+// beside them, else nine or three.
+__host__ __device__ __forceinline__ int pc_tile_shares(const PackView &v, bool rows) { return rows ? 2 : v.F * v.C <= 36864 ? 9 : 3; }
+
+// Workgroup b of a pack's operand tiles
+template <bool FROM_KINFO, bool ROWS>
 __device__ __forceinline__ void pc_pack_tile_block(const float *__restrict__ W, const uint8_t *__restrict__ pid,
-                                                   const uint8_t *__restrict__ keep, const LibArg &la, const PackView &v,
-                                                   int fb, int cb)
+                                                   const uint8_t *__restrict__ keep, const LibArg &la, const PackView &v, int b)
 {
-    if (v.f32) return pc_pack_tile_block_f32<FROM_KINFO>(W, pid, keep, la, v, fb, v.w3_fwd ? cb >> 1 : cb, cb & 1);
+    if (v.w3_fwd) {
+        if (ROWS) pc_pack_tile_parts<FROM_KINFO, 9, true>(W, pid, keep, la, v, b);
+        else if (pc_tile_shares(v, false) == 9) pc_pack_tile_parts<FROM_KINFO, 1, false>(W, pid, keep, la, v, b);
+        else pc_pack_tile_parts<FROM_KINFO, 3, false>(W, pid, keep, la, v, b);
+        return;
+    }
+    const int fb = b / (v.Cp >> 5), cb = b - fb * (v.Cp >> 5);
+    if (v.f32) return pc_pack_tile_block_f32<FROM_KINFO>(W, pid, keep, la, v, fb, cb);
     uint16_t (*tA)[32][PC_TILE_PITCH] = reinterpret_cast<uint16_t (*)[32][PC_TILE_PITCH]>(pc_tile_lds());   // [tap][filter][channel]
     uint16_t (*tB)[32][PC_TILE_PITCH] = tA + 9;                   // [tap][channel][filter]
     const int tid = threadIdx.x, cl = tid & 31, r0 = 4 * (tid >> 5);
@@ -1165,12 +1234,12 @@ __global__ void __launch_bounds__(64) pc_pack_ovf_merge_kernel(PackView v) { pc_
 
 
 // First launch of a pack: the first workgroups count the filter rows, the next ncm the channel rows (gather variant, else
-// none), the rest write the operand tiles (matrix-core variant), one 32 x 32 block each (with the parts of float32 weights: one orientation of it).
-static int pc_tile_cols(const PackView &v) { return v.Cp / 32 * (v.w3_fwd ? 2 : 1); }
+// none), the rest write the operand tiles (matrix-core variant), one 32 x 32 block each (with the parts of float32 weights: a share of it).
+static int pc_tile_wgs(const PackView &v, bool rows) { return (v.Fp / 32) * (v.Cp / 32) * (v.w3_fwd ? pc_tile_shares(v, rows) : 1); }
 static int pc_pack_row_wgs(int rows) { return (rows + PC_PACK_ROWS - 1) / PC_PACK_ROWS; }
+template <bool ROWS>
 __device__ __forceinline__ void pc_pack_stage1_body(const float *__restrict__ W, const uint8_t *__restrict__ pid,
-                                                    const uint8_t *__restrict__ keep, const LibArg &la, const PackView &v, int ncm,
-                                                    int tiles_c, int b)
+                                                    const uint8_t *__restrict__ keep, const LibArg &la, const PackView &v, int ncm, int b)
 {
     const int nfm = (v.F + PC_PACK_ROWS - 1) / PC_PACK_ROWS;
     if (b < nfm) {
@@ -1183,14 +1252,14 @@ __device__ __forceinline__ void pc_pack_stage1_body(const float *__restrict__ W,
         return;
     }
     b -= ncm;
-    pc_pack_tile_block<false>(W, pid, keep, la, v, b / tiles_c, b % tiles_c);
+    pc_pack_tile_block<false, ROWS>(W, pid, keep, la, v, b);
 }
 
 __global__ void __launch_bounds__(256)
 pc_pack_stage1_kernel(const float *__restrict__ W, const uint8_t *__restrict__ pid, const uint8_t *__restrict__ keep,
-                      LibArg la, PackView v, int ncm, int tiles_c)
+                      LibArg la, PackView v, int ncm)
 {
-    pc_pack_stage1_body(W, pid, keep, la, v, ncm, tiles_c, (int)blockIdx.x);
+    pc_pack_stage1_body<true>(W, pid, keep, la, v, ncm, (int)blockIdx.x);
 }
 
 // Several packs per launch: workgroup b serves block b - blk0[l] of pack l. The packs' views are read from their
@@ -1201,14 +1270,14 @@ struct PackBatchArg {
     const float *W[PC_BATCH_MAX];
     const uint8_t *pid[PC_BATCH_MAX], *keep[PC_BATCH_MAX];
     const PackView *view[PC_BATCH_MAX];
-    int32_t ncm[PC_BATCH_MAX], tiles_c[PC_BATCH_MAX], bf16[PC_BATCH_MAX];
+    int32_t ncm[PC_BATCH_MAX], bf16[PC_BATCH_MAX];
 };
 
 __global__ void __launch_bounds__(256) pc_pack_stage1_batch_kernel(PackBatchArg b, LibArg la)
 {
     const int l = pc_batch_find(b.blk0, b.n, (int)blockIdx.x);
     const PackView v = *b.view[l];
-    pc_pack_stage1_body(b.W[l], b.pid[l], b.keep[l], la, v, b.ncm[l], b.tiles_c[l], (int)blockIdx.x - b.blk0[l]);
+    pc_pack_stage1_body<false>(b.W[l], b.pid[l], b.keep[l], la, v, b.ncm[l], (int)blockIdx.x - b.blk0[l]);
 }
 
 // The 4 kept weights of kernel k; taps holds the 4 tap indices, one per byte, ascending from the low byte.
@@ -1231,17 +1300,17 @@ __device__ __forceinline__ uint32_t pc_taps_word(const LibArg &la, int p)
 // Values again from new weights with unchanged tables, one launch for the matrix-core variant: every workgroup rebuilds the
 // operand tiles of a block (masks from the kinfo table).
 __global__ void __launch_bounds__(256)
-pc_pack_revalue_kernel(const float *__restrict__ W, PackView v, int tiles_c)
+pc_pack_revalue_kernel(const float *__restrict__ W, PackView v)
 {
-    pc_pack_tile_block<true>(W, nullptr, nullptr, LibArg(), v, (int)blockIdx.x / tiles_c, (int)blockIdx.x % tiles_c);
+    pc_pack_tile_block<true, false>(W, nullptr, nullptr, LibArg(), v, (int)blockIdx.x);
 }
 
 // The same for several packs.
 __global__ void __launch_bounds__(256) pc_pack_revalue_batch_kernel(PackBatchArg b)
 {
-    const int l = pc_batch_find(b.blk0, b.n, (int)blockIdx.x), blk = (int)blockIdx.x - b.blk0[l];
+    const int l = pc_batch_find(b.blk0, b.n, (int)blockIdx.x);
     const PackView v = *b.view[l];
-    pc_pack_tile_block<true>(b.W[l], nullptr, nullptr, LibArg(), v, blk / b.tiles_c[l], blk % b.tiles_c[l]);
+    pc_pack_tile_block<true, false>(b.W[l], nullptr, nullptr, LibArg(), v, (int)blockIdx.x - b.blk0[l]);
 }
 
 // Places the kept kernels of one row at (kept kernels of the rows before) + (pattern group start) + (rank inside the group);
@@ -1482,12 +1551,11 @@ __device__ __forceinline__ void pc_pack_place_counted(const uint8_t *__restrict_
 }
 
 __global__ void __launch_bounds__(256)
-pc_pack_one_kernel(const float *__restrict__ W, const uint8_t *__restrict__ pid, const uint8_t *__restrict__ keep, LibArg la, PackView v,
-                   int tiles_c)
+pc_pack_one_kernel(const float *__restrict__ W, const uint8_t *__restrict__ pid, const uint8_t *__restrict__ keep, LibArg la, PackView v)
 {
     const int b = (int)blockIdx.x;
     if (b < v.F) pc_pack_place_counted(pid, keep, la, v, b);
-    else pc_pack_tile_block<false>(W, pid, keep, la, v, (b - v.F) / tiles_c, (b - v.F) % tiles_c);
+    else pc_pack_tile_block<false, true>(W, pid, keep, la, v, b - v.F);
 }
 
 // Re-gathers values with unchanged tables (one thread per kernel (f,c)).
@@ -1545,14 +1613,13 @@ pc_status pc_launch_pack(pc_ctx *ctx, pc_packed *pk, const float *W, const uint8
     const bool mfma = pk->variant == PC_VARIANT_MFMA;
     // the channel-major table serves the gather kernels' backward-data pass (the matrix-core kernels read operand tiles)
     const int nfm = pc_pack_row_wgs(v.F), ncm = mfma ? 0 : pc_pack_row_wgs(v.C);
-    const int tiles_c = pc_tile_cols(v), ntiles = mfma ? (v.Fp / 32) * tiles_c : 0;
+    const int ntiles = mfma ? pc_tile_wgs(v, true) : 0;
     if (mfma && v.C <= 512 && (int64_t)v.F * v.C <= PC_PACK_ONE && (((uintptr_t)pid | (uintptr_t)keep) & 15) == 0) {
-        hipLaunchKernelGGL(pc_pack_one_kernel, dim3((unsigned)(v.F + ntiles)), dim3(256), 0, st, W, pid, keep, la, v, tiles_c);
+        hipLaunchKernelGGL(pc_pack_one_kernel, dim3((unsigned)(v.F + ntiles)), dim3(256), 0, st, W, pid, keep, la, v);
         pc_launch_ovf_merge(ctx, v);
         return pc_hip_check(ctx, hipGetLastError(), "pack launch");
     }
-    hipLaunchKernelGGL(pc_pack_stage1_kernel, dim3((unsigned)(nfm + ncm + ntiles)), dim3(256), 0, st, W, pid, keep, la, v, ncm,
-                       tiles_c);
+    hipLaunchKernelGGL(pc_pack_stage1_kernel, dim3((unsigned)(nfm + ncm + ntiles)), dim3(256), 0, st, W, pid, keep, la, v, ncm);
     if (mfma) {
         hipLaunchKernelGGL(pc_pack_place_kernel<PLACE_SLOTS>, dim3((unsigned)v.F), dim3(256), 0, st, W, pid, keep, v.F, v.C,
                            (int64_t)v.C, (int64_t)1, la, bf16, v);
@@ -1582,7 +1649,6 @@ pc_status pc_launch_pack_batch(pc_ctx *ctx, int n, pc_packed *const *pk, const f
             s1.W[i] = W[l0 + i]; s1.pid[i] = pid[l0 + i]; s1.keep[i] = keep[l0 + i];
             s1.view[i] = p->v_dev;
             s1.ncm[i] = mfma ? 0 : pc_pack_row_wgs(p->v.C);
-            s1.tiles_c[i] = pc_tile_cols(p->v);
             s1.bf16[i] = p->dtype == PC_BF16;
         }
         sl = s1;
@@ -1591,7 +1657,7 @@ pc_status pc_launch_pack_batch(pc_ctx *ctx, int n, pc_packed *const *pk, const f
         for (int i = 0; i < m; ++i) {
             const pc_packed *p = pk[l0 + i];
             const bool mfma = p->variant == PC_VARIANT_MFMA;
-            s1.blk0[i + 1] = s1.blk0[i] + pc_pack_row_wgs(p->v.F) + s1.ncm[i] + (mfma ? (p->v.Fp / 32) * s1.tiles_c[i] : 0);
+            s1.blk0[i + 1] = s1.blk0[i] + pc_pack_row_wgs(p->v.F) + s1.ncm[i] + (mfma ? pc_tile_wgs(p->v, false) : 0);
             sl.blk0[i + 1] = sl.blk0[i] + (mfma ? p->v.F : 0);
             fm.blk0[i + 1] = fm.blk0[i] + (mfma ? 0 : p->v.F);
             cm.blk0[i + 1] = cm.blk0[i] + (mfma ? 0 : p->v.C);
@@ -1634,8 +1700,7 @@ pc_status pc_launch_update_values_batch(pc_ctx *ctx, int n, pc_packed *const *pk
         bpk[i] = p;
         b.W[i] = W[l];
         b.view[i] = p->v_dev;
-        b.tiles_c[i] = pc_tile_cols(p->v);
-        b.blk0[i + 1] = b.blk0[i] + (p->v.Fp / 32) * b.tiles_c[i];
+        b.blk0[i + 1] = b.blk0[i] + pc_tile_wgs(p->v, false);
         if (++b.n == PC_BATCH_MAX) {
             pc_status s = flush();
             if (s != PC_OK) return s;
@@ -1648,8 +1713,7 @@ pc_status pc_launch_update_values(pc_ctx *ctx, pc_packed *pk, const float *W)
 {
     PackView v = pk->v;
     if (pk->variant == PC_VARIANT_MFMA) {
-        const int tiles_c = pc_tile_cols(v), ntiles = (v.Fp / 32) * tiles_c;
-        hipLaunchKernelGGL(pc_pack_revalue_kernel, dim3((unsigned)ntiles), dim3(256), 0, ctx->stream, W, v, tiles_c);
+        hipLaunchKernelGGL(pc_pack_revalue_kernel, dim3((unsigned)pc_tile_wgs(v, false)), dim3(256), 0, ctx->stream, W, v);
         pc_launch_ovf_merge(ctx, v);
     } else {
         LibArg la;
