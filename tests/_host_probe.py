@@ -102,7 +102,10 @@ def alignment():
     same sizes, and back."""
     ctx = B.pc_create(0, None)
     direct = 0
-    for shape in [(9, 38, 41, 56, 64, 1), (32, 112, 112, 128, 128, 1), (64, 7, 7, 512, 512, 1), (64, 56, 56, 128, 128, 2), (64, 14, 14, 256, 512, 2), (13, 33, 47, 40, 72, 1)]:
+    kernels = ("conv_dma", "conv_solo", "conv_ring", "conv_keep", "conv_deep", "wgrad_dma_few", "wgrad_dma")
+    met = set()
+    for shape in [(9, 38, 41, 56, 64, 1), (32, 112, 112, 128, 128, 1), (64, 7, 7, 512, 512, 1), (64, 56, 56, 128, 128, 2), (64, 14, 14, 256, 512, 2), (13, 33, 47, 40, 72, 1),
+                  (32, 224, 224, 64, 64, 1), (61, 199, 198, 32, 16, 1), (1, 14, 14, 512, 512, 1), (128, 2, 2, 256, 512, 1)]:
         d, pk = layer(ctx, shape)
         calls = [lambda a: B.pc_conv_fwd(ctx, d, pk, a, DEV), lambda a: B.pc_conv_bwd_data(ctx, d, pk, a, DEV), lambda a: B.pc_conv_bwd_data_relu(ctx, d, pk, a, DEV, DEV),
                  lambda a: B.pc_conv_bwd_weight(ctx, d, pk, a, DEV, DEV), lambda a: B.pc_conv_bwd_weight(ctx, d, pk, DEV, a, DEV),
@@ -112,19 +115,23 @@ def alignment():
             for off in (2, 0, 8, 0):
                 call(DEV + off)
                 names.append(B.pc_last_kernel(ctx))
-            is_direct = [any(k in n for k in ("conv_dma", "conv_solo", "conv_ring", "wgrad_dma")) for n in names]
+            is_direct = [any(k in n for k in kernels) for n in names]
+            met.update(k for k in kernels if any(k in n for n in names))
             assert not is_direct[0] and not is_direct[2] and names[0] == names[2] and names[1] == names[3], (shape, names)
             direct += is_direct[1]
-        for code in (41, 43, 44) if shape[5] == 1 else (44, 48):      # forced, they are refused
+        small = shape[0] * shape[1] * shape[2] < 4096
+        for code in (41, 43, 44) + ((50,) if max(shape[3:5]) <= 64 else ()) + ((51, 53, 55) if small else ()) if shape[5] == 1 else (44, 48):      # forced, they are refused
             B.pc_set_plan_override(ctx, code, 0)
+            call = calls[3] if code in (44, 55) else calls[0]
+            call(DEV)
             try:
-                (calls[3] if code == 44 else calls[0])(DEV + 4)
+                call(DEV + 4)
                 assert False, (shape, code)
             except B.PcError as e:
                 assert e.status == B.PC_ERR_UNSUPPORTED
             B.pc_set_plan_override(ctx, -1, 0)
         B.pc_packed_free(pk)
-    assert direct >= 20, direct
+    assert direct >= 40 and met == set(kernels), (direct, met)
     B.pc_destroy(ctx)
 
 
