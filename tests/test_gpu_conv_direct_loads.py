@@ -1,6 +1,5 @@
 """The forward / backward-data kernels that load both operands straight to LDS (override codes 40 to 49; 37 and 38 for stride-2
-backward-data), element by element against the oracle, at the edges of their tiles: rows that run across images (one zero row
-between two of them), columns past the map, a last chunk of 8, 16 or 24 channels, partial row tiles, and lists of tiles that
+backward-data), element by element against the oracle, at the edges of their tiles: rows that run across images, columns past the map, a last chunk of 8, 16 or 24 channels, partial row tiles, and lists of tiles that
 continue in narrower ones."""
 import pytest
 
@@ -111,12 +110,13 @@ def test_several_tiles_per_workgroup_at_stride_2_backward(B, ctx, cfg, dims):
         g.close()
 
 
-@pytest.mark.parametrize("cfg", [41, 42, 43, 45, 46])
-def test_many_small_images(B, ctx, oracle, cfg):
-    """A zero row between every four: the widest tile has not the LDS for it."""
+@pytest.mark.parametrize("cfg", [40, 41, 42, 43, 45, 46, 50])
+@pytest.mark.parametrize("dims", [(70, 4, 4), (75, 2, 3), (90, 1, 5), (40, 1, 1)])
+def test_many_small_images(B, ctx, oracle, cfg, dims):
+    """More images than a tile has rows, down to one row each: the rows above and below most rows of a tile, or one of them, are zeros."""
     B.pc_set_plan_override(ctx, cfg, 0)
     try:
-        run_case(B, ctx, oracle, (70, 4, 4, 72, 64, 1), "bf16", 8, 0.3, B.PC_VARIANT_MFMA, ("direct", cfg))
+        run_case(B, ctx, oracle, dims + (56 if cfg == 50 else 72, 64, 1), "bf16", 8, 0.3, B.PC_VARIANT_MFMA, ("direct", cfg))
     finally:
         B.pc_set_plan_override(ctx, -1, 0)
 
