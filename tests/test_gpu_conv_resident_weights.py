@@ -36,10 +36,16 @@ def ctx(B):
     (20, 64, 65, 32, 64, 1),     # more tiles than workgroups
     (9, 96, 95, 64, 40, 1)])
 def test_every_element(B, ctx, oracle, shape):
+    from tests._harness import Case, GpuLayer
+    layer = I.Layer(*shape)
     B.pc_set_plan_override(ctx, 50, 0)
     try:
         run_case(B, ctx, oracle, shape, "bf16", 8, 0.3, B.PC_VARIANT_MFMA, "resident")
-        assert B.pc_last_kernel(ctx)
+        g = GpuLayer(B, ctx, Case(layer, "bf16", 8, I.kept_per_filter(0.3, layer.C), tag="resident"), variant=B.PC_VARIANT_MFMA)
+        for run, channels in ((g.fwd, layer.F), (g.bwd_data, layer.C)):      # (two fragments of 16 output channels a wavefront, or four)
+            run()
+            assert B.pc_last_kernel(ctx).startswith("pc_mfma_conv_keep_kernel<%d, " % (2 if channels <= 32 else 4)), B.pc_last_kernel(ctx)
+        g.close()
     finally:
         B.pc_set_plan_override(ctx, -1, 0)
 
