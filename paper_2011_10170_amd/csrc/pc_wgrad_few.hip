@@ -165,8 +165,8 @@ static bool plan_few(const pc_conv_desc *d, const FewCand &c, int num_cu, FewWgr
     a.mg_R = pc_udiv_magic(a.R); a.mg_I = pc_udiv_magic(a.I); a.mg_tc = pc_udiv_magic(a.tiles_c);
     a.x_bytes = (uint32_t)(px * d->C * 2); a.dy_bytes = (uint32_t)(px * d->F * 2);
     // Estimated time (us): a start, of every chunk a wait, its loads and its products (as LDS reads of a wavefront), workgroups that share a CU,
-    // the bytes staged by all, the sums of the wavefronts. Fitted to 900 timings of 230 layers (6 % rms); the tile taken was 0.9 % behind the
-    // fastest on average, 18 % at worst.
+    // the bytes staged by all, the sums of the wavefronts. Fitted to 900 timings of 230 layers (6 % rms); on the 133 layers
+    // of profiles/wgrad_few_timings_bf16.csv that come here the tile taken is 0.7 % behind the fastest on average, 9 % at worst.
     const int steps = (a.cells / 32 + 7) / 8, share = *lds <= 80 * 1024 ? 2 : 1, rounds = (*grid + share * num_cu - 1) / (share * num_cu);
     const double one = a.chunks * (1.02 + 0.000376 * (c.mf * a.cells + c.mc * a.xcells) + 0.0134 * steps * (2.25 * c.mf * c.mc + 9 * c.mc + c.mf));
     const double t = *grid <= num_cu ? one : rounds * one * (1.0 + 0.21 * (std::min((double)share, *grid / (double)num_cu) - 1.0));

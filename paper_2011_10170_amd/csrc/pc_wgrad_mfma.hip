@@ -882,9 +882,9 @@ static pc_status pc_mfma_bwd_weight_dma(pc_ctx *ctx, const pc_conv_desc *d, cons
         if (*choice < -1) return pc_mfma_bwd_weight_few(ctx, d, pk, x, dy, dw, -2 - *choice, launched);
     }
     if (!pc_wgrad_dma_plan_one(d, nslots, pc_kept_estimate(pk), ctx->num_cu, !forced ? -1 : ctx->plan_split > 0 && ctx->plan_split < WD_WAVES ? ctx->plan_split : 0, choice, &p)) return PC_OK;
-    // Few pixels: one launch without partial planes where its estimate is the lower one (up to 2000 to 3500 pixels). Of 133 layers of 1300 to 5500
-    // pixels in a graph those with an estimate 1.5 us above the other's were 10 % slower, those below it 1.3 times as fast; launch by launch,
-    // where the second launch costs 2 us more, the line would lie at 1.5 us above.
+    // Few pixels: one launch without partial planes where its estimate is the lower one (up to 2000 to 3500 pixels). On the 168 layers of
+    // profiles/wgrad_few_timings_bf16.csv (4 to 8400 pixels, 133 of them below the line) what is taken is 1.2 % behind the fastest of all tiles of both
+    // kernels in a graph, 14 % at worst; launch by launch, where the second launch costs up to 2 us more, 1.8 and 26 %: there the line would lie higher.
     const int few = forced || known ? -1 : pc_wgrad_few_tile(d, ctx->num_cu, p.us);
     if (few >= 0) {
         *choice = -2 - few;

@@ -364,13 +364,14 @@ def wgrad_choice():
     stored times of those and others."""
     ctx = B.pc_create(0, None)
     late = []
+    few = few_timings()
     for k, us in stored("profiles/wgrad_plan_timings_bf16.csv", 6, 5).items():
         d, pk = layer(ctx, k)
         watch("pc_mfma_wgrad_dma_kernel", 0, 88 + 112)
         B.pc_conv_bwd_weight(ctx, d, pk, DEV, DEV, DEV)
         assert "wgrad_dma" in B.pc_last_kernel(ctx), k
-        if "wgrad_dma_few" in B.pc_last_kernel(ctx):      # (another kernel: few pixels)
-            assert k[0] * k[1] * k[2] <= 8192 and k[5] == 1, k
+        if "wgrad_dma_few" in B.pc_last_kernel(ctx):      # (another kernel: its stored times are looked at below)
+            assert k in few, k
             B.pc_packed_free(pk)
             continue
         a = struct.unpack("<28i", seen()[0][88:])
@@ -378,6 +379,38 @@ def wgrad_choice():
         late.append(us[plan] / min(us.values()) if plan in us else None)
         B.pc_packed_free(pk)
     compare("bwd_weight", late, 1.057, 1.24, 0.05)      # 1.037, 1.19
+    B.pc_destroy(ctx)
+
+
+def few_timings():
+    """{layer: {(code, tile): (us in a graph, us launch by launch)}} of the kernel for few pixels (55) and the one with direct loads (44)."""
+    times = {}
+    for row in list(open("profiles/wgrad_few_timings_bf16.csv"))[1:]:
+        f = row.strip().split(",")
+        times.setdefault(tuple(int(v) for v in f[:6]), {})[(int(f[6]), int(f[7]))] = (float(f[8]), float(f[9]))
+    return times
+
+
+def wgrad_few_choice():
+    """Weight gradients of 4 to 8400 pixels: the kernel for few pixels or the one with direct loads, and the tile of either, against the stored times
+    of all tiles of both: those in a graph, which the line between the two is drawn for, and those launch by launch."""
+    ctx = B.pc_create(0, None)
+    late, chosen = [], set()
+    for k, us in few_timings().items():
+        d, pk = layer(ctx, k)
+        watch("pc_mfma_wgrad_dma_kernel", 0, 88 + 112)
+        B.pc_conv_bwd_weight(ctx, d, pk, DEV, DEV, DEV)
+        name = B.pc_last_kernel(ctx)
+        if "wgrad_dma_few" in name:
+            plan = (55, {"1, 1": 0, "1, 2": 1, "2, 1": 2, "2, 2": 3}[name.split("<")[1][:-1]])
+        else:
+            plan = (44, struct.unpack("<28i", seen()[0][88:])[25])
+        chosen.add(plan)
+        late.append([us[plan][i] / min(v[i] for v in us.values()) for i in range(2)])
+        B.pc_packed_free(pk)
+    assert {(55, 0), (55, 2), (55, 3), (44, 0), (44, 3)} <= chosen, chosen
+    compare("in a graph", [v[0] for v in late], 1.032, 1.19, 0.0)              # 1.012, 1.14
+    compare("launch by launch", [v[1] for v in late], 1.038, 1.31, 0.0)        # 1.018, 1.26
     B.pc_destroy(ctx)
 
 

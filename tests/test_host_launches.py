@@ -20,7 +20,7 @@ def stub(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("check", ["wgrad_lds", "wgrad_lds_narrow", "thin_planes", "changing_counts", "alignment", "noalloc_first_layer", "no_host_memory", "no_room", "no_room_first_layer", "wgrad_choice", "f32_wgrad_choice", "group_choice", "conv_choice", "f32_conv_choice"])
+@pytest.mark.parametrize("check", ["wgrad_lds", "wgrad_lds_narrow", "thin_planes", "changing_counts", "alignment", "noalloc_first_layer", "no_host_memory", "no_room", "no_room_first_layer", "wgrad_choice", "wgrad_few_choice", "f32_wgrad_choice", "group_choice", "conv_choice", "f32_conv_choice"])
 def test_host_side(stub, check):
     r = subprocess.run([sys.executable, "-m", "tests._host_probe", stub, check], cwd=ROOT, capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and r.stdout.endswith("ok\n"), r.stdout + r.stderr
