@@ -136,7 +136,7 @@ struct DeepCand { int code, mf, nf; };
 static const DeepCand kDeep[] = {{51, 1, 2}, {52, 1, 4}, {53, 2, 2}, {54, 2, 4}};
 constexpr int kNumDeep = sizeof(kDeep) / sizeof(kDeep[0]);
 
-static bool plan_deep(const MfmaArgs &g, bool flip, const DeepCand &c, DeepArgs *out, size_t *lds, int *grid, double *est, int num_cu)
+static bool plan_deep(const MfmaArgs &g, bool flip, const DeepCand &c, DeepArgs *out, size_t *lds, int *grid, double *est, double *least, int num_cu)
 {
     DeepArgs t;
     memset(&t, 0, sizeof(t));
@@ -169,6 +169,12 @@ static bool plan_deep(const MfmaArgs &g, bool flip, const DeepCand &c, DeepArgs 
     occ = std::min(occ, c.mf * c.nf <= (two ? 2 : 4) ? 2 : 1);
     const double n = (double)*grid / num_cu, share = std::max(1.0, 0.5 * (ceil(n) + n));
     *est = 2.89 + ceil(n / occ) * (two ? 1.42 : 1.01) + share * (0.0166 * t.count * t.CP / 64.0 + 0.0217 * 9.0 * c.mf * c.nf * (two ? 2 : 1));
+    // Those timings are of up to 4096 pixels. Several tiles per CU wait for LDS and for memory: 15 % below a fit to 2400 timings of 4 to 2000000 pixels is
+    // the estimate where it is the larger one (112 x 31 x 28, 496 -> 16: 47.9 us in tiles of 16 x 64, 32 by the line above, 31.0 by the kernel for direct
+    // loads; 65 x 22 x 20, 440 -> 32 18.6, 14.0. Six of 2443 drawn passes go to another kernel by it, five of them the faster one, one 3 % slower).
+    const double work = (two ? 0.861 * ceil(n / occ) : 0.0) + share * (0.0115 * t.count * t.CP / 64.0 + 0.0376 * 9.0 * c.mf * c.nf * (two ? 2 : 1));
+    const double moved = 0.0568e-6 * ((double)t.p_tiles * t.count * t.CP * 16.0 + (double)out_bytes) + 0.0069e-6 * *grid * (t.count * t.CP * 16.0 + 288.0 * c.mf * g.in_CH);
+    *least = 2.14 + pow(pow(work, 1.5) + pow(moved, 1.5), 1.0 / 1.5);
     *out = t;
     return true;
 }
@@ -189,17 +195,18 @@ pc_status pc_run_mfma_conv_deep(pc_ctx *ctx, int pcfg, double limit, const MfmaA
     DeepArgs best;
     size_t best_lds = 0;
     int best_grid = 0, best_k = -1;
-    double best_est = limit;
+    double best_est = limit, best_least = 0.0;
     for (int k = 0; k < kNumDeep; ++k) {
         if (pcfg >= 0 && pcfg != kDeep[k].code) continue;
         DeepArgs t;
         size_t lds;
         int grid;
-        double est;
-        if (!plan_deep(g, flip, kDeep[k], &t, &lds, &grid, &est, ctx->num_cu)) continue;
-        if (pcfg >= 0 || est < best_est) { best = t; best_lds = lds; best_grid = grid; best_k = k; best_est = est; }
+        double est, least;
+        if (!plan_deep(g, flip, kDeep[k], &t, &lds, &grid, &est, &least, ctx->num_cu)) continue;
+        if (pcfg >= 0 || est < best_est) { best = t; best_lds = lds; best_grid = grid; best_k = k; best_est = est; best_least = least; }
     }
-    if (best_k < 0) return PC_OK;
+    best_est = std::max(best_est, best_least);
+    if (best_k < 0 || (pcfg < 0 && best_est >= limit)) return PC_OK;
     if (us) {                        // only asked for
         *us = best_est;
         *launched = kDeep[best_k].code;
