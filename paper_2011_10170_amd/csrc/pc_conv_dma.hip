@@ -405,13 +405,13 @@ pc_mfma_conv_dma_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__ 
 // channels x two groups of pixels, tiles of 64 x 128 (BT = 4) and 64 x 64 (BT = 2).
 // What bounds it: a chunk of 64 x 256, 128 and 64 pixels takes 1.15, 0.64 and 0.39 us for 0.96, 0.48 and 0.24 us of matrix
 // instructions; below 64 x 128 the direct loads (48 KiB a chunk, of them 36 KiB weights that all row tiles load again). With a launch and
-// the first loads (2 us) and last stores around them, 128 images (us, the kernel chosen without this one -> here): 16 x 16
-// 128 -> 128 11.2 -> 9.9, 8 x 8 256 -> 256 11.9 -> 9.2, 4 x 4 512 -> 512 12.2 -> 10.3, 4 x 4 256 -> 512 8.3 -> 7.0; 64 images 7 x 7
-// 512 -> 512 17.3 -> 14.0; one image 56 x 56 256 -> 256 7.7 -> 6.7, 224 x 224 64 -> 64 9.4 -> 7.6.
-// Stride 2, backward-data: the same nine taps per chunk and fewer staged columns, 128 images 8 x 8 256 -> 512 16.9 -> 10.8, 64 images
-// 14 x 14 256 -> 512 17.7 -> 11.3, 56 x 56 128 -> 128 25.7 -> 23.0 (its bytes). Forward: 2 * BT + 1 fragments per row and four staged
+// the first loads (2 us) and last stores around them, in a graph, 128 images (us, the fastest kernel with operands in registers -> here): 16 x 16
+// 128 -> 128 11.5 -> 9.7, 8 x 8 256 -> 256 11.6 -> 9.3, 4 x 4 512 -> 512 11.9 -> 10.6, 4 x 4 256 -> 512 8.5 -> 7.2; 64 images 7 x 7
+// 512 -> 512 16.9 -> 14.9; one image 56 x 56 256 -> 256 7.9 -> 6.9.
+// Stride 2, backward-data: the same nine taps per chunk and fewer staged columns, 128 images 8 x 8 256 -> 512 16.8 -> 10.7, 64 images
+// 14 x 14 256 -> 512 17.5 -> 11.7, 56 x 56 128 -> 128 25.7 -> 22.6 (its bytes). Forward: 2 * BT + 1 fragments per row and four staged
 // pixels per output pixel make LDS the bound, 0.9 us a chunk of 64 x 128 for 0.48 of matrix instructions (1.5 where the input comes from
-// memory): 64 images 14 x 14 256 -> 512 16.0 -> 11.9, 128 images 16 x 16 128 -> 256 11.1 -> 8.6; of large maps with few channels
+// memory): 64 images 14 x 14 256 -> 512 12.5 -> 11.9, 128 images 16 x 16 128 -> 256 12.2 -> 8.4; of large maps with few channels
 // tiles of 128 channels read less (pc_mfma_conv_ring_kernel below).
 template <int MODE, int AT, int BT, int NBUF, int ACT>
 __global__ void __launch_bounds__(512, 2)
@@ -657,8 +657,8 @@ pc_mfma_conv_keep_kernel(const uint16_t *__restrict__ in, uint16_t *__restrict__
 // weights, a row of taps at a time, in a ring of three places (72 + 88 KiB: whole chunks of both would not fit twice). A wavefront
 // multiplies 64 channels x 64 pixels, so that a chunk reads 252 KiB of LDS where two tiles of 64 channels read 360, and an input
 // tile is loaded once for 128 channels. 1.56 us a chunk (0.96 of matrix instructions; LDS 1.2 and a wait at every row). 64 images, us,
-// with the best of the other kernels -> here: 56 x 56 64 -> 128 16.1 -> 14.8, 128 -> 128 25.7 -> 23.6, 28 x 28 128 -> 256 12.6 -> 11.7; 11
-// images 52 x 53 232 -> 480 27.6 -> 22.9; fastest of all on 9 of the 148 drawn layers in
+// with the best of the other kernels -> here: 56 x 56 64 -> 128 16.2 -> 14.0, 128 -> 128 25.6 -> 23.2, 28 x 28 128 -> 256 12.8 -> 11.6; 11
+// images 52 x 53 232 -> 480 27.3 -> 21.3; fastest of all on 9 of the 148 drawn layers in
 // profiles/plan_timings_bf16.csv.
 #define DR_B 44                      // direct loads of an input tile: 6 and 5 per wavefront in the first two steps of a chunk
 #define DR_W (2 * DR_B * 1024)       // where the ring begins
@@ -977,9 +977,9 @@ static const DmaKernel kDmaKernels[kNumDma][3] = {
     DM_ACTS(pc_mfma_conv_keep_kernel<4, 4, DM_KEEP_NBW),
     {&pc_mfma_conv_solo_kernel<DM_BWD2, 2, 4, 3, PC_ACT_NONE>, nullptr, nullptr},
     {&pc_mfma_conv_solo_kernel<DM_BWD2, 2, 2, 3, PC_ACT_NONE>, nullptr, nullptr}};
-// The first three for up to 32 output channels
-static const DmaKernel kDmaKeepNarrow[3] = DM_ACTS(pc_mfma_conv_keep_kernel<2, 4, DM_KEEP_NBW);
+// For up to 32 output channels: the first three of kDma (by their place there), and code 50
 static const DmaKernel kDmaNarrow[3][3] = {DM_PAIR(8, 2), DM_PAIR(4, 2), DM_PAIR(7, 2)};
+static const DmaKernel kDmaKeepNarrow[3] = DM_ACTS(pc_mfma_conv_keep_kernel<2, 4, DM_KEEP_NBW);
 #undef DM_ACTS
 #undef DM_PAIR
 

@@ -530,7 +530,10 @@ pc_topn_write_kernel(const float *__restrict__ R, int64_t L, int64_t chunk, int 
 // the layer, itself; then it flags its own row. So nothing is handed from one workgroup to another but through the end of a launch, and no
 // histogram has to be cleared. What bounds both is latency: the walk is a chain of bin starts, keys and two counting passes in LDS.
 // Selection of 256 x 256 kernels: 17.3 us with the three counting launches and the writing one above, each waiting for the one before,
-// 11.8 here; 130 x 128 16.3, 10.7; with four times the rows (320 x 320) 18.5, 19.9: there the walk outlasts the launches it saves.
+// 11.8 here; 130 x 128 16.3, 10.7. With more kernels the launches take little longer, while the walk grows with the rows and with the keys of the
+// bin, most of them where half is kept. 10, 30 and 50 % kept, in a graph, launches / here: 73728 kernels 16.1, 16.5, 16.6 / 11.7, 14.0, 15.4; 82944 16.4, 16.9, 16.9 / 13.3, 14.9, 16.7;
+// 92160 16.4, 17.0, 16.9 / 13.8, 16.8, 17.6; 102400 16.9, 17.3, 17.4 / 13.9, 16.2, 15.8: past the line every wavefront has a fifth row and
+// half of the layer kept gains 1 us, then nothing.
 #define PC_TOPN_BINNED 65536
 #define PC_BIN_ROW 1024
 #define PC_BINS 512

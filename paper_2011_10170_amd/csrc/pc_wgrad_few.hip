@@ -8,7 +8,8 @@
 // Here a workgroup of 8 wavefronts owns 16 * MF filters x 16 * MC channels of all nine taps and walks all pixels; the wavefronts take groups of
 // 32 pixels in turn, their sums are added in LDS in wavefront order and the kept taps leave in compact order. No scratch is needed. Launch by
 // launch 1 image 14 x 14, 512 -> 512: 12.3 -> 7.9 us; 4 images 14 x 14, 256 -> 256: 12.4 -> 6.0; in a graph 3 images 27 x 27, 24 -> 64:
-// 10.3 -> 7.5. Bound by a start (3 us) and then by the serial chain of one workgroup: 5000 pixels 96 -> 304 16.5 us, the pixels split 14.5.
+// 10.3 -> 7.5. (Against 64 bits its error is 0.91 to 1.23 times that of split pixels, 1.06 on average of 17 drawn layers, 2e-8 to 1e-7 both: float32 sums in
+// another order.) Bound by a start (3 us) and then by the serial chain of one workgroup: 5000 pixels 96 -> 304 16.5 us, the pixels split 14.5.
 //   Cells: x and dy are staged as the map with one zero column after every row and one zero row after every image (the direct loads of
 //     those lanes lie outside the tensor), so that a tap is a constant distance and nothing is masked: a zero of dy adds nothing.
 //   LDS: [block of 16 channels][cell][16]; a transposing read takes 4 cells of 16 channels from 128 bytes, and the 32 cells of a step are dealt to
