@@ -171,7 +171,8 @@ static bool plan_deep(const MfmaArgs &g, bool flip, const DeepCand &c, DeepArgs 
     *est = 2.89 + ceil(n / occ) * (two ? 1.42 : 1.01) + share * (0.0166 * t.count * t.CP / 64.0 + 0.0217 * 9.0 * c.mf * c.nf * (two ? 2 : 1));
     // Those timings are of up to 4096 pixels. Several tiles per CU wait for LDS and for memory: 15 % below a fit to 2400 timings of 4 to 2000000 pixels is
     // the estimate where it is the larger one (112 x 31 x 28, 496 -> 16: 47.9 us in tiles of 16 x 64, 32 by the line above, 31.0 by the kernel for direct
-    // loads; 65 x 22 x 20, 440 -> 32 18.6, 14.0. Six of 2443 drawn passes go to another kernel by it, five of them the faster one, one 3 % slower).
+    // loads; 65 x 22 x 20, 440 -> 32 18.6, 14.0). Of 7522 passes of drawn layers and networks it sends 23 to another kernel: 1.03 times as fast among
+    // themselves, 1.08 between passes of other weights and tensors; the worst 8 % slower (11 x 12 x 12, 512 -> 256 9.2 -> 9.9 us).
     const double work = (two ? 0.861 * ceil(n / occ) : 0.0) + share * (0.0115 * t.count * t.CP / 64.0 + 0.0376 * 9.0 * c.mf * c.nf * (two ? 2 : 1));
     const double moved = 0.0568e-6 * ((double)t.p_tiles * t.count * t.CP * 16.0 + (double)out_bytes) + 0.0069e-6 * *grid * (t.count * t.CP * 16.0 + 288.0 * c.mf * g.in_CH);
     *least = 2.14 + pow(pow(work, 1.5) + pow(moved, 1.5), 1.0 / 1.5);
